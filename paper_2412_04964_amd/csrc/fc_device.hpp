@@ -337,6 +337,21 @@ __device__ __forceinline__ void group_minmax(float &mn, float &mx, int lpg_rt)
     }
 }
 
+// Packed binary16 min / max as single instructions (the compiler's own sequence first canonicalizes each input
+// with a v_pk_max x, x; the inputs here come from memory and the result only has to be one of them).
+__device__ __forceinline__ h2 pk_min(h2 a, h2 b)
+{
+    h2 r;
+    asm("v_pk_min_f16 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
+__device__ __forceinline__ h2 pk_max(h2 a, h2 b)
+{
+    h2 r;
+    asm("v_pk_max_f16 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
+
 // ---------------------------------------------------------------------------
 // Eq. 1: scale, reciprocal and zero-point of one group from its min and max.
 //

@@ -49,21 +49,6 @@ constexpr int kSimTileElems = kSimBlockThreads * kSimLaneElems;
 static_assert(kSimWaveElems == kFusedAllreduceMaxGroup && kSimTileElems == kFusedAllreduceTileElems,
               "the launcher's applicability test describes this decomposition");
 
-// Packed binary16 min / max as single instructions (the compiler's own sequence first canonicalizes each input
-// with a v_pk_max x, x; the inputs here come from memory and the result only has to be one of them).
-__device__ __forceinline__ h2 pk_min(h2 a, h2 b)
-{
-    h2 r;
-    asm("v_pk_min_f16 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
-    return r;
-}
-__device__ __forceinline__ h2 pk_max(h2 a, h2 b)
-{
-    h2 r;
-    asm("v_pk_max_f16 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
-    return r;
-}
-
 template <int CODEC, int BITS_RS, int BITS_AG, int NSRC, int LPG>
 __global__ __launch_bounds__(kSimBlockThreads) void k_allreduce_fused(const uint16_t *__restrict__ x, int64_t n_elems,
                                                                      int lpg, uint16_t *__restrict__ y)

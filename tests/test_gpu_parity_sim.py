@@ -268,3 +268,28 @@ def test_volume_beyond_2_to_32_elements(fc, which):
     check(y[ridx].cpu().numpy(), ref(xs, group, bits, bits), "rows around 2^32 elements, " + which)
     # nothing outside the sampled rows is left unwritten: the fill value 7.0 would survive only by accident
     assert int((y == 7.0).sum().item()) < tokens
+
+
+# --------------------------------------------------------------------------- #
+# groups of 2048 ... 16384 elements: one workgroup per group, still one launch
+# --------------------------------------------------------------------------- #
+
+@pytest.mark.parametrize("name", ["asym", "sym", "fp8", "cmeta"])
+@pytest.mark.parametrize("group", [2048, 4096, 8192, 16384])          # 2, 4, 8 and 16 wavefronts to a workgroup
+@pytest.mark.parametrize("n_src", [1, 2, 4, 5, 8])                    # 5 and 8: more than half of the parameter lanes
+def test_wide_groups(fc, name, group, n_src):
+    if name == "asym":
+        gpu, ref = fc.allreduce_sim, oracle.allreduce_sim
+    else:
+        gpu, ref = variant(fc, name)
+    rng = np.random.default_rng(group + n_src)
+    for tokens, hidden, kind in ((1, group, None), (3, 2 * group, None), (17, group, 2), (2, 3 * group, 1), (5, group, 4)):
+        if kind is None:
+            x = synth_inputs.make_partials(n_src, tokens, hidden, seed=int(rng.integers(1 << 30)), outlier_frac=0.01)
+        else:
+            x = synth_inputs.make_partials_stress(n_src, tokens, hidden, kind, seed=int(rng.integers(1 << 30)))
+        xd = dev16(x)
+        for bi, bo in bit_pairs(name) if (tokens, kind) == (3, None) else bit_pairs(name)[:1]:
+            got = gpu(xd, group, bi, bo)
+            torch.cuda.synchronize()
+            check(got.cpu().numpy(), ref(x, group, bi, bo), "%s N=%d g=%d %dx%d %d->%d" % (name, n_src, group, tokens, hidden, bi, bo))
