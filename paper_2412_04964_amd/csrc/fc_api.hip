@@ -483,29 +483,9 @@ int fc_allreduce_sim_rot(const void *x_f16, int n_src, int64_t tokens, int64_t h
     if (!workspace || workspace_bytes < L.total) return FC_ERR_WORKSPACE;
     if (!aligned16(workspace)) return FC_ERR_ALIGN;
 
-    char *ws = static_cast<char *>(workspace);
-    const char *x = static_cast<const char *>(x_f16);
-    const bool packed = L.codes_rs == (size_t)n * bits_rs / 8 && L.meta == (size_t)(n / group) * sizeof(float) &&
-                        tokens * n_src <= 0x7FFFFFFF;
-    const int launches = packed ? 1 : n_src;
-    for (int j = 0; j < launches; ++j) {
-        rc = quantize_rot_impl(quantizer, x + (size_t)j * (size_t)n * 2, packed ? tokens * n_src : tokens, hidden,
-                               group, bits_rs,
-                               ws + L.off_codes1 + (size_t)j * L.codes_rs,
-                               reinterpret_cast<float *>(ws + L.off_scales1 + (size_t)j * L.meta),
-                               reinterpret_cast<float *>(ws + L.off_zeros1 + (size_t)j * L.meta), hip_stream);
-        if (rc != FC_OK) return rc;
-    }
-    rc = fused_impl(quantizer, ws + L.off_codes1, (int64_t)L.codes_rs,
-                    reinterpret_cast<const float *>(ws + L.off_scales1),
-                    reinterpret_cast<const float *>(ws + L.off_zeros1), (int64_t)(L.meta / sizeof(float)),
-                    n_src, tokens, hidden, group, bits_rs, bits_ag, ws + L.off_codes2,
-                    reinterpret_cast<float *>(ws + L.off_scales2), reinterpret_cast<float *>(ws + L.off_zeros2),
-                    hip_stream);
-    if (rc != FC_OK) return rc;
-    return dequantize_rot_impl(quantizer, ws + L.off_codes2, reinterpret_cast<const float *>(ws + L.off_scales2),
-                               reinterpret_cast<const float *>(ws + L.off_zeros2), tokens, hidden, group,
-                               bits_ag, y_f16, hip_stream);
+    // one kernel; nothing goes through the workspace
+    return hip_result(fc::launch_allreduce_rot(quantizer, bits_rs, bits_ag, x_f16, n_src, tokens, (int)hidden, group,
+                                               y_f16, static_cast<hipStream_t>(hip_stream)));
 }
 
 const char *fc_strerror(int code)

@@ -370,11 +370,10 @@ __device__ __forceinline__ h2 pk_max(h2 a, h2 b)
 // [2^-24, 65504]) before the reciprocal is taken, so that the zero-point and every
 // code are computed from the number that is stored; the zero-point is then rounded
 // to binary16 as well (saturating at +-65504; integers up to 2048 are unchanged).
-template <int BITS, bool HM = false>
-__device__ __forceinline__ void group_params(float mn, float mx, float &s, float &inv, float &zf)
+// The number of levels comes in as qmax = 2^bits - 1 and c = 1 / qmax: constants where the code width is one at compile time.
+template <bool HM>
+__device__ __forceinline__ void group_params_levels(float mn, float mx, float qmax, float c, float &s, float &inv, float &zf)
 {
-    constexpr float qmax = (float)((1 << BITS) - 1);
-    constexpr float c = 1.0f / qmax;
     const float r = mx - mn;
     const float q0 = r * c;
     const float e = fmaf(-qmax, q0, r);
@@ -401,6 +400,14 @@ __device__ __forceinline__ void group_params(float mn, float mx, float &s, float
         asm volatile("" : "+v"(zf));
         zf = (float)(_Float16)zf;
     }
+}
+
+template <int BITS, bool HM = false>
+__device__ __forceinline__ void group_params(float mn, float mx, float &s, float &inv, float &zf)
+{
+    constexpr float qmax = (float)((1 << BITS) - 1);
+    constexpr float c = 1.0f / qmax;
+    group_params_levels<HM>(mn, mx, qmax, c, s, inv, zf);
 }
 
 // the metadata word of the binary16 variant: scale in bits 0-15, zero-point in bits 16-31
@@ -592,11 +599,8 @@ __device__ __forceinline__ float group_max(float m, int lpg_rt)
 // sequences as group_params: r/7, r/127 and r/448 match the IEEE quotient for
 // every positive fp32 whose quotient is at least FLT_MIN, and smaller quotients
 // are replaced by 1 on both sides.
-template <int QM>
-__device__ __forceinline__ void group_params_absmax(float amax, float &s, float &inv)
+__device__ __forceinline__ void group_params_absmax_levels(float amax, float qm, float c, float &s, float &inv)
 {
-    constexpr float qm = (float)QM;
-    constexpr float c = 1.0f / qm;
     const float q0 = amax * c;
     const float e = fmaf(-qm, q0, amax);
     s = fmaf(e, c, q0);                    // == amax / qm
@@ -608,6 +612,14 @@ __device__ __forceinline__ void group_params_absmax(float amax, float &s, float 
     } else {
         inv = 1.0f / s;
     }
+}
+
+template <int QM>
+__device__ __forceinline__ void group_params_absmax(float amax, float &s, float &inv)
+{
+    constexpr float qm = (float)QM;
+    constexpr float c = 1.0f / qm;
+    group_params_absmax_levels(amax, qm, c, s, inv);
 }
 
 template <int BITS>

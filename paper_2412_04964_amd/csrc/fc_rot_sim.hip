@@ -1,0 +1,248 @@
+// fc_rot_sim.hip -- Algorithm 1 with the rotation around it, in ONE launch: every partial is read once, rotated,
+// quantized and dequantized into the sum; the sum is quantized, dequantized and rotated back; the result is written
+// once.  2 N + 2 bytes per element; nothing else goes through HBM.  Bit-identical to fc_quantize_rot x N ->
+// fc_dequant_reduce_requant -> fc_dequantize_rot.
+//
+// What bounds it: vector instructions, (N + 1) log2 B of them per element for the butterflies alone: 3165 per wavefront
+// of 2048 elements at N = 4 and B = 8192, which is 88 % of the issue slots of the 203 us it takes on 4 partials of
+// 8192 x 8192 (group 128, INT4).  The three steps took 255 us there, the codes and metadata going through HBM and the
+// rows through LDS five times.  The transform and its layout are those of fc_rot_wave.hpp; the partials are taken in
+// source order in a loop, the next one's loads in flight while one is coded.  The sum stays in the frame of the rotated values (see there): rounding is symmetric, so the
+// quantizer works on a negated value as on the value, and the inverse transform undoes the frame.
+//
+// Exactness of the short form of the codes, taken when every zero-point of the wavefront is below 2048 in magnitude
+// and no rounding passes the top code: t = rint(x * inv) and z are then small integers, the lower clamp cannot act
+// (x >= min), so q - z = t.  Otherwise the codes are formed literally.  Zeros may come out with either sign in the
+// short form and across frames; for the integer quantizers the sum and the result of the contract never hold -0 (every
+// dequantized value is q - z = +0 times a positive scale, and sums of +0 are +0), and the last multiply-add, which
+// adds +0, makes every zero of the result +0.
+#include "fc_rot_wave.hpp"
+#include "fc_launch.hpp"
+
+namespace fc {
+
+struct RotLevels {           // of one quantization: qmax and 1 / qmax (2^bits - 1, 2^(bits-1) - 1, or 448)
+    float q, c;
+};
+
+// scale, scaled reciprocal and zero-point of the lane's group from its min and max
+template <int CODEC>
+__device__ __forceinline__ void rot_params(float mn, float mx, RotLevels lv, float fwd, float &s, float &inv, float &zf)
+{
+    const float a = mn * fwd, b = mx * fwd;
+    zf = 0.0f;
+    if constexpr (CODEC == kAsym)
+        group_params_levels<false>(a, b, lv.q, lv.c, s, inv, zf);
+    else
+        group_params_absmax_levels(fmaxf(fabsf(a), fabsf(b)), lv.q, lv.c, s, inv);
+    inv *= fwd;
+}
+
+// Literal form of d = q - z for piece P
+template <int P>
+__device__ __forceinline__ void rot_literal_codes(float (&v)[4][8], float frame, float inv, float zf, float qmax)
+{
+    const float inv_p = of_piece<P>(inv), z_p = of_piece<P>(zf);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        const float u = rintf(v[P][i] * frame * inv_p) + z_p;
+        v[P][i] = (__builtin_amdgcn_fmed3f(u, 0.0f, qmax) - z_p) * frame;
+    }
+}
+
+// Short form of d for piece P (or its E4M3 code)
+template <bool FP8, int P>
+__device__ __forceinline__ void rot_short_codes(float (&v)[4][8], float inv)
+{
+    const float inv_p = of_piece<P>(inv);
+    if constexpr (FP8) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            int w = __builtin_amdgcn_cvt_pk_fp8_f32(v[P][4 * h] * inv_p, v[P][4 * h + 1] * inv_p, 0, false);
+            w = __builtin_amdgcn_cvt_pk_fp8_f32(v[P][4 * h + 2] * inv_p, v[P][4 * h + 3] * inv_p, w, true);
+            const f32x2 a = __builtin_amdgcn_cvt_pk_f32_fp8(w, false), b = __builtin_amdgcn_cvt_pk_f32_fp8(w, true);
+            v[P][4 * h] = a.x;
+            v[P][4 * h + 1] = a.y;
+            v[P][4 * h + 2] = b.x;
+            v[P][4 * h + 3] = b.y;
+        }
+    } else {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) v[P][i] = rintf(v[P][i] * inv_p);
+    }
+}
+
+// Every value becomes its dequantized code before the scale, in the lane's frame.  Where the short form does not hold
+// the literal differences are formed first; they are integers, so the short form with reciprocal 1 leaves them alone
+// (a one-sided branch: two alternatives cost 24 registers more).
+template <int CODEC>
+__device__ __forceinline__ void rot_codes(float (&v)[4][8], const RotLane &L, float mx, float inv, float zf, RotLevels lv)
+{
+    if constexpr (CODEC == kAsym) {
+        if (__builtin_amdgcn_ballot_w64(!(fabsf(zf) < 2048.0f) || rintf(mx * inv) > lv.q - zf) != 0) {
+            rot_literal_codes<0>(v, L.frame, inv, zf, lv.q);
+            rot_literal_codes<1>(v, L.frame, inv, zf, lv.q);
+            rot_literal_codes<2>(v, L.frame, inv, zf, lv.q);
+            rot_literal_codes<3>(v, L.frame, inv, zf, lv.q);
+            inv = 1.0f;
+        }
+    }
+    rot_short_codes<CODEC == kFp8, 0>(v, inv);
+    rot_short_codes<CODEC == kFp8, 1>(v, inv);
+    rot_short_codes<CODEC == kFp8, 2>(v, inv);
+    rot_short_codes<CODEC == kFp8, 3>(v, inv);
+}
+
+template <int P>
+__device__ __forceinline__ void rot_accumulate(const float (&d)[4][8], float s, float (&acc)[4][8])
+{
+    const float s_p = of_piece<P>(s);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) acc[P][i] = fmaf(d[P][i], s_p, acc[P][i]);
+}
+
+template <int P>
+__device__ __forceinline__ void rot_scale(float (&d)[4][8], float s)
+{
+    const float s_p = of_piece<P>(s);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) d[P][i] *= s_p;
+}
+
+template <int CODEC, int LB>
+__global__ __launch_bounds__(64 * rot_group_waves(LB)) __attribute__((amdgpu_waves_per_eu(4))) void k_allreduce_rot(
+    const uint16_t *__restrict__ x, int64_t n_elems, int n_src, int group_shift, RotLevels rs, RotLevels ag,
+    uint16_t *__restrict__ y)
+{
+    constexpr bool FP8 = CODEC == kFp8;
+    constexpr int kWaves = rot_group_waves(LB);
+    constexpr int kTile = 2048 * kWaves;
+    constexpr int kChunk = (512 * 1024) / (kTile * 2);                  // 512 KB of every partial per XCD and run
+    __shared__ __attribute__((aligned(16))) uint8_t pieces[rot_exchange_bytes(LB)];
+    __shared__ float mm[kWaves][4][2];
+
+    const u32 tid = threadIdx.x, lane = tid & 63u;
+    const u32 wave = (u32)__builtin_amdgcn_readfirstlane((int)(tid >> 6));
+    const RotLane L = rot_lane<FP8>(lane);
+    const u32 tile = xcd_tile<kChunk>((u32)((n_elems + kTile - 1) / kTile));
+    const int64_t e_tile = (int64_t)tile * kTile;
+    const int64_t left = (n_elems - e_tile) * 2;                       // bytes from the tile to the end of a partial
+
+    u32x4 raw[4];
+    auto fetch = [&](int j) {
+        const rsrc_t rx = make_rsrc(x + (int64_t)j * n_elems + e_tile, left);
+#pragma unroll
+        for (u32 p = 0; p < 4; ++p)
+            raw[p] = __builtin_amdgcn_raw_buffer_load_b128(rx, L.pos * 16, rot_piece_offset<LB>(wave, p, false) * 2,
+                                                           kStreamLoadPolicy);
+    };
+    constexpr float fwd = 1.0f / (float)(1 << ((LB + 1) / 2));          // 2^-ceil(n/2), n = LB
+    constexpr float back = 1.0f / (float)(1 << (LB / 2));               // 2^-floor(n/2)
+
+    float acc[4][8];
+#pragma unroll
+    for (int p = 0; p < 4; ++p)
+#pragma unroll
+        for (int i = 0; i < 8; ++i) acc[p][i] = 0.0f;
+
+    fetch(0);
+    for (int j = 0; j < n_src; ++j) {
+        float v[4][8];
+#pragma unroll
+        for (int p = 0; p < 4; ++p)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) first_stage(raw[p][i], v[p][2 * i], v[p][2 * i + 1]);
+        if (LB >= 12 && j > 0) lds_barrier();                          // every wavefront has taken the last exchange
+        rot_forward<LB, FP8>(v, L, pieces, wave);
+        float mn, mx, s, inv, zf;
+        rot_group_minmax<LB, FP8>(v, L, group_shift, wave, mm, mn, mx);
+        rot_params<CODEC>(mn, mx, rs, fwd, s, inv, zf);
+        if (j + 1 < n_src) fetch(j + 1);
+        rot_codes<CODEC>(v, L, mx, inv, zf, rs);
+        rot_accumulate<0>(v, s, acc);
+        rot_accumulate<1>(v, s, acc);
+        rot_accumulate<2>(v, s, acc);
+        rot_accumulate<3>(v, s, acc);
+    }
+
+    float mn, mx, s, inv, zf;
+    if (LB >= 12) lds_barrier();
+    rot_group_minmax<LB, FP8>(acc, L, group_shift, wave, mm, mn, mx);
+    rot_params<CODEC>(mn, mx, ag, 1.0f, s, inv, zf);
+    rot_codes<CODEC>(acc, L, mx, inv, zf, ag);
+    rot_scale<0>(acc, s);
+    rot_scale<1>(acc, s);
+    rot_scale<2>(acc, s);
+    rot_scale<3>(acc, s);
+    rot_inverse<LB, FP8, true>(acc, L, pieces, wave);
+
+    const rsrc_t ry = make_rsrc(y + e_tile, left);
+#pragma unroll
+    for (u32 p = 0; p < 4; ++p) {
+        u32x4 out;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            h2 r;
+            if constexpr (FP8) {
+                r.x = (_Float16)(acc[p][2 * i] * back);
+                r.y = (_Float16)(acc[p][2 * i + 1] * back);
+            } else {
+                r.x = (_Float16)fmaf(acc[p][2 * i], back, 0.0f);
+                r.y = (_Float16)fmaf(acc[p][2 * i + 1], back, 0.0f);
+            }
+            out[i] = as_u32(r);
+        }
+        __builtin_amdgcn_raw_buffer_store_b128(out, ry, L.pos * 16, rot_piece_offset<LB>(wave, p, true) * 2,
+                                               kStreamStorePolicy);
+    }
+}
+
+namespace {
+
+RotLevels levels(int codec, int bits)
+{
+    const float q = codec == CODEC_FP8 ? 448.0f : (float)((1 << (codec == CODEC_SYM ? bits - 1 : bits)) - 1);
+    return RotLevels{q, 1.0f / q};
+}
+
+template <int CODEC, int LB>
+hipError_t launch_one(const uint16_t *x, int n_src, int64_t n_elems, int group, RotLevels rs, RotLevels ag, uint16_t *y,
+                      hipStream_t stream)
+{
+    constexpr int kTile = 2048 * rot_group_waves(LB);
+    return launch_kernel(k_allreduce_rot<CODEC, LB>, dim3((unsigned)((n_elems + kTile - 1) / kTile)),
+                         dim3(64 * rot_group_waves(LB)), stream, x, n_elems, n_src, log2_int(group), rs, ag, y);
+}
+
+template <int CODEC>
+hipError_t launch_codec(int log_b, const uint16_t *x, int n_src, int64_t n_elems, int group, RotLevels rs, RotLevels ag,
+                        uint16_t *y, hipStream_t stream)
+{
+    switch (log_b) {
+    case 10: return launch_one<CODEC, 10>(x, n_src, n_elems, group, rs, ag, y, stream);
+    case 11: return launch_one<CODEC, 11>(x, n_src, n_elems, group, rs, ag, y, stream);
+    case 12: return launch_one<CODEC, 12>(x, n_src, n_elems, group, rs, ag, y, stream);
+    case 13: return launch_one<CODEC, 13>(x, n_src, n_elems, group, rs, ag, y, stream);
+    default: return hipErrorInvalidValue;
+    }
+}
+
+}  // namespace
+
+hipError_t launch_allreduce_rot(int codec, int bits_rs, int bits_ag, const void *x_f16, int n_src, int64_t tokens,
+                                int hidden, int group, void *y_f16, hipStream_t stream)
+{
+    const uint16_t *x = static_cast<const uint16_t *>(x_f16);
+    uint16_t *y = static_cast<uint16_t *>(y_f16);
+    const int lb = log2_int(rotation_block(hidden));
+    const int64_t n = tokens * hidden;
+    const RotLevels rs = levels(codec, bits_rs), ag = levels(codec, bits_ag);
+    switch (codec) {
+    case CODEC_ASYM: return launch_codec<kAsym>(lb, x, n_src, n, group, rs, ag, y, stream);
+    case CODEC_SYM: return launch_codec<kSym>(lb, x, n_src, n, group, rs, ag, y, stream);
+    case CODEC_FP8: return launch_codec<kFp8>(lb, x, n_src, n, group, rs, ag, y, stream);
+    default: return hipErrorInvalidValue;
+    }
+}
+
+}  // namespace fc

@@ -1,0 +1,370 @@
+// fc_rot_wave.hpp -- the Walsh-Hadamard transform of the rotation kernels, held in registers.
+//
+// A wavefront owns 2048 consecutive elements, 32 per lane: v[p][i], p = 0..3, i = 0..7.  With pos(lane) the lane's
+// place in its piece (a permutation of the lanes inside every 8, below), element bits are
+//     bits 0-2: i      bits 3-8: pos(lane)      bits 9, 10: p      bits 11, 12: wavefront of the workgroup
+// so a piece of a wavefront is 512 consecutive elements and every global access is coalesced as it is, with no
+// staging through LDS.  Stages run in the order of the bits:
+//   0-2    between registers.
+//   3-6    between lanes of a row of 16, ONE instruction per value: v_fmac_f32 with a DPP operand, y = dpp(y) * sgn + y.
+//          DPP offers lane ^ 1, ^ 2, ^ 7 (half-row mirror) and ^ 8 (rotation by 8) but not ^ 4; these four masks are
+//          independent, so bits 3-6 are laid over them: pos(lane) = lane ^ (lane & 4 ? 3 : 0) and bit 3..6 flips when
+//          the lane is xor-ed with 1, 2, 7, 8.  The accumulating operand cannot be negated, so the lane with the bit
+//          set computes (b - a) instead of a - b: it carries the value negated from then on (its "frame" is -1).  A
+//          rounded difference negates exactly, later stages between lanes of one frame are unaffected, and the
+//          inverse transform, run on values in this frame with the opposite signs, undoes it.  The one thing that
+//          is lost is the sign of a zero.
+//   7, 8   between rows: the partner's value comes through the LDS crossbar (ds_swizzle, ds_bpermute: no LDS memory),
+//          then one v_fma_f32.
+//   9, 10  between registers.
+//   11, 12 the wavefronts of a block exchange pieces for wavefront number through LDS (rotation_exchange), so that these bits are
+//          register bits too; bits 9, 10 then number the wavefronts.
+// FP8 codes keep the sign of zero, so that quantizer's lanes compute a - b itself in stages 3-6 (a DPP move and a
+// v_fma_f32, two instructions per value) and every frame is +1.
+#pragma once
+
+#include "fc_device.hpp"
+
+namespace fc {
+
+struct RotLane {
+    u32 lane, pos;           // pos: place of the lane's 8 elements in the piece
+    int far;                 // byte index of lane ^ 32
+    float s[6];              // +1 / -1 by bits 3..8 of the lane's elements
+    float frame;             // product of s[0..3]: the frame after stages 3-6 (1 for FP8)
+};
+
+template <bool FP8>
+__device__ __forceinline__ RotLane rot_lane(u32 lane)
+{
+    RotLane L;
+    L.lane = lane;
+    L.pos = lane ^ ((lane & 4u) ? 3u : 0u);
+    L.far = (int)((lane ^ 32u) * 4u);
+#pragma unroll
+    for (int b = 0; b < 6; ++b) L.s[b] = (L.pos >> b) & 1u ? -1.0f : 1.0f;
+    L.frame = FP8 ? 1.0f : ((__popc(L.pos & 15u) & 1) ? -1.0f : 1.0f);
+    return L;
+}
+
+constexpr int kDppRowRor8 = 0x128;
+
+// v[0..7] = dpp(v) * s + v.  s_nop: two wait states between the write of a register and its DPP read.
+#define FC_FMAC_DPP8(ctrl, sign)                                                                                     \
+    asm("s_nop 1\n\t"                                                                                                \
+        "v_fmac_f32_dpp %0, %0, " sign "%8 " ctrl " row_mask:0xf bank_mask:0xf\n\t"                                  \
+        "v_fmac_f32_dpp %1, %1, " sign "%8 " ctrl " row_mask:0xf bank_mask:0xf\n\t"                                  \
+        "v_fmac_f32_dpp %2, %2, " sign "%8 " ctrl " row_mask:0xf bank_mask:0xf\n\t"                                  \
+        "v_fmac_f32_dpp %3, %3, " sign "%8 " ctrl " row_mask:0xf bank_mask:0xf\n\t"                                  \
+        "v_fmac_f32_dpp %4, %4, " sign "%8 " ctrl " row_mask:0xf bank_mask:0xf\n\t"                                  \
+        "v_fmac_f32_dpp %5, %5, " sign "%8 " ctrl " row_mask:0xf bank_mask:0xf\n\t"                                  \
+        "v_fmac_f32_dpp %6, %6, " sign "%8 " ctrl " row_mask:0xf bank_mask:0xf\n\t"                                  \
+        "v_fmac_f32_dpp %7, %7, " sign "%8 " ctrl " row_mask:0xf bank_mask:0xf"                                      \
+        : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3]), "+v"(v[4]), "+v"(v[5]), "+v"(v[6]), "+v"(v[7])             \
+        : "v"(s))
+
+template <int BIT, bool INV>
+__device__ __forceinline__ void fmac_dpp8(float (&v)[8], float s)
+{
+    static_assert(BIT >= 3 && BIT <= 6, "stages inside a row of 16 lanes");
+    if constexpr (!INV) {
+        if constexpr (BIT == 3) FC_FMAC_DPP8("quad_perm:[1,0,3,2]", "");
+        if constexpr (BIT == 4) FC_FMAC_DPP8("quad_perm:[2,3,0,1]", "");
+        if constexpr (BIT == 5) FC_FMAC_DPP8("row_half_mirror", "");
+        if constexpr (BIT == 6) FC_FMAC_DPP8("row_ror:8", "");
+    } else {
+        if constexpr (BIT == 3) FC_FMAC_DPP8("quad_perm:[1,0,3,2]", "-");
+        if constexpr (BIT == 4) FC_FMAC_DPP8("quad_perm:[2,3,0,1]", "-");
+        if constexpr (BIT == 5) FC_FMAC_DPP8("row_half_mirror", "-");
+        if constexpr (BIT == 6) FC_FMAC_DPP8("row_ror:8", "-");
+    }
+}
+#undef FC_FMAC_DPP8
+
+// stages 3-6.  INV: the values come in the frame of the forward transform and leave in frame +1.
+template <bool FP8, bool INV>
+__device__ __forceinline__ void rot_row_stages(float (&v)[4][8], const RotLane &L)
+{
+#pragma unroll
+    for (int p = 0; p < 4; ++p) {
+        if constexpr (FP8) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) v[p][i] = fmaf(v[p][i], L.s[0], dpp_read<kDppQuadXor1>(v[p][i]));
+#pragma unroll
+            for (int i = 0; i < 8; ++i) v[p][i] = fmaf(v[p][i], L.s[1], dpp_read<kDppQuadXor2>(v[p][i]));
+#pragma unroll
+            for (int i = 0; i < 8; ++i) v[p][i] = fmaf(v[p][i], L.s[2], dpp_read<kDppRowHalfMirror>(v[p][i]));
+#pragma unroll
+            for (int i = 0; i < 8; ++i) v[p][i] = fmaf(v[p][i], L.s[3], dpp_read<kDppRowRor8>(v[p][i]));
+        } else {
+            fmac_dpp8<3, INV>(v[p], L.s[0]);
+            fmac_dpp8<4, INV>(v[p], L.s[1]);
+            fmac_dpp8<5, INV>(v[p], L.s[2]);
+            fmac_dpp8<6, INV>(v[p], L.s[3]);
+        }
+    }
+}
+
+__device__ __forceinline__ float row_swap(float v)                     // the value of lane ^ 16
+{
+    return __builtin_bit_cast(float, __builtin_amdgcn_ds_swizzle(__builtin_bit_cast(int, v), 0x401F));
+}
+
+__device__ __forceinline__ float half_swap(float v, const RotLane &L)  // the value of lane ^ 32
+{
+    return __builtin_bit_cast(float, __builtin_amdgcn_ds_bpermute(L.far, __builtin_bit_cast(int, v)));
+}
+
+// stages 7 and 8
+__device__ __forceinline__ void rot_cross_stages(float (&v)[4][8], const RotLane &L)
+{
+#pragma unroll
+    for (int p = 0; p < 4; ++p)
+#pragma unroll
+        for (int i = 0; i < 8; ++i) v[p][i] = fmaf(v[p][i], L.s[4], row_swap(v[p][i]));
+#pragma unroll
+    for (int p = 0; p < 4; ++p)
+#pragma unroll
+        for (int i = 0; i < 8; ++i) v[p][i] = fmaf(v[p][i], L.s[5], half_swap(v[p][i], L));
+}
+
+// First stage (span 1) on a pair of binary16 inputs held in one word: (lo + hi, lo - hi) in fp32.  Widening a
+// binary16 number is exact, so a mixed-precision multiply-add lo * 1 +- hi rounds the same real sum once, as the
+// conversion followed by an fp32 add does: one instruction per output instead of a conversion and an add.
+__device__ __forceinline__ void first_stage(u32 pair, float &sum, float &diff)
+{
+    asm("v_fma_mix_f32 %0, %1, 1.0, %1 op_sel:[0,0,1] op_sel_hi:[1,0,1]" : "=v"(sum) : "v"(pair));
+    asm("v_fma_mix_f32 %0, %1, 1.0, -%1 op_sel:[0,0,1] op_sel_hi:[1,0,1]" : "=v"(diff) : "v"(pair));
+}
+
+// one stage between the registers of a piece (span 1, 2, 4)
+template <int SPAN>
+__device__ __forceinline__ void rot_register_stage(float (&v)[4][8])
+{
+#pragma unroll
+    for (int p = 0; p < 4; ++p)
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+            if (!(i & SPAN)) {
+                const float a = v[p][i], b = v[p][i | SPAN];
+                v[p][i] = a + b;
+                v[p][i | SPAN] = a - b;
+            }
+}
+
+// one stage between pieces (P = 1, 2)
+template <int P>
+__device__ __forceinline__ void rot_piece_stage(float (&v)[4][8])
+{
+#pragma unroll
+    for (int p = 0; p < 4; ++p)
+        if (!(p & P))
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const float a = v[p][i], b = v[p | P][i];
+                v[p][i] = a + b;
+                v[p | P][i] = a - b;
+            }
+}
+
+// Barrier for data that goes through LDS: waits for this wavefront's LDS operations only, so that loads from memory
+// stay in flight across it.
+__device__ __forceinline__ void lds_barrier()
+{
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+}
+
+// Wavefronts per block of 2^LB elements, and per workgroup (blocks of at most one wavefront go two wavefronts to a
+// workgroup; these never meet)
+constexpr int rot_block_waves(int lb) { return lb <= 11 ? 1 : 1 << (lb - 11); }
+constexpr int rot_group_waves(int lb) { return lb <= 11 ? 2 : 1 << (lb - 11); }
+// bytes of LDS through which the wavefronts of a block exchange pieces (2 KB each)
+constexpr int rot_exchange_bytes(int lb) { return lb <= 11 ? 16 : rot_block_waves(lb) * 4 * 2048; }
+
+// Piece bits change places with wavefront bits; an involution.  LB = 13: the two piece bits with the two wavefront
+// bits.  LB = 12: the upper piece bit with the one wavefront bit.  Pieces lie in LDS by receiving wavefront, then by
+// sending wavefront, so that one address register serves all writes and one all reads.  The piece that stays goes
+// through LDS as well: sorting it out costs a branch per piece and nothing is gained (LDS is not what bounds these
+// kernels).  The caller sees to it that the previous readers of `lds` are done.
+template <int LB>
+__device__ __forceinline__ void rot_exchange(float (&v)[4][8], uint8_t *lds, u32 wave, u32 lane)
+{
+    static_assert(LB == 12 || LB == 13, "blocks of several wavefronts");
+    constexpr u32 kPerSender = LB == 13 ? 2048 : 4096, kPerReceiver = 8192;
+    uint8_t *out = lds + wave * kPerSender + lane * 16;
+    const uint8_t *in = lds + wave * kPerReceiver + lane * 16;
+#pragma unroll
+    for (u32 p = 0; p < 4; ++p)
+#pragma unroll
+        for (u32 h = 0; h < 2; ++h) {
+            const u32 at = (LB == 13 ? p * kPerReceiver : (p >> 1) * kPerReceiver + (p & 1u) * 2048) + h * 1024;
+            *reinterpret_cast<u32x4 *>(out + at) =
+                u32x4{__builtin_bit_cast(u32, v[p][4 * h]), __builtin_bit_cast(u32, v[p][4 * h + 1]),
+                      __builtin_bit_cast(u32, v[p][4 * h + 2]), __builtin_bit_cast(u32, v[p][4 * h + 3])};
+        }
+    lds_barrier();
+#pragma unroll
+    for (u32 p = 0; p < 4; ++p)
+#pragma unroll
+        for (u32 h = 0; h < 2; ++h) {
+            const u32x4 a = *reinterpret_cast<const u32x4 *>(in + p * 2048 + h * 1024);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const u32 w = a[i];        // (a bit_cast applied to the vector element itself reads element 0)
+                v[p][4 * h + i] = __builtin_bit_cast(float, w);
+            }
+        }
+}
+
+// Stages 1 ... LB-1 of the forward transform (the caller applies stage 0 while widening).  Blocks of several
+// wavefronts end exchanged.
+template <int LB, bool FP8>
+__device__ __forceinline__ void rot_forward(float (&v)[4][8], const RotLane &L, uint8_t *lds, u32 wave)
+{
+    rot_register_stage<2>(v);
+    rot_register_stage<4>(v);
+    rot_row_stages<FP8, false>(v, L);
+    rot_cross_stages(v, L);
+    rot_piece_stage<1>(v);
+    if constexpr (LB >= 11) rot_piece_stage<2>(v);
+    if constexpr (LB >= 12) {
+        rot_exchange<LB>(v, lds, wave, L.lane);
+        if constexpr (LB == 13) rot_piece_stage<1>(v);
+        rot_piece_stage<2>(v);
+    }
+}
+
+// All stages on values in the frame of the forward transform.  SWAPPED: blocks of several wavefronts come exchanged.
+// They end exchanged.
+template <int LB, bool FP8, bool SWAPPED>
+__device__ __forceinline__ void rot_inverse(float (&v)[4][8], const RotLane &L, uint8_t *lds, u32 wave)
+{
+    rot_register_stage<1>(v);
+    rot_register_stage<2>(v);
+    rot_register_stage<4>(v);
+    rot_row_stages<FP8, true>(v, L);
+    rot_cross_stages(v, L);
+    if constexpr (LB >= 12 && SWAPPED) {
+        rot_exchange<LB>(v, lds, wave, L.lane);
+        lds_barrier();                                     // the pieces are read; the exchange below writes there
+    }
+    rot_piece_stage<1>(v);
+    if constexpr (LB >= 11) rot_piece_stage<2>(v);
+    if constexpr (LB >= 12) {
+        rot_exchange<LB>(v, lds, wave, L.lane);
+        if constexpr (LB == 13) rot_piece_stage<1>(v);
+        rot_piece_stage<2>(v);
+    }
+}
+
+// element offset, inside the workgroup's first block's chunk, of piece p of a wavefront; after the exchange if `swapped`
+template <int LB>
+__device__ __forceinline__ u32 rot_piece_offset(u32 wave, u32 p, bool swapped)
+{
+    if constexpr (LB == 13)
+        return swapped ? (p * 4u + wave) * 512u : (wave * 4u + p) * 512u;
+    else if constexpr (LB == 12)
+        return swapped ? ((p & 2u) * 2u + wave * 2u + (p & 1u)) * 512u : (wave * 4u + p) * 512u;
+    else
+        return (wave * 4u + p) * 512u;
+}
+
+// ---------------------------------------------------------------------------
+// min / max of the groups.  Each lane first has one (min, max) pair per piece; a transposing reduction over bits 3
+// and 4 leaves ONE pair per lane, that of piece pos & 3, so that Eq. 1 is evaluated once per lane for all four
+// pieces.  Pairs are in the lane's frame; a partner across a frame boundary has min and max exchanged and negated,
+// which the DPP instruction's operand modifier does.
+// ---------------------------------------------------------------------------
+template <int CTRL_BIT, bool FP8>
+__device__ __forceinline__ void minmax_step(float &mn, float &mx, float other_mn, float other_mx)
+{
+    float a, b;
+#define FC_MINMAX_DPP(ctrl)                                                                                            \
+    if constexpr (FP8)                                                                                                 \
+        asm("s_nop 1\n\tv_min_f32_dpp %0, %2, %4 " ctrl " row_mask:0xf bank_mask:0xf\n\t"                              \
+            "v_max_f32_dpp %1, %3, %5 " ctrl " row_mask:0xf bank_mask:0xf"                                             \
+            : "=&v"(a), "=v"(b) : "v"(other_mn), "v"(other_mx), "v"(mn), "v"(mx));                                     \
+    else                                                                                                               \
+        asm("s_nop 1\n\tv_min_f32_dpp %0, -%3, %4 " ctrl " row_mask:0xf bank_mask:0xf\n\t"                             \
+            "v_max_f32_dpp %1, -%2, %5 " ctrl " row_mask:0xf bank_mask:0xf"                                            \
+            : "=&v"(a), "=v"(b) : "v"(other_mn), "v"(other_mx), "v"(mn), "v"(mx))
+    if constexpr (CTRL_BIT == 3) { FC_MINMAX_DPP("quad_perm:[1,0,3,2]"); }
+    if constexpr (CTRL_BIT == 4) { FC_MINMAX_DPP("quad_perm:[2,3,0,1]"); }
+    if constexpr (CTRL_BIT == 5) { FC_MINMAX_DPP("row_half_mirror"); }
+    if constexpr (CTRL_BIT == 6) { FC_MINMAX_DPP("row_ror:8"); }
+#undef FC_MINMAX_DPP
+    mn = a;
+    mx = b;
+}
+
+// min and max of the group that piece pos & 3 of the lane belongs to (identical in all its lanes, frame +1).  LDS slots
+// `slot` carry the pairs of groups that span wavefronts; the caller has a barrier between two uses of them.
+template <int LB, bool FP8>
+__device__ __forceinline__ void rot_group_minmax(const float (&v)[4][8], const RotLane &L, int group_shift, u32 wave,
+                                                 float (*slot)[4][2], float &mn_out, float &mx_out)
+{
+    float mn[4], mx[4];
+#pragma unroll
+    for (int p = 0; p < 4; ++p) lane_minmax(v[p], mn[p], mx[p]);
+    const bool b3 = (L.pos & 1u) != 0, b4 = (L.pos & 2u) != 0;
+    float n2[2], x2[2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        n2[h] = b3 ? mn[2 * h + 1] : mn[2 * h];
+        x2[h] = b3 ? mx[2 * h + 1] : mx[2 * h];
+        minmax_step<3, FP8>(n2[h], x2[h], b3 ? mn[2 * h] : mn[2 * h + 1], b3 ? mx[2 * h] : mx[2 * h + 1]);
+    }
+    float n = b4 ? n2[1] : n2[0], x = b4 ? x2[1] : x2[0];
+    minmax_step<4, FP8>(n, x, b4 ? n2[0] : n2[1], b4 ? x2[0] : x2[1]);
+    if (group_shift > 5) minmax_step<5, FP8>(n, x, n, x);
+    if (group_shift > 6) minmax_step<6, FP8>(n, x, n, x);
+    if (group_shift > 7) {
+        n = fminf(n, row_swap(n));
+        x = fmaxf(x, row_swap(x));
+    }
+    if (group_shift > 8) {
+        n = fminf(n, half_swap(n, L));
+        x = fmaxf(x, half_swap(x, L));
+    }
+    // element bits that number pieces flip with bits 3 and 4 of the lane now: bits 9, 10 (LB <= 11), bits 9, 11 (12),
+    // bits 11, 12 (13)
+    constexpr int kP0 = LB == 13 ? 11 : 9, kP1 = LB == 13 ? 12 : LB == 12 ? 11 : 10;
+    if (group_shift > kP0) minmax_step<3, FP8>(n, x, n, x);
+    if (group_shift > kP1) minmax_step<4, FP8>(n, x, n, x);
+    if constexpr (!FP8) {
+        const float t = L.frame < 0.0f ? -x : n;
+        x = L.frame < 0.0f ? -n : x;
+        n = t;
+    }
+    if constexpr (LB >= 12) {
+        // bits 9, 10 (LB = 13) or bit 10 (12) number the wavefronts
+        constexpr int kW0 = LB == 13 ? 9 : 10;
+        if (group_shift > kW0) {
+            if (L.lane < 4u) {                             // lanes 0 ... 3 hold pieces 0 ... 3
+                slot[wave][L.lane][0] = n;
+                slot[wave][L.lane][1] = x;
+            }
+            lds_barrier();
+            const u32 piece = L.pos & 3u;
+            n = fminf(n, slot[wave ^ 1u][piece][0]);
+            x = fmaxf(x, slot[wave ^ 1u][piece][1]);
+            if (LB == 13 && group_shift > 10) {
+                n = fminf(n, fminf(slot[wave ^ 2u][piece][0], slot[wave ^ 3u][piece][0]));
+                x = fmaxf(x, fmaxf(slot[wave ^ 2u][piece][1], slot[wave ^ 3u][piece][1]));
+            }
+        }
+    }
+    mn_out = n;
+    mx_out = x;
+}
+
+// the value that the lanes with pos & 3 == P of the quad hold, in all lanes
+template <int P>
+__device__ __forceinline__ float of_piece(float v)
+{
+    const int x = __builtin_bit_cast(int, v);
+    const int a = __builtin_amdgcn_update_dpp(0, x, P * 0x55, 0xF, 0xF, true);         // lane P of every quad
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(a, x, (3 - P) * 0x55, 0xF, 0xA, false));   // lanes 4-7, 12-15
+}
+
+}  // namespace fc

@@ -176,3 +176,30 @@ def test_rot_volume_beyond_2_to_32_elements(fc, hidden):
     assert_rot_triplet(got, want, oracle.ASYM, "rows around 2^32 elements, hidden %d" % hidden)
     wy = oracle.dequantize_rot(*want, hidden, group, bits, oracle.ASYM)
     assert same_bits(y[ridx].cpu().numpy().view(np.uint16), wy.view(np.uint16)), "dequantize_rot around 2^32 elements"
+
+
+@pytest.mark.parametrize("quantizer,bits_rs,bits_ag", [(oracle.ASYM, 4, 8), (oracle.SYM, 8, 4), (oracle.FP8, 8, 8)])
+@pytest.mark.parametrize("hidden", [1024, 3072, 2048, 4096, 12288, 8192])
+def test_one_launch_allreduce_every_group_and_value_kind(fc, quantizer, bits_rs, bits_ag, hidden):
+    # every group a block allows (inside a quad of lanes up to all wavefronts of the block), fan-ins 1 ... 8, an odd
+    # number of blocks (half-filled workgroups), values that reach huge zero-points and the top clamp, and rows of
+    # zeros of both signs (FP8 keeps the sign of a zero code)
+    block = hidden & -hidden
+    groups = [g for g in (32, 64, 128, 256, 512, 1024, 2048, 4096, 8192) if g <= block]
+    for k, group in enumerate(groups):
+        for n_src, kind in (((k % 8) + 1, k % synth_inputs.STRESS_KINDS), (3, 2), (2, None)):
+            if kind is None:
+                x = np.zeros((n_src, 3, hidden), np.float16)
+                x[:, 0] = -0.0
+                x[0, 1, ::2] = -0.0
+                x[1, 2, block // 2:] = np.float16(-0.0)
+                x[1, 2, 5] = 3.0
+            else:
+                x = synth_inputs.make_partials_stress(n_src, 3, hidden, kind, seed=hidden + group)
+            want = oracle.allreduce_sim_rot(x, group, bits_rs, bits_ag, quantizer)
+            y = Guarded((3, hidden), torch.float16)
+            fc.allreduce_sim_rot(dev(x.view(np.uint16)).view(torch.float16), group, bits_rs, bits_ag, quantizer, out=y.t)
+            torch.cuda.synchronize(); y.check()
+            got = y.t.cpu().numpy()
+            assert same_bits(got.view(np.uint16), want.view(np.uint16)), "q=%d N=%d h=%d g=%d kind %s: %s" % (
+                quantizer, n_src, hidden, group, kind, first_diff(got.view(np.uint16), want.view(np.uint16)))
