@@ -1,6 +1,7 @@
 """MI355X-native Flash Communication quantization path (arXiv 2412.04964).
 
-Thin ctypes binding over ``libfc.so`` (the C ABI in ``include/fc.h``).  The
+Thin binding over ``libfc.so`` (the C ABI in ``include/fc.h``): a native module
+for the ordinary call, checks in Python and ctypes for the rest.  The
 functions here only marshal arguments: they take torch CUDA tensors for device
 memory, pass raw pointers and the current HIP stream, and raise on any error
 code.  There is no CPU fallback: if the HIP library is missing or no GPU is

@@ -1,4 +1,4 @@
-"""Compile the HIP sources for gfx950 into ``libfc.so`` next to this file.
+"""Compile the HIP sources for gfx950 into ``libfc.so`` and the torch binding into ``_fc_torch.so`` next to this file.
 
     python -m paper_2412_04964_amd.build
 
@@ -30,6 +30,8 @@ BENCH_LIB = os.path.join(HERE, "libfc_bench.so")      # measurement aid (include
 # with -DFC_PLAIN_LANDING_READS (plain, compiler-ordered reads of the landing zones instead of the hand-ordered
 # ones): the GPU tests run those cases through both
 PLAIN_LIB = os.path.join(HERE, "libfc_plainreads.so")
+# CPython extension between torch tensors and the C ABI (host code only; built against the installed torch)
+TORCH_EXT = os.path.join(HERE, "_fc_torch.so")
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"
@@ -71,17 +73,43 @@ def _compile(unit):
     return obj, "\n".join(warn)
 
 
+def _compile_torch_ext():
+    import sysconfig
+
+    import torch
+    from torch.utils import cpp_extension
+
+    tmp = TORCH_EXT + ".tmp.%d" % os.getpid()
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-Wall",
+           "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1", "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI,
+           "-I", INCLUDE]
+    for path in [*cpp_extension.include_paths(), sysconfig.get_paths()["include"],
+                 os.path.join(os.path.dirname(os.path.dirname(HIPCC)), "include")]:
+        cmd += ["-isystem", path]
+    cmd += [os.path.join(CSRC, "fc_torch.cpp"), "-o", tmp]
+    for path in cpp_extension.library_paths():
+        cmd += ["-L" + path, "-Wl,-rpath," + path]
+    cmd += ["-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch", "-ltorch_python"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError("compiling fc_torch.cpp failed:\n%s\n%s" % (" ".join(cmd), r.stderr))
+    os.replace(tmp, TORCH_EXT)
+    return r.stderr
+
+
 def build(verbose: bool = False, jobs: int | None = None) -> str:
     """Compile every unit (always; this is the "does it build" check) and link."""
     os.makedirs(OBJDIR, exist_ok=True)
     jobs = jobs or min(8, os.cpu_count() or 1)
     with ThreadPoolExecutor(jobs) as ex:
+        ext = ex.submit(_compile_torch_ext)
         results = list(ex.map(_compile, UNITS + BENCH_UNITS + PLAIN_UNITS))
+        results.append((None, ext.result()))
     if verbose:
         for _, w in results:
             if w:
                 print(w, file=sys.stderr)
-    objs = [o for o, _ in results]
+    objs = [o for o, _ in results if o]
     n_u, n_b = len(UNITS), len(BENCH_UNITS)
     shared = [o for o, (src, _, _) in zip(objs[:n_u], UNITS) if src not in LANDING_SOURCES]
     for lib, members in ((LIB, objs[:n_u]), (BENCH_LIB, objs[n_u:n_u + n_b]), (PLAIN_LIB, shared + objs[n_u + n_b:])):

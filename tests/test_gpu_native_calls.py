@@ -1,0 +1,155 @@
+"""The native module behind the binding (csrc/fc_torch.cpp): the ordinary call goes through it and gives what the checked
+Python path of binding.py gives; everything else is left to that path."""
+import pytest
+
+torch = pytest.importorskip("torch")
+
+KINDS = ["asym", "sym", "fp8", "cmeta", "rot_asym", "rot_sym", "rot_fp8"]
+
+
+class Declines:
+    """stands in for the native module: takes no call"""
+    def __getattr__(self, name):
+        return lambda *a: None
+
+
+def _calls(b, kind, x, bits, outs=None):
+    """One pass through the four entry points of a quantizer family; every call's (name, args) and result."""
+    rot = kind.startswith("rot_")
+    q = kind[4:] if rot else kind
+    quantizer = {"asym": b.QUANTIZER_ASYM, "sym": b.QUANTIZER_SYM, "fp8": b.QUANTIZER_FP8, "cmeta": None}[q]
+    sfx = "" if q == "asym" else "_" + q
+    n, t, h = x.shape
+    g = 128
+    width = () if q == "fp8" else (bits,)
+    made = []
+
+    def call(name, *args, out=None):
+        made.append((name, (*args, out), getattr(b, name)(*args, out=out)))
+        return made[-1][2]
+
+    outs = outs or {}
+    parts = []
+    for j in range(n):
+        if rot:
+            parts.append(call("quantize_rot", x[j], g, bits, quantizer, out=outs.get("q")))
+        else:
+            parts.append(call("quantize" + sfx, x[j], g, *width, out=outs.get("q")))
+        parts[-1] = tuple(None if p is None else p.clone() for p in parts[-1])
+    arrays = [torch.stack(p) for p in zip(*parts) if p[0] is not None]
+    c = call("dequant_reduce_requant" + sfx, *arrays, h, g, *(width * 2), out=outs.get("f"))
+    if rot:
+        call("dequantize_rot", c[0], c[1], c[2] if q == "asym" else None, h, g, bits, quantizer, out=outs.get("d"))
+        name, extra = "allreduce_sim_rot", (bits, bits, quantizer)
+    else:
+        call("dequantize" + sfx, *c, h, g, *width, out=outs.get("d"))
+        name, extra = "allreduce_sim" + sfx, width * 2
+    made.append((name, (x, g, *extra, None, None), getattr(b, name)(x, g, *extra)))
+    ws = torch.empty(b.allreduce_sim_workspace_bytes(n, t, h, g, bits, bits), dtype=torch.uint8, device="cuda")
+    y = torch.empty(t, h, dtype=torch.float16, device="cuda")
+    made.append((name, (x, g, *extra, y, ws), getattr(b, name)(x, g, *extra, out=y, workspace=ws)))
+    assert made[-1][2] is y
+    return made
+
+
+def _flat(results):
+    return [t for r in results for t in (r if isinstance(r, tuple) else (r,)) if t is not None]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("kind,bits", [(k, w) for k in KINDS for w in (4, 8) if w == 8 or not k.endswith("fp8")])
+def test_native_calls_give_what_the_checked_path_gives(monkeypatch, kind, bits):
+    from paper_2412_04964_amd import binding as b
+    torch.manual_seed(1)
+    x = torch.randn(3, 5, 1024, device="cuda").half()
+    q = kind.replace("rot_", "")
+    code = lambda w: torch.empty(5, 1024 * w // 8, dtype=torch.uint8, device="cuda")
+    meta = lambda: torch.empty(5, 8, dtype=torch.int32 if q == "cmeta" else torch.float32, device="cuda")
+    coded = lambda: (code(bits), *[meta() for _ in range(2 if q == "asym" else 1)])
+    outs = {"q": coded(), "f": list(coded()), "d": torch.empty(5, 1024, dtype=torch.float16, device="cuda")}
+
+    got = {}
+    for given in (None, outs):
+        made = _calls(b, kind, x, bits, given)
+        native = b._calls()
+        for name, args, _ in made:                        # the native module takes every one of these calls
+            assert getattr(native, name)(*args) is not None, name
+        got[given is None] = [t.clone() for t in _flat(r for _, _, r in made)]
+        with monkeypatch.context() as m:
+            m.setattr(b, "_native", Declines())
+            want = _flat(r for _, _, r in _calls(b, kind, x, bits, given))
+        assert len(want) == len(got[given is None])
+        for g, w in zip(got[given is None], want):
+            assert g.shape == w.shape and g.dtype == w.dtype and torch.equal(g, w)
+
+
+@pytest.mark.gpu
+def test_native_calls_leave_everything_else_to_the_checked_path():
+    from paper_2412_04964_amd import binding as b
+    from torch.overrides import TorchFunctionMode
+    from torch.utils._python_dispatch import TorchDispatchMode
+
+    class Sub(torch.Tensor):
+        pass
+
+    x = torch.randn(4, 1024, device="cuda").half()
+    q = b._calls().quantize
+    assert q(x, 128, 4, None) is not None
+    out = b.quantize(x, 128, 4)
+    for args in [(x.float(), 128, 4, None), (x.cpu(), 128, 4, None), (x.t(), 128, 4, None), (x[0], 128, 4, None),
+                 (x.as_subclass(Sub), 128, 4, None), (x, 96, 4, None), (x, 2048, 4, None), (x, 128, 5, None),
+                 (x, 128.0, 4, None), (x, 128, True, None), (x, 1 << 40, 4, None), (x, 128, 4),
+                 (x, 128, 4, out[:2]), (x, 128, 4, (out[0], out[1], out[2][:3])), (x, 128, 4, iter(out)),
+                 (x, 128, 4, (out[1], out[0], out[2])), (None, 128, 4, None)]:
+        assert q(*args) is None, args[1:]
+    class Seen(TorchFunctionMode):
+        def __torch_function__(self, fn, types, args=(), kwargs=None):
+            return fn(*args, **(kwargs or {}))
+    class Dispatched(TorchDispatchMode):
+        def __torch_dispatch__(self, fn, types, args=(), kwargs=None):
+            return fn(*args, **(kwargs or {}))
+    for mode in (Seen, Dispatched):
+        with mode():
+            assert q(x, 128, 4, None) is None
+            assert torch.equal(b.quantize(x, 128, 4)[0], out[0])
+
+    def transformed(row):
+        assert q(row, 128, 4, None) is None
+        return row
+    torch.func.vmap(transformed)(x[None])
+    with torch.inference_mode():                          # an ordinary context: taken, same result
+        assert torch.equal(q(x, 128, 4, None)[0], out[0])
+    p = torch.nn.Parameter(x)
+    assert not b.quantize(p, 128, 4)[1].requires_grad and torch.equal(q(p, 128, 4, None)[0], out[0])
+    # refused by the library after the module's checks: the binding's error
+    odd = torch.zeros(4 * 1024 + 1, dtype=torch.float16, device="cuda")[1:].view(4, 1024)
+    with pytest.raises(b.FcError) as e:
+        b.quantize(odd, 128, 4)
+    assert e.value.code == -5
+
+
+@pytest.mark.gpu
+def test_native_calls_go_to_the_current_stream():
+    from paper_2412_04964_amd import binding as b
+    x = torch.randn(2, 64, 1024, device="cuda").half()
+    want = b.allreduce_sim(x, 128, 4, 4)
+    src, y = torch.zeros_like(x), torch.empty_like(want)
+    s = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(s):
+        for _ in range(20):
+            src.copy_(torch.zeros_like(x))                # ordered on s alone: each call sees the last copy of s
+            torch.cuda._sleep(200000)
+            src.copy_(x)
+            assert b._calls().allreduce_sim(src, 128, 4, 4, y, None) is y
+    s.synchronize()
+    assert torch.equal(y, want)
+
+
+def test_native_module_takes_no_cpu_tensor():
+    from paper_2412_04964_amd import binding as b
+    x = torch.zeros(4, 256, dtype=torch.float16)
+    assert b._calls().quantize(x, 128, 4, None) is None
+    assert b._calls().allreduce_sim(x[None], 128, 4, 4, None, None) is None
+    with pytest.raises(TypeError):
+        b.quantize(x, 128, 4)
