@@ -192,8 +192,7 @@ __global__ __launch_bounds__(64 * rot_group_waves(LB)) __attribute__((amdgpu_wav
             }
             out[i] = as_u32(r);
         }
-        __builtin_amdgcn_raw_buffer_store_b128(out, ry, L.pos * 16, rot_piece_offset<LB>(wave, p, true) * 2,
-                                               kStreamStorePolicy);
+        store_b128_at(out, ry, L.pos * 16, rot_piece_offset<LB>(wave, p, true) * 2);
     }
 }
 

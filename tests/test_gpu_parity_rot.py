@@ -203,3 +203,28 @@ def test_one_launch_allreduce_every_group_and_value_kind(fc, quantizer, bits_rs,
             got = y.t.cpu().numpy()
             assert same_bits(got.view(np.uint16), want.view(np.uint16)), "q=%d N=%d h=%d g=%d kind %s: %s" % (
                 quantizer, n_src, hidden, group, kind, first_diff(got.view(np.uint16), want.view(np.uint16)))
+
+
+@pytest.mark.parametrize("quantizer,bits", [(oracle.ASYM, 4), (oracle.SYM, 4), (oracle.FP8, 8)])
+@pytest.mark.parametrize("hidden", [1024, 2048, 4096, 8192])
+def test_full_chip_runs_repeat(fc, quantizer, bits, hidden):
+    # a volume that fills the chip several times over, eight times: the rotated kernels give the same bits every time, and
+    # the one-launch all-reduce those of the three steps (a register overwritten while a store still reads it shows
+    # in a few wavefronts in ten thousand, never at the sizes of the other tests)
+    tokens, group, n_src = (1 << 25) // hidden, 128, 2
+    x = synth_inputs.make_partials_device(n_src, tokens, hidden, hidden + bits, "cuda", 0.01, 20.0)
+    parts = [[t for t in fc.quantize_rot(x[j], group, bits, quantizer) if t is not None] for j in range(n_src)]
+    coded = [torch.stack(p) for p in zip(*parts)]
+    fused = {oracle.ASYM: fc.dequant_reduce_requant, oracle.SYM: fc.dequant_reduce_requant_sym,
+             oracle.FP8: fc.dequant_reduce_requant_fp8}[quantizer]
+    total = fused(*coded, hidden, group, *(() if quantizer == oracle.FP8 else (bits, bits)))
+    c, s, z = (*total, None)[:3]
+    want = fc.dequantize_rot(c, s, z, hidden, group, bits, quantizer).clone()
+    for _ in range(8):
+        again = [t for t in fc.quantize_rot(x[0], group, bits, quantizer) if t is not None]
+        for a, b in zip(again, parts[0]):
+            assert torch.equal(a.view(torch.uint8), b.view(torch.uint8))
+        y = fc.dequantize_rot(c, s, z, hidden, group, bits, quantizer)
+        assert torch.equal(y.view(torch.int16), want.view(torch.int16)), "dequantize_rot does not repeat"
+        y = fc.allreduce_sim_rot(x, group, bits, bits, quantizer)
+        assert torch.equal(y.view(torch.int16), want.view(torch.int16)), "one launch differs from the three steps"
