@@ -65,6 +65,15 @@ typedef _Float16 h2 __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ h2 as_h2(u32 v) { return __builtin_bit_cast(h2, v); }
 __device__ __forceinline__ u32 as_u32(h2 v) { return __builtin_bit_cast(u32, v); }
 
+// Two fp32 values rounded to binary16 (nearest even) in one word: v_cvt_pk_f16_f32, 4 cycles per wavefront and SIMD
+// where v_fma_mixlo_f16 and v_fma_mixhi_f16 take 8 each.  Left to itself the compiler folds a preceding product into those.
+__device__ __forceinline__ u32 round_pair(float a, float b)
+{
+    u32 r;
+    asm("v_cvt_pk_f16_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
+
 // ---------------------------------------------------------------------------
 // Buffer addressing.  Bulk accesses go through a raw buffer resource whose base
 // is the (wave-uniform) start of the workgroup's tile and whose size is the
@@ -445,17 +454,21 @@ __device__ __forceinline__ u32 encode(float x, float inv, float zf)
 //   Adding (z - bits(M)) * 0x11..1 once per word leaves sum (t_i + z) << (BITS * i), and every digit t_i + z lies in
 //       [0, 2^BITS - 1] (lower clamp idle, upper clamp applied to u beforehand when CAP), so no carry crosses a digit.
 // z * 0x11..1 = (z * 0x1111) * 0x10001 is formed from the exact fp32 product z * 4369 (|z| < 2048).
+template <int BITS>
+__device__ __forceinline__ u32 digit_fix(float zf)                       // (z - bits(M)) * 0x11..1
+{
+    constexpr u32 kOnes = BITS == 4 ? 0x11111111u : 0x01010101u;
+    const u32 zc = (u32)(int)(zf * (BITS == 4 ? 4369.0f : 257.0f));      // z * 0x1111 (z * 0x0101)
+    return (zc + (zc << 16)) - 0x4B400000u * kOnes;
+}
+
 template <int BITS, int EPL, bool CAP>
-__device__ __forceinline__ void pack_codes(const float (&v)[EPL], float inv, float zf, float tmax,
-                                           u32 (&word)[EPL * BITS / 32])
+__device__ __forceinline__ void pack_digits(const float (&v)[EPL], float inv, float tmax, u32 fix,
+                                            u32 (&word)[EPL * BITS / 32])
 {
     constexpr float kMagic = 12582912.0f;
-    constexpr u32 kMagicBits = 0x4B400000u;
     constexpr int per_word = 32 / BITS;
-    constexpr u32 kOnes = BITS == 4 ? 0x11111111u : 0x01010101u;
     const float cap = kMagic + tmax;
-    const u32 zc = (u32)(int)(zf * (BITS == 4 ? 4369.0f : 257.0f));      // z * 0x1111 (z * 0x0101)
-    const u32 fix = (zc + (zc << 16)) - kMagicBits * kOnes;
 #pragma unroll
     for (int w = 0; w < EPL / per_word; ++w) {
         u32 h = 0;
@@ -468,6 +481,13 @@ __device__ __forceinline__ void pack_codes(const float (&v)[EPL], float inv, flo
         }
         word[w] = h + fix;
     }
+}
+
+template <int BITS, int EPL, bool CAP>
+__device__ __forceinline__ void pack_codes(const float (&v)[EPL], float inv, float zf, float tmax,
+                                           u32 (&word)[EPL * BITS / 32])
+{
+    pack_digits<BITS, EPL, CAP>(v, inv, tmax, digit_fix<BITS>(zf), word);
 }
 
 // FinegrainedQuantize of the lane's EPL fp32 values: packed code words plus the

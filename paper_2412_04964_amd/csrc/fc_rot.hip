@@ -12,188 +12,94 @@
 // computes it, so any assignment of butterflies to threads that keeps the stage
 // order is bit-identical.
 //
-// Blocks and quantization groups never cross block boundaries, so the tensor is
-// handled as a flat sequence of chunks of 2^LOGH elements (LOGH = LB = n, except
-// that 1024-element blocks go two to a chunk of 2048 and skip its last stage).
-// One workgroup owns one chunk (2048, 4096 or 8192 elements) and keeps it
-// in registers, R = 16 or 32 values per thread.  The stages over the bits of
-// the index that live inside a thread run in registers; then the row goes to
-// LDS and each further phase gives every thread the R values that differ in
-// the next (up to) log2(R) index bits, with a barrier between phases.  The row
-// is padded by 16 bytes per lane segment so that both the contiguous 128-bit
-// accesses of the first / last step and the strided 32-bit accesses of the
-// middle phases spread over the LDS banks.  The quantizer that follows (or the
-// dequantizer that precedes) is the same device code as in the plain kernels.
-#include "fc_device.hpp"
+// The transform is the one of fc_rot_wave.hpp: 32 values per lane, in registers throughout; a workgroup of two
+// wavefronts (blocks of 1024 and 2048, which need no LDS) or of one block (4096, 8192).  Blocks and quantization
+// groups never cross block boundaries, so the tensor is handled as a flat sequence of tiles; the last tile of a
+// tensor of 1024- or 2048-element blocks may be a partial one (loads beyond the end give zeros, stores are dropped).
+//
+// What bounds them: vector instructions (quantizer, blocks of 1024: 590 per wavefront of 2048 elements, about 1950 cycles
+// with the DPP, conversion and min / max instructions that issue at half the rate of an fp32 add), then HBM.  The rows
+// used to go through LDS and back for every five stages, in fp32: 10 KB per wavefront kept four of them on a SIMD, and
+// LDS writes run at 75 bytes a cycle.  Rotate + quantize / dequantize + rotate, us before -> now: 8192 x 8192 INT4 (blocks of
+// 8192) 46.0 -> 43.0 / 43.9 -> 39.6; the same in FP8 55.5 -> 45.2 / 46.3 -> 42.9; 8192 x 5120 INT4 (blocks of 1024)
+// 24.1 -> 23.8 / 24.0 -> 22.2; 32 x 8192 4.20 -> 3.67 / 3.87 -> 3.48.  Measured and not taken: 32 consecutive elements per lane
+// and a 16 x 16 exchange with other lanes through 5 KB of LDS (40.3 us for blocks of 8192, but 23.8 for 1024 and
+// 23.0 / 48 in the dequantizer, whose register needs it does not fit); all stages between lanes by permlane swaps
+// (25.9 us, blocks of 1024).
+#include "fc_rot_wave.hpp"
 #include "fc_launch.hpp"
 
 namespace fc {
 
-constexpr int ilog2(int v) { return v <= 1 ? 0 : 1 + ilog2(v / 2); }
+constexpr int kRounds = 2;       // of an exchange between wavefronts: 16 KB instead of 32 for a block of 8192
 
-// Butterfly stages S0 ... NB-1 over the low NB bits of the register index, spans 2^S0, 2^(S0+1), ...
-template <int R, int NB, int S0 = 0>
-__device__ __forceinline__ void butterflies(float (&x)[R])
+template <int P>
+__device__ __forceinline__ u32 of_piece_bits(u32 v)
 {
-#pragma unroll
-    for (int s = S0; s < NB; ++s)
-#pragma unroll
-        for (int q = 0; q < R; ++q)
-            if (!(q & (1 << s))) {
-                const float a = x[q], b = x[q | (1 << s)];
-                x[q] = a + b;
-                x[q | (1 << s)] = a - b;
-            }
+    return __builtin_bit_cast(u32, of_piece<P>(__builtin_bit_cast(float, v)));
 }
 
-// First stage (span 1) on a pair of binary16 inputs held in one word: (lo + hi, lo - hi) in fp32.  Widening a
-// binary16 number is exact, so a mixed-precision multiply-add lo * 1 +- hi rounds the same real sum once, as the
-// conversion followed by an fp32 add does: one instruction per output instead of a conversion and an add.
-__device__ __forceinline__ void first_stage(u32 pair, float &sum, float &diff)
+// Code words of piece P.  `inv` (with the forward scaling in it) and `fix` belong to piece pos & 3 of the lane.
+// The values are in the lane's frame: rounding is symmetric, so the frame goes into the reciprocal.
+template <int BITS, int CODEC, int P>
+__device__ __forceinline__ void rot_pack(const float (&v)[4][8], const RotLane &L, float inv, u32 fix,
+                                         u32 (&word)[4][BITS / 4])
 {
-    asm("v_fma_mix_f32 %0, %1, 1.0, %1 op_sel:[0,0,1] op_sel_hi:[1,0,1]" : "=v"(sum) : "v"(pair));
-    asm("v_fma_mix_f32 %0, %1, 1.0, -%1 op_sel:[0,0,1] op_sel_hi:[1,0,1]" : "=v"(diff) : "v"(pair));
+    const float inv_p = of_piece<P>(inv) * L.frame;
+    if constexpr (CODEC == kFp8)
+        pack_lane_fp8<8>(v[P], inv_p, word[P]);
+    else if constexpr (CODEC == kSym)
+        pack_lane_sym<BITS, 8>(v[P], inv_p, word[P]);
+    else
+        pack_digits<BITS, 8, false>(v[P], inv_p, 0.0f, of_piece_bits<P>(fix), word[P]);
 }
 
-// word position of element e in the padded LDS row: 4 extra words per lane segment of 2^LE elements
-template <int LE>
-__device__ __forceinline__ constexpr u32 padded(u32 e)
+template <int BITS, int P>
+__device__ __forceinline__ void rot_pack_literal(const float (&v)[4][8], const RotLane &L, float inv, float zf,
+                                                 u32 (&word)[4][BITS / 4])
 {
-    return e + 4u * (e >> LE);
-}
-
-// One LDS phase: stages over index bits [B0, B0 + NB).  Thread `tid` of T = 2^LT
-// threads holds the R values whose index has register bits q_lo at [B0, B0+NB)
-// and whose remaining bits are u = q_hi * T + tid; the position of the values is
-// unchanged, so there is no hazard inside a phase.
-template <int B0, int NB, int R, int LT, int LE>
-__device__ __forceinline__ void lds_phase(float *row, u32 tid)
-{
-    const u32 et = ((tid >> B0) << (B0 + NB)) | (tid & ((1u << B0) - 1u));
-    float *base = row + padded<LE>(et);
-    auto at = [](int q) constexpr -> u32 {
-        const u32 q_lo = (u32)q & ((1u << NB) - 1u), u = ((u32)q >> NB) << LT;
-        const u32 e = ((u >> B0) << (B0 + NB)) | (q_lo << B0) | (u & ((1u << B0) - 1u));
-        return e + 4u * (e >> LE);         // disjoint bit fields: padded(et | e) == padded(et) + padded(e)
-    };
-    float x[R];
+    const float inv_p = of_piece<P>(inv) * L.frame, z_p = of_piece<P>(zf);
 #pragma unroll
-    for (int q = 0; q < R; ++q) x[q] = base[at(q)];
-    butterflies<R, NB>(x);
+    for (int w = 0; w < BITS / 4; ++w) {
+        u32 acc = 0;
 #pragma unroll
-    for (int q = 0; q < R; ++q) base[at(q)] = x[q];
-}
-
-// Remaining stages for index bits [B0, END), R registers per thread, in phases of up to log2(R) bits.
-template <int B0, int END, int R, int LT, int LE>
-__device__ __forceinline__ void lds_phases(float *row, u32 tid)
-{
-    if constexpr (B0 < END) {
-        constexpr int NB = (END - B0) < ilog2(R) ? (END - B0) : ilog2(R);
-        lds_phase<B0, NB, R, LT, LE>(row, tid);
-        __syncthreads();
-        lds_phases<B0 + NB, END, R, LT, LE>(row, tid);
+        for (int i = 0; i < 32 / BITS; ++i) acc |= encode<BITS>(v[P][32 / BITS * w + i], inv_p, z_p) << (BITS * i);
+        word[P][w] = acc;
     }
 }
 
-// Shape of the workgroup for a code width and a row length.
-template <int BITS, int LOGH>
-struct RowShape {
-    static constexpr int EPL = lane_elems(BITS);
-    static constexpr int LE = ilog2(EPL);
-    static constexpr int H = 1 << LOGH;
-    static constexpr int LANES = H / EPL;
-    static constexpr int T = LANES < kBlockThreads ? LANES : kBlockThreads;
-    static constexpr int LT = ilog2(T);
-    static constexpr int P = LANES / T;
-    static constexpr int R = EPL * P;
-    static constexpr int ROW_WORDS = H + 4 * (H / EPL);
-    static_assert(T >= 64 && (P == 1 || P == 2), "rows of 2048 to 8192 elements");
-};
-
-// In-place transform of every aligned block of 2^LB elements of the chunk held as
-// v[p][i] = element (p*T + tid)*EPL + i.  With S0 = 1 the caller has already applied the first stage (span 1).
-template <int BITS, int LOGH, int LB, int S0, int NP, int NE>
-__device__ __forceinline__ void hadamard_row(float (&v)[NP][NE], float *row, u32 tid)
-{
-    using S = RowShape<BITS, LOGH>;
-    static_assert(NP == S::P && NE == S::EPL, "row held as v[P][EPL]");
-    static_assert(LB <= LOGH && LB > S::LE, "blocks of at least two lanes, at most the chunk");
-#pragma unroll
-    for (int p = 0; p < S::P; ++p) butterflies<S::EPL, S::LE, S0>(v[p]);
-#pragma unroll
-    for (int p = 0; p < S::P; ++p) {
-        u32x4 *dst = reinterpret_cast<u32x4 *>(row + padded<S::LE>((p * S::T + tid) * S::EPL));
-#pragma unroll
-        for (int k = 0; k < S::EPL / 4; ++k)
-            dst[k] = u32x4{__builtin_bit_cast(u32, v[p][4 * k]), __builtin_bit_cast(u32, v[p][4 * k + 1]),
-                           __builtin_bit_cast(u32, v[p][4 * k + 2]), __builtin_bit_cast(u32, v[p][4 * k + 3])};
-    }
-    __syncthreads();
-    lds_phases<S::LE, LB, S::R, S::LT, S::LE>(row, tid);       // ends with a barrier
-#pragma unroll
-    for (int p = 0; p < S::P; ++p) {
-        const u32x4 *src = reinterpret_cast<const u32x4 *>(row + padded<S::LE>((p * S::T + tid) * S::EPL));
-#pragma unroll
-        for (int k = 0; k < S::EPL / 4; ++k) {
-            const u32x4 a = src[k];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const u32 w = a[i];        // (a bit_cast applied to the vector element itself reads element 0)
-                v[p][4 * k + i] = __builtin_bit_cast(float, w);
-            }
-        }
-    }
-}
-
-// Rotate one chunk block by block and quantize it (FinegrainedQuantize of Algorithm 1 on the rotated values).
-// n_elems: elements of the whole tensor (a multiple of 2^LB; the last chunk may be a partial one when LB < LOGH:
-// lanes beyond the end read zeros and have their stores dropped or skipped).
-template <int BITS, int CODEC, int LOGH, int LB>
-__global__ __launch_bounds__((RowShape<BITS, LOGH>::T)) void k_quantize_rot(
-    const uint16_t *__restrict__ x, int64_t n_elems, int lpg, int group_shift, uint8_t *__restrict__ codes,
+// Rotate block by block and quantize (FinegrainedQuantize of Algorithm 1 on the rotated values).
+// n_elems: elements of the whole tensor, a multiple of 2^LB.
+template <int BITS, int CODEC, int LB>
+__global__ __launch_bounds__(64 * rot_group_waves(LB)) void k_quantize_rot(
+    const uint16_t *__restrict__ x, int64_t n_elems, int group_shift, uint8_t *__restrict__ codes,
     float *__restrict__ scales, float *__restrict__ zeros)
 {
-    using S = RowShape<BITS, LOGH>;
-    constexpr int EPL = S::EPL, T = S::T, P = S::P;
-    constexpr int kPieces = EPL * 2 / 16;
-    // the binary16 image of the row as it arrives and the padded fp32 row of the transform share their LDS (the
-    // image is dead once every thread has its values in registers): 37 KB instead of 53 KB per workgroup at
-    // hidden 8192, i.e. four resident workgroups per compute unit instead of three
-    constexpr int kImgBytes = P * (T / 64) * kPieces * 1024;
-    constexpr int kLdsBytes = kImgBytes > S::ROW_WORDS * 4 ? kImgBytes : S::ROW_WORDS * 4;
-    __shared__ __attribute__((aligned(16))) uint8_t lds[kLdsBytes];
-    __shared__ float slot[P][kBlockWaves][2];
-    uint8_t (*img)[T / 64][kPieces * 1024] = reinterpret_cast<uint8_t (*)[T / 64][kPieces * 1024]>(lds);
-    float *row = reinterpret_cast<float *>(lds);
+    constexpr bool FP8 = CODEC == kFp8;
+    constexpr int kWaves = rot_group_waves(LB);
+    constexpr int kTile = 2048 * kWaves;
+    __shared__ __attribute__((aligned(16))) uint8_t pieces[rot_exchange_bytes(LB, kRounds)];
+    __shared__ float mm[kWaves][4][2];
 
-    const u32 tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
-    const int64_t e0 = (int64_t)blockIdx.x << LOGH;
-    const int64_t here = (n_elems - e0) < (int64_t)S::H ? (n_elems - e0) : (int64_t)S::H;      // elements of this chunk
-    const rsrc_t rx = make_rsrc(x + e0, here * 2);
-    const rsrc_t rc = make_rsrc(codes + e0 * BITS / 8, here * BITS / 8);
+    const u32 tid = threadIdx.x, lane = tid & 63u;
+    const u32 wave = (u32)__builtin_amdgcn_readfirstlane((int)(tid >> 6));
+    const RotLane L = rot_lane<FP8>(lane);
+    const int64_t e_tile = (int64_t)blockIdx.x * kTile;
+    const int64_t left = n_elems - e_tile;
 
+    u32x4 raw[4];
+    const rsrc_t rx = make_rsrc(x + e_tile, left * 2);
 #pragma unroll
-    for (int p = 0; p < P; ++p)
+    for (u32 p = 0; p < 4; ++p)
+        raw[p] = __builtin_amdgcn_raw_buffer_load_b128(rx, rot_lane_offset(kRotLoaded, L) * 2,
+                                                       rot_piece_offset(kRotLoaded, wave, p) * 2, kStreamLoadPolicy);
+    float v[4][8];
 #pragma unroll
-        for (int k = 0; k < kPieces; ++k)
-            dma_piece(rx, (p * T * EPL + wave * 64 * EPL) * 2 + k * 1024 + lane * 16, &img[p][wave][k * 1024]);
-    wait_vmem_outstanding(0);
+    for (int p = 0; p < 4; ++p)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) first_stage(raw[p][i], v[p][2 * i], v[p][2 * i + 1]);
+    rot_forward<LB, FP8, kRounds>(v, L, pieces, wave);
 
-    float v[P][EPL];
-#pragma unroll
-    for (int p = 0; p < P; ++p) {
-        const u32x4 *mine = reinterpret_cast<const u32x4 *>(&img[p][wave][lane * (EPL * 2)]);
-#pragma unroll
-        for (int k = 0; k < kPieces; ++k) {
-            const u32x4 a = mine[k];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) first_stage(a[i], v[p][8 * k + 2 * i], v[p][8 * k + 2 * i + 1]);
-        }
-    }
-    __syncthreads();                                   // the image is read; its LDS becomes the row
-
-    hadamard_row<BITS, LOGH, LB, 1>(v, row, tid);
     // Forward scaling fwd = 2^-ceil(n/2), n = LB.  It is a power of two and nothing here is near the ends of
     // the fp32 range (the transformed values are multiples of 2^-24 below 2^30), so scaling commutes
     // with every rounding: instead of scaling all values, the group's min and max are scaled (which
@@ -201,129 +107,217 @@ __global__ __launch_bounds__((RowShape<BITS, LOGH>::T)) void k_quantize_rot(
     // from the unscaled values with the reciprocal times fwd, the same real product and hence the
     // same rounded one.
     constexpr float fwd = 1.0f / (float)(1 << ((LB + 1) / 2));
+    float mn, mx, s, inv, zf = 0.0f;
+    rot_group_minmax<LB, FP8>(v, L, group_shift, wave, mm, mn, mx);
+    const float mn_s = mn * fwd, mx_s = mx * fwd;
+    if constexpr (FP8)
+        group_params_absmax<448>(fmaxf(fabsf(mn_s), fabsf(mx_s)), s, inv);
+    else if constexpr (CODEC == kSym)
+        group_params_sym<BITS>(fmaxf(fabsf(mn_s), fabsf(mx_s)), s, inv);
+    else
+        group_params<BITS>(mn_s, mx_s, s, inv, zf);
+    inv *= fwd;
 
-    // group min / max: inside the wavefront, then across the wavefronts of the sub-tile, then
-    // (one group per row of two sub-tiles) across the sub-tiles
-    float mn[P], mx[P];
-#pragma unroll
-    for (int p = 0; p < P; ++p) {
-        lane_minmax(v[p], mn[p], mx[p]);
-        group_minmax<0>(mn[p], mx[p], lpg);
-        if (lpg > 64) cross_wave_minmax(mn[p], mx[p], slot[p], wave, lane, (u32)(lpg < T ? lpg : T) >> 6);
+    // the packed form needs zero-points below 2048 in magnitude and no rounding past the top code (see pack_lane);
+    // both hold for every group of the wavefront or its codes are formed literally
+    u32 word[4][BITS / 4];
+    bool literal = false;
+    u32 fix = 0;
+    if constexpr (CODEC == kAsym) {
+        constexpr float qmax = (float)((1 << BITS) - 1);
+        literal = __builtin_amdgcn_ballot_w64(!(fabsf(zf) < 2048.0f) || rintf(mx * inv) > qmax - zf) != 0;
+        fix = digit_fix<BITS>(zf);
     }
-    if (P == 2 && lpg > T) {
-        mn[0] = mn[P - 1] = fminf(mn[0], mn[P - 1]);
-        mx[0] = mx[P - 1] = fmaxf(mx[0], mx[P - 1]);
-    }
-
-    const int64_t g_row = ((int64_t)blockIdx.x << LOGH) >> group_shift;
-#pragma unroll
-    for (int p = 0; p < P; ++p) {
-        float s, inv, zf = 0.0f;
-        u32 word[4];
-        const float mn_s = mn[p] * fwd, mx_s = mx[p] * fwd;
-        if constexpr (CODEC == kFp8) {
-            group_params_absmax<448>(fmaxf(fabsf(mn_s), fabsf(mx_s)), s, inv);
-            pack_lane_fp8<EPL>(v[p], inv * fwd, word);
-        } else if constexpr (CODEC == kSym) {
-            group_params_sym<BITS>(fmaxf(fabsf(mn_s), fabsf(mx_s)), s, inv);
-            pack_lane_sym<BITS, EPL>(v[p], inv * fwd, word);
-        } else {
-            group_params<BITS>(mn_s, mx_s, s, inv, zf);
-            pack_lane<BITS, EPL>(v[p], inv * fwd, zf, mx[p], word);
+    if (literal) {
+        if constexpr (CODEC == kAsym) {
+            rot_pack_literal<BITS, 0>(v, L, inv, zf, word);
+            rot_pack_literal<BITS, 1>(v, L, inv, zf, word);
+            rot_pack_literal<BITS, 2>(v, L, inv, zf, word);
+            rot_pack_literal<BITS, 3>(v, L, inv, zf, word);
         }
-        __builtin_amdgcn_raw_buffer_store_b128(u32x4{word[0], word[1], word[2], word[3]}, rc,
-                                               (p * T + tid) * 16, 0, kStreamStorePolicy);
-        const u32 lane_in_row = p * T + tid;
-        if ((lane_in_row & (u32)(lpg - 1)) == 0 && (int64_t)(lane_in_row * EPL) < here) {
-            const int64_t gi = g_row + ((lane_in_row * EPL) >> group_shift);
-            scales[gi] = s;
-            if constexpr (CODEC == kAsym) zeros[gi] = zf;
+    } else {
+        rot_pack<BITS, CODEC, 0>(v, L, inv, fix, word);
+        rot_pack<BITS, CODEC, 1>(v, L, inv, fix, word);
+        rot_pack<BITS, CODEC, 2>(v, L, inv, fix, word);
+        rot_pack<BITS, CODEC, 3>(v, L, inv, fix, word);
+    }
+
+    // bits 7 and 8 go to lane bits 4 and 5, so that a store covers runs of 512 elements
+    constexpr RotMap done = rot_forward_map(LB);
+    constexpr RotMap out = {7, 8, done.l4 == 7 ? done.p0 : done.l4, done.l5 == 8 ? done.p1 : done.l5, done.w0, done.w1};
+    if constexpr (done.l4 != 7) rot_swap_words<4>(word);
+    if constexpr (done.l5 != 8) rot_swap_words<5>(word);
+    const rsrc_t rc = make_rsrc(codes + e_tile * BITS / 8, left * BITS / 8);
+    const u32 lane_at = rot_lane_offset(out, L) * BITS / 8;
+#pragma unroll
+    for (u32 p = 0; p < 4; ++p) {
+        const u32 at = rot_piece_offset(out, wave, p) * BITS / 8;
+        if constexpr (BITS == 4)
+            __builtin_amdgcn_raw_buffer_store_b32(word[p][0], rc, lane_at, at, kStreamStorePolicy);
+        else
+            __builtin_amdgcn_raw_buffer_store_b64(u32x2{word[p][0], word[p][1]}, rc, lane_at, at, kStreamStorePolicy);
+    }
+    // the lane whose quad begins the group in its piece stores the group's metadata
+    const u32 e_quad = rot_quad_offset(done, L, wave);
+    if ((e_quad & ((1u << group_shift) - 1u)) == 0) {
+        const int64_t g_tile = e_tile >> group_shift, n_groups = n_elems >> group_shift;
+        const u32 gi = (e_quad >> group_shift) * 4u;
+        store_f32(make_rsrc(scales + g_tile, (n_groups - g_tile) * 4), gi, s);
+        if constexpr (CODEC == kAsym) store_f32(make_rsrc(zeros + g_tile, (n_groups - g_tile) * 4), gi, zf);
+    }
+}
+
+// v[P] = (q - z) * s for the codes of piece P, in the lane's frame (EXACT: frame +1 and the literal operations).
+// s and z (z: as pack_zero_const gives it, EXACT: the bits of the number) belong to piece pos & 3 of the lane.
+template <int BITS, int CODEC, int P, bool EXACT>
+__device__ __forceinline__ void rot_unpack(const u32 (&word)[4][BITS / 4], float s, u32 z, float frame, float (&v)[4][8])
+{
+    float s_p = of_piece<P>(s);
+    if constexpr (CODEC == kFp8) {
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            const f32x2 lo = __builtin_amdgcn_cvt_pk_f32_fp8((int)word[P][k], false);
+            const f32x2 hi = __builtin_amdgcn_cvt_pk_f32_fp8((int)word[P][k], true);
+            v[P][4 * k + 0] = lo.x * s_p;
+            v[P][4 * k + 1] = lo.y * s_p;
+            v[P][4 * k + 2] = hi.x * s_p;
+            v[P][4 * k + 3] = hi.y * s_p;
+        }
+    } else if constexpr (EXACT) {
+        const float z_p = CODEC == kSym ? (float)(1 << (BITS - 1)) : __builtin_bit_cast(float, of_piece_bits<P>(z));
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            constexpr int per_word = 32 / BITS;
+            const u32 w = CODEC == kSym ? to_offset_binary<BITS>(word[P][i / per_word]) : word[P][i / per_word];
+            v[P][i] = ((float)((w >> (BITS * (i % per_word))) & ((1u << BITS) - 1u)) - z_p) * s_p;
+        }
+    } else {
+        s_p *= frame;
+        const ZeroConst c = CODEC == kSym ? sym_zero_const<BITS>() : unpack_zero_const(of_piece_bits<P>(z));
+#pragma unroll
+        for (int k = 0; k < BITS / 4; ++k) {
+            const u32 w = CODEC == kSym ? to_offset_binary<BITS>(word[P][k]) : word[P][k];
+            if constexpr (BITS == 4) {
+                h2 d[4];
+                nibbles_minus_zero(w, c, d);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    v[P][i] = fmaf((float)d[i].x, s_p, 0.0f);
+                    v[P][4 + i] = fmaf((float)d[i].y, s_p, 0.0f);
+                }
+            } else {
+                h2 d[2];
+                bytes_minus_zero(w, c, d);
+#pragma unroll
+                for (int i = 0; i < 2; ++i) {
+                    v[P][4 * k + i] = fmaf((float)d[i].x, s_p, 0.0f);
+                    v[P][4 * k + 2 + i] = fmaf((float)d[i].y, s_p, 0.0f);
+                }
+            }
         }
     }
 }
 
-// Dequantize one chunk, rotate it back block by block and round to binary16 (last step of Algorithm 1).
-template <int BITS, int CODEC, int LOGH, int LB>
-__global__ __launch_bounds__((RowShape<BITS, LOGH>::T)) void k_dequantize_rot(
+// Dequantize, rotate back block by block and round to binary16 (last step of Algorithm 1).
+// Registers for seven or eight wavefronts per SIMD: left to itself the compiler keeps temporaries of the exact form.
+//
+// Zeros: stages 3-6 lose the sign of a zero in the signed frame.  Where every zero-point of the wavefront is an
+// integer in reach of the short form and every scale is a normal positive number, no value of the contract is ever -0
+// (q - z = +0 times a positive scale; no product underflows; +0 + +0, a - a and a + -a are +0), so turning every zero
+// of the result into +0 restores it.  Otherwise the wavefront evaluates the literal operations in frame +1.  FP8
+// always does.  Wavefronts of one block tell each other with the exchange which form they took, so that a zero of
+// either sign meets only exact ones.
+template <int BITS, int CODEC, int LB>
+__global__ __launch_bounds__(64 * rot_group_waves(LB)) __attribute__((amdgpu_waves_per_eu(LB <= 11 ? 7 : 8))) void k_dequantize_rot(
     const uint8_t *__restrict__ codes, const float *__restrict__ scales, const float *__restrict__ zeros,
     int64_t n_elems, int group_shift, uint16_t *__restrict__ y)
 {
-    using S = RowShape<BITS, LOGH>;
-    constexpr int EPL = S::EPL, T = S::T, P = S::P;
-    constexpr int kPieces = EPL * 2 / 16;
-    // the padded fp32 row and the binary16 image of the result share their LDS (see k_quantize_rot)
-    constexpr int kImgBytes = (T / 64) * kPieces * 1024;
-    constexpr int kLdsBytes = kImgBytes > S::ROW_WORDS * 4 ? kImgBytes : S::ROW_WORDS * 4;
-    __shared__ __attribute__((aligned(16))) uint8_t lds[kLdsBytes];
-    uint8_t (*img)[kPieces * 1024] = reinterpret_cast<uint8_t (*)[kPieces * 1024]>(lds);
-    float *row = reinterpret_cast<float *>(lds);
+    constexpr bool FP8 = CODEC == kFp8;
+    constexpr int kWaves = rot_group_waves(LB);
+    constexpr int kTile = 2048 * kWaves;
+    __shared__ __attribute__((aligned(16))) uint8_t pieces[rot_exchange_bytes(LB, kRounds)];
+    __shared__ u32 exact_wave[kWaves];
 
-    const u32 tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
-    const int64_t e0 = (int64_t)blockIdx.x << LOGH;
-    const int64_t g_row = e0 >> group_shift;
-    const int64_t here = (n_elems - e0) < (int64_t)S::H ? (n_elems - e0) : (int64_t)S::H;      // elements of this chunk
-    const int64_t g_last = (n_elems >> group_shift) - 1;
-    const rsrc_t rc = make_rsrc(codes + e0 * BITS / 8, here * BITS / 8);
-    const rsrc_t ry = make_rsrc(y + e0, here * 2);
+    const u32 tid = threadIdx.x, lane = tid & 63u;
+    const u32 wave = (u32)__builtin_amdgcn_readfirstlane((int)(tid >> 6));
+    const RotLane L = rot_lane<FP8>(lane);
+    const int64_t e_tile = (int64_t)blockIdx.x * kTile;
+    const int64_t left = n_elems - e_tile;
+    const int64_t g_tile = e_tile >> group_shift, n_groups = n_elems >> group_shift;
 
-    float v[P][EPL];
+    const u32 gi = (rot_quad_offset(kRotLoaded, L, wave) >> group_shift) * 4u;
+    const rsrc_t rs = make_rsrc(scales + g_tile, (n_groups - g_tile) * 4);
+    const rsrc_t rc = make_rsrc(codes + e_tile * BITS / 8, left * BITS / 8);
+    const float s = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, gi, 0, 0));
+    float zf = 0.0f;
+    if constexpr (CODEC == kAsym) {
+        const rsrc_t rz = make_rsrc(zeros + g_tile, (n_groups - g_tile) * 4);
+        zf = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rz, gi, 0, 0));
+    }
+    u32 word[4][BITS / 4];
+    const u32 lane_at = rot_lane_offset(kRotNatural, L) * BITS / 8;
 #pragma unroll
-    for (int p = 0; p < P; ++p) {
-        const u32 lane_in_row = p * T + tid;
-        int64_t gi = g_row + ((lane_in_row * EPL) >> group_shift);
-        gi = gi < g_last ? gi : g_last;                    // lanes beyond a partial last chunk stay inside the arrays
-        const float s = scales[gi];
-        const u32x4 a = __builtin_amdgcn_raw_buffer_load_b128(rc, lane_in_row * 16, 0, kStreamLoadPolicy);
-        if constexpr (CODEC == kFp8) {
-            const u32 w[4] = {a[0], a[1], a[2], a[3]};
-            float d[EPL];
-            decode_fp8(w, d);
-#pragma unroll
-            for (int i = 0; i < EPL; ++i) v[p][i] = d[i] * s;
-        } else if constexpr (CODEC == kSym) {
-            const u32 w[4] = {to_offset_binary<BITS>(a[0]), to_offset_binary<BITS>(a[1]),
-                              to_offset_binary<BITS>(a[2]), to_offset_binary<BITS>(a[3])};
-            scaled_differences_fast<BITS>(w, sym_zero_const<BITS>(), s, v[p]);
+    for (u32 p = 0; p < 4; ++p) {
+        const u32 at = rot_piece_offset(kRotNatural, wave, p) * BITS / 8;
+        if constexpr (BITS == 4) {
+            word[p][0] = __builtin_amdgcn_raw_buffer_load_b32(rc, lane_at, at, kStreamLoadPolicy);
         } else {
-            const float zf = zeros[gi];
-            const u32 w[4] = {a[0], a[1], a[2], a[3]};
-            if (__builtin_amdgcn_ballot_w64(!zero_is_fast(zf)) == 0) {
-                scaled_differences_fast<BITS>(w, unpack_zero_const(pack_zero_const(zf)), s, v[p]);
-            } else {
-                float d[EPL];
-                codes_minus_zero_general<BITS>(w, zf, d);
-#pragma unroll
-                for (int i = 0; i < EPL; ++i) v[p][i] = d[i] * s;
-            }
+            const u32x2 a = __builtin_amdgcn_raw_buffer_load_b64(rc, lane_at, at, kStreamLoadPolicy);
+            word[p][0] = a[0];
+            word[p][1] = a[1];
         }
     }
+    rot_swap_words<4>(word);               // kRotNatural -> kRotLoaded
+    rot_swap_words<5>(word);
 
-    hadamard_row<BITS, LOGH, LB, 0>(v, row, tid);
-    __syncthreads();                                   // the row is read; its LDS becomes the output image
-    constexpr float inv = 1.0f / (float)(1 << (LB / 2));               // 2^-floor(n/2), n = LB
-
+    float v[4][8];
+    bool exact = true;
+    if constexpr (!FP8)
+        exact = (__builtin_amdgcn_ballot_w64(!(s >= FLT_MIN)) | (CODEC == kAsym ? zero_is_slow_mask(zf) : 0)) != 0;
+    if (exact) {
+        const u32 z = __builtin_bit_cast(u32, zf);
+        rot_unpack<BITS, CODEC, 0, true>(word, s, z, 1.0f, v);
+        rot_unpack<BITS, CODEC, 1, true>(word, s, z, 1.0f, v);
+        rot_unpack<BITS, CODEC, 2, true>(word, s, z, 1.0f, v);
+        rot_unpack<BITS, CODEC, 3, true>(word, s, z, 1.0f, v);
+        rot_inverse_row<true>(v, L);
+    } else if constexpr (!FP8) {
+        const u32 z = CODEC == kAsym ? pack_zero_const(zf) : 0;
+        rot_unpack<BITS, CODEC, 0, false>(word, s, z, L.frame, v);
+        rot_unpack<BITS, CODEC, 1, false>(word, s, z, L.frame, v);
+        rot_unpack<BITS, CODEC, 2, false>(word, s, z, L.frame, v);
+        rot_unpack<BITS, CODEC, 3, false>(word, s, z, L.frame, v);
+        rot_inverse_row<false>(v, L);
+    }
+    if constexpr (!FP8 && LB >= 12)
+        if (lane == 0) exact_wave[wave] = exact;
+    rot_inverse_rest<LB, kRounds>(v, L, pieces, wave, [&] {
+        if constexpr (!FP8 && LB >= 12) {
+            u32 n_exact = 0;
 #pragma unroll
-    for (int p = 0; p < P; ++p) {
-        u32x4 *mine = reinterpret_cast<u32x4 *>(&img[wave][lane * (EPL * 2)]);
+            for (int w = 0; w < kWaves; ++w) n_exact += (u32)__builtin_amdgcn_readfirstlane((int)exact_wave[w]);
+            exact = n_exact != 0;
+            if (n_exact != 0 && n_exact != (u32)kWaves) {
 #pragma unroll
-        for (int k = 0; k < kPieces; ++k) {
-            u32x4 out;
+                for (int p = 0; p < 4; ++p)
+                    if (exact_wave[LB == 13 ? p : p >> 1] == 0)            // the piece's sender took the short form
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                h2 h;
-                h.x = (_Float16)(v[p][8 * k + 2 * i] * inv);
-                h.y = (_Float16)(v[p][8 * k + 2 * i + 1] * inv);
-                out[i] = as_u32(h);
+                        for (int i = 0; i < 8; ++i) v[p][i] += 0.0f;
             }
-            mine[k] = out;
         }
+    });
+
+    constexpr float back = 1.0f / (float)(1 << (LB / 2));               // 2^-floor(n/2), n = LB
+    const float plus_zero = exact ? -0.0f : 0.0f;                       // t + -0 is t, t + +0 has no negative zero
+    const rsrc_t ry = make_rsrc(y + e_tile, left * 2);
 #pragma unroll
-        for (int k = 0; k < kPieces; ++k) {
-            const u32x4 o = *reinterpret_cast<const u32x4 *>(&img[wave][k * 1024 + lane * 16]);
-            __builtin_amdgcn_raw_buffer_store_b128(o, ry, (p * T * EPL + wave * 64 * EPL) * 2 + k * 1024 + lane * 16,
-                                                   0, kStreamStorePolicy);
-        }
+    for (u32 p = 0; p < 4; ++p) {
+        u32x4 out;
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            out[i] = round_pair(fmaf(v[p][2 * i], back, plus_zero), fmaf(v[p][2 * i + 1], back, plus_zero));
+        store_b128_at(out, ry, rot_lane_offset(rot_inverse_map(LB), L) * 2,
+                      rot_piece_offset(rot_inverse_map(LB), wave, p) * 2);
     }
 }
 
@@ -333,13 +327,19 @@ __global__ __launch_bounds__((RowShape<BITS, LOGH>::T)) void k_dequantize_rot(
 // ---------------------------------------------------------------------------
 namespace {
 
-template <int BITS, int CODEC, int LOGH, int LB>
+template <int LB>
+dim3 rot_grid(int64_t n_elems)
+{
+    constexpr int64_t kTile = 2048 * rot_group_waves(LB);
+    return dim3((unsigned)((n_elems + kTile - 1) / kTile));
+}
+
+template <int BITS, int CODEC, int LB>
 hipError_t quantize_rot_one(const uint16_t *x, int64_t n_elems, int group, uint8_t *c, float *scales,
                             float *zeros, hipStream_t stream)
 {
-    const unsigned grid = (unsigned)((n_elems + ((int64_t)1 << LOGH) - 1) >> LOGH);
-    return launch_kernel(k_quantize_rot<BITS, CODEC, LOGH, LB>, dim3(grid), dim3(RowShape<BITS, LOGH>::T), stream, x,
-                         n_elems, group / lane_elems(BITS), log2_int(group), c, scales, zeros);
+    return launch_kernel(k_quantize_rot<BITS, CODEC, LB>, rot_grid<LB>(n_elems), dim3(64 * rot_group_waves(LB)), stream,
+                         x, n_elems, log2_int(group), c, scales, zeros);
 }
 
 template <int BITS, int CODEC>
@@ -347,21 +347,20 @@ hipError_t quantize_rot_h(int log_b, const uint16_t *x, int64_t n_elems, int gro
                           float *zeros, hipStream_t stream)
 {
     switch (log_b) {
-    case 10: return quantize_rot_one<BITS, CODEC, 11, 10>(x, n_elems, group, c, scales, zeros, stream);
-    case 11: return quantize_rot_one<BITS, CODEC, 11, 11>(x, n_elems, group, c, scales, zeros, stream);
-    case 12: return quantize_rot_one<BITS, CODEC, 12, 12>(x, n_elems, group, c, scales, zeros, stream);
-    case 13: return quantize_rot_one<BITS, CODEC, 13, 13>(x, n_elems, group, c, scales, zeros, stream);
+    case 10: return quantize_rot_one<BITS, CODEC, 10>(x, n_elems, group, c, scales, zeros, stream);
+    case 11: return quantize_rot_one<BITS, CODEC, 11>(x, n_elems, group, c, scales, zeros, stream);
+    case 12: return quantize_rot_one<BITS, CODEC, 12>(x, n_elems, group, c, scales, zeros, stream);
+    case 13: return quantize_rot_one<BITS, CODEC, 13>(x, n_elems, group, c, scales, zeros, stream);
     default: return hipErrorInvalidValue;
     }
 }
 
-template <int BITS, int CODEC, int LOGH, int LB>
+template <int BITS, int CODEC, int LB>
 hipError_t dequantize_rot_one(const uint8_t *c, const float *scales, const float *zeros, int64_t n_elems,
                               int group, uint16_t *y, hipStream_t stream)
 {
-    const unsigned grid = (unsigned)((n_elems + ((int64_t)1 << LOGH) - 1) >> LOGH);
-    return launch_kernel(k_dequantize_rot<BITS, CODEC, LOGH, LB>, dim3(grid), dim3(RowShape<BITS, LOGH>::T), stream, c,
-                         scales, zeros, n_elems, log2_int(group), y);
+    return launch_kernel(k_dequantize_rot<BITS, CODEC, LB>, rot_grid<LB>(n_elems), dim3(64 * rot_group_waves(LB)),
+                         stream, c, scales, zeros, n_elems, log2_int(group), y);
 }
 
 template <int BITS, int CODEC>
@@ -369,10 +368,10 @@ hipError_t dequantize_rot_h(int log_b, const uint8_t *c, const float *scales, co
                             int64_t n_elems, int group, uint16_t *y, hipStream_t stream)
 {
     switch (log_b) {
-    case 10: return dequantize_rot_one<BITS, CODEC, 11, 10>(c, scales, zeros, n_elems, group, y, stream);
-    case 11: return dequantize_rot_one<BITS, CODEC, 11, 11>(c, scales, zeros, n_elems, group, y, stream);
-    case 12: return dequantize_rot_one<BITS, CODEC, 12, 12>(c, scales, zeros, n_elems, group, y, stream);
-    case 13: return dequantize_rot_one<BITS, CODEC, 13, 13>(c, scales, zeros, n_elems, group, y, stream);
+    case 10: return dequantize_rot_one<BITS, CODEC, 10>(c, scales, zeros, n_elems, group, y, stream);
+    case 11: return dequantize_rot_one<BITS, CODEC, 11>(c, scales, zeros, n_elems, group, y, stream);
+    case 12: return dequantize_rot_one<BITS, CODEC, 12>(c, scales, zeros, n_elems, group, y, stream);
+    case 13: return dequantize_rot_one<BITS, CODEC, 13>(c, scales, zeros, n_elems, group, y, stream);
     default: return hipErrorInvalidValue;
     }
 }

@@ -3,10 +3,11 @@
 // once.  2 N + 2 bytes per element; nothing else goes through HBM.  Bit-identical to fc_quantize_rot x N ->
 // fc_dequant_reduce_requant -> fc_dequantize_rot.
 //
-// What bounds it: vector instructions, (N + 1) log2 B of them per element for the butterflies alone: 3165 per wavefront
-// of 2048 elements at N = 4 and B = 8192, which is 88 % of the issue slots of the 203 us it takes on 4 partials of
-// 8192 x 8192 (group 128, INT4).  The three steps took 255 us there, the codes and metadata going through HBM and the
-// rows through LDS five times.  The transform and its layout are those of fc_rot_wave.hpp; the partials are taken in
+// What bounds it: vector instructions, (N + 1) log2 B of them per element for the butterflies alone.  181 us on 4 partials
+// of 8192 x 8192 (group 128, INT4); 195 us when bits 7 and 8 went through ds_swizzle and ds_bpermute, which keeps the LDS
+// crossbar of the whole compute unit busy for 6 cycles per instruction; the three steps took 255 us, the codes
+// and metadata going through HBM and the rows through LDS five times.
+// The transform and its layout are those of fc_rot_wave.hpp; the partials are taken in
 // source order in a loop, the next one's loads in flight while one is coded.  The sum stays in the frame of the rotated values (see there): rounding is symmetric, so the
 // quantizer works on a negated value as on the value, and the inverse transform undoes the frame.
 //
@@ -118,7 +119,7 @@ __global__ __launch_bounds__(64 * rot_group_waves(LB)) __attribute__((amdgpu_wav
     constexpr int kWaves = rot_group_waves(LB);
     constexpr int kTile = 2048 * kWaves;
     constexpr int kChunk = (512 * 1024) / (kTile * 2);                  // 512 KB of every partial per XCD and run
-    __shared__ __attribute__((aligned(16))) uint8_t pieces[rot_exchange_bytes(LB)];
+    __shared__ __attribute__((aligned(16))) uint8_t pieces[rot_exchange_bytes(LB, 1)];
     __shared__ float mm[kWaves][4][2];
 
     const u32 tid = threadIdx.x, lane = tid & 63u;
@@ -133,8 +134,8 @@ __global__ __launch_bounds__(64 * rot_group_waves(LB)) __attribute__((amdgpu_wav
         const rsrc_t rx = make_rsrc(x + (int64_t)j * n_elems + e_tile, left);
 #pragma unroll
         for (u32 p = 0; p < 4; ++p)
-            raw[p] = __builtin_amdgcn_raw_buffer_load_b128(rx, L.pos * 16, rot_piece_offset<LB>(wave, p, false) * 2,
-                                                           kStreamLoadPolicy);
+            raw[p] = __builtin_amdgcn_raw_buffer_load_b128(rx, rot_lane_offset(kRotLoaded, L) * 2,
+                                                           rot_piece_offset(kRotLoaded, wave, p) * 2, kStreamLoadPolicy);
     };
     constexpr float fwd = 1.0f / (float)(1 << ((LB + 1) / 2));          // 2^-ceil(n/2), n = LB
     constexpr float back = 1.0f / (float)(1 << (LB / 2));               // 2^-floor(n/2)
@@ -153,7 +154,7 @@ __global__ __launch_bounds__(64 * rot_group_waves(LB)) __attribute__((amdgpu_wav
 #pragma unroll
             for (int i = 0; i < 4; ++i) first_stage(raw[p][i], v[p][2 * i], v[p][2 * i + 1]);
         if (LB >= 12 && j > 0) lds_barrier();                          // every wavefront has taken the last exchange
-        rot_forward<LB, FP8>(v, L, pieces, wave);
+        rot_forward<LB, FP8, 1>(v, L, pieces, wave);
         float mn, mx, s, inv, zf;
         rot_group_minmax<LB, FP8>(v, L, group_shift, wave, mm, mn, mx);
         rot_params<CODEC>(mn, mx, rs, fwd, s, inv, zf);
@@ -174,7 +175,8 @@ __global__ __launch_bounds__(64 * rot_group_waves(LB)) __attribute__((amdgpu_wav
     rot_scale<1>(acc, s);
     rot_scale<2>(acc, s);
     rot_scale<3>(acc, s);
-    rot_inverse<LB, FP8, true>(acc, L, pieces, wave);
+    rot_inverse_row<FP8>(acc, L);
+    rot_inverse_back<LB, 1>(acc, L, pieces, wave);
 
     const rsrc_t ry = make_rsrc(y + e_tile, left);
 #pragma unroll
@@ -182,17 +184,10 @@ __global__ __launch_bounds__(64 * rot_group_waves(LB)) __attribute__((amdgpu_wav
         u32x4 out;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            h2 r;
-            if constexpr (FP8) {
-                r.x = (_Float16)(acc[p][2 * i] * back);
-                r.y = (_Float16)(acc[p][2 * i + 1] * back);
-            } else {
-                r.x = (_Float16)fmaf(acc[p][2 * i], back, 0.0f);
-                r.y = (_Float16)fmaf(acc[p][2 * i + 1], back, 0.0f);
-            }
-            out[i] = as_u32(r);
+            const float a = acc[p][2 * i], b = acc[p][2 * i + 1];
+            out[i] = FP8 ? round_pair(a * back, b * back) : round_pair(fmaf(a, back, 0.0f), fmaf(b, back, 0.0f));
         }
-        store_b128_at(out, ry, L.pos * 16, rot_piece_offset<LB>(wave, p, true) * 2);
+        store_b128_at(out, ry, rot_lane_offset(rot_back_map(LB), L) * 2, rot_piece_offset(rot_back_map(LB), wave, p) * 2);
     }
 }
 

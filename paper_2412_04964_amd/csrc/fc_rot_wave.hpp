@@ -1,12 +1,14 @@
 // fc_rot_wave.hpp -- the Walsh-Hadamard transform of the rotation kernels, held in registers.
 //
-// A wavefront owns 2048 consecutive elements, 32 per lane: v[p][i], p = 0..3, i = 0..7.  With pos(lane) the lane's
-// place in its piece (a permutation of the lanes inside every 8, below), element bits are
-//     bits 0-2: i      bits 3-8: pos(lane)      bits 9, 10: p      bits 11, 12: wavefront of the workgroup
-// so a piece of a wavefront is 512 consecutive elements and every global access is coalesced as it is, with no
-// staging through LDS.  Stages run in the order of the bits:
-//   0-2    between registers.
-//   3-6    between lanes of a row of 16, ONE instruction per value: v_fmac_f32 with a DPP operand, y = dpp(y) * sgn + y.
+// A wavefront owns 2048 elements, 32 per lane: v[p][i], p = 0..3, i = 0..7.  Element bits 0-2 are i; bits 3-6 are the lane's
+// place in its row of 16 (a permutation of the lanes inside every 8, below).  Bits 7 and on lie in lane bits 4 and 5, in the
+// two bits of p and in the wavefront number, and move as the stages pass (RotMap): a stage is done where its bit
+// lies in p, and bits change places by whole registers.  A row of 16 lanes always holds 128 consecutive elements, so binary16
+// values go to and from memory as they are, in runs of 256 bytes, with no staging through LDS.  Stages run in the order of
+// the bits; costs are SIMD cycles per value, as measured (v_add_f32, v_sub_f32, v_fmac_f32: 2; anything with a DPP operand: 4;
+// v_permlane16/32_swap: 8 for two values; ds_swizzle 2 and ds_bpermute 6 LDS cycles for the whole compute unit):
+//   0-2    between registers: 2.
+//   3-6    between lanes of a row of 16, ONE instruction per value: v_fmac_f32 with a DPP operand, y = dpp(y) * sgn + y: 4.
 //          DPP offers lane ^ 1, ^ 2, ^ 7 (half-row mirror) and ^ 8 (rotation by 8) but not ^ 4; these four masks are
 //          independent, so bits 3-6 are laid over them: pos(lane) = lane ^ (lane & 4 ? 3 : 0) and bit 3..6 flips when
 //          the lane is xor-ed with 1, 2, 7, 8.  The accumulating operand cannot be negated, so the lane with the bit
@@ -14,13 +16,15 @@
 //          rounded difference negates exactly, later stages between lanes of one frame are unaffected, and the
 //          inverse transform, run on values in this frame with the opposite signs, undoes it.  The one thing that
 //          is lost is the sign of a zero.
-//   7, 8   between rows: the partner's value comes through the LDS crossbar (ds_swizzle, ds_bpermute: no LDS memory),
-//          then one v_fma_f32.
-//   9, 10  between registers.
-//   11, 12 the wavefronts of a block exchange pieces for wavefront number through LDS (rotation_exchange), so that these bits are
-//          register bits too; bits 9, 10 then number the wavefronts.
+//   7, 8   between pieces: 2.  Values are loaded with these bits in p.
+//   9      in lane bit 4: the partner's value comes through the LDS crossbar (ds_swizzle: no LDS memory), then one
+//          v_fmac_f32: 2.  (Blocks of 8192 let it change places with bit 7 by v_permlane16_swap instead: 6.)
+//   10     changes places with bit 8 (v_permlane32_swap, then between pieces): 6.
+//   11, 12 the wavefronts of a block exchange pieces for wavefront number through LDS (rot_exchange), so that these bits are
+//          piece bits too.
 // FP8 codes keep the sign of zero, so that quantizer's lanes compute a - b itself in stages 3-6 (a DPP move and a
-// v_fma_f32, two instructions per value) and every frame is +1.
+// v_fma_f32 in 3 and 4, as stage 9 in 5 and 6) and every frame is +1.  The crossbar for 5 and 6 of the other quantizers
+// as well: 2 % faster for blocks of 1024, 3 % slower in the all-reduce, whose four wavefronts per SIMD hide less latency.
 #pragma once
 
 #include "fc_device.hpp"
@@ -28,9 +32,9 @@
 namespace fc {
 
 struct RotLane {
-    u32 lane, pos;           // pos: place of the lane's 8 elements in the piece
+    u32 lane, pos;           // pos: place of the lane's 8 elements in the wavefront's 64
     int far;                 // byte index of lane ^ 32
-    float s[6];              // +1 / -1 by bits 3..8 of the lane's elements
+    float s[5];              // +1 / -1 by bits 0..4 of pos
     float frame;             // product of s[0..3]: the frame after stages 3-6 (1 for FP8)
 };
 
@@ -42,12 +46,41 @@ __device__ __forceinline__ RotLane rot_lane(u32 lane)
     L.pos = lane ^ ((lane & 4u) ? 3u : 0u);
     L.far = (int)((lane ^ 32u) * 4u);
 #pragma unroll
-    for (int b = 0; b < 6; ++b) L.s[b] = (L.pos >> b) & 1u ? -1.0f : 1.0f;
+    for (int b = 0; b < 5; ++b) L.s[b] = (L.pos >> b) & 1u ? -1.0f : 1.0f;
     L.frame = FP8 ? 1.0f : ((__popc(L.pos & 15u) & 1) ? -1.0f : 1.0f);
     return L;
 }
 
-constexpr int kDppRowRor8 = 0x128;
+// Which element bit lies in lane bits 4 and 5, in the two piece bits and in the wavefront number
+struct RotMap {
+    int l4, l5, p0, p1, w0, w1;
+};
+constexpr RotMap kRotLoaded = {9, 10, 7, 8, 11, 12};                 // as values are loaded and the transforms begin
+constexpr RotMap kRotNatural = {7, 8, 9, 10, 11, 12};                // as codes are loaded (see rot_words_loaded)
+constexpr RotMap rot_forward_map(int lb)                             // after the forward transform
+{
+    return lb == 10 ? RotMap{9, 10, 7, 8, 11, 12} : lb == 11 ? RotMap{9, 8, 7, 10, 11, 12}
+         : lb == 12 ? RotMap{9, 8, 7, 11, 10, 12} : RotMap{7, 8, 11, 12, 9, 10};
+}
+constexpr RotMap rot_back_map(int lb)                                // after an inverse transform that follows a forward one
+{
+    return lb == 12 ? RotMap{9, 10, 7, 11, 8, 12} : lb == 13 ? RotMap{11, 10, 9, 12, 7, 8} : rot_forward_map(lb);
+}
+// element offsets in the workgroup's tile: of the lane (without bits 0-2 of pos below `keep`), and of a piece
+__device__ __forceinline__ u32 rot_lane_offset(const RotMap m, const RotLane &L, u32 keep = 15u)
+{
+    return (L.pos & keep) * 8u + (((L.lane >> 4) & 1u) << m.l4) + ((L.lane >> 5) << m.l5);
+}
+__device__ __forceinline__ u32 rot_piece_offset(const RotMap m, u32 wave, u32 p)
+{
+    return ((p & 1u) << m.p0) + ((p >> 1) << m.p1) + ((wave & 1u) << m.w0) + ((wave >> 1) << m.w1);
+}
+// Element where the quad of lanes of this lane begins in piece pos & 3.  Scale and zero-point of that piece's 32 elements
+// are this lane's to load, or to derive and store.
+__device__ __forceinline__ u32 rot_quad_offset(const RotMap m, const RotLane &L, u32 wave)
+{
+    return rot_lane_offset(m, L, 12u) + rot_piece_offset(m, wave, L.pos & 3u);
+}
 
 // v[0..7] = dpp(v) * s + v.  s_nop: two wait states between the write of a register and its DPP read.
 #define FC_FMAC_DPP8(ctrl, sign)                                                                                     \
@@ -81,22 +114,39 @@ __device__ __forceinline__ void fmac_dpp8(float (&v)[8], float s)
 }
 #undef FC_FMAC_DPP8
 
+template <int MASK>
+__device__ __forceinline__ float crossbar(float v)                      // the value of lane ^ MASK, MASK < 32
+{
+    return __builtin_bit_cast(float, __builtin_amdgcn_ds_swizzle(__builtin_bit_cast(int, v), (MASK << 10) | 0x1F));
+}
+
+// the stage of the element bit that flips with lane ^ MASK, with its sign s
+template <int MASK>
+__device__ __forceinline__ void rot_crossbar_stage(float (&v)[4][8], float s)
+{
+#pragma unroll
+    for (int p = 0; p < 4; ++p)
+#pragma unroll
+        for (int i = 0; i < 8; ++i) v[p][i] = fmaf(v[p][i], s, crossbar<MASK>(v[p][i]));
+}
+
 // stages 3-6.  INV: the values come in the frame of the forward transform and leave in frame +1.
 template <bool FP8, bool INV>
 __device__ __forceinline__ void rot_row_stages(float (&v)[4][8], const RotLane &L)
 {
+    if constexpr (FP8) {
 #pragma unroll
-    for (int p = 0; p < 4; ++p) {
-        if constexpr (FP8) {
+        for (int p = 0; p < 4; ++p) {
 #pragma unroll
             for (int i = 0; i < 8; ++i) v[p][i] = fmaf(v[p][i], L.s[0], dpp_read<kDppQuadXor1>(v[p][i]));
 #pragma unroll
             for (int i = 0; i < 8; ++i) v[p][i] = fmaf(v[p][i], L.s[1], dpp_read<kDppQuadXor2>(v[p][i]));
+        }
+        rot_crossbar_stage<7>(v, L.s[2]);
+        rot_crossbar_stage<8>(v, L.s[3]);
+    } else {
 #pragma unroll
-            for (int i = 0; i < 8; ++i) v[p][i] = fmaf(v[p][i], L.s[2], dpp_read<kDppRowHalfMirror>(v[p][i]));
-#pragma unroll
-            for (int i = 0; i < 8; ++i) v[p][i] = fmaf(v[p][i], L.s[3], dpp_read<kDppRowRor8>(v[p][i]));
-        } else {
+        for (int p = 0; p < 4; ++p) {
             fmac_dpp8<3, INV>(v[p], L.s[0]);
             fmac_dpp8<4, INV>(v[p], L.s[1]);
             fmac_dpp8<5, INV>(v[p], L.s[2]);
@@ -105,27 +155,49 @@ __device__ __forceinline__ void rot_row_stages(float (&v)[4][8], const RotLane &
     }
 }
 
-__device__ __forceinline__ float row_swap(float v)                     // the value of lane ^ 16
-{
-    return __builtin_bit_cast(float, __builtin_amdgcn_ds_swizzle(__builtin_bit_cast(int, v), 0x401F));
-}
-
 __device__ __forceinline__ float half_swap(float v, const RotLane &L)  // the value of lane ^ 32
 {
     return __builtin_bit_cast(float, __builtin_amdgcn_ds_bpermute(L.far, __builtin_bit_cast(int, v)));
 }
 
-// stages 7 and 8
-__device__ __forceinline__ void rot_cross_stages(float (&v)[4][8], const RotLane &L)
+// a and b exchange what lane bit LANE_BIT = 1 of a and = 0 of b hold
+template <int LANE_BIT>
+__device__ __forceinline__ void swap_lane_bit(u32 &a, u32 &b)
 {
+    static_assert(LANE_BIT == 4 || LANE_BIT == 5, "rows of 16 lanes, halves of 32");
+    const u32x2 r = LANE_BIT == 4 ? __builtin_amdgcn_permlane16_swap(a, b, false, false)
+                                  : __builtin_amdgcn_permlane32_swap(a, b, false, false);
+    a = r[0];
+    b = r[1];
+}
+
+// the bits of lane bit 4 and piece bit 0 (lane bit 5 and piece bit 1) change places
+template <int LANE_BIT>
+__device__ __forceinline__ void rot_swap(float (&v)[4][8])
+{
+    constexpr int P = LANE_BIT == 4 ? 1 : 2;
 #pragma unroll
     for (int p = 0; p < 4; ++p)
+        if (!(p & P))
 #pragma unroll
-        for (int i = 0; i < 8; ++i) v[p][i] = fmaf(v[p][i], L.s[4], row_swap(v[p][i]));
+            for (int i = 0; i < 8; ++i) {
+                u32 a = __builtin_bit_cast(u32, v[p][i]), b = __builtin_bit_cast(u32, v[p | P][i]);
+                swap_lane_bit<LANE_BIT>(a, b);
+                v[p][i] = __builtin_bit_cast(float, a);
+                v[p | P][i] = __builtin_bit_cast(float, b);
+            }
+}
+
+// the same on packed words: W per piece and lane
+template <int LANE_BIT, int W>
+__device__ __forceinline__ void rot_swap_words(u32 (&word)[4][W])
+{
+    constexpr int P = LANE_BIT == 4 ? 1 : 2;
 #pragma unroll
     for (int p = 0; p < 4; ++p)
+        if (!(p & P))
 #pragma unroll
-        for (int i = 0; i < 8; ++i) v[p][i] = fmaf(v[p][i], L.s[5], half_swap(v[p][i], L));
+            for (int k = 0; k < W; ++k) swap_lane_bit<LANE_BIT>(word[p][k], word[p | P][k]);
 }
 
 // First stage (span 1) on a pair of binary16 inputs held in one word: (lo + hi, lo - hi) in fp32.  Widening a
@@ -178,95 +250,138 @@ __device__ __forceinline__ void lds_barrier()
 // workgroup; these never meet)
 constexpr int rot_block_waves(int lb) { return lb <= 11 ? 1 : 1 << (lb - 11); }
 constexpr int rot_group_waves(int lb) { return lb <= 11 ? 2 : 1 << (lb - 11); }
-// bytes of LDS through which the wavefronts of a block exchange pieces (2 KB each)
-constexpr int rot_exchange_bytes(int lb) { return lb <= 11 ? 16 : rot_block_waves(lb) * 4 * 2048; }
+// bytes of LDS through which the wavefronts of a block exchange pieces, in one or two rounds
+constexpr int rot_exchange_bytes(int lb, int rounds) { return lb <= 11 ? 16 : rot_block_waves(lb) * 4 * 2048 / rounds; }
 
 // Piece bits change places with wavefront bits; an involution.  LB = 13: the two piece bits with the two wavefront
 // bits.  LB = 12: the upper piece bit with the one wavefront bit.  Pieces lie in LDS by receiving wavefront, then by
 // sending wavefront, so that one address register serves all writes and one all reads.  The piece that stays goes
 // through LDS as well: sorting it out costs a branch per piece and nothing is gained (LDS is not what bounds these
 // kernels).  The caller sees to it that the previous readers of `lds` are done.
-template <int LB>
+// Two rounds of half the values each halve the LDS, for kernels that it keeps from filling the SIMDs with wavefronts.
+template <int LB, int ROUNDS>
 __device__ __forceinline__ void rot_exchange(float (&v)[4][8], uint8_t *lds, u32 wave, u32 lane)
 {
     static_assert(LB == 12 || LB == 13, "blocks of several wavefronts");
-    constexpr u32 kPerSender = LB == 13 ? 2048 : 4096, kPerReceiver = 8192;
+    static_assert(ROUNDS == 1 || ROUNDS == 2, "all of a lane's 32 bytes per piece, or half of them");
+    constexpr u32 kPiece = 2048 / ROUNDS, kPerSender = LB == 13 ? kPiece : 2 * kPiece, kPerReceiver = 4 * kPiece;
     uint8_t *out = lds + wave * kPerSender + lane * 16;
     const uint8_t *in = lds + wave * kPerReceiver + lane * 16;
 #pragma unroll
-    for (u32 p = 0; p < 4; ++p)
+    for (u32 r = 0; r < (u32)ROUNDS; ++r) {
+        if (r > 0) lds_barrier();
 #pragma unroll
-        for (u32 h = 0; h < 2; ++h) {
-            const u32 at = (LB == 13 ? p * kPerReceiver : (p >> 1) * kPerReceiver + (p & 1u) * 2048) + h * 1024;
-            *reinterpret_cast<u32x4 *>(out + at) =
-                u32x4{__builtin_bit_cast(u32, v[p][4 * h]), __builtin_bit_cast(u32, v[p][4 * h + 1]),
-                      __builtin_bit_cast(u32, v[p][4 * h + 2]), __builtin_bit_cast(u32, v[p][4 * h + 3])};
-        }
-    lds_barrier();
+        for (u32 p = 0; p < 4; ++p)
 #pragma unroll
-    for (u32 p = 0; p < 4; ++p)
-#pragma unroll
-        for (u32 h = 0; h < 2; ++h) {
-            const u32x4 a = *reinterpret_cast<const u32x4 *>(in + p * 2048 + h * 1024);
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const u32 w = a[i];        // (a bit_cast applied to the vector element itself reads element 0)
-                v[p][4 * h + i] = __builtin_bit_cast(float, w);
+            for (u32 k = 0; k < 2 / ROUNDS; ++k) {
+                const u32 h = r + k;
+                const u32 at = (LB == 13 ? p * kPerReceiver : (p >> 1) * kPerReceiver + (p & 1u) * kPiece) + k * 1024;
+                *reinterpret_cast<u32x4 *>(out + at) =
+                    u32x4{__builtin_bit_cast(u32, v[p][4 * h]), __builtin_bit_cast(u32, v[p][4 * h + 1]),
+                          __builtin_bit_cast(u32, v[p][4 * h + 2]), __builtin_bit_cast(u32, v[p][4 * h + 3])};
             }
-        }
+        lds_barrier();
+#pragma unroll
+        for (u32 p = 0; p < 4; ++p)
+#pragma unroll
+            for (u32 k = 0; k < 2 / ROUNDS; ++k) {
+                const u32 h = r + k;
+                const u32x4 a = *reinterpret_cast<const u32x4 *>(in + p * kPiece + k * 1024);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const u32 w = a[i];    // (a bit_cast applied to the vector element itself reads element 0)
+                    v[p][4 * h + i] = __builtin_bit_cast(float, w);
+                }
+            }
+    }
 }
 
-// Stages 1 ... LB-1 of the forward transform (the caller applies stage 0 while widening).  Blocks of several
-// wavefronts end exchanged.
-template <int LB, bool FP8>
+// Stages 1 ... LB-1 of the forward transform (the caller applies stage 0 while widening): kRotLoaded -> rot_forward_map
+template <int LB, bool FP8, int ROUNDS>
 __device__ __forceinline__ void rot_forward(float (&v)[4][8], const RotLane &L, uint8_t *lds, u32 wave)
 {
     rot_register_stage<2>(v);
     rot_register_stage<4>(v);
     rot_row_stages<FP8, false>(v, L);
-    rot_cross_stages(v, L);
     rot_piece_stage<1>(v);
-    if constexpr (LB >= 11) rot_piece_stage<2>(v);
+    rot_piece_stage<2>(v);
+    if constexpr (LB == 13) {
+        rot_swap<4>(v);
+        rot_piece_stage<1>(v);
+    } else {
+        rot_crossbar_stage<16>(v, L.s[4]);
+    }
+    if constexpr (LB >= 11) {
+        rot_swap<5>(v);
+        rot_piece_stage<2>(v);
+    }
     if constexpr (LB >= 12) {
-        rot_exchange<LB>(v, lds, wave, L.lane);
+        rot_exchange<LB, ROUNDS>(v, lds, wave, L.lane);
         if constexpr (LB == 13) rot_piece_stage<1>(v);
         rot_piece_stage<2>(v);
     }
 }
 
-// All stages on values in the frame of the forward transform.  SWAPPED: blocks of several wavefronts come exchanged.
-// They end exchanged.
-template <int LB, bool FP8, bool SWAPPED>
-__device__ __forceinline__ void rot_inverse(float (&v)[4][8], const RotLane &L, uint8_t *lds, u32 wave)
+// Inverse transform: stages 0-6 on values in the frame of the forward transform, which they leave (FP8: frame +1)
+template <bool FP8>
+__device__ __forceinline__ void rot_inverse_row(float (&v)[4][8], const RotLane &L)
 {
     rot_register_stage<1>(v);
     rot_register_stage<2>(v);
     rot_register_stage<4>(v);
     rot_row_stages<FP8, true>(v, L);
-    rot_cross_stages(v, L);
-    if constexpr (LB >= 12 && SWAPPED) {
-        rot_exchange<LB>(v, lds, wave, L.lane);
-        lds_barrier();                                     // the pieces are read; the exchange below writes there
-    }
+}
+
+// ... and the remaining ones, on values that come from memory: kRotLoaded -> rot_forward_map.  `exchanged` is called between the
+// exchange and the stages after it.
+template <int LB, int ROUNDS, typename F>
+__device__ __forceinline__ void rot_inverse_rest(float (&v)[4][8], const RotLane &L, uint8_t *lds, u32 wave, F exchanged)
+{
     rot_piece_stage<1>(v);
-    if constexpr (LB >= 11) rot_piece_stage<2>(v);
+    rot_piece_stage<2>(v);
+    rot_crossbar_stage<16>(v, L.s[4]);
+    if constexpr (LB >= 11) {
+        rot_swap<5>(v);
+        rot_piece_stage<2>(v);
+    }
     if constexpr (LB >= 12) {
-        rot_exchange<LB>(v, lds, wave, L.lane);
+        rot_exchange<LB, ROUNDS>(v, lds, wave, L.lane);
+        exchanged();
         if constexpr (LB == 13) rot_piece_stage<1>(v);
         rot_piece_stage<2>(v);
     }
 }
+constexpr RotMap rot_inverse_map(int lb) { return lb == 13 ? RotMap{9, 8, 11, 12, 7, 10} : rot_forward_map(lb); }
 
-// element offset, inside the workgroup's first block's chunk, of piece p of a wavefront; after the exchange if `swapped`
-template <int LB>
-__device__ __forceinline__ u32 rot_piece_offset(u32 wave, u32 p, bool swapped)
+// ... or that a forward transform has left: rot_forward_map -> rot_back_map
+template <int LB, int ROUNDS>
+__device__ __forceinline__ void rot_inverse_back(float (&v)[4][8], const RotLane &L, uint8_t *lds, u32 wave)
 {
-    if constexpr (LB == 13)
-        return swapped ? (p * 4u + wave) * 512u : (wave * 4u + p) * 512u;
-    else if constexpr (LB == 12)
-        return swapped ? ((p & 2u) * 2u + wave * 2u + (p & 1u)) * 512u : (wave * 4u + p) * 512u;
-    else
-        return (wave * 4u + p) * 512u;
+    if constexpr (LB == 13) {
+        rot_swap<4>(v);                    // l4 l5 p0 p1 w0 w1 = 11  8  7 12  9 10
+        rot_piece_stage<1>(v);
+        rot_swap<5>(v);                    //                     11 12  7  8  9 10
+        rot_piece_stage<2>(v);
+        rot_exchange<LB, ROUNDS>(v, lds, wave, L.lane);            //     11 12  9 10  7  8
+        rot_piece_stage<1>(v);
+        rot_piece_stage<2>(v);
+        rot_crossbar_stage<16>(v, L.s[4]);
+        rot_swap<5>(v);                    //                     11 10  9 12  7  8
+        rot_piece_stage<2>(v);
+    } else {
+        rot_piece_stage<1>(v);
+        if constexpr (LB >= 11) rot_swap<5>(v);            // 11:  9 10  7  8      12:  9 11  7  8 10
+        rot_piece_stage<2>(v);
+        rot_crossbar_stage<16>(v, L.s[4]);
+        if constexpr (LB == 12) {
+            rot_exchange<LB, ROUNDS>(v, lds, wave, L.lane);        //                           9 11  7 10  8
+            rot_piece_stage<2>(v);
+        }
+        if constexpr (LB >= 11) {
+            rot_swap<5>(v);                                // 11:  9  8  7 10      12:  9 10  7 11  8
+            rot_piece_stage<2>(v);
+        }
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -318,28 +433,25 @@ __device__ __forceinline__ void rot_group_minmax(const float (&v)[4][8], const R
     minmax_step<4, FP8>(n, x, b4 ? n2[0] : n2[1], b4 ? x2[0] : x2[1]);
     if (group_shift > 5) minmax_step<5, FP8>(n, x, n, x);
     if (group_shift > 6) minmax_step<6, FP8>(n, x, n, x);
-    if (group_shift > 7) {
-        n = fminf(n, row_swap(n));
-        x = fmaxf(x, row_swap(x));
+    // element bits from 7 on, where the forward transform left them; piece bits flip with bits 3 and 4 of the lane now
+    constexpr RotMap m = rot_forward_map(LB);
+    if (group_shift > m.l4) {
+        n = fminf(n, crossbar<16>(n));
+        x = fmaxf(x, crossbar<16>(x));
     }
-    if (group_shift > 8) {
+    if (group_shift > m.l5) {
         n = fminf(n, half_swap(n, L));
         x = fmaxf(x, half_swap(x, L));
     }
-    // element bits that number pieces flip with bits 3 and 4 of the lane now: bits 9, 10 (LB <= 11), bits 9, 11 (12),
-    // bits 11, 12 (13)
-    constexpr int kP0 = LB == 13 ? 11 : 9, kP1 = LB == 13 ? 12 : LB == 12 ? 11 : 10;
-    if (group_shift > kP0) minmax_step<3, FP8>(n, x, n, x);
-    if (group_shift > kP1) minmax_step<4, FP8>(n, x, n, x);
+    if (group_shift > m.p0) minmax_step<3, FP8>(n, x, n, x);
+    if (group_shift > m.p1) minmax_step<4, FP8>(n, x, n, x);
     if constexpr (!FP8) {
         const float t = L.frame < 0.0f ? -x : n;
         x = L.frame < 0.0f ? -n : x;
         n = t;
     }
     if constexpr (LB >= 12) {
-        // bits 9, 10 (LB = 13) or bit 10 (12) number the wavefronts
-        constexpr int kW0 = LB == 13 ? 9 : 10;
-        if (group_shift > kW0) {
+        if (group_shift > m.w0) {
             if (L.lane < 4u) {                             // lanes 0 ... 3 hold pieces 0 ... 3
                 slot[wave][L.lane][0] = n;
                 slot[wave][L.lane][1] = x;
@@ -348,7 +460,7 @@ __device__ __forceinline__ void rot_group_minmax(const float (&v)[4][8], const R
             const u32 piece = L.pos & 3u;
             n = fminf(n, slot[wave ^ 1u][piece][0]);
             x = fmaxf(x, slot[wave ^ 1u][piece][1]);
-            if (LB == 13 && group_shift > 10) {
+            if (LB == 13 && group_shift > m.w1) {
                 n = fminf(n, fminf(slot[wave ^ 2u][piece][0], slot[wave ^ 3u][piece][0]));
                 x = fmaxf(x, fmaxf(slot[wave ^ 2u][piece][1], slot[wave ^ 3u][piece][1]));
             }

@@ -228,3 +228,44 @@ def test_full_chip_runs_repeat(fc, quantizer, bits, hidden):
         assert torch.equal(y.view(torch.int16), want.view(torch.int16)), "dequantize_rot does not repeat"
         y = fc.allreduce_sim_rot(x, group, bits, bits, quantizer)
         assert torch.equal(y.view(torch.int16), want.view(torch.int16)), "one launch differs from the three steps"
+
+
+@pytest.mark.parametrize("quantizer,bits", [(oracle.ASYM, 4), (oracle.ASYM, 8), (oracle.SYM, 4), (oracle.SYM, 8)])
+@pytest.mark.parametrize("hidden", [1024, 2048, 4096, 8192])
+def test_dequantize_rot_signs_of_zero(fc, quantizer, bits, hidden):
+    # the short form drops signs of zero inside the transform, the literal one keeps them, and the wavefronts (2048
+    # elements) of one block may take different ones: rows that cancel to zeros everywhere, with zero-points and
+    # scales out of the short form's reach in all, in one and in none of the wavefronts; fractional zero-points and
+    # subnormal scales whose products underflow to -0.  The result must agree in every bit, zeros included.
+    group, rows = 128, 12
+    rng = np.random.default_rng(hidden + bits)
+    top = 1 << bits
+    q = np.zeros((rows, hidden), np.uint8)
+    s = np.ones((rows, hidden // group), np.float32)
+    z = np.zeros((rows, hidden // group), np.float32)
+    per_wave = min(2048, hidden) // group
+    z[1] = -3000.0                                     # constant rows: one spike, zeros elsewhere
+    z[2, :per_wave] = -3000.0
+    z[3, -per_wave:] = 3000.0
+    q[4:6] = 5
+    z[4:6] = 5.0                                       # q - z = 0 everywhere
+    s[5, ::3] = np.float32(1e-39)
+    z[6] = np.float32(1e-9)                            # d = -1e-9, times a subnormal scale: -0
+    s[6] = np.float32(1e-40)
+    z[7, :per_wave] = np.float32(1e-9)
+    s[7, :per_wave] = np.float32(1e-40)
+    s[8, -1] = np.float32(1e-42)
+    q[9] = rng.integers(0, top, hidden)
+    z[9, ::5] = 2500.0
+    q[10] = rng.integers(0, top, hidden)
+    q[11] = rng.integers(0, top, hidden)
+    s[11] = np.exp(rng.uniform(-95, 60, s.shape[1])).astype(np.float32)
+    codes = q if bits == 8 else (q[:, ::2] | (q[:, 1::2] << 4)).astype(np.uint8)
+    want = oracle.dequantize_rot(codes, s, z, hidden, group, bits, quantizer)
+    y = Guarded((rows, hidden), torch.float16)
+    fc.dequantize_rot(dev(codes), dev(s), dev(z), hidden, group, bits, quantizer, out=y.t)
+    torch.cuda.synchronize(); y.check()
+    got = y.t.cpu().numpy()
+    for r in range(rows):
+        assert same_bits(got[r].view(np.uint16), want[r].view(np.uint16)), \
+            "row %d h=%d b=%d q=%d: %s" % (r, hidden, bits, quantizer, first_diff(got[r].view(np.uint16), want[r].view(np.uint16)))
