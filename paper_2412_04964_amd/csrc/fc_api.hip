@@ -182,11 +182,10 @@ int allreduce_sim_impl(int codec, const void *x_f16, int n_src, int64_t tokens, 
     if (!aligned16(workspace)) return FC_ERR_ALIGN;
 
     // the three steps in one kernel, bit-identical, nothing goes through the workspace: one form for launch-bound
-    // volumes (asymmetric quantizer; the partials' quantizations spread over wavefronts), one for all others (every
-    // quantizer)
+    // volumes (the partials' quantizations spread over wavefronts), one for all others
     if (one_launch) {
-        if (codec == fc::CODEC_ASYM && fc::allreduce_small_applies(n, group))
-            return hip_result(fc::launch_allreduce_small(bits_rs, bits_ag, x_f16, n_src, n, group, y_f16,
+        if (fc::allreduce_small_applies(n_src, n, group))
+            return hip_result(fc::launch_allreduce_small(codec, bits_rs, bits_ag, x_f16, n_src, n, group, y_f16,
                                                          static_cast<hipStream_t>(hip_stream)));
         return hip_result(fc::launch_allreduce_fused(codec, bits_rs, bits_ag, x_f16, n_src, n, group, y_f16,
                                                      static_cast<hipStream_t>(hip_stream)));

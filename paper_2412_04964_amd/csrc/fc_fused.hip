@@ -47,19 +47,33 @@ static hipError_t launch_nl(const FusedArgs &a, hipStream_t stream)
             static_cast<uint8_t *>(a.codes_out), a.scales_out, a.zeros_out);
 }
 
+template <int CODEC, int NSRC>
+static hipError_t launch_small(const FusedArgs &a, hipStream_t stream)
+{
+    const int64_t wave_elems = fused_small_wave_elems(FC_BITS_IN);
+    const int64_t waves = (a.n_elems + wave_elems - 1) / wave_elems;
+    return launch_kernel(k_fused_small<CODEC, FC_BITS_IN, FC_BITS_OUT, NSRC>, dim3((unsigned)waves), dim3(64), stream,
+            static_cast<const uint8_t *>(a.codes_in), a.codes_stride, a.scales_in, a.zeros_in,
+            a.meta_stride, a.n_elems, log2_int(a.group), a.group / fused_small_lane_elems(FC_BITS_IN),
+            static_cast<uint8_t *>(a.codes_out), a.scales_out, a.zeros_out);
+}
+
 // one instantiation per group width in lanes: 1 ... 128 lanes in 128-thread workgroups, 256 lanes in
 // 256-thread workgroups (wider groups go to fc_wide.hip before this point)
 template <int NSRC>
 static hipError_t launch_n(const FusedArgs &a, hipStream_t stream)
 {
-    // launch-bound volumes (asymmetric quantizer, fp32 metadata): one code word per lane and source
-    if (a.codec == CODEC_ASYM && fused_small_applies(FC_BITS_IN, a.n_elems, a.group)) {
-        const int64_t wave_elems = fused_small_wave_elems(FC_BITS_IN);
-        const int64_t waves = (a.n_elems + wave_elems - 1) / wave_elems;
-        return launch_kernel(k_fused_small<FC_BITS_IN, FC_BITS_OUT, NSRC>, dim3((unsigned)waves), dim3(64), stream,
-                static_cast<const uint8_t *>(a.codes_in), a.codes_stride, a.scales_in, a.zeros_in,
-                a.meta_stride, a.n_elems, log2_int(a.group), a.group / fused_small_lane_elems(FC_BITS_IN),
-                static_cast<uint8_t *>(a.codes_out), a.scales_out, a.zeros_out);
+    // launch-bound volumes: one code word per lane and source
+    if (fused_small_applies(FC_BITS_IN, a.n_elems, a.group)) {
+        switch (a.codec) {
+        case CODEC_ASYM: return launch_small<kAsym, NSRC>(a, stream);
+        case CODEC_SYM: return launch_small<kSym, NSRC>(a, stream);
+        case CODEC_ASYMH: return launch_small<kAsymH, NSRC>(a, stream);
+#if FC_BITS_IN == 8 && FC_BITS_OUT == 8
+        case CODEC_FP8: return launch_small<kFp8, NSRC>(a, stream);
+#endif
+        default: return hipErrorInvalidValue;
+        }
     }
     switch (a.group / lane_elems(FC_BITS_IN)) {
     case 1: return launch_nl<NSRC, 1>(a, stream);

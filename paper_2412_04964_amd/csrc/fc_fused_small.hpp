@@ -6,8 +6,8 @@
 // elements at 8 bit, 8 at 4 bit), so the same volume spreads over four times as many single-wavefront workgroups
 // and every chain is a quarter as long; all loads (codes, scales, zero-points of every source) are issued before
 // the first use.  The arithmetic is the literal form of the contract in include/fc.h, the same that the bulk
-// kernel's general path evaluates: d = (float)q - z, acc = fma(d, s, acc) in source order from +0, then Eq. 1-2
-// on the sums.  Groups span g / E adjacent lanes (at most the wavefront: g <= 256 at 8 bit, 512 at 4 bit).
+// kernel's general path evaluates: d = (float)q - z, acc = fma(d, s, acc) in source order from +0, then Eq. 1-2 (the
+// quantizer's own equations) on the sums.  Groups span g / E adjacent lanes (at most the wavefront: g <= 256 at 8 bit, 512 at 4 bit).
 #pragma once
 
 #include "fc_device.hpp"
@@ -18,7 +18,9 @@ constexpr int fused_small_lane_elems(int bits_in) { return 32 / bits_in; }
 constexpr int fused_small_wave_elems(int bits_in) { return 64 * fused_small_lane_elems(bits_in); }
 // Up to this many wavefronts (eight per compute unit of the part) the launch is latency-bound and this kernel wins
 // (decode shape, N = 8 at 8 bit: 2.63 -> 2.14 us per launch under graph replay; the two forms cross between 2048
-// and 4096 wavefronts).
+// and 4096 wavefronts).  The other quantizers the same way (N = 8, hidden 8192, g = 128, bulk -> this one): symmetric 4 bit
+// 3.46 -> 2.29 us at 8 tokens, 3.79 -> 2.77 at 64, 3.95 -> 3.35 at 128 (the limit); compact metadata 3.64 -> 2.36, 3.88 -> 2.90,
+// 4.06 -> 3.71; FP8 2.67 -> 2.18 at 8 tokens, 3.16 -> 2.99 at 64 (its limit).
 constexpr int kFusedSmallMaxWaves = 2048;
 
 inline bool fused_small_applies(int bits_in, int64_t n_elems, int group)
@@ -27,7 +29,29 @@ inline bool fused_small_applies(int bits_in, int64_t n_elems, int group)
            (n_elems + fused_small_wave_elems(bits_in) - 1) / fused_small_wave_elems(bits_in) <= kFusedSmallMaxWaves;
 }
 
-template <int BITS_IN, int BITS_OUT, int NSRC>
+// Codes of the lane as numbers, before the scale: q - z, the signed code, or the value of the E4M3 byte
+template <int CODEC, int BITS>
+__device__ __forceinline__ void small_decode(u32 w, float z, float (&d)[32 / BITS])
+{
+    constexpr int E = 32 / BITS;
+    if constexpr (CODEC == kFp8) {
+        const f32x2 lo = __builtin_amdgcn_cvt_pk_f32_fp8((int)w, false), hi = __builtin_amdgcn_cvt_pk_f32_fp8((int)w, true);
+        d[0] = lo.x;
+        d[1] = lo.y;
+        d[2] = hi.x;
+        d[3] = hi.y;
+    } else {
+#pragma unroll
+        for (int i = 0; i < E; ++i) {
+            if constexpr (CODEC == kSym)
+                d[i] = (float)((int)(w << (32 - BITS * (i + 1))) >> (32 - BITS));
+            else
+                d[i] = (float)((w >> (BITS * i)) & ((1u << BITS) - 1u)) - z;
+        }
+    }
+}
+
+template <int CODEC, int BITS_IN, int BITS_OUT, int NSRC>
 __global__ __launch_bounds__(64) void k_fused_small(
     const uint8_t *__restrict__ codes_in, int64_t codes_stride,
     const float *__restrict__ scales_in, const float *__restrict__ zeros_in, int64_t meta_stride,
@@ -35,7 +59,6 @@ __global__ __launch_bounds__(64) void k_fused_small(
     uint8_t *__restrict__ codes_out, float *__restrict__ scales_out, float *__restrict__ zeros_out)
 {
     constexpr int E = fused_small_lane_elems(BITS_IN);
-    constexpr u32 kMask = (1u << BITS_IN) - 1u;
     constexpr int kOutBytes = E * BITS_OUT / 8;                 // 2, 4 or 8 code bytes per lane
     const u32 lane = threadIdx.x;
     const int64_t e_wave = (int64_t)blockIdx.x * (64 * E);
@@ -53,27 +76,44 @@ __global__ __launch_bounds__(64) void k_fused_small(
                                     (n_elems - e_wave) * BITS_IN / 8);
         w[j] = __builtin_amdgcn_raw_buffer_load_b32(rc, lane * 4, 0, 0);
         s[j] = scales_in[(int64_t)j * meta_stride + gi];
-        z[j] = zeros_in[(int64_t)j * meta_stride + gi];
+        z[j] = CODEC == kAsym ? zeros_in[(int64_t)j * meta_stride + gi] : 0.0f;
     }
 
     float acc[E];
 #pragma unroll
     for (int i = 0; i < E; ++i) acc[i] = 0.0f;
 #pragma unroll
-    for (int j = 0; j < NSRC; ++j)
+    for (int j = 0; j < NSRC; ++j) {
+        if constexpr (CODEC == kAsymH) unpack_meta(__builtin_bit_cast(u32, s[j]), s[j], z[j]);
+        float d[E];
+        small_decode<CODEC, BITS_IN>(w[j], z[j], d);
 #pragma unroll
-        for (int i = 0; i < E; ++i) {
-            const float d = (float)((w[j] >> (BITS_IN * i)) & kMask) - z[j];
-            acc[i] = fmaf(d, s[j], acc[i]);
-        }
+        for (int i = 0; i < E; ++i) acc[i] = fmaf(d[i], s[j], acc[i]);
+    }
 
-    float mn, mx, s2, inv, zf;
-    lane_minmax(acc, mn, mx);
-    group_minmax<0>(mn, mx, lpg);
-    group_params<BITS_OUT>(mn, mx, s2, inv, zf);
+    float s2, inv, zf = 0.0f;
     uint64_t packed = 0;
+    if constexpr (is_asym(CODEC)) {
+        float mn, mx;
+        lane_minmax(acc, mn, mx);
+        group_minmax<0>(mn, mx, lpg);
+        group_params<BITS_OUT, CODEC == kAsymH>(mn, mx, s2, inv, zf);
 #pragma unroll
-    for (int i = 0; i < E; ++i) packed |= (uint64_t)encode<BITS_OUT>(acc[i], inv, zf) << (BITS_OUT * i);
+        for (int i = 0; i < E; ++i) packed |= (uint64_t)encode<BITS_OUT>(acc[i], inv, zf) << (BITS_OUT * i);
+    } else {
+        const float amax = group_max<0>(lane_absmax(acc), lpg);
+        if constexpr (CODEC == kFp8) {
+            group_params_absmax<448>(amax, s2, inv);
+            u32 word[1];
+            pack_lane_fp8<4>(acc, inv, word);
+            packed = word[0];
+        } else {
+            group_params_sym<BITS_OUT>(amax, s2, inv);          // neither clamp of Eq. 4 can act (see pack_lane_sym)
+#pragma unroll
+            for (int i = 0; i < E; ++i)
+                packed |= (uint64_t)((u32)(int)rintf(acc[i] * inv) & ((1u << BITS_OUT) - 1u)) << (BITS_OUT * i);
+        }
+    }
 
     const rsrc_t ro = make_rsrc(codes_out + e_wave * BITS_OUT / 8, (n_elems - e_wave) * BITS_OUT / 8);
     if constexpr (kOutBytes == 8)
@@ -83,8 +123,8 @@ __global__ __launch_bounds__(64) void k_fused_small(
     else
         __builtin_amdgcn_raw_buffer_store_b16((uint16_t)packed, ro, lane * 2, 0, 0);
     if (live && (lane & (u32)(lpg - 1)) == 0) {
-        scales_out[g_mine] = s2;
-        zeros_out[g_mine] = zf;
+        scales_out[g_mine] = CODEC == kAsymH ? __builtin_bit_cast(float, pack_meta(s2, zf)) : s2;
+        if constexpr (CODEC == kAsym) zeros_out[g_mine] = zf;
     }
 }
 

@@ -87,12 +87,12 @@ hipError_t launch_dequantize_rot(int bits, int codec, const void *codes, const f
 hipError_t launch_allreduce_rot(int codec, int bits_rs, int bits_ag, const void *x_f16, int n_src, int64_t tokens,
                                 int hidden, int group, void *y_f16, hipStream_t stream);
 
-// fc_small.hip: the whole all-reduce (asymmetric quantizer, fp32 metadata) in one launch, for launch-bound
-// volumes: at most kSmallAllreduceMaxElems elements per partial and groups of at most 512 elements.
+// fc_small.hip: the whole all-reduce in one launch, for launch-bound volumes: at most kSmallAllreduceMaxElems elements
+// per partial, six times that over all partials, and groups of at most 512 elements.
 constexpr int64_t kSmallAllreduceMaxElems = (int64_t)1 << 20;
-bool allreduce_small_applies(int64_t n_elems, int group);
-hipError_t launch_allreduce_small(int bits_rs, int bits_ag, const void *x_f16, int n_src, int64_t n_elems, int group,
-                                  void *y_f16, hipStream_t stream);
+bool allreduce_small_applies(int n_src, int64_t n_elems, int group);
+hipError_t launch_allreduce_small(int codec, int bits_rs, int bits_ag, const void *x_f16, int n_src, int64_t n_elems,
+                                  int group, void *y_f16, hipStream_t stream);
 
 // fc_sim.hip (one translation unit per quantizer): the same in one launch for volumes that memory bandwidth bounds
 // (the N binary16 partials are read once, the binary16 result is written once, nothing else touches memory);

@@ -27,7 +27,44 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 constexpr int kSmallLaneElems = 8;
 constexpr int kSmallWaveElems = 64 * kSmallLaneElems;
 
-template <int BITS_RS, int BITS_AG, int NSRC>
+// FinegrainedQuantize of the lane's values and the inverse of Eq. 2 without its scale: d = q - z (the signed code, the value
+// of the E4M3 byte).  +0 is added to a signed code: the stored integer has no -0.
+template <int CODEC, int BITS>
+__device__ __forceinline__ void small_codes(const float (&v)[kSmallLaneElems], int lpg, float &s, float (&d)[kSmallLaneElems])
+{
+    constexpr int E = kSmallLaneElems;
+    float inv;
+    if constexpr (is_asym(CODEC)) {
+        float mn, mx, zf;
+        lane_minmax(v, mn, mx);
+        group_minmax<0>(mn, mx, lpg);
+        group_params<BITS, CODEC == kAsymH>(mn, mx, s, inv, zf);
+#pragma unroll
+        for (int i = 0; i < E; ++i) d[i] = (float)encode<BITS>(v[i], inv, zf) - zf;
+    } else {
+        const float amax = group_max<0>(lane_absmax(v), lpg);
+        if constexpr (CODEC == kFp8) {
+            group_params_absmax<448>(amax, s, inv);
+            u32 word[E / 4];
+            pack_lane_fp8<E>(v, inv, word);
+#pragma unroll
+            for (int k = 0; k < E / 4; ++k) {
+                const f32x2 lo = __builtin_amdgcn_cvt_pk_f32_fp8((int)word[k], false);
+                const f32x2 hi = __builtin_amdgcn_cvt_pk_f32_fp8((int)word[k], true);
+                d[4 * k + 0] = lo.x;
+                d[4 * k + 1] = lo.y;
+                d[4 * k + 2] = hi.x;
+                d[4 * k + 3] = hi.y;
+            }
+        } else {
+            group_params_sym<BITS>(amax, s, inv);
+#pragma unroll
+            for (int i = 0; i < E; ++i) d[i] = rintf(v[i] * inv) + 0.0f;
+        }
+    }
+}
+
+template <int CODEC, int BITS_RS, int BITS_AG, int NSRC>
 __global__ __launch_bounds__(64 * NSRC) void k_allreduce_small(const uint16_t *__restrict__ x, int64_t n_elems, int lpg,
                                                               uint16_t *__restrict__ y)
 {
@@ -51,13 +88,8 @@ __global__ __launch_bounds__(64 * NSRC) void k_allreduce_small(const uint16_t *_
             v[2 * k] = (float)p.x;
             v[2 * k + 1] = (float)p.y;
         }
-        float mn, mx, s, inv, zf;
-        lane_minmax(v, mn, mx);
-        group_minmax<0>(mn, mx, lpg);
-        group_params<BITS_RS>(mn, mx, s, inv, zf);
-        float d[E];
-#pragma unroll
-        for (int i = 0; i < E; ++i) d[i] = (float)encode<BITS_RS>(v[i], inv, zf) - zf;      // Dequantize: q - z
+        float s, d[E];
+        small_codes<CODEC, BITS_RS>(v, lpg, s, d);
         if constexpr (NSRC > 1) {
             f32x4 *mine = reinterpret_cast<f32x4 *>(&diff[j][lane][0]);
             mine[0] = f32x4{d[0], d[1], d[2], d[3]};
@@ -87,16 +119,14 @@ __global__ __launch_bounds__(64 * NSRC) void k_allreduce_small(const uint16_t *_
             for (int i = 0; i < E; ++i) acc[i] = fmaf(d[i], s, acc[i]);
         }
 
-        float mn2, mx2, s2, inv2, zf2;
-        lane_minmax(acc, mn2, mx2);
-        group_minmax<0>(mn2, mx2, lpg);
-        group_params<BITS_AG>(mn2, mx2, s2, inv2, zf2);
+        float s2, d2[E];
+        small_codes<CODEC, BITS_AG>(acc, lpg, s2, d2);
         u32x4 out;
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
             h2 p;
-            p.x = (_Float16)(((float)encode<BITS_AG>(acc[2 * k], inv2, zf2) - zf2) * s2);
-            p.y = (_Float16)(((float)encode<BITS_AG>(acc[2 * k + 1], inv2, zf2) - zf2) * s2);
+            p.x = (_Float16)(d2[2 * k] * s2);
+            p.y = (_Float16)(d2[2 * k + 1] * s2);
             out[k] = as_u32(p);
         }
         const rsrc_t ry = make_rsrc(y + e_tile, left);
@@ -104,39 +134,67 @@ __global__ __launch_bounds__(64 * NSRC) void k_allreduce_small(const uint16_t *_
     }
 }
 
-template <int BITS_RS, int BITS_AG>
+template <int CODEC, int BITS_RS, int BITS_AG, int NSRC>
+static hipError_t launch_small_one(const uint16_t *x, int64_t n_elems, int group, uint16_t *y, hipStream_t stream)
+{
+    return launch_kernel(k_allreduce_small<CODEC, BITS_RS, BITS_AG, NSRC>,
+                         dim3((unsigned)((n_elems + kSmallWaveElems - 1) / kSmallWaveElems)), dim3(64 * NSRC), stream, x,
+                         n_elems, group / kSmallLaneElems, y);
+}
+
+template <int CODEC, int BITS_RS, int BITS_AG>
 static hipError_t launch_small_bits(const uint16_t *x, int n_src, int64_t n_elems, int group, uint16_t *y, hipStream_t stream)
 {
-    const dim3 grid((unsigned)((n_elems + kSmallWaveElems - 1) / kSmallWaveElems));
-    const int lpg = group / kSmallLaneElems;
     switch (n_src) {
-    case 1: return launch_kernel(k_allreduce_small<BITS_RS, BITS_AG, 1>, grid, dim3(64 * 1), stream, x, n_elems, lpg, y);
-    case 2: return launch_kernel(k_allreduce_small<BITS_RS, BITS_AG, 2>, grid, dim3(64 * 2), stream, x, n_elems, lpg, y);
-    case 3: return launch_kernel(k_allreduce_small<BITS_RS, BITS_AG, 3>, grid, dim3(64 * 3), stream, x, n_elems, lpg, y);
-    case 4: return launch_kernel(k_allreduce_small<BITS_RS, BITS_AG, 4>, grid, dim3(64 * 4), stream, x, n_elems, lpg, y);
-    case 5: return launch_kernel(k_allreduce_small<BITS_RS, BITS_AG, 5>, grid, dim3(64 * 5), stream, x, n_elems, lpg, y);
-    case 6: return launch_kernel(k_allreduce_small<BITS_RS, BITS_AG, 6>, grid, dim3(64 * 6), stream, x, n_elems, lpg, y);
-    case 7: return launch_kernel(k_allreduce_small<BITS_RS, BITS_AG, 7>, grid, dim3(64 * 7), stream, x, n_elems, lpg, y);
-    case 8: return launch_kernel(k_allreduce_small<BITS_RS, BITS_AG, 8>, grid, dim3(64 * 8), stream, x, n_elems, lpg, y);
+    case 1: return launch_small_one<CODEC, BITS_RS, BITS_AG, 1>(x, n_elems, group, y, stream);
+    case 2: return launch_small_one<CODEC, BITS_RS, BITS_AG, 2>(x, n_elems, group, y, stream);
+    case 3: return launch_small_one<CODEC, BITS_RS, BITS_AG, 3>(x, n_elems, group, y, stream);
+    case 4: return launch_small_one<CODEC, BITS_RS, BITS_AG, 4>(x, n_elems, group, y, stream);
+    case 5: return launch_small_one<CODEC, BITS_RS, BITS_AG, 5>(x, n_elems, group, y, stream);
+    case 6: return launch_small_one<CODEC, BITS_RS, BITS_AG, 6>(x, n_elems, group, y, stream);
+    case 7: return launch_small_one<CODEC, BITS_RS, BITS_AG, 7>(x, n_elems, group, y, stream);
+    case 8: return launch_small_one<CODEC, BITS_RS, BITS_AG, 8>(x, n_elems, group, y, stream);
     default: return hipErrorInvalidValue;
     }
 }
 
-bool allreduce_small_applies(int64_t n_elems, int group)
+template <int CODEC>
+static hipError_t launch_small_codec(int bits_rs, int bits_ag, const uint16_t *x, int n_src, int64_t n_elems, int group,
+                                     uint16_t *y, hipStream_t stream)
 {
-    return group <= kSmallWaveElems && n_elems <= kSmallAllreduceMaxElems;
+    if constexpr (CODEC == kFp8) {
+        return launch_small_bits<kFp8, 8, 8>(x, n_src, n_elems, group, y, stream);
+    } else {
+        if (bits_rs == 4)
+            return bits_ag == 4 ? launch_small_bits<CODEC, 4, 4>(x, n_src, n_elems, group, y, stream)
+                                : launch_small_bits<CODEC, 4, 8>(x, n_src, n_elems, group, y, stream);
+        return bits_ag == 4 ? launch_small_bits<CODEC, 8, 4>(x, n_src, n_elems, group, y, stream)
+                            : launch_small_bits<CODEC, 8, 8>(x, n_src, n_elems, group, y, stream);
+    }
 }
 
-hipError_t launch_allreduce_small(int bits_rs, int bits_ag, const void *x_f16, int n_src, int64_t n_elems, int group,
-                                  void *y_f16, hipStream_t stream)
+// Where the two forms cross (hidden 8192, g = 128, us per launch under graph replay, bulk / this one): N = 8 partials of 8
+// tokens or fewer, symmetric 4.1 / 2.4; 32 tokens, asymmetric 4.77 / 3.57, symmetric 4.43 / 3.19, FP8 4.85 / 3.18, compact
+// metadata 4.60 / 3.58; 96 tokens 6.46 / 5.88, 5.71 / 5.08, 6.34 / 5.09, 6.42 / 5.91; 128 tokens, symmetric 6.11 / 6.30, compact
+// metadata 6.77 / 7.24.  N = 4 at 128 tokens 4.86 / 4.65, 4.36 / 4.12, 4.70 / 4.10, 4.72 / 4.63, at 160 tokens equal; N = 1 at 128
+// tokens equal.  Hence at most 2^20 elements per partial and 12 wavefronts per SIMD over all partials.
+bool allreduce_small_applies(int n_src, int64_t n_elems, int group)
+{
+    return group <= kSmallWaveElems && n_elems <= kSmallAllreduceMaxElems && n_src * n_elems <= 6 * kSmallAllreduceMaxElems;
+}
+
+hipError_t launch_allreduce_small(int codec, int bits_rs, int bits_ag, const void *x_f16, int n_src, int64_t n_elems,
+                                  int group, void *y_f16, hipStream_t stream)
 {
     const uint16_t *x = static_cast<const uint16_t *>(x_f16);
     uint16_t *y = static_cast<uint16_t *>(y_f16);
-    if (bits_rs == 4)
-        return bits_ag == 4 ? launch_small_bits<4, 4>(x, n_src, n_elems, group, y, stream)
-                            : launch_small_bits<4, 8>(x, n_src, n_elems, group, y, stream);
-    return bits_ag == 4 ? launch_small_bits<8, 4>(x, n_src, n_elems, group, y, stream)
-                        : launch_small_bits<8, 8>(x, n_src, n_elems, group, y, stream);
+    switch (codec) {
+    case CODEC_ASYM: return launch_small_codec<kAsym>(bits_rs, bits_ag, x, n_src, n_elems, group, y, stream);
+    case CODEC_SYM: return launch_small_codec<kSym>(bits_rs, bits_ag, x, n_src, n_elems, group, y, stream);
+    case CODEC_FP8: return launch_small_codec<kFp8>(bits_rs, bits_ag, x, n_src, n_elems, group, y, stream);
+    case CODEC_ASYMH: return launch_small_codec<kAsymH>(bits_rs, bits_ag, x, n_src, n_elems, group, y, stream);
+    default: return hipErrorInvalidValue;
+    }
 }
 
 }  // namespace fc

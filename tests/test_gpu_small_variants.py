@@ -1,0 +1,87 @@
+"""The launch-bound kernels of the symmetric, FP8 and compact-metadata quantizers (fused step and one-launch all-reduce),
+on both sides of their size limit: a case as given, and the same case with its token rows repeated up to the bulk kernels'
+volumes.  Both must give the oracle's bits.  Run with ``-m gpu`` on an MI355X."""
+import numpy as np
+import pytest
+
+import oracle
+import synth_inputs
+from test_gpu_parity import BULK_ELEMS, Guarded, bulk_reps, dev, fc, first_diff, same_bits, tile_tokens  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+PAIRS = {"sym": [(4, 4), (4, 8), (8, 4), (8, 8)], "cmeta": [(4, 4), (4, 8), (8, 4), (8, 8)], "fp8": [(8, 8)]}
+SHAPES = [(7, 2176, 128), (1, 32, 32), (3, 1056, 32), (5, 2048, 64), (2, 4096, 256), (3, 1536, 512), (31, 8192, 128)]
+
+
+def wire(name, n_src, tokens, hidden, group, bits, seed):
+    """codes and metadata of every source: quantized rows in the first source, arbitrary legal ones in the others"""
+    rng = np.random.default_rng(seed)
+    x = synth_inputs.make_partials_stress(n_src, tokens, hidden, seed % synth_inputs.STRESS_KINDS, seed=seed)
+    q = {"sym": lambda r: oracle.quantize_sym(r, group, bits), "fp8": lambda r: oracle.quantize_fp8(r, group),
+         "cmeta": lambda r: oracle.quantize_cmeta(r, group, bits)}[name]
+    parts = [q(x[j]) for j in range(n_src)]
+    c = np.stack([p[0] for p in parts])
+    m = np.stack([p[1] for p in parts])
+    for j in range(1, n_src, 2):
+        c[j] = rng.integers(0, 256, size=c[j].shape, dtype=np.uint8)          # every code, -2^(n-1) included
+        if name == "fp8":
+            c[j][(c[j] & 0x7F) == 0x7F] = 0x7E                                # no NaN bytes
+        if name != "cmeta":
+            m[j] = np.exp(rng.uniform(-100, 60, size=m[j].shape)).astype(np.float32)
+    return c, m
+
+
+@pytest.mark.parametrize("name", list(PAIRS))
+@pytest.mark.parametrize("n_src", [1, 2, 3, 5, 8])
+def test_fused_small_and_bulk(fc, name, n_src):
+    ref = getattr(oracle, "dequant_reduce_requant_" + name)
+    gpu = getattr(fc, "dequant_reduce_requant_" + name)
+    meta_type = torch.int32 if name == "cmeta" else torch.float32
+    for bits_in, bits_out in PAIRS[name]:
+        for k, (t, h, g) in enumerate(SHAPES):
+            bits = () if name == "fp8" else (bits_in, bits_out)
+            c, m = wire(name, n_src, t, h, g, bits_in, seed=10 * n_src + k)
+            want = ref(c, m, h, g, *bits)
+            for reps in (1, bulk_reps(t, h)):
+                if reps > 1 and (k % 3 or t * h < 1024):
+                    continue                                                  # the bulk kernels on every third shape
+                cr, mr = tile_tokens(c, reps), tile_tokens(m, reps)
+                co = Guarded((t * reps, h * bits_out // 8), torch.uint8)
+                mo = Guarded((t * reps, h // g), meta_type)
+                gpu(dev(cr), dev(mr.view(np.int32)) if name == "cmeta" else dev(mr), h, g, *bits, out=(co.t, mo.t))
+                torch.cuda.synchronize()
+                for part, got, w in zip(("codes", "metadata"), (co, mo), want):
+                    got.check()
+                    a = got.t.cpu().numpy()
+                    b = tile_tokens(w, reps)
+                    assert same_bits(a.view(np.uint8), b.view(np.uint8)), "%s N=%d %dx%d g=%d %d->%d x%d %s: %s" % (
+                        name, n_src, t, h, g, bits_in, bits_out, reps, part, first_diff(a.view(np.uint8), b.view(np.uint8)))
+
+
+@pytest.mark.parametrize("name", list(PAIRS))
+@pytest.mark.parametrize("n_src", [1, 2, 4, 7, 8])
+def test_allreduce_small_and_bulk(fc, name, n_src):
+    ref, gpu = getattr(oracle, "allreduce_sim_" + name), getattr(fc, "allreduce_sim_" + name)
+    for bits_rs, bits_ag in PAIRS[name]:
+        for k, (t, h, g) in enumerate(SHAPES):
+            bits = () if name == "fp8" else (bits_rs, bits_ag)
+            x = synth_inputs.make_partials_stress(n_src, t, h, (k + n_src) % synth_inputs.STRESS_KINDS, seed=k + 50 * n_src)
+            if k == 0:
+                x[:, 0] = -0.0                                                # groups of negative zeros
+                x[0, 1, ::2] = np.float16(-0.0)
+            want = ref(x, g, *bits)
+            for reps in (1, bulk_reps(t, h)):
+                if reps > 1 and (k % 3 or t * h < 1024):
+                    continue
+                xr = tile_tokens(x, reps)
+                assert (xr[0].size > BULK_ELEMS) == (reps > 1)
+                y = Guarded((t * reps, h), torch.float16)
+                gpu(dev(xr.view(np.uint16)).view(torch.float16), g, *bits, out=y.t)
+                torch.cuda.synchronize()
+                y.check()
+                a, b = y.t.cpu().numpy().view(np.uint16), tile_tokens(want, reps).view(np.uint16)
+                assert same_bits(a, b), "%s N=%d %dx%d g=%d %d->%d x%d: %s" % (name, n_src, t, h, g, bits_rs, bits_ag, reps,
+                                                                              first_diff(a, b))
