@@ -1016,6 +1016,44 @@ __device__ __forceinline__ void accumulate_fast(const u32 (&w)[4], float s, cons
     }
 }
 
+// The same for 4-bit codes by fp32 operations alone, which issue in 2 cycles where packed binary16, v_and_or and
+// v_fma_mix take 4 (224 cycles per source and lane of 32 codes instead of 272).  A word with one nibble kept at bit
+// 4k reads, as fp32, q * 2^(4k - 149): the encoding is linear below bit 24, subnormals included, and gfx950 multiplies
+// subnormals at full rate.  fma(that, 2^127, -z * 2^(4k - 22)) is then (q - z) * 2^(4k - 22), exact for the integers of
+// zero_is_fast, and the scale carries the other half of the factor: its products with the scale times 2^(22 - 4k) are
+// those of q - z with the scale, so the accumulation rounds the same numbers.  Needs |s| * 2^22 finite (scale_is_large_mask).
+template <int N>
+__device__ __forceinline__ void accumulate_nibbles(const u32 (&w)[4], float s, float zf, float (&acc)[N])
+{
+    static_assert(N == 32, "a lane's 128 bits of 4-bit codes");
+    constexpr float kUp = 0x1p127f;
+    float sk[4], zk[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        sk[k] = s * __builtin_bit_cast(float, (u32)(127 + 22 - 4 * k) << 23);
+        zk[k] = zf * __builtin_bit_cast(float, (u32)(127 - 22 + 4 * k) << 23);
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        u32 hi;                                               // spelled out: folded into the masks, the shift makes them
+        asm("v_lshrrev_b32 %0, 16, %1" : "=v"(hi) : "v"(w[i]));  // SDWA forms of 4 cycles each
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const float lo_d = fmaf(__builtin_bit_cast(float, w[i] & (0xFu << (4 * k))), kUp, -zk[k]);
+            const float hi_d = fmaf(__builtin_bit_cast(float, hi & (0xFu << (4 * k))), kUp, -zk[k]);
+            acc[8 * i + k] = fmaf(lo_d, sk[k], acc[8 * i + k]);
+            acc[8 * i + 4 + k] = fmaf(hi_d, sk[k], acc[8 * i + 4 + k]);
+        }
+    }
+}
+
+// lanes whose scale accumulate_nibbles cannot take (2^104 and more, infinities, NaN)
+__device__ __forceinline__ uint64_t scale_is_large_mask(float s)
+{
+    constexpr int kUge = 11;                                  // unordered-or: not less
+    return __builtin_amdgcn_fcmpf(fabsf(s), 0x1p104f, kUge);
+}
+
 template <int BITS>
 __device__ __forceinline__ void accumulate_general(const u32 (&w)[4], float s, float zf,
                                                    float (&acc)[128 / BITS])
@@ -1137,7 +1175,12 @@ __global__ __launch_bounds__(BT) void k_dequant_reduce_requant(
     constexpr int entries = NSRC * gw;
     constexpr bool kSpansWaves = LPG > 64;                    // a group takes more than one wavefront
     constexpr int K = (entries + 63) / 64;                    // table entries per lane
-    struct MetaRec { float s; u32 z; };                       // z: packed halves (fast) or fp32 bits
+    // 4-bit codes, up to 4 sources: accumulate_nibbles.  It has more instructions of fewer cycles, which pays while 8
+    // wavefronts share a SIMD; landing zones and registers leave fewer from 5 sources on.  8192 x 8192, INT4, us before
+    // and after, g = 128 / 1024: N = 2 24.4 -> 22.3 / 22.4 -> 21.3, N = 4 32.5 -> 31.1 / 32.6 -> 31.4, but N = 5
+    // 39.4 -> 40.7 / 38.8 -> 38.4, N = 6 44.3 -> 46.4 / 43.9 -> 44.8, N = 8 55.2 -> 58.7 / 53.9 -> 55.9.
+    constexpr bool kNibbles = BITS_IN == 4 && NSRC <= 4;
+    struct MetaRec { float s; u32 z; };                       // z: fp32 bits; packed halves for accumulate_fast
 
     __shared__ __attribute__((aligned(16))) uint8_t landing[kWaves][NSRC][1024];
     __shared__ MetaRec meta[LPG >= 8 ? 1 : kWaves][LPG >= 8 ? 1 : entries];
@@ -1183,8 +1226,10 @@ __global__ __launch_bounds__(BT) void k_dequant_reduce_requant(
         for (int j = 0; j < NSRC; ++j) issue_source(j);
         issue_order_fence();
         if constexpr (HM) unpack_meta(__builtin_bit_cast(u32, es), es, ez);
-        all_fast = zero_is_slow_mask(ez) == 0;
-        const u32 ezc = all_fast ? pack_zero_const(ez) : __builtin_bit_cast(u32, ez);
+        uint64_t slow = zero_is_slow_mask(ez);
+        if constexpr (kNibbles && !HM) slow |= scale_is_large_mask(es);
+        all_fast = slow == 0;
+        const u32 ezc = !kNibbles && all_fast ? pack_zero_const(ez) : __builtin_bit_cast(u32, ez);
         const u32 mine = ((LPG >= 64 ? 0u : lane / (u32)LPG)) * 4u;   // byte index of entry (0, my group)
 #pragma unroll
         for (int j = 0; j < NSRC; ++j) {
@@ -1222,7 +1267,10 @@ __global__ __launch_bounds__(BT) void k_dequant_reduce_requant(
         }
         uint64_t slow = 0;
 #pragma unroll
-        for (int it = 0; it < K; ++it) slow |= zero_is_slow_mask(mz[it]);
+        for (int it = 0; it < K; ++it) {
+            slow |= zero_is_slow_mask(mz[it]);
+            if constexpr (kNibbles && !HM) slow |= scale_is_large_mask(ms[it]);
+        }
         all_fast = slow == 0;
 #pragma unroll
         for (int it = 0; it < K; ++it) {
@@ -1230,7 +1278,7 @@ __global__ __launch_bounds__(BT) void k_dequant_reduce_requant(
             if (idx < entries) {
                 MetaRec r;
                 r.s = ms[it];
-                r.z = all_fast ? pack_zero_const(mz[it]) : __builtin_bit_cast(u32, mz[it]);
+                r.z = !kNibbles && all_fast ? pack_zero_const(mz[it]) : __builtin_bit_cast(u32, mz[it]);
                 meta[wave][idx] = r;
             }
         }
@@ -1256,9 +1304,12 @@ __global__ __launch_bounds__(BT) void k_dequant_reduce_requant(
                 r = my_meta[j * gw];
             lds_read_complete(a);
             const u32 w[4] = {a[0], a[1], a[2], a[3]};
-            if constexpr (decltype(fast_tag)::value)
-                accumulate_fast<BITS_IN>(w, r.s, unpack_zero_const(r.z), acc);
-            else
+            if constexpr (decltype(fast_tag)::value) {
+                if constexpr (kNibbles)
+                    accumulate_nibbles(w, r.s, __builtin_bit_cast(float, r.z), acc);
+                else
+                    accumulate_fast<BITS_IN>(w, r.s, unpack_zero_const(r.z), acc);
+            } else
                 accumulate_general<BITS_IN>(w, r.s, __builtin_bit_cast(float, r.z), acc);
             pin_values(acc);          // source j is folded in before source j+1 is waited for
         }

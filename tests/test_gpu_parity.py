@@ -246,6 +246,25 @@ def test_fused_extreme_scales(fc, bits_in):
         assert same_bits(got.view(np.uint16), y.view(np.uint16)), "extreme scales, dequantize"
 
 
+@pytest.mark.parametrize("n_src,group", [(1, 128), (2, 1024), (3, 32), (4, 128), (4, 8192), (5, 128)])
+@pytest.mark.parametrize("scale", [1.4e-45, 1e-40, 2.0 ** 104 * (1 - 2.0 ** -24), 2.0 ** 104, 2.0 ** 115, -3.5])
+def test_fused_scales_around_the_exponent_limit(fc, n_src, group, scale):
+    # 4-bit codes are dequantized with part of the exponent moved into the scale: the largest scale that may take it,
+    # the first that may not, subnormal and negative ones; every nibble position, zero-points at both ends of the
+    # short path; the most sources that take it and one more.  Ordinary rows meet general ones in the same launch.
+    rng = np.random.default_rng(16)
+    t, h = 5, 8192
+    c = rng.integers(0, 256, size=(n_src, t, h // 2), dtype=np.uint8)
+    s = np.full((n_src, t, h // group), scale, np.float32)
+    s[:, 2] = rng.uniform(0.01, 2.0, size=s[:, 2].shape).astype(np.float32)
+    z = np.rint(rng.uniform(-20, 30, size=s.shape)).astype(np.float32)
+    z[0, 0], z[0, 1], z[-1, 3], z[-1, 4] = -1700.0, 1000.0, -0.0, 0.0
+    for bits_out in (4, 8):
+        want = oracle.dequant_reduce_requant(c, s, z, h, group, 4, bits_out)
+        assert np.isfinite(want[1]).all()
+        assert_triplet(gpu_fused(fc, c, s, z, h, group, 4, bits_out), want, "scale %g -> %d" % (scale, bits_out))
+
+
 def test_fused_adversarial_sums(fc):
     # sums that are constant, zero, or nearly constant on a large offset
     group = 128
