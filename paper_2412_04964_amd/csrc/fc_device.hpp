@@ -1178,7 +1178,9 @@ __global__ __launch_bounds__(BT) void k_dequant_reduce_requant(
     // 4-bit codes, up to 4 sources: accumulate_nibbles.  It has more instructions of fewer cycles, which pays while 8
     // wavefronts share a SIMD; landing zones and registers leave fewer from 5 sources on.  8192 x 8192, INT4, us before
     // and after, g = 128 / 1024: N = 2 24.4 -> 22.3 / 22.4 -> 21.3, N = 4 32.5 -> 31.1 / 32.6 -> 31.4, but N = 5
-    // 39.4 -> 40.7 / 38.8 -> 38.4, N = 6 44.3 -> 46.4 / 43.9 -> 44.8, N = 8 55.2 -> 58.7 / 53.9 -> 55.9.
+    // 39.4 -> 40.7 / 38.8 -> 38.4, N = 6 44.3 -> 46.4 / 43.9 -> 44.8, N = 8 55.2 -> 58.7 / 53.9 -> 55.9.  Between other
+    // kernels (bench.py, N = 4, g = 128) the times spread more: fastest step 30.1 -> 29.7, median 30.71 -> 30.64, but
+    // one step in twenty takes 33 to 37 us, cause not found, and the mean goes from 30.77 to 31.02.
     constexpr bool kNibbles = BITS_IN == 4 && NSRC <= 4;
     struct MetaRec { float s; u32 z; };                       // z: fp32 bits; packed halves for accumulate_fast
 
