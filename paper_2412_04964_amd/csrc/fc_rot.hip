@@ -85,14 +85,17 @@ __global__ __launch_bounds__(64 * rot_group_waves(LB)) void k_quantize_rot(
     const u32 wave = (u32)__builtin_amdgcn_readfirstlane((int)(tid >> 6));
     const RotLane L = rot_lane<FP8>(lane);
     const int64_t e_tile = (int64_t)blockIdx.x * kTile;
-    const int64_t left = n_elems - e_tile;
+    const int64_t e_begin = rot_begin<LB>(e_tile, wave);
+    const int64_t left = n_elems - e_begin;
 
     u32x4 raw[4];
-    const rsrc_t rx = make_rsrc(x + e_tile, left * 2);
+    const rsrc_t rx = make_rsrc(x + e_begin, left * 2);
+    const u32 in_at = rot_lane_offset(kRotLoaded, L) * 2;
 #pragma unroll
-    for (u32 p = 0; p < 4; ++p)
-        raw[p] = __builtin_amdgcn_raw_buffer_load_b128(rx, rot_lane_offset(kRotLoaded, L) * 2,
-                                                       rot_piece_offset(kRotLoaded, wave, p) * 2, kStreamLoadPolicy);
+    for (u32 p = 0; p < 4; ++p) {
+        const RotAt at = rot_at<LB>(in_at, kRotLoaded, wave, p, 16);
+        raw[p] = __builtin_amdgcn_raw_buffer_load_b128(rx, at.vec, at.scalar, kStreamLoadPolicy);
+    }
     float v[4][8];
 #pragma unroll
     for (int p = 0; p < 4; ++p)
@@ -147,15 +150,15 @@ __global__ __launch_bounds__(64 * rot_group_waves(LB)) void k_quantize_rot(
     constexpr RotMap out = {7, 8, done.l4 == 7 ? done.p0 : done.l4, done.l5 == 8 ? done.p1 : done.l5, done.w0, done.w1};
     if constexpr (done.l4 != 7) rot_swap_words<4>(word);
     if constexpr (done.l5 != 8) rot_swap_words<5>(word);
-    const rsrc_t rc = make_rsrc(codes + e_tile * BITS / 8, left * BITS / 8);
+    const rsrc_t rc = make_rsrc(codes + e_begin * BITS / 8, left * BITS / 8);
     const u32 lane_at = rot_lane_offset(out, L) * BITS / 8;
 #pragma unroll
     for (u32 p = 0; p < 4; ++p) {
-        const u32 at = rot_piece_offset(out, wave, p) * BITS / 8;
+        const RotAt at = rot_at<LB>(lane_at, out, wave, p, BITS);
         if constexpr (BITS == 4)
-            __builtin_amdgcn_raw_buffer_store_b32(word[p][0], rc, lane_at, at, kStreamStorePolicy);
+            __builtin_amdgcn_raw_buffer_store_b32(word[p][0], rc, at.vec, at.scalar, kStreamStorePolicy);
         else
-            __builtin_amdgcn_raw_buffer_store_b64(u32x2{word[p][0], word[p][1]}, rc, lane_at, at, kStreamStorePolicy);
+            __builtin_amdgcn_raw_buffer_store_b64(u32x2{word[p][0], word[p][1]}, rc, at.vec, at.scalar, kStreamStorePolicy);
     }
     // the lane whose quad begins the group in its piece stores the group's metadata
     const u32 e_quad = rot_quad_offset(done, L, wave);
@@ -242,12 +245,13 @@ __global__ __launch_bounds__(64 * rot_group_waves(LB)) __attribute__((amdgpu_wav
     const u32 wave = (u32)__builtin_amdgcn_readfirstlane((int)(tid >> 6));
     const RotLane L = rot_lane<FP8>(lane);
     const int64_t e_tile = (int64_t)blockIdx.x * kTile;
-    const int64_t left = n_elems - e_tile;
+    const int64_t e_begin = rot_begin<LB>(e_tile, wave);
+    const int64_t left = n_elems - e_begin;
     const int64_t g_tile = e_tile >> group_shift, n_groups = n_elems >> group_shift;
 
     const u32 gi = (rot_quad_offset(kRotLoaded, L, wave) >> group_shift) * 4u;
     const rsrc_t rs = make_rsrc(scales + g_tile, (n_groups - g_tile) * 4);
-    const rsrc_t rc = make_rsrc(codes + e_tile * BITS / 8, left * BITS / 8);
+    const rsrc_t rc = make_rsrc(codes + e_begin * BITS / 8, left * BITS / 8);
     const float s = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, gi, 0, 0));
     float zf = 0.0f;
     if constexpr (CODEC == kAsym) {
@@ -258,11 +262,11 @@ __global__ __launch_bounds__(64 * rot_group_waves(LB)) __attribute__((amdgpu_wav
     const u32 lane_at = rot_lane_offset(kRotNatural, L) * BITS / 8;
 #pragma unroll
     for (u32 p = 0; p < 4; ++p) {
-        const u32 at = rot_piece_offset(kRotNatural, wave, p) * BITS / 8;
+        const RotAt at = rot_at<LB>(lane_at, kRotNatural, wave, p, BITS);
         if constexpr (BITS == 4) {
-            word[p][0] = __builtin_amdgcn_raw_buffer_load_b32(rc, lane_at, at, kStreamLoadPolicy);
+            word[p][0] = __builtin_amdgcn_raw_buffer_load_b32(rc, at.vec, at.scalar, kStreamLoadPolicy);
         } else {
-            const u32x2 a = __builtin_amdgcn_raw_buffer_load_b64(rc, lane_at, at, kStreamLoadPolicy);
+            const u32x2 a = __builtin_amdgcn_raw_buffer_load_b64(rc, at.vec, at.scalar, kStreamLoadPolicy);
             word[p][0] = a[0];
             word[p][1] = a[1];
         }
@@ -309,15 +313,16 @@ __global__ __launch_bounds__(64 * rot_group_waves(LB)) __attribute__((amdgpu_wav
 
     constexpr float back = 1.0f / (float)(1 << (LB / 2));               // 2^-floor(n/2), n = LB
     const float plus_zero = exact ? -0.0f : 0.0f;                       // t + -0 is t, t + +0 has no negative zero
-    const rsrc_t ry = make_rsrc(y + e_tile, left * 2);
+    const rsrc_t ry = make_rsrc(y + e_begin, left * 2);
+    const u32 out_at = rot_lane_offset(rot_inverse_map(LB), L) * 2;
 #pragma unroll
     for (u32 p = 0; p < 4; ++p) {
         u32x4 out;
 #pragma unroll
         for (int i = 0; i < 4; ++i)
             out[i] = round_pair(fmaf(v[p][2 * i], back, plus_zero), fmaf(v[p][2 * i + 1], back, plus_zero));
-        store_b128_at(out, ry, rot_lane_offset(rot_inverse_map(LB), L) * 2,
-                      rot_piece_offset(rot_inverse_map(LB), wave, p) * 2);
+        const RotAt at = rot_at<LB>(out_at, rot_inverse_map(LB), wave, p, 16);
+        store_b128_at(out, ry, at.vec, at.scalar);
     }
 }
 

@@ -127,15 +127,20 @@ __global__ __launch_bounds__(64 * rot_group_waves(LB)) __attribute__((amdgpu_wav
     const RotLane L = rot_lane<FP8>(lane);
     const u32 tile = xcd_tile<kChunk>((u32)((n_elems + kTile - 1) / kTile));
     const int64_t e_tile = (int64_t)tile * kTile;
-    const int64_t left = (n_elems - e_tile) * 2;                       // bytes from the tile to the end of a partial
+    const int64_t e_begin = rot_begin<LB>(e_tile, wave);
+    const int64_t left = (n_elems - e_begin) * 2;                      // bytes from there to the end of a partial
 
     u32x4 raw[4];
+    const u32 lane_at = rot_lane_offset(kRotLoaded, L) * 2;
     auto fetch = [&](int j) {
-        const rsrc_t rx = make_rsrc(x + (int64_t)j * n_elems + e_tile, left);
+        u32 in_at = lane_at;
+        asm volatile("" : "+v"(in_at));                                // the pieces' addresses stay out of the loop's registers
+        const rsrc_t rx = make_rsrc(x + (int64_t)j * n_elems + e_begin, left);
 #pragma unroll
-        for (u32 p = 0; p < 4; ++p)
-            raw[p] = __builtin_amdgcn_raw_buffer_load_b128(rx, rot_lane_offset(kRotLoaded, L) * 2,
-                                                           rot_piece_offset(kRotLoaded, wave, p) * 2, kStreamLoadPolicy);
+        for (u32 p = 0; p < 4; ++p) {
+            const RotAt at = rot_at<LB>(in_at, kRotLoaded, wave, p, 16);
+            raw[p] = __builtin_amdgcn_raw_buffer_load_b128(rx, at.vec, at.scalar, kStreamLoadPolicy);
+        }
     };
     constexpr float fwd = 1.0f / (float)(1 << ((LB + 1) / 2));          // 2^-ceil(n/2), n = LB
     constexpr float back = 1.0f / (float)(1 << (LB / 2));               // 2^-floor(n/2)
@@ -178,7 +183,8 @@ __global__ __launch_bounds__(64 * rot_group_waves(LB)) __attribute__((amdgpu_wav
     rot_inverse_row<FP8>(acc, L);
     rot_inverse_back<LB, 1>(acc, L, pieces, wave);
 
-    const rsrc_t ry = make_rsrc(y + e_tile, left);
+    const rsrc_t ry = make_rsrc(y + e_begin, left);
+    const u32 out_at = rot_lane_offset(rot_back_map(LB), L) * 2;
 #pragma unroll
     for (u32 p = 0; p < 4; ++p) {
         u32x4 out;
@@ -187,7 +193,8 @@ __global__ __launch_bounds__(64 * rot_group_waves(LB)) __attribute__((amdgpu_wav
             const float a = acc[p][2 * i], b = acc[p][2 * i + 1];
             out[i] = FP8 ? round_pair(a * back, b * back) : round_pair(fmaf(a, back, 0.0f), fmaf(b, back, 0.0f));
         }
-        store_b128_at(out, ry, rot_lane_offset(rot_back_map(LB), L) * 2, rot_piece_offset(rot_back_map(LB), wave, p) * 2);
+        const RotAt at = rot_at<LB>(out_at, rot_back_map(LB), wave, p, 16);
+        store_b128_at(out, ry, at.vec, at.scalar);
     }
 }
 

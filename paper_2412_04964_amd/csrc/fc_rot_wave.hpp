@@ -75,6 +75,27 @@ __device__ __forceinline__ u32 rot_piece_offset(const RotMap m, u32 wave, u32 p)
 {
     return ((p & 1u) << m.p0) + ((p >> 1) << m.p1) + ((wave & 1u) << m.w0) + ((wave >> 1) << m.w1);
 }
+// Where an access to a piece lies.  The range check of a buffer access compares the vector and the immediate offset with the
+// size of the resource; what it does where the scalar offset alone passes that size is not documented.  Blocks of 4096
+// and 8192 are whole tiles: nothing passes the end, and the piece may go into the scalar offset.  Blocks of 1024 and 2048 lie
+// two wavefronts to a tile, of which the last may hold fewer: there a wavefront's resource begins at its own 2048 elements
+// (rot_begin; size 0 where these lie past the end), the scalar offset is 0 and the piece goes into the immediate offset.
+constexpr bool rot_whole_tiles(int lb) { return lb >= 12; }
+template <int LB>
+__device__ __forceinline__ int64_t rot_begin(int64_t e_tile, u32 wave)
+{
+    return rot_whole_tiles(LB) ? e_tile : e_tile + (int64_t)wave * 2048;
+}
+struct RotAt {
+    u32 vec, scalar;         // byte offsets
+};
+// `lane_at`: rot_lane_offset(m, L) in bytes
+template <int LB>
+__device__ __forceinline__ RotAt rot_at(u32 lane_at, const RotMap m, u32 wave, u32 p, u32 bits)
+{
+    if (rot_whole_tiles(LB)) return RotAt{lane_at, rot_piece_offset(m, wave, p) * bits / 8};
+    return RotAt{lane_at + rot_piece_offset(m, 0, p) * bits / 8, 0};
+}
 // Element where the quad of lanes of this lane begins in piece pos & 3.  Scale and zero-point of that piece's 32 elements
 // are this lane's to load, or to derive and store.
 __device__ __forceinline__ u32 rot_quad_offset(const RotMap m, const RotLane &L, u32 wave)

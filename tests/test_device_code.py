@@ -1,0 +1,75 @@
+"""Properties of the compiled kernels that no run shows reliably, read from the gfx950 code objects of the built libfc.so
+(the AMD assembly of this repository's own sources)."""
+import os
+import re
+import struct
+import subprocess
+
+import pytest
+
+from paper_2412_04964_amd import build
+
+LLVM = os.path.join(os.path.dirname(os.path.dirname(build.HIPCC)), "llvm", "bin")
+BUNDLE = b"__CLANG_OFFLOAD_BUNDLE__"
+
+
+def code_objects(path):
+    """the gfx950 ELF images of the offload bundles in a library"""
+    blob = open(path, "rb").read()
+    at = blob.find(BUNDLE)
+    while at >= 0:
+        n, = struct.unpack_from("<Q", blob, at + 24)
+        entry = at + 32
+        for _ in range(n):
+            offset, size, name_len = struct.unpack_from("<QQQ", blob, entry)
+            name = blob[entry + 24:entry + 24 + name_len]
+            entry += 24 + name_len
+            if build.ARCH.encode() in name and size:
+                yield blob[at + offset:at + offset + size]
+        at = blob.find(BUNDLE, at + 24)
+
+
+@pytest.fixture(scope="module")
+def kernels(tmp_path_factory):
+    """{mangled name: [instruction, ...]} of every kernel of the library"""
+    tool = os.path.join(LLVM, "llvm-objdump")
+    if not os.path.exists(tool):
+        pytest.skip("no llvm-objdump beside the compiler")
+    found = {}
+    folder = tmp_path_factory.mktemp("code")
+    for i, image in enumerate(code_objects(build.LIB)):
+        elf = folder / ("%d.elf" % i)
+        elf.write_bytes(image)
+        text = subprocess.run([tool, "-d", "--no-show-raw-insn", "--no-leading-addr", str(elf)], check=True,
+                              capture_output=True, text=True).stdout
+        body = None
+        for line in text.splitlines():
+            head = re.match(r"(?:[0-9a-f]+ )?<(\S+)>:", line)
+            if head:
+                body = found.setdefault(head.group(1), [])
+            elif body is not None and line.strip():
+                body.append(line.split("//")[0].strip())
+    assert found, "no code object in %s" % build.LIB
+    return found
+
+
+BUFFER = re.compile(r"buffer_(load|store)\S* (?:(?P<data>\S+), )?\S+, s\[\d+:\d+\], (?P<offset>\S+)")
+
+
+def scalar_offset(instruction):
+    """the match of a buffer access whose scalar offset is a register"""
+    m = BUFFER.match(instruction)
+    return m if m and not re.fullmatch(r"-?\d+|0x[0-9a-f]+|off", m.group("offset")) else None
+
+
+def test_partial_rotation_tiles_have_no_scalar_offset(kernels):
+    # The last tile of blocks of 1024 and 2048 may be a partial one, so its accesses lean on the range check, which a
+    # scalar offset is not part of (what it does where that offset alone passes the end is not documented).
+    seen = 0
+    for name, body in kernels.items():
+        if not re.search(r"(quantize|allreduce)_rotI.*ELi1[01]EE", name):
+            continue
+        seen += 1
+        bad = [i for i in body if scalar_offset(i)]
+        assert not bad, "%s: %s" % (name, bad[0])
+    assert seen == 2 * (5 + 5 + 3)                 # two blocks; quantizer and dequantizer with five codes, all-reduce with three

@@ -13,7 +13,7 @@ pytestmark = pytest.mark.gpu
 
 torch = pytest.importorskip("torch")
 
-GUARD = 256       # bytes of poison on each side of every output buffer
+GUARD = 16384     # bytes of poison on each side of every output buffer: the largest tile that one workgroup writes
 POISON = 0xA5
 
 

@@ -118,6 +118,28 @@ def test_allreduce_sim_rot_matches_oracle(fc, quantizer, bits_rs, bits_ag):
                                                       first_diff(got.view(np.uint16), want.view(np.uint16)))
 
 
+@pytest.mark.parametrize("quantizer,bits", QUANTIZERS)
+@pytest.mark.parametrize("tokens,hidden", [(1, 1024), (1, 5120), (3, 2048), (3, 3072)])
+def test_partial_last_tile_stays_inside_the_buffers(fc, quantizer, bits, tokens, hidden):
+    # blocks of 1024 and 2048 lie 4096 elements to a workgroup: here the last one holds 1024 or 2048 (one wavefront has
+    # half of its elements, the other none).  Nothing past the end of codes, metadata and result may be written; the
+    # guard bands reach further than a tile.
+    x = synth_inputs.make_partials(2, tokens, hidden, seed=hidden + tokens)
+    for group in (32, 1024):
+        want = oracle.quantize_rot(x[0], group, bits, quantizer)
+        assert_rot_triplet(gpu_quantize_rot(fc, x[0], group, bits, quantizer), want, quantizer, "h=%d g=%d" % (hidden, group))
+        y = Guarded((tokens, hidden), torch.float16)
+        fc.dequantize_rot(*[dev(a) for a in want], hidden, group, bits, quantizer, out=y.t)
+        torch.cuda.synchronize(); y.check()
+        ref = oracle.dequantize_rot(*want, hidden, group, bits, quantizer)
+        assert same_bits(y.t.cpu().numpy().view(np.uint16), ref.view(np.uint16))
+        y = Guarded((tokens, hidden), torch.float16)
+        fc.allreduce_sim_rot(dev(x.view(np.uint16)).view(torch.float16), group, bits, bits, quantizer, out=y.t)
+        torch.cuda.synchronize(); y.check()
+        ref = oracle.allreduce_sim_rot(x, group, bits, bits, quantizer)
+        assert same_bits(y.t.cpu().numpy().view(np.uint16), ref.view(np.uint16))
+
+
 def test_rot_rejects_unsupported_rows_and_empty_is_noop(fc):
     x = torch.zeros((2, 2560), dtype=torch.float16, device="cuda")           # 5 x 512: blocks below 1024
     with pytest.raises(fc.FcError):
