@@ -219,12 +219,14 @@ def _coded_outputs(device, t, h, group, bits, out, meta):
     if out is None:
         return (torch.empty((t, h * bits // 8), dtype=torch.uint8, device=device),
                 *[torch.empty((t, h // group), dtype=dt, device=device) for dt, _ in meta])
-    if len(out) != 1 + len(meta):
-        raise ValueError("out must hold %d tensors" % (1 + len(meta)))
+    n = 1 + len(meta)
+    # one tuple for checks, call and result: another thread may change a list meanwhile
+    if len(out) != n or len(out := tuple(out)) != n:
+        raise ValueError("out must hold %d tensors" % n)
     _shape(_dev(out[0], torch.uint8, "codes (out)"), (t, h * bits // 8), "codes (out)")
     for o, (dt, name) in zip(out[1:], meta):
         _shape(_dev(o, dt, name + " (out)"), (t, h // group), name + " (out)")
-    return tuple(out)
+    return out
 
 
 def _coded_inputs(codes, metas, hidden, group, bits, meta):

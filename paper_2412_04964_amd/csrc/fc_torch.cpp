@@ -126,22 +126,34 @@ void *stream_of(int device) { return c10::hip::getCurrentHIPStream((c10::DeviceI
 struct Coded {
     std::array<const at::Tensor *, 3> t{};
     std::array<at::Tensor, 3> own;
-    PyObject *given = nullptr;             // the caller's tuple or list
+    PyObject *given = nullptr;             // the caller's buffers as a tuple of this call's own, see take()
 
-    // takes the caller's buffers (`out` is not None), or fails
+    Coded() = default;
+    Coded(const Coded &) = delete;
+    Coded &operator=(const Coded &) = delete;
+    ~Coded() { Py_XDECREF(given); }
+
+    // Takes the caller's buffers (`out` is not None), or fails.  A list may be changed by another thread while the
+    // library is called without the interpreter lock: checks, launch and result use one tuple taken from it here,
+    // which also keeps the tensors alive until the call has been made.
     bool take(PyObject *out, int n, int64_t tokens, int64_t hidden, int64_t group, int64_t bits, at::ScalarType meta,
               int device, bool at_least)
     {
-        const bool tuple = PyTuple_CheckExact(out);
-        if (!tuple && !PyList_CheckExact(out)) return false;
-        const Py_ssize_t len = tuple ? PyTuple_GET_SIZE(out) : PyList_GET_SIZE(out);
+        if (PyTuple_CheckExact(out)) {
+            Py_INCREF(out);
+            given = out;
+        } else if (PyList_CheckExact(out)) {
+            given = PyList_AsTuple(out);
+            if (!given) throw python_error();
+        } else {
+            return false;
+        }
+        const Py_ssize_t len = PyTuple_GET_SIZE(given);
         if (len != n && !(at_least && len > n)) return false;
         for (int i = 0; i < n; ++i) {
-            PyObject *o = tuple ? PyTuple_GET_ITEM(out, i) : PyList_GET_ITEM(out, i);
-            t[i] = plain(o, i ? meta : at::kByte, device);
+            t[i] = plain(PyTuple_GET_ITEM(given, i), i ? meta : at::kByte, device);
             if (!t[i] || !shape2(*t[i], tokens, i ? hidden / group : hidden * bits / 8)) return false;
         }
-        given = out;
         return true;
     }
     void allocate(int n, int64_t tokens, int64_t hidden, int64_t group, int64_t bits, at::ScalarType meta,
@@ -157,7 +169,6 @@ struct Coded {
     PyObject *result(int n, int nones) const
     {
         if (given && nones == 0) {
-            if (PyList_CheckExact(given)) return PyList_AsTuple(given);
             Py_INCREF(given);
             return given;
         }
@@ -168,7 +179,7 @@ struct Coded {
             if (i >= n) {
                 Py_INCREF(o);
             } else if (given) {
-                o = PyTuple_CheckExact(given) ? PyTuple_GET_ITEM(given, i) : PyList_GET_ITEM(given, i);
+                o = PyTuple_GET_ITEM(given, i);
                 Py_INCREF(o);
             } else {
                 o = THPVariable_Wrap(own[i]);

@@ -294,6 +294,27 @@ def test_binding_checks_every_tensor_against_the_geometry_before_the_c_call(monk
     with pytest.raises(TypeError): b.quantize(x.float(), G, 4)
 
 
+def test_binding_uses_the_outputs_that_it_has_checked(monkeypatch):
+    # a list of outputs may change between the checks and the call (another thread): what is checked is what is used
+    torch = pytest.importorskip("torch")
+    from paper_2412_04964_amd import binding as b
+
+    class Changing(list):
+        def __iter__(self):
+            return iter([torch.zeros(1, dtype=torch.uint8), self[1], self[2]])
+
+    class Unreachable:
+        def __getattr__(self, name):
+            raise AssertionError("%s reached with tensors that were not checked" % name)
+
+    monkeypatch.setattr(b, "_dev", lambda t, dtype, what: t)
+    monkeypatch.setattr(b, "lib", lambda: Unreachable())
+    monkeypatch.setattr(b, "_stream", lambda: 0)
+    x, meta = torch.zeros(4, 256, dtype=torch.float16), torch.zeros(4, 2)
+    with pytest.raises(ValueError, match="codes"):
+        b.quantize(x, 128, 4, out=Changing([torch.zeros(4, 128, dtype=torch.uint8), meta, meta]))
+
+
 def test_binding_refuses_tensors_of_another_device(monkeypatch):
     # the C ABI works on the device that is current on the calling thread; a tensor of another device is refused
     torch = pytest.importorskip("torch")

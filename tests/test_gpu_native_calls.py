@@ -1,5 +1,8 @@
 """The native module behind the binding (csrc/fc_torch.cpp): the ordinary call goes through it and gives what the checked
 Python path of binding.py gives; everything else is left to that path."""
+import sys
+import threading
+
 import pytest
 
 torch = pytest.importorskip("torch")
@@ -144,6 +147,41 @@ def test_native_calls_go_to_the_current_stream():
             assert b._calls().allreduce_sim(src, 128, 4, 4, y, None) is y
     s.synchronize()
     assert torch.equal(y, want)
+
+
+@pytest.mark.gpu
+def test_a_list_of_outputs_may_change_during_the_call():
+    # Another thread runs while the library is called without the interpreter lock.  It exchanges the entries of a list
+    # of outputs (always as a whole): the call must return the tensors that it wrote.
+    from paper_2412_04964_amd import binding as b
+    x = torch.randn(8, 1024, device="cuda").half()
+    want = b.quantize(x, 128, 4)
+    rot = b.quantize_rot(x, 128, 4, b.QUANTIZER_SYM)
+    sets = [[torch.empty_like(t) for t in want] for _ in range(2)]
+    shared, stop = list(sets[0]), threading.Event()
+
+    def exchange():
+        while not stop.is_set():
+            shared[:] = sets[1]
+            shared[:] = sets[0]
+
+    thread, interval = threading.Thread(target=exchange), sys.getswitchinterval()
+    sys.setswitchinterval(1e-6)
+    thread.start()
+    try:
+        for i in range(300):
+            for t in sets[0] + sets[1]:
+                t.zero_()
+            if i % 2:
+                got, expected = b.quantize(x, 128, 4, out=shared), want
+            else:
+                got, expected = b.quantize_rot(x, 128, 4, b.QUANTIZER_SYM, out=shared)[:2], rot[:2]
+            assert any(all(g is t for g, t in zip(got, s)) for s in sets), "tensors of two sets"
+            assert all(torch.equal(g, w) for g, w in zip(got, expected)), "tensors that were not written"
+    finally:
+        stop.set()
+        thread.join()
+        sys.setswitchinterval(interval)
 
 
 def test_native_module_takes_no_cpu_tensor():
