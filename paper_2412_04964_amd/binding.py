@@ -13,6 +13,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import warnings
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 # FC_LIBRARY overrides the location of the shared library (e.g. a differently tuned build)
@@ -114,14 +115,29 @@ def lib() -> ctypes.CDLL:
 _native = None
 
 
+class _NoNativeCalls:
+    """Stands in for the native module where it cannot be used: takes no call, so the code below makes it."""
+    def __getattr__(self, name):
+        return lambda *args: None
+
+
 def _calls():
-    """The native module, bound to the library on first use."""
+    """The native module, bound to the library on first use.  It belongs to the torch that it was compiled with; where it
+    is missing or torch is another one, every call goes through the checks and ctypes calls below."""
     global _native
     if _native is None:
         lib()
-        from . import _fc_torch
-        _fc_torch.load(_LIB_PATH, _check)
-        _native = _fc_torch
+        try:
+            import torch
+            from . import _fc_torch
+            if _fc_torch.torch_version != torch.__version__:
+                raise ImportError("compiled with torch %s, this is %s" % (_fc_torch.torch_version, torch.__version__))
+            _fc_torch.load(_LIB_PATH, _check)
+            _native = _fc_torch
+        except ImportError as e:
+            warnings.warn("the native calls (_fc_torch.so) cannot be used, calls take longer on the host: %s" % e,
+                          RuntimeWarning, stacklevel=3)
+            _native = _NoNativeCalls()
     return _native
 
 

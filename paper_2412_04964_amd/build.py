@@ -15,6 +15,7 @@ and one that matters for speed:
 """
 from __future__ import annotations
 
+import importlib.util
 import os
 import subprocess
 import sys
@@ -81,7 +82,7 @@ def _compile_torch_ext():
 
     tmp = TORCH_EXT + ".tmp.%d" % os.getpid()
     cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-Wall",
-           "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1", "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI,
+           "-DFC_TORCH_VERSION=\"%s\"" % torch.__version__, "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1", "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI,
            "-I", INCLUDE]
     for path in [*cpp_extension.include_paths(), sysconfig.get_paths()["include"],
                  os.path.join(os.path.dirname(os.path.dirname(HIPCC)), "include")]:
@@ -98,18 +99,14 @@ def _compile_torch_ext():
 
 
 def build(verbose: bool = False, jobs: int | None = None) -> str:
-    """Compile every unit (always; this is the "does it build" check) and link."""
+    """Compile every unit (always; this is the "does it build" check) and link.  The libraries need hipcc alone; without
+    torch only the torch binding is left out."""
     os.makedirs(OBJDIR, exist_ok=True)
     jobs = jobs or min(8, os.cpu_count() or 1)
     with ThreadPoolExecutor(jobs) as ex:
-        ext = ex.submit(_compile_torch_ext)
+        ext = ex.submit(_compile_torch_ext) if importlib.util.find_spec("torch") else None
         results = list(ex.map(_compile, UNITS + BENCH_UNITS + PLAIN_UNITS))
-        results.append((None, ext.result()))
-    if verbose:
-        for _, w in results:
-            if w:
-                print(w, file=sys.stderr)
-    objs = [o for o, _ in results if o]
+    objs = [o for o, _ in results]
     n_u, n_b = len(UNITS), len(BENCH_UNITS)
     shared = [o for o, (src, _, _) in zip(objs[:n_u], UNITS) if src not in LANDING_SOURCES]
     for lib, members in ((LIB, objs[:n_u]), (BENCH_LIB, objs[n_u:n_u + n_b]), (PLAIN_LIB, shared + objs[n_u + n_b:])):
@@ -119,6 +116,12 @@ def build(verbose: bool = False, jobs: int | None = None) -> str:
         if r.returncode != 0:
             raise RuntimeError("link failed:\n%s" % r.stderr)
         os.replace(tmp, lib)
+    warnings = [w for _, w in results]
+    warnings.append(ext.result() if ext else "torch is not installed: %s not built" % os.path.basename(TORCH_EXT))
+    if verbose:
+        for w in warnings:
+            if w:
+                print(w, file=sys.stderr)
     return LIB
 
 

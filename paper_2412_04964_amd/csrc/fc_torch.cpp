@@ -488,4 +488,10 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_fc_torch", nullptr, -1, methods, 
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__fc_torch(void) { return PyModule_Create(&module); }
+PyMODINIT_FUNC PyInit__fc_torch(void)
+{
+    PyObject *m = PyModule_Create(&module);
+    // the torch whose headers this was compiled with: binding.py does not use the module under another one
+    if (m && PyModule_AddStringConstant(m, "torch_version", FC_TORCH_VERSION) != 0) Py_CLEAR(m);
+    return m;
+}

@@ -2,6 +2,7 @@
 Python path of binding.py gives; everything else is left to that path."""
 import sys
 import threading
+import warnings
 
 import pytest
 
@@ -182,6 +183,31 @@ def test_a_list_of_outputs_may_change_during_the_call():
         stop.set()
         thread.join()
         sys.setswitchinterval(interval)
+
+
+@pytest.mark.parametrize("why", ["missing", "other torch"])
+def test_without_the_native_module_the_checked_path_takes_every_call(monkeypatch, why):
+    import paper_2412_04964_amd
+    from paper_2412_04964_amd import binding as b
+    monkeypatch.setattr(b, "_native", None)
+    if why == "missing":
+        monkeypatch.delattr(paper_2412_04964_amd, "_fc_torch", raising=False)
+        monkeypatch.setitem(sys.modules, "paper_2412_04964_amd._fc_torch", None)
+    else:
+        from paper_2412_04964_amd import _fc_torch
+        monkeypatch.setattr(_fc_torch, "torch_version", "0")
+    reached = []
+    monkeypatch.setattr(b, "_dev", lambda t, dtype, what: t)
+    monkeypatch.setattr(b, "_check", lambda rc, what: reached.append(what))
+    monkeypatch.setattr(b, "_stream", lambda: 0)
+    empty = torch.zeros(0, 256, dtype=torch.float16)      # a call that launches nothing
+    with pytest.warns(RuntimeWarning, match="_fc_torch"):
+        codes, scales, zeros = b.quantize(empty, 128, 4)
+    with warnings.catch_warnings():
+        warnings.simplefilter("error")                    # no second warning
+        b.dequantize(codes, scales, zeros, 256, 128, 4)
+    b.allreduce_sim(empty[None], 128, 4, 4)
+    assert reached == ["fc_quantize", "fc_dequantize", "fc_allreduce_sim"]
 
 
 def test_native_module_takes_no_cpu_tensor():
