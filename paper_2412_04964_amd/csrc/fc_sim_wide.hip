@@ -174,7 +174,7 @@ __global__ __launch_bounds__(kSimWideMaxThreads) void k_allreduce_wide(const uin
             r.y = (_Float16)(d[8 * k + 2 * i + 1] * s);
             out[i] = as_u32(r);
         }
-        __builtin_amdgcn_raw_buffer_store_b128(out, ry, tid * 16, k * piece, kStreamStorePolicy);
+        store_b128_at(out, ry, tid * 16, k * piece);
     }
 }
 

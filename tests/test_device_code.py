@@ -73,3 +73,31 @@ def test_partial_rotation_tiles_have_no_scalar_offset(kernels):
         bad = [i for i in body if scalar_offset(i)]
         assert not bad, "%s: %s" % (name, bad[0])
     assert seen == 2 * (5 + 5 + 3)                 # two blocks; quantizer and dequantizer with five codes, all-reduce with three
+
+
+def registers(operand):
+    """v7 -> {7}, v[4:7] -> {4, 5, 6, 7}; anything else -> empty"""
+    m = re.fullmatch(r"v(?:(\d+)|\[(\d+):(\d+)\])", operand)
+    return set() if not m else {int(m.group(1))} if m.group(1) else set(range(int(m.group(2)), int(m.group(3)) + 1))
+
+
+def test_wide_stores_with_a_scalar_offset_keep_their_data(kernels):
+    # A 96- or 128-bit store reads its data registers after it has issued; where its scalar offset is a register the compiler
+    # does not wait.  The wait state must follow before any of the data registers is written again.
+    seen = 0
+    for name, body in kernels.items():
+        for at, instruction in enumerate(body):
+            m = scalar_offset(instruction) if re.match(r"buffer_store_dwordx[34]\b", instruction) else None
+            if not m:
+                continue
+            seen += 1
+            data = registers(m.group("data"))
+            assert data, instruction
+            for later in body[at + 1:]:
+                if later.startswith("s_nop"):
+                    break
+                assert not later.startswith(("s_endpgm", "s_branch", "s_cbranch", "s_setpc")), "%s: no wait after %s" % (name, instruction)
+                operands = later.split(None, 1)[1].split(",") if " " in later else [""]
+                written = [] if later.startswith(("buffer_store", "global_store", "ds_write", "s_")) else operands[:1]
+                assert not any(registers(w.strip()) & data for w in written), "%s: %s overwrites %s" % (name, later, instruction)
+    assert seen > 0

@@ -279,9 +279,9 @@ def test_volume_beyond_2_to_32_elements(fc, which):
 @pytest.mark.parametrize("n_src", [1, 2, 4, 5, 8])                    # 5 and 8: more than half of the parameter lanes
 def test_wide_groups(fc, name, group, n_src):
     if name == "asym":
-        gpu, ref = fc.allreduce_sim, oracle.allreduce_sim
+        ref = oracle.allreduce_sim
     else:
-        gpu, ref = variant(fc, name)
+        _, ref = variant(fc, name)
     rng = np.random.default_rng(group + n_src)
     for tokens, hidden, kind in ((1, group, None), (3, 2 * group, None), (17, group, 2), (2, 3 * group, 1), (5, group, 4)):
         if kind is None:
@@ -290,6 +290,28 @@ def test_wide_groups(fc, name, group, n_src):
             x = synth_inputs.make_partials_stress(n_src, tokens, hidden, kind, seed=int(rng.integers(1 << 30)))
         xd = dev16(x)
         for bi, bo in bit_pairs(name) if (tokens, kind) == (3, None) else bit_pairs(name)[:1]:
-            got = gpu(xd, group, bi, bo)
+            guard = 16384                                             # a workgroup's tile
+            raw = torch.full((tokens * hidden + 2 * guard,), 7.0, dtype=torch.float16, device="cuda")
+            y = raw[guard:guard + tokens * hidden].view(tokens, hidden)
+            named = fc.allreduce_sim if name == "asym" else getattr(fc, "allreduce_sim_" + name)
+            named(xd, group, *(() if name == "fp8" else (bi, bo)), out=y)
             torch.cuda.synchronize()
-            check(got.cpu().numpy(), ref(x, group, bi, bo), "%s N=%d g=%d %dx%d %d->%d" % (name, n_src, group, tokens, hidden, bi, bo))
+            assert (raw[:guard] == 7.0).all() and (raw[guard + tokens * hidden:] == 7.0).all(), "write outside the output"
+            check(y.cpu().numpy(), ref(x, group, bi, bo), "%s N=%d g=%d %dx%d %d->%d" % (name, n_src, group, tokens, hidden, bi, bo))
+
+
+@pytest.mark.parametrize("name", ["asym", "sym", "fp8", "cmeta"])
+@pytest.mark.parametrize("group", [2048, 16384])
+def test_wide_groups_fill_the_chip(fc, name, group):
+    # a volume that fills the chip several times over, eight times, against the three steps: faults of a few wavefronts in
+    # ten thousand do not show at the sizes of the other tests
+    n_src, tokens = 2, (1 << 25) // group
+    x = synth_inputs.make_partials_device(n_src, tokens, group, group, "cuda", 0.01, 20.0)
+    sfx, bits = ("" if name == "asym" else "_" + name), bit_pairs(name)[0]
+    width = lambda *b: () if name == "fp8" else b
+    parts = [getattr(fc, "quantize" + sfx)(x[j], group, *width(bits[0])) for j in range(n_src)]
+    coded = getattr(fc, "dequant_reduce_requant" + sfx)(*[torch.stack(p) for p in zip(*parts)], group, group, *width(*bits))
+    want = getattr(fc, "dequantize" + sfx)(*coded, group, group, *width(bits[1]))
+    for _ in range(8):
+        y = getattr(fc, "allreduce_sim" + sfx)(x, group, *width(*bits))
+        assert torch.equal(y.view(torch.int16), want.view(torch.int16))
