@@ -83,6 +83,11 @@ hipError_t launch_quantize_rot(int bits, int codec, const void *x_f16, int64_t t
 hipError_t launch_dequantize_rot(int bits, int codec, const void *codes, const float *scales, const float *zeros,
                                  int64_t tokens, int hidden, int group, void *y_f16, hipStream_t stream);
 
+// fc_rot_rows.hip: the same for launch-bound volumes, blocks of 1024, 2048 and 4096 (2^log_b).
+hipError_t launch_quantize_rot_rows(int bits, int codec, const void *x_f16, int64_t n_elems, int log_b, int group,
+                                    void *codes, float *scales, float *zeros, hipStream_t stream);
+hipError_t launch_dequantize_rot_rows(int bits, int codec, const void *codes, const float *scales, const float *zeros,
+                                      int64_t n_elems, int log_b, int group, void *y_f16, hipStream_t stream);
 // fc_rot_sim.hip: the whole rotated all-reduce in one launch, every group and fan-in.
 hipError_t launch_allreduce_rot(int codec, int bits_rs, int bits_ag, const void *x_f16, int n_src, int64_t tokens,
                                 int hidden, int group, void *y_f16, hipStream_t stream);

@@ -17,12 +17,13 @@
 // groups never cross block boundaries, so the tensor is handled as a flat sequence of tiles; the last tile of a
 // tensor of 1024- or 2048-element blocks may be a partial one (loads beyond the end give zeros, stores are dropped).
 //
-// What bounds them: vector instructions (quantizer, blocks of 1024: 590 per wavefront of 2048 elements, about 1950 cycles
+// What bounds them: vector instructions (quantizer, blocks of 1024, 4 bit: 590 per wavefront of 2048 elements, about 1950 cycles
 // with the DPP, conversion and min / max instructions that issue at half the rate of an fp32 add), then HBM.  The rows
 // used to go through LDS and back for every five stages, in fp32: 10 KB per wavefront kept four of them on a SIMD, and
 // LDS writes run at 75 bytes a cycle.  Rotate + quantize / dequantize + rotate, us before -> now: 8192 x 8192 INT4 (blocks of
 // 8192) 46.0 -> 43.0 / 43.9 -> 39.6; the same in FP8 55.5 -> 45.2 / 46.3 -> 42.9; 8192 x 5120 INT4 (blocks of 1024)
-// 24.1 -> 23.8 / 24.0 -> 22.2; 32 x 8192 4.20 -> 3.67 / 3.87 -> 3.48.  Measured and not taken: 32 consecutive elements per lane
+// 23.9 -> 25.4 / 24.5 -> 22.7; 32 x 8192 4.20 -> 3.67 / 3.87 -> 3.48.  Where the form with the row in LDS is the faster one (the
+// 4-bit quantizer of blocks of 1024 above, launch-bound volumes) it is fc_rot_rows.hip that runs.  Measured and not taken: 32 consecutive elements per lane
 // and a 16 x 16 exchange with other lanes through 5 KB of LDS (40.3 us for blocks of 8192, but 23.8 for 1024 and
 // 23.0 / 48 in the dequantizer, whose register needs it does not fit); all stages between lanes by permlane swaps
 // (25.9 us, blocks of 1024).
@@ -381,6 +382,20 @@ hipError_t dequantize_rot_h(int log_b, const uint8_t *c, const float *scales, co
     }
 }
 
+// Whether the form of fc_rot_rows.hip is the faster one (its header has both sides' times): at 8 bit, where a wavefront here has
+// twice the work of one there, up to 2^21 elements, blocks of 4096 up to 3 * 2^20.  At 4 bit a wavefront has the same 2048
+// elements in both forms, and the register form is as fast or faster for blocks of 2048 and for the quantizer of blocks of 1024
+// while it has one workgroup per compute unit (2^20 elements).  The 4-bit quantizer of blocks of 1024, whose codes leave in
+// 32-bit stores here and in 128-bit stores there, crosses once more, between 2^23 and 2^25 elements.
+bool rot_rows_apply(bool quantize, int bits, int log_b, int64_t n_elems)
+{
+    constexpr int64_t k1M = (int64_t)1 << 20;
+    if (log_b > 12) return false;
+    if (n_elems <= (log_b == 12 ? 3 : 2) * k1M)
+        return bits == 8 || log_b == 12 || (log_b == 10 && !quantize) || n_elems > k1M;
+    return quantize && bits == 4 && log_b == 10 && n_elems > 16 * k1M;
+}
+
 }  // namespace
 
 hipError_t launch_quantize_rot(int bits, int codec, const void *x_f16, int64_t tokens, int hidden, int group,
@@ -390,6 +405,8 @@ hipError_t launch_quantize_rot(int bits, int codec, const void *x_f16, int64_t t
     uint8_t *c = static_cast<uint8_t *>(codes);
     const int lb = log2_int(rotation_block(hidden));
     const int64_t n = tokens * hidden;
+    if (rot_rows_apply(true, bits, lb, n))
+        return launch_quantize_rot_rows(bits, codec, x_f16, n, lb, group, codes, scales, zeros, stream);
     if (codec == CODEC_FP8)
         return bits == 8 ? quantize_rot_h<8, kFp8>(lb, x, n, group, c, scales, nullptr, stream)
                          : hipErrorInvalidValue;
@@ -407,6 +424,8 @@ hipError_t launch_dequantize_rot(int bits, int codec, const void *codes, const f
     uint16_t *y = static_cast<uint16_t *>(y_f16);
     const int lb = log2_int(rotation_block(hidden));
     const int64_t n = tokens * hidden;
+    if (rot_rows_apply(false, bits, lb, n))
+        return launch_dequantize_rot_rows(bits, codec, codes, scales, zeros, n, lb, group, y_f16, stream);
     if (codec == CODEC_FP8)
         return bits == 8 ? dequantize_rot_h<8, kFp8>(lb, c, scales, nullptr, n, group, y, stream)
                          : hipErrorInvalidValue;

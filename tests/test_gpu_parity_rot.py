@@ -140,6 +140,47 @@ def test_partial_last_tile_stays_inside_the_buffers(fc, quantizer, bits, tokens,
         assert same_bits(y.t.cpu().numpy().view(np.uint16), ref.view(np.uint16))
 
 
+# elements: both sides of every volume at which the rotated quantizer and dequantizer change their form
+VOLUMES = [1 << 20, (1 << 20) + 1, 1 << 21, (1 << 21) + 1, 3 << 20, (3 << 20) + 1, 1 << 24, (1 << 24) + 1]
+
+
+@pytest.mark.parametrize("quantizer,bits", QUANTIZERS)
+@pytest.mark.parametrize("hidden", [1024, 3072, 2048, 4096])
+def test_both_forms_give_the_same_bits(fc, quantizer, bits, hidden):
+    # rows of every kind, a few of them (compared with the oracle) and repeated up to the volumes of the other form; the
+    # number of rows is odd just above each limit, where blocks of 1024 and 2048 leave a partial last tile
+    rng = np.random.default_rng(hidden + bits)
+    x = synth_inputs.make_partials(1, 6, hidden, seed=hidden)[0]
+    x[1] = 0
+    x[2] = (rng.standard_normal(hidden) * np.exp(rng.uniform(-8, 8, hidden))).astype(np.float16)
+    x[3] = rng.standard_normal(hidden) * 1e-3 + 3.0
+    x[4] = np.float16(6e-8) * (np.arange(hidden) % 5)
+    few = dev(x.view(np.uint16)).view(torch.float16)
+    for group in (32, 1024):
+        want = oracle.quantize_rot(x, group, bits, quantizer)
+        s2, z2 = want[1].copy(), want[2].copy()
+        s2[5] = np.exp(rng.uniform(-10, 6, size=s2[5].shape))
+        if quantizer == oracle.ASYM:
+            z2[5, ::3] = rng.uniform(-3e4, 3e4, size=z2[5, ::3].shape)
+        wants = [dev(a) for a in want[:3 if quantizer == oracle.ASYM else 2]]
+        metas = [dev(s2), dev(z2)]
+        back = dev(oracle.dequantize_rot(want[0], s2, z2, hidden, group, bits, quantizer).view(np.int16))
+        for volume in VOLUMES:
+            rows = volume // hidden if volume % 2 == 0 else (volume // hidden + 1) | 1
+            pick = torch.arange(rows, device="cuda") % 6
+            c = Guarded((rows, hidden * bits // 8), torch.uint8)
+            s, z = [Guarded((rows, hidden // group), torch.float32) for _ in range(2)]
+            fc.quantize_rot(few[pick], group, bits, quantizer, out=(c.t, s.t, z.t))
+            y = Guarded((rows, hidden), torch.float16)
+            fc.dequantize_rot(wants[0][pick], metas[0][pick], metas[1][pick], hidden, group, bits, quantizer, out=y.t)
+            torch.cuda.synchronize()
+            for g in (c, s, z, y): g.check()
+            what = "h=%d g=%d rows=%d " % (hidden, group, rows)
+            for got, w in zip((c.t, s.t, z.t), wants):
+                assert torch.equal(got.view(torch.uint8), w[pick].view(torch.uint8)), what + "quantize"
+            assert torch.equal(y.t.view(torch.int16), back[pick]), what + "dequantize"
+
+
 def test_rot_rejects_unsupported_rows_and_empty_is_noop(fc):
     x = torch.zeros((2, 2560), dtype=torch.float16, device="cuda")           # 5 x 512: blocks below 1024
     with pytest.raises(fc.FcError):
