@@ -289,8 +289,9 @@ FC_API int fc_dequantize_rot(const void *codes, const float *scales, const float
                              int64_t tokens, int64_t hidden, int group, int bits, int quantizer,
                              void *y_f16, void *hip_stream);
 
-/* Algorithm 1 with the rotation around it, one kernel, bit-identical to fc_quantize_rot x n_src ->
-   fc_dequant_reduce_requant* -> fc_dequantize_rot; workspace as for fc_allreduce_sim. */
+/* Algorithm 1 with the rotation around it: fc_quantize_rot x n_src -> fc_dequant_reduce_requant* -> fc_dequantize_rot
+   through the workspace for launch-bound volumes of several sources, one kernel, bit-identical, for all others;
+   workspace as for fc_allreduce_sim. */
 FC_API int fc_allreduce_sim_rot(const void *x_f16, int n_src, int64_t tokens, int64_t hidden,
                                 int group, int bits_rs, int bits_ag, int quantizer, void *y_f16,
                                 void *workspace, size_t workspace_bytes, void *hip_stream);

@@ -163,11 +163,10 @@ int dequantize_impl(int codec, const void *codes, const float *scales, const flo
                                             static_cast<hipStream_t>(hip_stream)));
 }
 
-// one_launch: whether the single-kernel forms (which leave the workspace untouched) may stand in for the
-// three-kernel sequence
+// Algorithm 1 in one launch; nothing goes through the workspace
 int allreduce_sim_impl(int codec, const void *x_f16, int n_src, int64_t tokens, int64_t hidden,
                        int group, int bits_rs, int bits_ag, void *y_f16,
-                       void *workspace, size_t workspace_bytes, void *hip_stream, bool one_launch = true)
+                       void *workspace, size_t workspace_bytes, void *hip_stream)
 {
     int64_t n = 0;
     const int rc = check_shape(tokens, hidden, group, bits_rs, &n);
@@ -181,41 +180,12 @@ int allreduce_sim_impl(int codec, const void *x_f16, int n_src, int64_t tokens, 
     if (!workspace || workspace_bytes < L.total) return FC_ERR_WORKSPACE;
     if (!aligned16(workspace)) return FC_ERR_ALIGN;
 
-    // the three steps in one kernel, bit-identical, nothing goes through the workspace: one form for launch-bound
-    // volumes (the partials' quantizations spread over wavefronts), one for all others
-    if (one_launch) {
-        if (fc::allreduce_small_applies(n_src, n, group))
-            return hip_result(fc::launch_allreduce_small(codec, bits_rs, bits_ag, x_f16, n_src, n, group, y_f16,
-                                                         static_cast<hipStream_t>(hip_stream)));
-        return hip_result(fc::launch_allreduce_fused(codec, bits_rs, bits_ag, x_f16, n_src, n, group, y_f16,
+    // one form for launch-bound volumes (the partials' quantizations spread over wavefronts), one for all others
+    if (fc::allreduce_small_applies(n_src, n, group))
+        return hip_result(fc::launch_allreduce_small(codec, bits_rs, bits_ag, x_f16, n_src, n, group, y_f16,
                                                      static_cast<hipStream_t>(hip_stream)));
-    }
-
-    char *ws = static_cast<char *>(workspace);
-    const char *x = static_cast<const char *>(x_f16);
-    // the N partials are N*tokens rows of one tensor; when the workspace slabs need no padding they
-    // are quantized by one launch (what matters for launch-bound volumes), otherwise one by one
-    const bool packed = L.codes_rs == (size_t)n * bits_rs / 8 && L.meta == (size_t)(n / group) * sizeof(float) &&
-                        tokens <= kMaxElems / hidden / n_src;
-    const int launches = packed ? 1 : n_src;
-    for (int j = 0; j < launches; ++j) {
-        const int q = quantize_impl(codec, x + (size_t)j * (size_t)n * 2, packed ? tokens * n_src : tokens, hidden,
-                                    group, bits_rs, ws + L.off_codes1 + (size_t)j * L.codes_rs,
-                                    reinterpret_cast<float *>(ws + L.off_scales1 + (size_t)j * L.meta),
-                                    reinterpret_cast<float *>(ws + L.off_zeros1 + (size_t)j * L.meta),
-                                    hip_stream);
-        if (q != FC_OK) return q;
-    }
-    const int f = fused_impl(codec, ws + L.off_codes1, (int64_t)L.codes_rs,
-                             reinterpret_cast<const float *>(ws + L.off_scales1),
-                             reinterpret_cast<const float *>(ws + L.off_zeros1),
-                             (int64_t)(L.meta / sizeof(float)), n_src, tokens, hidden, group, bits_rs,
-                             bits_ag, ws + L.off_codes2, reinterpret_cast<float *>(ws + L.off_scales2),
-                             reinterpret_cast<float *>(ws + L.off_zeros2), hip_stream);
-    if (f != FC_OK) return f;
-    return dequantize_impl(codec, ws + L.off_codes2, reinterpret_cast<const float *>(ws + L.off_scales2),
-                           reinterpret_cast<const float *>(ws + L.off_zeros2), tokens, hidden, group,
-                           bits_ag, y_f16, hip_stream);
+    return hip_result(fc::launch_allreduce_fused(codec, bits_rs, bits_ag, x_f16, n_src, n, group, y_f16,
+                                                 static_cast<hipStream_t>(hip_stream)));
 }
 
 // Device address of the current device's copy of `scratch`, looked up once per device.
@@ -283,6 +253,57 @@ int dequantize_rot_impl(int codec, const void *codes, const float *scales, const
         return FC_ERR_ALIGN;
     return hip_result(fc::launch_dequantize_rot(bits, codec, codes, scales, sym ? nullptr : zeros, tokens,
                                                 (int)hidden, group, y_f16, static_cast<hipStream_t>(hip_stream)));
+}
+
+// Whether the N partials, N * tokens rows of one tensor, can be quantized by one launch: the workspace slabs need no padding
+bool slabs_are_dense(const SimLayout &L, int64_t n_elems, int group, int bits_rs)
+{
+    return L.codes_rs == (size_t)n_elems * bits_rs / 8 && L.meta == (size_t)(n_elems / group) * sizeof(float);
+}
+
+// Algorithm 1 as its three steps through the workspace, on checked arguments; rotate: with the Hadamard rotation around it
+int three_steps(bool rotate, int codec, const void *x_f16, int n_src, int64_t tokens, int64_t hidden, int group,
+                int bits_rs, int bits_ag, void *y_f16, const SimLayout &L, void *workspace, void *hip_stream)
+{
+    const int64_t n = tokens * hidden;
+    char *ws = static_cast<char *>(workspace);
+    const char *x = static_cast<const char *>(x_f16);
+    const auto quantize = rotate ? quantize_rot_impl : quantize_impl;
+    const auto dequantize = rotate ? dequantize_rot_impl : dequantize_impl;
+    // one launch for all partials is what matters for launch-bound volumes
+    const bool packed = slabs_are_dense(L, n, group, bits_rs) && tokens <= kMaxElems / hidden / n_src &&
+                        tokens <= 0x7FFFFFFF / n_src;
+    const int launches = packed ? 1 : n_src;
+    for (int j = 0; j < launches; ++j) {
+        const int q = quantize(codec, x + (size_t)j * (size_t)n * 2, packed ? tokens * n_src : tokens, hidden,
+                               group, bits_rs, ws + L.off_codes1 + (size_t)j * L.codes_rs,
+                               reinterpret_cast<float *>(ws + L.off_scales1 + (size_t)j * L.meta),
+                               reinterpret_cast<float *>(ws + L.off_zeros1 + (size_t)j * L.meta), hip_stream);
+        if (q != FC_OK) return q;
+    }
+    const int f = fused_impl(codec, ws + L.off_codes1, (int64_t)L.codes_rs,
+                             reinterpret_cast<const float *>(ws + L.off_scales1),
+                             reinterpret_cast<const float *>(ws + L.off_zeros1),
+                             (int64_t)(L.meta / sizeof(float)), n_src, tokens, hidden, group, bits_rs,
+                             bits_ag, ws + L.off_codes2, reinterpret_cast<float *>(ws + L.off_scales2),
+                             reinterpret_cast<float *>(ws + L.off_zeros2), hip_stream);
+    if (f != FC_OK) return f;
+    return dequantize(codec, ws + L.off_codes2, reinterpret_cast<const float *>(ws + L.off_scales2),
+                      reinterpret_cast<const float *>(ws + L.off_zeros2), tokens, hidden, group,
+                      bits_ag, y_f16, hip_stream);
+}
+
+// Whether the three steps are the faster form of the rotated all-reduce.  The one launch works through the sources one after
+// the other, 2.2 us each (FP8 2.5) until the chip is full; the three steps take 10 us, their quantizations spread over the chip.  Hidden
+// 8192, group 128, INT4, three steps / one launch, us under graph replay: N = 8, 1 token 10.2 / 18.5, 32 11.3 / 21.2, 128 15.9 / 18.9,
+// 192 20.0 / 20.0, 256 22.4 / 20.1; N = 4, 8 tokens 10.3 / 11.4, 96 12.3 / 12.4, 128 12.6 / 11.6; N = 3 10.2 / 9.7.  FP8: N = 8,
+// 8 tokens 10.8 / 23.1, 256 23.3 / 24.9; N = 3, 8 tokens 10.7 / 11.3, 64 11.6 / 11.4.  Where the slabs need padding every
+// partial is a launch of its own: N = 8, one token, group 8192 35.5 / 20.0.
+bool rot_steps_apply(const SimLayout &L, int codec, int n_src, int64_t n_elems, int group, int bits_rs)
+{
+    const bool fp8 = codec == fc::CODEC_FP8;
+    return n_src >= (fp8 ? 3 : 4) && n_elems <= ((int64_t)n_src * (fp8 ? 4 : 3) << 16) &&
+           slabs_are_dense(L, n_elems, group, bits_rs);
 }
 
 }  // namespace
@@ -368,17 +389,16 @@ int fc_allreduce_sim_static(const void *x_f16, int n_src, int64_t tokens, int64_
     if (n == 0) return FC_OK;
     if (!x_f16 || !y_f16) return FC_ERR_NULL;
     if (!aligned16(x_f16) || !aligned16(y_f16)) return FC_ERR_ALIGN;
-    if (sim_layout(n_src, n, group, bits_rs, bits_ag).total > (size_t)FC_STATIC_SCRATCH_BYTES)
-        return FC_ERR_WORKSPACE;
+    const SimLayout L = sim_layout(n_src, n, group, bits_rs, bits_ag);
+    if (L.total > (size_t)FC_STATIC_SCRATCH_BYTES) return FC_ERR_WORKSPACE;
     void *ws = nullptr;
     const int sc = static_scratch(&ws);
     if (sc != FC_OK) return sc;
     // nothing in the scratch has to start at zero: every byte a kernel reads there was written by
     // the kernel before it in this call
-    // always the three-kernel sequence through the scratch array (the single-kernel forms need no intermediates
-    // at all; fc_allreduce_sim takes them where they apply)
-    return allreduce_sim_impl(fc::CODEC_ASYM, x_f16, n_src, tokens, hidden, group, bits_rs, bits_ag, y_f16,
-                              ws, (size_t)FC_STATIC_SCRATCH_BYTES, hip_stream, false);
+    // always the three-kernel sequence through the scratch array (fc_allreduce_sim's one kernel needs no intermediates)
+    return three_steps(false, fc::CODEC_ASYM, x_f16, n_src, tokens, hidden, group, bits_rs, bits_ag, y_f16, L, ws,
+                       hip_stream);
 }
 
 int fc_allreduce_sim_sym(const void *x_f16, int n_src, int64_t tokens, int64_t hidden,
@@ -482,6 +502,9 @@ int fc_allreduce_sim_rot(const void *x_f16, int n_src, int64_t tokens, int64_t h
     if (!workspace || workspace_bytes < L.total) return FC_ERR_WORKSPACE;
     if (!aligned16(workspace)) return FC_ERR_ALIGN;
 
+    if (rot_steps_apply(L, quantizer, n_src, n, group, bits_rs))
+        return three_steps(true, quantizer, x_f16, n_src, tokens, hidden, group, bits_rs, bits_ag, y_f16, L, workspace,
+                           hip_stream);
     // one kernel; nothing goes through the workspace
     return hip_result(fc::launch_allreduce_rot(quantizer, bits_rs, bits_ag, x_f16, n_src, tokens, (int)hidden, group,
                                                y_f16, static_cast<hipStream_t>(hip_stream)));
