@@ -93,7 +93,7 @@ hipError_t launch_allreduce_rot(int codec, int bits_rs, int bits_ag, const void 
                                 int hidden, int group, void *y_f16, hipStream_t stream);
 
 // fc_small.hip: the whole all-reduce in one launch, for launch-bound volumes: at most kSmallAllreduceMaxElems elements
-// per partial, six times that over all partials, and groups of at most 512 elements.
+// per partial (of seven partials 6/7 of that) and groups of at most 512 elements.
 constexpr int64_t kSmallAllreduceMaxElems = (int64_t)1 << 20;
 bool allreduce_small_applies(int n_src, int64_t n_elems, int group);
 hipError_t launch_allreduce_small(int codec, int bits_rs, int bits_ag, const void *x_f16, int n_src, int64_t n_elems,

@@ -173,14 +173,19 @@ static hipError_t launch_small_codec(int bits_rs, int bits_ag, const uint16_t *x
     }
 }
 
-// Where the two forms cross (hidden 8192, g = 128, us per launch under graph replay, bulk / this one): N = 8 partials of 8
-// tokens or fewer, symmetric 4.1 / 2.4; 32 tokens, asymmetric 4.77 / 3.57, symmetric 4.43 / 3.19, FP8 4.85 / 3.18, compact
-// metadata 4.60 / 3.58; 96 tokens 6.46 / 5.88, 5.71 / 5.08, 6.34 / 5.09, 6.42 / 5.91; 128 tokens, symmetric 6.11 / 6.30, compact
-// metadata 6.77 / 7.24.  N = 4 at 128 tokens 4.86 / 4.65, 4.36 / 4.12, 4.70 / 4.10, 4.72 / 4.63, at 160 tokens equal; N = 1 at 128
-// tokens equal.  Hence at most 2^20 elements per partial and 12 wavefronts per SIMD over all partials.
+// Where the two forms cross (hidden 8192, g = 128, us per launch under graph replay, this one / bulk; asymmetric INT8, symmetric
+// INT4, compact metadata INT4, FP8):
+//   N = 8   64 tokens 4.02 / 4.58, 3.33 / 4.29, 4.12 / 4.47, 3.31 / 4.79; 128 tokens (the limit) 5.77 / 5.95, 4.53 / 5.10,
+//           5.84 / 5.97, 4.66 / 5.84; 160 tokens 6.69 / 6.46, 5.17 / 5.20, 6.71 / 6.02, 5.23 / 6.43
+//   N = 7   96 tokens 5.63 / 5.57, 4.37 / 4.84, 5.44 / 5.45, 4.44 / 5.58; 128 tokens 6.25 / 5.54, 4.86 / 4.81, 6.27 / 5.54,
+//           4.99 / 5.35: seven wavefronts leave one of a workgroup's SIMDs half empty
+//   N = 4   128 tokens 4.01 / 4.11, 3.31 / 3.63, 4.04 / 4.10, 3.36 / 4.00; 160 tokens 4.37 / 4.15, 3.54 / 3.65, 4.47 / 4.13,
+//           3.56 / 4.01
+// Hence at most 2^20 elements per partial, and of seven partials at most 6 * 2^20 altogether.
 bool allreduce_small_applies(int n_src, int64_t n_elems, int group)
 {
-    return group <= kSmallWaveElems && n_elems <= kSmallAllreduceMaxElems && n_src * n_elems <= 6 * kSmallAllreduceMaxElems;
+    return group <= kSmallWaveElems && n_elems <= kSmallAllreduceMaxElems &&
+           (n_src != 7 || n_src * n_elems <= 6 * kSmallAllreduceMaxElems);
 }
 
 hipError_t launch_allreduce_small(int codec, int bits_rs, int bits_ag, const void *x_f16, int n_src, int64_t n_elems,

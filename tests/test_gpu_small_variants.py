@@ -85,3 +85,23 @@ def test_allreduce_small_and_bulk(fc, name, n_src):
                 a, b = y.t.cpu().numpy().view(np.uint16), tile_tokens(want, reps).view(np.uint16)
                 assert same_bits(a, b), "%s N=%d %dx%d g=%d %d->%d x%d: %s" % (name, n_src, t, h, g, bits_rs, bits_ag, reps,
                                                                               first_diff(a, b))
+
+
+@pytest.mark.parametrize("name", ["asym"] + list(PAIRS))
+@pytest.mark.parametrize("n_src,limit", [(4, 1 << 20), (7, (6 << 20) // 7), (8, 1 << 20)])
+def test_allreduce_at_the_limit_of_the_launch_bound_kernel(fc, name, n_src, limit):
+    # the largest volume of the launch-bound kernel and the next row on the bulk kernel, from a few rows of every kind
+    t, h, g = 6, 1024, 128
+    bits = () if name == "fp8" else (4, 8)
+    sfx = "" if name == "asym" else "_" + name
+    x = np.concatenate([synth_inputs.make_partials_stress(n_src, 1, h, k % synth_inputs.STRESS_KINDS, seed=k + n_src)
+                        for k in range(t)], axis=1)
+    want = dev(getattr(oracle, "allreduce_sim" + sfx)(x, g, *bits).view(np.int16))
+    few = dev(x.view(np.uint16)).view(torch.float16)
+    for rows in (limit // h, limit // h + 1):
+        pick = torch.arange(rows, device="cuda") % t
+        y = Guarded((rows, h), torch.float16)
+        getattr(fc, "allreduce_sim" + sfx)(few[:, pick], g, *bits, out=y.t)
+        torch.cuda.synchronize()
+        y.check()
+        assert torch.equal(y.t.view(torch.int16), want[pick]), "%s N=%d rows=%d" % (name, n_src, rows)
