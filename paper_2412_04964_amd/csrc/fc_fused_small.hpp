@@ -11,22 +11,32 @@
 #pragma once
 
 #include "fc_device.hpp"
+#include "fc_launch.hpp"
 
 namespace fc {
 
 constexpr int fused_small_lane_elems(int bits_in) { return 32 / bits_in; }
 constexpr int fused_small_wave_elems(int bits_in) { return 64 * fused_small_lane_elems(bits_in); }
-// Up to this many wavefronts (eight per compute unit of the part) the launch is latency-bound and this kernel wins
+// Up to this many wavefronts (eight per compute unit of the part) the asymmetric quantizer's launch is latency-bound and this kernel wins
 // (decode shape, N = 8 at 8 bit: 2.63 -> 2.14 us per launch under graph replay; the two forms cross between 2048
 // and 4096 wavefronts).  The other quantizers the same way (N = 8, hidden 8192, g = 128, bulk -> this one): symmetric 4 bit
 // 3.46 -> 2.29 us at 8 tokens, 3.79 -> 2.77 at 64, 3.95 -> 3.35 at 128 (the limit); compact metadata 3.64 -> 2.36, 3.88 -> 2.90,
 // 4.06 -> 3.71; FP8 2.67 -> 2.18 at 8 tokens, 3.16 -> 2.99 at 64 (its limit).
 constexpr int kFusedSmallMaxWaves = 2048;
 
-inline bool fused_small_applies(int bits_in, int64_t n_elems, int group)
+// The other quantizers' bulk kernels read less metadata.  With few sources, and groups of 32 lanes and more to reduce here, they are
+// the faster ones from fewer wavefronts on (hidden 2048, g = 256, 2048 wavefronts, bulk / this one: 8 -> 8 bit, N = 2, symmetric
+// 2.37 / 2.57 us, FP8 2.32 / 2.58, compact metadata 2.50 / 2.72; N = 4 2.72 / 2.83 with compact metadata; N = 2 at 4 bit
+// 2.53 / 2.72, 2.74 / 2.89; but g = 32, 8 -> 8 bit, N = 3, compact metadata 2.74 / 2.59).  The forms cross at about 448
+// wavefronts per source at 8 bit and twice that at 4 bit.
+constexpr int kFusedSmallWavesPerSource = 448;
+
+inline bool fused_small_applies(int codec, int bits_in, int n_src, int64_t n_elems, int group)
 {
-    return group <= fused_small_wave_elems(bits_in) &&
-           (n_elems + fused_small_wave_elems(bits_in) - 1) / fused_small_wave_elems(bits_in) <= kFusedSmallMaxWaves;
+    const int64_t waves = (n_elems + fused_small_wave_elems(bits_in) - 1) / fused_small_wave_elems(bits_in);
+    if (group > fused_small_wave_elems(bits_in) || waves > kFusedSmallMaxWaves) return false;
+    if (codec == CODEC_ASYM || group < 32 * fused_small_lane_elems(bits_in)) return true;
+    return waves <= n_src * kFusedSmallWavesPerSource * (8 / bits_in);
 }
 
 // Codes of the lane as numbers, before the scale: q - z, the signed code, or the value of the E4M3 byte

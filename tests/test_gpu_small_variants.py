@@ -62,6 +62,30 @@ def test_fused_small_and_bulk(fc, name, n_src):
 
 
 @pytest.mark.parametrize("name", list(PAIRS))
+@pytest.mark.parametrize("n_src", [1, 2, 3, 4, 5, 8])
+def test_fused_at_the_limit_of_the_launch_bound_kernel(fc, name, n_src):
+    # the largest volume of the launch-bound kernel (a number of wavefronts, by fan-in where a group spans 32 lanes) and the next row on the bulk kernel
+    t, h = 6, 1024
+    meta_type = torch.int32 if name == "cmeta" else torch.float32
+    for (bits_in, bits_out), lanes in [(p, l) for p in PAIRS[name] for l in (16, 32)]:
+        g = lanes * 32 // bits_in
+        bits = () if name == "fp8" else (bits_in, bits_out)
+        c, m = wire(name, n_src, t, h, g, bits_in, seed=n_src)
+        want = [dev(np.ascontiguousarray(a).view(np.uint8)) for a in getattr(oracle, "dequant_reduce_requant_" + name)(c, m, h, g, *bits)]
+        few_c, few_m = dev(c), dev(m.view(np.int32)) if name == "cmeta" else dev(m)
+        limit = (2048 if lanes < 32 else min(2048, 448 * n_src * (8 // bits_in))) * (2048 // bits_in)      # elements
+        for rows in (limit // h, limit // h + 1):
+            pick = torch.arange(rows, device="cuda") % t
+            co = Guarded((rows, h * bits_out // 8), torch.uint8)
+            mo = Guarded((rows, h // g), meta_type)
+            getattr(fc, "dequant_reduce_requant_" + name)(few_c[:, pick], few_m[:, pick], h, g, *bits, out=(co.t, mo.t))
+            torch.cuda.synchronize()
+            for got, w in zip((co, mo), want):
+                got.check()
+                assert torch.equal(got.t.view(torch.uint8), w[pick]), "%s N=%d %d->%d rows=%d" % (name, n_src, bits_in, bits_out, rows)
+
+
+@pytest.mark.parametrize("name", list(PAIRS))
 @pytest.mark.parametrize("n_src", [1, 2, 4, 7, 8])
 def test_allreduce_small_and_bulk(fc, name, n_src):
     ref, gpu = getattr(oracle, "allreduce_sim_" + name), getattr(fc, "allreduce_sim_" + name)
