@@ -1155,8 +1155,9 @@ __global__ __launch_bounds__(quantize_block_threads(BITS, LPG)) void k_quantize(
 // WRAP: 0 in the library.  The benchmark aid instantiates WRAP > 0, which makes every workgroup work on tile
 // (its tile % WRAP): the instruction stream of a full launch with its memory traffic confined to a few tiles that
 // stay in the L2, i.e. the time the kernel's arithmetic takes when HBM is out of the picture.
+// SHORT: 4-bit codes by accumulate_fast whatever the fan-in, for launches of at most one workgroup per compute unit.
 template <int BITS_IN, int BITS_OUT, int NSRC, int LPG, bool HM = false, int BT = fused_block_threads(LPG),
-          int WRAP = 0>
+          int WRAP = 0, bool SHORT = false>
 __global__ __launch_bounds__(BT) void k_dequant_reduce_requant(
     const uint8_t *__restrict__ codes_in, int64_t codes_stride,
     const float *__restrict__ scales_in, const float *__restrict__ zeros_in, int64_t meta_stride,
@@ -1177,12 +1178,16 @@ __global__ __launch_bounds__(BT) void k_dequant_reduce_requant(
     constexpr bool kSpansWaves = LPG > 64;                    // a group takes more than one wavefront
     constexpr int K = (entries + 63) / 64;                    // table entries per lane
     // 4-bit codes, up to 4 sources: accumulate_nibbles.  It has more instructions of fewer cycles, which pays while 8
-    // wavefronts share a SIMD; landing zones and registers leave fewer from 5 sources on.  8192 x 8192, INT4, us before
-    // and after, g = 128 / 1024: N = 2 24.4 -> 22.3 / 22.4 -> 21.3, N = 4 32.5 -> 31.1 / 32.6 -> 31.4, but N = 5
-    // 39.4 -> 40.7 / 38.8 -> 38.4, N = 6 44.3 -> 46.4 / 43.9 -> 44.8, N = 8 55.2 -> 58.7 / 53.9 -> 55.9.  Between other
-    // kernels (bench.py, N = 4, g = 128) the times spread more: fastest step 30.1 -> 29.7, median 30.71 -> 30.64, but
-    // one step in twenty takes 33 to 37 us, cause not found, and the mean goes from 30.77 to 31.02.
-    constexpr bool kNibbles = BITS_IN == 4 && NSRC <= 4;
+    // wavefronts share a SIMD; landing zones and registers leave fewer from 5 sources on, and a wavefront that is alone on
+    // its SIMD waits for the longer chain (SHORT).  8192 x 8192, us, accumulate_fast -> accumulate_nibbles, medians of
+    // replayed graphs over buffers that rotate through 1.2 GB: g = 128, INT4 N = 1 18.2 -> 16.4, N = 2 25.5 -> 21.4, N = 3
+    // 30.4 -> 25.9, N = 4 34.2 -> 30.2; 4 -> 8 bit 21.5 -> 19.2, 27.6 -> 24.2, 32.8 -> 29.2, 36.8 -> 34.5; compact metadata
+    // N = 4 34.1 -> 30.1 and 35.9 -> 33.6; g = 1024 N = 4 34.8 -> 29.8; g = 32 equal.  But N = 5 39.4 -> 40.7, N = 6 44.3 ->
+    // 46.4, N = 8 55.2 -> 58.7.  Between other kernels (bench.py, N = 4, g = 128) the gain is small, mean 30.72 -> 30.65 us over
+    // ten runs each in turn, with a wider spread of the steps (half of them in 30.4 to 31.0 -> 30.2 to 31.5); in one session of
+    // nine, possibly on another card, four runs each in turn gave 31.8 -> 36.2 and the cause was not found (shader clock and
+    // temperature do not move in the others).
+    constexpr bool kNibbles = BITS_IN == 4 && NSRC <= 4 && !SHORT;
     struct MetaRec { float s; u32 z; };                       // z: fp32 bits; packed halves for accumulate_fast
 
     __shared__ __attribute__((aligned(16))) uint8_t landing[kWaves][NSRC][1024];

@@ -34,6 +34,23 @@ static hipError_t launch_nl(const FusedArgs &a, hipStream_t stream)
                 a.n_elems, log2_int(a.group),
                 static_cast<uint8_t *>(a.codes_out), a.scales_out);
     }
+    // Groups too wide for fc_fused_small.hpp, at most one workgroup per compute unit: the shorter chain of instructions
+    // (hidden 8192, 8 to 128 tokens, us under graph replay, accumulate_nibbles / accumulate_fast: g = 1024, INT4 N = 4
+    // 3.29 / 3.14 at 8 tokens, 3.38 / 3.23 at 128, but 3.69 / 3.91 at 160, where a second workgroup comes in; N = 3 4 -> 8 bit
+    // 3.27 / 3.11 at 128, compact metadata N = 4 3.38 / 3.14; g = 8192 3.59 / 3.47 at 256 tokens, 3.99 / 4.14 at 384).
+    if constexpr (FC_BITS_IN == 4 && NSRC <= 4 && LPG >= 32) {
+        constexpr int kComputeUnits = 256;
+        if (blocks <= kComputeUnits && a.codec == CODEC_ASYM)
+            return launch_kernel(k_dequant_reduce_requant<FC_BITS_IN, FC_BITS_OUT, NSRC, LPG, false, BT, 0, true>, dim3((unsigned)blocks), dim3(BT), stream,
+                    static_cast<const uint8_t *>(a.codes_in), a.codes_stride, a.scales_in, a.zeros_in,
+                    a.meta_stride, a.n_elems, log2_int(a.group),
+                    static_cast<uint8_t *>(a.codes_out), a.scales_out, a.zeros_out);
+        if (blocks <= kComputeUnits && a.codec == CODEC_ASYMH)
+            return launch_kernel(k_dequant_reduce_requant<FC_BITS_IN, FC_BITS_OUT, NSRC, LPG, true, BT, 0, true>, dim3((unsigned)blocks), dim3(BT), stream,
+                    static_cast<const uint8_t *>(a.codes_in), a.codes_stride, a.scales_in, nullptr,
+                    a.meta_stride, a.n_elems, log2_int(a.group),
+                    static_cast<uint8_t *>(a.codes_out), a.scales_out, nullptr);
+    }
     if (a.codec == CODEC_ASYMH) {
         return launch_kernel(k_dequant_reduce_requant<FC_BITS_IN, FC_BITS_OUT, NSRC, LPG, true>, dim3((unsigned)blocks), dim3(BT), stream,
                 static_cast<const uint8_t *>(a.codes_in), a.codes_stride, a.scales_in, nullptr,

@@ -85,6 +85,40 @@ def test_fused_at_the_limit_of_the_launch_bound_kernel(fc, name, n_src):
                 assert torch.equal(got.t.view(torch.uint8), w[pick]), "%s N=%d %d->%d rows=%d" % (name, n_src, bits_in, bits_out, rows)
 
 
+@pytest.mark.parametrize("name", ["asym", "cmeta"])
+@pytest.mark.parametrize("n_src", [1, 2, 3, 4])
+@pytest.mark.parametrize("group", [1024, 2048, 4096, 8192])
+def test_fused_wide_groups_with_one_workgroup_per_compute_unit(fc, name, n_src, group):
+    # 4-bit codes, at most 256 workgroups (4096 elements each, 8192 for the widest groups): another fold than above that.
+    # Rows with ordinary, huge, fractional and out-of-reach metadata.
+    t, sfx = 5, "" if name == "asym" else "_cmeta"
+    rng = np.random.default_rng(group + n_src)
+    x = synth_inputs.make_partials(n_src, t, group, seed=group + n_src)
+    parts = [getattr(oracle, "quantize" + sfx)(x[j], group, 4) for j in range(n_src)]
+    wire = [np.stack(p) for p in zip(*parts)]
+    wire[0][:] = rng.integers(0, 256, size=wire[0].shape, dtype=np.uint8)
+    if name == "asym":
+        wire[1][:, 1], wire[2][:, 2], wire[2][-1, 3], wire[2][0, 4] = 2.0 ** 105, 2.5, 5000.0, -1700.0
+    else:
+        halves = wire[1].view(np.uint16).reshape(n_src, t, -1, 2)
+        halves[:, 2, :, 1], halves[-1, 3, :, 1] = np.float16(2.5).view(np.uint16), np.float16(5000.0).view(np.uint16)
+    few = [dev(w.view(np.int32) if w.dtype == np.uint32 else w) for w in wire]
+    for bits_out in (4, 8):
+        want = [dev(np.ascontiguousarray(a).view(np.uint8))
+                for a in getattr(oracle, "dequant_reduce_requant" + sfx)(*wire, group, group, 4, bits_out)]
+        limit = 256 * (8192 if group == 8192 else 4096)
+        for rows in (1, limit // group, limit // group + 1, 2 * limit // group + 3):
+            pick = torch.arange(rows, device="cuda") % t
+            outs = [Guarded((rows, group * bits_out // 8), torch.uint8)]
+            outs += [Guarded((rows, 1), few[1].dtype) for _ in few[1:]]
+            getattr(fc, "dequant_reduce_requant" + sfx)(*[w[:, pick] for w in few], group, group, 4, bits_out,
+                                                        out=tuple(o.t for o in outs))
+            torch.cuda.synchronize()
+            for got, w in zip(outs, want):
+                got.check()
+                assert torch.equal(got.t.view(torch.uint8), w[pick]), "%s N=%d g=%d ->%d rows=%d" % (name, n_src, group, bits_out, rows)
+
+
 @pytest.mark.parametrize("name", list(PAIRS))
 @pytest.mark.parametrize("n_src", [1, 2, 4, 7, 8])
 def test_allreduce_small_and_bulk(fc, name, n_src):
