@@ -222,8 +222,14 @@ __device__ __forceinline__ void rot_unpack(const u32 (&word)[4][BITS / 4], float
     }
 }
 
+// Wavefronts per SIMD to leave registers for: left to itself the compiler keeps temporaries of the exact form.  Seven would make
+// the asymmetric 8-bit kernel of blocks of 2048 spill (8192 x 2048, g = 128: 11.1 us, with six 10.5).
+constexpr int rot_dequantize_waves(int bits, int codec, int lb)
+{
+    return lb >= 12 ? 8 : lb == 11 && bits == 8 && codec == kAsym ? 6 : 7;
+}
+
 // Dequantize, rotate back block by block and round to binary16 (last step of Algorithm 1).
-// Registers for seven or eight wavefronts per SIMD: left to itself the compiler keeps temporaries of the exact form.
 //
 // Zeros: stages 3-6 lose the sign of a zero in the signed frame.  Where every zero-point of the wavefront is an
 // integer in reach of the short form and every scale is a normal positive number, no value of the contract is ever -0
@@ -232,7 +238,7 @@ __device__ __forceinline__ void rot_unpack(const u32 (&word)[4][BITS / 4], float
 // always does.  Wavefronts of one block tell each other with the exchange which form they took, so that a zero of
 // either sign meets only exact ones.
 template <int BITS, int CODEC, int LB>
-__global__ __launch_bounds__(64 * rot_group_waves(LB)) __attribute__((amdgpu_waves_per_eu(LB <= 11 ? 7 : 8))) void k_dequantize_rot(
+__global__ __launch_bounds__(64 * rot_group_waves(LB)) __attribute__((amdgpu_waves_per_eu(rot_dequantize_waves(BITS, CODEC, LB)))) void k_dequantize_rot(
     const uint8_t *__restrict__ codes, const float *__restrict__ scales, const float *__restrict__ zeros,
     int64_t n_elems, int group_shift, uint16_t *__restrict__ y)
 {

@@ -29,6 +29,24 @@ def code_objects(path):
         at = blob.find(BUNDLE, at + 24)
 
 
+def test_no_kernel_uses_scratch_memory(tmp_path):
+    # a register that spills goes through memory in every wavefront; one of the rotated dequantizers was 1 to 5 % slower for it
+    tool = os.path.join(LLVM, "llvm-readelf")
+    if not os.path.exists(tool):
+        pytest.skip("no llvm-readelf beside the compiler")
+    seen, elf = 0, tmp_path / "code.elf"
+    for image in code_objects(build.LIB):
+        elf.write_bytes(image)
+        notes = subprocess.run([tool, "--notes", str(elf)], check=True, capture_output=True, text=True).stdout
+        names = re.findall(r"\.name:\s+(_Z\S+)", notes)
+        scratch = re.findall(r"\.private_segment_fixed_size:\s+(\d+)", notes)
+        assert len(names) == len(scratch)
+        spilled = [n for n, size in zip(names, scratch) if int(size)]
+        assert not spilled, spilled[0]
+        seen += len(names)
+    assert seen > 0
+
+
 @pytest.fixture(scope="module")
 def kernels(tmp_path_factory):
     """{mangled name: [instruction, ...]} of every kernel of the library"""
