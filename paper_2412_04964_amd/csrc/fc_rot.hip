@@ -389,15 +389,16 @@ hipError_t dequantize_rot_h(int log_b, const uint8_t *c, const float *scales, co
 }
 
 // Whether the form of fc_rot_rows.hip is the faster one (its header has both sides' times): at 8 bit, where a wavefront here has
-// twice the work of one there, up to 2^21 elements, blocks of 4096 up to 3 * 2^20.  At 4 bit a wavefront has the same 2048
-// elements in both forms, and the register form is as fast or faster for blocks of 2048 and for the quantizer of blocks of 1024
-// while it has one workgroup per compute unit (2^20 elements).  The 4-bit quantizer of blocks of 1024, whose codes leave in
-// 32-bit stores here and in 128-bit stores there, crosses once more, between 2^23 and 2^25 elements.
-bool rot_rows_apply(bool quantize, int bits, int log_b, int64_t n_elems)
+// twice the work of one there, up to 2^21 elements, blocks of 4096 up to 3 * 2^20, FP8 there up to 2^22 (5.4 against 5.7 us to
+// dequantize).  At 4 bit a wavefront has the same 2048 elements in both forms, and the register form is as fast or faster for
+// blocks of 2048 and for the quantizer of blocks of 1024 while it has one workgroup per compute unit (2^20 elements).  The 4-bit
+// quantizer of blocks of 1024, whose codes leave in 32-bit stores here and in 128-bit stores there, crosses once more, between
+// 2^23 and 2^25 elements.
+bool rot_rows_apply(bool quantize, int codec, int bits, int log_b, int64_t n_elems)
 {
     constexpr int64_t k1M = (int64_t)1 << 20;
     if (log_b > 12) return false;
-    if (n_elems <= (log_b == 12 ? 3 : 2) * k1M)
+    if (n_elems <= (log_b < 12 ? 2 : codec == CODEC_FP8 ? 4 : 3) * k1M)
         return bits == 8 || log_b == 12 || (log_b == 10 && !quantize) || n_elems > k1M;
     return quantize && bits == 4 && log_b == 10 && n_elems > 16 * k1M;
 }
@@ -411,7 +412,7 @@ hipError_t launch_quantize_rot(int bits, int codec, const void *x_f16, int64_t t
     uint8_t *c = static_cast<uint8_t *>(codes);
     const int lb = log2_int(rotation_block(hidden));
     const int64_t n = tokens * hidden;
-    if (rot_rows_apply(true, bits, lb, n))
+    if (rot_rows_apply(true, codec, bits, lb, n))
         return launch_quantize_rot_rows(bits, codec, x_f16, n, lb, group, codes, scales, zeros, stream);
     if (codec == CODEC_FP8)
         return bits == 8 ? quantize_rot_h<8, kFp8>(lb, x, n, group, c, scales, nullptr, stream)
@@ -430,7 +431,7 @@ hipError_t launch_dequantize_rot(int bits, int codec, const void *codes, const f
     uint16_t *y = static_cast<uint16_t *>(y_f16);
     const int lb = log2_int(rotation_block(hidden));
     const int64_t n = tokens * hidden;
-    if (rot_rows_apply(false, bits, lb, n))
+    if (rot_rows_apply(false, codec, bits, lb, n))
         return launch_dequantize_rot_rows(bits, codec, codes, scales, zeros, n, lb, group, y_f16, stream);
     if (codec == CODEC_FP8)
         return bits == 8 ? dequantize_rot_h<8, kFp8>(lb, c, scales, nullptr, n, group, y, stream)
