@@ -82,11 +82,6 @@ def cpu_model():
     return "unknown"
 
 
-# VALU issue peak of the part: 256 compute units x 4 SIMDs at 2.4 GHz, one wave64 instruction per SIMD every 2 cycles
-# (fp32 add, multiply, FMA and bitwise operations; conversions, min / max, shifts and packed binary16 take 4)
-VALU_PEAK_WAVE_INSTR_PER_S = 256 * 4 * 2.4e9 / 2
-
-
 def cpu_baseline(w, x_host, budget_s=20.0):
     """The oracle's fused step on the host, single thread, full volume if it fits
     the time budget (else the leading rows)."""
@@ -348,11 +343,11 @@ def main():
         probe_s = p0.elapsed_time(p1) * 1e-3 / p_reps
         del PC, PS, PZ
 
-    # The whole all-reduce as the library runs it (fc_allreduce_sim and its counterparts): with groups of at
-    # most 1024 elements that is ONE launch which reads the N partials and writes the result, nothing else.  Timed
-    # over the same rotating buffer sets; launch-bound volumes replay a HIP graph of B calls like the stages above.
+    # The whole all-reduce as the library runs it (fc_allreduce_sim and its counterparts): without rotation that is
+    # ONE launch which reads the N partials and writes the result, nothing else.  Timed over the same rotating
+    # buffer sets; launch-bound volumes replay a HIP graph of B calls like the stages above.
     sim_s = None
-    if not w.rotate and g <= 1024:
+    if not w.rotate:
         WS = torch.empty(max(16, fc.allreduce_sim_workspace_bytes(N, T, H, g, w.bits_in, w.bits_out)),
                          dtype=torch.uint8, device=dev)
 
@@ -507,9 +502,10 @@ def main():
                 "bound": "alu", "unit": "wave64 VALU instructions/s",
                 "instructions_per_launch": valu,
                 "instructions_source": "stored constant: profiles/traffic_%s.txt (rocprofv3 --pmc SQ_INSTS_VALU)" % w.name,
-                "achieved": round(rate, 1), "peak": VALU_PEAK_WAVE_INSTR_PER_S,
-                "frac": round(rate / VALU_PEAK_WAVE_INSTR_PER_S, 4),
-                "what": "peak = 256 CUs x 4 SIMDs x 2.4 GHz / 2 cycles per wave64 fp32 instruction",
+                "achieved": round(rate, 1),
+                "what": "a count, not a share of a peak: a wave64 instruction issues in 2 cycles (fp32 add, multiply, FMA, "
+                        "bitwise) or 4 (conversions, min / max, shifts, packed binary16) of its SIMD; fused_over_compute_only "
+                        "above is the share that the arithmetic could take",
             }
     # the paper's own figures: other hardware (L40, A100) and other quantities (end-to-end all-reduce latency
     # against NCCL, time to first token), quoted as context only, never as a baseline for `value`
