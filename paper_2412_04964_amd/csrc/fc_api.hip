@@ -294,16 +294,32 @@ int three_steps(bool rotate, int codec, const void *x_f16, int n_src, int64_t to
 }
 
 // Whether the three steps are the faster form of the rotated all-reduce.  The one launch works through the sources one after
-// the other, 2.2 us each (FP8 2.5) until the chip is full; the three steps take 10 us, their quantizations spread over the chip.  Hidden
-// 8192, group 128, INT4, three steps / one launch, us under graph replay: N = 8, 1 token 10.2 / 18.5, 32 11.3 / 21.2, 128 15.9 / 18.9,
-// 192 20.0 / 20.0, 256 22.4 / 20.1; N = 4, 8 tokens 10.3 / 11.4, 96 12.3 / 12.4, 128 12.6 / 11.6; N = 3 10.2 / 9.7.  FP8: N = 8,
-// 8 tokens 10.8 / 23.1, 256 23.3 / 24.9; N = 3, 8 tokens 10.7 / 11.3, 64 11.6 / 11.4.  Where the slabs need padding every
-// partial is a launch of its own: N = 8, one token, group 8192 35.5 / 20.0.
-bool rot_steps_apply(const SimLayout &L, int codec, int n_src, int64_t n_elems, int group, int bits_rs)
+// the other, 1.4 us each in blocks of up to 2048 elements, 2.2 us in blocks of 8192 (FP8 1.8 / 2.4), until the chip is full; the
+// three steps take 8 to 10 us, their quantizations spread over the chip.  Up to this many elements, in units of 2^16, by the
+// block and the number of sources, the steps are faster; the line lies where the larger loss on either side is smallest.  Group
+// 128, three steps / one launch, us under graph replay:
+//   INT4, block 2048: N = 4, 256 K elements 9.2 / 9.9, 384 K 9.8 / 9.3; N = 5, 512 K 10.6 / 11.4, 768 K 11.2 / 11.1; N = 8, 1536 K
+//     19.0 / 21.8, 2048 K 21.7 / 22.1.  Six sources cross more than once: 1024 K 13.6 / 12.9, 1536 K 16.9 / 17.7.
+//   INT4, block 4096: N = 4, 256 K 9.9 / 11.4, 768 K 11.5 / 11.0; N = 8, 2048 K 23.1 / 24.3.
+//   INT4, block 8192: N = 3, 8 K 9.4 / 9.0; N = 4, 512 K 10.7 / 11.3, 1024 K 12.9 / 12.2; N = 8, 8 K 9.7 / 17.9, 2048 K 22.8 / 21.5.
+//   FP8, block 2048: N = 2, 2 K 7.2 / 7.0; N = 3, 256 K 8.5 / 9.4, 768 K 10.7 / 9.4; N = 8, 2048 K 21.0 / 27.2.
+//   FP8, block 8192: N = 3, 256 K 10.7 / 11.1, 768 K 12.7 / 11.5; N = 8, 2048 K 23.6 / 26.2.
+// Groups of 1024 elements and more cost the steps another 0.9 us, the one launch 0.4: four sources of short blocks never cross
+// then (64 K 10.0 / 9.4), in blocks of 4096 earlier (256 K 10.9 / 10.8).  Where the slabs need padding every partial is a launch
+// of its own: N = 8, one token of 8192, group 8192 35.5 / 20.0.
+bool rot_steps_apply(const SimLayout &L, int codec, int n_src, int64_t n_elems, int64_t hidden, int group, int bits_rs)
 {
+    //                                           n_src 3  4   5   6   7   8
+    static constexpr unsigned char kLimit[2][3][6] = {{{0, 4, 8, 24, 28, 32}, {0, 8, 28, 32, 32, 32}, {0, 8, 16, 18, 21, 28}},
+                                                      {{7, 28, 32, 34, 40, 40}, {8, 32, 40, 40, 44, 48}, {6, 18, 24, 40, 44, 48}}};
+    static_assert(FC_MAX_SRC == 8, "one column per fan-in");
+    if (n_src < 3 || !slabs_are_dense(L, n_elems, group, bits_rs)) return false;
     const bool fp8 = codec == fc::CODEC_FP8;
-    return n_src >= (fp8 ? 3 : 4) && n_elems <= ((int64_t)n_src * (fp8 ? 4 : 3) << 16) &&
-           slabs_are_dense(L, n_elems, group, bits_rs);
+    const int block = fc::rotation_block(hidden);
+    const int row = block == 8192 ? 2 : block == 4096 ? 1 : 0;
+    int limit = kLimit[fp8][row][n_src - 3];
+    if (!fp8 && n_src == 4 && group >= 1024 && row < 2) limit = 4 * row;
+    return n_elems <= (int64_t)limit << 16;
 }
 
 }  // namespace
@@ -502,7 +518,7 @@ int fc_allreduce_sim_rot(const void *x_f16, int n_src, int64_t tokens, int64_t h
     if (!workspace || workspace_bytes < L.total) return FC_ERR_WORKSPACE;
     if (!aligned16(workspace)) return FC_ERR_ALIGN;
 
-    if (rot_steps_apply(L, quantizer, n_src, n, group, bits_rs))
+    if (rot_steps_apply(L, quantizer, n_src, n, hidden, group, bits_rs))
         return three_steps(true, quantizer, x_f16, n_src, tokens, hidden, group, bits_rs, bits_ag, y_f16, L, workspace,
                            hip_stream);
     // one kernel; nothing goes through the workspace

@@ -183,12 +183,15 @@ def test_both_forms_give_the_same_bits(fc, quantizer, bits, hidden):
 
 @pytest.mark.parametrize("quantizer,n_src", [(oracle.ASYM, 3), (oracle.ASYM, 4), (oracle.ASYM, 8), (oracle.SYM, 5), (oracle.SYM, 8),
                                              (oracle.FP8, 2), (oracle.FP8, 3), (oracle.FP8, 8)])
-@pytest.mark.parametrize("hidden", [1024, 3072, 8192])
+@pytest.mark.parametrize("hidden", [1024, 3072, 4096, 8192])
 def test_allreduce_sim_rot_on_both_sides_of_the_limit(fc, quantizer, n_src, hidden):
-    # up to n_src * 3 * 2^16 elements (FP8: 2^18) the three steps run, through the workspace, above it one kernel; slabs of a
-    # length that needs padding always take the kernel.  A few rows (compared with the oracle) are repeated up to the limit.
+    # up to a limit (2^16 elements; by block, code and number of sources) the three steps run, through the workspace, above it
+    # one kernel, which leaves the workspace alone; slabs of a length that needs padding always take the kernel.  A few rows
+    # (compared with the oracle) are repeated up to the limit.
     bits = 8 if quantizer == oracle.FP8 else 4
-    limit = n_src * ((4 if quantizer == oracle.FP8 else 3) << 16)
+    column = n_src - 3
+    limit = {1024: ((0, 4, 8, 24, 28, 32), (7, 28, 32, 34, 40, 40)), 4096: ((0, 8, 28, 32, 32, 32), (8, 32, 40, 40, 44, 48)),
+             8192: ((0, 8, 16, 18, 21, 28), (6, 18, 24, 40, 44, 48))}[hidden & -hidden][bits == 8][column] << 16 if column >= 0 else 0
     x = synth_inputs.make_partials(n_src, 5, hidden, seed=hidden + n_src)
     x[:, 1] = 0
     x[0, 2] = np.float16(6e-8) * (np.arange(hidden) % 5)
@@ -196,7 +199,9 @@ def test_allreduce_sim_rot_on_both_sides_of_the_limit(fc, quantizer, n_src, hidd
     few = dev(x.view(np.uint16)).view(torch.float16)
     for group in (128, 1024):
         want = dev(oracle.allreduce_sim_rot(x, group, bits, bits, quantizer).view(np.int16))
-        for rows in (1, 2, 5, 12, limit // hidden, limit // hidden + 1, limit // hidden + 3):
+        if n_src == 4 and group == 1024 and hidden < 8192:
+            limit = {1024: 0, 4096: 4 << 16}[hidden & -hidden]
+        for rows in sorted({1, 2, 5, 12, limit // hidden, limit // hidden + 1, limit // hidden + 4} - {0}):
             pick = torch.arange(rows, device="cuda") % 5
             need = fc.allreduce_sim_workspace_bytes(n_src, rows, hidden, group, bits, bits)
             space = torch.full((need + 64,), 0xA5, dtype=torch.uint8, device="cuda")
@@ -204,6 +209,8 @@ def test_allreduce_sim_rot_on_both_sides_of_the_limit(fc, quantizer, n_src, hidd
             fc.allreduce_sim_rot(few[:, pick], group, bits, bits, quantizer, out=y.t, workspace=space[:need])
             torch.cuda.synchronize(); y.check()
             assert (space[need:] == 0xA5).all(), "written past the workspace"
+            steps = rows * hidden <= limit and rows * hidden // group % 4 == 0
+            assert bool((space[:need] != 0xA5).any()) == steps, "N=%d h=%d g=%d rows=%d: form" % (n_src, hidden, group, rows)
             assert torch.equal(y.t.view(torch.int16), want[pick]), "N=%d h=%d g=%d rows=%d" % (n_src, hidden, group, rows)
 
 
