@@ -28,13 +28,17 @@ constexpr int kFusedSmallMaxWaves = 2048;
 // the faster ones from fewer wavefronts on (hidden 2048, g = 256, 2048 wavefronts, bulk / this one: 8 -> 8 bit, N = 2, symmetric
 // 2.37 / 2.57 us, FP8 2.32 / 2.58, compact metadata 2.50 / 2.72; N = 4 2.72 / 2.83 with compact metadata; N = 2 at 4 bit
 // 2.53 / 2.72, 2.74 / 2.89; but g = 32, 8 -> 8 bit, N = 3, compact metadata 2.74 / 2.59).  The forms cross at about 448
-// wavefronts per source at 8 bit and twice that at 4 bit.
+// wavefronts per source at 8 bit and twice that at 4 bit.  A volume of at most three workgroups of the bulk kernel starts sooner
+// there than as 24 of these (8 bit, one row of 4096, N = 1, FP8 2.24 / 2.40 us, symmetric 2.23 / 2.39; N = 3 2.27 / 2.37; compact
+// metadata N = 2 2.37 / 2.34; 6144: FP8 N = 3 2.28 / 2.39; 7168: 2.41 / 2.41); from four sources on its chain is too long.
 constexpr int kFusedSmallWavesPerSource = 448;
+constexpr int kFusedSmallMinWaves = 24;
 
 inline bool fused_small_applies(int codec, int bits_in, int n_src, int64_t n_elems, int group)
 {
     const int64_t waves = (n_elems + fused_small_wave_elems(bits_in) - 1) / fused_small_wave_elems(bits_in);
     if (group > fused_small_wave_elems(bits_in) || waves > kFusedSmallMaxWaves) return false;
+    if (codec != CODEC_ASYM && bits_in == 8 && n_src <= (codec == CODEC_ASYMH ? 1 : 3) && waves <= kFusedSmallMinWaves) return false;
     if (codec == CODEC_ASYM || group < 32 * fused_small_lane_elems(bits_in)) return true;
     return waves <= n_src * kFusedSmallWavesPerSource * (8 / bits_in);
 }

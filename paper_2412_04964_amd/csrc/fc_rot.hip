@@ -388,19 +388,30 @@ hipError_t dequantize_rot_h(int log_b, const uint8_t *c, const float *scales, co
     }
 }
 
-// Whether the form of fc_rot_rows.hip is the faster one (its header has both sides' times): at 8 bit, where a wavefront here has
-// twice the work of one there, up to 2^21 elements, blocks of 4096 up to 3 * 2^20, FP8 there up to 2^22 (5.4 against 5.7 us to
-// dequantize).  At 4 bit a wavefront has the same 2048 elements in both forms, and the register form is as fast or faster for
-// blocks of 2048 and for the quantizer of blocks of 1024 while it has one workgroup per compute unit (2^20 elements).  The 4-bit
-// quantizer of blocks of 1024, whose codes leave in 32-bit stores here and in 128-bit stores there, crosses once more, between
-// 2^23 and 2^25 elements.
+// Whether the form of fc_rot_rows.hip is the faster one (its header has both sides' times).  At 8 bit, where a wavefront here has
+// twice the work of one there, up to 5 * 2^19 elements, FP8 3 * 2^20 (2.5 M: INT8 dequantize, blocks of 2048 3.83 / 3.98; FP8
+// 3.73 / 4.05; 3 M 4.21 / 4.13 and 4.10 / 4.22), blocks of 4096 up to 3 * 2^20, FP8 there up to 2^22.  At 4 bit a wavefront has
+// the same 2048 elements in both forms, and the register form is as fast or faster for blocks of 2048 while it has one workgroup
+// per compute unit (2^20 elements).  The 4-bit quantizer of blocks of 1024, whose codes leave in 32-bit stores here and in 128-bit
+// stores there, crosses at 3 * 2^20 (2.5 M 3.90 / 4.06, 4 M 4.78 / 4.66) and once more between 2^23 and 2^25 elements.
+// With the third wavefront per SIMD of the register form, above 2^22 elements and mostly above 5 * 2^20, the row form is the
+// faster one again for a while, us per launch, rows / registers: 4 bit quantize, blocks of 1024 5.3 M 5.43 / 6.03, 6.6 M
+// 6.17 / 6.33, 7.3 M 6.40 / 6.41; 2048 5 M 5.80 / 5.79, 5.3 M 6.01 / 6.59, 6.3 M 6.76 / 6.77; 4096 4.1 M 5.61 / 5.83, 6 M 6.56 / 6.95, 6.6 M
+// 7.05 / 7.08; 8 bit quantize, 2048 5.6 M 6.46 / 6.60, 4096 6.73 / 6.90, but 1024 6.44 / 6.24; 4 bit dequantize, 1024 5.6 M
+// 4.94 / 5.12, 2048 5.62 / 5.45; FP8 quantize / dequantize, 2048 4.1 M 5.48 / 5.72 and 4.77 / 4.87, 5.3 M 6.18 / 6.57 and
+// 5.42 / 6.00, 6.6 M 7.01 / 6.78 and 6.36 / 6.31; 4096 6 M 6.69 / 7.19 and 6.02 / 6.29, 7 M 7.29 / 7.36 and 6.76 / 6.70.
 bool rot_rows_apply(bool quantize, int codec, int bits, int log_b, int64_t n_elems)
 {
     constexpr int64_t k1M = (int64_t)1 << 20;
     if (log_b > 12) return false;
-    if (n_elems <= (log_b < 12 ? 2 : codec == CODEC_FP8 ? 4 : 3) * k1M)
-        return bits == 8 || log_b == 12 || (log_b == 10 && !quantize) || n_elems > k1M;
-    return quantize && bits == 4 && log_b == 10 && n_elems > 16 * k1M;
+    const bool fp8 = codec == CODEC_FP8;
+    const bool q4 = quantize && bits == 4, q4_short = q4 && log_b == 10;
+    const int64_t half_m = log_b == 12 ? (fp8 ? 8 : 6) : fp8 || q4_short ? 6 : bits == 8 ? 5 : 4;
+    if (n_elems <= half_m * (k1M / 2)) return bits == 8 || log_b != 11 || n_elems > k1M;
+    if (q4_short && n_elems > 16 * k1M) return true;
+    const bool third = log_b == 10 ? (bits == 4 || (fp8 && quantize)) : (quantize || fp8);
+    const int from = q4_short || (q4 && log_b == 12) || (fp8 && log_b > 10) ? 4 : 5, to = q4_short ? 7 : 6;
+    return third && n_elems > from * k1M && n_elems <= to * k1M;
 }
 
 }  // namespace

@@ -141,7 +141,8 @@ def test_partial_last_tile_stays_inside_the_buffers(fc, quantizer, bits, tokens,
 
 
 # elements: both sides of every volume at which the rotated quantizer and dequantizer change their form
-VOLUMES = [1 << 20, (1 << 20) + 1, 1 << 21, (1 << 21) + 1, 3 << 20, (3 << 20) + 1, 1 << 22, (1 << 22) + 1, 1 << 24, (1 << 24) + 1]
+VOLUMES = [1 << 20, (1 << 20) + 1, 1 << 21, (1 << 21) + 1, 5 << 19, (5 << 19) + 1, 3 << 20, (3 << 20) + 1, 1 << 22, (1 << 22) + 1,
+           5 << 20, (5 << 20) + 1, 6 << 20, (6 << 20) + 1, 7 << 20, (7 << 20) + 1, 1 << 24, (1 << 24) + 1]
 
 
 @pytest.mark.parametrize("quantizer,bits", QUANTIZERS)
