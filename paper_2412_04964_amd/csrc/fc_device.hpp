@@ -1155,7 +1155,7 @@ __global__ __launch_bounds__(quantize_block_threads(BITS, LPG)) void k_quantize(
 // WRAP: 0 in the library.  The benchmark aid instantiates WRAP > 0, which makes every workgroup work on tile
 // (its tile % WRAP): the instruction stream of a full launch with its memory traffic confined to a few tiles that
 // stay in the L2, i.e. the time the kernel's arithmetic takes when HBM is out of the picture.
-// SHORT: 4-bit codes by accumulate_fast whatever the fan-in, for launches of at most one workgroup per compute unit.
+// SHORT: 4-bit codes by accumulate_fast whatever the fan-in, where a launch chooses it (launch_nl).
 template <int BITS_IN, int BITS_OUT, int NSRC, int LPG, bool HM = false, int BT = fused_block_threads(LPG),
           int WRAP = 0, bool SHORT = false>
 __global__ __launch_bounds__(BT) void k_dequant_reduce_requant(

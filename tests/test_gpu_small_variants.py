@@ -88,9 +88,10 @@ def test_fused_at_the_limit_of_the_launch_bound_kernel(fc, name, n_src):
 
 @pytest.mark.parametrize("name", ["asym", "cmeta"])
 @pytest.mark.parametrize("n_src", [1, 2, 3, 4])
-@pytest.mark.parametrize("group", [1024, 2048, 4096, 8192])
-def test_fused_wide_groups_with_one_workgroup_per_compute_unit(fc, name, n_src, group):
-    # 4-bit codes, at most 256 workgroups (4096 elements each, 8192 for the widest groups): another fold than above that.
+@pytest.mark.parametrize("group", [256, 512, 1024, 2048, 4096, 8192])
+def test_fused_wide_groups_where_the_fold_changes(fc, name, n_src, group):
+    # 4-bit codes, groups from 1024 on, at most 256 workgroups (4096 elements each, 8192 for the widest groups): another fold than
+    # above that; groups from 256 on, two or three sources, 4 -> 8 bit: the same fold from 6 * 2^20 up to 32 * 2^20 elements.
     # Rows with ordinary, huge, fractional and out-of-reach metadata.
     t, sfx = 5, "" if name == "asym" else "_cmeta"
     rng = np.random.default_rng(group + n_src)
@@ -108,7 +109,10 @@ def test_fused_wide_groups_with_one_workgroup_per_compute_unit(fc, name, n_src, 
         want = [dev(np.ascontiguousarray(a).view(np.uint8))
                 for a in getattr(oracle, "dequant_reduce_requant" + sfx)(*wire, group, group, 4, bits_out)]
         limit = 256 * (8192 if group == 8192 else 4096)
-        for rows in (1, limit // group, limit // group + 1, 2 * limit // group + 3):
+        volumes = [1, limit // group, limit // group + 1, 2 * limit // group + 3]
+        if bits_out == 8 and n_src in (2, 3):
+            volumes += [v // group + more for v in (6 << 20, 32 << 20) for more in (0, 1)]
+        for rows in volumes:
             pick = torch.arange(rows, device="cuda") % t
             outs = [Guarded((rows, group * bits_out // 8), torch.uint8)]
             outs += [Guarded((rows, 1), few[1].dtype) for _ in few[1:]]
