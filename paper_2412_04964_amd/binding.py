@@ -130,8 +130,9 @@ def _calls():
         try:
             import torch
             from . import _fc_torch
-            if _fc_torch.torch_version != torch.__version__:
-                raise ImportError("compiled with torch %s, this is %s" % (_fc_torch.torch_version, torch.__version__))
+            built_with = getattr(_fc_torch, "torch_version", "of an unknown version")     # earlier builds do not say
+            if built_with != torch.__version__:
+                raise ImportError("compiled with torch %s, this is %s" % (built_with, torch.__version__))
             _fc_torch.load(_LIB_PATH, _check)
             _native = _fc_torch
         except ImportError as e:

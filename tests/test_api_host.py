@@ -315,6 +315,21 @@ def test_binding_uses_the_outputs_that_it_has_checked(monkeypatch):
         b.quantize(x, 128, 4, out=Changing([torch.zeros(4, 128, dtype=torch.uint8), meta, meta]))
 
 
+def test_a_native_module_that_does_not_say_its_torch_is_not_used(monkeypatch, L):
+    # one left from an earlier build: the checked path takes the calls, nothing raises
+    pytest.importorskip("torch")
+    import sys
+    import types
+    import paper_2412_04964_amd
+    from paper_2412_04964_amd import binding as b
+    old = types.ModuleType("paper_2412_04964_amd._fc_torch")
+    monkeypatch.setitem(sys.modules, old.__name__, old)
+    monkeypatch.setattr(paper_2412_04964_amd, "_fc_torch", old, raising=False)
+    monkeypatch.setattr(b, "_native", None)
+    with pytest.warns(RuntimeWarning, match="unknown version"):
+        assert b._calls().quantize(None) is None
+
+
 def test_binding_refuses_tensors_of_another_device(monkeypatch):
     # the C ABI works on the device that is current on the calling thread; a tensor of another device is refused
     torch = pytest.importorskip("torch")
