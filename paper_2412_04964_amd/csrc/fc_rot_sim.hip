@@ -3,9 +3,9 @@
 // once.  2 N + 2 bytes per element; nothing else goes through HBM.  Bit-identical to fc_quantize_rot x N ->
 // fc_dequant_reduce_requant -> fc_dequantize_rot.
 //
-// What bounds it: vector instructions, (N + 1) log2 B of them per element for the butterflies alone.  181 us on 4 partials
+// What bounds it: vector instructions, (N + 1) log2 B of them per element for the butterflies alone.  180 to 186 us by card on 4 partials
 // of 8192 x 8192 (group 128, INT4); 195 us when bits 7 and 8 went through ds_swizzle and ds_bpermute, which keeps the LDS
-// crossbar of the whole compute unit busy for 6 cycles per instruction; the three steps took 255 us, the codes
+// crossbar of the whole compute unit busy for 6 cycles per instruction; the three steps took 247 to 255 us, the codes
 // and metadata going through HBM and the rows through LDS five times.
 // The transform and its layout are those of fc_rot_wave.hpp; the partials are taken in
 // source order in a loop, the next one's loads in flight while one is coded.  The sum stays in the frame of the rotated values (see there): rounding is symmetric, so the

@@ -3,8 +3,9 @@
 // What a decode-sized call spends its time on is the host: the checks of binding.py ask each tensor for its type,
 // shape, contiguity and device through the Python interpreter, and ctypes converts ten to fifteen arguments; that is
 // 11 us of the 13 us a call takes where the kernel needs 2.  The functions here make the same checks on the tensors
-// themselves, allocate missing outputs, take the current stream and call the library: 3 us a call (three steps of a
-// decode rank 38.3 -> 9.2 us, of a 512-token chunk 37.7 -> 13.0 us, a decode all-reduce 11.1 -> 3.1 us).
+// themselves, allocate missing outputs, take the current stream and call the library: 3 us a call (inputs
+// changing from call to call: three steps of a decode rank 39.0 -> 10.7 us, of a 512-token chunk 38.6 -> 14.8 us, a decode
+// all-reduce 11.2 -> 3.5 us, which is its kernel).
 //
 // They take the ordinary call only.  Anything else -- a tensor of another type, shape, layout, device or Python class,
 // an integer that is not a Python int, a geometry the library does not have, an active tracing, dispatch or function
