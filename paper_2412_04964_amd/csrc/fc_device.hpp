@@ -244,6 +244,8 @@ constexpr int kDppQuadXor1 = 0xB1;        // quad_perm:[1,0,3,2]
 constexpr int kDppQuadXor2 = 0x4E;        // quad_perm:[2,3,0,1]
 constexpr int kDppRowHalfMirror = 0x141;  // lane i <-> 7-i inside each 8 lanes
 constexpr int kDppRowMirror = 0x140;      // lane i <-> 15-i inside each 16 lanes
+constexpr int kDppRowRor4 = 0x124;        // from lane i-4 of the 16 lanes (modulo 16)
+constexpr int kDppRowRor8 = 0x128;
 
 // min / max of a value with the same value in the lane that CTRL selects, in ONE instruction (the DPP operand
 // modifier on v_min_f32 / v_max_f32 themselves).  Written as inline assembly because the compiler's own sequence
@@ -258,6 +260,10 @@ __device__ __forceinline__ float dpp_min(float v)
         asm("s_nop 1\n\tv_min_f32_dpp %0, %1, %1 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf bound_ctrl:1" : "=v"(r) : "v"(v));
     else if constexpr (CTRL == kDppQuadXor2)
         asm("s_nop 1\n\tv_min_f32_dpp %0, %1, %1 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf bound_ctrl:1" : "=v"(r) : "v"(v));
+    else if constexpr (CTRL == kDppRowRor4)
+        asm("s_nop 1\n\tv_min_f32_dpp %0, %1, %1 row_ror:4 row_mask:0xf bank_mask:0xf" : "=v"(r) : "v"(v));
+    else if constexpr (CTRL == kDppRowRor8)
+        asm("s_nop 1\n\tv_min_f32_dpp %0, %1, %1 row_ror:8 row_mask:0xf bank_mask:0xf" : "=v"(r) : "v"(v));
     else if constexpr (CTRL == kDppRowHalfMirror)
         asm("s_nop 1\n\tv_min_f32_dpp %0, %1, %1 row_half_mirror row_mask:0xf bank_mask:0xf bound_ctrl:1" : "=v"(r) : "v"(v));
     else {
@@ -275,6 +281,10 @@ __device__ __forceinline__ float dpp_max(float v)
         asm("s_nop 1\n\tv_max_f32_dpp %0, %1, %1 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf bound_ctrl:1" : "=v"(r) : "v"(v));
     else if constexpr (CTRL == kDppQuadXor2)
         asm("s_nop 1\n\tv_max_f32_dpp %0, %1, %1 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf bound_ctrl:1" : "=v"(r) : "v"(v));
+    else if constexpr (CTRL == kDppRowRor4)
+        asm("s_nop 1\n\tv_max_f32_dpp %0, %1, %1 row_ror:4 row_mask:0xf bank_mask:0xf" : "=v"(r) : "v"(v));
+    else if constexpr (CTRL == kDppRowRor8)
+        asm("s_nop 1\n\tv_max_f32_dpp %0, %1, %1 row_ror:8 row_mask:0xf bank_mask:0xf" : "=v"(r) : "v"(v));
     else if constexpr (CTRL == kDppRowHalfMirror)
         asm("s_nop 1\n\tv_max_f32_dpp %0, %1, %1 row_half_mirror row_mask:0xf bank_mask:0xf bound_ctrl:1" : "=v"(r) : "v"(v));
     else {

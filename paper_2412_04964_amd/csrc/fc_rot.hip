@@ -17,18 +17,17 @@
 // groups never cross block boundaries, so the tensor is handled as a flat sequence of tiles; the last tile of a
 // tensor of 1024- or 2048-element blocks may be a partial one (loads beyond the end give zeros, stores are dropped).
 //
-// What bounds them: vector instructions (quantizer, blocks of 1024, 4 bit: 590 per wavefront of 2048 elements, about 1950 cycles
-// with the DPP, conversion and min / max instructions that issue at half the rate of an fp32 add) in blocks of 8192, whose
-// wavefronts wait to issue 50 to 60 % of their time; in blocks of 1024 as much the wait for memory (dequantizer, 8192 x 5120: 42 %
-// and 38 %, 5.6 wavefronts per SIMD in the mean), since a wavefront loads, transforms, stores and ends.  The rows
-// used to go through LDS and back for every five stages, in fp32: 10 KB per wavefront kept four of them on a SIMD, and
-// LDS writes run at 75 bytes a cycle.  Rotate + quantize / dequantize + rotate, us before -> now: 8192 x 8192 INT4 (blocks of
-// 8192) 46.0 -> 43.0 / 43.9 -> 39.6; the same in FP8 55.5 -> 45.2 / 46.3 -> 42.9; 8192 x 5120 INT4 (blocks of 1024)
-// 23.9 -> 25.4 / 24.5 -> 22.7; 32 x 8192 4.20 -> 3.67 / 3.87 -> 3.48.  Where the form with the row in LDS is the faster one (the
-// 4-bit quantizer of blocks of 1024 above, launch-bound volumes) it is fc_rot_rows.hip that runs.  Measured and not taken: 32 consecutive elements per lane
-// and a 16 x 16 exchange with other lanes through 5 KB of LDS (40.3 us for blocks of 8192, but 23.8 for 1024 and
-// 23.0 / 48 in the dequantizer, whose register needs it does not fit); all stages between lanes by permlane swaps
-// (25.9 us, blocks of 1024).
+// What bounds them: vector instructions and which of them issue side by side (rot_priority in fc_rot_wave.hpp) in blocks of 8192, as much
+// the wait for memory in blocks of 1024, since a wavefront loads, transforms, stores and ends.  Rotate + quantize / dequantize + rotate,
+// us, with the rows in LDS between phases of four or five stages (fc_rot_rows.hip) -> in registers -> with raised priority and, blocks of
+// 4096 and 8192, element bits 9 and 10 by way of the exchange (quantizer): 8192 x 8192 INT4 46.0 -> 43.5 -> 37.5 / 43.9 -> 39.7 -> 38.4;
+// the same in FP8 55.5 -> 45.2 -> 44 / 46.3 -> 42.9 -> 42.2; 8192 x 4096 INT8 - -> 22.9 -> 20.8 / - -> 21.9 -> 21.1; 8192 x 5120 INT4 (blocks of
+// 1024) 22.9 -> 25.4 -> 20.7 / 24.5 -> 22.0 -> 21.4.  Launch-bound volumes run in fc_rot_rows.hip where that is faster.
+// Measured and not taken: 32 consecutive elements per lane and a 16 x 16 exchange with other lanes through 5 KB of LDS (40.3 us for blocks
+// of 8192, when this form took 43.0, but 23.8 for 1024 and 23.0 / 48 in the dequantizer, whose register needs it does not fit); all stages
+// between lanes by permlane swaps; persistent workgroups that load the next tile while they transform the current one (4, 5, 6, 12
+// wavefronts per SIMD: 24.3, 23.6, 25.8, 22.5 us against 21.6, quantize 8192 x 5120; dequantize no gain); fewer wavefronts per
+// SIMD by holding LDS (3 to 7: no gain).
 #include "fc_rot_wave.hpp"
 #include "fc_launch.hpp"
 
@@ -42,7 +41,7 @@ __device__ __forceinline__ u32 of_piece_bits(u32 v)
     return __builtin_bit_cast(u32, of_piece<P>(__builtin_bit_cast(float, v)));
 }
 
-// Code words of piece P.  `inv` (with the forward scaling in it) and `fix` belong to piece pos & 3 of the lane.
+// Code words of piece P.  `inv` (with the forward scaling in it) and `fix` belong to piece lane & 3 of the lane.
 // The values are in the lane's frame: rounding is symmetric, so the frame goes into the reciprocal.
 template <int BITS, int CODEC, int P>
 __device__ __forceinline__ void rot_pack(const float (&v)[4][8], const RotLane &L, float inv, u32 fix,
@@ -73,7 +72,7 @@ __device__ __forceinline__ void rot_pack_literal(const float (&v)[4][8], const R
 
 // Rotate block by block and quantize (FinegrainedQuantize of Algorithm 1 on the rotated values).
 // n_elems: elements of the whole tensor, a multiple of 2^LB.
-template <int BITS, int CODEC, int LB>
+template <int BITS, int CODEC, int LB, bool SWAPS>
 __global__ __launch_bounds__(64 * rot_group_waves(LB)) void k_quantize_rot(
     const uint16_t *__restrict__ x, int64_t n_elems, int group_shift, uint8_t *__restrict__ codes,
     float *__restrict__ scales, float *__restrict__ zeros)
@@ -82,11 +81,11 @@ __global__ __launch_bounds__(64 * rot_group_waves(LB)) void k_quantize_rot(
     constexpr int kWaves = rot_group_waves(LB);
     constexpr int kTile = 2048 * kWaves;
     __shared__ __attribute__((aligned(16))) uint8_t pieces[rot_exchange_bytes(LB, kRounds)];
-    __shared__ float mm[kWaves][4][2];
+    __shared__ float mm[kWaves][kRotSlots][2];
 
     const u32 tid = threadIdx.x, lane = tid & 63u;
     const u32 wave = (u32)__builtin_amdgcn_readfirstlane((int)(tid >> 6));
-    const RotLane L = rot_lane<FP8>(lane);
+    const RotLane L = rot_lane<FP8, rot_forward_framed(LB, SWAPS)>(lane);
     const int64_t e_tile = (int64_t)blockIdx.x * kTile;
     const int64_t e_begin = rot_begin<LB>(e_tile, wave);
     const int64_t left = n_elems - e_begin;
@@ -104,7 +103,7 @@ __global__ __launch_bounds__(64 * rot_group_waves(LB)) void k_quantize_rot(
     for (int p = 0; p < 4; ++p)
 #pragma unroll
         for (int i = 0; i < 4; ++i) first_stage(raw[p][i], v[p][2 * i], v[p][2 * i + 1]);
-    rot_forward<LB, FP8, kRounds>(v, L, pieces, wave);
+    rot_forward<LB, SWAPS, FP8, kRounds, false>(v, L, pieces, wave);
 
     // Forward scaling fwd = 2^-ceil(n/2), n = LB.  It is a power of two and nothing here is near the ends of
     // the fp32 range (the transformed values are multiples of 2^-24 below 2^30), so scaling commutes
@@ -114,7 +113,7 @@ __global__ __launch_bounds__(64 * rot_group_waves(LB)) void k_quantize_rot(
     // same rounded one.
     constexpr float fwd = 1.0f / (float)(1 << ((LB + 1) / 2));
     float mn, mx, s, inv, zf = 0.0f;
-    rot_group_minmax<LB, FP8>(v, L, group_shift, wave, mm, mn, mx);
+    rot_group_minmax<LB, SWAPS, FP8>(v, L, group_shift, wave, mm, mn, mx);
     const float mn_s = mn * fwd, mx_s = mx * fwd;
     if constexpr (FP8)
         group_params_absmax<448>(fmaxf(fabsf(mn_s), fabsf(mx_s)), s, inv);
@@ -148,11 +147,12 @@ __global__ __launch_bounds__(64 * rot_group_waves(LB)) void k_quantize_rot(
         rot_pack<BITS, CODEC, 3>(v, L, inv, fix, word);
     }
 
-    // bits 7 and 8 go to lane bits 4 and 5, so that a store covers runs of 512 elements
-    constexpr RotMap done = rot_forward_map(LB);
-    constexpr RotMap out = {7, 8, done.l4 == 7 ? done.p0 : done.l4, done.l5 == 8 ? done.p1 : done.l5, done.w0, done.w1};
-    if constexpr (done.l4 != 7) rot_swap_words<4>(word);
-    if constexpr (done.l5 != 8) rot_swap_words<5>(word);
+    // Blocks of 1024 and 2048: bits 7 and 8 go to lane bits 4 and 5, so that a store covers runs of 512 elements.  The others store runs
+    // of 128 (a pass through LDS for runs of a whole block: 38.8 us instead of 38.4, 8192 x 8192 INT4).
+    constexpr RotMap done = rot_forward_map(LB, SWAPS);
+    constexpr RotMap out = LB >= 12 ? done : RotMap{7, 8, done.l4 == 7 ? done.p0 : done.l4, done.l5 == 8 ? done.p1 : done.l5, done.w0, done.w1};
+    if constexpr (out.l4 != done.l4) rot_swap_words<4>(word);
+    if constexpr (out.l5 != done.l5) rot_swap_words<5>(word);
     const rsrc_t rc = make_rsrc(codes + e_begin * BITS / 8, left * BITS / 8);
     const u32 lane_at = rot_lane_offset(out, L) * BITS / 8;
 #pragma unroll
@@ -174,7 +174,7 @@ __global__ __launch_bounds__(64 * rot_group_waves(LB)) void k_quantize_rot(
 }
 
 // v[P] = (q - z) * s for the codes of piece P, in the lane's frame (EXACT: frame +1 and the literal operations).
-// s and z (z: as pack_zero_const gives it, EXACT: the bits of the number) belong to piece pos & 3 of the lane.
+// s and z (z: as pack_zero_const gives it, EXACT: the bits of the number) belong to piece lane & 3 of the lane.
 template <int BITS, int CODEC, int P, bool EXACT>
 __device__ __forceinline__ void rot_unpack(const u32 (&word)[4][BITS / 4], float s, u32 z, float frame, float (&v)[4][8])
 {
@@ -293,14 +293,14 @@ __global__ __launch_bounds__(64 * rot_group_waves(LB)) __attribute__((amdgpu_wav
         rot_unpack<BITS, CODEC, 1, true>(word, s, z, 1.0f, v);
         rot_unpack<BITS, CODEC, 2, true>(word, s, z, 1.0f, v);
         rot_unpack<BITS, CODEC, 3, true>(word, s, z, 1.0f, v);
-        rot_inverse_row<true>(v, L);
+        rot_inverse_row<true, false>(v, L);
     } else if constexpr (!FP8) {
         const u32 z = CODEC == kAsym ? pack_zero_const(zf) : 0;
         rot_unpack<BITS, CODEC, 0, false>(word, s, z, L.frame, v);
         rot_unpack<BITS, CODEC, 1, false>(word, s, z, L.frame, v);
         rot_unpack<BITS, CODEC, 2, false>(word, s, z, L.frame, v);
         rot_unpack<BITS, CODEC, 3, false>(word, s, z, L.frame, v);
-        rot_inverse_row<false>(v, L);
+        rot_inverse_row<false, false>(v, L);
     }
     if constexpr (!FP8 && LB >= 12)
         if (lane == 0) exact_wave[wave] = exact;
@@ -352,8 +352,12 @@ template <int BITS, int CODEC, int LB>
 hipError_t quantize_rot_one(const uint16_t *x, int64_t n_elems, int group, uint8_t *c, float *scales,
                             float *zeros, hipStream_t stream)
 {
-    return launch_kernel(k_quantize_rot<BITS, CODEC, LB>, rot_grid<LB>(n_elems), dim3(64 * rot_group_waves(LB)), stream,
-                         x, n_elems, log2_int(group), c, scales, zeros);
+    const dim3 grid = rot_grid<LB>(n_elems), block(64 * rot_group_waves(LB));
+    const int sh = log2_int(group);
+    if constexpr (LB == 13 && CODEC != kFp8)
+        if (!rot_swaps_apply(false, n_elems))
+            return launch_kernel(k_quantize_rot<BITS, CODEC, LB, false>, grid, block, stream, x, n_elems, sh, c, scales, zeros);
+    return launch_kernel(k_quantize_rot<BITS, CODEC, LB, true>, grid, block, stream, x, n_elems, sh, c, scales, zeros);
 }
 
 template <int BITS, int CODEC>
@@ -390,30 +394,21 @@ hipError_t dequantize_rot_h(int log_b, const uint8_t *c, const float *scales, co
     }
 }
 
-// Whether the form of fc_rot_rows.hip is the faster one (its header has both sides' times).  At 8 bit, where a wavefront here has
-// twice the work of one there, up to 5 * 2^19 elements, FP8 3 * 2^20 (2.5 M: INT8 dequantize, blocks of 2048 3.83 / 3.98; FP8
-// 3.73 / 4.05; 3 M 4.21 / 4.13 and 4.10 / 4.22), blocks of 4096 up to 3 * 2^20, FP8 there up to 2^22.  At 4 bit a wavefront has
-// the same 2048 elements in both forms, and the register form is as fast or faster for blocks of 2048 while it has one workgroup
-// per compute unit (2^20 elements).  The 4-bit quantizer of blocks of 1024, whose codes leave in 32-bit stores here and in 128-bit
-// stores there, crosses at 3 * 2^20 (2.5 M 3.90 / 4.06, 4 M 4.78 / 4.66) and once more between 2^23 and 2^25 elements.
-// With the third wavefront per SIMD of the register form, above 2^22 elements and mostly above 5 * 2^20, the row form is the
-// faster one again for a while, us per launch, rows / registers: 4 bit quantize, blocks of 1024 5.3 M 5.43 / 6.03, 6.6 M
-// 6.17 / 6.33, 7.3 M 6.40 / 6.41; 2048 5 M 5.80 / 5.79, 5.3 M 6.01 / 6.59, 6.3 M 6.76 / 6.77; 4096 4.1 M 5.61 / 5.83, 6 M 6.56 / 6.95, 6.6 M
-// 7.05 / 7.08; 8 bit quantize, 2048 5.6 M 6.46 / 6.60, 4096 6.73 / 6.90, but 1024 6.44 / 6.24; 4 bit dequantize, 1024 5.6 M
-// 4.94 / 5.12, 2048 5.62 / 5.45; FP8 quantize / dequantize, 2048 4.1 M 5.48 / 5.72 and 4.77 / 4.87, 5.3 M 6.18 / 6.57 and
-// 5.42 / 6.00, 6.6 M 7.01 / 6.78 and 6.36 / 6.31; 4096 6 M 6.69 / 7.19 and 6.02 / 6.29, 7 M 7.29 / 7.36 and 6.76 / 6.70.
+// Whether the form of fc_rot_rows.hip is the faster one (its header has both sides' times).  At 8 bit a wavefront here has twice the
+// work of one there, and FP8's stages cost most in a chain that nothing covers, so the limits lie between 2^21 and 2^22 elements;
+// at 4 bit a wavefront has 2048 elements in both forms, blocks of 2048 are faster here while they have one workgroup per
+// compute unit (2^20 elements), the quantizer of blocks of 4096 always (64 K 3.34 / 3.20, 2 M 4.66 / 4.53).  Just past the third
+// wavefront per SIMD, 5 to 6 * 2^20 elements, the row form wins once more in two cases (rows / registers, 5.5 M: 4-bit dequantizer, blocks
+// of 1024 4.90 / 5.12; FP8 quantizer, 2048 6.19 / 6.50; 6.5 M 5.44 / 5.22, 6.91 / 6.88).
 bool rot_rows_apply(bool quantize, int codec, int bits, int log_b, int64_t n_elems)
 {
+    // up to so many times 2^19 elements; quantize, dequantize; 4 bit, 8 bit, FP8; blocks of 1024, 2048, 4096
+    static constexpr unsigned char kLimit[2][3][3] = {{{4, 4, 0}, {4, 5, 4}, {6, 8, 8}}, {{4, 4, 4}, {4, 4, 6}, {5, 6, 8}}};
     constexpr int64_t k1M = (int64_t)1 << 20;
     if (log_b > 12) return false;
     const bool fp8 = codec == CODEC_FP8;
-    const bool q4 = quantize && bits == 4, q4_short = q4 && log_b == 10;
-    const int64_t half_m = log_b == 12 ? (fp8 ? 8 : 6) : fp8 || q4_short ? 6 : bits == 8 ? 5 : 4;
-    if (n_elems <= half_m * (k1M / 2)) return bits == 8 || log_b != 11 || n_elems > k1M;
-    if (q4_short && n_elems > 16 * k1M) return true;
-    const bool third = log_b == 10 ? (bits == 4 || (fp8 && quantize)) : (quantize || fp8);
-    const int from = q4_short || (q4 && log_b == 12) || (fp8 && log_b > 10) ? 4 : 5, to = q4_short ? 7 : 6;
-    return third && n_elems > from * k1M && n_elems <= to * k1M;
+    if (n_elems <= kLimit[!quantize][fp8 ? 2 : bits == 8][log_b - 10] * (k1M / 2)) return bits == 8 || log_b != 11 || n_elems > k1M;
+    return (quantize ? fp8 && log_b == 11 : bits == 4 && log_b == 10) && n_elems > 5 * k1M && n_elems <= 6 * k1M;
 }
 
 }  // namespace

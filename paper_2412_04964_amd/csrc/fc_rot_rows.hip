@@ -8,14 +8,16 @@
 //
 // What bounds it: latency of one wavefront.  us per launch under graph replay, this / register form, group 128, quantize and
 // dequantize (rot_rows_apply says where each is taken):
-//   8 bit, blocks of 1024: 64 K elements 2.93 / 3.23, 2.59 / 2.97; 1 M 3.30 / 3.37, 3.02 / 3.15; 2 M 3.76 / 3.98,
-//     3.47 / 3.71; 3 M 4.36 / 3.98, 4.01 / 3.82; 8 M 8.76 / 7.20, 7.78 / 6.36.  FP8: 64 K 2.87 / 3.40, 2.49 / 3.22.
-//   8 bit, blocks of 4096: 64 K 3.30 / 3.65, 2.94 / 3.43; 2 M 4.05 / 4.50, 3.74 / 4.30; 3 M 4.53 / 4.59, 4.22 / 4.55;
-//     4 M 5.85 / 5.40, 5.61 / 5.61.
-//   4 bit, blocks of 1024: 64 K 3.18 / 3.22, 2.80 / 2.93; 1 M 3.34 / 3.35, 3.06 / 3.05; 2 M 3.61 / 3.92, 3.52 / 3.69;
-//     4 M 5.11 / 5.20, 5.24 / 4.89; 8 M 7.27 / 7.20; 32 M 19.4 / 20.6, 20.5 / 18.4; 8192 x 5120 23.9 / 25.4, 24.5 / 22.7.
-//   4 bit, blocks of 2048: 1 M 3.60 / 3.43, 3.31 / 3.12; 2 M 3.94 / 4.17, 3.78 / 3.84.
-//   4 bit, blocks of 4096: 64 K 3.66 / 3.67, 3.23 / 3.37; 3 M 4.56 / 4.70, 4.45 / 4.52; 4 M 5.97 / 5.84, 5.74 / 5.58.
+//   8 bit, blocks of 1024: 1 M elements 3.51 / 3.57, 3.08 / 3.20; 2 M 4.02 / 4.17, 3.62 / 3.85; 2.5 M 4.38 / 4.33, 3.95 / 3.93;
+//     8 M 8.00 / 6.76, 7.23 / 5.78.  FP8: 1 M 3.37 / 3.81, 2.98 / 3.47; 3 M 4.67 / 4.79, 4.21 / 4.19; 4 M 5.22 / 5.11, 4.81 / 4.37.
+//   8 bit, blocks of 2048: 2 M 4.06 / 4.42, 3.65 / 3.94; 3 M 4.82 / 4.77, 4.39 / 4.11.  FP8: 3 M 4.70 / 4.99, 4.24 / 4.28; 4 M
+//     5.25 / 5.33, 4.81 / 4.48; 5 M 5.89 / 5.83, 5.43 / 4.99.
+//   8 bit, blocks of 4096: 2 M 4.45 / 4.52, 3.89 / 4.43; 3 M 5.13 / 4.91, 4.53 / 4.75; 4 M 5.78 / 5.24, 5.17 / 5.01.  FP8: 3 M
+//     5.02 / 5.39, 4.46 / 4.82; 4 M 5.67 / 5.79, 5.10 / 5.11; 5 M 6.30 / 6.20, 5.69 / 5.49.
+//   4 bit, blocks of 1024: 64 K 2.88 / 2.89, 2.49 / 2.55; 1 M 3.61 / 3.55, 3.08 / 3.06; 2 M 3.99 / 4.13, 3.50 / 3.69; 2.5 M 4.37 / 4.32,
+//     3.95 / 3.74; 8 M 6.95 / 6.60, 6.05 / 5.57; 16 M 11.41 / 10.24, 11.01 / 9.94; 8192 x 5120 22.9 / 20.7.
+//   4 bit, blocks of 2048: 1 M 3.83 / 3.61, 3.33 / 3.14; 1.5 M 4.08 / 4.22, 3.59 / 3.75; 2.5 M 4.77 / 4.53, 4.29 / 3.85.
+//   4 bit, blocks of 4096, dequantize: 64 K 2.93 / 3.07; 2 M 4.19 / 4.26; 3 M 4.60 / 4.56; 4 M 5.09 / 4.89.
 //   Blocks of 8192: the register form at every volume.
 #include "fc_rot_wave.hpp"
 #include "fc_launch.hpp"
@@ -284,7 +286,9 @@ hipError_t quantize_block(int log_b, const uint16_t *x, int64_t n_elems, int gro
     switch (log_b) {
     case 10: return quantize_one<BITS, CODEC, 11, 10>(x, n_elems, group, c, scales, zeros, stream);
     case 11: return quantize_one<BITS, CODEC, 11, 11>(x, n_elems, group, c, scales, zeros, stream);
-    case 12: return quantize_one<BITS, CODEC, 12, 12>(x, n_elems, group, c, scales, zeros, stream);
+    case 12:
+        if constexpr (BITS == 8) return quantize_one<BITS, CODEC, 12, 12>(x, n_elems, group, c, scales, zeros, stream);
+        return hipErrorInvalidValue;       // 4 bit: the register form at every volume
     default: return hipErrorInvalidValue;
     }
 }

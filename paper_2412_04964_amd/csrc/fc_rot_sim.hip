@@ -3,10 +3,12 @@
 // once.  2 N + 2 bytes per element; nothing else goes through HBM.  Bit-identical to fc_quantize_rot x N ->
 // fc_dequant_reduce_requant -> fc_dequantize_rot.
 //
-// What bounds it: vector instructions, (N + 1) log2 B of them per element for the butterflies alone.  180 to 186 us by card on 4 partials
-// of 8192 x 8192 (group 128, INT4); 195 us when bits 7 and 8 went through ds_swizzle and ds_bpermute, which keeps the LDS
-// crossbar of the whole compute unit busy for 6 cycles per instruction; the three steps took 247 to 255 us, the codes
-// and metadata going through HBM and the rows through LDS five times.
+// What bounds it: vector instructions, (N + 1) log2 B of them per element for the butterflies alone, and which of them can issue side
+// by side (rot_priority in fc_rot_wave.hpp).  4 partials of 8192 x 8192 (group 128, INT4): 166 us; 181 without the raised priority, 187 when element
+// bits 9 and 10 also came into registers by permlane swaps; 195 when bits 7 and 8 went through ds_swizzle and ds_bpermute, which keeps
+// the LDS crossbar of the whole compute unit busy for 6 cycles per instruction; the three steps took 247 to 255 us, the codes
+// and metadata going through HBM and the rows through LDS five times.  4 x 8192 x 4096 92.5 -> 83; 4 x 8192 x 5120 96 -> 88;
+// FP8 4 x 4096 x 8192 106 -> 103.  Five wavefronts per SIMD instead of four: slower.
 // The transform and its layout are those of fc_rot_wave.hpp; the partials are taken in
 // source order in a loop, the next one's loads in flight while one is coded.  The sum stays in the frame of the rotated values (see there): rounding is symmetric, so the
 // quantizer works on a negated value as on the value, and the inverse transform undoes the frame.
@@ -43,11 +45,11 @@ __device__ __forceinline__ void rot_params(float mn, float mx, RotLevels lv, flo
 template <int P>
 __device__ __forceinline__ void rot_literal_codes(float (&v)[4][8], float frame, float inv, float zf, float qmax)
 {
-    const float inv_p = of_piece<P>(inv), z_p = of_piece<P>(zf);
+    const float inv_p = of_piece<P>(inv) * frame, z_p = of_piece<P>(zf), z_f = z_p * frame;
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
-        const float u = rintf(v[P][i] * frame * inv_p) + z_p;
-        v[P][i] = (__builtin_amdgcn_fmed3f(u, 0.0f, qmax) - z_p) * frame;
+        const float u = rintf(v[P][i] * inv_p) + z_p;
+        v[P][i] = fmaf(__builtin_amdgcn_fmed3f(u, 0.0f, qmax), frame, -z_f);           // (code - z) * frame, rounded alike
     }
 }
 
@@ -110,28 +112,35 @@ __device__ __forceinline__ void rot_scale(float (&d)[4][8], float s)
     for (int i = 0; i < 8; ++i) d[P][i] *= s_p;
 }
 
+// The lane number, for what is derived from it after the first loads: left to itself the compiler derives it all before
+// them, 30 instructions and 0.07 us of every launch.
+__device__ __forceinline__ u32 after_loads(u32 lane)
+{
+    asm volatile("" : "+v"(lane) : : "memory");
+    return lane;
+}
+
 template <int CODEC, int LB>
 __global__ __launch_bounds__(64 * rot_group_waves(LB)) __attribute__((amdgpu_waves_per_eu(4))) void k_allreduce_rot(
     const uint16_t *__restrict__ x, int64_t n_elems, int n_src, int group_shift, RotLevels rs, RotLevels ag,
     uint16_t *__restrict__ y)
 {
-    constexpr bool FP8 = CODEC == kFp8;
+    constexpr bool FP8 = CODEC == kFp8, SWAPS = FP8;                    // see rot_swaps_apply
     constexpr int kWaves = rot_group_waves(LB);
     constexpr int kTile = 2048 * kWaves;
     constexpr int kChunk = (512 * 1024) / (kTile * 2);                  // 512 KB of every partial per XCD and run
     __shared__ __attribute__((aligned(16))) uint8_t pieces[rot_exchange_bytes(LB, 1)];
-    __shared__ float mm[kWaves][4][2];
+    __shared__ float mm[kWaves][kRotSlots][2];
 
     const u32 tid = threadIdx.x, lane = tid & 63u;
     const u32 wave = (u32)__builtin_amdgcn_readfirstlane((int)(tid >> 6));
-    const RotLane L = rot_lane<FP8>(lane);
     const u32 tile = xcd_tile<kChunk>((u32)((n_elems + kTile - 1) / kTile));
     const int64_t e_tile = (int64_t)tile * kTile;
     const int64_t e_begin = rot_begin<LB>(e_tile, wave);
     const int64_t left = (n_elems - e_begin) * 2;                      // bytes from there to the end of a partial
 
     u32x4 raw[4];
-    const u32 lane_at = rot_lane_offset(kRotLoaded, L) * 2;
+    const u32 lane_at = rot_lane_offset(kRotLoaded, rot_lane<FP8>(lane)) * 2;
     auto fetch = [&](int j) {
         u32 in_at = lane_at;
         asm volatile("" : "+v"(in_at));                                // the pieces' addresses stay out of the loop's registers
@@ -145,23 +154,25 @@ __global__ __launch_bounds__(64 * rot_group_waves(LB)) __attribute__((amdgpu_wav
     constexpr float fwd = 1.0f / (float)(1 << ((LB + 1) / 2));          // 2^-ceil(n/2), n = LB
     constexpr float back = 1.0f / (float)(1 << (LB / 2));               // 2^-floor(n/2)
 
+    fetch(0);
+    const RotLane L = rot_lane<FP8, rot_forward_framed(LB, SWAPS)>(after_loads(lane));
     float acc[4][8];
 #pragma unroll
     for (int p = 0; p < 4; ++p)
 #pragma unroll
         for (int i = 0; i < 8; ++i) acc[p][i] = 0.0f;
 
-    fetch(0);
-    for (int j = 0; j < n_src; ++j) {
+    int j = 0;
+    do {                                                               // n_src >= 1; a loop that may be skipped has its loads moved behind the test
         float v[4][8];
 #pragma unroll
         for (int p = 0; p < 4; ++p)
 #pragma unroll
             for (int i = 0; i < 4; ++i) first_stage(raw[p][i], v[p][2 * i], v[p][2 * i + 1]);
         if (LB >= 12 && j > 0) lds_barrier();                          // every wavefront has taken the last exchange
-        rot_forward<LB, FP8, 1>(v, L, pieces, wave);
+        rot_forward<LB, SWAPS, FP8, 1, (LB >= 12)>(v, L, pieces, wave);
         float mn, mx, s, inv, zf;
-        rot_group_minmax<LB, FP8>(v, L, group_shift, wave, mm, mn, mx);
+        rot_group_minmax<LB, SWAPS, FP8>(v, L, group_shift, wave, mm, mn, mx);
         rot_params<CODEC>(mn, mx, rs, fwd, s, inv, zf);
         if (j + 1 < n_src) fetch(j + 1);
         rot_codes<CODEC>(v, L, mx, inv, zf, rs);
@@ -169,32 +180,55 @@ __global__ __launch_bounds__(64 * rot_group_waves(LB)) __attribute__((amdgpu_wav
         rot_accumulate<1>(v, s, acc);
         rot_accumulate<2>(v, s, acc);
         rot_accumulate<3>(v, s, acc);
-    }
+    } while (++j < n_src);
 
     float mn, mx, s, inv, zf;
     if (LB >= 12) lds_barrier();
-    rot_group_minmax<LB, FP8>(acc, L, group_shift, wave, mm, mn, mx);
+    rot_group_minmax<LB, SWAPS, FP8>(acc, L, group_shift, wave, mm, mn, mx);
     rot_params<CODEC>(mn, mx, ag, 1.0f, s, inv, zf);
     rot_codes<CODEC>(acc, L, mx, inv, zf, ag);
     rot_scale<0>(acc, s);
     rot_scale<1>(acc, s);
     rot_scale<2>(acc, s);
     rot_scale<3>(acc, s);
-    rot_inverse_row<FP8>(acc, L);
-    rot_inverse_back<LB, 1>(acc, L, pieces, wave);
+    const float frame = rot_inverse_back<LB, SWAPS, FP8, 1>(acc, L, pieces, wave);
 
     const rsrc_t ry = make_rsrc(y + e_begin, left);
-    const u32 out_at = rot_lane_offset(rot_back_map(LB), L) * 2;
+    const float scale = back * frame;
+    u32x4 out[4];
 #pragma unroll
-    for (u32 p = 0; p < 4; ++p) {
-        u32x4 out;
+    for (u32 p = 0; p < 4; ++p)
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const float a = acc[p][2 * i], b = acc[p][2 * i + 1];
-            out[i] = FP8 ? round_pair(a * back, b * back) : round_pair(fmaf(a, back, 0.0f), fmaf(b, back, 0.0f));
+            out[p][i] = FP8 ? round_pair(a * scale, b * scale) : round_pair(fmaf(a, scale, 0.0f), fmaf(b, scale, 0.0f));
         }
-        const RotAt at = rot_at<LB>(out_at, rot_back_map(LB), wave, p, 16);
-        store_b128_at(out, ry, at.vec, at.scalar);
+    if constexpr (LB == 12 || (LB == 13 && !SWAPS)) {
+        // the values' binary16 image goes through LDS, so that every store of a wavefront is one run of 1 KB.  16-byte units;
+        // the low four bits of a unit's number are xor-ed with its element bits 9 and on, which vary along a row of lanes
+        // and else lie in the same banks (LB = 12: the fourth that varies is 5, unit bit 2).
+        auto banks = [](u32 h) -> u32 { return LB == 13 ? h : (h & 3u) | ((h & 4u) << 1); };
+        lds_barrier();                                                 // every wavefront has taken the exchange
+        const u32 high = L.pos & (LB == 13 ? 15u : 7u);
+        const u32 low = (lane >> 4) + (LB == 13 ? wave * 4 : ((L.pos >> 1) & 4u) + wave * 8);
+        uint8_t *mine = pieces + high * 1024 + ((low ^ banks(high)) * 16);
+#pragma unroll
+        for (u32 p = 0; p < 4; ++p) *reinterpret_cast<u32x4 *>(mine + p * 256) = out[p];
+        lds_barrier();
+#pragma unroll
+        for (u32 k = 0; k < 4; ++k) {
+            const u32 run = k * kWaves + wave;                         // of 64 units
+            store_b128_at(*reinterpret_cast<const u32x4 *>(pieces + run * 1024 + ((lane ^ banks(run)) * 16)), ry,
+                          lane * 16 + k * (kWaves * 1024), wave * 1024);
+        }
+    } else {
+        constexpr RotMap done = rot_back_map(LB, SWAPS);
+        const u32 out_at = rot_lane_offset(done, L) * 2;
+#pragma unroll
+        for (u32 p = 0; p < 4; ++p) {
+            const RotAt at = rot_at<LB>(out_at, done, wave, p, 16);
+            store_b128_at(out[p], ry, at.vec, at.scalar);
+        }
     }
 }
 

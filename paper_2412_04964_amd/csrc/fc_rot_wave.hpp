@@ -1,12 +1,12 @@
 // fc_rot_wave.hpp -- the Walsh-Hadamard transform of the rotation kernels, held in registers.
 //
-// A wavefront owns 2048 elements, 32 per lane: v[p][i], p = 0..3, i = 0..7.  Element bits 0-2 are i; bits 3-6 are the lane's
-// place in its row of 16 (a permutation of the lanes inside every 8, below).  Bits 7 and on lie in lane bits 4 and 5, in the
-// two bits of p and in the wavefront number, and move as the stages pass (RotMap): a stage is done where its bit
-// lies in p, and bits change places by whole registers.  A row of 16 lanes always holds 128 consecutive elements, so binary16
-// values go to and from memory as they are, in runs of 256 bytes, with no staging through LDS.  Stages run in the order of
-// the bits; costs are SIMD cycles per value, as measured (v_add_f32, v_sub_f32, v_fmac_f32: 2; anything with a DPP operand: 4;
-// v_permlane16/32_swap: 8 for two values; ds_swizzle 2 and ds_bpermute 6 LDS cycles for the whole compute unit):
+// A wavefront owns 2048 elements, 32 per lane: v[p][i], p = 0..3, i = 0..7.  Element bits 0-2 are i.  The other bits lie in the lane's
+// place in its row of 16 (a permutation of the lanes inside every 8, below), in lane bits 4 and 5, in the two bits of p and in the
+// wavefront number, and move as the stages pass (RotMap): where a stage runs between registers its bit lies in p.  Values are loaded
+// and stored in runs of at least 256 bytes, a 16-byte access per lane and piece, with no staging through LDS.  Stages run in the
+// order of the bits; costs are SIMD cycles per value, as measured where nothing else limits (v_add_f32, v_sub_f32, v_fmac_f32:
+// 2; anything with a DPP operand: 4, and see rot_priority; v_permlane16/32_swap: 8 for two values; ds_swizzle 2 and ds_bpermute 6 LDS
+// cycles for the whole compute unit):
 //   0-2    between registers: 2.
 //   3-6    between lanes of a row of 16, ONE instruction per value: v_fmac_f32 with a DPP operand, y = dpp(y) * sgn + y: 4.
 //          DPP offers lane ^ 1, ^ 2, ^ 7 (half-row mirror) and ^ 8 (rotation by 8) but not ^ 4; these four masks are
@@ -17,14 +17,17 @@
 //          inverse transform, run on values in this frame with the opposite signs, undoes it.  The one thing that
 //          is lost is the sign of a zero.
 //   7, 8   between pieces: 2.  Values are loaded with these bits in p.
+//   blocks of 1024 and 2048 (a wavefront, or half of one):
 //   9      in lane bit 4: the partner's value comes through the LDS crossbar (ds_swizzle: no LDS memory), then one
-//          v_fmac_f32: 2.  (Blocks of 8192 let it change places with bit 7 by v_permlane16_swap instead: 6.)
+//          v_fmac_f32: 2.
 //   10     changes places with bit 8 (v_permlane32_swap, then between pieces): 6.
-//   11, 12 the wavefronts of a block exchange pieces for wavefront number through LDS (rot_exchange), so that these bits are
-//          piece bits too.
-// FP8 codes keep the sign of zero, so that quantizer's lanes compute a - b itself in stages 3-6 (a DPP move and a
-// v_fma_f32 in 3 and 4, as stage 9 in 5 and 6) and every frame is +1.  The crossbar for 5 and 6 of the other quantizers
-// as well: 2 % faster for blocks of 1024, 3 % slower in the all-reduce, whose four wavefronts per SIMD hide less latency.
+//   blocks of 4096 and 8192: all values go through LDS once (rot_exchange), where wavefronts exchange pieces and lanes
+//          change places: 9, of blocks of 8192 also 10, comes into the row of 16 (DPP: 4), the last two bits into p (2); what
+//          took their places, 5 to 8, needs no more stages.  The form `swaps` of blocks of 8192 brings 9 and 10 into p by swaps
+//          (6 each) and only 11 and 12 through LDS.
+// FP8 codes keep the sign of zero, so that quantizer's lanes compute a - b itself in the stages inside a row (a DPP move and a
+// v_fma_f32 in 3 and 4, the crossbar as in stage 9 in 5 and 6 and, blocks of 4096, 9) and every frame is +1.  The crossbar for 5 and 6
+// of the other quantizers as well: 2 % faster for blocks of 1024, 3 % slower in the all-reduce.
 #pragma once
 
 #include "fc_device.hpp"
@@ -33,43 +36,54 @@ namespace fc {
 
 struct RotLane {
     u32 lane, pos;           // pos: place of the lane's 8 elements in the wavefront's 64
-    int far;                 // byte index of lane ^ 32
     float s[5];              // +1 / -1 by bits 0..4 of pos
-    float frame;             // product of s[0..3]: the frame after stages 3-6 (1 for FP8)
+    float frame;             // the frame after the DPP stages, the product of their s (1 for FP8)
 };
 
-template <bool FP8>
+// FRAMED: bits of pos, and lane bits 4 and 5, that hold element bits whose stage was a DPP one
+template <bool FP8, u32 FRAMED = 15u>
 __device__ __forceinline__ RotLane rot_lane(u32 lane)
 {
     RotLane L;
     L.lane = lane;
     L.pos = lane ^ ((lane & 4u) ? 3u : 0u);
-    L.far = (int)((lane ^ 32u) * 4u);
 #pragma unroll
     for (int b = 0; b < 5; ++b) L.s[b] = (L.pos >> b) & 1u ? -1.0f : 1.0f;
-    L.frame = FP8 ? 1.0f : ((__popc(L.pos & 15u) & 1) ? -1.0f : 1.0f);
+    L.frame = FP8 ? 1.0f : ((__popc(L.pos & FRAMED) & 1) ? -1.0f : 1.0f);
     return L;
 }
 
-// Which element bit lies in lane bits 4 and 5, in the two piece bits and in the wavefront number
+// Which element bit lies in lane bits 4 and 5, in the two piece bits, in the wavefront number and in bits 0-3 of pos
 struct RotMap {
     int l4, l5, p0, p1, w0, w1;
+    int r0 = 3, r1 = 4, r2 = 5, r3 = 6;
 };
 constexpr RotMap kRotLoaded = {9, 10, 7, 8, 11, 12};                 // as values are loaded and the transforms begin
 constexpr RotMap kRotNatural = {7, 8, 9, 10, 11, 12};                // as codes are loaded (see rot_words_loaded)
-constexpr RotMap rot_forward_map(int lb)                             // after the forward transform
+// A block of 8192 has two forms, `swaps` or not (rot_swaps_apply); the other blocks have one.
+constexpr RotMap rot_forward_map(int lb, bool swaps)                 // after the forward transform
 {
     return lb == 10 ? RotMap{9, 10, 7, 8, 11, 12} : lb == 11 ? RotMap{9, 8, 7, 10, 11, 12}
-         : lb == 12 ? RotMap{9, 8, 7, 11, 10, 12} : RotMap{7, 8, 11, 12, 9, 10};
+         : lb == 12 ? RotMap{5, 6, 10, 11, 8, 12, 3, 4, 9, 7}
+         : swaps ? RotMap{7, 8, 11, 12, 9, 10} : RotMap{5, 6, 11, 12, 7, 8, 3, 4, 9, 10};
 }
-constexpr RotMap rot_back_map(int lb)                                // after an inverse transform that follows a forward one
+constexpr RotMap rot_back_map(int lb, bool swaps)                    // after the inverse transform that follows a forward one
 {
-    return lb == 12 ? RotMap{9, 10, 7, 11, 8, 12} : lb == 13 ? RotMap{11, 10, 9, 12, 7, 8} : rot_forward_map(lb);
+    return lb == 12 ? RotMap{3, 4, 7, 8, 6, 12, 9, 10, 11, 5}
+         : lb == 13 ? (swaps ? RotMap{11, 10, 9, 12, 7, 8} : RotMap{3, 4, 7, 8, 5, 6, 9, 10, 11, 12})
+         : rot_forward_map(lb, swaps);
 }
-// element offsets in the workgroup's tile: of the lane (without bits 0-2 of pos below `keep`), and of a piece
+constexpr u32 rot_forward_framed(int lb, bool swaps)                 // see rot_lane
+{
+    return lb == 12 ? 55u : lb == 13 && !swaps ? 63u : 15u;
+}
+// element offsets in the workgroup's tile: of the lane (without the bits of pos that `keep` leaves out), and of a piece
 __device__ __forceinline__ u32 rot_lane_offset(const RotMap m, const RotLane &L, u32 keep = 15u)
 {
-    return (L.pos & keep) * 8u + (((L.lane >> 4) & 1u) << m.l4) + ((L.lane >> 5) << m.l5);
+    const u32 r = L.pos & keep;
+    const u32 row = m.r0 == 3 && m.r2 == 5 ? r * 8u
+                  : ((r & 1u) << m.r0) + (((r >> 1) & 1u) << m.r1) + (((r >> 2) & 1u) << m.r2) + ((r >> 3) << m.r3);
+    return row + (((L.lane >> 4) & 1u) << m.l4) + ((L.lane >> 5) << m.l5);
 }
 __device__ __forceinline__ u32 rot_piece_offset(const RotMap m, u32 wave, u32 p)
 {
@@ -96,11 +110,11 @@ __device__ __forceinline__ RotAt rot_at(u32 lane_at, const RotMap m, u32 wave, u
     if (rot_whole_tiles(LB)) return RotAt{lane_at, rot_piece_offset(m, wave, p) * bits / 8};
     return RotAt{lane_at + rot_piece_offset(m, 0, p) * bits / 8, 0};
 }
-// Element where the quad of lanes of this lane begins in piece pos & 3.  Scale and zero-point of that piece's 32 elements
+// Element where the quad of lanes of this lane begins in piece lane & 3.  Scale and zero-point of that piece's 32 elements
 // are this lane's to load, or to derive and store.
 __device__ __forceinline__ u32 rot_quad_offset(const RotMap m, const RotLane &L, u32 wave)
 {
-    return rot_lane_offset(m, L, 12u) + rot_piece_offset(m, wave, L.pos & 3u);
+    return rot_lane_offset(m, L, 12u) + rot_piece_offset(m, wave, L.lane & 3u);
 }
 
 // v[0..7] = dpp(v) * s + v.  s_nop: two wait states between the write of a register and its DPP read.
@@ -151,10 +165,51 @@ __device__ __forceinline__ void rot_crossbar_stage(float (&v)[4][8], float s)
         for (int i = 0; i < 8; ++i) v[p][i] = fmaf(v[p][i], s, crossbar<MASK>(v[p][i]));
 }
 
+// Two wavefronts' additions, multiplications, FMAs and logical operations run side by side on a SIMD, 2 cycles each in the mean;
+// an instruction with a DPP operand (also SDWA, v_permlane*, packed binary16, v_fma_mix, v_cvt_pk_f16_f32) has it to itself for 4
+// cycles, and wavefronts at random places of the transform that issue some keep the others' additions from pairing: a stream of three
+// additions to one DPP instruction takes 4.0 cycles per instruction, without DPP 2.1.  Stretches of DPP instructions therefore run at a
+// raised wave priority: they go through at their own rate, and the additions of all wavefronts meet afterwards.  us, without /
+// with: all-reduce, 4 x 8192 x 8192, INT4, group 128 181 / 166, 4 x 8192 x 5120 96 / 90; quantize 8192 x 8192 INT4 43.3 / 38.6; the
+// other way round (additions first) 184 and 43.6.
+// PINNED: nothing moves across (the all-reduce in blocks of 8192 is 2 % faster for it, in blocks of 1024 and 2048 1 % slower, the single
+// transforms as fast or 2 % slower).
+template <int PRIORITY, bool PINNED>
+__device__ __forceinline__ void rot_priority(float (&v)[4][8])
+{
+    if constexpr (PINNED) {
+#pragma unroll
+        for (int p = 0; p < 4; ++p) pin_values(v[p]);
+    }
+    __builtin_amdgcn_s_setprio(PRIORITY);
+    if constexpr (PINNED) {
+#pragma unroll
+        for (int p = 0; p < 4; ++p) pin_values(v[p]);
+    }
+}
+
+// The stage of the element bit in bit B of pos.  INV: the values come in the frame of the forward transform and leave
+// without this bit's share of it.  FP8: no frames; the partner's value is moved, then one v_fma_f32.
+template <int B, bool FP8, bool INV>
+__device__ __forceinline__ void rot_row_stage(float (&v)[4][8], const RotLane &L)
+{
+    constexpr int kCtrl[4] = {kDppQuadXor1, kDppQuadXor2, kDppRowHalfMirror, kDppRowRor8};
+#pragma unroll
+    for (int p = 0; p < 4; ++p) {
+        if constexpr (FP8) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) v[p][i] = fmaf(v[p][i], L.s[B], dpp_read<kCtrl[B]>(v[p][i]));
+        } else {
+            fmac_dpp8<3 + B, INV>(v[p], L.s[B]);
+        }
+    }
+}
+
 // stages 3-6.  INV: the values come in the frame of the forward transform and leave in frame +1.
-template <bool FP8, bool INV>
+template <bool FP8, bool INV, bool PINNED>
 __device__ __forceinline__ void rot_row_stages(float (&v)[4][8], const RotLane &L)
 {
+    rot_priority<1, PINNED>(v);
     if constexpr (FP8) {
 #pragma unroll
         for (int p = 0; p < 4; ++p) {
@@ -174,11 +229,7 @@ __device__ __forceinline__ void rot_row_stages(float (&v)[4][8], const RotLane &
             fmac_dpp8<6, INV>(v[p], L.s[3]);
         }
     }
-}
-
-__device__ __forceinline__ float half_swap(float v, const RotLane &L)  // the value of lane ^ 32
-{
-    return __builtin_bit_cast(float, __builtin_amdgcn_ds_bpermute(L.far, __builtin_bit_cast(int, v)));
+    rot_priority<0, PINNED>(v);
 }
 
 // a and b exchange what lane bit LANE_BIT = 1 of a and = 0 of b hold
@@ -192,7 +243,9 @@ __device__ __forceinline__ void swap_lane_bit(u32 &a, u32 &b)
     b = r[1];
 }
 
-// the bits of lane bit 4 and piece bit 0 (lane bit 5 and piece bit 1) change places
+// The bits of lane bit 4 and piece bit 0 (lane bit 5 and piece bit 1) change places.  A swap needs wait states behind the
+// vector instruction that wrote its operands; the compiler sees to that unless this was written in assembly: then
+// settle_pieces comes first.
 template <int LANE_BIT>
 __device__ __forceinline__ void rot_swap(float (&v)[4][8])
 {
@@ -221,6 +274,14 @@ __device__ __forceinline__ void rot_swap_words(u32 (&word)[4][W])
             for (int k = 0; k < W; ++k) swap_lane_bit<LANE_BIT>(word[p][k], word[p | P][k]);
 }
 
+__device__ __forceinline__ void settle_pieces(float (&v)[4][8])
+{
+#pragma unroll
+    for (int p = 0; p < 4; ++p)
+        asm("s_nop 1" : "+v"(v[p][0]), "+v"(v[p][1]), "+v"(v[p][2]), "+v"(v[p][3]), "+v"(v[p][4]), "+v"(v[p][5]),
+                        "+v"(v[p][6]), "+v"(v[p][7]));
+}
+
 // First stage (span 1) on a pair of binary16 inputs held in one word: (lo + hi, lo - hi) in fp32.  Widening a
 // binary16 number is exact, so a mixed-precision multiply-add lo * 1 +- hi rounds the same real sum once, as the
 // conversion followed by an fp32 add does: one instruction per output instead of a conversion and an add.
@@ -245,8 +306,9 @@ __device__ __forceinline__ void rot_register_stage(float (&v)[4][8])
             }
 }
 
-// one stage between pieces (P = 1, 2)
-template <int P>
+// one stage between pieces (P = 1, 2).  FLIPPED: the second value of a pair comes negated, in the frame of a DPP stage of this
+// bit, which the stage of the inverse transform undoes.
+template <int P, bool FLIPPED = false>
 __device__ __forceinline__ void rot_piece_stage(float (&v)[4][8])
 {
 #pragma unroll
@@ -255,8 +317,8 @@ __device__ __forceinline__ void rot_piece_stage(float (&v)[4][8])
 #pragma unroll
             for (int i = 0; i < 8; ++i) {
                 const float a = v[p][i], b = v[p | P][i];
-                v[p][i] = a + b;
-                v[p | P][i] = a - b;
+                v[p][i] = FLIPPED ? a - b : a + b;
+                v[p | P][i] = FLIPPED ? a + b : a - b;
             }
 }
 
@@ -280,14 +342,21 @@ constexpr int rot_exchange_bytes(int lb, int rounds) { return lb <= 11 ? 16 : ro
 // through LDS as well: sorting it out costs a branch per piece and nothing is gained (LDS is not what bounds these
 // kernels).  The caller sees to it that the previous readers of `lds` are done.
 // Two rounds of half the values each halve the LDS, for kernels that it keeps from filling the SIMDs with wavefronts.
+//
+// The lanes may change places as well, and for LB = 12 the lower piece bit with a lane bit: a lane writes its 16 bytes of a 1 KB
+// run at `out_lane` (odd pieces: at out_lane ^ out_odd), and takes those at `in_lane`, of odd pieces at
+// (in_lane ^ in_odd) + in_step.
+struct RotPlaces {
+    u32 out_lane, out_odd, in_lane, in_odd, in_step;
+};
 template <int LB, int ROUNDS>
-__device__ __forceinline__ void rot_exchange(float (&v)[4][8], uint8_t *lds, u32 wave, u32 lane)
+__device__ __forceinline__ void rot_exchange(float (&v)[4][8], uint8_t *lds, u32 wave, const RotPlaces at_lane)
 {
     static_assert(LB == 12 || LB == 13, "blocks of several wavefronts");
     static_assert(ROUNDS == 1 || ROUNDS == 2, "all of a lane's 32 bytes per piece, or half of them");
     constexpr u32 kPiece = 2048 / ROUNDS, kPerSender = LB == 13 ? kPiece : 2 * kPiece, kPerReceiver = 4 * kPiece;
-    uint8_t *out = lds + wave * kPerSender + lane * 16;
-    const uint8_t *in = lds + wave * kPerReceiver + lane * 16;
+    uint8_t *out = lds + wave * kPerSender;
+    const uint8_t *in = lds + wave * kPerReceiver;
 #pragma unroll
     for (u32 r = 0; r < (u32)ROUNDS; ++r) {
         if (r > 0) lds_barrier();
@@ -297,7 +366,7 @@ __device__ __forceinline__ void rot_exchange(float (&v)[4][8], uint8_t *lds, u32
             for (u32 k = 0; k < 2 / ROUNDS; ++k) {
                 const u32 h = r + k;
                 const u32 at = (LB == 13 ? p * kPerReceiver : (p >> 1) * kPerReceiver + (p & 1u) * kPiece) + k * 1024;
-                *reinterpret_cast<u32x4 *>(out + at) =
+                *reinterpret_cast<u32x4 *>(out + (p & 1u ? at_lane.out_lane ^ at_lane.out_odd : at_lane.out_lane) + at) =
                     u32x4{__builtin_bit_cast(u32, v[p][4 * h]), __builtin_bit_cast(u32, v[p][4 * h + 1]),
                           __builtin_bit_cast(u32, v[p][4 * h + 2]), __builtin_bit_cast(u32, v[p][4 * h + 3])};
             }
@@ -307,7 +376,8 @@ __device__ __forceinline__ void rot_exchange(float (&v)[4][8], uint8_t *lds, u32
 #pragma unroll
             for (u32 k = 0; k < 2 / ROUNDS; ++k) {
                 const u32 h = r + k;
-                const u32x4 a = *reinterpret_cast<const u32x4 *>(in + p * kPiece + k * 1024);
+                const u32 at = (LB == 13 ? p * kPiece : (p >> 1) * kPerSender) + (p & 1u) * at_lane.in_step + k * 1024;
+                const u32x4 a = *reinterpret_cast<const u32x4 *>(in + (p & 1u ? at_lane.in_lane ^ at_lane.in_odd : at_lane.in_lane) + at);
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
                     const u32 w = a[i];    // (a bit_cast applied to the vector element itself reads element 0)
@@ -316,41 +386,86 @@ __device__ __forceinline__ void rot_exchange(float (&v)[4][8], uint8_t *lds, u32
             }
     }
 }
+// every lane keeps its place, every piece its lower bit
+template <int LB, int ROUNDS>
+__device__ __forceinline__ RotPlaces rot_same_places(u32 lane)
+{
+    return RotPlaces{lane * 16, 0, lane * 16, 0, LB == 13 ? 0u : 2048u / ROUNDS};
+}
+
+// The places of the exchanges of the forward and of the back transform, where a lane takes over from the one that holds its
+// element bits, wherever they lie.  Element bits of pos 0-3 / lane 4 5 / pieces:
+//   LB = 13  forward  3 4 5 6 / 9 10 / 7 8   -> 3 4 9 10 / 5 6 / 11 12      back  3 4 9 10 / 11 12 / 5 6 -> 9 10 11 12 / 3 4 / 7 8
+//   LB = 12  forward  3 4 5 6 / 9 10 / 7 8   -> 3 4 9 7 / 5 6 / 10 11       back  3 4 9 7 / 10 11 / 5 6  -> 9 10 11 5 / 3 4 / 7 8
+// The xor terms keep the 16 lanes of a row in different banks on both sides.
+template <int LB, int ROUNDS, bool BACK>
+__device__ __forceinline__ RotPlaces rot_places(const RotLane &L)
+{
+    constexpr u32 kPiece = 2048 / ROUNDS;
+    auto out = [](u32 lane) -> u32 {
+        return (lane * 16u) ^ (BACK ? ((lane >> 4) & 3u) << 4 : ((lane >> 4) & (LB == 13 ? 3u : 1u)) << 6);
+    };
+    auto lane_of = [](u32 pos, u32 rows) -> u32 { return (pos ^ ((pos & 4u) ? 3u : 0u)) | (rows << 4); };
+    const u32 rows = (L.lane >> 4) & 3u, r = L.pos & 15u, r3 = r >> 3;
+    if constexpr (LB == 13) {
+        const u32 from = BACK ? lane_of(rows | ((r & 3u) << 2), r >> 2) : lane_of((r & 3u) | (rows << 2), r >> 2);
+        return RotPlaces{out(L.lane), 0, out(from), 0, 0};
+    } else if constexpr (BACK) {
+        const u32 from = lane_of(rows | ((r & 1u) << 2), (r >> 1) & 3u);
+        return RotPlaces{out(L.lane), 128, (out(from) ^ (r3 << 7)) + r3 * kPiece, 128, 0};
+    } else {
+        const u32 from = lane_of((r & 3u) | (rows << 2), (r >> 2) & 1u);
+        return RotPlaces{out(L.lane), 128, (out(from) ^ (r3 << 7)) + r3 * kPiece, 0, 512};
+    }
+}
 
 // Stages 1 ... LB-1 of the forward transform (the caller applies stage 0 while widening): kRotLoaded -> rot_forward_map
-template <int LB, bool FP8, int ROUNDS>
+template <int LB, bool SWAPS, bool FP8, int ROUNDS, bool PINNED>
 __device__ __forceinline__ void rot_forward(float (&v)[4][8], const RotLane &L, uint8_t *lds, u32 wave)
 {
     rot_register_stage<2>(v);
     rot_register_stage<4>(v);
-    rot_row_stages<FP8, false>(v, L);
+    rot_row_stages<FP8, false, PINNED>(v, L);
     rot_piece_stage<1>(v);
     rot_piece_stage<2>(v);
-    if constexpr (LB == 13) {
+    if constexpr (LB == 13 && SWAPS) {
         rot_swap<4>(v);
         rot_piece_stage<1>(v);
-    } else {
-        rot_crossbar_stage<16>(v, L.s[4]);
-    }
-    if constexpr (LB >= 11) {
         rot_swap<5>(v);
         rot_piece_stage<2>(v);
-    }
-    if constexpr (LB >= 12) {
-        rot_exchange<LB, ROUNDS>(v, lds, wave, L.lane);
-        if constexpr (LB == 13) rot_piece_stage<1>(v);
+        rot_exchange<LB, ROUNDS>(v, lds, wave, rot_same_places<LB, ROUNDS>(L.lane));
+        rot_piece_stage<1>(v);
         rot_piece_stage<2>(v);
+    } else if constexpr (LB >= 12) {
+        rot_exchange<LB, ROUNDS>(v, lds, wave, rot_places<LB, ROUNDS, false>(L));
+        if constexpr (FP8) {
+            rot_crossbar_stage<7>(v, L.s[2]);
+            static_assert(LB == 12 || !FP8, "blocks of 8192: the other form");
+        } else {                           // through the crossbar instead: all-reduce 166 -> 179 us
+            rot_priority<1, PINNED>(v);
+            rot_row_stage<2, false, false>(v, L);
+            if constexpr (LB == 13) rot_row_stage<3, false, false>(v, L);
+            rot_priority<0, PINNED>(v);
+        }
+        rot_piece_stage<1>(v);
+        rot_piece_stage<2>(v);
+    } else {
+        rot_crossbar_stage<16>(v, L.s[4]);
+        if constexpr (LB == 11) {
+            rot_swap<5>(v);
+            rot_piece_stage<2>(v);
+        }
     }
 }
 
 // Inverse transform: stages 0-6 on values in the frame of the forward transform, which they leave (FP8: frame +1)
-template <bool FP8>
+template <bool FP8, bool PINNED>
 __device__ __forceinline__ void rot_inverse_row(float (&v)[4][8], const RotLane &L)
 {
     rot_register_stage<1>(v);
     rot_register_stage<2>(v);
     rot_register_stage<4>(v);
-    rot_row_stages<FP8, true>(v, L);
+    rot_row_stages<FP8, true, PINNED>(v, L);
 }
 
 // ... and the remaining ones, on values that come from memory: kRotLoaded -> rot_forward_map.  `exchanged` is called between the
@@ -366,48 +481,84 @@ __device__ __forceinline__ void rot_inverse_rest(float (&v)[4][8], const RotLane
         rot_piece_stage<2>(v);
     }
     if constexpr (LB >= 12) {
-        rot_exchange<LB, ROUNDS>(v, lds, wave, L.lane);
+        rot_exchange<LB, ROUNDS>(v, lds, wave, rot_same_places<LB, ROUNDS>(L.lane));
         exchanged();
         if constexpr (LB == 13) rot_piece_stage<1>(v);
         rot_piece_stage<2>(v);
     }
 }
-constexpr RotMap rot_inverse_map(int lb) { return lb == 13 ? RotMap{9, 8, 11, 12, 7, 10} : rot_forward_map(lb); }
-
-// ... or that a forward transform has left: rot_forward_map -> rot_back_map
-template <int LB, int ROUNDS>
-__device__ __forceinline__ void rot_inverse_back(float (&v)[4][8], const RotLane &L, uint8_t *lds, u32 wave)
+constexpr RotMap rot_inverse_map(int lb)
 {
-    if constexpr (LB == 13) {
+    return lb == 13 ? RotMap{9, 8, 11, 12, 7, 10} : lb == 12 ? RotMap{9, 8, 7, 11, 10, 12} : rot_forward_map(lb, true);
+}
+
+// The inverse transform of values that a forward transform has left, in its frame: rot_forward_map -> rot_back_map.
+// Returns the frame of the results.
+template <int LB, bool SWAPS, bool FP8, int ROUNDS>
+__device__ __forceinline__ float rot_inverse_back(float (&v)[4][8], const RotLane &L, uint8_t *lds, u32 wave)
+{
+    if constexpr (LB == 13 && SWAPS) {
+        rot_inverse_row<FP8, true>(v, L);
         rot_swap<4>(v);                    // l4 l5 p0 p1 w0 w1 = 11  8  7 12  9 10
         rot_piece_stage<1>(v);
         rot_swap<5>(v);                    //                     11 12  7  8  9 10
         rot_piece_stage<2>(v);
-        rot_exchange<LB, ROUNDS>(v, lds, wave, L.lane);            //     11 12  9 10  7  8
+        rot_exchange<LB, ROUNDS>(v, lds, wave, rot_same_places<LB, ROUNDS>(L.lane));       //     11 12  9 10  7  8
         rot_piece_stage<1>(v);
         rot_piece_stage<2>(v);
         rot_crossbar_stage<16>(v, L.s[4]);
         rot_swap<5>(v);                    //                     11 10  9 12  7  8
         rot_piece_stage<2>(v);
-    } else {
+        return 1.0f;
+    } else if constexpr (LB >= 12) {
+        rot_register_stage<1>(v);
+        rot_register_stage<2>(v);
+        rot_register_stage<4>(v);
+        rot_priority<1, true>(v);
+        rot_row_stage<0, FP8, true>(v, L);
+        rot_row_stage<1, FP8, true>(v, L);
+        if constexpr (!FP8) settle_pieces(v);
+        rot_swap<4>(v);                    // 5 into piece bit 0
+        rot_priority<0, true>(v);
+        rot_piece_stage<1, !FP8>(v);
+        rot_swap<5>(v);                    // 6 into piece bit 1
+        rot_piece_stage<2, !FP8>(v);
+        rot_exchange<LB, ROUNDS>(v, lds, wave, rot_places<LB, ROUNDS, true>(L));
         rot_piece_stage<1>(v);
-        if constexpr (LB >= 11) rot_swap<5>(v);            // 11:  9 10  7  8      12:  9 11  7  8 10
+        rot_piece_stage<2>(v);
+        // 9 ... LB-1 in the row: 9 (and 10 of blocks of 8192) was a DPP stage of the forward transform
+        rot_priority<1, true>(v);
+        rot_row_stage<0, FP8, true>(v, L);
+        rot_row_stage<1, FP8, LB == 13>(v, L);
+        rot_row_stage<2, FP8, false>(v, L);
+        if constexpr (LB == 13) rot_row_stage<3, FP8, false>(v, L);
+        rot_priority<0, true>(v);
+        return FP8 ? 1.0f : LB == 13 ? L.s[2] * L.s[3] : L.s[1] * L.s[2];
+    } else {
+        rot_inverse_row<FP8, false>(v, L);
+        rot_piece_stage<1>(v);
+        if constexpr (LB == 11) rot_swap<5>(v);            //  9 10  7  8
         rot_piece_stage<2>(v);
         rot_crossbar_stage<16>(v, L.s[4]);
-        if constexpr (LB == 12) {
-            rot_exchange<LB, ROUNDS>(v, lds, wave, L.lane);        //                           9 11  7 10  8
+        if constexpr (LB == 11) {
+            rot_swap<5>(v);                                //  9  8  7 10
             rot_piece_stage<2>(v);
         }
-        if constexpr (LB >= 11) {
-            rot_swap<5>(v);                                // 11:  9  8  7 10      12:  9 10  7 11  8
-            rot_piece_stage<2>(v);
-        }
+        return 1.0f;
     }
 }
 
+// Blocks of 8192, the two forms of the transform: `swaps` has fewer instructions that issue alone, the other form fewer in all (and lays
+// a group of 256 elements across wavefronts).  us, swaps / exchange: quantize INT4, group 128 4.14 / 4.21 (128 tokens), 4.44 / 4.50
+// (256), 5.23 / 5.00 (320), 7.96 / 7.52 (1024), 42 / 38 (8192); sym, group 1024 4.49 / 4.50, 5.25 / 5.05, 7.88 / 7.51; all-reduce of two partials
+// INT4 8.75 / 8.78 (128), 10.9 / 10.6 (320), 18.2 / 17.3 (1024), of four 178 / 166 (8192).  Hence the quantizer by the volume, at one workgroup
+// per compute unit, the all-reduce always without swaps.  FP8 always with: its stages in a row cost a move and a multiply-add
+// or a pass through the crossbar (all-reduce of two 8.26 / 8.65 at one token, 130 / 132 at 8192).
+inline bool rot_swaps_apply(bool fp8, int64_t n_elems) { return fp8 || n_elems <= ((int64_t)256 << 13); }
+
 // ---------------------------------------------------------------------------
 // min / max of the groups.  Each lane first has one (min, max) pair per piece; a transposing reduction over bits 3
-// and 4 leaves ONE pair per lane, that of piece pos & 3, so that Eq. 1 is evaluated once per lane for all four
+// and 4 leaves ONE pair per lane, that of piece lane & 3, so that Eq. 1 is evaluated once per lane for all four
 // pieces.  Pairs are in the lane's frame; a partner across a frame boundary has min and max exchanged and negated,
 // which the DPP instruction's operand modifier does.
 // ---------------------------------------------------------------------------
@@ -433,16 +584,44 @@ __device__ __forceinline__ void minmax_step(float &mn, float &mx, float other_mn
     mx = b;
 }
 
-// min and max of the group that piece pos & 3 of the lane belongs to (identical in all its lanes, frame +1).  LDS slots
+// One instruction each; the compiler's own would first canonicalize the inputs.
+__device__ __forceinline__ void minmax_with(float &mn, float &mx, float other_mn, float other_mx)
+{
+    asm("v_min_f32 %0, %0, %1" : "+v"(mn) : "v"(other_mn));
+    asm("v_max_f32 %0, %0, %1" : "+v"(mx) : "v"(other_mx));
+}
+
+// with the pair of lane ^ 16 (LANE_BIT = 4) or lane ^ 32
+template <int LANE_BIT>
+__device__ __forceinline__ void minmax_across(float &mn, float &mx)
+{
+    u32 a = __builtin_bit_cast(u32, mn), b = a, c = __builtin_bit_cast(u32, mx), d = c;
+    asm("s_nop 1" : "+v"(a), "+v"(b), "+v"(c), "+v"(d));     // see rot_swap
+    swap_lane_bit<LANE_BIT>(a, b);
+    swap_lane_bit<LANE_BIT>(c, d);
+    mn = __builtin_bit_cast(float, a);
+    mx = __builtin_bit_cast(float, c);
+    minmax_with(mn, mx, __builtin_bit_cast(float, b), __builtin_bit_cast(float, d));
+}
+
+template <int CTRL>
+__device__ __forceinline__ void minmax_dpp(float &mn, float &mx)
+{
+    mn = dpp_min<CTRL>(mn);
+    mx = dpp_max<CTRL>(mx);
+}
+
+// min and max of the group that piece lane & 3 of the lane belongs to (identical in all its lanes, frame +1).  LDS slots
 // `slot` carry the pairs of groups that span wavefronts; the caller has a barrier between two uses of them.
-template <int LB, bool FP8>
+constexpr int kRotSlots = 16;              // pairs per wavefront: those of the lanes of its first row
+template <int LB, bool SWAPS, bool FP8>
 __device__ __forceinline__ void rot_group_minmax(const float (&v)[4][8], const RotLane &L, int group_shift, u32 wave,
-                                                 float (*slot)[4][2], float &mn_out, float &mx_out)
+                                                 float (*slot)[kRotSlots][2], float &mn_out, float &mx_out)
 {
     float mn[4], mx[4];
 #pragma unroll
     for (int p = 0; p < 4; ++p) lane_minmax(v[p], mn[p], mx[p]);
-    const bool b3 = (L.pos & 1u) != 0, b4 = (L.pos & 2u) != 0;
+    const bool b3 = (L.lane & 1u) != 0, b4 = (L.lane & 2u) != 0;
     float n2[2], x2[2];
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
@@ -452,38 +631,47 @@ __device__ __forceinline__ void rot_group_minmax(const float (&v)[4][8], const R
     }
     float n = b4 ? n2[1] : n2[0], x = b4 ? x2[1] : x2[0];
     minmax_step<4, FP8>(n, x, b4 ? n2[0] : n2[1], b4 ? x2[0] : x2[1]);
-    if (group_shift > 5) minmax_step<5, FP8>(n, x, n, x);
-    if (group_shift > 6) minmax_step<6, FP8>(n, x, n, x);
-    // element bits from 7 on, where the forward transform left them; piece bits flip with bits 3 and 4 of the lane now
-    constexpr RotMap m = rot_forward_map(LB);
-    if (group_shift > m.l4) {
-        n = fminf(n, crossbar<16>(n));
-        x = fmaxf(x, crossbar<16>(x));
-    }
-    if (group_shift > m.l5) {
-        n = fminf(n, half_swap(n, L));
-        x = fmaxf(x, half_swap(x, L));
-    }
-    if (group_shift > m.p0) minmax_step<3, FP8>(n, x, n, x);
-    if (group_shift > m.p1) minmax_step<4, FP8>(n, x, n, x);
     if constexpr (!FP8) {
         const float t = L.frame < 0.0f ? -x : n;
         x = L.frame < 0.0f ? -n : x;
         n = t;
     }
+    // the other element bits, where the forward transform left them; partners hold the same piece (lane & 3) throughout,
+    // piece bits flip with lane bits 0 and 1
+    constexpr RotMap m = rot_forward_map(LB, SWAPS);
+    if constexpr (m.r2 == 5) {
+        if (group_shift > 6) {             // the other three quads of the row
+            minmax_dpp<kDppRowRor4>(n, x);
+            minmax_dpp<kDppRowRor8>(n, x);
+        } else if (group_shift > 5) {      // lane ^ 4, as lane ^ 3 ^ 7
+            float n3, x3;
+            asm("s_nop 1\n\tv_mov_b32_dpp %2, %0 quad_perm:[3,2,1,0] row_mask:0xf bank_mask:0xf\n\t"
+                "v_mov_b32_dpp %3, %1 quad_perm:[3,2,1,0] row_mask:0xf bank_mask:0xf\n\ts_nop 1\n\t"
+                "v_min_f32_dpp %0, %2, %0 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
+                "v_max_f32_dpp %1, %3, %1 row_half_mirror row_mask:0xf bank_mask:0xf"
+                : "+v"(n), "+v"(x), "=&v"(n3), "=&v"(x3));
+        }
+    }
+    if (group_shift > m.l4) minmax_across<4>(n, x);
+    if (group_shift > m.l5) minmax_across<5>(n, x);
+    if constexpr (m.r2 != 5) {
+        if (group_shift > m.r2) minmax_with(n, x, crossbar<4>(n), crossbar<4>(x));
+        if (group_shift > m.r3) minmax_dpp<kDppRowRor8>(n, x);
+    }
+    if (group_shift > m.p0) minmax_dpp<kDppQuadXor1>(n, x);
+    if (group_shift > m.p1) minmax_dpp<kDppQuadXor2>(n, x);
     if constexpr (LB >= 12) {
         if (group_shift > m.w0) {
-            if (L.lane < 4u) {                             // lanes 0 ... 3 hold pieces 0 ... 3
+            if (L.lane < (u32)kRotSlots) {
                 slot[wave][L.lane][0] = n;
                 slot[wave][L.lane][1] = x;
             }
             lds_barrier();
-            const u32 piece = L.pos & 3u;
-            n = fminf(n, slot[wave ^ 1u][piece][0]);
-            x = fmaxf(x, slot[wave ^ 1u][piece][1]);
+            const u32 at = L.lane & (kRotSlots - 1u);
+            minmax_with(n, x, slot[wave ^ 1u][at][0], slot[wave ^ 1u][at][1]);
             if (LB == 13 && group_shift > m.w1) {
-                n = fminf(n, fminf(slot[wave ^ 2u][piece][0], slot[wave ^ 3u][piece][0]));
-                x = fmaxf(x, fmaxf(slot[wave ^ 2u][piece][1], slot[wave ^ 3u][piece][1]));
+                minmax_with(n, x, slot[wave ^ 2u][at][0], slot[wave ^ 2u][at][1]);
+                minmax_with(n, x, slot[wave ^ 3u][at][0], slot[wave ^ 3u][at][1]);
             }
         }
     }
@@ -491,13 +679,13 @@ __device__ __forceinline__ void rot_group_minmax(const float (&v)[4][8], const R
     mx_out = x;
 }
 
-// the value that the lanes with pos & 3 == P of the quad hold, in all lanes
+// the value that the lanes with lane & 3 == P of the quad hold, in all lanes
 template <int P>
 __device__ __forceinline__ float of_piece(float v)
 {
-    const int x = __builtin_bit_cast(int, v);
-    const int a = __builtin_amdgcn_update_dpp(0, x, P * 0x55, 0xF, 0xF, true);         // lane P of every quad
-    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(a, x, (3 - P) * 0x55, 0xF, 0xA, false));   // lanes 4-7, 12-15
+    float r = dpp_read<P * 0x55>(v);
+    asm("" : "+v"(r));                     // else the DPP operand is folded into every multiplication (4 cycles instead of 2)
+    return r;
 }
 
 }  // namespace fc

@@ -182,6 +182,35 @@ def test_both_forms_give_the_same_bits(fc, quantizer, bits, hidden):
             assert torch.equal(y.t.view(torch.int16), back[pick]), what + "dequantize"
 
 
+@pytest.mark.parametrize("quantizer,bits", QUANTIZERS)
+@pytest.mark.parametrize("hidden", [8192, 12288])
+def test_wide_blocks_both_layouts_every_group(fc, quantizer, bits, hidden):
+    # Blocks of 8192 quantize in one layout of the lanes up to 2^21 elements and in another above, where a group of 256 elements and
+    # more spans wavefronts; blocks of 4096 (hidden 12288) lay groups of 512 and more across them.  Every group, rows of every
+    # kind, compared with the oracle and repeated up to both sides of the limit.
+    rng = np.random.default_rng(hidden + bits)
+    x = synth_inputs.make_partials(1, 5, hidden, seed=hidden + 1)[0]
+    x[1] = (rng.standard_normal(hidden) * np.exp(rng.uniform(-8, 8, hidden))).astype(np.float16)
+    x[2] = rng.standard_normal(hidden) * 1e-3 + 3.0
+    x[3] = np.float16(6e-8) * (np.arange(hidden) % 5)
+    x[4, ::2] = np.float16(-0.0)
+    few = dev(x.view(np.uint16)).view(torch.float16)
+    n_meta = 3 if quantizer == oracle.ASYM else 2
+    for group in (32, 64, 128, 256, 512, 1024, 2048, 4096, 8192):
+        if hidden % group:
+            continue
+        wants = [dev(a) for a in oracle.quantize_rot(x, group, bits, quantizer)[:n_meta]]
+        for rows in (5, (1 << 21) // hidden, (1 << 21) // hidden + 1):
+            pick = torch.arange(rows, device="cuda") % 5
+            c = Guarded((rows, hidden * bits // 8), torch.uint8)
+            s, z = [Guarded((rows, hidden // group), torch.float32) for _ in range(2)]
+            fc.quantize_rot(few[pick], group, bits, quantizer, out=(c.t, s.t, z.t))
+            torch.cuda.synchronize()
+            for g in (c, s, z): g.check()
+            for got, w in zip((c.t, s.t, z.t), wants):
+                assert torch.equal(got.view(torch.uint8), w[pick].view(torch.uint8)), "h=%d g=%d rows=%d" % (hidden, group, rows)
+
+
 @pytest.mark.parametrize("quantizer,n_src", [(oracle.ASYM, 3), (oracle.ASYM, 4), (oracle.ASYM, 8), (oracle.SYM, 5), (oracle.SYM, 8),
                                              (oracle.FP8, 2), (oracle.FP8, 3), (oracle.FP8, 8)])
 @pytest.mark.parametrize("hidden", [1024, 3072, 4096, 8192])
