@@ -72,7 +72,7 @@ __device__ __forceinline__ void rot_pack_literal(const float (&v)[4][8], const R
 
 // Rotate block by block and quantize (FinegrainedQuantize of Algorithm 1 on the rotated values).
 // n_elems: elements of the whole tensor, a multiple of 2^LB.
-template <int BITS, int CODEC, int LB, bool SWAPS>
+template <int BITS, int CODEC, bool SWAPS, int LB>
 __global__ __launch_bounds__(64 * rot_group_waves(LB)) void k_quantize_rot(
     const uint16_t *__restrict__ x, int64_t n_elems, int group_shift, uint8_t *__restrict__ codes,
     float *__restrict__ scales, float *__restrict__ zeros)
@@ -224,11 +224,12 @@ __device__ __forceinline__ void rot_unpack(const u32 (&word)[4][BITS / 4], float
     }
 }
 
-// Wavefronts per SIMD to leave registers for: left to itself the compiler keeps temporaries of the exact form.  Seven would make
-// the asymmetric 8-bit kernel of blocks of 2048 spill (8192 x 2048, g = 128: 11.1 us, with six 10.5).
+// Wavefronts per SIMD to leave registers for: left to itself the compiler keeps temporaries of the exact form.  One more would make
+// the integer 8-bit kernels spill (asymmetric, 8192 x 2048, g = 128: with seven 11.1 us, with six 10.5).
 constexpr int rot_dequantize_waves(int bits, int codec, int lb)
 {
-    return lb >= 12 ? 8 : lb == 11 && bits == 8 && codec == kAsym ? 6 : 7;
+    if (lb >= 12) return bits == 8 && codec != kFp8 ? 7 : 8;
+    return bits == 8 && codec == kAsym ? 6 : 7;
 }
 
 // Dequantize, rotate back block by block and round to binary16 (last step of Algorithm 1).
@@ -356,8 +357,8 @@ hipError_t quantize_rot_one(const uint16_t *x, int64_t n_elems, int group, uint8
     const int sh = log2_int(group);
     if constexpr (LB == 13 && CODEC != kFp8)
         if (!rot_swaps_apply(false, n_elems))
-            return launch_kernel(k_quantize_rot<BITS, CODEC, LB, false>, grid, block, stream, x, n_elems, sh, c, scales, zeros);
-    return launch_kernel(k_quantize_rot<BITS, CODEC, LB, true>, grid, block, stream, x, n_elems, sh, c, scales, zeros);
+            return launch_kernel(k_quantize_rot<BITS, CODEC, false, LB>, grid, block, stream, x, n_elems, sh, c, scales, zeros);
+    return launch_kernel(k_quantize_rot<BITS, CODEC, true, LB>, grid, block, stream, x, n_elems, sh, c, scales, zeros);
 }
 
 template <int BITS, int CODEC>
