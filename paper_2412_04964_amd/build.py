@@ -90,7 +90,7 @@ def _compile_torch_ext():
     cmd += [os.path.join(CSRC, "fc_torch.cpp"), "-o", tmp]
     for path in cpp_extension.library_paths():
         cmd += ["-L" + path, "-Wl,-rpath," + path]
-    cmd += ["-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch", "-ltorch_python"]
+    cmd += ["-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_hip", "-ltorch", "-ltorch_python"]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError("compiling fc_torch.cpp failed:\n%s\n%s" % (" ".join(cmd), r.stderr))

@@ -18,6 +18,7 @@
 #include <dlfcn.h>
 
 #include <ATen/ATen.h>
+#include <ATen/hip/EmptyTensor.h>
 #include <ATen/PythonTorchFunctionTLS.h>
 #include <c10/core/impl/LocalDispatchKeySet.h>
 #include <c10/hip/HIPFunctions.h>
@@ -104,9 +105,14 @@ bool geometry(int64_t hidden, int64_t group)
     return group >= 32 && group <= 16384 && (group & (group - 1)) == 0 && hidden > 0 && hidden % group == 0;
 }
 
-at::Tensor empty2(int64_t a, int64_t b, at::ScalarType dtype, const at::Tensor &like)
+// An uninitialized tensor.  What torch.empty does behind its dispatcher, which no mode, transform or tracing watches here (see
+// plain_context): 0.27 us less of 0.9 a tensor (quantize with its three results allocated 5.95 -> 5.15 us, a launch alone takes 2.9).
+// Where torch has been asked to fill new memory it is torch.empty itself.
+at::Tensor empty(at::IntArrayRef shape, at::ScalarType dtype, const at::Tensor &like)
 {
-    return at::empty({a, b}, at::TensorOptions().dtype(dtype).device(like.device()));
+    if (at::globalContext().deterministicAlgorithms() && at::globalContext().deterministicFillUninitializedMemory())
+        return at::empty(shape, at::TensorOptions().dtype(dtype).device(like.device()));
+    return at::Tensor(at::detail::empty_cuda(shape, dtype, like.device(), std::nullopt));
 }
 
 PyObject *fallback() { Py_RETURN_NONE; }
@@ -161,7 +167,7 @@ struct Coded {
                   const at::Tensor &like)
     {
         for (int i = 0; i < n; ++i) {
-            own[i] = empty2(tokens, i ? hidden / group : hidden * bits / 8, i ? meta : at::kByte, like);
+            own[i] = empty({tokens, i ? hidden / group : hidden * bits / 8}, i ? meta : at::kByte, like);
             t[i] = &own[i];
         }
     }
@@ -312,7 +318,7 @@ PyObject *fused(PyObject *, PyObject *const *a, Py_ssize_t n_args)
 const at::Tensor *result_tensor(PyObject *out, int64_t t, int64_t h, const at::Tensor &like, int device, at::Tensor &own)
 {
     if (out == Py_None) {
-        own = empty2(t, h, at::kHalf, like);
+        own = empty({t, h}, at::kHalf, like);
         return &own;
     }
     const at::Tensor *y = plain(out, at::kHalf, device);
@@ -410,7 +416,7 @@ PyObject *allreduce(PyObject *, PyObject *const *a, Py_ssize_t n_args)
     const at::Tensor *y = result_tensor(out, t, h, *x, device, own);
     if (!y) return fallback();
     if (!ws) {
-        own_ws = at::empty({need > 16 ? need : 16}, at::TensorOptions().dtype(at::kByte).device(x->device()));
+        own_ws = empty({need > 16 ? need : 16}, at::kByte, *x);
         ws = &own_ws;
     }
     const void *px = x->data_ptr();

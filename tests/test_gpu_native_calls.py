@@ -217,3 +217,29 @@ def test_native_module_takes_no_cpu_tensor():
     assert b._calls().allreduce_sim(x[None], 128, 4, 4, None, None) is None
     with pytest.raises(TypeError):
         b.quantize(x, 128, 4)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("inference", [False, True])
+def test_allocated_results_are_tensors_like_those_of_torch_empty(inference):
+    # the native calls allocate without torch's dispatcher: type, place, layout, storage, autograd state, the allocator's
+    # bookkeeping and torch's request to fill new memory are those of torch.empty
+    from paper_2412_04964_amd import binding as b
+    x = torch.randn(3, 5, 1024, device="cuda").half()
+    with torch.inference_mode(inference):
+        for t in [*b.quantize(x[0], 128, 4), b.allreduce_sim(x, 128, 4, 8), b.quantize_cmeta(x[0][:0], 128, 8)[1]]:
+            like = torch.empty(tuple(t.shape), dtype=t.dtype, device="cuda")
+            assert type(t) is type(like) and t.device == like.device and t.stride() == like.stride()
+            assert t.untyped_storage().nbytes() == like.untyped_storage().nbytes() and t.storage_offset() == 0
+            assert t.requires_grad == like.requires_grad and t.is_inference() == like.is_inference()
+            t.record_stream(torch.cuda.current_stream())
+    before = torch.cuda.memory_allocated()
+    kept = b.quantize(x[0], 128, 8)
+    assert torch.cuda.memory_allocated() > before
+    want = [k.clone() for k in kept]
+    torch.use_deterministic_algorithms(True)
+    try:
+        again = b._calls().quantize(x[0], 128, 8, None)
+    finally:
+        torch.use_deterministic_algorithms(False)
+    assert again is not None and all(torch.equal(a, w) for a, w in zip(again, want))
