@@ -19,10 +19,11 @@
 //
 // What bounds them: vector instructions and which of them issue side by side (rot_priority in fc_rot_wave.hpp) in blocks of 8192, as much
 // the wait for memory in blocks of 1024, since a wavefront loads, transforms, stores and ends.  Rotate + quantize / dequantize + rotate,
-// us, with the rows in LDS between phases of four or five stages (fc_rot_rows.hip) -> in registers -> with raised priority and, blocks of
-// 4096 and 8192, element bits 9 and 10 by way of the exchange (quantizer): 8192 x 8192 INT4 46.0 -> 43.5 -> 37.5 / 43.9 -> 39.7 -> 38.4;
-// the same in FP8 55.5 -> 45.2 -> 44 / 46.3 -> 42.9 -> 42.2; 8192 x 4096 INT8 - -> 22.9 -> 20.8 / - -> 21.9 -> 21.1; 8192 x 5120 INT4 (blocks of
-// 1024) 22.9 -> 25.4 -> 20.7 / 24.5 -> 22.0 -> 21.4.  Launch-bound volumes run in fc_rot_rows.hip where that is faster.
+// us, with the rows in LDS between phases of four or five stages (fc_rot_rows.hip) -> in registers -> with raised priority over the stages in
+// a row and, blocks of 4096 and 8192, element bits 9 and 10 by way of the exchange (quantizer) -> with raised priority over the
+// first stage and the unpacking too: 8192 x 8192 INT4 46.0 -> 43.5 -> 37.5 -> 35.9 / 43.9 -> 39.7 -> 38.4 -> 36.0; the same in FP8 55.5 -> 45.2 -> 44
+// -> 43.5 / 46.3 -> 42.9 -> 42.2 -> 41.0; 8192 x 4096 INT8 - -> 22.9 -> 20.8 -> 19.9 / - -> 21.9 -> 21.1 -> 20.5; 8192 x 5120 INT4 (blocks of
+// 1024) 22.9 -> 25.4 -> 20.8 -> 19.7 / 24.5 -> 22.0 -> 21.4 -> 19.9.  Launch-bound volumes run in fc_rot_rows.hip where that is faster.
 // Measured and not taken: 32 consecutive elements per lane and a 16 x 16 exchange with other lanes through 5 KB of LDS (40.3 us for blocks
 // of 8192, when this form took 43.0, but 23.8 for 1024 and 23.0 / 48 in the dequantizer, whose register needs it does not fit); all stages
 // between lanes by permlane swaps; persistent workgroups that load the next tile while they transform the current one (4, 5, 6, 12
@@ -99,10 +100,21 @@ __global__ __launch_bounds__(64 * rot_group_waves(LB)) void k_quantize_rot(
         raw[p] = __builtin_amdgcn_raw_buffer_load_b128(rx, at.vec, at.scalar, kStreamLoadPolicy);
     }
     float v[4][8];
+    if constexpr (FP8) {
 #pragma unroll
-    for (int p = 0; p < 4; ++p)
+        for (int p = 0; p < 4; ++p)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) first_stage(raw[p][i], v[p][2 * i], v[p][2 * i + 1]);
+            for (int i = 0; i < 4; ++i) first_stage(raw[p][i], v[p][2 * i], v[p][2 * i + 1]);
+        rot_register_stage<2>(v);
+        rot_register_stage<4>(v);
+    } else {
+#pragma unroll
+        for (int p = 0; p < 4; ++p)
+            rot_first_stages<1>(v[p], [&] {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) first_stage(raw[p][i], v[p][2 * i], v[p][2 * i + 1]);
+            });
+    }
     rot_forward<LB, SWAPS, FP8, kRounds, false>(v, L, pieces, wave);
 
     // Forward scaling fwd = 2^-ceil(n/2), n = LB.  It is a power of two and nothing here is near the ends of
@@ -224,12 +236,11 @@ __device__ __forceinline__ void rot_unpack(const u32 (&word)[4][BITS / 4], float
     }
 }
 
-// Wavefronts per SIMD to leave registers for: left to itself the compiler keeps temporaries of the exact form.  One more would make
-// the integer 8-bit kernels spill (asymmetric, 8192 x 2048, g = 128: with seven 11.1 us, with six 10.5).
-constexpr int rot_dequantize_waves(int bits, int codec, int lb)
+// ... and its stages 0-2 of the inverse transform
+template <int BITS, int CODEC, int P, bool EXACT>
+__device__ __forceinline__ void rot_unpack_stages(const u32 (&word)[4][BITS / 4], float s, u32 z, float frame, float (&v)[4][8])
 {
-    if (lb >= 12) return bits == 8 && codec != kFp8 ? 7 : 8;
-    return bits == 8 && codec == kAsym ? 6 : 7;
+    rot_first_stages<0>(v[P], [&] { rot_unpack<BITS, CODEC, P, EXACT>(word, s, z, frame, v); });
 }
 
 // Dequantize, rotate back block by block and round to binary16 (last step of Algorithm 1).
@@ -241,7 +252,7 @@ constexpr int rot_dequantize_waves(int bits, int codec, int lb)
 // always does.  Wavefronts of one block tell each other with the exchange which form they took, so that a zero of
 // either sign meets only exact ones.
 template <int BITS, int CODEC, int LB>
-__global__ __launch_bounds__(64 * rot_group_waves(LB)) __attribute__((amdgpu_waves_per_eu(rot_dequantize_waves(BITS, CODEC, LB)))) void k_dequantize_rot(
+__global__ __launch_bounds__(64 * rot_group_waves(LB)) void k_dequantize_rot(
     const uint8_t *__restrict__ codes, const float *__restrict__ scales, const float *__restrict__ zeros,
     int64_t n_elems, int group_shift, uint16_t *__restrict__ y)
 {
@@ -290,18 +301,18 @@ __global__ __launch_bounds__(64 * rot_group_waves(LB)) __attribute__((amdgpu_wav
         exact = (__builtin_amdgcn_ballot_w64(!(s >= FLT_MIN)) | (CODEC == kAsym ? zero_is_slow_mask(zf) : 0)) != 0;
     if (exact) {
         const u32 z = __builtin_bit_cast(u32, zf);
-        rot_unpack<BITS, CODEC, 0, true>(word, s, z, 1.0f, v);
-        rot_unpack<BITS, CODEC, 1, true>(word, s, z, 1.0f, v);
-        rot_unpack<BITS, CODEC, 2, true>(word, s, z, 1.0f, v);
-        rot_unpack<BITS, CODEC, 3, true>(word, s, z, 1.0f, v);
-        rot_inverse_row<true, false>(v, L);
+        rot_unpack_stages<BITS, CODEC, 0, true>(word, s, z, 1.0f, v);
+        rot_unpack_stages<BITS, CODEC, 1, true>(word, s, z, 1.0f, v);
+        rot_unpack_stages<BITS, CODEC, 2, true>(word, s, z, 1.0f, v);
+        rot_unpack_stages<BITS, CODEC, 3, true>(word, s, z, 1.0f, v);
+        rot_row_stages<true, true, false, !FP8>(v, L);
     } else if constexpr (!FP8) {
         const u32 z = CODEC == kAsym ? pack_zero_const(zf) : 0;
-        rot_unpack<BITS, CODEC, 0, false>(word, s, z, L.frame, v);
-        rot_unpack<BITS, CODEC, 1, false>(word, s, z, L.frame, v);
-        rot_unpack<BITS, CODEC, 2, false>(word, s, z, L.frame, v);
-        rot_unpack<BITS, CODEC, 3, false>(word, s, z, L.frame, v);
-        rot_inverse_row<false, false>(v, L);
+        rot_unpack_stages<BITS, CODEC, 0, false>(word, s, z, L.frame, v);
+        rot_unpack_stages<BITS, CODEC, 1, false>(word, s, z, L.frame, v);
+        rot_unpack_stages<BITS, CODEC, 2, false>(word, s, z, L.frame, v);
+        rot_unpack_stages<BITS, CODEC, 3, false>(word, s, z, L.frame, v);
+        rot_row_stages<false, true, false>(v, L);
     }
     if constexpr (!FP8 && LB >= 12)
         if (lane == 0) exact_wave[wave] = exact;

@@ -4,11 +4,12 @@
 // fc_dequant_reduce_requant -> fc_dequantize_rot.
 //
 // What bounds it: vector instructions, (N + 1) log2 B of them per element for the butterflies alone, and which of them can issue side
-// by side (rot_priority in fc_rot_wave.hpp).  4 partials of 8192 x 8192 (group 128, INT4): 166 us; 181 without the raised priority, 187 when element
+// by side (rot_priority in fc_rot_wave.hpp).  4 partials of 8192 x 8192 (group 128, INT4): 161 us; 166 when the
+// first stage ran at the ordinary priority, 181 when all did, 187 when element
 // bits 9 and 10 also came into registers by permlane swaps; 195 when bits 7 and 8 went through ds_swizzle and ds_bpermute, which keeps
 // the LDS crossbar of the whole compute unit busy for 6 cycles per instruction; the three steps took 247 to 255 us, the codes
-// and metadata going through HBM and the rows through LDS five times.  4 x 8192 x 4096 92.5 -> 83; 4 x 8192 x 5120 96 -> 88;
-// FP8 4 x 4096 x 8192 106 -> 103.  Five wavefronts per SIMD instead of four: slower.
+// and metadata going through HBM and the rows through LDS five times.  4 x 8192 x 4096 92.5 -> 79.5; 4 x 8192 x 5120 96 -> 84;
+// FP8 4 x 4096 x 8192 106 -> 97.5.  Five wavefronts per SIMD instead of four: slower.
 // The transform and its layout are those of fc_rot_wave.hpp; the partials are taken in
 // source order in a loop, the next one's loads in flight while one is coded.  The sum stays in the frame of the rotated values (see there): rounding is symmetric, so the
 // quantizer works on a negated value as on the value, and the inverse transform undoes the frame.
@@ -165,10 +166,23 @@ __global__ __launch_bounds__(64 * rot_group_waves(LB)) __attribute__((amdgpu_wav
     int j = 0;
     do {                                                               // n_src >= 1; a loop that may be skipped has its loads moved behind the test
         float v[4][8];
+        if constexpr (LB >= 12) {          // all pieces at once, in any order: 256 tokens of 8192 13.66 us, piece by piece 13.85; the same for large volumes
+            __builtin_amdgcn_s_setprio(1);
 #pragma unroll
-        for (int p = 0; p < 4; ++p)
+            for (int p = 0; p < 4; ++p)
 #pragma unroll
-            for (int i = 0; i < 4; ++i) first_stage(raw[p][i], v[p][2 * i], v[p][2 * i + 1]);
+                for (int i = 0; i < 4; ++i) first_stage(raw[p][i], v[p][2 * i], v[p][2 * i + 1]);
+            __builtin_amdgcn_s_setprio(0);
+            rot_register_stage<2>(v);
+            rot_register_stage<4>(v);
+        } else {
+#pragma unroll
+            for (int p = 0; p < 4; ++p)
+                rot_first_stages<1>(v[p], [&] {
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) first_stage(raw[p][i], v[p][2 * i], v[p][2 * i + 1]);
+                });
+        }
         if (LB >= 12 && j > 0) lds_barrier();                          // every wavefront has taken the last exchange
         rot_forward<LB, SWAPS, FP8, 1, (LB >= 12)>(v, L, pieces, wave);
         float mn, mx, s, inv, zf;
@@ -191,7 +205,9 @@ __global__ __launch_bounds__(64 * rot_group_waves(LB)) __attribute__((amdgpu_wav
     rot_scale<1>(acc, s);
     rot_scale<2>(acc, s);
     rot_scale<3>(acc, s);
-    const float frame = rot_inverse_back<LB, SWAPS, FP8, 1>(acc, L, pieces, wave);
+    RotLane M = L;                         // nothing that is derived from it for the rest is held in registers over the loop
+    asm volatile("" : "+v"(M.lane), "+v"(M.pos));
+    const float frame = rot_inverse_back<LB, SWAPS, FP8, 1>(acc, M, pieces, wave);
 
     const rsrc_t ry = make_rsrc(y + e_begin, left);
     const float scale = back * frame;
@@ -209,8 +225,8 @@ __global__ __launch_bounds__(64 * rot_group_waves(LB)) __attribute__((amdgpu_wav
         // and else lie in the same banks (LB = 12: the fourth that varies is 5, unit bit 2).
         auto banks = [](u32 h) -> u32 { return LB == 13 ? h : (h & 3u) | ((h & 4u) << 1); };
         lds_barrier();                                                 // every wavefront has taken the exchange
-        const u32 high = L.pos & (LB == 13 ? 15u : 7u);
-        const u32 low = (lane >> 4) + (LB == 13 ? wave * 4 : ((L.pos >> 1) & 4u) + wave * 8);
+        const u32 high = M.pos & (LB == 13 ? 15u : 7u);
+        const u32 low = (M.lane >> 4) + (LB == 13 ? wave * 4 : ((M.pos >> 1) & 4u) + wave * 8);
         uint8_t *mine = pieces + high * 1024 + ((low ^ banks(high)) * 16);
 #pragma unroll
         for (u32 p = 0; p < 4; ++p) *reinterpret_cast<u32x4 *>(mine + p * 256) = out[p];
@@ -218,12 +234,12 @@ __global__ __launch_bounds__(64 * rot_group_waves(LB)) __attribute__((amdgpu_wav
 #pragma unroll
         for (u32 k = 0; k < 4; ++k) {
             const u32 run = k * kWaves + wave;                         // of 64 units
-            store_b128_at(*reinterpret_cast<const u32x4 *>(pieces + run * 1024 + ((lane ^ banks(run)) * 16)), ry,
-                          lane * 16 + k * (kWaves * 1024), wave * 1024);
+            store_b128_at(*reinterpret_cast<const u32x4 *>(pieces + run * 1024 + ((M.lane ^ banks(run)) * 16)), ry,
+                          M.lane * 16 + k * (kWaves * 1024), wave * 1024);
         }
     } else {
         constexpr RotMap done = rot_back_map(LB, SWAPS);
-        const u32 out_at = rot_lane_offset(done, L) * 2;
+        const u32 out_at = rot_lane_offset(done, M) * 2;
 #pragma unroll
         for (u32 p = 0; p < 4; ++p) {
             const RotAt at = rot_at<LB>(out_at, done, wave, p, 16);

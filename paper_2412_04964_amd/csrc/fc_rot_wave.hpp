@@ -205,8 +205,10 @@ __device__ __forceinline__ void rot_row_stage(float (&v)[4][8], const RotLane &L
     }
 }
 
-// stages 3-6.  INV: the values come in the frame of the forward transform and leave in frame +1.
-template <bool FP8, bool INV, bool PINNED>
+// stages 3-6.  INV: the values come in the frame of the forward transform and leave in frame +1.  RARE: piece after piece, with few registers
+// (left to itself the compiler has so many results of the crossbar in flight that the kernel gets 72 to 80 registers, where 64 let
+// eight wavefronts onto a SIMD: dequantize INT8 8192 x 2048 11.0 / 9.5 us).
+template <bool FP8, bool INV, bool PINNED, bool RARE = false>
 __device__ __forceinline__ void rot_row_stages(float (&v)[4][8], const RotLane &L)
 {
     rot_priority<1, PINNED>(v);
@@ -218,8 +220,19 @@ __device__ __forceinline__ void rot_row_stages(float (&v)[4][8], const RotLane &
 #pragma unroll
             for (int i = 0; i < 8; ++i) v[p][i] = fmaf(v[p][i], L.s[1], dpp_read<kDppQuadXor2>(v[p][i]));
         }
-        rot_crossbar_stage<7>(v, L.s[2]);
-        rot_crossbar_stage<8>(v, L.s[3]);
+        if constexpr (RARE) {
+#pragma unroll
+            for (int p = 0; p < 4; ++p) {
+#pragma unroll
+                for (int i = 0; i < 8; ++i) v[p][i] = fmaf(v[p][i], L.s[2], crossbar<7>(v[p][i]));
+#pragma unroll
+                for (int i = 0; i < 8; ++i) v[p][i] = fmaf(v[p][i], L.s[3], crossbar<8>(v[p][i]));
+                pin_values(v[p]);
+            }
+        } else {
+            rot_crossbar_stage<7>(v, L.s[2]);
+            rot_crossbar_stage<8>(v, L.s[3]);
+        }
     } else {
 #pragma unroll
         for (int p = 0; p < 4; ++p) {
@@ -245,10 +258,12 @@ __device__ __forceinline__ void swap_lane_bit(u32 &a, u32 &b)
 
 // The bits of lane bit 4 and piece bit 0 (lane bit 5 and piece bit 1) change places.  A swap needs wait states behind the
 // vector instruction that wrote its operands; the compiler sees to that unless this was written in assembly: then
-// settle_pieces comes first.
-template <int LANE_BIT>
+// settle_pieces comes first.  ALONE: at raised priority (see rot_priority), for FP8, whose transforms swap most: quantize 4096 x 8192
+// 24.2 / 23.8 us, 1024 x 8192 8.7 / 8.2, all-reduce of four 4096 x 8192 103.8 / 100.3; with integer codes no gain to 1 % slower.
+template <int LANE_BIT, bool ALONE = false>
 __device__ __forceinline__ void rot_swap(float (&v)[4][8])
 {
+    if constexpr (ALONE) rot_priority<1, true>(v);
     constexpr int P = LANE_BIT == 4 ? 1 : 2;
 #pragma unroll
     for (int p = 0; p < 4; ++p)
@@ -260,6 +275,7 @@ __device__ __forceinline__ void rot_swap(float (&v)[4][8])
                 v[p][i] = __builtin_bit_cast(float, a);
                 v[p | P][i] = __builtin_bit_cast(float, b);
             }
+    if constexpr (ALONE) rot_priority<0, true>(v);
 }
 
 // the same on packed words: W per piece and lane
@@ -293,17 +309,40 @@ __device__ __forceinline__ void first_stage(u32 pair, float &sum, float &diff)
 
 // one stage between the registers of a piece (span 1, 2, 4)
 template <int SPAN>
+__device__ __forceinline__ void rot_register_stage(float (&v)[8])
+{
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+        if (!(i & SPAN)) {
+            const float a = v[i], b = v[i | SPAN];
+            v[i] = a + b;
+            v[i | SPAN] = a - b;
+        }
+}
+template <int SPAN>
 __device__ __forceinline__ void rot_register_stage(float (&v)[4][8])
 {
 #pragma unroll
-    for (int p = 0; p < 4; ++p)
-#pragma unroll
-        for (int i = 0; i < 8; ++i)
-            if (!(i & SPAN)) {
-                const float a = v[p][i], b = v[p][i | SPAN];
-                v[p][i] = a + b;
-                v[p][i | SPAN] = a - b;
-            }
+    for (int p = 0; p < 4; ++p) rot_register_stage<SPAN>(v[p]);
+}
+
+// Stages 0-2 of a piece, whose values `form` forms from what was loaded by instructions that issue alone (v_fma_mix_f32, v_cvt_pk_f32_fp8),
+// hence at raised priority (see rot_priority); FIRST: the first of the three that it leaves to do.  us, without / with: quantize INT4
+// (group 128) 8192 x 8192 37.9 / 35.9, x 5120 20.8 / 19.7, INT8 x 4096 20.2 / 19.4; dequantize INT4 37.9 / 36.0, 20.8 / 19.6, FP8
+// 4096 x 8192 22.0 / 21.2; all-reduce of four INT4 x 8192 164.3 / 160.7, x 5120 87.9 / 84.0, FP8 4096 x 8192 102.0 / 97.5.  Not in FP8's
+// quantizer (24.2 / 25.9).  Where a launch has a wavefront per SIMD or less there is nobody to give way to, and the order costs up to 1 %;
+// all four pieces before the next stages are as fast for large volumes and cost the single transforms 2 % there.
+template <int FIRST, typename F>
+__device__ __forceinline__ void rot_first_stages(float (&v)[8], F form)
+{
+    __builtin_amdgcn_s_setprio(1);
+    form();
+    pin_values(v);
+    __builtin_amdgcn_s_setprio(0);
+    pin_values(v);
+    if constexpr (FIRST == 0) rot_register_stage<1>(v);
+    rot_register_stage<2>(v);
+    rot_register_stage<4>(v);
 }
 
 // one stage between pieces (P = 1, 2).  FLIPPED: the second value of a pair comes negated, in the frame of a DPP stage of this
@@ -419,19 +458,17 @@ __device__ __forceinline__ RotPlaces rot_places(const RotLane &L)
     }
 }
 
-// Stages 1 ... LB-1 of the forward transform (the caller applies stage 0 while widening): kRotLoaded -> rot_forward_map
+// Stages 3 ... LB-1 of the forward transform (0-2: rot_first_stages): kRotLoaded -> rot_forward_map
 template <int LB, bool SWAPS, bool FP8, int ROUNDS, bool PINNED>
 __device__ __forceinline__ void rot_forward(float (&v)[4][8], const RotLane &L, uint8_t *lds, u32 wave)
 {
-    rot_register_stage<2>(v);
-    rot_register_stage<4>(v);
     rot_row_stages<FP8, false, PINNED>(v, L);
     rot_piece_stage<1>(v);
     rot_piece_stage<2>(v);
     if constexpr (LB == 13 && SWAPS) {
-        rot_swap<4>(v);
+        rot_swap<4, FP8>(v);
         rot_piece_stage<1>(v);
-        rot_swap<5>(v);
+        rot_swap<5, FP8>(v);
         rot_piece_stage<2>(v);
         rot_exchange<LB, ROUNDS>(v, lds, wave, rot_same_places<LB, ROUNDS>(L.lane));
         rot_piece_stage<1>(v);
@@ -452,7 +489,7 @@ __device__ __forceinline__ void rot_forward(float (&v)[4][8], const RotLane &L, 
     } else {
         rot_crossbar_stage<16>(v, L.s[4]);
         if constexpr (LB == 11) {
-            rot_swap<5>(v);
+            rot_swap<5, FP8>(v);
             rot_piece_stage<2>(v);
         }
     }
@@ -499,15 +536,15 @@ __device__ __forceinline__ float rot_inverse_back(float (&v)[4][8], const RotLan
 {
     if constexpr (LB == 13 && SWAPS) {
         rot_inverse_row<FP8, true>(v, L);
-        rot_swap<4>(v);                    // l4 l5 p0 p1 w0 w1 = 11  8  7 12  9 10
+        rot_swap<4, FP8>(v);                    // l4 l5 p0 p1 w0 w1 = 11  8  7 12  9 10
         rot_piece_stage<1>(v);
-        rot_swap<5>(v);                    //                     11 12  7  8  9 10
+        rot_swap<5, FP8>(v);                    //                     11 12  7  8  9 10
         rot_piece_stage<2>(v);
         rot_exchange<LB, ROUNDS>(v, lds, wave, rot_same_places<LB, ROUNDS>(L.lane));       //     11 12  9 10  7  8
         rot_piece_stage<1>(v);
         rot_piece_stage<2>(v);
         rot_crossbar_stage<16>(v, L.s[4]);
-        rot_swap<5>(v);                    //                     11 10  9 12  7  8
+        rot_swap<5, FP8>(v);                    //                     11 10  9 12  7  8
         rot_piece_stage<2>(v);
         return 1.0f;
     } else if constexpr (LB >= 12) {
@@ -518,10 +555,10 @@ __device__ __forceinline__ float rot_inverse_back(float (&v)[4][8], const RotLan
         rot_row_stage<0, FP8, true>(v, L);
         rot_row_stage<1, FP8, true>(v, L);
         if constexpr (!FP8) settle_pieces(v);
-        rot_swap<4>(v);                    // 5 into piece bit 0
+        rot_swap<4, FP8>(v);                    // 5 into piece bit 0
         rot_priority<0, true>(v);
         rot_piece_stage<1, !FP8>(v);
-        rot_swap<5>(v);                    // 6 into piece bit 1
+        rot_swap<5, FP8>(v);                    // 6 into piece bit 1
         rot_piece_stage<2, !FP8>(v);
         rot_exchange<LB, ROUNDS>(v, lds, wave, rot_places<LB, ROUNDS, true>(L));
         rot_piece_stage<1>(v);
@@ -537,11 +574,11 @@ __device__ __forceinline__ float rot_inverse_back(float (&v)[4][8], const RotLan
     } else {
         rot_inverse_row<FP8, false>(v, L);
         rot_piece_stage<1>(v);
-        if constexpr (LB == 11) rot_swap<5>(v);            //  9 10  7  8
+        if constexpr (LB == 11) rot_swap<5, FP8>(v);            //  9 10  7  8
         rot_piece_stage<2>(v);
         rot_crossbar_stage<16>(v, L.s[4]);
         if constexpr (LB == 11) {
-            rot_swap<5>(v);                                //  9  8  7 10
+            rot_swap<5, FP8>(v);                                //  9  8  7 10
             rot_piece_stage<2>(v);
         }
         return 1.0f;
