@@ -124,7 +124,7 @@ __global__ __launch_bounds__(64 * rot_group_waves(LB)) void k_quantize_rot(
                 for (int i = 0; i < 4; ++i) first_stage(raw[p][i], v[p][2 * i], v[p][2 * i + 1]);
             });
     }
-    rot_forward<LB, SWAPS, FP8, kRounds, false>(v, L, pieces, wave);
+    rot_forward<LB, SWAPS, FP8, kRounds, kRaised>(v, L, pieces, wave);
 
     // Forward scaling fwd = 2^-ceil(n/2), n = LB.  It is a power of two and nothing here is near the ends of
     // the fp32 range (the transformed values are multiples of 2^-24 below 2^30), so scaling commutes
@@ -316,14 +316,14 @@ __global__ __launch_bounds__(64 * rot_group_waves(LB)) void k_dequantize_rot(
         rot_unpack_stages<BITS, CODEC, 1, true>(word, s, z, 1.0f, v);
         rot_unpack_stages<BITS, CODEC, 2, true>(word, s, z, 1.0f, v);
         rot_unpack_stages<BITS, CODEC, 3, true>(word, s, z, 1.0f, v);
-        rot_row_stages<true, true, false, !FP8>(v, L);
+        rot_row_stages<true, true, kRaised, !FP8>(v, L);
     } else if constexpr (!FP8) {
         const u32 z = CODEC == kAsym ? pack_zero_const(zf) : 0;
         rot_unpack_stages<BITS, CODEC, 0, false>(word, s, z, L.frame, v);
         rot_unpack_stages<BITS, CODEC, 1, false>(word, s, z, L.frame, v);
         rot_unpack_stages<BITS, CODEC, 2, false>(word, s, z, L.frame, v);
         rot_unpack_stages<BITS, CODEC, 3, false>(word, s, z, L.frame, v);
-        rot_row_stages<false, true, false>(v, L);
+        rot_row_stages<false, true, kRaised>(v, L);
     }
     if constexpr (!FP8 && LB >= 12)
         if (lane == 0) exact_wave[wave] = exact;

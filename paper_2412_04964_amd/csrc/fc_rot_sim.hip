@@ -114,19 +114,27 @@ __device__ __forceinline__ void rot_scale(float (&d)[4][8], float s)
 }
 
 // The lane number, for what is derived from it after the first loads: left to itself the compiler derives it all before
-// them, 30 instructions and 0.07 us of every launch.
+// them, 30 instructions and 0.07 us of every launch (not with KEPT: the form for one wavefront per SIMD in blocks of 8192 is 0.03 us
+// faster without it).
+template <bool KEPT>
 __device__ __forceinline__ u32 after_loads(u32 lane)
 {
-    asm volatile("" : "+v"(lane) : : "memory");
+    if constexpr (!KEPT) asm volatile("" : "+v"(lane) : : "memory");
     return lane;
 }
 
-template <int CODEC, int LB>
+// ALONE: no wavefront shares its SIMD (launches of at most one workgroup per compute unit), so nothing is raised above another, and blocks
+// of 8192 take the layout with the shorter chain (rot_swaps_apply).  us, the other form / this, two partials, group 128: INT4 one
+// token of 8192 7.41 / 7.25, 200 tokens 8.95 / 8.86, sym INT8 7.24 / 7.03, 8.74 / 8.66, FP8 8.40 / 8.32; FP8 in blocks of 4096 one token
+// 7.87 / 7.72, 256 tokens 8.98 / 8.81.  Integer codes in blocks of 4096 and all shorter blocks are as fast without it; past the
+// limit it loses at once (257 x 4096 8.40 / 9.17).
+template <int CODEC, bool ALONE, int LB>
 __global__ __launch_bounds__(64 * rot_group_waves(LB)) __attribute__((amdgpu_waves_per_eu(4))) void k_allreduce_rot(
     const uint16_t *__restrict__ x, int64_t n_elems, int n_src, int group_shift, RotLevels rs, RotLevels ag,
     uint16_t *__restrict__ y)
 {
-    constexpr bool FP8 = CODEC == kFp8, SWAPS = FP8;                    // see rot_swaps_apply
+    constexpr bool FP8 = CODEC == kFp8, SWAPS = FP8 || ALONE;           // see rot_swaps_apply
+    constexpr RotOrder kOrder = ALONE ? kFlat : LB >= 12 ? kPinned : kRaised;
     constexpr int kWaves = rot_group_waves(LB);
     constexpr int kTile = 2048 * kWaves;
     constexpr int kChunk = (512 * 1024) / (kTile * 2);                  // 512 KB of every partial per XCD and run
@@ -156,7 +164,7 @@ __global__ __launch_bounds__(64 * rot_group_waves(LB)) __attribute__((amdgpu_wav
     constexpr float back = 1.0f / (float)(1 << (LB / 2));               // 2^-floor(n/2)
 
     fetch(0);
-    const RotLane L = rot_lane<FP8, rot_forward_framed(LB, SWAPS)>(after_loads(lane));
+    const RotLane L = rot_lane<FP8, rot_forward_framed(LB, SWAPS)>(after_loads<ALONE && LB == 13>(lane));
     float acc[4][8];
 #pragma unroll
     for (int p = 0; p < 4; ++p)
@@ -166,25 +174,27 @@ __global__ __launch_bounds__(64 * rot_group_waves(LB)) __attribute__((amdgpu_wav
     int j = 0;
     do {                                                               // n_src >= 1; a loop that may be skipped has its loads moved behind the test
         float v[4][8];
-        if constexpr (LB >= 12) {          // all pieces at once, in any order: 256 tokens of 8192 13.66 us, piece by piece 13.85; the same for large volumes
-            __builtin_amdgcn_s_setprio(1);
-#pragma unroll
-            for (int p = 0; p < 4; ++p)
-#pragma unroll
-                for (int i = 0; i < 4; ++i) first_stage(raw[p][i], v[p][2 * i], v[p][2 * i + 1]);
-            __builtin_amdgcn_s_setprio(0);
-            rot_register_stage<2>(v);
-            rot_register_stage<4>(v);
-        } else {
+        // All pieces at once, in any order: 256 tokens of 8192 13.66 us, piece by piece 13.85, four of 30 x 2048 8.93 / 9.15; the same for large
+        // volumes, except FP8 in short blocks (4 x 8192 x 5120 104.7 / 102.5).
+        if constexpr (FP8 && LB < 12) {
 #pragma unroll
             for (int p = 0; p < 4; ++p)
                 rot_first_stages<1>(v[p], [&] {
 #pragma unroll
                     for (int i = 0; i < 4; ++i) first_stage(raw[p][i], v[p][2 * i], v[p][2 * i + 1]);
                 });
+        } else {
+            if constexpr (!ALONE) __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+            for (int p = 0; p < 4; ++p)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) first_stage(raw[p][i], v[p][2 * i], v[p][2 * i + 1]);
+            if constexpr (!ALONE) __builtin_amdgcn_s_setprio(0);
+            rot_register_stage<2>(v);
+            rot_register_stage<4>(v);
         }
         if (LB >= 12 && j > 0) lds_barrier();                          // every wavefront has taken the last exchange
-        rot_forward<LB, SWAPS, FP8, 1, (LB >= 12)>(v, L, pieces, wave);
+        rot_forward<LB, SWAPS, FP8, 1, kOrder>(v, L, pieces, wave);
         float mn, mx, s, inv, zf;
         rot_group_minmax<LB, SWAPS, FP8>(v, L, group_shift, wave, mm, mn, mx);
         rot_params<CODEC>(mn, mx, rs, fwd, s, inv, zf);
@@ -205,9 +215,9 @@ __global__ __launch_bounds__(64 * rot_group_waves(LB)) __attribute__((amdgpu_wav
     rot_scale<1>(acc, s);
     rot_scale<2>(acc, s);
     rot_scale<3>(acc, s);
-    RotLane M = L;                         // nothing that is derived from it for the rest is held in registers over the loop
-    asm volatile("" : "+v"(M.lane), "+v"(M.pos));
-    const float frame = rot_inverse_back<LB, SWAPS, FP8, 1>(acc, M, pieces, wave);
+    RotLane M = L;                         // nothing derived from it for the rest is held in registers over the loop, of which ALONE has enough
+    if constexpr (!ALONE) asm volatile("" : "+v"(M.lane), "+v"(M.pos));
+    const float frame = rot_inverse_back<LB, SWAPS, FP8, 1, kOrder>(acc, M, pieces, wave);
 
     const rsrc_t ry = make_rsrc(y + e_begin, left);
     const float scale = back * frame;
@@ -261,8 +271,11 @@ hipError_t launch_one(const uint16_t *x, int n_src, int64_t n_elems, int group, 
                       hipStream_t stream)
 {
     constexpr int kTile = 2048 * rot_group_waves(LB);
-    return launch_kernel(k_allreduce_rot<CODEC, LB>, dim3((unsigned)((n_elems + kTile - 1) / kTile)),
-                         dim3(64 * rot_group_waves(LB)), stream, x, n_elems, n_src, log2_int(group), rs, ag, y);
+    const dim3 grid((unsigned)((n_elems + kTile - 1) / kTile)), block(64 * rot_group_waves(LB));
+    if constexpr (LB == 13 || (LB == 12 && CODEC == kFp8))              // see k_allreduce_rot
+        if (n_elems <= 256 * (int64_t)kTile)
+            return launch_kernel(k_allreduce_rot<CODEC, true, LB>, grid, block, stream, x, n_elems, n_src, log2_int(group), rs, ag, y);
+    return launch_kernel(k_allreduce_rot<CODEC, false, LB>, grid, block, stream, x, n_elems, n_src, log2_int(group), rs, ag, y);
 }
 
 template <int CODEC>

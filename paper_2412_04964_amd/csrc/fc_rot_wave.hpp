@@ -172,17 +172,19 @@ __device__ __forceinline__ void rot_crossbar_stage(float (&v)[4][8], float s)
 // raised wave priority: they go through at their own rate, and the additions of all wavefronts meet afterwards.  us, without /
 // with: all-reduce, 4 x 8192 x 8192, INT4, group 128 181 / 166, 4 x 8192 x 5120 96 / 90; quantize 8192 x 8192 INT4 43.3 / 38.6; the
 // other way round (additions first) 184 and 43.6.
-// PINNED: nothing moves across (the all-reduce in blocks of 8192 is 2 % faster for it, in blocks of 1024 and 2048 1 % slower, the single
-// transforms as fast or 2 % slower).
-template <int PRIORITY, bool PINNED>
+// kPinned: nothing moves across (the all-reduce in blocks of 8192 is 2 % faster for it, in blocks of 1024 and 2048 1 % slower, the single
+// transforms as fast or 2 % slower).  kFlat: no priorities, for a wavefront that has its SIMD to itself (see ALONE in fc_rot_sim.hip).
+enum RotOrder { kRaised, kPinned, kFlat };
+template <int PRIORITY, RotOrder ORDER>
 __device__ __forceinline__ void rot_priority(float (&v)[4][8])
 {
-    if constexpr (PINNED) {
+    if constexpr (ORDER == kFlat) return;
+    if constexpr (ORDER == kPinned) {
 #pragma unroll
         for (int p = 0; p < 4; ++p) pin_values(v[p]);
     }
     __builtin_amdgcn_s_setprio(PRIORITY);
-    if constexpr (PINNED) {
+    if constexpr (ORDER == kPinned) {
 #pragma unroll
         for (int p = 0; p < 4; ++p) pin_values(v[p]);
     }
@@ -208,10 +210,10 @@ __device__ __forceinline__ void rot_row_stage(float (&v)[4][8], const RotLane &L
 // stages 3-6.  INV: the values come in the frame of the forward transform and leave in frame +1.  RARE: piece after piece, with few registers
 // (left to itself the compiler has so many results of the crossbar in flight that the kernel gets 72 to 80 registers, where 64 let
 // eight wavefronts onto a SIMD: dequantize INT8 8192 x 2048 11.0 / 9.5 us).
-template <bool FP8, bool INV, bool PINNED, bool RARE = false>
+template <bool FP8, bool INV, RotOrder ORDER, bool RARE = false>
 __device__ __forceinline__ void rot_row_stages(float (&v)[4][8], const RotLane &L)
 {
-    rot_priority<1, PINNED>(v);
+    rot_priority<1, ORDER>(v);
     if constexpr (FP8) {
 #pragma unroll
         for (int p = 0; p < 4; ++p) {
@@ -242,7 +244,7 @@ __device__ __forceinline__ void rot_row_stages(float (&v)[4][8], const RotLane &
             fmac_dpp8<6, INV>(v[p], L.s[3]);
         }
     }
-    rot_priority<0, PINNED>(v);
+    rot_priority<0, ORDER>(v);
 }
 
 // a and b exchange what lane bit LANE_BIT = 1 of a and = 0 of b hold
@@ -260,10 +262,11 @@ __device__ __forceinline__ void swap_lane_bit(u32 &a, u32 &b)
 // vector instruction that wrote its operands; the compiler sees to that unless this was written in assembly: then
 // settle_pieces comes first.  ALONE: at raised priority (see rot_priority), for FP8, whose transforms swap most: quantize 4096 x 8192
 // 24.2 / 23.8 us, 1024 x 8192 8.7 / 8.2, all-reduce of four 4096 x 8192 103.8 / 100.3; with integer codes no gain to 1 % slower.
-template <int LANE_BIT, bool ALONE = false>
+template <int LANE_BIT, bool ALONE = false, RotOrder ORDER = kPinned>
 __device__ __forceinline__ void rot_swap(float (&v)[4][8])
 {
-    if constexpr (ALONE) rot_priority<1, true>(v);
+    constexpr RotOrder kOrder = ALONE && ORDER != kFlat ? kPinned : kFlat;
+    rot_priority<1, kOrder>(v);
     constexpr int P = LANE_BIT == 4 ? 1 : 2;
 #pragma unroll
     for (int p = 0; p < 4; ++p)
@@ -275,7 +278,7 @@ __device__ __forceinline__ void rot_swap(float (&v)[4][8])
                 v[p][i] = __builtin_bit_cast(float, a);
                 v[p | P][i] = __builtin_bit_cast(float, b);
             }
-    if constexpr (ALONE) rot_priority<0, true>(v);
+    rot_priority<0, kOrder>(v);
 }
 
 // the same on packed words: W per piece and lane
@@ -459,16 +462,16 @@ __device__ __forceinline__ RotPlaces rot_places(const RotLane &L)
 }
 
 // Stages 3 ... LB-1 of the forward transform (0-2: rot_first_stages): kRotLoaded -> rot_forward_map
-template <int LB, bool SWAPS, bool FP8, int ROUNDS, bool PINNED>
+template <int LB, bool SWAPS, bool FP8, int ROUNDS, RotOrder ORDER>
 __device__ __forceinline__ void rot_forward(float (&v)[4][8], const RotLane &L, uint8_t *lds, u32 wave)
 {
-    rot_row_stages<FP8, false, PINNED>(v, L);
+    rot_row_stages<FP8, false, ORDER>(v, L);
     rot_piece_stage<1>(v);
     rot_piece_stage<2>(v);
     if constexpr (LB == 13 && SWAPS) {
-        rot_swap<4, FP8>(v);
+        rot_swap<4, FP8, ORDER>(v);
         rot_piece_stage<1>(v);
-        rot_swap<5, FP8>(v);
+        rot_swap<5, FP8, ORDER>(v);
         rot_piece_stage<2>(v);
         rot_exchange<LB, ROUNDS>(v, lds, wave, rot_same_places<LB, ROUNDS>(L.lane));
         rot_piece_stage<1>(v);
@@ -479,30 +482,30 @@ __device__ __forceinline__ void rot_forward(float (&v)[4][8], const RotLane &L, 
             rot_crossbar_stage<7>(v, L.s[2]);
             static_assert(LB == 12 || !FP8, "blocks of 8192: the other form");
         } else {                           // through the crossbar instead: all-reduce 166 -> 179 us
-            rot_priority<1, PINNED>(v);
+            rot_priority<1, ORDER>(v);
             rot_row_stage<2, false, false>(v, L);
             if constexpr (LB == 13) rot_row_stage<3, false, false>(v, L);
-            rot_priority<0, PINNED>(v);
+            rot_priority<0, ORDER>(v);
         }
         rot_piece_stage<1>(v);
         rot_piece_stage<2>(v);
     } else {
         rot_crossbar_stage<16>(v, L.s[4]);
         if constexpr (LB == 11) {
-            rot_swap<5, FP8>(v);
+            rot_swap<5, FP8, ORDER>(v);
             rot_piece_stage<2>(v);
         }
     }
 }
 
 // Inverse transform: stages 0-6 on values in the frame of the forward transform, which they leave (FP8: frame +1)
-template <bool FP8, bool PINNED>
+template <bool FP8, RotOrder ORDER>
 __device__ __forceinline__ void rot_inverse_row(float (&v)[4][8], const RotLane &L)
 {
     rot_register_stage<1>(v);
     rot_register_stage<2>(v);
     rot_register_stage<4>(v);
-    rot_row_stages<FP8, true, PINNED>(v, L);
+    rot_row_stages<FP8, true, ORDER>(v, L);
 }
 
 // ... and the remaining ones, on values that come from memory: kRotLoaded -> rot_forward_map.  `exchanged` is called between the
@@ -531,54 +534,54 @@ constexpr RotMap rot_inverse_map(int lb)
 
 // The inverse transform of values that a forward transform has left, in its frame: rot_forward_map -> rot_back_map.
 // Returns the frame of the results.
-template <int LB, bool SWAPS, bool FP8, int ROUNDS>
+template <int LB, bool SWAPS, bool FP8, int ROUNDS, RotOrder ORDER>
 __device__ __forceinline__ float rot_inverse_back(float (&v)[4][8], const RotLane &L, uint8_t *lds, u32 wave)
 {
     if constexpr (LB == 13 && SWAPS) {
-        rot_inverse_row<FP8, true>(v, L);
-        rot_swap<4, FP8>(v);                    // l4 l5 p0 p1 w0 w1 = 11  8  7 12  9 10
+        rot_inverse_row<FP8, ORDER>(v, L);
+        rot_swap<4, FP8, ORDER>(v);                    // l4 l5 p0 p1 w0 w1 = 11  8  7 12  9 10
         rot_piece_stage<1>(v);
-        rot_swap<5, FP8>(v);                    //                     11 12  7  8  9 10
+        rot_swap<5, FP8, ORDER>(v);                    //                     11 12  7  8  9 10
         rot_piece_stage<2>(v);
         rot_exchange<LB, ROUNDS>(v, lds, wave, rot_same_places<LB, ROUNDS>(L.lane));       //     11 12  9 10  7  8
         rot_piece_stage<1>(v);
         rot_piece_stage<2>(v);
         rot_crossbar_stage<16>(v, L.s[4]);
-        rot_swap<5, FP8>(v);                    //                     11 10  9 12  7  8
+        rot_swap<5, FP8, ORDER>(v);                    //                     11 10  9 12  7  8
         rot_piece_stage<2>(v);
         return 1.0f;
     } else if constexpr (LB >= 12) {
         rot_register_stage<1>(v);
         rot_register_stage<2>(v);
         rot_register_stage<4>(v);
-        rot_priority<1, true>(v);
+        rot_priority<1, ORDER>(v);
         rot_row_stage<0, FP8, true>(v, L);
         rot_row_stage<1, FP8, true>(v, L);
         if constexpr (!FP8) settle_pieces(v);
-        rot_swap<4, FP8>(v);                    // 5 into piece bit 0
-        rot_priority<0, true>(v);
+        rot_swap<4, FP8, ORDER>(v);                    // 5 into piece bit 0
+        rot_priority<0, ORDER>(v);
         rot_piece_stage<1, !FP8>(v);
-        rot_swap<5, FP8>(v);                    // 6 into piece bit 1
+        rot_swap<5, FP8, ORDER>(v);                    // 6 into piece bit 1
         rot_piece_stage<2, !FP8>(v);
         rot_exchange<LB, ROUNDS>(v, lds, wave, rot_places<LB, ROUNDS, true>(L));
         rot_piece_stage<1>(v);
         rot_piece_stage<2>(v);
         // 9 ... LB-1 in the row: 9 (and 10 of blocks of 8192) was a DPP stage of the forward transform
-        rot_priority<1, true>(v);
+        rot_priority<1, ORDER>(v);
         rot_row_stage<0, FP8, true>(v, L);
         rot_row_stage<1, FP8, LB == 13>(v, L);
         rot_row_stage<2, FP8, false>(v, L);
         if constexpr (LB == 13) rot_row_stage<3, FP8, false>(v, L);
-        rot_priority<0, true>(v);
+        rot_priority<0, ORDER>(v);
         return FP8 ? 1.0f : LB == 13 ? L.s[2] * L.s[3] : L.s[1] * L.s[2];
     } else {
-        rot_inverse_row<FP8, false>(v, L);
+        rot_inverse_row<FP8, ORDER>(v, L);
         rot_piece_stage<1>(v);
-        if constexpr (LB == 11) rot_swap<5, FP8>(v);            //  9 10  7  8
+        if constexpr (LB == 11) rot_swap<5, FP8, ORDER>(v);            //  9 10  7  8
         rot_piece_stage<2>(v);
         rot_crossbar_stage<16>(v, L.s[4]);
         if constexpr (LB == 11) {
-            rot_swap<5, FP8>(v);                                //  9  8  7 10
+            rot_swap<5, FP8, ORDER>(v);                                //  9  8  7 10
             rot_piece_stage<2>(v);
         }
         return 1.0f;
@@ -588,8 +591,8 @@ __device__ __forceinline__ float rot_inverse_back(float (&v)[4][8], const RotLan
 // Blocks of 8192, the two forms of the transform: `swaps` has fewer instructions that issue alone, the other form fewer in all (and lays
 // a group of 256 elements across wavefronts).  us, swaps / exchange: quantize INT4, group 128 4.14 / 4.21 (128 tokens), 4.44 / 4.50
 // (256), 5.23 / 5.00 (320), 7.96 / 7.52 (1024), 42 / 38 (8192); sym, group 1024 4.49 / 4.50, 5.25 / 5.05, 7.88 / 7.51; all-reduce of two partials
-// INT4 8.75 / 8.78 (128), 10.9 / 10.6 (320), 18.2 / 17.3 (1024), of four 178 / 166 (8192).  Hence the quantizer by the volume, at one workgroup
-// per compute unit, the all-reduce always without swaps.  FP8 always with: its stages in a row cost a move and a multiply-add
+// INT4 7.29 / 7.46 (1), 7.63 / 7.76 (32), 9.05 / 9.17 (256), 10.9 / 10.6 (320), 18.2 / 17.3 (1024), of four 178 / 166 (8192).  Hence by the volume, at one workgroup
+// per compute unit (the all-reduce: ALONE in fc_rot_sim.hip).  FP8 always with: its stages in a row cost a move and a multiply-add
 // or a pass through the crossbar (all-reduce of two 8.26 / 8.65 at one token, 130 / 132 at 8192).
 inline bool rot_swaps_apply(bool fp8, int64_t n_elems) { return fp8 || n_elems <= ((int64_t)256 << 13); }
 

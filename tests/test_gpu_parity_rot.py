@@ -331,6 +331,26 @@ def test_one_launch_allreduce_every_group_and_value_kind(fc, quantizer, bits_rs,
                 quantizer, n_src, hidden, group, kind, first_diff(got.view(np.uint16), want.view(np.uint16)))
 
 
+@pytest.mark.parametrize("quantizer,bits_rs,bits_ag", [(oracle.ASYM, 4, 8), (oracle.SYM, 8, 4), (oracle.FP8, 8, 8)])
+@pytest.mark.parametrize("hidden", [1024, 3072, 2048, 4096, 12288, 8192])
+def test_one_launch_allreduce_both_forms_every_group(fc, quantizer, bits_rs, bits_ag, hidden):
+    # launches of at most a workgroup per compute unit (2^20 elements in blocks of 4096, 2^21 in blocks of 8192) have a form of
+    # their own, in blocks of 8192 also a layout: the value kinds above in five rows, repeated up to both sides of these limits
+    for k, group in enumerate(g for g in (32, 64, 128, 256, 512, 1024, 2048, 4096, 8192) if g <= hidden & -hidden):
+        n_src = 1 + k % 3
+        x = synth_inputs.make_partials_stress(n_src, 5, hidden, k % synth_inputs.STRESS_KINDS, seed=hidden + group)
+        x[:, 1] = np.float16(-0.0)
+        x[0, 2, ::2] = 0
+        few = dev(x.view(np.uint16)).view(torch.float16)
+        want = dev(oracle.allreduce_sim_rot(x, group, bits_rs, bits_ag, quantizer).view(np.int16))
+        for rows in (limit // hidden + more for limit in (1 << 20, 1 << 21) for more in (0, 1)):
+            pick = torch.arange(rows, device="cuda") % 5
+            y = Guarded((rows, hidden), torch.float16)
+            fc.allreduce_sim_rot(few[:, pick], group, bits_rs, bits_ag, quantizer, out=y.t)
+            torch.cuda.synchronize(); y.check()
+            assert torch.equal(y.t.view(torch.int16), want[pick]), "N=%d h=%d g=%d rows=%d" % (n_src, hidden, group, rows)
+
+
 @pytest.mark.parametrize("quantizer,bits", [(oracle.ASYM, 4), (oracle.SYM, 4), (oracle.FP8, 8)])
 @pytest.mark.parametrize("hidden", [1024, 2048, 4096, 8192])
 def test_full_chip_runs_repeat(fc, quantizer, bits, hidden):
