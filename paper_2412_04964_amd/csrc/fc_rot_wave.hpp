@@ -117,37 +117,48 @@ __device__ __forceinline__ u32 rot_quad_offset(const RotMap m, const RotLane &L,
     return rot_lane_offset(m, L, 12u) + rot_piece_offset(m, wave, L.lane & 3u);
 }
 
-// v[0..7] = dpp(v) * s + v.  s_nop: two wait states between the write of a register and its DPP read.
-#define FC_FMAC_DPP8(ctrl, sign)                                                                                     \
-    asm("s_nop 1\n\t"                                                                                                \
-        "v_fmac_f32_dpp %0, %0, " sign "%8 " ctrl " row_mask:0xf bank_mask:0xf\n\t"                                  \
-        "v_fmac_f32_dpp %1, %1, " sign "%8 " ctrl " row_mask:0xf bank_mask:0xf\n\t"                                  \
-        "v_fmac_f32_dpp %2, %2, " sign "%8 " ctrl " row_mask:0xf bank_mask:0xf\n\t"                                  \
-        "v_fmac_f32_dpp %3, %3, " sign "%8 " ctrl " row_mask:0xf bank_mask:0xf\n\t"                                  \
-        "v_fmac_f32_dpp %4, %4, " sign "%8 " ctrl " row_mask:0xf bank_mask:0xf\n\t"                                  \
-        "v_fmac_f32_dpp %5, %5, " sign "%8 " ctrl " row_mask:0xf bank_mask:0xf\n\t"                                  \
-        "v_fmac_f32_dpp %6, %6, " sign "%8 " ctrl " row_mask:0xf bank_mask:0xf\n\t"                                  \
-        "v_fmac_f32_dpp %7, %7, " sign "%8 " ctrl " row_mask:0xf bank_mask:0xf"                                      \
-        : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3]), "+v"(v[4]), "+v"(v[5]), "+v"(v[6]), "+v"(v[7])             \
-        : "v"(s))
+// Stages of the element bits in bits FIRST ... FIRST + COUNT - 1 of pos, v[0..7] = dpp(v) * s + v each, INV: with -s.  s_nop: two
+// wait states between the write of a register and its DPP read; behind the first stage the other seven values lie between.  With an
+// s_nop before every stage: all-reduce of two of one token of 8192 7.20 / 7.15 us, of 12 x 2048 6.06 / 5.96; no change where wavefronts share a SIMD.
+#define FC_FMAC_DPP8(ctrl, s)                                                                                        \
+    "v_fmac_f32_dpp %0, %0, " s " " ctrl " row_mask:0xf bank_mask:0xf\n\t"                                           \
+    "v_fmac_f32_dpp %1, %1, " s " " ctrl " row_mask:0xf bank_mask:0xf\n\t"                                           \
+    "v_fmac_f32_dpp %2, %2, " s " " ctrl " row_mask:0xf bank_mask:0xf\n\t"                                           \
+    "v_fmac_f32_dpp %3, %3, " s " " ctrl " row_mask:0xf bank_mask:0xf\n\t"                                           \
+    "v_fmac_f32_dpp %4, %4, " s " " ctrl " row_mask:0xf bank_mask:0xf\n\t"                                           \
+    "v_fmac_f32_dpp %5, %5, " s " " ctrl " row_mask:0xf bank_mask:0xf\n\t"                                           \
+    "v_fmac_f32_dpp %6, %6, " s " " ctrl " row_mask:0xf bank_mask:0xf\n\t"                                           \
+    "v_fmac_f32_dpp %7, %7, " s " " ctrl " row_mask:0xf bank_mask:0xf\n\t"
+#define FC_BIT0 "quad_perm:[1,0,3,2]"
+#define FC_BIT1 "quad_perm:[2,3,0,1]"
+#define FC_BIT2 "row_half_mirror"
+#define FC_BIT3 "row_ror:8"
+#define FC_ROW_VALUES                                                                                                \
+    "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3]), "+v"(v[4]), "+v"(v[5]), "+v"(v[6]), "+v"(v[7])
 
-template <int BIT, bool INV>
-__device__ __forceinline__ void fmac_dpp8(float (&v)[8], float s)
+template <int FIRST, int COUNT, bool INV>
+__device__ __forceinline__ void fmac_dpp8(float (&v)[8], const float (&s)[5])
 {
-    static_assert(BIT >= 3 && BIT <= 6, "stages inside a row of 16 lanes");
-    if constexpr (!INV) {
-        if constexpr (BIT == 3) FC_FMAC_DPP8("quad_perm:[1,0,3,2]", "");
-        if constexpr (BIT == 4) FC_FMAC_DPP8("quad_perm:[2,3,0,1]", "");
-        if constexpr (BIT == 5) FC_FMAC_DPP8("row_half_mirror", "");
-        if constexpr (BIT == 6) FC_FMAC_DPP8("row_ror:8", "");
-    } else {
-        if constexpr (BIT == 3) FC_FMAC_DPP8("quad_perm:[1,0,3,2]", "-");
-        if constexpr (BIT == 4) FC_FMAC_DPP8("quad_perm:[2,3,0,1]", "-");
-        if constexpr (BIT == 5) FC_FMAC_DPP8("row_half_mirror", "-");
-        if constexpr (BIT == 6) FC_FMAC_DPP8("row_ror:8", "-");
-    }
+    constexpr int kForm = FIRST * 100 + COUNT * 10 + INV;
+    static_assert(kForm == 40 || kForm == 41 || kForm == 11 || kForm == 21 || kForm == 120 || kForm == 210 || kForm == 220, "as the transforms need them");
+    if constexpr (kForm == 40)
+        asm("s_nop 1\n\t" FC_FMAC_DPP8(FC_BIT0, "%8") FC_FMAC_DPP8(FC_BIT1, "%9") FC_FMAC_DPP8(FC_BIT2, "%10") FC_FMAC_DPP8(FC_BIT3, "%11")
+            : FC_ROW_VALUES : "v"(s[0]), "v"(s[1]), "v"(s[2]), "v"(s[3]));
+    if constexpr (kForm == 41)
+        asm("s_nop 1\n\t" FC_FMAC_DPP8(FC_BIT0, "-%8") FC_FMAC_DPP8(FC_BIT1, "-%9") FC_FMAC_DPP8(FC_BIT2, "-%10") FC_FMAC_DPP8(FC_BIT3, "-%11")
+            : FC_ROW_VALUES : "v"(s[0]), "v"(s[1]), "v"(s[2]), "v"(s[3]));
+    if constexpr (kForm == 11) asm("s_nop 1\n\t" FC_FMAC_DPP8(FC_BIT0, "-%8") : FC_ROW_VALUES : "v"(s[0]));
+    if constexpr (kForm == 21) asm("s_nop 1\n\t" FC_FMAC_DPP8(FC_BIT0, "-%8") FC_FMAC_DPP8(FC_BIT1, "-%9") : FC_ROW_VALUES : "v"(s[0]), "v"(s[1]));
+    if constexpr (kForm == 120) asm("s_nop 1\n\t" FC_FMAC_DPP8(FC_BIT1, "%8") FC_FMAC_DPP8(FC_BIT2, "%9") : FC_ROW_VALUES : "v"(s[1]), "v"(s[2]));
+    if constexpr (kForm == 210) asm("s_nop 1\n\t" FC_FMAC_DPP8(FC_BIT2, "%8") : FC_ROW_VALUES : "v"(s[2]));
+    if constexpr (kForm == 220) asm("s_nop 1\n\t" FC_FMAC_DPP8(FC_BIT2, "%8") FC_FMAC_DPP8(FC_BIT3, "%9") : FC_ROW_VALUES : "v"(s[2]), "v"(s[3]));
 }
 #undef FC_FMAC_DPP8
+#undef FC_BIT0
+#undef FC_BIT1
+#undef FC_BIT2
+#undef FC_BIT3
+#undef FC_ROW_VALUES
 
 template <int MASK>
 __device__ __forceinline__ float crossbar(float v)                      // the value of lane ^ MASK, MASK < 32
@@ -190,20 +201,21 @@ __device__ __forceinline__ void rot_priority(float (&v)[4][8])
     }
 }
 
-// The stage of the element bit in bit B of pos.  INV: the values come in the frame of the forward transform and leave
-// without this bit's share of it.  FP8: no frames; the partner's value is moved, then one v_fma_f32.
-template <int B, bool FP8, bool INV>
-__device__ __forceinline__ void rot_row_stage(float (&v)[4][8], const RotLane &L)
+// The stages of the element bits in bits FIRST ... FIRST + COUNT - 1 of pos.  INV: the values come in the frame of the forward transform
+// and leave without these bits' share of it.  FP8: no frames; the partner's value is moved, then one v_fma_f32.
+template <int FIRST, int COUNT, bool FP8, bool INV>
+__device__ __forceinline__ void rot_row_some(float (&v)[4][8], const RotLane &L)
 {
     constexpr int kCtrl[4] = {kDppQuadXor1, kDppQuadXor2, kDppRowHalfMirror, kDppRowRor8};
+    if constexpr (FP8) {
 #pragma unroll
-    for (int p = 0; p < 4; ++p) {
-        if constexpr (FP8) {
+        for (int p = 0; p < 4; ++p)
 #pragma unroll
-            for (int i = 0; i < 8; ++i) v[p][i] = fmaf(v[p][i], L.s[B], dpp_read<kCtrl[B]>(v[p][i]));
-        } else {
-            fmac_dpp8<3 + B, INV>(v[p], L.s[B]);
-        }
+            for (int i = 0; i < 8; ++i) v[p][i] = fmaf(v[p][i], L.s[FIRST], dpp_read<kCtrl[FIRST]>(v[p][i]));
+        if constexpr (COUNT > 1) rot_row_some<FIRST + 1, COUNT - 1, FP8, INV>(v, L);
+    } else {
+#pragma unroll
+        for (int p = 0; p < 4; ++p) fmac_dpp8<FIRST, COUNT, INV>(v[p], L.s);
     }
 }
 
@@ -238,10 +250,7 @@ __device__ __forceinline__ void rot_row_stages(float (&v)[4][8], const RotLane &
     } else {
 #pragma unroll
         for (int p = 0; p < 4; ++p) {
-            fmac_dpp8<3, INV>(v[p], L.s[0]);
-            fmac_dpp8<4, INV>(v[p], L.s[1]);
-            fmac_dpp8<5, INV>(v[p], L.s[2]);
-            fmac_dpp8<6, INV>(v[p], L.s[3]);
+            fmac_dpp8<0, 4, INV>(v[p], L.s);
         }
     }
     rot_priority<0, ORDER>(v);
@@ -483,8 +492,7 @@ __device__ __forceinline__ void rot_forward(float (&v)[4][8], const RotLane &L, 
             static_assert(LB == 12 || !FP8, "blocks of 8192: the other form");
         } else {                           // through the crossbar instead: all-reduce 166 -> 179 us
             rot_priority<1, ORDER>(v);
-            rot_row_stage<2, false, false>(v, L);
-            if constexpr (LB == 13) rot_row_stage<3, false, false>(v, L);
+            rot_row_some<2, LB == 13 ? 2 : 1, false, false>(v, L);
             rot_priority<0, ORDER>(v);
         }
         rot_piece_stage<1>(v);
@@ -555,8 +563,7 @@ __device__ __forceinline__ float rot_inverse_back(float (&v)[4][8], const RotLan
         rot_register_stage<2>(v);
         rot_register_stage<4>(v);
         rot_priority<1, ORDER>(v);
-        rot_row_stage<0, FP8, true>(v, L);
-        rot_row_stage<1, FP8, true>(v, L);
+        rot_row_some<0, 2, FP8, true>(v, L);
         if constexpr (!FP8) settle_pieces(v);
         rot_swap<4, FP8, ORDER>(v);                    // 5 into piece bit 0
         rot_priority<0, ORDER>(v);
@@ -568,10 +575,13 @@ __device__ __forceinline__ float rot_inverse_back(float (&v)[4][8], const RotLan
         rot_piece_stage<2>(v);
         // 9 ... LB-1 in the row: 9 (and 10 of blocks of 8192) was a DPP stage of the forward transform
         rot_priority<1, ORDER>(v);
-        rot_row_stage<0, FP8, true>(v, L);
-        rot_row_stage<1, FP8, LB == 13>(v, L);
-        rot_row_stage<2, FP8, false>(v, L);
-        if constexpr (LB == 13) rot_row_stage<3, FP8, false>(v, L);
+        if constexpr (LB == 13) {
+            rot_row_some<0, 2, FP8, true>(v, L);
+            rot_row_some<2, 2, FP8, false>(v, L);
+        } else {
+            rot_row_some<0, 1, FP8, true>(v, L);
+            rot_row_some<1, 2, FP8, false>(v, L);
+        }
         rot_priority<0, ORDER>(v);
         return FP8 ? 1.0f : LB == 13 ? L.s[2] * L.s[3] : L.s[1] * L.s[2];
     } else {
