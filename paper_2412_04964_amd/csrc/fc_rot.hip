@@ -74,7 +74,8 @@ __device__ __forceinline__ void rot_pack_literal(const float (&v)[4][8], const R
 // A wavefront runs at raised priority until its loads are issued: among seven others in the middle of their transforms it would
 // take eight times as long to get there.  us, without / with: quantize INT4 8192 x 8192 37.7 / 35.1, x 5120 21.0 / 20.6, INT8 x 4096
 // 20.8 / 20.0, x 2048 10.9 / 10.1; dequantize 37.5 / 35.9, 20.9 / 19.3, 20.7 / 19.9, 9.6 / 9.4, FP8 4096 x 8192 21.7 / 21.1; no change up to 1024 x
-// 8192, nor for the all-reduce, whose wavefronts live longer.  Raised again for the last instructions: no gain.
+// 8192, nor for the all-reduce, whose wavefronts live longer.  Raised again for the last instructions: no gain.  The quantizer of blocks of
+// 1024 with integer 8-bit codes is slower for it (cause not found): 8192 x 5120 23.5 / 24.9.
 __device__ __forceinline__ void rot_to_loads() { __builtin_amdgcn_s_setprio(3); }
 __device__ __forceinline__ void rot_loads_issued() { asm volatile("s_setprio 0" ::: "memory"); }
 
@@ -91,7 +92,8 @@ __global__ __launch_bounds__(64 * rot_group_waves(LB)) void k_quantize_rot(
     __shared__ __attribute__((aligned(16))) uint8_t pieces[rot_exchange_bytes(LB, kRounds)];
     __shared__ float mm[kWaves][kRotSlots][2];
 
-    rot_to_loads();
+    constexpr bool kLoadsFirst = !(LB == 10 && BITS == 8 && !FP8);
+    if constexpr (kLoadsFirst) rot_to_loads();
     const u32 tid = threadIdx.x, lane = tid & 63u;
     const u32 wave = (u32)__builtin_amdgcn_readfirstlane((int)(tid >> 6));
     const RotLane L = rot_lane<FP8, rot_forward_framed(LB, SWAPS)>(lane);
@@ -107,7 +109,7 @@ __global__ __launch_bounds__(64 * rot_group_waves(LB)) void k_quantize_rot(
         const RotAt at = rot_at<LB>(in_at, kRotLoaded, wave, p, 16);
         raw[p] = __builtin_amdgcn_raw_buffer_load_b128(rx, at.vec, at.scalar, kStreamLoadPolicy);
     }
-    rot_loads_issued();
+    if constexpr (kLoadsFirst) rot_loads_issued();
     float v[4][8];
     if constexpr (FP8) {
 #pragma unroll
