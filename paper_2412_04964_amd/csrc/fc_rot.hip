@@ -135,15 +135,15 @@ __global__ __launch_bounds__(64 * rot_group_waves(LB)) void k_quantize_rot(
     // from the unscaled values with the reciprocal times fwd, the same real product and hence the
     // same rounded one.
     constexpr float fwd = 1.0f / (float)(1 << ((LB + 1) / 2));
-    float mn, mx, s, inv, zf = 0.0f;
-    rot_group_minmax<LB, SWAPS, FP8>(v, L, group_shift, wave, mm, mn, mx);
-    const float mn_s = mn * fwd, mx_s = mx * fwd;
-    if constexpr (FP8)
-        group_params_absmax<448>(fmaxf(fabsf(mn_s), fabsf(mx_s)), s, inv);
-    else if constexpr (CODEC == kSym)
-        group_params_sym<BITS>(fmaxf(fabsf(mn_s), fabsf(mx_s)), s, inv);
-    else
-        group_params<BITS>(mn_s, mx_s, s, inv, zf);
+    float mn, mx = 0.0f, s, inv, zf = 0.0f;
+    if constexpr (CODEC == kAsym) {
+        rot_group_minmax<LB, SWAPS>(v, L, group_shift, wave, mm, mn, mx);
+        group_params<BITS>(mn * fwd, mx * fwd, s, inv, zf);
+    } else {
+        const float amax = rot_group_absmax<LB, SWAPS>(v, L, group_shift, wave, mm) * fwd;
+        if constexpr (FP8) group_params_absmax<448>(amax, s, inv);
+        else group_params_sym<BITS>(amax, s, inv);
+    }
     inv *= fwd;
 
     // the packed form needs zero-points below 2048 in magnitude and no rounding past the top code (see pack_lane);

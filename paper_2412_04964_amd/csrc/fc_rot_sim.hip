@@ -29,16 +29,19 @@ struct RotLevels {           // of one quantization: qmax and 1 / qmax (2^bits -
     float q, c;
 };
 
-// scale, scaled reciprocal and zero-point of the lane's group from its min and max
-template <int CODEC>
-__device__ __forceinline__ void rot_params(float mn, float mx, RotLevels lv, float fwd, float &s, float &inv, float &zf)
+// scale, scaled reciprocal, zero-point and (asymmetric) maximum of the lane's group
+template <int CODEC, int LB, bool SWAPS>
+__device__ __forceinline__ void rot_params(const float (&v)[4][8], const RotLane &L, int group_shift, u32 wave, float (*slot)[kRotSlots][2],
+                                           RotLevels lv, float fwd, float &mx, float &s, float &inv, float &zf)
 {
-    const float a = mn * fwd, b = mx * fwd;
-    zf = 0.0f;
-    if constexpr (CODEC == kAsym)
-        group_params_levels<false>(a, b, lv.q, lv.c, s, inv, zf);
-    else
-        group_params_absmax_levels(fmaxf(fabsf(a), fabsf(b)), lv.q, lv.c, s, inv);
+    zf = mx = 0.0f;
+    if constexpr (CODEC == kAsym) {
+        float mn;
+        rot_group_minmax<LB, SWAPS>(v, L, group_shift, wave, slot, mn, mx);
+        group_params_levels<false>(mn * fwd, mx * fwd, lv.q, lv.c, s, inv, zf);
+    } else {
+        group_params_absmax_levels(rot_group_absmax<LB, SWAPS>(v, L, group_shift, wave, slot) * fwd, lv.q, lv.c, s, inv);
+    }
     inv *= fwd;
 }
 
@@ -195,9 +198,8 @@ __global__ __launch_bounds__(64 * rot_group_waves(LB)) __attribute__((amdgpu_wav
         }
         if (LB >= 12 && j > 0) lds_barrier();                          // every wavefront has taken the last exchange
         rot_forward<LB, SWAPS, FP8, 1, kOrder>(v, L, pieces, wave);
-        float mn, mx, s, inv, zf;
-        rot_group_minmax<LB, SWAPS, FP8>(v, L, group_shift, wave, mm, mn, mx);
-        rot_params<CODEC>(mn, mx, rs, fwd, s, inv, zf);
+        float mx, s, inv, zf;
+        rot_params<CODEC, LB, SWAPS>(v, L, group_shift, wave, mm, rs, fwd, mx, s, inv, zf);
         if (j + 1 < n_src) fetch(j + 1);
         rot_codes<CODEC>(v, L, mx, inv, zf, rs);
         rot_accumulate<0>(v, s, acc);
@@ -206,10 +208,9 @@ __global__ __launch_bounds__(64 * rot_group_waves(LB)) __attribute__((amdgpu_wav
         rot_accumulate<3>(v, s, acc);
     } while (++j < n_src);
 
-    float mn, mx, s, inv, zf;
+    float mx, s, inv, zf;
     if (LB >= 12) lds_barrier();
-    rot_group_minmax<LB, SWAPS, FP8>(acc, L, group_shift, wave, mm, mn, mx);
-    rot_params<CODEC>(mn, mx, ag, 1.0f, s, inv, zf);
+    rot_params<CODEC, LB, SWAPS>(acc, L, group_shift, wave, mm, ag, 1.0f, mx, s, inv, zf);
     rot_codes<CODEC>(acc, L, mx, inv, zf, ag);
     rot_scale<0>(acc, s);
     rot_scale<1>(acc, s);
