@@ -74,10 +74,20 @@ __device__ __forceinline__ void rot_pack_literal(const float (&v)[4][8], const R
 // A wavefront runs at raised priority until its loads are issued: among seven others in the middle of their transforms it would
 // take eight times as long to get there.  us, without / with: quantize INT4 8192 x 8192 37.7 / 35.1, x 5120 21.0 / 20.6, INT8 x 4096
 // 20.8 / 20.0, x 2048 10.9 / 10.1; dequantize 37.5 / 35.9, 20.9 / 19.3, 20.7 / 19.9, 9.6 / 9.4, FP8 4096 x 8192 21.7 / 21.1; no change up to 1024 x
-// 8192, nor for the all-reduce, whose wavefronts live longer.  Raised again for the last instructions: no gain.  The quantizer of blocks of
-// 1024 with integer 8-bit codes is slower for it (cause not found): 8192 x 5120 23.5 / 24.9.
+// 8192, nor for the all-reduce, whose wavefronts live longer.  Raised again for the last instructions: no gain.
 __device__ __forceinline__ void rot_to_loads() { __builtin_amdgcn_s_setprio(3); }
 __device__ __forceinline__ void rot_loads_issued() { asm volatile("s_setprio 0" ::: "memory"); }
+
+// Whether a quantizer's wavefronts run at raised priority until their loads are issued and over the first stage.  Not in blocks of 1024 with
+// integer codes where there are more wavefronts than the chip holds at once (8 per SIMD, 2^24 elements): cards differ there.  us,
+// raised / not, on two cards, and the rows in LDS: 8192 x 5120 INT4 20.6, 25.2 / 22.2, 22.6, 24.2, INT8 24.4, 28.1 / 23.5, 23.9, 25.6; 4000 x 5120
+// -, 14.5 / -, 13.3, 13.2; below the limit both cards gain (2000 x 5120 7.00 / 7.50).  Blocks of 2048 and 4096 gain more on the one
+// (21.5 / 23.4) than they lose on the other (24.4 / 24.0).
+template <int LB, bool FP8>
+__device__ __forceinline__ bool rot_raised(int64_t n_elems)
+{
+    return LB != 10 || FP8 || n_elems <= (int64_t)8 * 1024 * 2048;
+}
 
 // Rotate block by block and quantize (FinegrainedQuantize of Algorithm 1 on the rotated values).
 // n_elems: elements of the whole tensor, a multiple of 2^LB.
@@ -92,8 +102,8 @@ __global__ __launch_bounds__(64 * rot_group_waves(LB)) void k_quantize_rot(
     __shared__ __attribute__((aligned(16))) uint8_t pieces[rot_exchange_bytes(LB, kRounds)];
     __shared__ float mm[kWaves][kRotSlots][2];
 
-    constexpr bool kLoadsFirst = !(LB == 10 && BITS == 8 && !FP8);
-    if constexpr (kLoadsFirst) rot_to_loads();
+    const bool raised = rot_raised<LB, FP8>(n_elems);
+    if (raised) rot_to_loads();
     const u32 tid = threadIdx.x, lane = tid & 63u;
     const u32 wave = (u32)__builtin_amdgcn_readfirstlane((int)(tid >> 6));
     const RotLane L = rot_lane<FP8, rot_forward_framed(LB, SWAPS)>(lane);
@@ -109,7 +119,7 @@ __global__ __launch_bounds__(64 * rot_group_waves(LB)) void k_quantize_rot(
         const RotAt at = rot_at<LB>(in_at, kRotLoaded, wave, p, 16);
         raw[p] = __builtin_amdgcn_raw_buffer_load_b128(rx, at.vec, at.scalar, kStreamLoadPolicy);
     }
-    if constexpr (kLoadsFirst) rot_loads_issued();
+    if (raised) rot_loads_issued();
     float v[4][8];
     if constexpr (FP8) {
 #pragma unroll
@@ -124,7 +134,7 @@ __global__ __launch_bounds__(64 * rot_group_waves(LB)) void k_quantize_rot(
             rot_first_stages<1>(v[p], [&] {
 #pragma unroll
                 for (int i = 0; i < 4; ++i) first_stage(raw[p][i], v[p][2 * i], v[p][2 * i + 1]);
-            });
+            }, raised);
     }
     rot_forward<LB, SWAPS, FP8, kRounds, kRaised>(v, L, pieces, wave);
 

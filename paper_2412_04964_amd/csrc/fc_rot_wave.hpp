@@ -339,15 +339,15 @@ __device__ __forceinline__ void rot_register_stage(float (&v)[4][8])
 }
 
 // Stages 0-2 of a piece, whose values `form` forms from what was loaded by instructions that issue alone (v_fma_mix_f32, v_cvt_pk_f32_fp8),
-// hence at raised priority (see rot_priority); FIRST: the first of the three that it leaves to do.  us, without / with: quantize INT4
+// hence at raised priority (see rot_priority; `raised`: rot_raised in fc_rot.hip); FIRST: the first of the three that it leaves to do.  us, without / with: quantize INT4
 // (group 128) 8192 x 8192 37.9 / 35.9, x 5120 20.8 / 19.7, INT8 x 4096 20.2 / 19.4; dequantize INT4 37.9 / 36.0, 20.8 / 19.6, FP8
 // 4096 x 8192 22.0 / 21.2; all-reduce of four INT4 x 8192 164.3 / 160.7, x 5120 87.9 / 84.0, FP8 4096 x 8192 102.0 / 97.5.  Not in FP8's
 // quantizer (24.2 / 25.9).  Where a launch has a wavefront per SIMD or less there is nobody to give way to, and the order costs up to 1 %;
 // all four pieces before the next stages are as fast for large volumes and cost the single transforms 2 % there.
 template <int FIRST, typename F>
-__device__ __forceinline__ void rot_first_stages(float (&v)[8], F form)
+__device__ __forceinline__ void rot_first_stages(float (&v)[8], F form, bool raised = true)
 {
-    __builtin_amdgcn_s_setprio(1);
+    if (raised) __builtin_amdgcn_s_setprio(1);
     form();
     pin_values(v);
     __builtin_amdgcn_s_setprio(0);
