@@ -23,7 +23,7 @@
 // a row and, blocks of 4096 and 8192, element bits 9 and 10 by way of the exchange (quantizer) -> with raised priority over the
 // first stage and the unpacking too: 8192 x 8192 INT4 46.0 -> 43.5 -> 37.5 -> 35.9 / 43.9 -> 39.7 -> 38.4 -> 36.0; the same in FP8 55.5 -> 45.2 -> 44
 // -> 43.5 / 46.3 -> 42.9 -> 42.2 -> 41.0; 8192 x 4096 INT8 - -> 22.9 -> 20.8 -> 19.9 / - -> 21.9 -> 21.1 -> 20.5; 8192 x 5120 INT4 (blocks of
-// 1024) 22.9 -> 25.4 -> 20.8 -> 19.7 / 24.5 -> 22.0 -> 21.4 -> 19.9.  Launch-bound volumes run in fc_rot_rows.hip where that is faster.
+// 1024) 22.9 -> 25.4 -> 22.6 (rot_raised) / 24.5 -> 22.0 -> 21.4 -> 19.9 -> 18.9.  Launch-bound volumes run in fc_rot_rows.hip where that is faster.
 // Measured and not taken: 32 consecutive elements per lane and a 16 x 16 exchange with other lanes through 5 KB of LDS (40.3 us for blocks
 // of 8192, when this form took 43.0, but 23.8 for 1024 and 23.0 / 48 in the dequantizer, whose register needs it does not fit); all stages
 // between lanes by permlane swaps; persistent workgroups that load the next tile while they transform the current one (4, 5, 6, 12

@@ -15,7 +15,7 @@
 //   8 bit, blocks of 4096: 2 M 4.45 / 4.52, 3.89 / 4.43; 3 M 5.13 / 4.91, 4.53 / 4.75; 4 M 5.78 / 5.24, 5.17 / 5.01.  FP8: 3 M
 //     5.02 / 5.39, 4.46 / 4.82; 4 M 5.67 / 5.79, 5.10 / 5.11; 5 M 6.30 / 6.20, 5.69 / 5.49.
 //   4 bit, blocks of 1024: 64 K 2.88 / 2.89, 2.49 / 2.55; 1 M 3.61 / 3.55, 3.08 / 3.06; 2 M 3.99 / 4.13, 3.50 / 3.69; 2.5 M 4.37 / 4.32,
-//     3.95 / 3.74; 8 M 6.95 / 6.60, 6.05 / 5.57; 16 M 11.41 / 10.24, 11.01 / 9.94; 8192 x 5120 22.9 / 20.7.
+//     3.95 / 3.74; 8 M 6.95 / 6.60, 6.05 / 5.57; 16 M 11.41 / 10.24, 11.01 / 9.94; 8192 x 5120 24.2 / 22.6.
 //   4 bit, blocks of 2048: 1 M 3.83 / 3.61, 3.33 / 3.14; 1.5 M 4.08 / 4.22, 3.59 / 3.75; 2.5 M 4.77 / 4.53, 4.29 / 3.85.
 //   4 bit, blocks of 4096, dequantize: 64 K 2.93 / 3.07; 2 M 4.19 / 4.26; 3 M 4.60 / 4.56; 4 M 5.09 / 4.89.
 //   Blocks of 8192: the register form at every volume.
