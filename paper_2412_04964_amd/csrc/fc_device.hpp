@@ -1198,6 +1198,11 @@ __global__ __launch_bounds__(BT) void k_dequant_reduce_requant(
     // nine, possibly on another card, four runs each in turn gave 31.8 -> 36.2 and the cause was not found (shader clock and
     // temperature do not move in the others).
     constexpr bool kNibbles = BITS_IN == 4 && NSRC <= 4 && !SHORT;
+    // Up to two sources: raised priority until the code loads are issued, since a new wavefront shares its SIMD with seven others in
+    // the middle of their arithmetic.  8192 x 8192 between other stages, us: g = 128 N = 1 16.2 -> 15.3, N = 2 20.9 -> 19.9 (other cards 21.2
+    // -> 19.8, 21.9 -> 21.4, 20.3 -> 19.5), g = 1024 20.3 -> 19.3, 4 -> 8 bit 24.75 -> 24.5; 4000 x 5120 9.05 -> 8.6; g = 32 24.6 -> 24.8;
+    // up to 1000 x 8192 equal.  N = 3 equal; N = 4 30.8 -> 33.0, on one card 31.7 -> 36.9: memory answers the bursts of its loads worse.
+    constexpr bool kLoadsFirst = kNibbles && NSRC <= 2 && LPG > 1 && !HM;
     struct MetaRec { float s; u32 z; };                       // z: fp32 bits; packed halves for accumulate_fast
 
     __shared__ __attribute__((aligned(16))) uint8_t landing[kWaves][NSRC][1024];
@@ -1206,6 +1211,7 @@ __global__ __launch_bounds__(BT) void k_dequant_reduce_requant(
     __shared__ __attribute__((aligned(16))) uint8_t out_img[kOutBytes == 32 ? kWaves : 1]
                                                             [kOutBytes == 32 ? 2048 : 16];
 
+    if constexpr (kLoadsFirst) __builtin_amdgcn_s_setprio(3);
     const u32 tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
     const int64_t n_groups = n_elems >> group_shift;
 
@@ -1242,6 +1248,7 @@ __global__ __launch_bounds__(BT) void k_dequant_reduce_requant(
         issue_order_fence();
 #pragma unroll
         for (int j = 0; j < NSRC; ++j) issue_source(j);
+        if constexpr (kLoadsFirst) asm volatile("s_setprio 0" ::: "memory");
         issue_order_fence();
         if constexpr (HM) unpack_meta(__builtin_bit_cast(u32, es), es, ez);
         uint64_t slow = zero_is_slow_mask(ez);
@@ -1276,6 +1283,7 @@ __global__ __launch_bounds__(BT) void k_dequant_reduce_requant(
         // --- codes: straight into the landing zone
 #pragma unroll
         for (int j = 0; j < NSRC; ++j) issue_source(j);
+        if constexpr (kLoadsFirst) asm volatile("s_setprio 0" ::: "memory");
         issue_order_fence();
 
         // --- table: check, convert, publish
