@@ -547,6 +547,7 @@ __device__ __forceinline__ float rot_inverse_back(float (&v)[4][8], const RotLan
 {
     if constexpr (LB == 13 && SWAPS) {
         rot_inverse_row<FP8, ORDER>(v, L);
+        if constexpr (!FP8) settle_pieces(v);
         rot_swap<4, FP8, ORDER>(v);                    // l4 l5 p0 p1 w0 w1 = 11  8  7 12  9 10
         rot_piece_stage<1>(v);
         rot_swap<5, FP8, ORDER>(v);                    //                     11 12  7  8  9 10

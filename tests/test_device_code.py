@@ -119,3 +119,63 @@ def test_wide_stores_with_a_scalar_offset_keep_their_data(kernels):
                 written = [] if later.startswith(("buffer_store", "global_store", "ds_write", "s_")) else operands[:1]
                 assert not any(registers(w.strip()) & data for w in written), "%s: %s overwrites %s" % (name, later, instruction)
     assert seen > 0
+
+
+def assembled(tmp_path, source):
+    """(kernel, [(instruction, number of the asm statement it was written in or None), ...]) of a source file"""
+    out = tmp_path / (source + ".s")
+    subprocess.run([build.HIPCC, *build.FLAGS, "--cuda-device-only", "-S", os.path.join(build.CSRC, source), "-o", str(out)],
+                   check=True, capture_output=True)
+    name, body, statement, inside = None, [], 0, False
+    for line in out.read_text().splitlines():
+        head = re.match(r"(_Z\w+):", line)
+        if head:
+            if name:
+                yield name, body
+            name, body = head.group(1), []
+        elif "#ASMSTART" in line:
+            statement, inside = statement + 1, True
+        elif "#ASMEND" in line:
+            inside = False
+        elif name:
+            text = line.split(";")[0].strip()
+            if text and not text.startswith(".") and not text.endswith(":"):
+                body.append((text, statement if inside else None))
+    if name:
+        yield name, body
+
+
+@pytest.mark.parametrize("source", ["fc_rot.hip", "fc_rot_rows.hip", "fc_rot_sim.hip"])
+def test_lane_exchanges_wait_for_what_assembly_wrote(tmp_path, source):
+    # v_permlane*_swap and DPP operands need two wait states behind the vector instruction that wrote them.  The compiler sees to
+    # that for its own instructions but not for those of asm statements: there the source has to, by an asm statement of s_nop
+    # alone or by what follows the write in its own statement.  What else happens to lie between is the compiler's choice of the day.
+    if not os.path.exists(build.HIPCC):
+        pytest.skip("no hipcc")
+    seen = 0
+    for name, body in assembled(tmp_path, source):
+        written, waits = {}, {}                           # of every register: the asm statement that wrote it last; wait states since
+        for at, (text, statement) in enumerate(body):
+            op, _, rest = text.partition(" ")
+            operands = [o.strip().split(" ")[0].strip("-|") for o in rest.split(",")]
+            swap = op.startswith("v_permlane")
+            if swap or "_dpp" in op:
+                seen += 1
+                if statement is None:
+                    for r in set().union(*(registers(o) for o in (operands[:2] if swap else operands[1:2]))):
+                        assert r not in written or waits[r] >= 2, "%s: %s, %d wait states behind an asm statement" % (name, text, waits[r])
+            if op == "s_nop" and statement is not None:
+                near = [s for _, s in body[max(at - 1, 0):at + 2]]
+                alone = near.count(statement) == 1        # the only instruction of its statement
+                for r in written:
+                    if alone or written[r] == statement:
+                        waits[r] += int(rest, 0) + 1
+            elif statement is not None:
+                for r in written:
+                    waits[r] += written[r] == statement
+            targets = operands[:2] if swap else operands[:1] if op.startswith(("v_", "buffer_load", "global_load", "ds_")) else []
+            for r in set().union(*(registers(o) for o in targets)):
+                written.pop(r, None)
+                if statement is not None and op.startswith("v_"):
+                    written[r], waits[r] = statement, 0
+    assert seen > 0
