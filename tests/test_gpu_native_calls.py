@@ -241,10 +241,22 @@ def test_allocated_results_are_tensors_like_those_of_torch_empty(inference):
     for k in kept:
         torch.empty_like(k)
     assert after - before == allocated() - after >= sum(k.untyped_storage().nbytes() for k in kept) > 0
-    want = [k.clone() for k in kept]
-    torch.use_deterministic_algorithms(True)
-    try:
-        again = b._calls().quantize(x[0], 128, 8, None)
-    finally:
-        torch.use_deterministic_algorithms(False)
-    assert again is not None and all(torch.equal(a, w) for a, w in zip(again, want))
+
+
+@pytest.mark.gpu
+def test_allocated_results_are_filled_where_torch_was_asked_to():
+    # torch.use_deterministic_algorithms has torch.empty fill new memory.  The kernels overwrite every byte of it, so what shows
+    # the fill is torch's own record of the operations that ran: one per result.
+    from paper_2412_04964_amd import binding as b
+    x = torch.randn(5, 1024, device="cuda").half()
+    got = {}
+    for fill in (False, True):
+        torch.use_deterministic_algorithms(fill)
+        try:
+            with torch.profiler.profile(activities=[torch.profiler.ProfilerActivity.CPU], acc_events=True) as record:
+                got[fill] = b._calls().quantize(x, 128, 8, None)
+        finally:
+            torch.use_deterministic_algorithms(False)
+        assert got[fill] is not None
+        assert sum(e.count for e in record.key_averages() if e.key == "aten::fill_") == (3 if fill else 0)
+    assert all(torch.equal(a, w) for a, w in zip(got[True], got[False]))
