@@ -179,3 +179,18 @@ def test_lane_exchanges_wait_for_what_assembly_wrote(tmp_path, source):
                 if statement is not None and op.startswith("v_"):
                     written[r], waits[r] = statement, 0
     assert seen > 0
+
+
+def test_rotated_tiles_are_loaded_before_anything_waits(kernels):
+    # A wavefront of the rotation kernels loads one tile and lives for it: a load behind the wait for another one costs a launch-bound call
+    # the latency of memory once more.  (The all-reduce loads its first source so, and later ones further down.)
+    seen = 0
+    for name, body in kernels.items():
+        if not re.search(r"(quantize|dequantize|allreduce)_rotI", name):
+            continue
+        seen += 1
+        loads = [at for at, i in enumerate(body) if i.startswith("buffer_load")]
+        wait = next(at for at, i in enumerate(body) if i.startswith("s_waitcnt") and "vmcnt" in i)
+        first = 4 if "allreduce" in name else len(loads)
+        assert sum(at < wait for at in loads) >= first >= 4, "%s: %d of %d loads before the first wait" % (name, sum(at < wait for at in loads), first)
+    assert seen >= 4 * (5 + 5 + 3)                 # four blocks; quantizer and dequantizer with five codes, all-reduce with three
