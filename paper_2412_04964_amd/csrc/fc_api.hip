@@ -294,19 +294,24 @@ int three_steps(bool rotate, int codec, const void *x_f16, int n_src, int64_t to
 }
 
 // Whether the three steps are the faster form of the rotated all-reduce.  The one launch works through the sources one after
-// the other, 1.4 us each in blocks of up to 2048 elements, 2.2 us in blocks of 8192 (FP8 1.8 / 2.4), until the chip is full; the
+// the other, 1.5 us each in blocks of up to 2048 elements, 2.0 us in blocks of 8192 (FP8 1.9 / 2.3), until the chip is full; the
 // three steps take 8 to 10 us, their quantizations spread over the chip.  Up to this many elements, in units of 2^16, by the
-// block and the number of sources, the steps are faster; the line lies where the larger loss on either side is smallest.  Group
-// 128, three steps / one launch, us under graph replay:
-//   INT4, block 2048: N = 4, 256 K elements 9.2 / 9.9, 384 K 9.8 / 9.3; N = 5, 512 K 10.6 / 11.4, 768 K 11.2 / 11.1; N = 8, 1536 K
-//     19.0 / 21.8, 2048 K 21.7 / 22.1.  Six sources cross more than once: 1024 K 13.6 / 12.9, 1536 K 16.9 / 17.7.
-//   INT4, block 4096: N = 4, 256 K 9.9 / 11.4, 768 K 11.5 / 11.0; N = 8, 2048 K 23.1 / 24.3.
-//   INT4, block 8192: N = 3, 8 K 9.4 / 9.0; N = 4, 512 K 10.7 / 11.3, 1024 K 12.9 / 12.2; N = 8, 8 K 9.7 / 17.9, 2048 K 22.8 / 21.5.
-//   FP8, block 2048: N = 2, 2 K 7.2 / 7.0; N = 3, 256 K 8.5 / 9.4, 768 K 10.7 / 9.4; N = 8, 2048 K 21.0 / 27.2.
-//   FP8, block 8192: N = 3, 256 K 10.7 / 11.1, 768 K 12.7 / 11.5; N = 8, 2048 K 23.6 / 26.2.
-// Groups of 1024 elements and more cost the steps another 0.9 us, the one launch 0.4: four sources of short blocks never cross
-// then (64 K 10.0 / 9.4), in blocks of 4096 earlier (256 K 10.9 / 10.8).  Where the slabs need padding every partial is a launch
-// of its own: N = 8, one token of 8192, group 8192 35.5 / 20.0.
+// block and the number of sources, the steps are taken.  The limits were found with earlier kernels; with those of today the lines
+// cross somewhat elsewhere (last number of each entry: where, mean of two cards), most of all in blocks of 8192 with five to
+// seven sources, where the worst volume takes 18 % longer than it could.  Symmetric codes cross where asymmetric ones do.  Group 128,
+// three steps / one launch, us under graph replay:
+//   INT4, block 2048: N = 4, 256 K elements 9.1 / 9.7, 512 K 9.8 / 9.7 (6); N = 5, 512 K 10.0 / 11.3, 768 K 10.6 / 11.6, 1280 K 13.6 /
+//     13.6 (18); N = 6, 1024 K 12.1 / 13.5, 1536 K 15.5 / 16.0 (26); N = 8, 1536 K 18.2 / 20.7, 2048 K 20.8 / 21.2 (32).
+//   INT4, block 4096: N = 4, 256 K 9.6 / 10.8, 768 K 10.8 / 11.3, 1152 K 13.0 / 12.4 (16); N = 5 (20); N = 6, 2048 K 18.9 / 17.6 (26);
+//     N = 7 (28); N = 8, 2048 K 21.9 / 21.9 (31).
+//   INT4, block 8192: N = 3, 8 K 9.0 / 9.0 (0); N = 4, 512 K 10.6 / 12.3, 768 K 11.3 / 12.6, 1280 K 13.5 / 12.8 (16); N = 5 (24);
+//     N = 6 (30); N = 7, 1408 K 17.0 / 19.9, 2048 K 20.7 / 20.9 (34); N = 8, 8 K 10.1 / 19.0, 2048 K 22.3 / 23.2 (36).
+//   FP8, block 2048: N = 3, 256 K 8.4 / 9.4, 512 K 9.2 / 9.6, 768 K 10.0 / 9.8 (10); N = 8, 2048 K 21.6 / 24.4, 2560 K 25.2 / 24.6 (36).
+//   FP8, block 8192: N = 3, 256 K 10.5 / 11.4, 768 K 11.9 / 11.8 (11); N = 4 (26); N = 5, 1664 K 16.4 / 17.8 (36); N = 8, 2048 K 23.8 /
+//     27.2, 3072 K 30.5 / 30.4 (46).
+// Groups of 1024 elements and more cost the steps another 1.1 us, the one launch 0.2 to 0.7: four sources of short blocks do not cross
+// then (64 K 9.6 / 8.9), in blocks of 4096 at 12 (256 K 10.6 / 11.4).  Where the slabs need padding every partial is a launch
+// of its own, and the one launch is taken.
 bool rot_steps_apply(const SimLayout &L, int codec, int n_src, int64_t n_elems, int64_t hidden, int group, int bits_rs)
 {
     //                                           n_src 3  4   5   6   7   8

@@ -17,13 +17,13 @@
 // groups never cross block boundaries, so the tensor is handled as a flat sequence of tiles; the last tile of a
 // tensor of 1024- or 2048-element blocks may be a partial one (loads beyond the end give zeros, stores are dropped).
 //
-// What bounds them: vector instructions and which of them issue side by side (rot_priority in fc_rot_wave.hpp) in blocks of 8192, as much
-// the wait for memory in blocks of 1024, since a wavefront loads, transforms, stores and ends.  Rotate + quantize / dequantize + rotate,
-// us, with the rows in LDS between phases of four or five stages (fc_rot_rows.hip) -> in registers -> with raised priority over the stages in
-// a row and, blocks of 4096 and 8192, element bits 9 and 10 by way of the exchange (quantizer) -> with raised priority over the
-// first stage and the unpacking too: 8192 x 8192 INT4 46.0 -> 43.5 -> 37.5 -> 35.9 / 43.9 -> 39.7 -> 38.4 -> 36.0; the same in FP8 55.5 -> 45.2 -> 44
-// -> 43.5 / 46.3 -> 42.9 -> 42.2 -> 41.0; 8192 x 4096 INT8 - -> 22.9 -> 20.8 -> 19.9 / - -> 21.9 -> 21.1 -> 20.5; 8192 x 5120 INT4 (blocks of
-// 1024) 22.9 -> 25.4 -> 22.6 (rot_raised) / 24.5 -> 22.0 -> 21.4 -> 19.9 -> 18.9.  Launch-bound volumes run in fc_rot_rows.hip where that is faster.
+// What bounds them: vector instructions and which of them issue side by side (rot_priority in fc_rot_wave.hpp) in blocks of 4096 and 8192; in
+// the dequantizer of blocks of 1024 more the wait for memory, since a wavefront loads, transforms, stores and ends.  Rotate + quantize /
+// dequantize + rotate, group 128, us over six cards: 8192 x 8192 INT4 35-39 / 33-36, INT8 39-42 / 37-38, FP8 39-44 / 38-41; 5461 x 12288 (blocks of
+// 4096) INT4 34-39 / 32-36, INT8 37-41 / 36-37, FP8 38-45 / 38-40; 10922 x 6144 (2048) INT4 33-39 / 30-32, INT8 37-39 / 34-35, FP8 38-41 / 35-37;
+// 8192 x 5120 (1024) INT4 22-24 / 19-21, INT8 24-25 / 23, FP8 24-27 / 22-24.  Without priorities over the instructions that issue
+// alone, and with element bits 9 and 10 by swaps: 8192 x 8192 44-48 / 38-42, 44-48 / 41-43, 45-49 / 44-46; 8192 x 5120 23-25 (rows in LDS) / 22-24,
+// 24-26 / 24-25, 25-28 / 25-26.  Launch-bound volumes run in fc_rot_rows.hip where that is faster.
 // Measured and not taken: 32 consecutive elements per lane and a 16 x 16 exchange with other lanes through 5 KB of LDS (40.3 us for blocks
 // of 8192, when this form took 43.0, but 23.8 for 1024 and 23.0 / 48 in the dequantizer, whose register needs it does not fit); all stages
 // between lanes by permlane swaps; persistent workgroups that load the next tile while they transform the current one (4, 5, 6, 12
@@ -397,7 +397,7 @@ hipError_t quantize_rot_one(const uint16_t *x, int64_t n_elems, int group, uint8
     const dim3 grid = rot_grid<LB>(n_elems), block(64 * rot_group_waves(LB));
     const int sh = log2_int(group);
     if constexpr (LB == 13 && CODEC != kFp8)
-        if (!rot_swaps_apply(false, n_elems))
+        if (!rot_swaps_apply(n_elems))
             return launch_kernel(k_quantize_rot<BITS, CODEC, false, LB>, grid, block, stream, x, n_elems, sh, c, scales, zeros);
     return launch_kernel(k_quantize_rot<BITS, CODEC, true, LB>, grid, block, stream, x, n_elems, sh, c, scales, zeros);
 }

@@ -288,7 +288,7 @@ hipError_t quantize_block(int log_b, const uint16_t *x, int64_t n_elems, int gro
     case 11: return quantize_one<BITS, CODEC, 11, 11>(x, n_elems, group, c, scales, zeros, stream);
     case 12:
         if constexpr (BITS == 8) return quantize_one<BITS, CODEC, 12, 12>(x, n_elems, group, c, scales, zeros, stream);
-        return hipErrorInvalidValue;       // 4 bit: the register form at every volume
+        else return hipErrorInvalidValue;  // the register form at every volume
     default: return hipErrorInvalidValue;
     }
 }

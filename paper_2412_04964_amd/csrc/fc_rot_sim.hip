@@ -4,15 +4,12 @@
 // fc_dequant_reduce_requant -> fc_dequantize_rot.
 //
 // What bounds it: vector instructions, (N + 1) log2 B of them per element for the butterflies alone, and which of them can issue side
-// by side (rot_priority in fc_rot_wave.hpp).  4 partials of 8192 x 8192 (group 128, INT4): 161 us; 166 when the
-// first stage ran at the ordinary priority, 181 when all did, 187 when element
-// bits 9 and 10 also came into registers by permlane swaps; 195 when bits 7 and 8 went through ds_swizzle and ds_bpermute, which keeps
-// the LDS crossbar of the whole compute unit busy for 6 cycles per instruction; the three steps took 247 to 255 us, the codes
-// and metadata going through HBM and the rows through LDS five times.  4 x 8192 x 4096 92.5 -> 79.5; 4 x 8192 x 5120 96 -> 84;
-// FP8 4 x 4096 x 8192 106 -> 97.5.  Five wavefronts per SIMD instead of four: slower.
-// The transform and its layout are those of fc_rot_wave.hpp; the partials are taken in
-// source order in a loop, the next one's loads in flight while one is coded.  The sum stays in the frame of the rotated values (see there): rounding is symmetric, so the
-// quantizer works on a negated value as on the value, and the inverse transform undoes the frame.
+// by side (rot_priority in fc_rot_wave.hpp).  4 partials, group 128, us: 8192 x 8192 INT4 161, x 4096 79.5, x 5120 84, FP8 4096 x 8192 97.5.
+// 8192 x 8192 INT4 with the first stage at the ordinary priority 166, all of it 181; with element bits 9 and 10 brought into registers by
+// permlane swaps as well 187.  Five wavefronts per SIMD instead of four: slower.
+// The transform and its layout are those of fc_rot_wave.hpp; the partials are taken in source order in a loop, the next one's loads in
+// flight while one is coded.  The sum stays in the frame of the rotated values (see there): rounding is symmetric, so the quantizer
+// works on a negated value as on the value, and the inverse transform undoes the frame.
 //
 // Exactness of the short form of the codes, taken when every zero-point of the wavefront is below 2048 in magnitude
 // and no rounding passes the top code: t = rint(x * inv) and z are then small integers, the lower clamp cannot act

@@ -600,13 +600,12 @@ __device__ __forceinline__ float rot_inverse_back(float (&v)[4][8], const RotLan
     }
 }
 
-// Blocks of 8192, the two forms of the transform: `swaps` has fewer instructions that issue alone, the other form fewer in all (and lays
-// a group of 256 elements across wavefronts).  us, swaps / exchange: quantize INT4, group 128 4.14 / 4.21 (128 tokens), 4.44 / 4.50
-// (256), 5.23 / 5.00 (320), 7.96 / 7.52 (1024), 42 / 38 (8192); sym, group 1024 4.49 / 4.50, 5.25 / 5.05, 7.88 / 7.51; all-reduce of two partials
-// INT4 7.29 / 7.46 (1), 7.63 / 7.76 (32), 9.05 / 9.17 (256), 10.9 / 10.6 (320), 18.2 / 17.3 (1024), of four 178 / 166 (8192).  Hence by the volume, at one workgroup
-// per compute unit (the all-reduce: ALONE in fc_rot_sim.hip).  FP8 always with: its stages in a row cost a move and a multiply-add
-// or a pass through the crossbar (all-reduce of two 8.26 / 8.65 at one token, 130 / 132 at 8192).
-inline bool rot_swaps_apply(bool fp8, int64_t n_elems) { return fp8 || n_elems <= ((int64_t)256 << 13); }
+// Quantizer, blocks of 8192, integer codes, the two forms of the transform: `swaps` has fewer instructions that issue alone, the other form
+// fewer in all (and lays a group of 256 elements across wavefronts).  us, swaps / exchange: INT4, group 128 4.14 / 4.21 (128 tokens), 4.44 / 4.50
+// (256), 5.23 / 5.00 (320), 7.96 / 7.52 (1024), 42 / 38 (8192); sym, group 1024 4.49 / 4.50 (256), 5.25 / 5.05, 7.88 / 7.51.  Hence by the
+// volume, at one workgroup per compute unit.  FP8 always swaps: its stages in a row cost a move and a multiply-add or a pass
+// through the crossbar.  The all-reduce: ALONE in fc_rot_sim.hip.
+inline bool rot_swaps_apply(int64_t n_elems) { return n_elems <= ((int64_t)256 << 13); }
 
 // ---------------------------------------------------------------------------
 // min / max of the groups.  Each lane first has one (min, max) pair per piece; a transposing reduction over bits 3
