@@ -78,18 +78,15 @@ __device__ __forceinline__ void rot_pack_literal(const float (&v)[4][8], const R
 __device__ __forceinline__ void rot_to_loads() { __builtin_amdgcn_s_setprio(3); }
 __device__ __forceinline__ void rot_loads_issued() { asm volatile("s_setprio 0" ::: "memory"); }
 
-// Whether a quantizer's wavefronts run at raised priority until their loads are issued, and over the first stage (FP8: over the stages in a
-// row, and the swap in blocks of 2048).  Up to as many wavefronts as the chip holds at once (8 per SIMD, 2^24 elements) every card
-// gains; above, cards differ.  us, raised / not, on two cards: INT8 6826 x 6144 25.5, 28.9 / 25.5, 25.8, 5461 x 12288 38.8, 44.7 / 39.7, 40.3, 8192 x
-// 8192 40.0, 45.2 / 40.9, 41.4, 8192 x 5120 24.4, 28.1 / 23.5, 23.9; FP8 13107 x 5120 37.7, 43.5 / 38.1, 40.3, 4096 x 6144 16.9, 19.4 / 17.6, 18.5; INT4
-// 8192 x 5120 20.6, 25.2 / 22.2, 22.6, 4000 x 5120 -, 14.5 / -, 13.3.  These are not raised there.  4-bit codes in wider blocks gain more on
-// the one card than they lose on the other (8192 x 4096 18.0, 22.4 / 20.0, 21.5; in 22.0 and 23.2 without any priority), FP8 in blocks of 4096
-// and 8192 gains on both.
-template <int BITS, bool FP8, int LB>
+// Whether a quantizer's wavefronts run at raised priority until their loads are issued and over the first stage.  Not in blocks of 1024 with
+// integer codes where there are more wavefronts than the chip holds at once (8 per SIMD, 2^24 elements): cards differ there.  us,
+// raised / not, on two cards, and the rows in LDS: 8192 x 5120 INT4 20.6, 25.2 / 22.2, 22.6, 24.2, INT8 24.4, 28.1 / 23.5, 23.9, 25.6; 4000 x 5120
+// -, 14.5 / -, 13.3, 13.2; below the limit both cards gain (2000 x 5120 7.00 / 7.50).  Blocks of 2048 and 4096 gain more on the one
+// (21.5 / 23.4) than they lose on the other (24.4 / 24.0).
+template <int LB, bool FP8>
 __device__ __forceinline__ bool rot_raised(int64_t n_elems)
 {
-    constexpr bool kAlways = FP8 ? LB >= 12 : BITS == 4 && LB >= 11;
-    return kAlways || n_elems <= (int64_t)8 * 1024 * 2048;
+    return LB != 10 || FP8 || n_elems <= (int64_t)8 * 1024 * 2048;
 }
 
 // Rotate block by block and quantize (FinegrainedQuantize of Algorithm 1 on the rotated values).
@@ -105,7 +102,7 @@ __global__ __launch_bounds__(64 * rot_group_waves(LB)) void k_quantize_rot(
     __shared__ __attribute__((aligned(16))) uint8_t pieces[rot_exchange_bytes(LB, kRounds)];
     __shared__ float mm[kWaves][kRotSlots][2];
 
-    const bool raised = rot_raised<BITS, FP8, LB>(n_elems);
+    const bool raised = rot_raised<LB, FP8>(n_elems);
     if (raised) rot_to_loads();
     const u32 tid = threadIdx.x, lane = tid & 63u;
     const u32 wave = (u32)__builtin_amdgcn_readfirstlane((int)(tid >> 6));
@@ -143,7 +140,7 @@ __global__ __launch_bounds__(64 * rot_group_waves(LB)) void k_quantize_rot(
                 for (int i = 0; i < 4; ++i) first_stage(raw[p][i], v[p][2 * i], v[p][2 * i + 1]);
             }, raised);
     }
-    rot_forward<LB, SWAPS, FP8, kRounds, kRaised>(v, L, pieces, wave, !FP8 || raised);
+    rot_forward<LB, SWAPS, FP8, kRounds, kRaised>(v, L, pieces, wave);
 
     // Forward scaling fwd = 2^-ceil(n/2), n = LB.  It is a power of two and nothing here is near the ends of
     // the fp32 range (the transformed values are multiples of 2^-24 below 2^30), so scaling commutes

@@ -185,17 +185,16 @@ __device__ __forceinline__ void rot_crossbar_stage(float (&v)[4][8], float s)
 // other way round (additions first) 184 and 43.6.
 // kPinned: nothing moves across (the all-reduce in blocks of 8192 is 2 % faster for it, in blocks of 1024 and 2048 1 % slower, the single
 // transforms as fast or 2 % slower).  kFlat: no priorities, for a wavefront that has its SIMD to itself (see ALONE in fc_rot_sim.hip).
-// `raised`: the same decided by the volume, for FP8's quantizer (rot_raised in fc_rot.hip).
 enum RotOrder { kRaised, kPinned, kFlat };
 template <int PRIORITY, RotOrder ORDER>
-__device__ __forceinline__ void rot_priority(float (&v)[4][8], bool raised = true)
+__device__ __forceinline__ void rot_priority(float (&v)[4][8])
 {
     if constexpr (ORDER == kFlat) return;
     if constexpr (ORDER == kPinned) {
 #pragma unroll
         for (int p = 0; p < 4; ++p) pin_values(v[p]);
     }
-    if (raised || PRIORITY == 0) __builtin_amdgcn_s_setprio(PRIORITY);
+    __builtin_amdgcn_s_setprio(PRIORITY);
     if constexpr (ORDER == kPinned) {
 #pragma unroll
         for (int p = 0; p < 4; ++p) pin_values(v[p]);
@@ -224,9 +223,9 @@ __device__ __forceinline__ void rot_row_some(float (&v)[4][8], const RotLane &L)
 // (left to itself the compiler has so many results of the crossbar in flight that the kernel gets 72 to 80 registers, where 64 let
 // eight wavefronts onto a SIMD: dequantize INT8 8192 x 2048 11.0 / 9.5 us).
 template <bool FP8, bool INV, RotOrder ORDER, bool RARE = false>
-__device__ __forceinline__ void rot_row_stages(float (&v)[4][8], const RotLane &L, bool raised = true)
+__device__ __forceinline__ void rot_row_stages(float (&v)[4][8], const RotLane &L)
 {
-    rot_priority<1, ORDER>(v, raised);
+    rot_priority<1, ORDER>(v);
     if constexpr (FP8) {
 #pragma unroll
         for (int p = 0; p < 4; ++p) {
@@ -273,10 +272,10 @@ __device__ __forceinline__ void swap_lane_bit(u32 &a, u32 &b)
 // settle_pieces comes first.  ALONE: at raised priority (see rot_priority), for FP8, whose transforms swap most: quantize 4096 x 8192
 // 24.2 / 23.8 us, 1024 x 8192 8.7 / 8.2, all-reduce of four 4096 x 8192 103.8 / 100.3; with integer codes no gain to 1 % slower.
 template <int LANE_BIT, bool ALONE = false, RotOrder ORDER = kPinned>
-__device__ __forceinline__ void rot_swap(float (&v)[4][8], bool raised = true)
+__device__ __forceinline__ void rot_swap(float (&v)[4][8])
 {
     constexpr RotOrder kOrder = ALONE && ORDER != kFlat ? kPinned : kFlat;
-    rot_priority<1, kOrder>(v, raised);
+    rot_priority<1, kOrder>(v);
     constexpr int P = LANE_BIT == 4 ? 1 : 2;
 #pragma unroll
     for (int p = 0; p < 4; ++p)
@@ -473,9 +472,9 @@ __device__ __forceinline__ RotPlaces rot_places(const RotLane &L)
 
 // Stages 3 ... LB-1 of the forward transform (0-2: rot_first_stages): kRotLoaded -> rot_forward_map
 template <int LB, bool SWAPS, bool FP8, int ROUNDS, RotOrder ORDER>
-__device__ __forceinline__ void rot_forward(float (&v)[4][8], const RotLane &L, uint8_t *lds, u32 wave, bool raised = true)
+__device__ __forceinline__ void rot_forward(float (&v)[4][8], const RotLane &L, uint8_t *lds, u32 wave)
 {
-    rot_row_stages<FP8, false, ORDER>(v, L, raised);
+    rot_row_stages<FP8, false, ORDER>(v, L);
     rot_piece_stage<1>(v);
     rot_piece_stage<2>(v);
     if constexpr (LB == 13 && SWAPS) {
@@ -501,7 +500,7 @@ __device__ __forceinline__ void rot_forward(float (&v)[4][8], const RotLane &L, 
     } else {
         rot_crossbar_stage<16>(v, L.s[4]);
         if constexpr (LB == 11) {
-            rot_swap<5, FP8, ORDER>(v, raised);
+            rot_swap<5, FP8, ORDER>(v);
             rot_piece_stage<2>(v);
         }
     }

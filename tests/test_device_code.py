@@ -205,19 +205,3 @@ def test_fused_step_is_raised_only_where_every_card_gains(kernels):
         if m and any(re.match(r"s_setprio [123]", i) for i in body):
             raised.add(tuple(map(int, m.groups())))       # bits before, bits after, sources
     assert raised == {(4, 4, 1), (4, 4, 2), (4, 8, 1)}
-
-
-def test_rotated_quantizers_are_raised_by_volume_where_cards_differ(kernels):
-    # A quantizer's wavefronts run at raised priority until their loads are issued, always or up to 2^24 elements: above, some cards
-    # take longer for it with 8-bit codes in blocks of up to 8192, FP8 and 4-bit codes in blocks of up to 2048 and of 1024.
-    found = {}
-    for name, body in kernels.items():
-        m = re.search(r"k_quantize_rotILi(\d)ELi(\d)ELb[01]ELi(\d+)E", name)
-        if not m:
-            continue
-        bits, codec, log_b = map(int, m.groups())         # codec: 0 asymmetric, 1 symmetric, 2 FP8
-        first = next(at for at, i in enumerate(body) if i.startswith("s_setprio 3"))
-        by_volume = any(i.startswith("s_cbranch") for i in body[:first])
-        assert found.setdefault((bits, codec, log_b), by_volume) == by_volume
-    want = {(8, c, b) for c in (0, 1) for b in (10, 11, 12, 13)} | {(8, 2, 10), (8, 2, 11)} | {(4, c, 10) for c in (0, 1)}
-    assert len(found) == 4 * 5 and {k for k, v in found.items() if v} == want
