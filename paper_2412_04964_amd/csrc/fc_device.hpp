@@ -1198,15 +1198,11 @@ __global__ __launch_bounds__(BT) void k_dequant_reduce_requant(
     // nine, possibly on another card, four runs each in turn gave 31.8 -> 36.2 and the cause was not found (shader clock and
     // temperature do not move in the others).
     constexpr bool kNibbles = BITS_IN == 4 && NSRC <= 4 && !SHORT;
-    // Raised priority until the code loads are issued, since a new wavefront shares its SIMD with seven others in the middle of their
-    // arithmetic: one source, and two that are coded again at 4 bit.  8192 x 8192 between other stages, us: g = 128 N = 1
-    // 16.2 -> 15.3, N = 2 20.9 -> 19.9 (other cards 21.2 -> 19.8, 21.9 -> 21.4, 20.3 -> 19.5), g = 1024 20.3 -> 19.3; 4000 x 5120 9.05 -> 8.6; N = 1 4 -> 8
-    // bit, replayed graphs, 2560 x 8192 8.4 -> 7.5; up to 1000 x 8192 equal.  Not where memory answers the bursts of the loads worse, as
-    // it does by card: two sources coded again at 8 bit (replayed graphs, two cards, not raised / raised: 5120 x 8192 g = 128 18.6 / 21.2, 17.0 /
-    // 16.7, g = 64 21.2 / 22.6, 17.7 / 17.4; 8192 x 8192 27.1 / 29.7, 24.6 / 24.4); N = 4 30.8 / 33.0, on one card 31.7 / 36.9; N = 3 and
-    // g = 32 equal.  Compact metadata is as it was before this: not raised, though on one card it would gain as much (8192 x 8192 g = 128
-    // N = 1 16.4 / 15.4, N = 2 21.3 / 20.7).
-    constexpr bool kLoadsFirst = kNibbles && (NSRC == 1 || (NSRC == 2 && BITS_OUT == 4)) && LPG > 1 && !HM;
+    // Up to two sources: raised priority until the code loads are issued, since a new wavefront shares its SIMD with seven others in
+    // the middle of their arithmetic.  8192 x 8192 between other stages, us: g = 128 N = 1 16.2 -> 15.3, N = 2 20.9 -> 19.9 (other cards 21.2
+    // -> 19.8, 21.9 -> 21.4, 20.3 -> 19.5), g = 1024 20.3 -> 19.3, 4 -> 8 bit 24.75 -> 24.5; 4000 x 5120 9.05 -> 8.6; g = 32 24.6 -> 24.8;
+    // up to 1000 x 8192 equal.  N = 3 equal; N = 4 30.8 -> 33.0, on one card 31.7 -> 36.9: memory answers the bursts of its loads worse.
+    constexpr bool kLoadsFirst = kNibbles && NSRC <= 2 && LPG > 1 && !HM;
     struct MetaRec { float s; u32 z; };                       // z: fp32 bits; packed halves for accumulate_fast
 
     __shared__ __attribute__((aligned(16))) uint8_t landing[kWaves][NSRC][1024];

@@ -194,14 +194,3 @@ def test_rotated_tiles_are_loaded_before_anything_waits(kernels):
         first = 4 if "allreduce" in name else len(loads)
         assert sum(at < wait for at in loads) >= first >= 4, "%s: %d of %d loads before the first wait" % (name, sum(at < wait for at in loads), first)
     assert seen >= 4 * (5 + 5 + 3)                 # four blocks; quantizer and dequantizer with five codes, all-reduce with three
-
-
-def test_fused_step_is_raised_only_where_every_card_gains(kernels):
-    # Raised priority until the code loads are issued sends them in bursts, which some cards answer worse: two sources of 4 bit
-    # coded again at 8 bit took up to 14 % longer there.
-    raised = set()
-    for name, body in kernels.items():
-        m = re.search(r"k_dequant_reduce_requantILi(\d)ELi(\d)ELi(\d)E", name)
-        if m and any(re.match(r"s_setprio [123]", i) for i in body):
-            raised.add(tuple(map(int, m.groups())))       # bits before, bits after, sources
-    assert raised == {(4, 4, 1), (4, 4, 2), (4, 8, 1)}
