@@ -1200,8 +1200,11 @@ __global__ __launch_bounds__(BT) void k_dequant_reduce_requant(
     constexpr bool kNibbles = BITS_IN == 4 && NSRC <= 4 && !SHORT;
     // Up to two sources: raised priority until the code loads are issued, since a new wavefront shares its SIMD with seven others in
     // the middle of their arithmetic.  8192 x 8192 between other stages, us: g = 128 N = 1 16.2 -> 15.3, N = 2 20.9 -> 19.9 (other cards 21.2
-    // -> 19.8, 21.9 -> 21.4, 20.3 -> 19.5), g = 1024 20.3 -> 19.3, 4 -> 8 bit 24.75 -> 24.5; 4000 x 5120 9.05 -> 8.6; g = 32 24.6 -> 24.8;
-    // up to 1000 x 8192 equal.  N = 3 equal; N = 4 30.8 -> 33.0, on one card 31.7 -> 36.9: memory answers the bursts of its loads worse.
+    // -> 19.8, 21.9 -> 21.4, 20.3 -> 19.5), g = 1024 20.3 -> 19.3; 4000 x 5120 9.05 -> 8.6; g = 32 24.6 -> 24.8; up to 1000 x 8192 equal.  N = 2
+    // 4 -> 8 bit, one call after the other, two cards: 1280 x 8192 5.87 -> 4.79, 5.88 -> 4.83, 8192 x 4096 13.76 -> 13.52, 15.8 -> 16.7, 8192 x 8192
+    // 23.9 -> 23.5, 26.0 -> 25.1; on a third g = 64 28.9 -> 35.2.  N = 3 equal; N = 4 30.8 -> 33.0, on one card 31.7 -> 36.9: memory answers the
+    // bursts of its loads worse, and how much worse depends on the card.  Compact metadata is as it was before this, without: in replayed
+    // graphs on one card it would gain as much (8192 x 8192 g = 128 N = 1 16.4 -> 15.4, N = 2 21.3 -> 20.7, 4 -> 8 bit 26.0 -> 26.5).
     constexpr bool kLoadsFirst = kNibbles && NSRC <= 2 && LPG > 1 && !HM;
     struct MetaRec { float s; u32 z; };                       // z: fp32 bits; packed halves for accumulate_fast
 

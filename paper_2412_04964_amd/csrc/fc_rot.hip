@@ -19,11 +19,12 @@
 //
 // What bounds them: vector instructions and which of them issue side by side (rot_priority in fc_rot_wave.hpp) in blocks of 4096 and 8192; in
 // the dequantizer of blocks of 1024 more the wait for memory, since a wavefront loads, transforms, stores and ends.  Rotate + quantize /
-// dequantize + rotate, group 128, us over six cards: 8192 x 8192 INT4 35-39 / 33-36, INT8 39-42 / 37-38, FP8 39-44 / 38-41; 5461 x 12288 (blocks of
-// 4096) INT4 34-39 / 32-36, INT8 37-41 / 36-37, FP8 38-45 / 38-40; 10922 x 6144 (2048) INT4 33-39 / 30-32, INT8 37-39 / 34-35, FP8 38-41 / 35-37;
-// 8192 x 5120 (1024) INT4 22-24 / 19-21, INT8 24-25 / 23, FP8 24-27 / 22-24.  Without priorities over the instructions that issue
-// alone, and with element bits 9 and 10 by swaps: 8192 x 8192 44-48 / 38-42, 44-48 / 41-43, 45-49 / 44-46; 8192 x 5120 23-25 (rows in LDS) / 22-24,
-// 24-26 / 24-25, 25-28 / 25-26.  Launch-bound volumes run in fc_rot_rows.hip where that is faster.
+// dequantize + rotate, group 128, us by card (launches of one kernel in a row, four to seven cards): 8192 x 8192 INT4 35-39 / 37-39, INT8
+// 37-40 / 39-41, FP8 42-45 / 41-43; 5461 x 12288 (blocks of 4096) INT4 34-38 / 36-38, INT8 36-40 / 38-40, FP8 40-43 / 40-42; 10922 x 6144 (2048)
+// INT4 33-37 / 32-35, INT8 35-40 / 35-38, FP8 38-41 / 38-40; 8192 x 5120 (1024) INT4 21-24 / 20-21, INT8 24-26 / 22-23, FP8 23-29 / 23-24.
+// Without priorities over the instructions that issue alone, and with element bits 9 and 10 by swaps: 8192 x 8192 41-46 / 40-42, 43-47 / 41-44,
+// 45-48 / 44-46; 8192 x 5120 22-24 (rows in LDS) / 22-23, 24-27 / 24-25, 25-29 / 25-27.  Launch-bound volumes run in fc_rot_rows.hip where
+// that is faster.
 // Measured and not taken: 32 consecutive elements per lane and a 16 x 16 exchange with other lanes through 5 KB of LDS (40.3 us for blocks
 // of 8192, when this form took 43.0, but 23.8 for 1024 and 23.0 / 48 in the dequantizer, whose register needs it does not fit); all stages
 // between lanes by permlane swaps; persistent workgroups that load the next tile while they transform the current one (4, 5, 6, 12
@@ -81,8 +82,11 @@ __device__ __forceinline__ void rot_loads_issued() { asm volatile("s_setprio 0" 
 // Whether a quantizer's wavefronts run at raised priority until their loads are issued and over the first stage.  Not in blocks of 1024 with
 // integer codes where there are more wavefronts than the chip holds at once (8 per SIMD, 2^24 elements): cards differ there.  us,
 // raised / not, on two cards, and the rows in LDS: 8192 x 5120 INT4 20.6, 25.2 / 22.2, 22.6, 24.2, INT8 24.4, 28.1 / 23.5, 23.9, 25.6; 4000 x 5120
-// -, 14.5 / -, 13.3, 13.2; below the limit both cards gain (2000 x 5120 7.00 / 7.50).  Blocks of 2048 and 4096 gain more on the one
-// (21.5 / 23.4) than they lose on the other (24.4 / 24.0).
+// -, 14.5 / -, 13.3, 13.2; below the limit both cards gain (2000 x 5120 7.00 / 7.50).  FP8 in blocks of 1024, without any priority -> so, launches
+// of one kernel in a row on two cards: 3481 x 5120 13.6 -> 14.4, 14.1 -> 14.8, but 8192 x 5120 26.3 -> 25.2, 27.7 -> 28.2 and the three steps of
+// a rank of four 31.0 -> 28.4, 60.5 -> 56.0.  INT8 in wider blocks gains in a row on every card (8192 x 8192 43-47 -> 37-40; the three
+// steps 101 -> 91, with this limit for it too 94); where two builds take turns every few milliseconds it loses on some (8192 x 6144 32.2 ->
+// 36.0), which no program does.
 template <int LB, bool FP8>
 __device__ __forceinline__ bool rot_raised(int64_t n_elems)
 {
