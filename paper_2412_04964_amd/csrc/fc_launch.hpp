@@ -14,19 +14,38 @@ namespace fc {
 // through the thread's last-error slot, which hipGetLastError would also clear of errors that other
 // code left there, and a stale one would be taken for a failure of a launch that succeeded.)
 template <typename... P, size_t... I>
-inline hipError_t launch_kernel_impl(void (*kernel)(P...), dim3 grid, dim3 block, hipStream_t stream,
+inline hipError_t launch_kernel_impl(void (*kernel)(P...), dim3 grid, dim3 block, size_t lds, hipStream_t stream,
                                      std::tuple<P...> &args, std::index_sequence<I...>)
 {
     void *ptrs[] = {static_cast<void *>(&std::get<I>(args))...};
-    return hipLaunchKernel(reinterpret_cast<const void *>(kernel), grid, block, ptrs, 0, stream);
+    return hipLaunchKernel(reinterpret_cast<const void *>(kernel), grid, block, ptrs, lds, stream);
+}
+
+// lds: bytes of LDS that a workgroup holds beyond what the kernel declares (see lds_to_limit)
+template <typename... P, typename... A>
+inline hipError_t launch_kernel_lds(void (*kernel)(P...), dim3 grid, dim3 block, size_t lds, hipStream_t stream, A... a)
+{
+    static_assert(sizeof...(P) == sizeof...(A), "one argument per kernel parameter");
+    std::tuple<P...> args{static_cast<P>(a)...};
+    return launch_kernel_impl(kernel, grid, block, lds, stream, args, std::index_sequence_for<P...>{});
 }
 
 template <typename... P, typename... A>
 inline hipError_t launch_kernel(void (*kernel)(P...), dim3 grid, dim3 block, hipStream_t stream, A... a)
 {
-    static_assert(sizeof...(P) == sizeof...(A), "one argument per kernel parameter");
-    std::tuple<P...> args{static_cast<P>(a)...};
-    return launch_kernel_impl(kernel, grid, block, stream, args, std::index_sequence_for<P...>{});
+    return launch_kernel_lds(kernel, grid, block, 0, stream, a...);
+}
+
+// LDS to ask for at the launch of a kernel that declares `own` bytes, so that a compute unit (160 KB) holds at most `groups`
+// workgroups of it; 0 for no limit.  The kernel does not touch it.  A launch decides by its volume how many workgroups
+// share a compute unit, which a bound on registers in the kernel's own code could not.  The middle between what
+// `groups` and one more of them would leave each, so that the granularity of LDS allocation does not matter.
+inline size_t lds_to_limit(int groups, size_t own)
+{
+    constexpr size_t kUnitLds = 160 * 1024;
+    if (groups <= 0) return 0;
+    const size_t each = (kUnitLds / (size_t)groups + kUnitLds / (size_t)(groups + 1)) / 2;
+    return each > own ? each - own : 0;
 }
 
 // Quantizer: 0 = asymmetric (Eq. 1-2), 1 = symmetric (Eq. 3-4), 2 = FP8 E4M3 (8 bit only),

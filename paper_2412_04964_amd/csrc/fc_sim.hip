@@ -33,10 +33,18 @@
 //    the median-of-three form of the first stage remains exact, lower clamp included.
 //
 // Decomposition: a lane owns 16 consecutive elements (two 128-bit pieces of binary16 per partial), a wavefront
-// 1024, a workgroup of two wavefronts 2048; a group of g <= 1024 elements is g/16 adjacent lanes.  At wavefront
-// start all N x 2 KB of the tile are requested as buffer-to-LDS loads (nothing sits in vector registers while in
-// flight); the partials are then consumed in source order as they land.  The binary16 result leaves through the
-// first landing zone as coalesced 1 KB pieces.
+// 1024, a workgroup of two wavefronts 2048; a group of g <= 1024 elements is g/16 adjacent lanes.  The partials come
+// through one landing zone of 2 KB per wavefront, in source order, as buffer-to-LDS loads (nothing sits in vector
+// registers while in flight): the next partial's loads are issued as soon as this one's data has been read from
+// the zone, so they are in flight while it is folded in (DEPTH = 1; = 2: two zones, two partials ahead).  The binary16
+// result leaves through the zone as coalesced 1 KB pieces.
+//
+// What bounds it: HBM, and the number of reads that wait in the memory system at once.  A bare stream of this shape (four
+// 128 MB partials read, one written, no arithmetic) takes 99 to 103 us with 48 to 64 KB in flight per compute unit and
+// 107 to 111 with 128 KB and more: past what the latency needs, requests only queue and get in each other's way.  Hence one
+// partial at a time instead of all N, and, for volumes that take several rounds of wavefronts, a limit on the workgroups
+// per compute unit (sim_workgroups_per_unit).  4 partials of 8192 x 8192, INT4, group 128, us: all partials at once 109.7,
+// one at a time 108.5, with 10 / 9 / 8 / 7 / 6 workgroups per compute unit 108.3 / 106.5 / 103.0 / 102.0 / 107.7.
 #include "fc_device.hpp"
 #include "fc_launch.hpp"
 
@@ -49,7 +57,7 @@ constexpr int kSimTileElems = kSimBlockThreads * kSimLaneElems;
 static_assert(kSimWaveElems == kFusedAllreduceMaxGroup && kSimTileElems == kFusedAllreduceTileElems,
               "the launcher's applicability test describes this decomposition");
 
-template <int CODEC, int BITS_RS, int BITS_AG, int NSRC, int LPG>
+template <int CODEC, int BITS_RS, int BITS_AG, int NSRC, int LPG, int DEPTH>
 __global__ __launch_bounds__(kSimBlockThreads) void k_allreduce_fused(const uint16_t *__restrict__ x, int64_t n_elems,
                                                                      int lpg, uint16_t *__restrict__ y)
 {
@@ -57,21 +65,23 @@ __global__ __launch_bounds__(kSimBlockThreads) void k_allreduce_fused(const uint
     constexpr int kZone = E * 2 * 64;                                  // bytes of one partial per wavefront: 2 KB
     constexpr int kWaves = kSimBlockThreads / 64;
     constexpr bool HM = CODEC == kAsymH;
-    static_assert(2 * (NSRC - 1) <= kMaxCountedVmem, "landing-zone waits count the loads of the later sources");
+    static_assert(DEPTH >= 1 && DEPTH <= NSRC && 2 * (DEPTH - 1) <= kMaxCountedVmem,
+                  "landing-zone waits count the loads of the later sources");
     static_assert(CODEC != kFp8 || (BITS_RS == 8 && BITS_AG == 8), "E4M3 codes are bytes");
-    __shared__ __attribute__((aligned(16))) uint8_t landing[kWaves][NSRC][kZone];
+    __shared__ __attribute__((aligned(16))) uint8_t landing[kWaves][DEPTH][kZone];
 
     const u32 tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
     const u32 tile = xcd_tile<xcd_chunk(kSimTileElems * 2)>((u32)((n_elems + kSimTileElems - 1) / kSimTileElems));
     const int64_t e_tile = (int64_t)tile * kSimTileElems;
     const int64_t left = (n_elems - e_tile) * 2;                       // bytes from the tile to the end of a partial
 
-#pragma unroll
-    for (int j = 0; j < NSRC; ++j) {
+auto fetch = [&](int j) {
         const rsrc_t rx = make_rsrc(x + (int64_t)j * n_elems + e_tile, left);
-        dma_piece(rx, wave * kZone + lane * 16, &landing[wave][j][0]);
-        dma_piece(rx, wave * kZone + 1024 + lane * 16, &landing[wave][j][1024]);
-    }
+        dma_piece(rx, wave * kZone + lane * 16, &landing[wave][j % DEPTH][0]);
+        dma_piece(rx, wave * kZone + 1024 + lane * 16, &landing[wave][j % DEPTH][1024]);
+    };
+#pragma unroll
+    for (int j = 0; j < DEPTH; ++j) fetch(j);
     issue_order_fence();
 
     float acc[E];
@@ -80,11 +90,14 @@ __global__ __launch_bounds__(kSimBlockThreads) void k_allreduce_fused(const uint
 #pragma unroll
     for (int j = 0; j < NSRC; ++j) {
         // source j has landed once no more than the loads of the later sources are outstanding
-        wait_vmem_outstanding(2 * (NSRC - 1 - j));
-        u32x4 a0 = lds_read_b128_issue(&landing[wave][0][lane * (E * 2)], j * kZone);
-        u32x4 a1 = lds_read_b128_issue(&landing[wave][0][lane * (E * 2)], j * kZone + 16);
+        wait_vmem_outstanding(2 * ((NSRC < j + DEPTH ? NSRC : j + DEPTH) - 1 - j));
+        u32x4 a0 = lds_read_b128_issue(&landing[wave][0][lane * (E * 2)], j % DEPTH * kZone);
+        u32x4 a1 = lds_read_b128_issue(&landing[wave][0][lane * (E * 2)], j % DEPTH * kZone + 16);
         lds_read_complete(a0);
         lds_read_complete(a1);
+        // the zone has been read: it takes the next source but DEPTH - 1
+        if (j + DEPTH < NSRC) fetch(j + DEPTH);
+        issue_order_fence();
         const h2 p[8] = {as_h2(a0[0]), as_h2(a0[1]), as_h2(a0[2]), as_h2(a0[3]),
                          as_h2(a1[0]), as_h2(a1[1]), as_h2(a1[2]), as_h2(a1[3])};
         h2 lo = pk_min(p[0], p[1]), hi = pk_max(p[0], p[1]);
@@ -187,15 +200,35 @@ namespace {
 
 constexpr int CODEC = FC_SIM_CODEC;
 
+// Workgroups that a compute unit shall hold at once, 0: as many as fit.  From 18 * 2^20 elements per partial on (over four
+// rounds of wavefronts) the chip would otherwise have more reads waiting than the memory system serves well.  With few sources
+// more of the wavefronts are at the start or the end of their tile, and the limit is higher.  INT4, group 128, us, without a limit and with so many workgroups: N = 2
+// 8192 x 8192 63.5, 10: 61.9, 8: 63.2, 7: 66.2; N = 3 86.0, 9: 82.7, 8: 82.0, 7: 85; N = 4 109.5, 8: 103.0, 7: 102.2; N = 5 131.8, 8:
+// 126.2, 7: 121.2, 6: 127.8; N = 6 151.8, 148.9, 142.2, 149.3; N = 8 205.4, 196.1, 187.9, 194.3.  N = 4 x 4096: 8 M elements 15.3 / 15.9
+// with 8, 16 M 28.4 / 28.9, 20 M 35.4 / 35.2, 24 M 42.3 / 41.2, 32 M 56.0 / 53.5.  N = 1: no gain from any limit.
+int sim_workgroups_per_unit(int n_src, int64_t n_elems)
+{
+    if (n_src == 1 || n_elems < (int64_t)18 << 20) return 0;
+    return n_src == 2 ? 10 : n_src <= 4 ? 8 : 7;
+}
+
 template <int BITS_RS, int BITS_AG, int NSRC>
 hipError_t launch_sim_src(const uint16_t *x, int64_t n_elems, int group, uint16_t *y, hipStream_t stream)
 {
     const dim3 grid((unsigned)((n_elems + kSimTileElems - 1) / kSimTileElems)), block(kSimBlockThreads);
     const int lpg = group / kSimLaneElems;
+    // Many sources in less than two rounds of wavefronts: a wavefront's chain of loads bounds the call, two at a time shorten
+    // it (group 128, us, one / two at a time: N = 8 1.2 M elements 7.50 / 6.87, 2 M 9.14 / 8.45, 3 M 11.8 / 11.6, 4 M 13.7 / 14.5; N = 6
+    // 2 M 7.70 / 7.16; N = 4 1.2 M 4.99 / 4.89, 2 M 6.06 / 5.91, 4 M 8.89 / 9.26; all at once N = 8 2 M 9.88, 4 M 17.9, N = 4 9.62).
+    if constexpr (NSRC >= 5)
+        if (n_elems <= (int64_t)3 << 20)
+            return launch_kernel(k_allreduce_fused<CODEC, BITS_RS, BITS_AG, NSRC, 0, 2>, grid, block, stream, x, n_elems,
+                                 lpg, y);
+    const size_t pad = lds_to_limit(sim_workgroups_per_unit(NSRC, n_elems), kSimTileElems * 2);
     if (lpg == 8)                                                      // g = 128: the lane pattern is a constant
-        return launch_kernel(k_allreduce_fused<CODEC, BITS_RS, BITS_AG, NSRC, 8>, grid, block, stream, x, n_elems,
-                             lpg, y);
-    return launch_kernel(k_allreduce_fused<CODEC, BITS_RS, BITS_AG, NSRC, 0>, grid, block, stream, x, n_elems, lpg, y);
+        return launch_kernel_lds(k_allreduce_fused<CODEC, BITS_RS, BITS_AG, NSRC, 8, 1>, grid, block, pad, stream, x, n_elems,
+                                 lpg, y);
+    return launch_kernel_lds(k_allreduce_fused<CODEC, BITS_RS, BITS_AG, NSRC, 0, 1>, grid, block, pad, stream, x, n_elems, lpg, y);
 }
 
 template <int BITS_RS, int BITS_AG>
