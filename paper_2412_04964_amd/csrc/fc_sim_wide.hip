@@ -13,8 +13,12 @@
 // per partial.  After the first barrier lane l works out scale, reciprocal and zero-point of source l / 8 (one
 // evaluation of Eq. 1 per wavefront for all N sources), and they are broadcast by v_readlane.
 //
-// Measured, 4 partials of 8192 x 8192, one group per token, INT4: 111 us a call (6.0 TB/s on 10 bytes per element)
-// against 168 us for the three kernels that these groups took before, whose codes and metadata travel through HBM.
+// Large volumes run with a limited number of workgroups per compute unit (wide_workgroups_per_unit): with all that fit,
+// more reads wait in the memory system than it serves well (see fc_sim.hip).
+//
+// Measured, 4 partials of 8192 x 8192, INT4: groups of 2048 101 us a call (6.6 TB/s on 10 bytes per element; without the limit
+// 115), of 4096 102 (110), one group per token 102 (112), against 168 us for the three kernels, whose codes and
+// metadata travel through HBM.
 #include "fc_device.hpp"
 #include "fc_launch.hpp"
 
@@ -186,13 +190,29 @@ namespace {
 
 constexpr int CODEC = FC_SIM_CODEC;
 
+// Workgroups that a compute unit shall hold at once, 0: as many as fit.  From 12 * 2^20 elements per partial on: 16 wavefronts with
+// two sources, 14 with three, 12 from four on, in workgroups of two or more (groups of 8192: two workgroups in every case; of
+// 16384: no limit, one workgroup to a compute unit is too few).  INT4, us, without and with so many workgroups: 8192 x 8192, groups
+// of 2048, N = 1 42.9 / 16: 42.9, 12: 41.7, 8: 46.9; N = 2 68.3 / 10: 63.1, 8: 60.8, 7: 63.2; N = 3 93.8 / 8: 86.7, 7: 80.9, 6: 83.7; N = 4
+// 114.9 / 7: 104.3, 6: 100.7, 5: 106.1; N = 6 163.9 / 7: 157, 6: 154, 5: 150; N = 8 209.6 / 7: 200, 6: 190, 5: 189; groups of 4096 N = 2
+// 67.2 / 4: 61.3, 3: 65.1; N = 3 86.7 / 4: 83.3, 3: 81.1; N = 4 109.8 / 3: 101.8, 2: 111.5; N = 8 203.8 / 3: 184.4.  Groups of
+// 2048, N = 4, 6.5 M elements 13.4 / 6: 14.2, 13 M 24.2 / 23.6, 26 M 45.9 / 42.4; N = 8 23.1 / 23.5, 42.4 / 41.2, 82.1 / 76.6.
+int wide_workgroups_per_unit(int n_src, int64_t n_elems, int group)
+{
+    if (n_src == 1 || group > 8192 || n_elems < (int64_t)12 << 20) return 0;
+    const int waves = n_src == 2 ? 16 : n_src == 3 ? 14 : 12, per_group = group / 1024;
+    return waves / per_group > 2 ? waves / per_group : 2;
+}
+
 template <int BITS_RS, int BITS_AG>
 hipError_t launch_wide_bits(const uint16_t *x, int n_src, int64_t n_elems, int group, uint16_t *y, hipStream_t stream)
 {
     const dim3 grid((unsigned)(n_elems / group)), block(group / 16);
     const int sh = log2_int(group);
+    const size_t pad = lds_to_limit(wide_workgroups_per_unit(n_src, n_elems, group),
+                                    (size_t)(n_src + 1) * kSimWideMaxWaves * 2 * sizeof(float));
 #define FC_SIM_WIDE(N) \
-    case N: return launch_kernel(k_allreduce_wide<CODEC, BITS_RS, BITS_AG, N>, grid, block, stream, x, n_elems, sh, y);
+    case N: return launch_kernel_lds(k_allreduce_wide<CODEC, BITS_RS, BITS_AG, N>, grid, block, pad, stream, x, n_elems, sh, y);
     switch (n_src) {
         FC_SIM_WIDE(1) FC_SIM_WIDE(2) FC_SIM_WIDE(3) FC_SIM_WIDE(4)
         FC_SIM_WIDE(5) FC_SIM_WIDE(6) FC_SIM_WIDE(7) FC_SIM_WIDE(8)
