@@ -244,6 +244,23 @@ def test_allreduce_sim_rot_on_both_sides_of_the_limit(fc, quantizer, n_src, hidd
             assert torch.equal(y.t.view(torch.int16), want[pick]), "N=%d h=%d g=%d rows=%d" % (n_src, hidden, group, rows)
 
 
+@pytest.mark.parametrize("quantizer,n_src", [(oracle.ASYM, 3), (oracle.ASYM, 4), (oracle.ASYM, 8), (oracle.SYM, 5), (oracle.FP8, 3), (oracle.FP8, 7)])
+@pytest.mark.parametrize("hidden", [2048, 4096, 8192])
+def test_allreduce_sim_rot_few_coarse_groups(fc, quantizer, n_src, hidden):
+    # one to seven groups per partial: the three steps lay one partial's metadata right behind the other's, not on multiples of 16 bytes
+    bits = 8 if quantizer == oracle.FP8 else 4
+    for group, rows in ((hidden, 1), (hidden, 2), (hidden, 7), (hidden // 2, 1), (hidden // 2, 3)):
+        x = synth_inputs.make_partials_stress(n_src, rows, hidden, (rows + n_src) % synth_inputs.STRESS_KINDS, seed=hidden + rows)
+        need = fc.allreduce_sim_workspace_bytes(n_src, rows, hidden, group, bits, bits)
+        space = torch.full((need + 64,), 0xA5, dtype=torch.uint8, device="cuda")
+        y = Guarded((rows, hidden), torch.float16)
+        fc.allreduce_sim_rot(dev(x.view(np.uint16)).view(torch.float16), group, bits, bits, quantizer, out=y.t, workspace=space[:need])
+        torch.cuda.synchronize(); y.check()
+        assert (space[need:] == 0xA5).all(), "written past the workspace"
+        want = oracle.allreduce_sim_rot(x, group, bits, bits, quantizer)
+        assert same_bits(y.t.cpu().numpy().view(np.uint16), want.view(np.uint16)), "N=%d h=%d g=%d rows=%d" % (n_src, hidden, group, rows)
+
+
 def test_rot_rejects_unsupported_rows_and_empty_is_noop(fc):
     x = torch.zeros((2, 2560), dtype=torch.float16, device="cuda")           # 5 x 512: blocks below 1024
     with pytest.raises(fc.FcError):
