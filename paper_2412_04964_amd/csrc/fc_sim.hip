@@ -222,8 +222,10 @@ hipError_t launch_sim_src(const uint16_t *x, int64_t n_elems, int group, uint16_
     // 2 M 7.70 / 7.16; N = 4 1.2 M 4.99 / 4.89, 2 M 6.06 / 5.91, 4 M 8.89 / 9.26; all at once N = 8 2 M 9.88, 4 M 17.9, N = 4 9.62).
     if constexpr (NSRC >= 5)
         if (n_elems <= (int64_t)3 << 20)
-            return launch_kernel(k_allreduce_fused<CODEC, BITS_RS, BITS_AG, NSRC, 0, 2>, grid, block, stream, x, n_elems,
-                                 lpg, y);
+            return lpg == 8 ? launch_kernel(k_allreduce_fused<CODEC, BITS_RS, BITS_AG, NSRC, 8, 2>, grid, block, stream, x,
+                                            n_elems, lpg, y)
+                            : launch_kernel(k_allreduce_fused<CODEC, BITS_RS, BITS_AG, NSRC, 0, 2>, grid, block, stream, x,
+                                            n_elems, lpg, y);
     const size_t pad = lds_to_limit(sim_workgroups_per_unit(NSRC, n_elems), kSimTileElems * 2);
     if (lpg == 8)                                                      // g = 128: the lane pattern is a constant
         return launch_kernel_lds(k_allreduce_fused<CODEC, BITS_RS, BITS_AG, NSRC, 8, 1>, grid, block, pad, stream, x, n_elems,
