@@ -5,8 +5,7 @@
 // binary16 result, with both quantizations happening in registers.  Every rounding of the three-kernel path is
 // kept: FinegrainedQuantize of each partial (Eq. 1-2) gives codes q_j, scale s_j and zero-point z_j of the group;
 // the sum is acc = fma(q_j - z_j, s_j, acc) in source order from +0; FinegrainedQuantize of acc with the second
-// bit-width; Dequantize to binary16.  Codes are formed literally as in Eq. 2 (the packed fast paths of the bulk
-// kernels are proven equal to this form) and never leave the lane, so the result is bit-identical to
+// bit-width; Dequantize to binary16.  Codes never leave the lane, and the result is bit-identical to
 // fc_quantize x N -> fc_dequant_reduce_requant -> fc_dequantize while a decode-sized all-reduce costs one launch
 // instead of three.
 //
@@ -28,8 +27,12 @@ constexpr int kSmallLaneElems = 8;
 constexpr int kSmallWaveElems = 64 * kSmallLaneElems;
 
 // FinegrainedQuantize of the lane's values and the inverse of Eq. 2 without its scale: d = q - z (the signed code, the value
-// of the E4M3 byte).  +0 is added to a signed code: the stored integer has no -0.
-template <int CODEC, int BITS>
+// of the E4M3 byte).  +0 is added to a signed code: the stored integer has no -0.  Asymmetric codes are not formed as integers:
+// clamp(t + z) - z is a median of three on t where t and z are integers of few bits (HALF: the values were binary16), and the
+// literal fp32 operations otherwise; fc_sim.hip has the reasons.  us under graph replay, codes as integers / so, INT4, group 128,
+// hidden 8192: N = 2 64 tokens 2.92 / 2.79, 115 tokens 3.52 / 3.25; N = 4 3.49 / 3.26, 4.30 / 3.96; N = 8 32 tokens 3.52 / 3.33,
+// 64 tokens 4.51 / 4.09, 115 tokens 6.69 / 6.05.
+template <int CODEC, int BITS, bool HALF>
 __device__ __forceinline__ void small_codes(const float (&v)[kSmallLaneElems], int lpg, float &s, float (&d)[kSmallLaneElems])
 {
     constexpr int E = kSmallLaneElems;
@@ -39,8 +42,13 @@ __device__ __forceinline__ void small_codes(const float (&v)[kSmallLaneElems], i
         lane_minmax(v, mn, mx);
         group_minmax<0>(mn, mx, lpg);
         group_params<BITS, CODEC == kAsymH>(mn, mx, s, inv, zf);
+        constexpr float qmax = (float)((1 << BITS) - 1);
+        const float d_lo = 0.0f - zf, d_hi = qmax - zf;
 #pragma unroll
-        for (int i = 0; i < E; ++i) d[i] = (float)encode<BITS>(v[i], inv, zf) - zf;
+        for (int i = 0; i < E; ++i) {
+            const float t = rintf(v[i] * inv);
+            d[i] = HALF ? __builtin_amdgcn_fmed3f(t, d_lo, d_hi) : __builtin_amdgcn_fmed3f(t + zf, 0.0f, qmax) - zf;
+        }
     } else {
         const float amax = group_max<0>(lane_absmax(v), lpg);
         if constexpr (CODEC == kFp8) {
@@ -89,7 +97,7 @@ __global__ __launch_bounds__(64 * NSRC) void k_allreduce_small(const uint16_t *_
             v[2 * k + 1] = (float)p.y;
         }
         float s, d[E];
-        small_codes<CODEC, BITS_RS>(v, lpg, s, d);
+        small_codes<CODEC, BITS_RS, true>(v, lpg, s, d);
         if constexpr (NSRC > 1) {
             f32x4 *mine = reinterpret_cast<f32x4 *>(&diff[j][lane][0]);
             mine[0] = f32x4{d[0], d[1], d[2], d[3]};
@@ -120,7 +128,7 @@ __global__ __launch_bounds__(64 * NSRC) void k_allreduce_small(const uint16_t *_
         }
 
         float s2, d2[E];
-        small_codes<CODEC, BITS_AG>(acc, lpg, s2, d2);
+        small_codes<CODEC, BITS_AG, false>(acc, lpg, s2, d2);
         u32x4 out;
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
@@ -175,12 +183,12 @@ static hipError_t launch_small_codec(int bits_rs, int bits_ag, const uint16_t *x
 
 // Where the two forms cross (hidden 8192, g = 128, us per launch under graph replay, this one / bulk; asymmetric INT8, symmetric
 // INT4, compact metadata INT4, FP8):
-//   N = 8   64 tokens 4.02 / 4.58, 3.33 / 4.29, 4.12 / 4.47, 3.31 / 4.79; 128 tokens (the limit) 5.77 / 5.95, 4.53 / 5.10,
-//           5.84 / 5.97, 4.66 / 5.84; 160 tokens 6.69 / 6.46, 5.17 / 5.20, 6.71 / 6.02, 5.23 / 6.43
-//   N = 7   96 tokens 5.63 / 5.57, 4.37 / 4.84, 5.44 / 5.45, 4.44 / 5.58; 128 tokens 6.25 / 5.54, 4.86 / 4.81, 6.27 / 5.54,
-//           4.99 / 5.35: seven wavefronts leave one of a workgroup's SIMDs half empty
-//   N = 4   128 tokens 4.01 / 4.11, 3.31 / 3.63, 4.04 / 4.10, 3.36 / 4.00; 160 tokens 4.37 / 4.15, 3.54 / 3.65, 4.47 / 4.13,
-//           3.56 / 4.01
+//   N = 8   64 tokens 4.07 / 5.09, 3.82 / 4.72, 4.14 / 4.94, 3.86 / 4.93; 128 tokens (the limit) 6.55 / 6.72, 6.26 / 5.92,
+//           6.60 / 6.68, 6.29 / 6.83; 160 tokens 7.35 / 6.88, 6.96 / 6.29, 7.48 / 7.02, 6.99 / 6.95
+//   N = 7   96 tokens 5.65 / 6.06, 5.37 / 5.14, 5.62 / 5.99, 5.37 / 5.97; 128 tokens 6.72 / 6.30, 6.43 / 5.48, 6.76 / 6.30,
+//           6.38 / 6.16: seven wavefronts leave one of a workgroup's SIMDs half empty
+//   N = 4   128 tokens 4.19 / 4.87, 4.03 / 4.51, 4.25 / 5.01, 4.01 / 4.70; 160 tokens 4.88 / 5.04, 4.59 / 4.74, 4.90 / 5.18,
+//           4.62 / 4.96; 192 tokens 5.23 / 5.21, 4.95 / 4.98, 5.25 / 5.35, 4.98 / 5.12
 // Hence at most 2^20 elements per partial, and of seven partials at most 6 * 2^20 altogether.
 bool allreduce_small_applies(int n_src, int64_t n_elems, int group)
 {
