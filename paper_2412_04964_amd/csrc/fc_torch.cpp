@@ -415,13 +415,20 @@ PyObject *allreduce(PyObject *, PyObject *const *a, Py_ssize_t n_args)
     at::Tensor own, own_ws;
     const at::Tensor *y = result_tensor(out, t, h, *x, device, own);
     if (!y) return fallback();
-    if (!ws) {
+    const void *px = x->data_ptr();
+    void *py = y->data_ptr(), *stream = stream_of(device);
+    // Only the rotated call writes to its workspace.  The others want the address and size of one and leave it alone (fc.h): where
+    // the caller gives none, they get the result's address, and nothing is allocated (2 x 16 x 4096, result allocated: 4.6 -> 4.0 us).
+    void *pw = py;
+    size_t bytes = (size_t)need;
+    if (KIND == kRot && !ws) {
         own_ws = empty({need > 16 ? need : 16}, at::kByte, *x);
         ws = &own_ws;
     }
-    const void *px = x->data_ptr();
-    void *py = y->data_ptr(), *pw = ws->data_ptr(), *stream = stream_of(device);
-    const size_t bytes = (size_t)ws->numel();
+    if (ws) {
+        pw = ws->data_ptr();
+        bytes = (size_t)ws->numel();
+    }
     const int ns = (int)n, g = (int)group, b1 = (int)rs, b2 = (int)ag;
     int rc;
     const char *name;

@@ -244,6 +244,26 @@ def test_allocated_results_are_tensors_like_those_of_torch_empty(inference):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("name", ["allreduce_sim", "allreduce_sim_sym", "allreduce_sim_fp8", "allreduce_sim_cmeta", "allreduce_sim_rot"])
+@pytest.mark.parametrize("n,t,h,g", [(2, 3, 1024, 32), (1, 1, 2048, 1024), (3, 520, 4096, 2048), (8, 0, 1024, 128)])
+def test_all_reduce_without_a_workspace_allocates_its_result(name, n, t, h, g):
+    # the rotated call also a workspace; the result is the one with a workspace given
+    from paper_2412_04964_amd import binding as b
+    x = torch.randn(n, t, h, device="cuda").half()
+    args = (g,) if name.endswith("fp8") else (g, 4, 8)
+    need = b.allreduce_sim_workspace_bytes(n, t, h, g, *(args[1:] or (8, 8)))
+    space = torch.empty(max(need, 16), dtype=torch.uint8, device="cuda")
+    extra = (b.QUANTIZER_ASYM,) if name.endswith("rot") else ()
+    want = getattr(b, name)(x, *args, *extra, workspace=space)
+    allocated = lambda: torch.cuda.memory_stats()["allocated_bytes.all.allocated"]
+    before = allocated()
+    got = getattr(b._calls(), name)(x, *args, *extra, None, None)
+    new = allocated() - before
+    assert torch.equal(got.view(torch.int16), want.view(torch.int16))
+    assert (new > want.numel() * 2 + 511) == name.endswith("rot") or t == 0
+
+
+@pytest.mark.gpu
 def test_allocated_results_are_filled_where_torch_was_asked_to():
     # torch.use_deterministic_algorithms has torch.empty fill new memory.  The kernels overwrite every byte of it, so what shows
     # the fill is torch's own record of the operations that ran: one per result.
