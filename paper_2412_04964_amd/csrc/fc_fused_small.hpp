@@ -17,18 +17,38 @@ namespace fc {
 
 constexpr int fused_small_lane_elems(int bits_in) { return 32 / bits_in; }
 constexpr int fused_small_wave_elems(int bits_in) { return 64 * fused_small_lane_elems(bits_in); }
-// Up to this many wavefronts (eight per compute unit of the part) the asymmetric quantizer's launch is latency-bound and this kernel wins
-// (decode shape, N = 8 at 8 bit: 2.63 -> 2.14 us per launch under graph replay; the two forms cross between 2048
-// and 4096 wavefronts).  The other quantizers the same way (N = 8, hidden 8192, g = 128, bulk -> this one): symmetric 4 bit
-// 3.46 -> 2.29 us at 8 tokens, 3.79 -> 2.77 at 64, 3.95 -> 3.35 at 128 (the limit); compact metadata 3.64 -> 2.36, 3.88 -> 2.90,
-// 4.06 -> 3.71; FP8 2.67 -> 2.18 at 8 tokens, 3.16 -> 2.99 at 64 (its limit).
-constexpr int kFusedSmallMaxWaves = 2048;
+// Up to how many wavefronts of this kernel, in units of 1024 (one per SIMD of the part), a launch takes it rather than the
+// bulk kernel, whose wavefronts hold four times the elements: past that many the bulk kernel's shorter instruction stream per element
+// counts more than the number of wavefronts.  By lanes to a group and number of sources; us under graph replay, bulk / this one, at 2048,
+// 3072, 4096, 6144 wavefronts, hidden 4096:
+//   4 lanes (groups of 32 at 4 bit) and 16:
+//     asymmetric 4 -> 4 bit  N = 1 2.56 / 2.47, 2.77 / 2.91; N = 2 2.83 / 2.74, 3.24 / 3.04, 3.35 / 3.34; N = 3 3.38 / 2.88, 3.63 / 3.16,
+//       3.65 / 3.45, 3.98 / 4.10; N = 4 3.59 / 3.01, 3.88 / 3.36, 3.93 / 3.74, 4.33 / 4.46; N = 8 4.15 / 3.78, 5.22 / 4.39, 5.34 / 5.03, 5.84 /
+//       6.45; compact metadata and 4 -> 8 bit cross at the same places
+//     symmetric 4 -> 4 bit  N = 2 2.55 / 2.76, 3.15 / 3.08, 3.26 / 3.35; N = 3 3.07 / 2.74, 3.60 / 2.99, 3.67 / 3.26, 3.89 / 3.76; N = 4
+//       3.23 / 2.80, 3.94 / 3.06, 3.94 / 3.37, 4.27 / 3.91; N = 8 3.99 / 3.35, 5.10 / 3.97, 5.25 / 4.46, 5.72 / 5.29
+//     8 -> 8 bit, N = 3  asymmetric 2.94 / 2.69, 3.32 / 2.93, 3.41 / 3.18; symmetric 2.76 / 2.58, 3.03 / 2.83, 3.07 / 3.04; compact metadata
+//       2.78 / 2.88, 3.19 / 3.14, 3.25 / 3.38; FP8 2.74 / 2.58, 2.88 / 2.83, 2.95 / 3.04; N = 4  2.95 / 2.80, 3.35 / 3.08, 3.40 / 3.43; FP8 2.69 /
+//       2.58, 3.02 / 2.84, 3.09 / 3.05; N = 8  3.53 / 3.44, 4.14 / 3.96, 4.35 / 4.61; FP8 3.19 / 2.98, 3.69 / 3.46, 3.92 / 3.86
+//   32 and 64 lanes (groups of 128 and 256 at 8 bit, of 256 and 512 at 4 bit), the same order of entries:
+//     asymmetric 4 -> 4 bit  N = 2 2.78 / 2.81, 3.22 / 3.29; N = 3 3.27 / 3.07, 3.57 / 3.40, 3.62 / 3.68; N = 4 3.58 / 3.17, 3.86 / 3.50,
+//       3.95 / 3.85, 4.31 / 4.58; N = 8 4.06 / 3.79, 5.16 / 4.27, 5.30 / 4.85, 5.81 / 6.06; symmetric N = 4 3.24 / 2.92, 3.92 / 3.21, 3.92 / 3.51,
+//       4.27 / 4.07; N = 8 4.00 / 3.36, 5.07 / 3.84, 5.26 / 4.26, 5.64 / 5.13
+//     8 -> 8 bit  asymmetric N = 3 2.79 / 2.87; N = 4 2.97 / 2.94, 3.39 / 3.19, 3.41 / 3.46; N = 6 3.22 / 3.18, 3.73 / 3.51, 3.86 / 3.84; N = 8
+//       3.40 / 3.42, 4.07 / 3.81, 4.25 / 4.34; symmetric N = 6 3.14 / 2.88, 3.63 / 3.10, 3.75 / 3.40; FP8 N = 6 2.95 / 2.83, 3.31 / 3.06, 3.52 / 3.35;
+//       compact metadata N = 4 2.90 / 3.09, N = 6 3.21 / 3.04, 3.76 / 3.28, 3.84 / 3.62
+inline int fused_small_limit(int codec, int bits_in, int n_src, bool wide)
+{
+    if (codec == CODEC_SYM && bits_in == 4 && n_src >= (wide ? 4 : 3)) return 6;
+    if (wide) return n_src >= 6 ? 4 : n_src >= 4 && (bits_in == 4 || codec == CODEC_ASYM) ? 3 : n_src == 3 && bits_in == 4 ? 3 : 2;
+    return n_src >= 4 ? 4 : n_src == 3 ? (bits_in == 4 ? 4 : 3) : n_src == 2 && bits_in == 4 ? 3 : 2;
+}
 
 // The other quantizers' bulk kernels read less metadata.  With few sources, and groups of 32 lanes and more to reduce here, they are
 // the faster ones from fewer wavefronts on (hidden 2048, g = 256, 2048 wavefronts, bulk / this one: 8 -> 8 bit, N = 2, symmetric
 // 2.37 / 2.57 us, FP8 2.32 / 2.58, compact metadata 2.50 / 2.72; N = 4 2.72 / 2.83 with compact metadata; N = 2 at 4 bit
-// 2.53 / 2.72, 2.74 / 2.89; but g = 32, 8 -> 8 bit, N = 3, compact metadata 2.74 / 2.59).  The forms cross at about 448
-// wavefronts per source at 8 bit and twice that at 4 bit.  A volume of at most three workgroups of the bulk kernel starts sooner
+// 2.53 / 2.72, 2.74 / 2.89).  The forms cross at about 448
+// wavefronts per source at 8 bit, up to five sources, and twice that at 4 bit, up to two.  A volume of at most three workgroups of the bulk kernel starts sooner
 // there than as 24 of these (8 bit, one row of 4096, N = 1, FP8 2.24 / 2.40 us, symmetric 2.23 / 2.39; N = 3 2.27 / 2.37; compact
 // metadata N = 2 2.37 / 2.34; 6144: FP8 N = 3 2.28 / 2.39; 7168: 2.41 / 2.41); from four sources on its chain is too long.
 constexpr int kFusedSmallWavesPerSource = 448;
@@ -37,9 +57,10 @@ constexpr int kFusedSmallMinWaves = 24;
 inline bool fused_small_applies(int codec, int bits_in, int n_src, int64_t n_elems, int group)
 {
     const int64_t waves = (n_elems + fused_small_wave_elems(bits_in) - 1) / fused_small_wave_elems(bits_in);
-    if (group > fused_small_wave_elems(bits_in) || waves > kFusedSmallMaxWaves) return false;
+    const bool wide = group >= 32 * fused_small_lane_elems(bits_in);
+    if (group > fused_small_wave_elems(bits_in) || waves > fused_small_limit(codec, bits_in, n_src, wide) * 1024) return false;
     if (codec != CODEC_ASYM && bits_in == 8 && n_src <= (codec == CODEC_ASYMH ? 1 : 3) && waves <= kFusedSmallMinWaves) return false;
-    if (codec == CODEC_ASYM || group < 32 * fused_small_lane_elems(bits_in)) return true;
+    if (codec == CODEC_ASYM || !wide || n_src > (bits_in == 8 ? 5 : 2)) return true;
     return waves <= n_src * kFusedSmallWavesPerSource * (8 / bits_in);
 }
 
