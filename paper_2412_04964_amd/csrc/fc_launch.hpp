@@ -120,7 +120,7 @@ hipError_t launch_allreduce_small(int codec, int bits_rs, int bits_ag, const voi
 
 // fc_sim.hip (one translation unit per quantizer): the same in one launch for volumes that memory bandwidth bounds
 // (the N binary16 partials are read once, the binary16 result is written once, nothing else touches memory);
-// groups of at most 1024 elements, every quantizer.  fc_sim_wide.hip: the same for groups of 2048 to 16384.
+// groups of at most 1024 elements, every quantizer.  fc_sim_wide.hip: the same for groups of 1024 to 16384.
 constexpr int kFusedAllreduceMaxGroup = 1024;         // one wavefront's 64 lanes x 16 elements
 constexpr int kFusedAllreduceTileElems = 2048;        // one workgroup
 #define FC_DECLARE_SIM(name)                                                                                       \
@@ -130,11 +130,25 @@ constexpr int kFusedAllreduceTileElems = 2048;        // one workgroup
                                             int group, void *y_f16, hipStream_t stream);
 FC_DECLARE_SIM(asym) FC_DECLARE_SIM(sym) FC_DECLARE_SIM(fp8) FC_DECLARE_SIM(cmeta)
 #undef FC_DECLARE_SIM
+// Groups of 1024 fit both kernels: a wavefront of fc_sim.hip, or a workgroup of one wavefront of fc_sim_wide.hip, which works out Eq. 1 of all
+// sources in one evaluation and has all of them in flight.  That is the shorter chain for small volumes and fewer instructions per
+// element for the asymmetric quantizers; with six sources and more of 2 M elements it has too much in flight, and the max|x| of the others costs
+// the first kernel less.  us, fc_sim / fc_sim_wide, hidden 8192: INT4 N = 2 64 tokens 3.40 / 3.01, 400 5.61 / 5.29, 1000 10.11 / 10.50,
+// 2500 22.7 / 21.4, 8192 65.5 / 62.6; N = 4 8 tokens 3.99 / 3.14, 160 5.33 / 4.90, 400 8.13 / 7.82, 1000 15.9 / 15.7, 2500 36.9 / 35.1, 8192 105.7 /
+// 103.0; N = 8 8 tokens 5.75 / 4.19, 160 7.98 / 7.01, 260 9.90 / 9.81, 400 12.1 / 13.2; symmetric INT8 N = 2 400 tokens 4.96 / 5.29, N = 4
+// 8 tokens 3.66 / 2.99, 160 4.98 / 4.58, 400 7.63 / 7.72, 8192 103.5 / 103.6; FP8 N = 8 160 tokens 7.57 / 7.11, 400 11.8 / 13.3.
+inline bool allreduce_wide_applies(int codec, int n_src, int64_t n_elems, int group)
+{
+    constexpr int64_t k1M = (int64_t)1 << 20;
+    if (group != kFusedAllreduceMaxGroup) return group > kFusedAllreduceMaxGroup;
+    if (n_elems <= 3 * k1M / 2) return true;
+    return (codec == CODEC_ASYM || codec == CODEC_ASYMH) && n_src <= 4 && (n_elems <= 4 * k1M || n_elems >= 12 * k1M);
+}
 inline hipError_t launch_allreduce_fused(int codec, int bits_rs, int bits_ag, const void *x_f16, int n_src,
                                          int64_t n_elems, int group, void *y_f16, hipStream_t stream)
 {
     // volumes of up to 2^36 elements: at most 2^25 workgroups of either form
-    const bool wide = group > kFusedAllreduceMaxGroup;
+    const bool wide = allreduce_wide_applies(codec, n_src, n_elems, group);
 #define FC_SIM_CASE(CODEC, name)                                                                                     \
     case CODEC:                                                                                                      \
         return (wide ? launch_allreduce_wide_##name : launch_allreduce_fused_##name)(bits_rs, bits_ag, x_f16, n_src, \

@@ -1,11 +1,12 @@
-// fc_sim_wide.hip -- Algorithm 1 in ONE launch for groups wider than a wavefront's tile of fc_sim.hip: 2048 to 16384
-// elements, the coarse end of the paper's block-size study, up to one group per token (Section 3.2.1).
+// fc_sim_wide.hip -- Algorithm 1 in ONE launch for groups wider than a wavefront's tile of fc_sim.hip, 2048 to 16384
+// elements, the coarse end of the paper's block-size study, up to one group per token (Section 3.2.1); and for groups of one such tile
+// where it is the faster form (allreduce_wide_applies).
 //
 // What bounds it: HBM, 2 N + 2 bytes per output element as in fc_sim.hip; the arithmetic is the same, term by term
 // (see the exactness notes there), so the result is bit-identical to fc_quantize x N -> fc_dequant_reduce_requant ->
 // fc_dequantize.
 //
-// Decomposition: one workgroup of group / 16 threads (2 to 16 wavefronts) owns one group.  Because every lane belongs
+// Decomposition: one workgroup of group / 16 threads (1 to 16 wavefronts) owns one group.  Because every lane belongs
 // to the same group it does not matter which of the group's elements a lane holds: a lane takes two pieces of 8
 // elements, each one coalesced 128-bit access, straight into registers and back, and nothing is staged in LDS.  All N
 // partials of the group stay in registers (8 N words per lane) between their min / max and their codes, so the

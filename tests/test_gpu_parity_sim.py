@@ -338,3 +338,22 @@ def test_volumes_where_the_form_changes(fc, name, n_src, group, limit):
         y = torch.full((tokens, hidden), 7.0, dtype=torch.float16, device="cuda")
         getattr(fc, "allreduce_sim" + sfx)(base[:, at], group, *(() if name == "fp8" else bits), out=y)
         assert torch.equal(y.view(torch.int16), want[at]), "%s N=%d g=%d %d rows" % (name, n_src, group, tokens)
+
+
+@pytest.mark.parametrize("name", ["asym", "sym", "fp8", "cmeta"])
+@pytest.mark.parametrize("n_src", [1, 2, 4, 5, 8])
+def test_groups_of_1024_in_both_forms(fc, name, n_src):
+    # a wavefront's tile, or a workgroup of one wavefront: by volume (3 * 2^19, 4 * 2^20 and 12 * 2^20 elements), quantizer and fan-in
+    hidden, rows = 3072, 13
+    x = synth_inputs.make_partials_stress(n_src, rows, hidden, n_src % synth_inputs.STRESS_KINDS, seed=n_src)
+    ref = oracle.allreduce_sim if name == "asym" else variant(fc, name)[1]
+    sfx = "" if name == "asym" else "_" + name
+    base = dev16(x)
+    for bits in bit_pairs(name):
+        want = dev16(ref(x, 1024, *bits)).view(torch.int16)
+        for tokens in (1, 2, 512, 513, 1365, 1366, 4096):
+            at = torch.arange(tokens, device="cuda") % rows
+            y = torch.full((tokens + 2, hidden), 7.0, dtype=torch.float16, device="cuda")
+            getattr(fc, "allreduce_sim" + sfx)(base[:, at], 1024, *(() if name == "fp8" else bits), out=y[1:-1])
+            assert torch.equal(y[1:-1].view(torch.int16), want[at]), "%s N=%d %d rows" % (name, n_src, tokens)
+            assert (y[0] == 7.0).all() and (y[-1] == 7.0).all(), "write outside the output"
