@@ -383,3 +383,25 @@ def test_value_distributions_end_to_end(fc, kind):
             got = got.cpu().numpy()
             assert same_bits(got.view(np.uint16), want.view(np.uint16)), "%s %s: %s" % (
                 what, name, first_diff(got.view(np.uint16), want.view(np.uint16)))
+
+
+@pytest.mark.parametrize("variant", ["asym", "sym", "cmeta"])
+@pytest.mark.parametrize("group", [32, 128, 1024])
+def test_codecs_where_a_launch_limits_its_wavefronts(fc, variant, group):
+    # 4-bit codes from 36 * 2^20 elements on; rows do not depend on each other: a few of them over and over
+    hidden, rows = 4096, 23
+    sfx = "" if variant == "asym" else "_" + variant
+    x = synth_inputs.make_partials(1, rows, hidden, seed=group, outlier_frac=0.01)[0]
+    coded = getattr(oracle, "quantize" + sfx)(x, group, 4)
+    back = getattr(oracle, "dequantize" + sfx)(*coded, hidden, group, 4)
+    xd = torch.from_numpy(x.view(np.uint16)).cuda().view(torch.float16)
+    want = [torch.from_numpy(np.ascontiguousarray(a).view(np.uint8)).cuda() for a in coded]
+    want_y = torch.from_numpy(back.view(np.int16)).cuda()
+    for tokens in (36 * 256 - 1, 36 * 256, 36 * 256 + 1):
+        at = torch.arange(tokens, device="cuda") % rows
+        got = getattr(fc, "quantize" + sfx)(xd[at], group, 4)
+        for g, w in zip(got, want):
+            assert torch.equal(g.view(torch.uint8), w[at]), "%s g=%d %d rows" % (variant, group, tokens)
+        y = torch.full((tokens + 2, hidden), 7.0, dtype=torch.float16, device="cuda")
+        getattr(fc, "dequantize" + sfx)(*got, hidden, group, 4, out=y[1:-1])
+        assert torch.equal(y[1:-1].view(torch.int16), want_y[at]) and (y[0] == 7.0).all() and (y[-1] == 7.0).all()
