@@ -196,7 +196,11 @@ __global__ __launch_bounds__(64 * rot_group_waves(LB)) __attribute__((amdgpu_wav
         if (LB >= 12 && j > 0) lds_barrier();                          // every wavefront has taken the last exchange
         rot_forward<LB, SWAPS, FP8, 1, kOrder>(v, L, pieces, wave);
         float mx, s, inv, zf;
-        rot_params<CODEC, LB, SWAPS>(v, L, group_shift, wave, mm, rs, fwd, mx, s, inv, zf);
+        int shift = group_shift;
+        // its comparisons stay scalar and in the loop: hoisted, they come back through vector registers (us, before / so: two partials of one token of 4096 6.59 / 6.44,
+        // of 100 x 8192 8.29 / 8.18, eight of 4096 x 6144 105.8 / 103.8, four of 8192 x 8192 1 % at most)
+        asm volatile("" : "+s"(shift));
+        rot_params<CODEC, LB, SWAPS>(v, L, shift, wave, mm, rs, fwd, mx, s, inv, zf);
         if (j + 1 < n_src) fetch(j + 1);
         rot_codes<CODEC>(v, L, mx, inv, zf, rs);
         rot_accumulate<0>(v, s, acc);
