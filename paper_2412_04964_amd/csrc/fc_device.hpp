@@ -54,8 +54,6 @@ constexpr int block_elems(int bits) { return kBlockThreads * lane_elems(bits); }
 // 4-in/1-out copy, up to 3 % on the 8-bit fused kernel).  256-lane groups need 256 threads, the span
 // over which the kernel reduces a group across wavefronts.
 constexpr int fused_block_threads(int lpg) { return (lpg > 0 && lpg <= 128) ? 128 : kBlockThreads; }
-// The stand-alone 4-bit quantizer gains the same way (1.8 %); the 8-bit one and the dequantizer do not.
-constexpr int quantize_block_threads(int bits, int lpg) { return (bits == 4 && lpg > 0) ? 128 : kBlockThreads; }
 
 typedef uint32_t u32;
 typedef u32 u32x2 __attribute__((ext_vector_type(2)));
@@ -1091,15 +1089,13 @@ __device__ __forceinline__ void accumulate_general(const u32 (&w)[4], float s, f
 // bytes are fetched as coalesced 1 KB pieces straight into LDS (an image of
 // global memory) and each lane then reads its EPL contiguous values from there.
 // CODEC selects the quantizer (`zeros` is used by kAsym only; with kAsymH `scales`
-// is the array of 32-bit metadata words).
-template <int BITS, int LPG, int CODEC>
-__global__ __launch_bounds__(quantize_block_threads(BITS, LPG)) void k_quantize(
+// is the array of 32-bit metadata words).  EPL and BT: see quantize_form.
+template <int BITS, int LPG, int CODEC, int EPL, int BT>
+__global__ __launch_bounds__(BT) void k_quantize(
     const uint16_t *__restrict__ x, int64_t n_elems, int lpg, int group_shift,
     uint8_t *__restrict__ codes, float *__restrict__ scales, float *__restrict__ zeros)
 {
-    constexpr int EPL = lane_elems(BITS);
     constexpr int kPieces = EPL * 2 / 16;                       // 1 KB pieces per wavefront
-    constexpr int BT = quantize_block_threads(BITS, LPG);
     __shared__ __attribute__((aligned(16))) uint8_t img[BT / 64][kPieces * 1024];
 
     const u32 tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
@@ -1137,7 +1133,7 @@ __global__ __launch_bounds__(quantize_block_threads(BITS, LPG)) void k_quantize(
         quantize_lane_sym<BITS, EPL, LPG>(v, lpg, word, s);
     else
         quantize_lane<BITS, EPL, LPG, CODEC == kAsymH>(v, lpg, word, s, zf);
-    store_codes<16>(word, rc, wave, lane, nullptr);
+    store_codes<EPL * BITS / 8>(word, rc, wave, lane, nullptr);
     const int lpg_v = LPG > 0 ? LPG : lpg;
     if ((tid & (lpg_v - 1)) == 0) {
         const u32 gi = (tid * EPL) >> group_shift;
