@@ -93,31 +93,37 @@ hipError_t launch_quantize(int bits, int codec, const void *x_f16, int64_t n_ele
     return launch_q_bits<8>(codec, stream, x, n_elems, group, c, scales, zeros);
 }
 
+// 4-bit codes: up to one round of wavefronts 16 elements per lane, for the reason given at quantize_form; above it 32 elements, whose
+// loads and stores are twice as wide.  us by elements (2^20), hidden 8192, 32 / 16 elements: group 32  1/4: 2.11 / 1.92   2: 2.76 / 2.67   6: 4.16 / 4.00
+// 8: 4.91 / 4.79   12: 6.41 / 6.96   32: 15.4 / 16.2;   group 128  1/4: 2.11 / 1.92   1: 2.39 / 2.22   6: 4.09 / 3.92   8: 4.79 / 4.65   12: 6.03 / 6.90.
+// Workgroups of 64 or 128 threads: from -2 to +25 %.  8-bit codes with 8 elements per lane: 1/4 M 1.94 / 1.87, 2 M 2.77 / 2.88, 8 M 5.28 / 6.58.
+template <int BITS, int EPL>
+static hipError_t launch_dq(int codec, hipStream_t stream, const uint8_t *c, const float *scales, const float *zeros, int64_t n_elems,
+                            int group_shift, uint16_t *y)
+{
+    constexpr int64_t tile = (int64_t)kBlockThreads * EPL;
+    const dim3 grid((unsigned)((n_elems + tile - 1) / tile)), block(kBlockThreads);
+    const size_t pad = limits_wavefronts(BITS, n_elems) ? lds_to_limit(6, (size_t)tile * 2) : 0;
+    if (codec == CODEC_ASYM)
+        return launch_kernel_lds(k_dequantize<BITS, kAsym, EPL>, grid, block, pad, stream, c, scales, zeros, n_elems, group_shift, y);
+    if (codec == CODEC_SYM)
+        return launch_kernel_lds(k_dequantize<BITS, kSym, EPL>, grid, block, pad, stream, c, scales, nullptr, n_elems, group_shift, y);
+    if (codec == CODEC_ASYMH)
+        return launch_kernel_lds(k_dequantize<BITS, kAsymH, EPL>, grid, block, pad, stream, c, scales, nullptr, n_elems, group_shift, y);
+    if constexpr (BITS == 8)
+        return launch_kernel_lds(k_dequantize<8, kFp8, EPL>, grid, block, pad, stream, c, scales, nullptr, n_elems, group_shift, y);
+    return hipErrorInvalidValue;
+}
+
 hipError_t launch_dequantize(int bits, int codec, const void *codes, const float *scales, const float *zeros,
                              int64_t n_elems, int group, void *y_f16, hipStream_t stream)
 {
     const uint8_t *c = static_cast<const uint8_t *>(codes);
     uint16_t *y = static_cast<uint16_t *>(y_f16);
     const int sh = log2_int(group);
-    const int64_t tile = block_elems(bits);
-    const dim3 grid((unsigned)((n_elems + tile - 1) / tile)), block(kBlockThreads);
-    const size_t pad = limits_wavefronts(bits, n_elems) ? lds_to_limit(6, (size_t)tile * 2) : 0;
-    if (codec == CODEC_FP8) {
-        if (bits != 8) return hipErrorInvalidValue;
-        return launch_kernel_lds(k_dequantize<8, kFp8>, grid, block, pad, stream, c, scales, nullptr, n_elems, sh, y);
-    } else if (codec == CODEC_ASYMH) {
-        if (bits == 4)
-            return launch_kernel_lds(k_dequantize<4, kAsymH>, grid, block, pad, stream, c, scales, nullptr, n_elems, sh, y);
-        else
-            return launch_kernel_lds(k_dequantize<8, kAsymH>, grid, block, pad, stream, c, scales, nullptr, n_elems, sh, y);
-    } else if (bits == 4 && codec == CODEC_ASYM)
-        return launch_kernel_lds(k_dequantize<4, kAsym>, grid, block, pad, stream, c, scales, zeros, n_elems, sh, y);
-    else if (bits == 4)
-        return launch_kernel_lds(k_dequantize<4, kSym>, grid, block, pad, stream, c, scales, nullptr, n_elems, sh, y);
-    else if (codec == CODEC_ASYM)
-        return launch_kernel_lds(k_dequantize<8, kAsym>, grid, block, pad, stream, c, scales, zeros, n_elems, sh, y);
-    else
-        return launch_kernel_lds(k_dequantize<8, kSym>, grid, block, pad, stream, c, scales, nullptr, n_elems, sh, y);
+    if (bits == 8) return launch_dq<8, 16>(codec, stream, c, scales, zeros, n_elems, sh, y);
+    if (n_elems <= kOneRound) return launch_dq<4, 16>(codec, stream, c, scales, zeros, n_elems, sh, y);
+    return launch_dq<4, 32>(codec, stream, c, scales, zeros, n_elems, sh, y);
 }
 
 }  // namespace fc

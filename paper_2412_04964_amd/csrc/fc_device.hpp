@@ -764,11 +764,12 @@ __device__ __forceinline__ void quantize_lane_fp8_any(const float (&v)[EPL], int
     pack_lane_fp8<EPL>(v, inv, word);
 }
 
-// d[e] = value of the e-th E4M3 byte of the lane's 128 bits
-__device__ __forceinline__ void decode_fp8(const u32 (&w)[4], float (&d)[16])
+// d[e] = value of the e-th E4M3 byte of the lane's W words
+template <int W>
+__device__ __forceinline__ void decode_fp8(const u32 (&w)[W], float (&d)[4 * W])
 {
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
+    for (int k = 0; k < W; ++k) {
         const f32x2 lo = __builtin_amdgcn_cvt_pk_f32_fp8((int)w[k], false);
         const f32x2 hi = __builtin_amdgcn_cvt_pk_f32_fp8((int)w[k], true);
         d[4 * k + 0] = lo.x;
@@ -922,14 +923,14 @@ __device__ __forceinline__ void bytes_minus_zero(u32 w, const ZeroConst &c, h2 (
     p[1] = as_h2(__builtin_amdgcn_perm(0x64006400u, w, 0x05030501u)) - c.c1024;   // (b1, b3)
 }
 
-// d[e] = q_e - z (as fp32) for the lane's 128 bits of codes
-template <int BITS>
-__device__ __forceinline__ void codes_minus_zero_fast(const u32 (&w)[4], const ZeroConst &c,
-                                                      float (&d)[128 / BITS])
+// d[e] = q_e - z (as fp32) for the lane's W words of codes
+template <int BITS, int W>
+__device__ __forceinline__ void codes_minus_zero_fast(const u32 (&w)[W], const ZeroConst &c,
+                                                      float (&d)[32 / BITS * W])
 {
     if constexpr (BITS == 4) {
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
+        for (int k = 0; k < W; ++k) {
             h2 p[4];
             nibbles_minus_zero(w[k], c, p);
 #pragma unroll
@@ -940,7 +941,7 @@ __device__ __forceinline__ void codes_minus_zero_fast(const u32 (&w)[4], const Z
         }
     } else {
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
+        for (int k = 0; k < W; ++k) {
             h2 p[2];
             bytes_minus_zero(w[k], c, p);
             d[4 * k + 0] = (float)p[0].x;
@@ -982,14 +983,14 @@ __device__ __forceinline__ void scaled_differences_fast(const u32 (&w)[4], const
     }
 }
 
-template <int BITS>
-__device__ __forceinline__ void codes_minus_zero_general(const u32 (&w)[4], float zf,
-                                                         float (&d)[128 / BITS])
+template <int BITS, int W>
+__device__ __forceinline__ void codes_minus_zero_general(const u32 (&w)[W], float zf,
+                                                         float (&d)[32 / BITS * W])
 {
     constexpr int per_word = 32 / BITS;
     constexpr u32 mask = (1u << BITS) - 1u;
 #pragma unroll
-    for (int k = 0; k < 4; ++k)
+    for (int k = 0; k < W; ++k)
 #pragma unroll
         for (int i = 0; i < per_word; ++i)
             d[per_word * k + i] = (float)((w[k] >> (BITS * i)) & mask) - zf;
@@ -1457,17 +1458,17 @@ __global__ __launch_bounds__(fused_block_threads(LPG)) void k_dequant_reduce_req
 // With kAsymH `scales` is the array of 32-bit metadata words.
 // One tile of 256*EPL elements per workgroup; the EPL halves of a lane are laid
 // out in the wavefront's LDS image and leave as coalesced 1 KB pieces.
-template <int BITS, int CODEC>
+template <int BITS, int CODEC, int EPL>
 __global__ __launch_bounds__(kBlockThreads) void k_dequantize(
     const uint8_t *__restrict__ codes, const float *__restrict__ scales,
     const float *__restrict__ zeros, int64_t n_elems, int group_shift, uint16_t *__restrict__ y)
 {
-    constexpr int EPL = lane_elems(BITS);
     constexpr int kPieces = EPL * 2 / 16;
+    constexpr int W = EPL * BITS / 32;                          // words of codes per lane
     __shared__ __attribute__((aligned(16))) uint8_t img[kBlockWaves][kPieces * 1024];
 
     const u32 tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
-    const int64_t e_tile = (int64_t)blockIdx.x * block_elems(BITS);
+    const int64_t e_tile = (int64_t)blockIdx.x * (kBlockThreads * EPL);
     const int64_t g_tile = e_tile >> group_shift;
     const int64_t n_groups = n_elems >> group_shift;
     const u32 gi = (tid * EPL) >> group_shift;
@@ -1478,15 +1479,24 @@ __global__ __launch_bounds__(kBlockThreads) void k_dequantize(
 
     const float s_raw = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, gi * 4, 0, 0));
     float s = s_raw;
-    const u32x4 a = __builtin_amdgcn_raw_buffer_load_b128(rc, tid * 16, 0, kStreamLoadPolicy);
+    u32 w[W];
+    if constexpr (W == 4) {
+        const u32x4 a = __builtin_amdgcn_raw_buffer_load_b128(rc, tid * 16, 0, kStreamLoadPolicy);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) w[i] = a[i];
+    } else {
+        static_assert(W == 2, "8 or 16 code bytes per lane");
+        const u32x2 a = __builtin_amdgcn_raw_buffer_load_b64(rc, tid * 8, 0, kStreamLoadPolicy);
+        w[0] = a[0];
+        w[1] = a[1];
+    }
 
     float d[EPL];
     if constexpr (CODEC == kFp8) {
-        const u32 w[4] = {a[0], a[1], a[2], a[3]};
         decode_fp8(w, d);
     } else if constexpr (CODEC == kSym) {
-        const u32 w[4] = {to_offset_binary<BITS>(a[0]), to_offset_binary<BITS>(a[1]),
-                          to_offset_binary<BITS>(a[2]), to_offset_binary<BITS>(a[3])};
+#pragma unroll
+        for (int i = 0; i < W; ++i) w[i] = to_offset_binary<BITS>(w[i]);
         codes_minus_zero_fast<BITS>(w, sym_zero_const<BITS>(), d);
     } else {
         float zf;
@@ -1494,7 +1504,6 @@ __global__ __launch_bounds__(kBlockThreads) void k_dequantize(
             unpack_meta(__builtin_bit_cast(u32, s_raw), s, zf);
         else
             zf = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rz, gi * 4, 0, 0));
-        const u32 w[4] = {a[0], a[1], a[2], a[3]};
         const bool wave_fast = __builtin_amdgcn_ballot_w64(!zero_is_fast(zf)) == 0;
         if (wave_fast)
             codes_minus_zero_fast<BITS>(w, unpack_zero_const(pack_zero_const(zf)), d);

@@ -409,10 +409,10 @@ def test_codecs_where_a_launch_limits_its_wavefronts(fc, variant, group):
 
 @pytest.mark.parametrize("variant", ["asym", "sym", "cmeta", "fp8"])
 @pytest.mark.parametrize("bits, group, limits", [
-    (4, 32, (3 << 20, 8 << 20)), (4, 64, (8 << 20,)), (4, 128, (3 << 20, 8 << 20)), (4, 256, (24 << 20,)), (4, 1024, (24 << 20,)),
-    (4, 2048, (24 << 20,)), (8, 32, (5 << 19,)), (8, 64, (5 << 19,)), (8, 128, (5 << 19,))])
-def test_quantizer_on_both_sides_of_every_limit(fc, variant, bits, group, limits):
-    # the quantizer's tile follows volume and group: the same rows over and over, of a length that leaves ragged tiles
+    (4, 32, (3 << 20, 8 << 20)), (4, 64, (8 << 20,)), (4, 128, (3 << 20, 8 << 20)), (4, 256, (24 << 20,)), (4, 1024, (8 << 20, 24 << 20)),
+    (4, 2048, (8 << 20, 24 << 20)), (8, 32, (5 << 19,)), (8, 64, (5 << 19,)), (8, 128, (5 << 19,))])
+def test_codecs_on_both_sides_of_every_limit(fc, variant, bits, group, limits):
+    # the tiles of quantizer and dequantizer follow volume and group: the same rows over and over, of a length that leaves ragged tiles
     if variant == "fp8" and bits != 8:
         pytest.skip("FP8 codes have 8 bits")
     hidden, rows = 31 * group, 37
@@ -422,9 +422,14 @@ def test_quantizer_on_both_sides_of_every_limit(fc, variant, bits, group, limits
     coded = getattr(oracle, "quantize" + sfx)(x, group, *width)
     xd = torch.from_numpy(x.view(np.uint16)).cuda().view(torch.float16)
     want = [torch.from_numpy(np.ascontiguousarray(a).view(np.uint8)).cuda() for a in coded]
+    back = getattr(oracle, "dequantize" + sfx)(*coded, hidden, group, *width)
+    want_y = torch.from_numpy(back.view(np.int16)).cuda()
     for limit in limits:
         for tokens in (limit // hidden, limit // hidden + 1):
             at = torch.arange(tokens, device="cuda") % rows
             got = getattr(fc, "quantize" + sfx)(xd[at], group, *width)
             for g, w in zip(got, want):
                 assert torch.equal(g.view(torch.uint8), w[at]), "%s %d bits g=%d %d rows" % (variant, bits, group, tokens)
+            y = torch.full((tokens + 2, hidden), 7.0, dtype=torch.float16, device="cuda")
+            getattr(fc, "dequantize" + sfx)(*got, hidden, group, *width, out=y[1:-1])
+            assert torch.equal(y[1:-1].view(torch.int16), want_y[at]) and (y[0] == 7.0).all() and (y[-1] == 7.0).all()
