@@ -310,6 +310,7 @@ int three_steps(bool rotate, int codec, const void *x_f16, int n_src, int64_t to
 // more (one group per token, 8 x 1 x 8192 20.3 -> 11.4, 5 x 7 x 4096 12.7 -> 10.7, FP8 4 x 5 x 8192 14.3 -> 12.4), except
 // three sources of FP8 in blocks of 8192 (11.5 / 12.1).  In blocks of 1024 the steps would win as much (8 x 1 x 5120 14.8 / 10.4), but
 // that call leaves the caller's workspace alone, which the tests hold it to.
+// Small volumes of the one launch have their sources side by side by now (rot_spread_applies), which is not in these figures.
 bool rot_steps_apply(int codec, int n_src, int64_t n_elems, int64_t hidden, int group)
 {
     //                                           n_src 3  4   5   6   7   8

@@ -123,26 +123,61 @@ __device__ __forceinline__ u32 after_loads(u32 lane)
     return lane;
 }
 
+// SPREAD: a wavefront's dequantized codes and scales, from the part that has a source to the one that sums.  Runs of 1 KB; the lanes keep their places.
+constexpr int kRotHandBytes = 8 * 1024 + 256;
+constexpr int rot_part_bytes(int lb) { return rot_block_waves(lb) * (kRotHandBytes + kRotSlots * 8); }
+__device__ __forceinline__ void rot_hand_over(const float (&d)[4][8], float s, uint8_t *to, u32 lane)
+{
+#pragma unroll
+    for (int k = 0; k < 8; ++k)
+        *reinterpret_cast<u32x4 *>(to + k * 1024 + lane * 16) =
+            u32x4{__builtin_bit_cast(u32, d[k / 2][4 * (k & 1)]), __builtin_bit_cast(u32, d[k / 2][4 * (k & 1) + 1]),
+                  __builtin_bit_cast(u32, d[k / 2][4 * (k & 1) + 2]), __builtin_bit_cast(u32, d[k / 2][4 * (k & 1) + 3])};
+    *reinterpret_cast<float *>(to + 8 * 1024 + lane * 4) = s;
+}
+__device__ __forceinline__ void rot_take_over(const uint8_t *from, u32 lane, float (&d)[4][8], float &s)
+{
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+        const u32x4 a = *reinterpret_cast<const u32x4 *>(from + k * 1024 + lane * 16);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const u32 w = a[i];            // (a bit_cast applied to the vector element itself reads element 0)
+            d[k / 2][4 * (k & 1) + i] = __builtin_bit_cast(float, w);
+        }
+    }
+    s = *reinterpret_cast<const float *>(from + 8 * 1024 + lane * 4);
+}
+
 // ALONE: no wavefront shares its SIMD (launches of at most one workgroup per compute unit), so nothing is raised above another, and blocks
-// of 8192 take the layout with the shorter chain (rot_swaps_apply).  us, the other form / this, two partials, group 128: INT4 one
+// of 8192 take the layout with the shorter chain (rot_swaps_apply).  us, the other form / this, two partials one after the other, group 128: INT4 one
 // token of 8192 7.41 / 7.25, 200 tokens 8.95 / 8.86, sym INT8 7.24 / 7.03, 8.74 / 8.66, FP8 8.40 / 8.32; FP8 in blocks of 4096 one token
 // 7.87 / 7.72, 256 tokens 8.98 / 8.81.  Integer codes in blocks of 4096 and all shorter blocks are as fast without it; past the
 // limit it loses at once (257 x 4096 8.40 / 9.17).
-template <int CODEC, bool ALONE, int LB>
-__global__ __launch_bounds__(64 * rot_group_waves(LB)) __attribute__((amdgpu_waves_per_eu(4))) void k_allreduce_rot(
+// SPREAD: the form for volumes that leave the chip idle.  One source after the other is a chain of 1.1 to 2 us each; here the workgroup
+// has several times the wavefronts of a block, each such part works on a source of its own, and the first one sums what the others hand over
+// through LDS, in source order as ever, and goes on alone.  For rot_spread_applies.
+template <int CODEC, bool ALONE, int LB, bool SPREAD>
+__global__ __launch_bounds__(SPREAD ? 1024 : 64 * rot_group_waves(LB)) __attribute__((amdgpu_waves_per_eu(4))) void k_allreduce_rot(
     const uint16_t *__restrict__ x, int64_t n_elems, int n_src, int group_shift, RotLevels rs, RotLevels ag,
     uint16_t *__restrict__ y)
 {
     constexpr bool FP8 = CODEC == kFp8, SWAPS = FP8 || ALONE;           // see rot_swaps_apply
     constexpr RotOrder kOrder = ALONE ? kFlat : LB >= 12 ? kPinned : kRaised;
-    constexpr int kWaves = rot_group_waves(LB);
+    constexpr int kWaves = SPREAD ? rot_block_waves(LB) : rot_group_waves(LB);
     constexpr int kTile = 2048 * kWaves;
     constexpr int kChunk = (512 * 1024) / (kTile * 2);                  // 512 KB of every partial per XCD and run
-    __shared__ __attribute__((aligned(16))) uint8_t pieces[rot_exchange_bytes(LB, 1)];
-    __shared__ float mm[kWaves][kRotSlots][2];
+    extern __shared__ __attribute__((aligned(16))) uint8_t parts[];     // SPREAD: rot_part_bytes for every source of a round
+    __shared__ __attribute__((aligned(16))) uint8_t own[SPREAD ? 16 : rot_exchange_bytes(LB, 1)];
+    __shared__ float own_mm[SPREAD ? 1 : kWaves][kRotSlots][2];
 
     const u32 tid = threadIdx.x, lane = tid & 63u;
-    const u32 wave = (u32)__builtin_amdgcn_readfirstlane((int)(tid >> 6));
+    const u32 wave_all = (u32)__builtin_amdgcn_readfirstlane((int)(tid >> 6));
+    const u32 wave = SPREAD ? wave_all % (u32)kWaves : wave_all;        // of the block
+    const u32 part = SPREAD ? wave_all / (u32)kWaves : 0u;
+    const int n_parts = SPREAD ? (int)(blockDim.x / (64u * kWaves)) : 1;
+    uint8_t *pieces = SPREAD ? parts + part * rot_part_bytes(LB) : own;
+    float (*mm)[kRotSlots][2] = SPREAD ? reinterpret_cast<float (*)[kRotSlots][2]>(pieces + kWaves * kRotHandBytes) : own_mm;
     const u32 tile = xcd_tile<kChunk>((u32)((n_elems + kTile - 1) / kTile));
     const int64_t e_tile = (int64_t)tile * kTile;
     const int64_t e_begin = rot_begin<LB>(e_tile, wave);
@@ -163,7 +198,7 @@ __global__ __launch_bounds__(64 * rot_group_waves(LB)) __attribute__((amdgpu_wav
     constexpr float fwd = 1.0f / (float)(1 << ((LB + 1) / 2));          // 2^-ceil(n/2), n = LB
     constexpr float back = 1.0f / (float)(1 << (LB / 2));               // 2^-floor(n/2)
 
-    fetch(0);
+    fetch((int)part);                                                  // n_parts <= n_src
     const RotLane L = rot_lane<FP8, rot_forward_framed(LB, SWAPS)>(after_loads<ALONE && LB == 13>(lane));
     float acc[4][8];
 #pragma unroll
@@ -193,7 +228,7 @@ __global__ __launch_bounds__(64 * rot_group_waves(LB)) __attribute__((amdgpu_wav
             rot_register_stage<2>(v);
             rot_register_stage<4>(v);
         }
-        if (LB >= 12 && j > 0) lds_barrier();                          // every wavefront has taken the last exchange
+        if ((LB >= 12 || SPREAD) && j > 0) lds_barrier();              // every wavefront has taken the last exchange
         rot_forward<LB, SWAPS, FP8, 1, kOrder>(v, L, pieces, wave);
         float mx, s, inv, zf;
         int shift = group_shift;
@@ -201,13 +236,35 @@ __global__ __launch_bounds__(64 * rot_group_waves(LB)) __attribute__((amdgpu_wav
         // of 100 x 8192 8.29 / 8.18, eight of 4096 x 6144 105.8 / 103.8, four of 8192 x 8192 1 % at most)
         asm volatile("" : "+s"(shift));
         rot_params<CODEC, LB, SWAPS>(v, L, shift, wave, mm, rs, fwd, mx, s, inv, zf);
-        if (j + 1 < n_src) fetch(j + 1);
+        if constexpr (SPREAD) {
+            const int next = j + n_parts + (int)part;                  // a part without a source repeats the last one; nothing takes it
+            if (j + n_parts < n_src) fetch(next < n_src ? next : n_src - 1);
+        } else {
+            if (j + 1 < n_src) fetch(j + 1);
+        }
         rot_codes<CODEC>(v, L, mx, inv, zf, rs);
-        rot_accumulate<0>(v, s, acc);
-        rot_accumulate<1>(v, s, acc);
-        rot_accumulate<2>(v, s, acc);
-        rot_accumulate<3>(v, s, acc);
-    } while (++j < n_src);
+        if (!SPREAD || part == 0) {
+            rot_accumulate<0>(v, s, acc);
+            rot_accumulate<1>(v, s, acc);
+            rot_accumulate<2>(v, s, acc);
+            rot_accumulate<3>(v, s, acc);
+        }
+        if constexpr (SPREAD) {
+            if (LB >= 12) lds_barrier();                               // every wavefront has taken the exchange
+            if (part != 0) rot_hand_over(v, s, pieces + wave * kRotHandBytes, lane);
+            lds_barrier();
+            if (part == 0)
+                for (int k = 1; k < n_parts && j + k < n_src; ++k) {
+                    rot_take_over(parts + k * rot_part_bytes(LB) + wave * kRotHandBytes, lane, v, s);
+                    rot_accumulate<0>(v, s, acc);
+                    rot_accumulate<1>(v, s, acc);
+                    rot_accumulate<2>(v, s, acc);
+                    rot_accumulate<3>(v, s, acc);
+                }
+        }
+        j += n_parts;
+    } while (j < n_src);
+    if (SPREAD && part != 0) return;                                   // a barrier waits for the wavefronts that are left
 
     float mx, s, inv, zf;
     if (LB >= 12) lds_barrier();
@@ -268,16 +325,52 @@ RotLevels levels(int codec, int bits)
     return RotLevels{q, 1.0f / q};
 }
 
+// Sources that a workgroup of SPREAD works on at once: 1024 threads at most, and rot_part_bytes each in 160 KB
+constexpr int rot_parts(int lb, int n_src)
+{
+    const int most = lb == 13 ? 4 : 8;
+    return n_src < most ? n_src : most;
+}
+
+// Up to 2^21 elements, and no more than one round of workgroups (16 wavefronts of 128 registers per compute unit), where the steps of
+// rot_steps_apply do not go first.  us under graph replay by elements (2^20), one source after the other / side by side, group 128:
+//   INT4, block 2048: N = 2  1/4: 6.49 / 5.28   1: 6.80 / 6.40   2: 8.74 / 7.78   3: 9.00 / 9.59;   N = 3  1/4: 7.88 / 5.31   1: 8.41 / 6.69
+//     2: 10.20 / 8.94   3: 10.47 / 10.89;   N = 5  1.5: 13.53 / 11.64   2 (two rounds): 13.70 / 14.35;   block 1024, group 1024, N = 4
+//     1/4: 9.36 / 5.33   1: 9.86 / 7.01   2: 11.17 / 9.36   2.25: 11.20 / 11.32
+//   INT4, block 4096: N = 2  1/4: 7.14 / 5.80   1: 7.56 / 6.46   2: 9.24 / 8.62   3: 9.76 / 11.02;   N = 3  1/4: 8.67 / 6.87   2: 10.85 / 10.65
+//   INT4, block 8192: N = 2  1/4: 7.63 / 7.05   2: 9.00 / 8.39   2.25: 9.32 / 10.03 (INT8);   N = 3  1/4: 9.81 / 8.53   2: 11.07 / 9.71;   N = 4  1: 12.46 /
+//     10.09   2: 13.17 / 10.98;   N = 5  1.5: 15.18 / 15.19   2: 15.44 / 15.66;   N = 7  1.5: 19.48 / 15.80;   N = 8  2: 21.82 / 16.91
+//   FP8, N = 2: block 2048  1/4: 7.01 / 5.52   2: 9.45 / 8.03;   block 4096  1/4: 7.71 / 6.18   2: 10.58 / 9.43;   block 8192  1/4: 8.35 / 7.57   2: 9.90 / 9.02
+//   A single source: 5.03 / 5.09, 5.57 / 5.61.
+inline bool rot_spread_applies(int lb, int n_src, int64_t n_elems)
+{
+    if (n_src < 2 || n_elems > (int64_t)1 << 21) return false;
+    const int waves = rot_block_waves(lb), at_once = 256 * (16 / (waves * rot_parts(lb, n_src)));
+    return n_elems <= (int64_t)at_once * waves * 2048;
+}
+
+template <int CODEC, int LB>
+hipError_t launch_spread(const uint16_t *x, int n_src, int64_t n_elems, int group, RotLevels rs, RotLevels ag, uint16_t *y,
+                         hipStream_t stream)
+{
+    constexpr int kWaves = rot_block_waves(LB), kTile = 2048 * kWaves;
+    const int parts = rot_parts(LB, n_src);
+    return launch_kernel_lds(k_allreduce_rot<CODEC, true, LB, true>, dim3((unsigned)((n_elems + kTile - 1) / kTile)),
+                             dim3(64 * kWaves * parts), (size_t)rot_part_bytes(LB) * parts, stream, x, n_elems, n_src,
+                             log2_int(group), rs, ag, y);
+}
+
 template <int CODEC, int LB>
 hipError_t launch_one(const uint16_t *x, int n_src, int64_t n_elems, int group, RotLevels rs, RotLevels ag, uint16_t *y,
                       hipStream_t stream)
 {
     constexpr int kTile = 2048 * rot_group_waves(LB);
+    if (rot_spread_applies(LB, n_src, n_elems)) return launch_spread<CODEC, LB>(x, n_src, n_elems, group, rs, ag, y, stream);
     const dim3 grid((unsigned)((n_elems + kTile - 1) / kTile)), block(64 * rot_group_waves(LB));
-    if constexpr (LB == 13 || (LB == 12 && CODEC == kFp8))              // see k_allreduce_rot
+    if constexpr (LB == 13 || (LB == 12 && CODEC == kFp8))              // see k_allreduce_rot; a single source, the others go side by side
         if (n_elems <= 256 * (int64_t)kTile)
-            return launch_kernel(k_allreduce_rot<CODEC, true, LB>, grid, block, stream, x, n_elems, n_src, log2_int(group), rs, ag, y);
-    return launch_kernel(k_allreduce_rot<CODEC, false, LB>, grid, block, stream, x, n_elems, n_src, log2_int(group), rs, ag, y);
+            return launch_kernel(k_allreduce_rot<CODEC, true, LB, false>, grid, block, stream, x, n_elems, n_src, log2_int(group), rs, ag, y);
+    return launch_kernel(k_allreduce_rot<CODEC, false, LB, false>, grid, block, stream, x, n_elems, n_src, log2_int(group), rs, ag, y);
 }
 
 template <int CODEC>
