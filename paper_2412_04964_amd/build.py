@@ -46,7 +46,7 @@ FLAGS = [
 
 # (source, object suffix, extra defines)
 UNITS = [("fc_api.hip", "api", []), ("fc_codec.hip", "codec", []), ("fc_wide.hip", "wide", []),
-         ("fc_rot.hip", "rot", []), ("fc_rot_rows.hip", "rot_rows", []), ("fc_rot_sim.hip", "rot_sim", []),
+         ("fc_rot.hip", "rot", []), ("fc_rot_rows.hip", "rot_rows", []), ("fc_rot_fine.hip", "rot_fine", []), ("fc_rot_sim.hip", "rot_sim", []),
          ("fc_small.hip", "small", [])]
 for _c in range(4):      # one unit per quantizer: asymmetric, symmetric, FP8, asymmetric with binary16 metadata
     UNITS.append(("fc_sim.hip", "sim_%d" % _c, ["-DFC_SIM_CODEC=%d" % _c]))

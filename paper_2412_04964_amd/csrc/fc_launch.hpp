@@ -102,9 +102,16 @@ hipError_t launch_quantize_rot(int bits, int codec, const void *x_f16, int64_t t
 hipError_t launch_dequantize_rot(int bits, int codec, const void *codes, const float *scales, const float *zeros,
                                  int64_t tokens, int hidden, int group, void *y_f16, hipStream_t stream);
 
-// fc_rot_rows.hip: the same for launch-bound volumes, blocks of 1024, 2048 and 4096 (2^log_b).
-hipError_t launch_quantize_rot_rows(int bits, int codec, const void *x_f16, int64_t n_elems, int log_b, int group,
+// fc_rot_fine.hip: the same for launch-bound volumes.
+hipError_t launch_quantize_rot_fine(int bits, int codec, const void *x_f16, int64_t n_elems, int log_b, int group,
                                     void *codes, float *scales, float *zeros, hipStream_t stream);
+hipError_t launch_dequantize_rot_fine(int bits, int codec, const void *codes, const float *scales, const float *zeros,
+                                      int64_t n_elems, int log_b, int group, void *y_f16, hipStream_t stream);
+
+// fc_rot_rows.hip: the same for volumes between those and a full chip, blocks of 1024, 2048 and 4096 (2^log_b); the quantizer for FP8, the
+// dequantizer at 4 bit in blocks of 1024 only.
+hipError_t launch_quantize_rot_rows(const void *x_f16, int64_t n_elems, int log_b, int group, void *codes, float *scales,
+                                    hipStream_t stream);
 hipError_t launch_dequantize_rot_rows(int bits, int codec, const void *codes, const float *scales, const float *zeros,
                                       int64_t n_elems, int log_b, int group, void *y_f16, hipStream_t stream);
 // fc_rot_sim.hip: the whole rotated all-reduce in one launch, every group and fan-in.

@@ -1,0 +1,274 @@
+// fc_rot_fine.hip -- the rotated quantizer and dequantizer for launch-bound volumes: 8 elements per lane.
+//
+// The same arithmetic as fc_rot.hip (butterflies in the order of the spans, so bit-identical), split finer: a wavefront there
+// works through 2048 elements as one chain of dependent instructions, here through 512.  A lane holds 8 consecutive elements (bits 0-2 in
+// registers, 3-8 in the lanes), a workgroup one block; the bits of the wavefronts go through LDS, two at a time.
+//
+// What bounds it: latency, of the launch (1.6 us), of one load, of the chain of some 250 instructions and of one barrier or two; past one
+// wavefront per SIMD (2^19 elements) the instructions themselves, of which there are more per element than in the other forms.  us per launch
+// under graph replay, group 128, the other forms (fc_rot.hip, fc_rot_rows.hip) / this one (rot_fine_applies says where it is taken):
+//   quantize, INT4, blocks of 1024: 10 K elements 3.07 / 2.34; 1/2 M 3.25 / 2.74; 1 M 3.76 / 3.09; 2 M 4.09 / 3.92; 2.5 M 4.53 / 4.71
+//     2048: 3.02 / 2.46; 1 M 3.79 / 3.32; 2 M 4.38 / 4.15; 2.5 M 4.55 / 4.66.   4096: 3.21 / 2.76; 1 M 3.98 / 3.44; 2 M 4.51 / 4.36; 2.5 M 4.72 / 5.05
+//     8192, group 64: 3.43 / 3.61; 1 M 4.27 / 4.35.   One group per block of 4096, symmetric: 3.29 / 2.95; 2 M 4.57 / 4.37
+//   INT8, blocks of 1024: 2.79 / 2.36; 1 M 3.69 / 3.13; 2 M 4.21 / 4.09.   2048: 1 M 3.68 / 3.27; 2.5 M 4.68 / 4.72.   FP8, 1024: 2.77 / 2.33; 1 M 3.57 /
+//     3.07; 2 M 4.13 / 3.97.   8192: 3.67 / 3.54; 1 M 4.44 / 4.27; 2 M 4.77 / 4.76; 2.5 M 5.48 / 5.98
+//   dequantize, INT4, blocks of 1024: 2.77 / 2.20; 1/2 M 2.89 / 2.49; 1 M 3.09 / 2.82; 1.5 M 3.27 / 3.50.   2048: 3.04 / 2.22; 1 M 3.11 / 2.92; 2 M 3.97 /
+//     3.72; 2.5 M 3.85 / 4.20.   4096: 3.09 / 2.45; 1 M 3.46 / 2.97; 2 M 4.26 / 3.90.   8192, group 64: 3.39 / 3.16; 1 M 3.75 / 3.72; 2 M 4.09 / 4.19
+//   INT8, blocks of 1024: 2.51 / 2.19; 1 M 3.07 / 2.95; 2 M 3.75 / 3.77.   FP8, 4096: 2.66 / 2.43; 1 M 3.25 / 3.18; 2 M 3.97 / 4.08
+// The frames of fc_rot.hip save an instruction per value and stage between lanes: equal up to 1 M elements, 2 M 3.83 for 3.92.
+#include "fc_rot_wave.hpp"
+#include "fc_launch.hpp"
+
+namespace fc {
+
+constexpr int fine_waves(int lb) { return 1 << (lb - 9); }
+// an exchange holds 32 bytes of every lane; blocks of 4096 and 8192 take two in turn
+constexpr int fine_exchanges(int lb) { return lb > 11 ? 2 : 1; }
+
+// Stages 7 and 8: lanes 16 and 32 apart.  After the swap of a value with itself a holds what the lower lanes have, b the upper ones'
+template <int LANE_BIT>
+__device__ __forceinline__ void fine_swap_stage(float (&v)[8], float s)
+{
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        u32 a = __builtin_bit_cast(u32, v[i]), b = a;
+        swap_lane_bit<LANE_BIT>(a, b);
+        v[i] = fmaf(__builtin_bit_cast(float, b), s, __builtin_bit_cast(float, a));
+    }
+}
+
+__device__ __forceinline__ void fine_put(const float (&v)[8], uint8_t *at)
+{
+    *reinterpret_cast<u32x4 *>(at) = u32x4{__builtin_bit_cast(u32, v[0]), __builtin_bit_cast(u32, v[1]), __builtin_bit_cast(u32, v[2]),
+                                           __builtin_bit_cast(u32, v[3])};
+    *reinterpret_cast<u32x4 *>(at + 1024) = u32x4{__builtin_bit_cast(u32, v[4]), __builtin_bit_cast(u32, v[5]), __builtin_bit_cast(u32, v[6]),
+                                                  __builtin_bit_cast(u32, v[7])};
+}
+__device__ __forceinline__ void fine_get(const uint8_t *at, float (&v)[8])
+{
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        const u32x4 a = *reinterpret_cast<const u32x4 *>(at + k * 1024);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const u32 w = a[i];            // (a bit_cast applied to the vector element itself reads element 0)
+            v[4 * k + i] = __builtin_bit_cast(float, w);
+        }
+    }
+}
+
+// Stages of wavefront bits B0 and (NB = 2) B0 + 1: every wavefront forms its own results from the values of two or four
+template <int B0, int NB>
+__device__ __forceinline__ void fine_wave_stages(float (&v)[8], uint8_t *lds, u32 wave, u32 lane)
+{
+    const float s0 = (wave >> B0) & 1u ? -1.0f : 1.0f;
+    fine_put(v, lds + wave * 2048 + lane * 16);
+    lds_barrier();
+    float a[8];
+    fine_get(lds + (wave ^ (1u << B0)) * 2048 + lane * 16, a);
+    if constexpr (NB == 1) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) v[i] = fmaf(v[i], s0, a[i]);
+    } else {
+        const float s1 = (wave >> (B0 + 1)) & 1u ? -1.0f : 1.0f;
+        float b[8], c[8];
+        fine_get(lds + (wave ^ (2u << B0)) * 2048 + lane * 16, b);
+        fine_get(lds + (wave ^ (3u << B0)) * 2048 + lane * 16, c);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) v[i] = fmaf(fmaf(v[i], s0, a[i]), s1, fmaf(b[i], s0, c[i]));
+    }
+}
+
+// Stages S0 ... LB-1 of the transform of the block.  Every stage multiplies by +1 or -1 and adds, so zeros have the contract's signs
+// (the frames of fc_rot.hip would need its literal form besides)
+template <int LB, int S0>
+__device__ __forceinline__ void fine_transform(float (&v)[8], const RotLane &L, uint8_t *lds, u32 wave)
+{
+    if constexpr (S0 == 0) rot_register_stage<1>(v);
+    rot_register_stage<2>(v);
+    rot_register_stage<4>(v);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) v[i] = fmaf(v[i], L.s[0], dpp_read<kDppQuadXor1>(v[i]));
+#pragma unroll
+    for (int i = 0; i < 8; ++i) v[i] = fmaf(v[i], L.s[1], dpp_read<kDppQuadXor2>(v[i]));
+#pragma unroll
+    for (int i = 0; i < 8; ++i) v[i] = fmaf(v[i], L.s[2], dpp_read<kDppRowHalfMirror>(v[i]));
+#pragma unroll
+    for (int i = 0; i < 8; ++i) v[i] = fmaf(v[i], L.s[3], dpp_read<kDppRowRor8>(v[i]));
+    fine_swap_stage<4>(v, L.s[4]);
+    fine_swap_stage<5>(v, L.lane & 32u ? -1.0f : 1.0f);
+    if constexpr (LB == 10) fine_wave_stages<0, 1>(v, lds, wave, L.lane);
+    else fine_wave_stages<0, 2>(v, lds, wave, L.lane);
+    if constexpr (LB == 12) fine_wave_stages<2, 1>(v, lds + fine_waves(LB) * 2048, wave, L.lane);
+    if constexpr (LB == 13) fine_wave_stages<2, 2>(v, lds + fine_waves(LB) * 2048, wave, L.lane);
+}
+
+// Rotate a block and quantize it.  lpg: lanes per group
+template <int BITS, int CODEC, int LB>
+__global__ __launch_bounds__(64 * fine_waves(LB)) void k_quantize_rot_fine(
+    const uint16_t *__restrict__ x, int lpg, int group_shift, uint8_t *__restrict__ codes, float *__restrict__ scales,
+    float *__restrict__ zeros)
+{
+    constexpr bool FP8 = CODEC == kFp8;
+    __shared__ __attribute__((aligned(16))) uint8_t lds[fine_exchanges(LB) * fine_waves(LB) * 2048];
+    __shared__ float slot[fine_waves(LB)][2];
+    const u32 tid = threadIdx.x, lane = tid & 63u;
+    const u32 wave = (u32)__builtin_amdgcn_readfirstlane((int)(tid >> 6));
+    const int64_t e0 = (int64_t)blockIdx.x << LB;
+    const RotLane L = rot_lane<true>(lane);
+    const u32 at = wave * 64 + L.pos;                                  // of the lane's 8 elements
+    const u32x4 raw = *reinterpret_cast<const u32x4 *>(x + e0 + at * 8);
+    float v[8];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) first_stage(raw[i], v[2 * i], v[2 * i + 1]);
+    fine_transform<LB, 1>(v, L, lds, wave);
+
+    // the forward scaling goes into the group's min and max and its reciprocal (see k_quantize_rot)
+    constexpr float fwd = 1.0f / (float)(1 << ((LB + 1) / 2));
+    float mn, mx, s, inv, zf = 0.0f;
+    lane_minmax(v, mn, mx);
+    group_minmax<0>(mn, mx, lpg);
+    if (lpg > 64) cross_wave_minmax(mn, mx, slot, wave, lane, (u32)lpg >> 6);
+
+    u32 word[BITS / 4];
+    const float mn_s = mn * fwd, mx_s = mx * fwd;
+    if constexpr (FP8) {
+        group_params_absmax<448>(fmaxf(fabsf(mn_s), fabsf(mx_s)), s, inv);
+        pack_lane_fp8<8>(v, inv * fwd, word);
+    } else if constexpr (CODEC == kSym) {
+        group_params_sym<BITS>(fmaxf(fabsf(mn_s), fabsf(mx_s)), s, inv);
+        pack_lane_sym<BITS, 8>(v, inv * fwd, word);
+    } else {
+        group_params<BITS>(mn_s, mx_s, s, inv, zf);
+        pack_lane<BITS, 8>(v, inv * fwd, zf, mx, word);
+    }
+    uint8_t *to = codes + (e0 + at * 8) * BITS / 8;
+    if constexpr (BITS == 4) *reinterpret_cast<u32 *>(to) = word[0];
+    else *reinterpret_cast<u32x2 *>(to) = u32x2{word[0], word[1]};
+    if ((tid & (u32)(lpg - 1)) == 0) {
+        const int64_t gi = (e0 + tid * 8) >> group_shift;
+        scales[gi] = s;
+        if constexpr (CODEC == kAsym) zeros[gi] = zf;
+    }
+}
+
+// Dequantize a block and rotate it back
+template <int BITS, int CODEC, int LB>
+__global__ __launch_bounds__(64 * fine_waves(LB)) void k_dequantize_rot_fine(
+    const uint8_t *__restrict__ codes, const float *__restrict__ scales, const float *__restrict__ zeros, int group_shift,
+    uint16_t *__restrict__ y)
+{
+    constexpr int W = BITS / 4;
+    __shared__ __attribute__((aligned(16))) uint8_t lds[fine_exchanges(LB) * fine_waves(LB) * 2048];
+    const u32 tid = threadIdx.x, lane = tid & 63u;
+    const u32 wave = (u32)__builtin_amdgcn_readfirstlane((int)(tid >> 6));
+    const int64_t e0 = (int64_t)blockIdx.x << LB;
+    const RotLane L = rot_lane<true>(lane);
+    const u32 at = wave * 64 + L.pos;
+    const int64_t gi = (e0 + tid * 8) >> group_shift;
+    const float s = scales[gi];
+    u32 w[W];
+    const uint8_t *from = codes + (e0 + at * 8) * BITS / 8;
+    if constexpr (BITS == 4) w[0] = *reinterpret_cast<const u32 *>(from);
+    else {
+        const u32x2 a = *reinterpret_cast<const u32x2 *>(from);
+        w[0] = a[0];
+        w[1] = a[1];
+    }
+    float v[8];
+    if constexpr (CODEC == kFp8) {
+        decode_fp8(w, v);
+    } else if constexpr (CODEC == kSym) {
+#pragma unroll
+        for (int i = 0; i < W; ++i) w[i] = to_offset_binary<BITS>(w[i]);
+        codes_minus_zero_fast<BITS>(w, sym_zero_const<BITS>(), v);
+    } else {
+        codes_minus_zero_general<BITS>(w, zeros[gi], v);
+    }
+#pragma unroll
+    for (int i = 0; i < 8; ++i) v[i] *= s;
+    fine_transform<LB, 0>(v, L, lds, wave);
+
+    constexpr float back = 1.0f / (float)(1 << (LB / 2));              // 2^-floor(n/2), n = LB
+    u32x4 out;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) out[i] = round_pair(v[2 * i] * back, v[2 * i + 1] * back);
+    *reinterpret_cast<u32x4 *>(y + e0 + at * 8) = out;
+}
+
+namespace {
+
+template <int BITS, int CODEC, int LB>
+hipError_t quantize_one(const uint16_t *x, int64_t n_elems, int group, uint8_t *c, float *scales, float *zeros, hipStream_t stream)
+{
+    return launch_kernel(k_quantize_rot_fine<BITS, CODEC, LB>, dim3((unsigned)(n_elems >> LB)), dim3(64 * fine_waves(LB)), stream, x,
+                         group / 8, log2_int(group), c, scales, zeros);
+}
+
+template <int BITS, int CODEC, int LB>
+hipError_t dequantize_one(const uint8_t *c, const float *scales, const float *zeros, int64_t n_elems, int group, uint16_t *y,
+                          hipStream_t stream)
+{
+    return launch_kernel(k_dequantize_rot_fine<BITS, CODEC, LB>, dim3((unsigned)(n_elems >> LB)), dim3(64 * fine_waves(LB)), stream, c,
+                         scales, zeros, log2_int(group), y);
+}
+
+template <int BITS, int CODEC>
+hipError_t quantize_block(int log_b, const uint16_t *x, int64_t n_elems, int group, uint8_t *c, float *scales, float *zeros,
+                          hipStream_t stream)
+{
+    switch (log_b) {
+    case 10: return quantize_one<BITS, CODEC, 10>(x, n_elems, group, c, scales, zeros, stream);
+    case 11: return quantize_one<BITS, CODEC, 11>(x, n_elems, group, c, scales, zeros, stream);
+    case 12: return quantize_one<BITS, CODEC, 12>(x, n_elems, group, c, scales, zeros, stream);
+    case 13:
+        if constexpr (CODEC == kFp8) return quantize_one<BITS, CODEC, 13>(x, n_elems, group, c, scales, zeros, stream);
+        return hipErrorInvalidValue;       // integer codes: the form of fc_rot.hip at every volume
+    default: return hipErrorInvalidValue;
+    }
+}
+
+template <int BITS, int CODEC>
+hipError_t dequantize_block(int log_b, const uint8_t *c, const float *scales, const float *zeros, int64_t n_elems, int group,
+                            uint16_t *y, hipStream_t stream)
+{
+    switch (log_b) {
+    case 10: return dequantize_one<BITS, CODEC, 10>(c, scales, zeros, n_elems, group, y, stream);
+    case 11: return dequantize_one<BITS, CODEC, 11>(c, scales, zeros, n_elems, group, y, stream);
+    case 12: return dequantize_one<BITS, CODEC, 12>(c, scales, zeros, n_elems, group, y, stream);
+    case 13: return dequantize_one<BITS, CODEC, 13>(c, scales, zeros, n_elems, group, y, stream);
+    default: return hipErrorInvalidValue;
+    }
+}
+
+}  // namespace
+
+hipError_t launch_quantize_rot_fine(int bits, int codec, const void *x_f16, int64_t n_elems, int log_b, int group, void *codes,
+                                    float *scales, float *zeros, hipStream_t stream)
+{
+    const uint16_t *x = static_cast<const uint16_t *>(x_f16);
+    uint8_t *c = static_cast<uint8_t *>(codes);
+    if (codec == CODEC_FP8)
+        return bits == 8 ? quantize_block<8, kFp8>(log_b, x, n_elems, group, c, scales, nullptr, stream) : hipErrorInvalidValue;
+    if (bits == 4)
+        return codec == CODEC_ASYM ? quantize_block<4, kAsym>(log_b, x, n_elems, group, c, scales, zeros, stream)
+                                   : quantize_block<4, kSym>(log_b, x, n_elems, group, c, scales, nullptr, stream);
+    return codec == CODEC_ASYM ? quantize_block<8, kAsym>(log_b, x, n_elems, group, c, scales, zeros, stream)
+                               : quantize_block<8, kSym>(log_b, x, n_elems, group, c, scales, nullptr, stream);
+}
+
+hipError_t launch_dequantize_rot_fine(int bits, int codec, const void *codes, const float *scales, const float *zeros, int64_t n_elems,
+                                      int log_b, int group, void *y_f16, hipStream_t stream)
+{
+    const uint8_t *c = static_cast<const uint8_t *>(codes);
+    uint16_t *y = static_cast<uint16_t *>(y_f16);
+    if (codec == CODEC_FP8)
+        return bits == 8 ? dequantize_block<8, kFp8>(log_b, c, scales, nullptr, n_elems, group, y, stream) : hipErrorInvalidValue;
+    if (bits == 4)
+        return codec == CODEC_ASYM ? dequantize_block<4, kAsym>(log_b, c, scales, zeros, n_elems, group, y, stream)
+                                   : dequantize_block<4, kSym>(log_b, c, scales, nullptr, n_elems, group, y, stream);
+    return codec == CODEC_ASYM ? dequantize_block<8, kAsym>(log_b, c, scales, zeros, n_elems, group, y, stream)
+                               : dequantize_block<8, kSym>(log_b, c, scales, nullptr, n_elems, group, y, stream);
+}
+
+}  // namespace fc

@@ -1,4 +1,5 @@
-// fc_rot_rows.hip -- the rotated quantizer and dequantizer for launch-bound volumes: the row in LDS.
+// fc_rot_rows.hip -- the rotated quantizer (FP8) and dequantizer between the launch-bound volumes of fc_rot_fine.hip and those that fill the
+// chip: the row in LDS.
 //
 // The same arithmetic as fc_rot.hip (butterflies in the order of the spans, so bit-identical), split the other way: a lane
 // holds one 128-bit word of codes, 32 elements at 4 bit and 16 at 8 bit, as in the plain kernels, transforms these, and then the row lies
@@ -6,19 +7,15 @@
 // between phases.  More LDS traffic than the register form of fc_rot.hip, which wins once the chip is full, but shorter
 // chains of dependent instructions: a wavefront of that form works through 2048 elements, here 1024 at 8 bit.
 //
-// What bounds it: latency of one wavefront.  us per launch under graph replay, this / register form, group 128, quantize and
-// dequantize (rot_rows_apply says where each is taken):
-//   8 bit, blocks of 1024: 1 M elements 3.51 / 3.57, 3.08 / 3.20; 2 M 4.02 / 4.17, 3.62 / 3.85; 2.5 M 4.38 / 4.33, 3.95 / 3.93;
-//     8 M 8.00 / 6.76, 7.23 / 5.78.  FP8: 1 M 3.37 / 3.81, 2.98 / 3.47; 3 M 4.67 / 4.79, 4.21 / 4.19; 4 M 5.22 / 5.11, 4.81 / 4.37.
-//   8 bit, blocks of 2048: 2 M 4.06 / 4.42, 3.65 / 3.94; 3 M 4.82 / 4.77, 4.39 / 4.11.  FP8: 3 M 4.70 / 4.99, 4.24 / 4.28; 4 M
-//     5.25 / 5.33, 4.81 / 4.48; 5 M 5.89 / 5.83, 5.43 / 4.99.
-//   8 bit, blocks of 4096: 2 M 4.45 / 4.52, 3.89 / 4.43; 3 M 5.13 / 4.91, 4.53 / 4.75; 4 M 5.78 / 5.24, 5.17 / 5.01.  FP8: 3 M
-//     5.02 / 5.39, 4.46 / 4.82; 4 M 5.67 / 5.79, 5.10 / 5.11; 5 M 6.30 / 6.20, 5.69 / 5.49.
-//   4 bit, blocks of 1024: 64 K 2.88 / 2.89, 2.49 / 2.55; 1 M 3.61 / 3.55, 3.08 / 3.06; 2 M 3.99 / 4.13, 3.50 / 3.69; 2.5 M 4.37 / 4.32,
-//     3.95 / 3.74; 8 M 6.95 / 6.60, 6.05 / 5.57; 16 M 11.41 / 10.24, 11.01 / 9.94; 8192 x 5120 24.2 / 22.6.
-//   4 bit, blocks of 2048: 1 M 3.83 / 3.61, 3.33 / 3.14; 1.5 M 4.08 / 4.22, 3.59 / 3.75; 2.5 M 4.77 / 4.53, 4.29 / 3.85.
-//   4 bit, blocks of 4096, dequantize: 64 K 2.93 / 3.07; 2 M 4.19 / 4.26; 3 M 4.60 / 4.56; 4 M 5.09 / 4.89.
-//   Blocks of 8192: the register form at every volume.
+// What bounds it: latency of one wavefront.  us per launch under graph replay, this / register form, group 128
+// (rot_rows_apply says where each is taken):
+//   quantize FP8, blocks of 1024: 3 M 4.67 / 4.79; 4 M 5.22 / 5.11; 2048: 3 M 4.70 / 4.99; 4 M 5.25 / 5.33; 5 M 5.89 / 5.83; 4096: 3 M
+//     5.02 / 5.39; 4 M 5.67 / 5.79; 5 M 6.30 / 6.20.
+//   dequantize, blocks of 1024: 8 bit 1 M elements 3.08 / 3.20; 2 M 3.62 / 3.85; 2.5 M 3.95 / 3.93; 8 M 7.23 / 5.78; FP8 1 M 2.98 / 3.47;
+//     3 M 4.21 / 4.19; 4 M 4.81 / 4.37; 4 bit 1 M 3.08 / 3.06; 2 M 3.50 / 3.69; 2.5 M 3.95 / 3.74; 8 M 6.05 / 5.57; 16 M 11.01 / 9.94.
+//   2048: 8 bit 2 M 3.65 / 3.94; 3 M 4.39 / 4.11; FP8 3 M 4.24 / 4.28; 4 M 4.81 / 4.48.
+//   4096: 8 bit 2 M 3.89 / 4.43; 3 M 4.53 / 4.75; 4 M 5.17 / 5.01; FP8 3 M 4.46 / 4.82; 4 M 5.10 / 5.11; 5 M 5.69 / 5.49.
+//   Blocks of 8192: the register form.
 #include "fc_rot_wave.hpp"
 #include "fc_launch.hpp"
 
@@ -125,14 +122,14 @@ __device__ __forceinline__ void hadamard_row(float (&v)[NE], float *row, u32 tid
     }
 }
 
-// Rotate one row block by block and quantize it (FinegrainedQuantize of Algorithm 1 on the rotated values).
+// Rotate one row block by block and quantize it to FP8 (FinegrainedQuantize of Algorithm 1 on the rotated values).
 // n_elems: elements of the whole tensor (a multiple of 2^LB; the last row may be a partial one when LB < LOGH:
 // lanes beyond the end read zeros and have their stores dropped or skipped).
-template <int BITS, int CODEC, int LOGH, int LB>
-__global__ __launch_bounds__((RowShape<BITS, LOGH>::T)) void k_quantize_rot_rows(
-    const uint16_t *__restrict__ x, int64_t n_elems, int lpg, int group_shift, uint8_t *__restrict__ codes,
-    float *__restrict__ scales, float *__restrict__ zeros)
+template <int LOGH, int LB>
+__global__ __launch_bounds__((RowShape<8, LOGH>::T)) void k_quantize_rot_rows(
+    const uint16_t *__restrict__ x, int64_t n_elems, int lpg, int group_shift, uint8_t *__restrict__ codes, float *__restrict__ scales)
 {
+    constexpr int BITS = 8;
     using S = RowShape<BITS, LOGH>;
     constexpr int EPL = S::EPL, kPieces = S::kPieces;
     __shared__ __attribute__((aligned(16))) uint8_t lds[S::kLdsBytes];
@@ -164,28 +161,17 @@ __global__ __launch_bounds__((RowShape<BITS, LOGH>::T)) void k_quantize_rot_rows
     hadamard_row<BITS, LOGH, LB, 1>(v, row, tid);
     // the forward scaling goes into the group's min and max and its reciprocal (see k_quantize_rot)
     constexpr float fwd = 1.0f / (float)(1 << ((LB + 1) / 2));
-    float mn, mx, s, inv, zf = 0.0f;
+    float mn, mx, s, inv;
     lane_minmax(v, mn, mx);
     group_minmax<0>(mn, mx, lpg);
     if (lpg > 64) cross_wave_minmax(mn, mx, slot, wave, lane, (u32)lpg >> 6);
 
     u32 word[4];
-    const float mn_s = mn * fwd, mx_s = mx * fwd;
-    if constexpr (CODEC == kFp8) {
-        group_params_absmax<448>(fmaxf(fabsf(mn_s), fabsf(mx_s)), s, inv);
-        pack_lane_fp8<EPL>(v, inv * fwd, word);
-    } else if constexpr (CODEC == kSym) {
-        group_params_sym<BITS>(fmaxf(fabsf(mn_s), fabsf(mx_s)), s, inv);
-        pack_lane_sym<BITS, EPL>(v, inv * fwd, word);
-    } else {
-        group_params<BITS>(mn_s, mx_s, s, inv, zf);
-        pack_lane<BITS, EPL>(v, inv * fwd, zf, mx, word);
-    }
+    group_params_absmax<448>(fmaxf(fabsf(mn * fwd), fabsf(mx * fwd)), s, inv);
+    pack_lane_fp8<EPL>(v, inv * fwd, word);
     __builtin_amdgcn_raw_buffer_store_b128(u32x4{word[0], word[1], word[2], word[3]}, rc, tid * 16, 0, kStreamStorePolicy);
     if ((tid & (u32)(lpg - 1)) == 0 && (int64_t)(tid * EPL) < here) {
-        const int64_t gi = (e0 >> group_shift) + ((tid * EPL) >> group_shift);
-        scales[gi] = s;
-        if constexpr (CODEC == kAsym) zeros[gi] = zf;
+        scales[(e0 >> group_shift) + ((tid * EPL) >> group_shift)] = s;
     }
 }
 
@@ -260,13 +246,12 @@ __global__ __launch_bounds__((RowShape<BITS, LOGH>::T)) void k_dequantize_rot_ro
 
 namespace {
 
-template <int BITS, int CODEC, int LOGH, int LB>
-hipError_t quantize_one(const uint16_t *x, int64_t n_elems, int group, uint8_t *c, float *scales, float *zeros,
-                        hipStream_t stream)
+template <int LOGH, int LB>
+hipError_t quantize_one(const uint16_t *x, int64_t n_elems, int group, uint8_t *c, float *scales, hipStream_t stream)
 {
     const unsigned grid = (unsigned)((n_elems + ((int64_t)1 << LOGH) - 1) >> LOGH);
-    return launch_kernel(k_quantize_rot_rows<BITS, CODEC, LOGH, LB>, dim3(grid), dim3(RowShape<BITS, LOGH>::T), stream, x,
-                         n_elems, group / lane_elems(BITS), log2_int(group), c, scales, zeros);
+    return launch_kernel(k_quantize_rot_rows<LOGH, LB>, dim3(grid), dim3(RowShape<8, LOGH>::T), stream, x, n_elems,
+                         group / lane_elems(8), log2_int(group), c, scales);
 }
 
 template <int BITS, int CODEC, int LOGH, int LB>
@@ -280,46 +265,30 @@ hipError_t dequantize_one(const uint8_t *c, const float *scales, const float *ze
 
 // blocks of 1024 go two to a row
 template <int BITS, int CODEC>
-hipError_t quantize_block(int log_b, const uint16_t *x, int64_t n_elems, int group, uint8_t *c, float *scales,
-                          float *zeros, hipStream_t stream)
-{
-    switch (log_b) {
-    case 10: return quantize_one<BITS, CODEC, 11, 10>(x, n_elems, group, c, scales, zeros, stream);
-    case 11: return quantize_one<BITS, CODEC, 11, 11>(x, n_elems, group, c, scales, zeros, stream);
-    case 12:
-        if constexpr (BITS == 8) return quantize_one<BITS, CODEC, 12, 12>(x, n_elems, group, c, scales, zeros, stream);
-        else return hipErrorInvalidValue;  // the register form at every volume
-    default: return hipErrorInvalidValue;
-    }
-}
-
-template <int BITS, int CODEC>
 hipError_t dequantize_block(int log_b, const uint8_t *c, const float *scales, const float *zeros, int64_t n_elems,
                             int group, uint16_t *y, hipStream_t stream)
 {
-    switch (log_b) {
-    case 10: return dequantize_one<BITS, CODEC, 11, 10>(c, scales, zeros, n_elems, group, y, stream);
-    case 11: return dequantize_one<BITS, CODEC, 11, 11>(c, scales, zeros, n_elems, group, y, stream);
-    case 12: return dequantize_one<BITS, CODEC, 12, 12>(c, scales, zeros, n_elems, group, y, stream);
-    default: return hipErrorInvalidValue;
+    if (log_b == 10) return dequantize_one<BITS, CODEC, 11, 10>(c, scales, zeros, n_elems, group, y, stream);
+    if constexpr (BITS == 8) {             // at 4 bit the other forms
+        if (log_b == 11) return dequantize_one<BITS, CODEC, 11, 11>(c, scales, zeros, n_elems, group, y, stream);
+        if (log_b == 12) return dequantize_one<BITS, CODEC, 12, 12>(c, scales, zeros, n_elems, group, y, stream);
     }
+    return hipErrorInvalidValue;
 }
 
 }  // namespace
 
-hipError_t launch_quantize_rot_rows(int bits, int codec, const void *x_f16, int64_t n_elems, int log_b, int group,
-                                    void *codes, float *scales, float *zeros, hipStream_t stream)
+hipError_t launch_quantize_rot_rows(const void *x_f16, int64_t n_elems, int log_b, int group, void *codes, float *scales,
+                                    hipStream_t stream)
 {
     const uint16_t *x = static_cast<const uint16_t *>(x_f16);
     uint8_t *c = static_cast<uint8_t *>(codes);
-    if (codec == CODEC_FP8)
-        return bits == 8 ? quantize_block<8, kFp8>(log_b, x, n_elems, group, c, scales, nullptr, stream)
-                         : hipErrorInvalidValue;
-    if (bits == 4)
-        return codec == CODEC_ASYM ? quantize_block<4, kAsym>(log_b, x, n_elems, group, c, scales, zeros, stream)
-                                   : quantize_block<4, kSym>(log_b, x, n_elems, group, c, scales, nullptr, stream);
-    return codec == CODEC_ASYM ? quantize_block<8, kAsym>(log_b, x, n_elems, group, c, scales, zeros, stream)
-                               : quantize_block<8, kSym>(log_b, x, n_elems, group, c, scales, nullptr, stream);
+    switch (log_b) {
+    case 10: return quantize_one<11, 10>(x, n_elems, group, c, scales, stream);
+    case 11: return quantize_one<11, 11>(x, n_elems, group, c, scales, stream);
+    case 12: return quantize_one<12, 12>(x, n_elems, group, c, scales, stream);
+    default: return hipErrorInvalidValue;
+    }
 }
 
 hipError_t launch_dequantize_rot_rows(int bits, int codec, const void *codes, const float *scales, const float *zeros,

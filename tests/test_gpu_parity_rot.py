@@ -458,3 +458,30 @@ def test_allreduce_sim_rot_sources_side_by_side(fc, quantizer, n_src, hidden):
             fc.allreduce_sim_rot(few[:, pick], group, bits, bits, quantizer, out=y.t)
             torch.cuda.synchronize(); y.check()
             assert torch.equal(y.t.view(torch.int16), want[pick]), "N=%d h=%d g=%d rows=%d" % (n_src, hidden, group, rows)
+
+
+@pytest.mark.parametrize("quantizer,bits", [(oracle.ASYM, 4), (oracle.ASYM, 8), (oracle.SYM, 4), (oracle.SYM, 8), (oracle.FP8, 8)])
+@pytest.mark.parametrize("hidden", [1024, 2048, 4096, 8192])
+def test_rot_codecs_on_both_sides_of_the_volume_limits(fc, quantizer, bits, hidden):
+    # 2^20, 2^21 and 5 * 2^19 elements, where other forms of the rotated quantizer and dequantizer take over
+    x = synth_inputs.make_partials(1, 5, hidden, seed=hidden + bits, outlier_frac=0.01)[0]
+    x[1] = 0
+    x[2] = np.float16(6e-8) * (np.arange(hidden) % 5)
+    x[3] += np.float16(300.0)
+    x[4, ::3] = np.float16(-0.0)
+    few = dev(x.view(np.uint16)).view(torch.float16)
+    for group in (32, 256, hidden):
+        coded = oracle.quantize_rot(x, group, bits, quantizer)
+        back = dev(oracle.dequantize_rot(*coded, hidden, group, bits, quantizer).view(np.int16))
+        want = [dev(np.ascontiguousarray(a).view(np.uint8)) for a in coded[:3 if quantizer == oracle.ASYM else 2]]
+        for limit in (1 << 20, 1 << 21, 5 << 19):
+            for rows in (1, limit // hidden, limit // hidden + 1):
+                pick = torch.arange(rows, device="cuda") % 5
+                got = fc.quantize_rot(few[pick], group, bits, quantizer)
+                what = "h=%d g=%d rows=%d" % (hidden, group, rows)
+                for a, w in zip(got, want):
+                    assert torch.equal(a.view(torch.uint8), w[pick]), what
+                y = Guarded((rows, hidden), torch.float16)
+                fc.dequantize_rot(got[0], got[1], got[2] if quantizer == oracle.ASYM else None, hidden, group, bits, quantizer, out=y.t)
+                torch.cuda.synchronize(); y.check()
+                assert torch.equal(y.t.view(torch.int16), back[pick]), what
