@@ -228,6 +228,13 @@ __device__ __forceinline__ void dma_piece(rsrc_t r, u32 off, void *lds_piece)
     __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_void *)lds_piece, 16, off, 0, 0, kStreamLoadPolicy);
 }
 
+// Barrier for data that goes through LDS: waits for this wavefront's LDS operations only, so that loads from memory
+// stay in flight across it.
+__device__ __forceinline__ void lds_barrier()
+{
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+}
+
 // ---------------------------------------------------------------------------
 // cross-lane min / max over the LPG adjacent lanes that share a group
 // ---------------------------------------------------------------------------

@@ -34,7 +34,7 @@ static hipError_t launch_nl(const FusedArgs &a, hipStream_t stream)
                 a.n_elems, log2_int(a.group),
                 static_cast<uint8_t *>(a.codes_out), a.scales_out);
     }
-    // Groups too wide for fc_fused_small.hpp, at most one workgroup per compute unit: the shorter chain of instructions
+    // Where fc_fused_small.hpp is not taken, at most one workgroup per compute unit: the shorter chain of instructions
     // (hidden 8192, 8 to 128 tokens, us under graph replay, accumulate_nibbles / accumulate_fast: g = 1024, INT4 N = 4
     // 3.29 / 3.14 at 8 tokens, 3.38 / 3.23 at 128, but 3.69 / 3.91 at 160, where a second workgroup comes in; N = 3 4 -> 8 bit
     // 3.27 / 3.11 at 128, compact metadata N = 4 3.38 / 3.14; g = 8192 3.59 / 3.47 at 256 tokens, 3.99 / 4.14 at 384).
@@ -43,7 +43,7 @@ static hipError_t launch_nl(const FusedArgs &a, hipStream_t stream)
     // 8 M 5.12 / 5.00, 16 M 10.67 / 9.67, 28 M 16.08 / 14.02, 32 M 16.82 / 15.31; N = 3 8 M 6.19 / 5.76, 12 M 9.87 / 9.19, 20 M
     // 14.08 / 12.91, 32 M 21.73 / 17.90; g = 1024 the same; over 1.2 GB of buffers both are equal up to
     // 40 M, 64 M 23.5 / 25.2, 28.6 / 29.6.  g = 128, N = 2 8 M 5.08 / 5.52, 24 M 13.2 / 14.5; N = 4 16 M 12.46 / 12.79).
-    constexpr bool kAloneOnUnit = FC_BITS_IN == 4 && NSRC <= 4 && LPG >= 32;
+    constexpr bool kAloneOnUnit = FC_BITS_IN == 4 && ((NSRC <= 2 && LPG >= 32) || (NSRC <= 4 && LPG == 256));
     constexpr bool kCached = FC_BITS_IN == 4 && FC_BITS_OUT == 8 && (NSRC == 2 || NSRC == 3) && LPG >= 8;
     if constexpr (kAloneOnUnit || kCached) {
         constexpr int kComputeUnits = 256;
@@ -78,9 +78,14 @@ static hipError_t launch_nl(const FusedArgs &a, hipStream_t stream)
 template <int CODEC, int NSRC>
 static hipError_t launch_small(const FusedArgs &a, hipStream_t stream)
 {
+    if (a.group > fused_small_wave_elems(FC_BITS_IN))
+        return launch_kernel(k_fused_small<CODEC, FC_BITS_IN, FC_BITS_OUT, NSRC, true>, dim3((unsigned)(a.n_elems / a.group)), dim3(a.group / 8),
+                stream, static_cast<const uint8_t *>(a.codes_in), a.codes_stride, a.scales_in, a.zeros_in,
+                a.meta_stride, a.n_elems, log2_int(a.group), a.group / 8,
+                static_cast<uint8_t *>(a.codes_out), a.scales_out, a.zeros_out);
     const int64_t wave_elems = fused_small_wave_elems(FC_BITS_IN);
     const int64_t waves = (a.n_elems + wave_elems - 1) / wave_elems;
-    return launch_kernel(k_fused_small<CODEC, FC_BITS_IN, FC_BITS_OUT, NSRC>, dim3((unsigned)waves), dim3(64), stream,
+    return launch_kernel(k_fused_small<CODEC, FC_BITS_IN, FC_BITS_OUT, NSRC, false>, dim3((unsigned)waves), dim3(64), stream,
             static_cast<const uint8_t *>(a.codes_in), a.codes_stride, a.scales_in, a.zeros_in,
             a.meta_stride, a.n_elems, log2_int(a.group), a.group / fused_small_lane_elems(FC_BITS_IN),
             static_cast<uint8_t *>(a.codes_out), a.scales_out, a.zeros_out);

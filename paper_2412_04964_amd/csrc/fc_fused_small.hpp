@@ -7,7 +7,8 @@
 // and every chain is a quarter as long; all loads (codes, scales, zero-points of every source) are issued before
 // the first use.  The arithmetic is the literal form of the contract in include/fc.h, the same that the bulk
 // kernel's general path evaluates: d = (float)q - z, acc = fma(d, s, acc) in source order from +0, then Eq. 1-2 (the
-// quantizer's own equations) on the sums.  Groups span g / E adjacent lanes (at most the wavefront: g <= 256 at 8 bit, 512 at 4 bit).
+// quantizer's own equations) on the sums.  Groups span g / E adjacent lanes; those that are wider than a wavefront (256 elements at 8 bit, 512
+// at 4 bit) have a workgroup each.
 #pragma once
 
 #include "fc_device.hpp"
@@ -54,11 +55,30 @@ inline int fused_small_limit(int codec, int bits_in, int n_src, bool wide)
 constexpr int kFusedSmallWavesPerSource = 448;
 constexpr int kFusedSmallMinWaves = 24;
 
+// Groups of several wavefronts (SPANS below): 8 elements per lane and one barrier, against 16 or 32 per lane in the bulk kernel, and against one
+// workgroup that walks through the sources of a group of 8192 at 8 bit.  us by elements (2^20), hidden 8192, bulk / this one:
+//   4 -> 4 bit, group 1024: N = 2  1/4: 2.59 / 2.31   1/2: 2.60 / 2.44   1: 2.69 / 2.64, symmetric 2.40 / 2.54;   N = 3  1/2: 2.87 / 2.56   2: 3.66 / 3.49   2.5: 3.87 /
+//     4.01;   N = 4  1/64: 2.84 / 2.36   1: 3.26 / 3.07   2: 3.90 / 3.79   3: 4.35 / 4.52;   N = 8  1/4: 3.73 / 2.87   1: 4.01 / 3.55   2: 5.28 / 4.74   3: 5.92 / 6.11;
+//     compact metadata N = 4  1/2: 3.01 / 2.71   1.5: 3.83 / 3.84   2: 3.89 / 3.93, 4 -> 8 bit, group 2048, N = 8  1.5: 5.24 / 4.86   2: 5.33 / 5.69
+//   group 4096: N = 4  1/2: 3.05 / 2.79   2: 4.08 / 3.80;   N = 8  1: 4.06 / 3.56.   group 8192: N = 4  1/4: 3.19 / 3.19   1: 3.42 / 3.53
+//   8 -> 8 bit, group 512: N = 8  1/4: 3.24 / 2.92   1/2: 3.36 / 3.20   1.5: 4.92 / 5.32;   N = 2  1/8: 2.33 / 2.23;   group 1024: N = 8  1/4: 3.21 / 2.99   1/2: 3.32 /
+//     3.47;   N = 4  1/64: 2.53 / 2.28   1/2: 2.84 / 2.98, FP8 1/4: 2.25 / 2.30;   group 4096: N = 4  1/4: 2.77 / 2.78
+//   group 8192: N = 2  1: 3.98 / 3.29   4: 5.47 / 5.33;   N = 4  1: 5.84 / 3.69   4: 7.97 / 7.17   6: 9.49 / 9.42;   N = 8  1/2: 8.44 / 4.30   4: 11.98 / 9.95;   FP8 N = 4
+//     1: 4.87 / 3.28   4: 6.84 / 6.38   6: 8.21 / 8.89
+inline bool fused_spans_applies(int codec, int bits_in, int n_src, int64_t n_elems, int group)
+{
+    constexpr int64_t k1M = (int64_t)1 << 20;
+    if (bits_in == 4) return group <= 4096 && n_elems <= (n_src <= 2 ? k1M * 3 / 4 : codec == CODEC_ASYMH ? k1M * 3 / 2 : 2 * k1M);
+    if (group == 8192) return n_elems <= 4 * k1M;
+    return group <= 2048 && n_elems <= (n_src >= 5 ? k1M / 4 : n_src >= 2 ? k1M / 8 : 0);
+}
+
 inline bool fused_small_applies(int codec, int bits_in, int n_src, int64_t n_elems, int group)
 {
     const int64_t waves = (n_elems + fused_small_wave_elems(bits_in) - 1) / fused_small_wave_elems(bits_in);
+    if (group > fused_small_wave_elems(bits_in)) return fused_spans_applies(codec, bits_in, n_src, n_elems, group);
     const bool wide = group >= 32 * fused_small_lane_elems(bits_in);
-    if (group > fused_small_wave_elems(bits_in) || waves > fused_small_limit(codec, bits_in, n_src, wide) * 1024) return false;
+    if (waves > fused_small_limit(codec, bits_in, n_src, wide) * 1024) return false;
     if (codec != CODEC_ASYM && bits_in == 8 && n_src <= (codec == CODEC_ASYMH ? 1 : 3) && waves <= kFusedSmallMinWaves) return false;
     if (codec == CODEC_ASYM || !wide || n_src > (bits_in == 8 ? 5 : 2)) return true;
     return waves <= n_src * kFusedSmallWavesPerSource * (8 / bits_in);
@@ -66,7 +86,7 @@ inline bool fused_small_applies(int codec, int bits_in, int n_src, int64_t n_ele
 
 // Codes of the lane as numbers, before the scale: q - z, the signed code, or the value of the E4M3 byte
 template <int CODEC, int BITS>
-__device__ __forceinline__ void small_decode(u32 w, float z, float (&d)[32 / BITS])
+__device__ __forceinline__ void small_decode(u32 w, float z, float *d)
 {
     constexpr int E = 32 / BITS;
     if constexpr (CODEC == kFp8) {
@@ -86,30 +106,55 @@ __device__ __forceinline__ void small_decode(u32 w, float z, float (&d)[32 / BIT
     }
 }
 
-template <int CODEC, int BITS_IN, int BITS_OUT, int NSRC>
-__global__ __launch_bounds__(64) void k_fused_small(
+// min and max of a group that is the whole workgroup, up to 16 wavefronts (identical in all lanes): in the wavefront, then every lane takes
+// one wavefront's pair
+__device__ __forceinline__ void span_minmax(float &mn, float &mx, float (*slot)[2])
+{
+    group_minmax<0>(mn, mx, 64);
+    const u32 n_waves = blockDim.x >> 6, lane = threadIdx.x & 63u;
+    if (lane == 0) {
+        slot[threadIdx.x >> 6][0] = mn;
+        slot[threadIdx.x >> 6][1] = mx;
+    }
+    lds_barrier();
+    mn = slot[lane & (n_waves - 1u)][0];
+    mx = slot[lane & (n_waves - 1u)][1];
+    group_minmax<0>(mn, mx, (int)n_waves);
+}
+
+// SPANS: a group takes several wavefronts, which are the workgroup; 8 elements per lane
+template <int CODEC, int BITS_IN, int BITS_OUT, int NSRC, bool SPANS>
+__global__ __launch_bounds__(SPANS ? 1024 : 64) void k_fused_small(
     const uint8_t *__restrict__ codes_in, int64_t codes_stride,
     const float *__restrict__ scales_in, const float *__restrict__ zeros_in, int64_t meta_stride,
     int64_t n_elems, int group_shift, int lpg,
     uint8_t *__restrict__ codes_out, float *__restrict__ scales_out, float *__restrict__ zeros_out)
 {
-    constexpr int E = fused_small_lane_elems(BITS_IN);
+    constexpr int E = SPANS ? 8 : fused_small_lane_elems(BITS_IN);
+    constexpr int W = E * BITS_IN / 32;                         // code words per lane and source
     constexpr int kOutBytes = E * BITS_OUT / 8;                 // 2, 4 or 8 code bytes per lane
-    const u32 lane = threadIdx.x;
-    const int64_t e_wave = (int64_t)blockIdx.x * (64 * E);
+    __shared__ float slot[SPANS ? 16 : 1][2];
+    const u32 lane = threadIdx.x;                               // of the workgroup
+    const int64_t e_wave = (int64_t)blockIdx.x * ((SPANS ? (int)blockDim.x : 64) * E);
     const int64_t e_lane = e_wave + (int64_t)lane * E;
     const bool live = e_lane < n_elems;                         // (the volume is a multiple of the group, hence of E)
     const int64_t n_groups = n_elems >> group_shift;
     const int64_t g_mine = e_lane >> group_shift;
     const int64_t gi = g_mine < n_groups ? g_mine : n_groups - 1;   // lanes beyond the end stay inside the arrays
 
-    u32 w[NSRC];
+    u32 w[NSRC][W];
     float s[NSRC], z[NSRC];
 #pragma unroll
     for (int j = 0; j < NSRC; ++j) {
         const rsrc_t rc = make_rsrc(codes_in + (int64_t)j * codes_stride + e_wave * BITS_IN / 8,
                                     (n_elems - e_wave) * BITS_IN / 8);
-        w[j] = __builtin_amdgcn_raw_buffer_load_b32(rc, lane * 4, 0, 0);
+        if constexpr (W == 1) {
+            w[j][0] = __builtin_amdgcn_raw_buffer_load_b32(rc, lane * 4, 0, 0);
+        } else {
+            const u32x2 a = __builtin_amdgcn_raw_buffer_load_b64(rc, lane * 8, 0, 0);
+            w[j][0] = a[0];
+            w[j][1] = a[1];
+        }
         s[j] = scales_in[(int64_t)j * meta_stride + gi];
         z[j] = CODEC == kAsym ? zeros_in[(int64_t)j * meta_stride + gi] : 0.0f;
     }
@@ -121,7 +166,8 @@ __global__ __launch_bounds__(64) void k_fused_small(
     for (int j = 0; j < NSRC; ++j) {
         if constexpr (CODEC == kAsymH) unpack_meta(__builtin_bit_cast(u32, s[j]), s[j], z[j]);
         float d[E];
-        small_decode<CODEC, BITS_IN>(w[j], z[j], d);
+#pragma unroll
+        for (int k = 0; k < W; ++k) small_decode<CODEC, BITS_IN>(w[j][k], z[j], d + k * (E / W));
 #pragma unroll
         for (int i = 0; i < E; ++i) acc[i] = fmaf(d[i], s[j], acc[i]);
     }
@@ -131,17 +177,25 @@ __global__ __launch_bounds__(64) void k_fused_small(
     if constexpr (is_asym(CODEC)) {
         float mn, mx;
         lane_minmax(acc, mn, mx);
-        group_minmax<0>(mn, mx, lpg);
+        if constexpr (SPANS) span_minmax(mn, mx, slot);
+        else group_minmax<0>(mn, mx, lpg);
         group_params<BITS_OUT, CODEC == kAsymH>(mn, mx, s2, inv, zf);
 #pragma unroll
         for (int i = 0; i < E; ++i) packed |= (uint64_t)encode<BITS_OUT>(acc[i], inv, zf) << (BITS_OUT * i);
     } else {
-        const float amax = group_max<0>(lane_absmax(acc), lpg);
+        float amax = lane_absmax(acc);
+        if constexpr (SPANS) {
+            float lo = -amax;
+            span_minmax(lo, amax, slot);
+        } else {
+            amax = group_max<0>(amax, lpg);
+        }
         if constexpr (CODEC == kFp8) {
             group_params_absmax<448>(amax, s2, inv);
-            u32 word[1];
-            pack_lane_fp8<4>(acc, inv, word);
+            u32 word[E / 4];
+            pack_lane_fp8<E>(acc, inv, word);
             packed = word[0];
+            if constexpr (E == 8) packed |= (uint64_t)word[1] << 32;
         } else {
             group_params_sym<BITS_OUT>(amax, s2, inv);          // neither clamp of Eq. 4 can act (see pack_lane_sym)
 #pragma unroll

@@ -373,13 +373,6 @@ __device__ __forceinline__ void rot_piece_stage(float (&v)[4][8])
             }
 }
 
-// Barrier for data that goes through LDS: waits for this wavefront's LDS operations only, so that loads from memory
-// stay in flight across it.
-__device__ __forceinline__ void lds_barrier()
-{
-    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-}
-
 // Wavefronts per block of 2^LB elements, and per workgroup (blocks of at most one wavefront go two wavefronts to a
 // workgroup; these never meet)
 constexpr int rot_block_waves(int lb) { return lb <= 11 ? 1 : 1 << (lb - 11); }
