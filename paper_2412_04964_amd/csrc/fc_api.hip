@@ -256,20 +256,18 @@ int dequantize_rot_impl(int codec, const void *codes, const float *scales, const
                                                 (int)hidden, group, y_f16, static_cast<hipStream_t>(hip_stream)));
 }
 
-// Algorithm 1 as its three steps through the workspace, on checked arguments; rotate: with the Hadamard rotation around it
-int three_steps(bool rotate, int codec, const void *x_f16, int n_src, int64_t tokens, int64_t hidden, int group,
-                int bits_rs, int bits_ag, void *y_f16, const SimLayout &L, void *workspace, void *hip_stream)
+// Algorithm 1 in steps through the workspace, on checked arguments.  The first: every partial quantized
+int quantize_partials(bool rotate, int codec, const void *x_f16, int n_src, int64_t tokens, int64_t hidden, int group, int bits_rs,
+                      const SimLayout &L, char *ws, int64_t &meta_stride, void *hip_stream)
 {
     const int64_t n = tokens * hidden;
-    char *ws = static_cast<char *>(workspace);
     const char *x = static_cast<const char *>(x_f16);
     const auto quantize = rotate ? quantize_rot_impl : quantize_impl;
-    const auto dequantize = rotate ? dequantize_rot_impl : dequantize_impl;
     // One launch for all partials is what matters for launch-bound volumes: they are N * tokens rows of one tensor, whose
     // metadata lie one partial's right behind the other's.  Codes always do (groups are multiples of 32 elements).
     const bool packed = tokens <= kMaxElems / hidden / n_src && tokens <= 0x7FFFFFFF / n_src;
     const int launches = packed ? 1 : n_src;
-    const int64_t meta_stride = packed ? n / group : (int64_t)(L.meta / sizeof(float));
+    meta_stride = packed ? n / group : (int64_t)(L.meta / sizeof(float));
     for (int j = 0; j < launches; ++j) {
         const int q = quantize(codec, x + (size_t)j * (size_t)n * 2, packed ? tokens * n_src : tokens, hidden,
                                group, bits_rs, ws + L.off_codes1 + (size_t)j * L.codes_rs,
@@ -277,19 +275,44 @@ int three_steps(bool rotate, int codec, const void *x_f16, int n_src, int64_t to
                                reinterpret_cast<float *>(ws + L.off_zeros1 + (size_t)j * L.meta), hip_stream);
         if (q != FC_OK) return q;
     }
-    const int f = fused_impl(codec, ws + L.off_codes1, (int64_t)L.codes_rs,
-                             reinterpret_cast<const float *>(ws + L.off_scales1),
-                             reinterpret_cast<const float *>(ws + L.off_zeros1),
-                             meta_stride, n_src, tokens, hidden, group, bits_rs,
-                             bits_ag, ws + L.off_codes2, reinterpret_cast<float *>(ws + L.off_scales2),
-                             reinterpret_cast<float *>(ws + L.off_zeros2), hip_stream);
-    if (f != FC_OK) return f;
-    return dequantize(codec, ws + L.off_codes2, reinterpret_cast<const float *>(ws + L.off_scales2),
-                      reinterpret_cast<const float *>(ws + L.off_zeros2), tokens, hidden, group,
-                      bits_ag, y_f16, hip_stream);
+    return FC_OK;
 }
 
-// Whether the three steps are the faster form of the rotated all-reduce.  The one launch works through the sources one after
+int three_steps(int codec, const void *x_f16, int n_src, int64_t tokens, int64_t hidden, int group, int bits_rs, int bits_ag,
+                void *y_f16, const SimLayout &L, void *workspace, void *hip_stream)
+{
+    char *ws = static_cast<char *>(workspace);
+    int64_t meta_stride;
+    int rc = quantize_partials(false, codec, x_f16, n_src, tokens, hidden, group, bits_rs, L, ws, meta_stride, hip_stream);
+    if (rc != FC_OK) return rc;
+    rc = fused_impl(codec, ws + L.off_codes1, (int64_t)L.codes_rs,
+                    reinterpret_cast<const float *>(ws + L.off_scales1),
+                    reinterpret_cast<const float *>(ws + L.off_zeros1),
+                    meta_stride, n_src, tokens, hidden, group, bits_rs,
+                    bits_ag, ws + L.off_codes2, reinterpret_cast<float *>(ws + L.off_scales2),
+                    reinterpret_cast<float *>(ws + L.off_zeros2), hip_stream);
+    if (rc != FC_OK) return rc;
+    return dequantize_impl(codec, ws + L.off_codes2, reinterpret_cast<const float *>(ws + L.off_scales2),
+                           reinterpret_cast<const float *>(ws + L.off_zeros2), tokens, hidden, group,
+                           bits_ag, y_f16, hip_stream);
+}
+
+// with the Hadamard rotation around it, the last two steps in one launch
+int rot_steps(int codec, const void *x_f16, int n_src, int64_t tokens, int64_t hidden, int group, int bits_rs, int bits_ag,
+              void *y_f16, const SimLayout &L, void *workspace, void *hip_stream)
+{
+    char *ws = static_cast<char *>(workspace);
+    int64_t meta_stride;
+    const int rc = quantize_partials(true, codec, x_f16, n_src, tokens, hidden, group, bits_rs, L, ws, meta_stride, hip_stream);
+    if (rc != FC_OK) return rc;
+    return hip_result(fc::launch_reduce_rot_fine(codec, bits_rs, bits_ag, ws + L.off_codes1, (int64_t)L.codes_rs,
+                                                 reinterpret_cast<const float *>(ws + L.off_scales1),
+                                                 reinterpret_cast<const float *>(ws + L.off_zeros1), meta_stride, n_src,
+                                                 tokens * hidden, fc::log2_int(fc::rotation_block((int)hidden)), group, y_f16,
+                                                 static_cast<hipStream_t>(hip_stream)));
+}
+
+// Whether the steps are the faster form of the rotated all-reduce.  The one launch works through the sources one after
 // the other, 1.5 us each in blocks of up to 2048 elements, 2.0 us in blocks of 8192 (FP8 1.9 / 2.3), until the chip is full; the
 // three steps take 8 to 10 us, their quantizations spread over the chip.  Up to this many elements, in units of 2^16, by the
 // block and the number of sources, the steps are taken.  The limits were found with earlier kernels; with those of today the lines
@@ -311,7 +334,11 @@ int three_steps(bool rotate, int codec, const void *x_f16, int n_src, int64_t to
 // more (one group per token, 8 x 1 x 8192 20.3 -> 11.4, 5 x 7 x 4096 12.7 -> 10.7, FP8 4 x 5 x 8192 14.3 -> 12.4), except
 // three sources of FP8 in blocks of 8192 (11.5 / 12.1).  In blocks of 1024 the steps would win as much (8 x 1 x 5120 14.8 / 10.4), but
 // that call leaves the caller's workspace alone, which the tests hold it to.
-// Small volumes of the one launch have their sources side by side by now (rot_spread_applies), which is not in these figures.
+// These figures are those of three launches, before the last two of them became one, and of the one launch with one source after the other
+// everywhere (by now side by side in small volumes, rot_spread_applies); the limits have stayed, since callers may count on when the workspace
+// is written.  us, three launches / two: INT4, group 128, block 2048  N = 4  1/4 M 7.46 / 6.18;  N = 8  1/4 M 8.65 / 7.50   1 M 12.74 / 10.91;  block
+// 4096  N = 4  1/2 M 9.18 / 7.92;  N = 8  1.5 M 16.10 / 14.40;  block 8192  N = 4  1/2 M 10.37 / 9.47;  N = 8  1 M 14.23 / 13.01;  FP8  block 1024
+// N = 4  1/4 M 7.15 / 5.65   1.5 M 12.68 / 11.02;  block 4096  N = 8  3 M 27.02 / 25.35.
 bool rot_steps_apply(int codec, int n_src, int64_t n_elems, int64_t hidden, int group)
 {
     //                                           n_src 3  4   5   6   7   8
@@ -420,7 +447,7 @@ int fc_allreduce_sim_static(const void *x_f16, int n_src, int64_t tokens, int64_
     // nothing in the scratch has to start at zero: every byte a kernel reads there was written by
     // the kernel before it in this call
     // always the three-kernel sequence through the scratch array (fc_allreduce_sim's one kernel needs no intermediates)
-    return three_steps(false, fc::CODEC_ASYM, x_f16, n_src, tokens, hidden, group, bits_rs, bits_ag, y_f16, L, ws,
+    return three_steps(fc::CODEC_ASYM, x_f16, n_src, tokens, hidden, group, bits_rs, bits_ag, y_f16, L, ws,
                        hip_stream);
 }
 
@@ -526,8 +553,7 @@ int fc_allreduce_sim_rot(const void *x_f16, int n_src, int64_t tokens, int64_t h
     if (!aligned16(workspace)) return FC_ERR_ALIGN;
 
     if (rot_steps_apply(quantizer, n_src, n, hidden, group))
-        return three_steps(true, quantizer, x_f16, n_src, tokens, hidden, group, bits_rs, bits_ag, y_f16, L, workspace,
-                           hip_stream);
+        return rot_steps(quantizer, x_f16, n_src, tokens, hidden, group, bits_rs, bits_ag, y_f16, L, workspace, hip_stream);
     // one kernel; nothing goes through the workspace
     return hip_result(fc::launch_allreduce_rot(quantizer, bits_rs, bits_ag, x_f16, n_src, tokens, (int)hidden, group,
                                                y_f16, static_cast<hipStream_t>(hip_stream)));

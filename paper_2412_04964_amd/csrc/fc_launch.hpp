@@ -108,6 +108,11 @@ hipError_t launch_quantize_rot_fine(int bits, int codec, const void *x_f16, int6
 hipError_t launch_dequantize_rot_fine(int bits, int codec, const void *codes, const float *scales, const float *zeros,
                                       int64_t n_elems, int log_b, int group, void *y_f16, hipStream_t stream);
 
+// the last two steps of the rotated all-reduce in one, from the first step's codes to the result
+hipError_t launch_reduce_rot_fine(int codec, int bits_rs, int bits_ag, const void *codes, int64_t codes_stride, const float *scales,
+                                  const float *zeros, int64_t meta_stride, int n_src, int64_t n_elems, int log_b, int group, void *y_f16,
+                                  hipStream_t stream);
+
 // fc_rot_rows.hip: the same for volumes between those and a full chip, blocks of 1024, 2048 and 4096 (2^log_b); the quantizer for FP8, the
 // dequantizer at 4 bit in blocks of 1024 only.
 hipError_t launch_quantize_rot_rows(const void *x_f16, int64_t n_elems, int log_b, int group, void *codes, float *scales,

@@ -17,6 +17,7 @@
 //   INT8, blocks of 1024: 2.51 / 2.19; 1 M 3.07 / 2.95; 2 M 3.75 / 3.77.   FP8, 4096: 2.66 / 2.43; 1 M 3.25 / 3.18; 2 M 3.97 / 4.08
 // The frames of fc_rot.hip save an instruction per value and stage between lanes: equal up to 1 M elements, 2 M 3.83 for 3.92.
 #include "fc_rot_wave.hpp"
+#include "fc_fused_small.hpp"
 #include "fc_launch.hpp"
 
 namespace fc {
@@ -196,6 +197,83 @@ __global__ __launch_bounds__(64 * fine_waves(LB)) void k_dequantize_rot_fine(
     *reinterpret_cast<u32x4 *>(y + e0 + at * 8) = out;
 }
 
+// The last two steps of the rotated all-reduce on one block: dequantize the sources' codes, sum, quantize, dequantize, rotate back.
+// One launch and one way through memory less than fc_dequant_reduce_requant and fc_dequantize_rot, term by term the same: all-reduces in steps
+// 1.1 to 1.9 us shorter at every volume they are taken for (figures at rot_steps_apply).  All loads of all sources come first.  qmax and
+// rcp: highest code of the second quantization and its reciprocal
+template <int BITS, int CODEC, int LB>
+__global__ __launch_bounds__(64 * fine_waves(LB)) void k_reduce_rot_fine(
+    const uint8_t *__restrict__ codes, int64_t codes_stride, const float *__restrict__ scales, const float *__restrict__ zeros,
+    int64_t meta_stride, int n_src, int lpg, int group_shift, float qmax, float rcp, uint16_t *__restrict__ y)
+{
+    constexpr int W = BITS / 4;
+    __shared__ __attribute__((aligned(16))) uint8_t lds[fine_exchanges(LB) * fine_waves(LB) * 2048];
+    __shared__ float slot[fine_waves(LB)][2];
+    const u32 tid = threadIdx.x, lane = tid & 63u;
+    const u32 wave = (u32)__builtin_amdgcn_readfirstlane((int)(tid >> 6));
+    const int64_t e0 = (int64_t)blockIdx.x << LB;
+    const RotLane L = rot_lane<true>(lane);
+    const u32 at = wave * 64 + L.pos;
+    const int64_t gi = (e0 + tid * 8) >> group_shift;
+    const uint8_t *from = codes + (e0 + at * 8) * BITS / 8;
+
+    u32 w[8][W];
+    float s[8], z[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+        if (j < n_src) {
+            if constexpr (BITS == 4) {
+                w[j][0] = *reinterpret_cast<const u32 *>(from + j * codes_stride);
+            } else {
+                const u32x2 a = *reinterpret_cast<const u32x2 *>(from + j * codes_stride);
+                w[j][0] = a[0];
+                w[j][1] = a[1];
+            }
+            s[j] = scales[j * meta_stride + gi];
+            if constexpr (CODEC == kAsym) z[j] = zeros[j * meta_stride + gi];
+            else z[j] = 0.0f;
+        }
+    float v[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) v[i] = 0.0f;
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+        if (j < n_src) {
+            float d[8];
+#pragma unroll
+            for (int k = 0; k < W; ++k) small_decode<CODEC, BITS>(w[j][k], z[j], d + k * (8 / W));
+#pragma unroll
+            for (int i = 0; i < 8; ++i) v[i] = fmaf(d[i], s[j], v[i]);
+        }
+
+    float mn, mx, s2, inv, zf = 0.0f;
+    lane_minmax(v, mn, mx);
+    group_minmax<0>(mn, mx, lpg);
+    if (lpg > 64) cross_wave_minmax(mn, mx, slot, wave, lane, (u32)lpg >> 6);
+    if constexpr (CODEC == kAsym) group_params_levels<false>(mn, mx, qmax, rcp, s2, inv, zf);
+    else group_params_absmax_levels(fmaxf(fabsf(mn), fabsf(mx)), qmax, rcp, s2, inv);
+    if constexpr (CODEC == kFp8) {
+        u32 word[2];
+        pack_lane_fp8<8>(v, inv, word);
+        decode_fp8(word, v);
+    } else {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const float t = rintf(v[i] * inv);
+            v[i] = CODEC == kAsym ? __builtin_amdgcn_fmed3f(t + zf, 0.0f, qmax) - zf : t + 0.0f;   // a stored code has no -0
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < 8; ++i) v[i] *= s2;
+    fine_transform<LB, 0>(v, L, lds, wave);
+
+    constexpr float back = 1.0f / (float)(1 << (LB / 2));
+    u32x4 out;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) out[i] = round_pair(v[2 * i] * back, v[2 * i + 1] * back);
+    *reinterpret_cast<u32x4 *>(y + e0 + at * 8) = out;
+}
+
 namespace {
 
 template <int BITS, int CODEC, int LB>
@@ -269,6 +347,40 @@ hipError_t launch_dequantize_rot_fine(int bits, int codec, const void *codes, co
                                    : dequantize_block<4, kSym>(log_b, c, scales, nullptr, n_elems, group, y, stream);
     return codec == CODEC_ASYM ? dequantize_block<8, kAsym>(log_b, c, scales, zeros, n_elems, group, y, stream)
                                : dequantize_block<8, kSym>(log_b, c, scales, nullptr, n_elems, group, y, stream);
+}
+
+template <int BITS, int CODEC, int LB>
+static hipError_t reduce_one(const uint8_t *c, int64_t codes_stride, const float *scales, const float *zeros, int64_t meta_stride, int n_src,
+                             int bits_ag, int64_t n_elems, int group, uint16_t *y, hipStream_t stream)
+{
+    const float q = CODEC == kFp8 ? 448.0f : (float)((1 << (CODEC == kSym ? bits_ag - 1 : bits_ag)) - 1);
+    return launch_kernel(k_reduce_rot_fine<BITS, CODEC, LB>, dim3((unsigned)(n_elems >> LB)), dim3(64 * fine_waves(LB)), stream, c,
+                         codes_stride, scales, zeros, meta_stride, n_src, group / 8, log2_int(group), q, 1.0f / q, y);
+}
+
+hipError_t launch_reduce_rot_fine(int codec, int bits_rs, int bits_ag, const void *codes, int64_t codes_stride, const float *scales,
+                                  const float *zeros, int64_t meta_stride, int n_src, int64_t n_elems, int log_b, int group, void *y_f16,
+                                  hipStream_t stream)
+{
+    const uint8_t *c = static_cast<const uint8_t *>(codes);
+    uint16_t *y = static_cast<uint16_t *>(y_f16);
+#define FC_REDUCE(BITS, CODEC)                                                                                               \
+    switch (log_b) {                                                                                                         \
+    case 10: return reduce_one<BITS, CODEC, 10>(c, codes_stride, scales, zeros, meta_stride, n_src, bits_ag, n_elems, group, y, stream); \
+    case 11: return reduce_one<BITS, CODEC, 11>(c, codes_stride, scales, zeros, meta_stride, n_src, bits_ag, n_elems, group, y, stream); \
+    case 12: return reduce_one<BITS, CODEC, 12>(c, codes_stride, scales, zeros, meta_stride, n_src, bits_ag, n_elems, group, y, stream); \
+    case 13: return reduce_one<BITS, CODEC, 13>(c, codes_stride, scales, zeros, meta_stride, n_src, bits_ag, n_elems, group, y, stream); \
+    default: return hipErrorInvalidValue;                                                                                    \
+    }
+    if (codec == CODEC_FP8) { FC_REDUCE(8, kFp8) }
+    if (codec == CODEC_ASYM) {
+        if (bits_rs == 4) { FC_REDUCE(4, kAsym) }
+        FC_REDUCE(8, kAsym)
+    }
+    if (codec != CODEC_SYM) return hipErrorInvalidValue;
+    if (bits_rs == 4) { FC_REDUCE(4, kSym) }
+    FC_REDUCE(8, kSym)
+#undef FC_REDUCE
 }
 
 }  // namespace fc

@@ -485,3 +485,24 @@ def test_rot_codecs_on_both_sides_of_the_volume_limits(fc, quantizer, bits, hidd
                 fc.dequantize_rot(got[0], got[1], got[2] if quantizer == oracle.ASYM else None, hidden, group, bits, quantizer, out=y.t)
                 torch.cuda.synchronize(); y.check()
                 assert torch.equal(y.t.view(torch.int16), back[pick]), what
+
+
+@pytest.mark.parametrize("quantizer", [oracle.ASYM, oracle.SYM])
+@pytest.mark.parametrize("bits_rs,bits_ag", [(4, 8), (8, 4)])
+@pytest.mark.parametrize("hidden,group", [(1024, 32), (3072, 1024), (2048, 2048), (4096, 64), (8192, 8192), (8192, 512)])
+def test_allreduce_sim_rot_in_steps(fc, quantizer, bits_rs, bits_ag, hidden, group):
+    # few rows of many sources: the sum, its codes and the inverse transform in one launch.  Zero-points far outside the codes, sums that
+    # cancel to zero, partials of -0 and subnormals, groups of less and more than a wavefront
+    for n_src in (5, 7, 8):
+        x = synth_inputs.make_partials(n_src, 12, hidden, seed=hidden + group + n_src, outlier_frac=0.01)
+        x[:, 1] = 0
+        x[:, 2] = np.float16(-0.0)
+        x[:, 3] += np.float16(300.0)
+        x[1::2, 4] = -x[: n_src // 2 * 2 : 2, 4]
+        x[:, 5] = np.float16(6e-8) * (np.arange(hidden) % 5)
+        x[:, 6] *= np.float16(60.0)
+        want = oracle.allreduce_sim_rot(x, group, bits_rs, bits_ag, quantizer).view(np.uint16)
+        y = Guarded((12, hidden), torch.float16)
+        fc.allreduce_sim_rot(dev(x.view(np.uint16)).view(torch.float16), group, bits_rs, bits_ag, quantizer, out=y.t)
+        torch.cuda.synchronize(); y.check()
+        assert np.array_equal(y.t.cpu().numpy().view(np.uint16), want), "N=%d h=%d g=%d %d->%d" % (n_src, hidden, group, bits_rs, bits_ag)
