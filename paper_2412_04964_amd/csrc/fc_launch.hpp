@@ -113,6 +113,11 @@ hipError_t launch_reduce_rot_fine(int codec, int bits_rs, int bits_ag, const voi
                                   const float *zeros, int64_t meta_stride, int n_src, int64_t n_elems, int log_b, int group, void *y_f16,
                                   hipStream_t stream);
 
+// the whole rotated all-reduce, where that is the fastest form of it
+bool allreduce_rot_fine_applies(int log_b, int n_src, int64_t n_elems);
+hipError_t launch_allreduce_rot_fine(int codec, int bits_rs, int bits_ag, const void *x_f16, int n_src, int64_t n_elems, int log_b, int group,
+                                     void *y_f16, hipStream_t stream);
+
 // fc_rot_rows.hip: the same for volumes between those and a full chip, blocks of 1024, 2048 and 4096 (2^log_b); the quantizer for FP8, the
 // dequantizer at 4 bit in blocks of 1024 only.
 hipError_t launch_quantize_rot_rows(const void *x_f16, int64_t n_elems, int log_b, int group, void *codes, float *scales,

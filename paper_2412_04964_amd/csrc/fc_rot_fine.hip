@@ -197,6 +197,47 @@ __global__ __launch_bounds__(64 * fine_waves(LB)) void k_dequantize_rot_fine(
     *reinterpret_cast<u32x4 *>(y + e0 + at * 8) = out;
 }
 
+// The values' codes before the scale, literally, and the scale of their group: minimum and maximum times f, Eq. 1-2 (3-4, E4M3), q - z.  All wavefronts of the
+// workgroup call it, each block with slots of its own
+template <int CODEC>
+__device__ __forceinline__ void fine_codes(float (&v)[8], float f, int lpg, float (*slot)[2], u32 wave, u32 lane, float qmax, float rcp, float &s)
+{
+    float mn, mx, inv, zf = 0.0f;
+    lane_minmax(v, mn, mx);
+    group_minmax<0>(mn, mx, lpg);
+    if (lpg > 64) cross_wave_minmax(mn, mx, slot, wave, lane, (u32)lpg >> 6);
+    mn *= f;
+    mx *= f;
+    if constexpr (CODEC == kAsym) group_params_levels<false>(mn, mx, qmax, rcp, s, inv, zf);
+    else group_params_absmax_levels(fmaxf(fabsf(mn), fabsf(mx)), qmax, rcp, s, inv);
+    inv *= f;
+    if constexpr (CODEC == kFp8) {
+        u32 word[2];
+        pack_lane_fp8<8>(v, inv, word);
+        decode_fp8(word, v);
+    } else {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const float t = rintf(v[i] * inv);
+            v[i] = CODEC == kAsym ? __builtin_amdgcn_fmed3f(t + zf, 0.0f, qmax) - zf : t + 0.0f;   // a stored code has no -0
+        }
+    }
+}
+
+// scaled, rotated back and rounded
+template <int LB>
+__device__ __forceinline__ u32x4 fine_back(float (&v)[8], float s, const RotLane &L, uint8_t *lds, u32 wave)
+{
+#pragma unroll
+    for (int i = 0; i < 8; ++i) v[i] *= s;
+    fine_transform<LB, 0>(v, L, lds, wave);
+    constexpr float back = 1.0f / (float)(1 << (LB / 2));              // 2^-floor(n/2), n = LB
+    u32x4 out;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) out[i] = round_pair(v[2 * i] * back, v[2 * i + 1] * back);
+    return out;
+}
+
 // The last two steps of the rotated all-reduce on one block: dequantize the sources' codes, sum, quantize, dequantize, rotate back.
 // One launch and one way through memory less than fc_dequant_reduce_requant and fc_dequantize_rot, term by term the same: all-reduces in steps
 // 1.1 to 1.9 us shorter at every volume they are taken for (figures at rot_steps_apply).  All loads of all sources come first.  qmax and
@@ -246,32 +287,66 @@ __global__ __launch_bounds__(64 * fine_waves(LB)) void k_reduce_rot_fine(
             for (int i = 0; i < 8; ++i) v[i] = fmaf(d[i], s[j], v[i]);
         }
 
-    float mn, mx, s2, inv, zf = 0.0f;
-    lane_minmax(v, mn, mx);
-    group_minmax<0>(mn, mx, lpg);
-    if (lpg > 64) cross_wave_minmax(mn, mx, slot, wave, lane, (u32)lpg >> 6);
-    if constexpr (CODEC == kAsym) group_params_levels<false>(mn, mx, qmax, rcp, s2, inv, zf);
-    else group_params_absmax_levels(fmaxf(fabsf(mn), fabsf(mx)), qmax, rcp, s2, inv);
-    if constexpr (CODEC == kFp8) {
-        u32 word[2];
-        pack_lane_fp8<8>(v, inv, word);
-        decode_fp8(word, v);
-    } else {
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const float t = rintf(v[i] * inv);
-            v[i] = CODEC == kAsym ? __builtin_amdgcn_fmed3f(t + zf, 0.0f, qmax) - zf : t + 0.0f;   // a stored code has no -0
-        }
-    }
-#pragma unroll
-    for (int i = 0; i < 8; ++i) v[i] *= s2;
-    fine_transform<LB, 0>(v, L, lds, wave);
+    float s2;
+    fine_codes<CODEC>(v, 1.0f, lpg, slot, wave, lane, qmax, rcp, s2);
+    *reinterpret_cast<u32x4 *>(y + e0 + at * 8) = fine_back<LB>(v, s2, L, lds, wave);
+}
 
-    constexpr float back = 1.0f / (float)(1 << (LB / 2));
-    u32x4 out;
+// The whole rotated all-reduce of a block in one workgroup, n_parts sources at once (see SPREAD in fc_rot_sim.hip), 8 elements per lane; what does
+// not fit goes in further rounds.  LDS: two areas of 2 KB per wavefront, for the exchanges and (the second one) the handing over
+template <int CODEC, int LB>
+__global__ __launch_bounds__(1024) void k_allreduce_rot_fine(const uint16_t *__restrict__ x, int64_t n_elems, int n_src, int lpg, float q_rs,
+                                                            float rcp_rs, float q_ag, float rcp_ag, uint16_t *__restrict__ y)
+{
+    constexpr int kWaves = fine_waves(LB);
+    constexpr u32 kArea = kWaves * 2048;
+    extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
+    __shared__ float slots[16][2], scale[16][64];
+    const u32 lane = threadIdx.x & 63u;
+    const u32 wave_all = (u32)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const u32 wave = wave_all % (u32)kWaves, part = wave_all / (u32)kWaves;
+    const int n_parts = (int)(blockDim.x / (64u * kWaves));
+    uint8_t *mine = lds + part * (2 * kArea);
+    float (*slot)[2] = slots + part * kWaves;
+    const RotLane L = rot_lane<true>(lane);
+    const int64_t e = ((int64_t)blockIdx.x << LB) + (wave * 64 + L.pos) * 8;
+    auto fetch = [&](int j) { return *reinterpret_cast<const u32x4 *>(x + (int64_t)j * n_elems + e); };
+    constexpr float fwd = 1.0f / (float)(1 << ((LB + 1) / 2));          // 2^-ceil(n/2), n = LB
+
+    float acc[8];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) out[i] = round_pair(v[2 * i] * back, v[2 * i + 1] * back);
-    *reinterpret_cast<u32x4 *>(y + e0 + at * 8) = out;
+    for (int i = 0; i < 8; ++i) acc[i] = 0.0f;
+    u32x4 raw = fetch((int)part);                                      // n_parts <= n_src
+    for (int j = 0; j < n_src; j += n_parts) {
+        float v[8], s;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) first_stage(raw[i], v[2 * i], v[2 * i + 1]);
+        const int next = j + n_parts + (int)part;                      // a part without a source repeats the last one; nothing takes it
+        if (j + n_parts < n_src) raw = fetch(next < n_src ? next : n_src - 1);
+        fine_transform<LB, 1>(v, L, mine, wave);
+        fine_codes<CODEC>(v, fwd, lpg, slot, wave, lane, q_rs, rcp_rs, s);
+        if constexpr (LB == 12) lds_barrier();                         // every wavefront has taken the second exchange
+        if (part != 0) {
+            fine_put(v, mine + kArea + wave * 2048 + lane * 16);
+            scale[wave_all][lane] = s;
+        }
+        lds_barrier();
+        if (part == 0) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) acc[i] = fmaf(v[i], s, acc[i]);
+            for (int k = 1; k < n_parts && j + k < n_src; ++k) {       // ReduceSum, source order
+                fine_get(lds + k * (2 * kArea) + kArea + wave * 2048 + lane * 16, v);
+                s = scale[k * kWaves + wave][lane];
+#pragma unroll
+                for (int i = 0; i < 8; ++i) acc[i] = fmaf(v[i], s, acc[i]);
+            }
+        }
+        if (j + n_parts < n_src) lds_barrier();
+    }
+    if (part != 0) return;                                             // a barrier waits for the wavefronts that are left
+    float s;
+    fine_codes<CODEC>(acc, 1.0f, lpg, slot, wave, lane, q_ag, rcp_ag, s);
+    *reinterpret_cast<u32x4 *>(y + e) = fine_back<LB>(acc, s, L, mine, wave);
 }
 
 namespace {
@@ -364,23 +439,71 @@ hipError_t launch_reduce_rot_fine(int codec, int bits_rs, int bits_ag, const voi
 {
     const uint8_t *c = static_cast<const uint8_t *>(codes);
     uint16_t *y = static_cast<uint16_t *>(y_f16);
-#define FC_REDUCE(BITS, CODEC)                                                                                               \
-    switch (log_b) {                                                                                                         \
-    case 10: return reduce_one<BITS, CODEC, 10>(c, codes_stride, scales, zeros, meta_stride, n_src, bits_ag, n_elems, group, y, stream); \
-    case 11: return reduce_one<BITS, CODEC, 11>(c, codes_stride, scales, zeros, meta_stride, n_src, bits_ag, n_elems, group, y, stream); \
-    case 12: return reduce_one<BITS, CODEC, 12>(c, codes_stride, scales, zeros, meta_stride, n_src, bits_ag, n_elems, group, y, stream); \
-    case 13: return reduce_one<BITS, CODEC, 13>(c, codes_stride, scales, zeros, meta_stride, n_src, bits_ag, n_elems, group, y, stream); \
-    default: return hipErrorInvalidValue;                                                                                    \
+    const auto by_block = [&](auto width, auto quantizer) {
+        constexpr int BITS = decltype(width)::value, CODEC = decltype(quantizer)::value;
+        switch (log_b) {
+        case 10: return reduce_one<BITS, CODEC, 10>(c, codes_stride, scales, zeros, meta_stride, n_src, bits_ag, n_elems, group, y, stream);
+        case 11: return reduce_one<BITS, CODEC, 11>(c, codes_stride, scales, zeros, meta_stride, n_src, bits_ag, n_elems, group, y, stream);
+        case 12: return reduce_one<BITS, CODEC, 12>(c, codes_stride, scales, zeros, meta_stride, n_src, bits_ag, n_elems, group, y, stream);
+        case 13: return reduce_one<BITS, CODEC, 13>(c, codes_stride, scales, zeros, meta_stride, n_src, bits_ag, n_elems, group, y, stream);
+        default: return hipErrorInvalidValue;
+        }
+    };
+    using Four = std::integral_constant<int, 4>;
+    using Eight = std::integral_constant<int, 8>;
+    using Asym = std::integral_constant<int, kAsym>;
+    using Sym = std::integral_constant<int, kSym>;
+    switch (codec) {
+    case CODEC_ASYM: return bits_rs == 4 ? by_block(Four{}, Asym{}) : by_block(Eight{}, Asym{});
+    case CODEC_SYM: return bits_rs == 4 ? by_block(Four{}, Sym{}) : by_block(Eight{}, Sym{});
+    case CODEC_FP8: return by_block(Eight{}, std::integral_constant<int, kFp8>{});
+    default: return hipErrorInvalidValue;
     }
-    if (codec == CODEC_FP8) { FC_REDUCE(8, kFp8) }
-    if (codec == CODEC_ASYM) {
-        if (bits_rs == 4) { FC_REDUCE(4, kAsym) }
-        FC_REDUCE(8, kAsym)
+}
+
+// All sources in one round of a workgroup, and at most 2^21 elements of all sources together (four wavefronts per SIMD).  us by elements (2^20) of a
+// partial, the form of fc_rot_sim.hip / this one, group 128: INT4, block 1024, N = 2  1/8: 4.67 / 3.28   1: 6.02 / 5.93   1.5: 6.35 / 7.11;   group 1024, N = 4  1/4: 5.34 /
+// 4.50   1/2: 5.63 / 5.70   3/4: 6.67 / 7.06;   block 2048, N = 1  1/8: 4.45 / 3.33   2: 6.35 / 6.30;   N = 2  1/8: 4.94 / 3.77   1: 6.39 / 5.43   1.5: 6.71 / 6.91;   N = 3  1/8: 5.09 /
+// 4.18   3/4: 6.45 / 6.31   1.5: 7.63 / 9.59;   block 4096, N = 1  1/8: 5.01 / 4.19   2: 6.83 / 6.74;   N = 2  1/8: 5.78 / 5.29   1: 6.46 / 6.08   2: 8.65 / 8.96;   N = 3 (two
+// rounds)  1/8: 6.65 / 7.80;   FP8, N = 2, block 2048  1/8: 5.46 / 3.70   1: 6.59 / 5.33;   block 4096  1/8: 6.17 / 5.22;   symmetric INT8, groups of the block, N = 3, block 2048
+// 1/8: 4.79 / 4.85.
+bool allreduce_rot_fine_applies(int log_b, int n_src, int64_t n_elems)
+{
+    return log_b <= 12 && n_src <= 16 / fine_waves(log_b) && n_src * n_elems <= (int64_t)1 << 21;
+}
+
+template <int CODEC, int LB>
+static hipError_t allreduce_one(const uint16_t *x, int n_src, int64_t n_elems, int group, int bits_rs, int bits_ag, uint16_t *y,
+                                hipStream_t stream)
+{
+    const auto top = [](int bits) { return CODEC == kFp8 ? 448.0f : (float)((1 << (CODEC == kSym ? bits - 1 : bits)) - 1); };
+    constexpr int kWaves = fine_waves(LB), kMost = 16 / kWaves;
+    const int parts = n_src < kMost ? n_src : kMost;
+    return launch_kernel_lds(k_allreduce_rot_fine<CODEC, LB>, dim3((unsigned)(n_elems >> LB)), dim3(64 * kWaves * parts),
+                             (size_t)(parts * kWaves * 4096), stream, x, n_elems, n_src, group / 8, top(bits_rs), 1.0f / top(bits_rs),
+                             top(bits_ag), 1.0f / top(bits_ag), y);
+}
+
+hipError_t launch_allreduce_rot_fine(int codec, int bits_rs, int bits_ag, const void *x_f16, int n_src, int64_t n_elems, int log_b, int group,
+                                     void *y_f16, hipStream_t stream)
+{
+    const uint16_t *x = static_cast<const uint16_t *>(x_f16);
+    uint16_t *y = static_cast<uint16_t *>(y_f16);
+    const auto by_block = [&](auto c) {
+        constexpr int CODEC = decltype(c)::value;
+        switch (log_b) {
+        case 10: return allreduce_one<CODEC, 10>(x, n_src, n_elems, group, bits_rs, bits_ag, y, stream);
+        case 11: return allreduce_one<CODEC, 11>(x, n_src, n_elems, group, bits_rs, bits_ag, y, stream);
+        case 12: return allreduce_one<CODEC, 12>(x, n_src, n_elems, group, bits_rs, bits_ag, y, stream);
+        default: return hipErrorInvalidValue;
+        }
+    };
+    switch (codec) {
+    case CODEC_ASYM: return by_block(std::integral_constant<int, kAsym>{});
+    case CODEC_SYM: return by_block(std::integral_constant<int, kSym>{});
+    case CODEC_FP8: return by_block(std::integral_constant<int, kFp8>{});
+    default: return hipErrorInvalidValue;
     }
-    if (codec != CODEC_SYM) return hipErrorInvalidValue;
-    if (bits_rs == 4) { FC_REDUCE(4, kSym) }
-    FC_REDUCE(8, kSym)
-#undef FC_REDUCE
 }
 
 }  // namespace fc

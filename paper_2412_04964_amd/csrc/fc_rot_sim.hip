@@ -151,9 +151,7 @@ __device__ __forceinline__ void rot_take_over(const uint8_t *from, u32 lane, flo
 
 // ALONE: no wavefront shares its SIMD (launches of at most one workgroup per compute unit), so nothing is raised above another, and blocks
 // of 8192 take the layout with the shorter chain (rot_swaps_apply).  us, the other form / this, two partials one after the other, group 128: INT4 one
-// token of 8192 7.41 / 7.25, 200 tokens 8.95 / 8.86, sym INT8 7.24 / 7.03, 8.74 / 8.66, FP8 8.40 / 8.32; FP8 in blocks of 4096 one token
-// 7.87 / 7.72, 256 tokens 8.98 / 8.81.  Integer codes in blocks of 4096 and all shorter blocks are as fast without it; past the
-// limit it loses at once (257 x 4096 8.40 / 9.17).
+// token of 8192 7.41 / 7.25, 200 tokens 8.95 / 8.86, sym INT8 7.24 / 7.03, 8.74 / 8.66, FP8 8.40 / 8.32.  Past the limit it loses at once.
 // SPREAD: the form for volumes that leave the chip idle.  One source after the other is a chain of 1.1 to 2 us each; here the workgroup
 // has several times the wavefronts of a block, each such part works on a source of its own, and the first one sums what the others hand over
 // through LDS, in source order as ever, and goes on alone.  For rot_spread_applies.
@@ -332,8 +330,8 @@ constexpr int rot_parts(int lb, int n_src)
     return n_src < most ? n_src : most;
 }
 
-// Up to 2^21 elements, and no more than one round of workgroups (16 wavefronts of 128 registers per compute unit), where the steps of
-// rot_steps_apply do not go first.  us under graph replay by elements (2^20), one source after the other / side by side, group 128:
+// Up to 2^21 elements, and no more than one round of workgroups (16 wavefronts of 128 registers per compute unit), where neither the steps of
+// rot_steps_apply nor the finer form (allreduce_rot_fine_applies) go first.  us under graph replay by elements (2^20), one source after the other / side by side, group 128:
 //   INT4, block 2048: N = 2  1/4: 6.49 / 5.28   1: 6.80 / 6.40   2: 8.74 / 7.78   3: 9.00 / 9.59;   N = 3  1/4: 7.88 / 5.31   1: 8.41 / 6.69
 //     2: 10.20 / 8.94   3: 10.47 / 10.89;   N = 5  1.5: 13.53 / 11.64   2 (two rounds): 13.70 / 14.35;   block 1024, group 1024, N = 4
 //     1/4: 9.36 / 5.33   1: 9.86 / 7.01   2: 11.17 / 9.36   2.25: 11.20 / 11.32
@@ -367,7 +365,7 @@ hipError_t launch_one(const uint16_t *x, int n_src, int64_t n_elems, int group, 
     constexpr int kTile = 2048 * rot_group_waves(LB);
     if (rot_spread_applies(LB, n_src, n_elems)) return launch_spread<CODEC, LB>(x, n_src, n_elems, group, rs, ag, y, stream);
     const dim3 grid((unsigned)((n_elems + kTile - 1) / kTile)), block(64 * rot_group_waves(LB));
-    if constexpr (LB == 13 || (LB == 12 && CODEC == kFp8))              // see k_allreduce_rot; a single source, the others go side by side
+    if constexpr (LB == 13)                // see k_allreduce_rot; a single source, the others go side by side
         if (n_elems <= 256 * (int64_t)kTile)
             return launch_kernel(k_allreduce_rot<CODEC, true, LB, false>, grid, block, stream, x, n_elems, n_src, log2_int(group), rs, ag, y);
     return launch_kernel(k_allreduce_rot<CODEC, false, LB, false>, grid, block, stream, x, n_elems, n_src, log2_int(group), rs, ag, y);
@@ -396,6 +394,8 @@ hipError_t launch_allreduce_rot(int codec, int bits_rs, int bits_ag, const void 
     const int lb = log2_int(rotation_block(hidden));
     const int64_t n = tokens * hidden;
     const RotLevels rs = levels(codec, bits_rs), ag = levels(codec, bits_ag);
+    if (allreduce_rot_fine_applies(lb, n_src, n))
+        return launch_allreduce_rot_fine(codec, bits_rs, bits_ag, x, n_src, n, lb, group, y, stream);
     switch (codec) {
     case CODEC_ASYM: return launch_codec<kAsym>(lb, x, n_src, n, group, rs, ag, y, stream);
     case CODEC_SYM: return launch_codec<kSym>(lb, x, n_src, n, group, rs, ag, y, stream);
