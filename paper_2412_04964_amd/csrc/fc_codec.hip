@@ -1,5 +1,6 @@
 // fc_codec.hip -- launchers of the stand-alone quantize and dequantize kernels.
 #include "fc_device.hpp"
+#include "fc_fused_small.hpp"
 #include "fc_launch.hpp"
 
 namespace fc {
@@ -10,7 +11,7 @@ namespace fc {
 // 20 52.0); symmetric 128 M 57.8 / 52.6.  8-bit codes write half as much as they read, and no limit gains anything.
 static bool limits_wavefronts(int bits, int64_t n_elems) { return bits == 4 && n_elems >= (int64_t)36 << 20; }
 
-// Elements per lane and threads per workgroup of the quantizer.  A wavefront waits for all that it reads before it computes, so the
+// Elements per lane and threads per workgroup of the quantizer for 4-bit codes, past quantize_small_applies.  A wavefront waits for all that it reads before it computes, so the
 // finer its tile the earlier arithmetic and stores begin, and the more evenly the memory system is asked; a wider tile has fewer reductions
 // and metadata per element, which counts where a group spans 16 lanes or more.  us by elements (2^20), hidden 8192, 16 elements per lane in
 // workgroups of 64 / 128 / 256 threads, and 32 elements in workgroups of 128:
@@ -20,18 +21,88 @@ static bool limits_wavefronts(int bits, int64_t n_elems) { return bits == 4 && n
 //   16 elements in workgroups of 64, and 32 in workgroups of 256 (of 128 for group 256):
 //                group 256    6: 4.93 4.79   16: 8.99 8.89   24: 12.10 12.22   32: 15.36 15.67   128: 52.4 53.5
 //                group 1024   6: 4.97 4.85   16: 8.92 8.98   24: 11.98 12.25   32: 15.08 15.67   128: 51.3 54.0
-//   8-bit codes have 16 elements in any case; workgroups of 64 and of 256: group 32  1/4: 2.10 2.17   1: 2.70 2.77   4: 4.29 4.10   16: 10.37 10.40;
-//                group 128  1/4: 2.12 2.20   2: 3.06 3.09   3: 3.55 3.49   32: 18.1 17.7;   group 256  1: 2.84 2.80
+//   8-bit codes have 16 elements in any case; workgroups of 64 and of 256: group 32  4: 4.29 4.10   16: 10.37 10.40   64: 33.3 33.5;   group 128  3: 3.55 3.49
+//     32: 18.1 17.7
 constexpr int64_t kOneRound = (int64_t)8 << 20;          // elements that 256 compute units of 32 wavefronts hold, at 16 per lane
 struct QuantizeForm {
     int epl, threads;
 };
-static QuantizeForm quantize_form(int bits, int64_t n_elems, int group)
+static QuantizeForm quantize_form(int64_t n_elems, int group)
 {
-    if (bits == 8) return {16, group <= 128 && n_elems <= (int64_t)5 << 19 ? 64 : 256};
-    if (group <= 128) return {16, n_elems > (int64_t)3 << 20 && n_elems <= kOneRound ? 128 : 64};
+    if (group <= 128) return {16, n_elems <= kOneRound ? 128 : 64};
     if (group <= 1024 && n_elems >= 3 * kOneRound) return {16, 64};
     return {32, group == 256 ? 128 : 256};
+}
+
+// Few elements: 8 per lane, loaded straight into registers instead of through LDS, since a lane's 16 bytes are one access.  us by elements (2^20),
+// hidden 8192, the other forms / this one: 4-bit codes, group 32  1/8: 2.09 / 2.03   1/2: 2.54 / 2.23   1: 2.68 / 2.34   2: 3.05 / 2.77   2.5: 3.24 / 3.19   3: 3.42 / 3.44;
+// group 128  1: 2.72 / 2.37   2: 3.05 / 2.66   2.5: 3.27 / 3.14;   group 256  1/2: 2.70 / 2.32   2.5: 3.44 / 3.30;   8-bit codes, group 32  1/2: 2.53 / 2.28   1: 2.72 /
+// 2.35   1.5: 2.89 / 2.59   2: 3.06 / 3.17;   group 256  1.5: 3.00 / 2.71   2: 3.11 / 3.20.  Workgroups of 64 instead of 256 threads: 1 M 2.44, 2 M 3.00.
+// SPANS, a group of more than 512 is a workgroup, its wavefronts exchange minimum and maximum with one barrier: 4-bit codes, group 1024  1/8: 2.55 / 2.09   1: 2.95 / 2.50   2: 3.25 /
+// 3.00   3: 3.79 / 3.98;   group 2048  1: 2.98 / 2.47   3: 3.83 / 3.69   4: 4.08 / 4.49;   group 8192  1/4: 3.05 / 2.30   1: 3.35 / 2.72   3: 4.33 / 3.84   4: 4.57 / 4.53;   8-bit codes,
+// group 1024  1: 2.89 / 2.55   1.5: 3.12 / 2.90   2: 3.25 / 3.28;   group 4096  1/4: 2.54 / 2.21   2: 3.59 / 3.24   3: 4.03 / 4.36.
+static bool quantize_small_applies(int bits, int64_t n_elems, int group)
+{
+    const int halves = (bits == 4 ? 5 : 3) + (group >= 2048 ? 1 : 0);    // of 2^20 elements
+    return group <= 8192 && n_elems <= halves * ((int64_t)1 << 19);
+}
+template <int BITS, int CODEC, bool SPANS>
+__global__ __launch_bounds__(SPANS ? 1024 : kBlockThreads) void k_quantize_small(const uint16_t *__restrict__ x, int64_t n_elems, int lpg, int group_shift,
+                                                         uint8_t *__restrict__ codes, float *__restrict__ scales, float *__restrict__ zeros)
+{
+    constexpr int E = 8;
+    __shared__ float slot[SPANS ? 16 : 1][2];
+    const int64_t e = ((int64_t)blockIdx.x * (SPANS ? (int)blockDim.x : kBlockThreads) + threadIdx.x) * E;
+    const bool live = SPANS || e < n_elems;
+    const u32x4 raw = *reinterpret_cast<const u32x4 *>(x + (live ? e : 0));
+    float v[E];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const h2 p = as_h2(raw[k]);
+        v[2 * k] = (float)p.x;
+        v[2 * k + 1] = (float)p.y;
+    }
+    float mn, mx, s, inv, zf = 0.0f;
+    u32 word[BITS / 4];
+    lane_minmax(v, mn, mx);
+    if constexpr (SPANS) span_minmax(mn, mx, slot);
+    else group_minmax<0>(mn, mx, lpg);
+    if constexpr (CODEC == kFp8) {
+        group_params_absmax<448>(fmaxf(fabsf(mn), fabsf(mx)), s, inv);
+        pack_lane_fp8<E>(v, inv, word);
+    } else if constexpr (CODEC == kSym) {
+        group_params_sym<BITS>(fmaxf(fabsf(mn), fabsf(mx)), s, inv);
+        pack_lane_sym<BITS, E>(v, inv, word);
+    } else {
+        group_params<BITS, CODEC == kAsymH>(mn, mx, s, inv, zf);
+        pack_lane<BITS, E>(v, inv, zf, mx, word);
+    }
+    if (!live) return;
+    uint8_t *to = codes + e * BITS / 8;
+    if constexpr (BITS == 4) *reinterpret_cast<u32 *>(to) = word[0];
+    else *reinterpret_cast<u32x2 *>(to) = u32x2{word[0], word[1]};
+    if ((threadIdx.x & (u32)(lpg - 1)) == 0) {
+        const int64_t gi = e >> group_shift;
+        scales[gi] = CODEC == kAsymH ? __builtin_bit_cast(float, pack_meta(s, zf)) : s;
+        if constexpr (CODEC == kAsym) zeros[gi] = zf;
+    }
+}
+
+template <int BITS, bool SPANS>
+static hipError_t launch_q_small(int codec, hipStream_t stream, const uint16_t *x, int64_t n_elems, int group, uint8_t *c, float *scales,
+                                 float *zeros)
+{
+    const dim3 block(SPANS ? group / 8 : kBlockThreads), grid((unsigned)((n_elems + block.x * 8 - 1) / (block.x * 8)));
+    const int lpg = group / 8, sh = log2_int(group);
+    switch (codec) {
+    case CODEC_ASYM: return launch_kernel(k_quantize_small<BITS, kAsym, SPANS>, grid, block, stream, x, n_elems, lpg, sh, c, scales, zeros);
+    case CODEC_SYM: return launch_kernel(k_quantize_small<BITS, kSym, SPANS>, grid, block, stream, x, n_elems, lpg, sh, c, scales, nullptr);
+    case CODEC_ASYMH: return launch_kernel(k_quantize_small<BITS, kAsymH, SPANS>, grid, block, stream, x, n_elems, lpg, sh, c, scales, nullptr);
+    case CODEC_FP8:
+        if constexpr (BITS == 8) return launch_kernel(k_quantize_small<8, kFp8, SPANS>, grid, block, stream, x, n_elems, lpg, sh, c, scales, nullptr);
+        [[fallthrough]];
+    default: return hipErrorInvalidValue;
+    }
 }
 
 template <int BITS, int EPL, int BT, int LPG>
@@ -69,14 +140,19 @@ template <int BITS>
 static hipError_t launch_q_bits(int codec, hipStream_t stream, const uint16_t *x, int64_t n_elems, int group,
                                 uint8_t *c, float *scales, float *zeros)
 {
-    const QuantizeForm f = quantize_form(BITS, n_elems, group);
-    if (group <= 128) {
-        if (f.threads == 64) return launch_q_narrow<BITS, 64>(codec, stream, x, n_elems, group, c, scales, zeros);
-        return launch_q_narrow<BITS, BITS == 4 ? 128 : 256>(codec, stream, x, n_elems, group, c, scales, zeros);
-    }
+    if (quantize_small_applies(BITS, n_elems, group))
+        return group > 512 ? launch_q_small<BITS, true>(codec, stream, x, n_elems, group, c, scales, zeros)
+                           : launch_q_small<BITS, false>(codec, stream, x, n_elems, group, c, scales, zeros);
+    if (is_wide_group(BITS, group)) return launch_quantize_wide(BITS, codec, x, n_elems, group, c, scales, zeros, stream);
     if constexpr (BITS == 4) {
+        const QuantizeForm f = quantize_form(n_elems, group);
+        if (group <= 128)
+            return f.threads == 64 ? launch_q_narrow<4, 64>(codec, stream, x, n_elems, group, c, scales, zeros)
+                                   : launch_q_narrow<4, 128>(codec, stream, x, n_elems, group, c, scales, zeros);
         if (f.epl == 16) return launch_q<4, 16, 64, 0>(codec, stream, x, n_elems, group, c, scales, zeros);
         if (group == 256) return launch_q<4, 32, 128, 8>(codec, stream, x, n_elems, group, c, scales, zeros);
+    } else if (group <= 128) {
+        return launch_q_narrow<8, 256>(codec, stream, x, n_elems, group, c, scales, zeros);
     }
     return launch_q<BITS, lane_elems(BITS), 256, 0>(codec, stream, x, n_elems, group, c, scales, zeros);
 }
@@ -85,8 +161,6 @@ hipError_t launch_quantize(int bits, int codec, const void *x_f16, int64_t n_ele
                            void *codes, float *scales, float *zeros, hipStream_t stream)
 {
     if (codec == CODEC_FP8 && bits != 8) return hipErrorInvalidValue;
-    if (is_wide_group(bits, group))
-        return launch_quantize_wide(bits, codec, x_f16, n_elems, group, codes, scales, zeros, stream);
     const uint16_t *x = static_cast<const uint16_t *>(x_f16);
     uint8_t *c = static_cast<uint8_t *>(codes);
     if (bits == 4) return launch_q_bits<4>(codec, stream, x, n_elems, group, c, scales, zeros);
