@@ -52,7 +52,7 @@ __global__ __launch_bounds__(SPANS ? 1024 : kBlockThreads) void k_quantize_small
 {
     constexpr int E = 8;
     __shared__ float slot[SPANS ? 16 : 1][2];
-    const int64_t e = ((int64_t)blockIdx.x * (SPANS ? (int)blockDim.x : kBlockThreads) + threadIdx.x) * E;
+    const int64_t e = (SPANS ? (int64_t)blockIdx.x << group_shift : (int64_t)blockIdx.x * (kBlockThreads * E)) + threadIdx.x * E;
     const bool live = SPANS || e < n_elems;
     const u32x4 raw = *reinterpret_cast<const u32x4 *>(x + (live ? e : 0));
     float v[E];
@@ -65,7 +65,7 @@ __global__ __launch_bounds__(SPANS ? 1024 : kBlockThreads) void k_quantize_small
     float mn, mx, s, inv, zf = 0.0f;
     u32 word[BITS / 4];
     lane_minmax(v, mn, mx);
-    if constexpr (SPANS) span_minmax(mn, mx, slot);
+    if constexpr (SPANS) span_minmax(mn, mx, (u32)lpg >> 6, slot);
     else group_minmax<0>(mn, mx, lpg);
     if constexpr (CODEC == kFp8) {
         group_params_absmax<448>(fmaxf(fabsf(mn), fabsf(mx)), s, inv);

@@ -75,20 +75,24 @@ static hipError_t launch_nl(const FusedArgs &a, hipStream_t stream)
             static_cast<uint8_t *>(a.codes_out), a.scales_out, a.zeros_out);
 }
 
+template <int CODEC, int NSRC, int BT>
+static hipError_t launch_small_bt(const FusedArgs &a, int64_t blocks, int threads, int lane_elems, hipStream_t stream)
+{
+    return launch_kernel(k_fused_small<CODEC, FC_BITS_IN, FC_BITS_OUT, NSRC, BT>, dim3((unsigned)blocks), dim3(threads), stream,
+            static_cast<const uint8_t *>(a.codes_in), a.codes_stride, a.scales_in, a.zeros_in,
+            a.meta_stride, a.n_elems, log2_int(a.group), a.group / lane_elems,
+            static_cast<uint8_t *>(a.codes_out), a.scales_out, a.zeros_out);
+}
+
 template <int CODEC, int NSRC>
 static hipError_t launch_small(const FusedArgs &a, hipStream_t stream)
 {
     if (a.group > fused_small_wave_elems(FC_BITS_IN))
-        return launch_kernel(k_fused_small<CODEC, FC_BITS_IN, FC_BITS_OUT, NSRC, true>, dim3((unsigned)(a.n_elems / a.group)), dim3(a.group / 8),
-                stream, static_cast<const uint8_t *>(a.codes_in), a.codes_stride, a.scales_in, a.zeros_in,
-                a.meta_stride, a.n_elems, log2_int(a.group), a.group / 8,
-                static_cast<uint8_t *>(a.codes_out), a.scales_out, a.zeros_out);
-    const int64_t wave_elems = fused_small_wave_elems(FC_BITS_IN);
-    const int64_t waves = (a.n_elems + wave_elems - 1) / wave_elems;
-    return launch_kernel(k_fused_small<CODEC, FC_BITS_IN, FC_BITS_OUT, NSRC, false>, dim3((unsigned)waves), dim3(64), stream,
-            static_cast<const uint8_t *>(a.codes_in), a.codes_stride, a.scales_in, a.zeros_in,
-            a.meta_stride, a.n_elems, log2_int(a.group), a.group / fused_small_lane_elems(FC_BITS_IN),
-            static_cast<uint8_t *>(a.codes_out), a.scales_out, a.zeros_out);
+        return launch_small_bt<CODEC, NSRC, 0>(a, a.n_elems / a.group, a.group / 8, 8, stream);
+    const int64_t wave_elems = fused_small_wave_elems(FC_BITS_IN), waves = (a.n_elems + wave_elems - 1) / wave_elems;
+    const int lane_elems = fused_small_lane_elems(FC_BITS_IN);
+    if (waves <= kFusedSmallAlone) return launch_small_bt<CODEC, NSRC, 64>(a, waves, 64, lane_elems, stream);
+    return launch_small_bt<CODEC, NSRC, kBlockThreads>(a, (waves + kBlockWaves - 1) / kBlockWaves, kBlockThreads, lane_elems, stream);
 }
 
 // one instantiation per group width in lanes: 1 ... 128 lanes in 128-thread workgroups, 256 lanes in

@@ -20,39 +20,33 @@ constexpr int fused_small_lane_elems(int bits_in) { return 32 / bits_in; }
 constexpr int fused_small_wave_elems(int bits_in) { return 64 * fused_small_lane_elems(bits_in); }
 // Up to how many wavefronts of this kernel, in units of 1024 (one per SIMD of the part), a launch takes it rather than the
 // bulk kernel, whose wavefronts hold four times the elements: past that many the bulk kernel's shorter instruction stream per element
-// counts more than the number of wavefronts.  By lanes to a group and number of sources; us under graph replay, bulk / this one, at 2048,
-// 3072, 4096, 6144 wavefronts, hidden 4096:
-//   4 lanes (groups of 32 at 4 bit) and 16:
-//     asymmetric 4 -> 4 bit  N = 1 2.56 / 2.47, 2.77 / 2.91; N = 2 2.83 / 2.74, 3.24 / 3.04, 3.35 / 3.34; N = 3 3.38 / 2.88, 3.63 / 3.16,
-//       3.65 / 3.45, 3.98 / 4.10; N = 4 3.59 / 3.01, 3.88 / 3.36, 3.93 / 3.74, 4.33 / 4.46; N = 8 4.15 / 3.78, 5.22 / 4.39, 5.34 / 5.03, 5.84 /
-//       6.45; compact metadata and 4 -> 8 bit cross at the same places
-//     symmetric 4 -> 4 bit  N = 2 2.55 / 2.76, 3.15 / 3.08, 3.26 / 3.35; N = 3 3.07 / 2.74, 3.60 / 2.99, 3.67 / 3.26, 3.89 / 3.76; N = 4
-//       3.23 / 2.80, 3.94 / 3.06, 3.94 / 3.37, 4.27 / 3.91; N = 8 3.99 / 3.35, 5.10 / 3.97, 5.25 / 4.46, 5.72 / 5.29
-//     8 -> 8 bit, N = 3  asymmetric 2.94 / 2.69, 3.32 / 2.93, 3.41 / 3.18; symmetric 2.76 / 2.58, 3.03 / 2.83, 3.07 / 3.04; compact metadata
-//       2.78 / 2.88, 3.19 / 3.14, 3.25 / 3.38; FP8 2.74 / 2.58, 2.88 / 2.83, 2.95 / 3.04; N = 4  2.95 / 2.80, 3.35 / 3.08, 3.40 / 3.43; FP8 2.69 /
-//       2.58, 3.02 / 2.84, 3.09 / 3.05; N = 8  3.53 / 3.44, 4.14 / 3.96, 4.35 / 4.61; FP8 3.19 / 2.98, 3.69 / 3.46, 3.92 / 3.86
-//   32 and 64 lanes (groups of 128 and 256 at 8 bit, of 256 and 512 at 4 bit), the same order of entries:
-//     asymmetric 4 -> 4 bit  N = 2 2.78 / 2.81, 3.22 / 3.29; N = 3 3.27 / 3.07, 3.57 / 3.40, 3.62 / 3.68; N = 4 3.58 / 3.17, 3.86 / 3.50,
-//       3.95 / 3.85, 4.31 / 4.58; N = 8 4.06 / 3.79, 5.16 / 4.27, 5.30 / 4.85, 5.81 / 6.06; symmetric N = 4 3.24 / 2.92, 3.92 / 3.21, 3.92 / 3.51,
-//       4.27 / 4.07; N = 8 4.00 / 3.36, 5.07 / 3.84, 5.26 / 4.26, 5.64 / 5.13
-//     8 -> 8 bit  asymmetric N = 3 2.79 / 2.87; N = 4 2.97 / 2.94, 3.39 / 3.19, 3.41 / 3.46; N = 6 3.22 / 3.18, 3.73 / 3.51, 3.86 / 3.84; N = 8
-//       3.40 / 3.42, 4.07 / 3.81, 4.25 / 4.34; symmetric N = 6 3.14 / 2.88, 3.63 / 3.10, 3.75 / 3.40; FP8 N = 6 2.95 / 2.83, 3.31 / 3.06, 3.52 / 3.35;
-//       compact metadata N = 4 2.90 / 3.09, N = 6 3.21 / 3.04, 3.76 / 3.28, 3.84 / 3.62
+// counts more than the number of wavefronts.  Time against the bulk kernel's, per cent, replayed graphs, hidden 4096, at 1024 x 1.5, 2, 3, 4, 5,
+// 6, 7 wavefronts (us at 3072: asymmetric 4 -> 4 bit, N = 4, group 128 3.88 / 3.07):
+//   16 lanes to a group (128 elements at 4 bit, 64 at 8 bit)
+//     asymmetric 4 -> 4 bit  N = 2 -23 -19 -19 -13 -12 -8 -3; N = 4 -26 -23 -21 -16 -14 -11 -5; N = 8 -25 -21 -29 -19 -12 -6 -2
+//       4 -> 8 bit  N = 1 -13 -10 -3 +4 +4 +11; N = 2 -20 -13 -15 -8 -5 -2 +5; N = 4 -25 -21 -18 -12 -8 -2 +7; N = 8 -24 -19 -26 -13 -11 -2 +3
+//     symmetric 4 -> 4 bit  N = 2 -13 -10 -20 -16 -14 -11 -6; N = 8 -28 -24 -31 -24 -19 -12 -6
+//     compact metadata 4 -> 4 bit  N = 2 -18 -19 -17 -9 -5 +1 +6; N = 8 -18 -13 -20 -9 -1 +8 +13
+//     8 -> 8 bit, asymmetric  N = 2 -17 -17 -20 -17 -19 -16 -14; N = 4 -17 -15 -18 -15 -13 -11 -8; N = 8 -21 -17 -21 -15 -7 +1; symmetric N = 4 -15 -14 -21 -18 -16
+//       -15 -12; FP8 N = 1 -2 -1 -5 -6 -5 -3 +1; N = 4 -13 -12 -16 -14 -12 -12 -10; compact metadata N = 4 -13 -11 -16 -11 -10 -4 -1
+//   64 lanes (512 and 256 elements), the same order
+//     asymmetric 4 -> 4 bit  N = 2 -16 -8 -12 -6 -3 +1 +6; N = 8 -20 -16 -22 -12 -10 -4 +6; 4 -> 8 bit  N = 4 -20 -19 -14 -4 +0 +4 +10
+//     symmetric 4 -> 4 bit  N = 4 -19 -16 -24 -18 -13 -11 -6; compact metadata  N = 4 -18 -16 -12 -4 +2 +5 +15
+//     8 -> 8 bit, asymmetric  N = 4 -12 -9 -13 -7 -4 -2 -1; N = 8 -14 -10 -13 -8 -3 +7; compact metadata  N = 4 -7 -4 -10 -5 -3 +5 +7; FP8 N = 1 +0 +1 +0 -4 -1 +2
+// Workgroups of 256 threads start faster than four of 64 (N = 8 4 -> 4 bit 1.5 M elements 4.29 / 3.64 us, N = 4 1/4 M 2.35 / 2.14, 2 M 3.69 / 3.27), except
+// that a wavefront has a compute unit to itself in the smallest launches (N = 8 10 K elements 2.22 / 2.30): 64 threads up to kFusedSmallAlone wavefronts.
+// The number is a constant of the kernel: as an argument it costs 0.04 us, read from the launch's description 0.15 (1/4 M 2.70 / 2.53).
+constexpr int kFusedSmallAlone = 256;
 inline int fused_small_limit(int codec, int bits_in, int n_src, bool wide)
 {
-    if (codec == CODEC_SYM && bits_in == 4 && n_src >= (wide ? 4 : 3)) return 6;
-    if (wide) return n_src >= 6 ? 4 : n_src >= 4 && (bits_in == 4 || codec == CODEC_ASYM) ? 3 : n_src == 3 && bits_in == 4 ? 3 : 2;
-    return n_src >= 4 ? 4 : n_src == 3 ? (bits_in == 4 ? 4 : 3) : n_src == 2 && bits_in == 4 ? 3 : 2;
+    if (n_src == 1) return bits_in == 8 ? 3 : 2;
+    if (bits_in == 8) return wide ? 5 : 6;
+    return codec == CODEC_SYM ? 6 : codec == CODEC_ASYMH ? 4 : 5;
 }
 
-// The other quantizers' bulk kernels read less metadata.  With few sources, and groups of 32 lanes and more to reduce here, they are
-// the faster ones from fewer wavefronts on (hidden 2048, g = 256, 2048 wavefronts, bulk / this one: 8 -> 8 bit, N = 2, symmetric
-// 2.37 / 2.57 us, FP8 2.32 / 2.58, compact metadata 2.50 / 2.72; N = 4 2.72 / 2.83 with compact metadata; N = 2 at 4 bit
-// 2.53 / 2.72, 2.74 / 2.89).  The forms cross at about 448
-// wavefronts per source at 8 bit, up to five sources, and twice that at 4 bit, up to two.  A volume of at most three workgroups of the bulk kernel starts sooner
-// there than as 24 of these (8 bit, one row of 4096, N = 1, FP8 2.24 / 2.40 us, symmetric 2.23 / 2.39; N = 3 2.27 / 2.37; compact
-// metadata N = 2 2.37 / 2.34; 6144: FP8 N = 3 2.28 / 2.39; 7168: 2.41 / 2.41); from four sources on its chain is too long.
-constexpr int kFusedSmallWavesPerSource = 448;
+// The other quantizers' bulk kernels read less metadata.  With few sources at 8 bit, a volume of at most three workgroups of the bulk kernel starts sooner
+// there (one to three sources, 16 to 24 wavefronts: symmetric and FP8 N = 1 and 2 3 to 5 per cent, FP8 N = 3 3, compact metadata N = 1 4); from four sources on
+// its chain is too long.
 constexpr int kFusedSmallMinWaves = 24;
 
 // Groups of several wavefronts (SPANS below): 8 elements per lane and one barrier, against 16 or 32 per lane in the bulk kernel, and against one
@@ -80,8 +74,7 @@ inline bool fused_small_applies(int codec, int bits_in, int n_src, int64_t n_ele
     const bool wide = group >= 32 * fused_small_lane_elems(bits_in);
     if (waves > fused_small_limit(codec, bits_in, n_src, wide) * 1024) return false;
     if (codec != CODEC_ASYM && bits_in == 8 && n_src <= (codec == CODEC_ASYMH ? 1 : 3) && waves <= kFusedSmallMinWaves) return false;
-    if (codec == CODEC_ASYM || !wide || n_src > (bits_in == 8 ? 5 : 2)) return true;
-    return waves <= n_src * kFusedSmallWavesPerSource * (8 / bits_in);
+    return true;
 }
 
 // Codes of the lane as numbers, before the scale: q - z, the signed code, or the value of the E4M3 byte
@@ -108,10 +101,10 @@ __device__ __forceinline__ void small_decode(u32 w, float z, float *d)
 
 // min and max of a group that is the whole workgroup, up to 16 wavefronts (identical in all lanes): in the wavefront, then every lane takes
 // one wavefront's pair
-__device__ __forceinline__ void span_minmax(float &mn, float &mx, float (*slot)[2])
+__device__ __forceinline__ void span_minmax(float &mn, float &mx, u32 n_waves, float (*slot)[2])
 {
     group_minmax<0>(mn, mx, 64);
-    const u32 n_waves = blockDim.x >> 6, lane = threadIdx.x & 63u;
+    const u32 lane = threadIdx.x & 63u;
     if (lane == 0) {
         slot[threadIdx.x >> 6][0] = mn;
         slot[threadIdx.x >> 6][1] = mx;
@@ -122,20 +115,21 @@ __device__ __forceinline__ void span_minmax(float &mn, float &mx, float (*slot)[
     group_minmax<0>(mn, mx, (int)n_waves);
 }
 
-// SPANS: a group takes several wavefronts, which are the workgroup; 8 elements per lane
-template <int CODEC, int BITS_IN, int BITS_OUT, int NSRC, bool SPANS>
-__global__ __launch_bounds__(SPANS ? 1024 : 64) void k_fused_small(
+// BT: threads per workgroup, or 0 (SPANS): a group takes several wavefronts, which are the workgroup; 8 elements per lane
+template <int CODEC, int BITS_IN, int BITS_OUT, int NSRC, int BT>
+__global__ __launch_bounds__(BT == 0 ? 1024 : BT) void k_fused_small(
     const uint8_t *__restrict__ codes_in, int64_t codes_stride,
     const float *__restrict__ scales_in, const float *__restrict__ zeros_in, int64_t meta_stride,
     int64_t n_elems, int group_shift, int lpg,
     uint8_t *__restrict__ codes_out, float *__restrict__ scales_out, float *__restrict__ zeros_out)
 {
+    constexpr bool SPANS = BT == 0;
     constexpr int E = SPANS ? 8 : fused_small_lane_elems(BITS_IN);
     constexpr int W = E * BITS_IN / 32;                         // code words per lane and source
     constexpr int kOutBytes = E * BITS_OUT / 8;                 // 2, 4 or 8 code bytes per lane
     __shared__ float slot[SPANS ? 16 : 1][2];
     const u32 lane = threadIdx.x;                               // of the workgroup
-    const int64_t e_wave = (int64_t)blockIdx.x * ((SPANS ? (int)blockDim.x : 64) * E);
+    const int64_t e_wave = SPANS ? (int64_t)blockIdx.x << group_shift : (int64_t)blockIdx.x * (BT * E);
     const int64_t e_lane = e_wave + (int64_t)lane * E;
     const bool live = e_lane < n_elems;                         // (the volume is a multiple of the group, hence of E)
     const int64_t n_groups = n_elems >> group_shift;
@@ -177,7 +171,7 @@ __global__ __launch_bounds__(SPANS ? 1024 : 64) void k_fused_small(
     if constexpr (is_asym(CODEC)) {
         float mn, mx;
         lane_minmax(acc, mn, mx);
-        if constexpr (SPANS) span_minmax(mn, mx, slot);
+        if constexpr (SPANS) span_minmax(mn, mx, (u32)lpg >> 6, slot);
         else group_minmax<0>(mn, mx, lpg);
         group_params<BITS_OUT, CODEC == kAsymH>(mn, mx, s2, inv, zf);
 #pragma unroll
@@ -186,7 +180,7 @@ __global__ __launch_bounds__(SPANS ? 1024 : 64) void k_fused_small(
         float amax = lane_absmax(acc);
         if constexpr (SPANS) {
             float lo = -amax;
-            span_minmax(lo, amax, slot);
+            span_minmax(lo, amax, (u32)lpg >> 6, slot);
         } else {
             amax = group_max<0>(amax, lpg);
         }

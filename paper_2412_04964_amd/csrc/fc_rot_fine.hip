@@ -305,7 +305,7 @@ __global__ __launch_bounds__(1024) void k_allreduce_rot_fine(const uint16_t *__r
     const u32 lane = threadIdx.x & 63u;
     const u32 wave_all = (u32)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const u32 wave = wave_all % (u32)kWaves, part = wave_all / (u32)kWaves;
-    const int n_parts = (int)(blockDim.x / (64u * kWaves));
+    const int n_parts = n_src < 16 / kWaves ? n_src : 16 / kWaves;
     uint8_t *mine = lds + part * (2 * kArea);
     float (*slot)[2] = slots + part * kWaves;
     const RotLane L = rot_lane<true>(lane);

@@ -126,6 +126,12 @@ __device__ __forceinline__ u32 after_loads(u32 lane)
 // SPREAD: a wavefront's dequantized codes and scales, from the part that has a source to the one that sums.  Runs of 1 KB; the lanes keep their places.
 constexpr int kRotHandBytes = 8 * 1024 + 256;
 constexpr int rot_part_bytes(int lb) { return rot_block_waves(lb) * (kRotHandBytes + kRotSlots * 8); }
+// Sources that a workgroup of SPREAD works on at once: 1024 threads at most, and rot_part_bytes each in 160 KB
+__host__ __device__ constexpr int rot_parts(int lb, int n_src)
+{
+    const int most = lb == 13 ? 4 : 8;
+    return n_src < most ? n_src : most;
+}
 __device__ __forceinline__ void rot_hand_over(const float (&d)[4][8], float s, uint8_t *to, u32 lane)
 {
 #pragma unroll
@@ -173,7 +179,7 @@ __global__ __launch_bounds__(SPREAD ? 1024 : 64 * rot_group_waves(LB)) __attribu
     const u32 wave_all = (u32)__builtin_amdgcn_readfirstlane((int)(tid >> 6));
     const u32 wave = SPREAD ? wave_all % (u32)kWaves : wave_all;        // of the block
     const u32 part = SPREAD ? wave_all / (u32)kWaves : 0u;
-    const int n_parts = SPREAD ? (int)(blockDim.x / (64u * kWaves)) : 1;
+    const int n_parts = SPREAD ? rot_parts(LB, n_src) : 1;
     uint8_t *pieces = SPREAD ? parts + part * rot_part_bytes(LB) : own;
     float (*mm)[kRotSlots][2] = SPREAD ? reinterpret_cast<float (*)[kRotSlots][2]>(pieces + kWaves * kRotHandBytes) : own_mm;
     const u32 tile = xcd_tile<kChunk>((u32)((n_elems + kTile - 1) / kTile));
@@ -321,13 +327,6 @@ RotLevels levels(int codec, int bits)
 {
     const float q = codec == CODEC_FP8 ? 448.0f : (float)((1 << (codec == CODEC_SYM ? bits - 1 : bits)) - 1);
     return RotLevels{q, 1.0f / q};
-}
-
-// Sources that a workgroup of SPREAD works on at once: 1024 threads at most, and rot_part_bytes each in 160 KB
-constexpr int rot_parts(int lb, int n_src)
-{
-    const int most = lb == 13 ? 4 : 8;
-    return n_src < most ? n_src : most;
 }
 
 // Up to 2^21 elements, and no more than one round of workgroups (16 wavefronts of 128 registers per compute unit), where neither the steps of

@@ -42,7 +42,7 @@ def test_fused_on_both_sides_of_every_limit(fc, name, n_src):
             want = [dev(np.ascontiguousarray(a).view(np.uint8))
                     for a in getattr(oracle, "dequant_reduce_requant" + sfx)(*few, h, g, *bits)]
             few = [dev(a.view(np.int32)) if a.dtype == np.uint32 else dev(a) for a in few]
-            for k in (2, 3, 4, 6):
+            for k in (2, 3, 4, 5, 6):
                 limit = k * 1024 * (2048 // bits_in) // h
                 for rows in (limit, limit + 1):
                     pick = torch.arange(rows, device="cuda") % t
