@@ -335,20 +335,26 @@ int rot_steps(int codec, const void *x_f16, int n_src, int64_t tokens, int64_t h
 // three sources of FP8 in blocks of 8192 (11.5 / 12.1).  In blocks of 1024 the steps would win as much (8 x 1 x 5120 14.8 / 10.4), but
 // that call leaves the caller's workspace alone, which the tests hold it to.
 // These figures are those of three launches, before the last two of them became one, and of the one launch with one source after the other
-// everywhere (by now side by side in small volumes, rot_spread_applies); the limits have stayed, since callers may count on when the workspace
+// everywhere (by now side by side in small volumes, rot_spread_applies); most limits have stayed, since callers may count on when the workspace
 // is written.  us, three launches / two: INT4, group 128, block 2048  N = 4  1/4 M 7.46 / 6.18;  N = 8  1/4 M 8.65 / 7.50   1 M 12.74 / 10.91;  block
 // 4096  N = 4  1/2 M 9.18 / 7.92;  N = 8  1.5 M 16.10 / 14.40;  block 8192  N = 4  1/2 M 10.37 / 9.47;  N = 8  1 M 14.23 / 13.01;  FP8  block 1024
 // N = 4  1/4 M 7.15 / 5.65   1.5 M 12.68 / 11.02;  block 4096  N = 8  3 M 27.02 / 25.35.
+// With today's forms, two launches / one, lie the limits of six and seven sources, and FP8's of four: INT4, block 1024  N = 6  1/2 M 8.29 / 6.66   1 M 9.73 / 8.30
+// 1.25 M 10.64 / 13.85   2 M 14.09 / 14.25;  N = 7  1 M 10.12 / 8.60   2.25 M 17.63 / 16.10;  block 2048  N = 7  1/8 M 6.35 / 6.62   1/2 M 8.37 / 7.25   2 M 16.06 / 17.93;
+// block 4096  N = 6  1/2 M 8.83 / 8.71   1 M 10.40 / 9.48   1.5 M 12.73 / 16.14   2.25 M 17.81 / 17.60;  N = 7  2 M 16.92 / 18.41;  block 8192  N = 6  1/2 M 10.40 / 14.68   1.5 M
+// 13.37 / 15.44   2 M 16.08 / 16.06;  N = 7  1.5 M 14.84 / 15.83   1.75 M 16.46 / 16.16;  FP8  N = 4  block 1024  1/2 M 6.93 / 4.90   2 M 12.23 / 9.96;  block 4096  1/2 M
+// 7.66 / 8.06   1 M 9.79 / 8.68   2 M 13.34 / 12.01;  N = 6  block 1024  1 M 10.55 / 9.01   1.25 M 11.48 / 16.87.
 bool rot_steps_apply(int codec, int n_src, int64_t n_elems, int64_t hidden, int group)
 {
     //                                           n_src 3  4   5   6   7   8
-    static constexpr unsigned char kLimit[2][3][6] = {{{0, 4, 8, 24, 28, 32}, {0, 8, 28, 32, 32, 32}, {0, 8, 16, 18, 21, 28}},
-                                                      {{7, 28, 32, 34, 40, 40}, {8, 32, 40, 40, 44, 48}, {6, 18, 24, 40, 44, 48}}};
+    static constexpr unsigned char kLimit[2][3][6] = {{{0, 4, 8, 32, 36, 32}, {0, 8, 28, 35, 36, 32}, {0, 8, 16, 30, 28, 28}},
+                                                      {{7, 0, 32, 34, 40, 40}, {8, 8, 40, 40, 44, 48}, {6, 18, 24, 40, 44, 48}}};
     static_assert(FC_MAX_SRC == 8, "one column per fan-in");
     if (n_src < 3) return false;
     const bool fp8 = codec == fc::CODEC_FP8;
     const int block = fc::rotation_block(hidden);
     const int row = block == 8192 ? 2 : block == 4096 ? 1 : 0;
+    if (row == 0 && (n_src == 6 || n_src == 7) && n_elems <= (int64_t)1 << 20) return false;
     int limit = kLimit[fp8][row][n_src - 3];
     if (!fp8 && n_src == 4 && group >= 1024 && row < 2) limit = 4 * row;
     const bool padded = n_elems / group % 4 != 0;
