@@ -162,9 +162,8 @@ __device__ __forceinline__ void rot_take_over(const uint8_t *from, u32 lane, flo
 // has several times the wavefronts of a block, each such part works on a source of its own, and the first one sums what the others hand over
 // through LDS, in source order as ever, and goes on alone.  For rot_spread_applies.
 template <int CODEC, bool ALONE, int LB, bool SPREAD>
-__global__ __launch_bounds__(SPREAD ? 1024 : 64 * rot_group_waves(LB)) __attribute__((amdgpu_waves_per_eu(4))) void k_allreduce_rot(
-    const uint16_t *__restrict__ x, int64_t n_elems, int n_src, int group_shift, RotLevels rs, RotLevels ag,
-    uint16_t *__restrict__ y)
+__device__ __forceinline__ void allreduce_rot(const uint16_t *__restrict__ x, int64_t n_elems, int n_src, int group_shift, RotLevels rs,
+                                              RotLevels ag, uint16_t *__restrict__ y)
 {
     constexpr bool FP8 = CODEC == kFp8, SWAPS = FP8 || ALONE;           // see rot_swaps_apply
     constexpr RotOrder kOrder = ALONE ? kFlat : LB >= 12 ? kPinned : kRaised;
@@ -321,6 +320,22 @@ __global__ __launch_bounds__(SPREAD ? 1024 : 64 * rot_group_waves(LB)) __attribu
     }
 }
 
+template <int CODEC, bool ALONE, int LB>
+__global__ __launch_bounds__(64 * rot_group_waves(LB)) __attribute__((amdgpu_waves_per_eu(4))) void k_allreduce_rot(
+    const uint16_t *__restrict__ x, int64_t n_elems, int n_src, int group_shift, RotLevels rs, RotLevels ag,
+    uint16_t *__restrict__ y)
+{
+    allreduce_rot<CODEC, ALONE, LB, false>(x, n_elems, n_src, group_shift, rs, ag, y);
+}
+
+template <int CODEC, int LB>
+__global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4))) void k_allreduce_rot_spread(
+    const uint16_t *__restrict__ x, int64_t n_elems, int n_src, int group_shift, RotLevels rs, RotLevels ag,
+    uint16_t *__restrict__ y)
+{
+    allreduce_rot<CODEC, true, LB, true>(x, n_elems, n_src, group_shift, rs, ag, y);
+}
+
 namespace {
 
 RotLevels levels(int codec, int bits)
@@ -352,7 +367,7 @@ hipError_t launch_spread(const uint16_t *x, int n_src, int64_t n_elems, int grou
 {
     constexpr int kWaves = rot_block_waves(LB), kTile = 2048 * kWaves;
     const int parts = rot_parts(LB, n_src);
-    return launch_kernel_lds(k_allreduce_rot<CODEC, true, LB, true>, dim3((unsigned)((n_elems + kTile - 1) / kTile)),
+    return launch_kernel_lds(k_allreduce_rot_spread<CODEC, LB>, dim3((unsigned)((n_elems + kTile - 1) / kTile)),
                              dim3(64 * kWaves * parts), (size_t)rot_part_bytes(LB) * parts, stream, x, n_elems, n_src,
                              log2_int(group), rs, ag, y);
 }
@@ -366,8 +381,8 @@ hipError_t launch_one(const uint16_t *x, int n_src, int64_t n_elems, int group, 
     const dim3 grid((unsigned)((n_elems + kTile - 1) / kTile)), block(64 * rot_group_waves(LB));
     if constexpr (LB == 13)                // see k_allreduce_rot; a single source, the others go side by side
         if (n_elems <= 256 * (int64_t)kTile)
-            return launch_kernel(k_allreduce_rot<CODEC, true, LB, false>, grid, block, stream, x, n_elems, n_src, log2_int(group), rs, ag, y);
-    return launch_kernel(k_allreduce_rot<CODEC, false, LB, false>, grid, block, stream, x, n_elems, n_src, log2_int(group), rs, ag, y);
+            return launch_kernel(k_allreduce_rot<CODEC, true, LB>, grid, block, stream, x, n_elems, n_src, log2_int(group), rs, ag, y);
+    return launch_kernel(k_allreduce_rot<CODEC, false, LB>, grid, block, stream, x, n_elems, n_src, log2_int(group), rs, ag, y);
 }
 
 template <int CODEC>

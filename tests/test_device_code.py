@@ -93,6 +93,15 @@ def test_partial_rotation_tiles_have_no_scalar_offset(kernels):
     assert seen == 2 * (5 + 5 + 3)                 # two blocks; quantizer and dequantizer with five codes, all-reduce with three
 
 
+def test_partial_tiles_of_sources_side_by_side_have_no_scalar_offset(kernels):
+    # the same for the form of the all-reduce in which the sources of a block go side by side
+    spread = {name: body for name, body in kernels.items() if re.search(r"allreduce_rot_spreadI.*ELi1[01]EE", name)}
+    assert len(spread) == 2 * 3
+    for name, body in spread.items():
+        bad = [i for i in body if scalar_offset(i)]
+        assert not bad, "%s: %s" % (name, bad[0])
+
+
 def registers(operand):
     """v7 -> {7}, v[4:7] -> {4, 5, 6, 7}; anything else -> empty"""
     m = re.fullmatch(r"v(?:(\d+)|\[(\d+):(\d+)\])", operand)
