@@ -4,7 +4,7 @@
 // figure; rotation table of Section 4).
 //
 // One workgroup owns one group.  It is 128 or 256 threads wide and walks the
-// group in P sub-tiles of blockDim.x 128-bit code pieces, so every global access
+// group in P sub-tiles of as many 128-bit code pieces, so every global access
 // stays one coalesced 16 bytes per lane; the lane's values of all P sub-tiles
 // stay in registers between the min/max pass and the packing pass.  min/max are
 // reduced in the lane, across the wavefront (DPP / shuffles), then across the
@@ -17,7 +17,11 @@
 
 namespace fc {
 
-// min and max over the whole workgroup; every wavefront must call it once
+// The workgroup's size is a constant of the kernels: blockDim comes from the launch's description, a load more before the first address, and
+// brings 14 hidden arguments along.  us, so read / so: quantize 8 bit, group 2048, 3 M elements 3.96 / 3.82; 4 bit, group 4096, 4 M 4.42 / 4.29, 16 M 10.13 / 9.49;
+// fused 8 -> 8 bit, N = 4, group 8192, 4.5 M 8.59 / 7.90, 16 M 18.99 / 17.54; FP8, N = 2  8 M 7.15 / 6.45.
+// min and max over the whole workgroup of BT threads; every wavefront must call it once
+template <int BT>
 __device__ __forceinline__ void block_minmax(float &mn, float &mx, float (*slot)[2], u32 wave, u32 lane)
 {
     group_minmax<0>(mn, mx, 64);
@@ -26,7 +30,7 @@ __device__ __forceinline__ void block_minmax(float &mn, float &mx, float (*slot)
         slot[wave][1] = mx;
     }
     __syncthreads();
-    const u32 n_waves = blockDim.x >> 6;
+    constexpr u32 n_waves = BT / 64;
     for (u32 w = 0; w < n_waves; ++w) {
         mn = fminf(mn, slot[w][0]);
         mx = fmaxf(mx, slot[w][1]);
@@ -34,19 +38,19 @@ __device__ __forceinline__ void block_minmax(float &mn, float &mx, float (*slot)
 }
 
 // FinegrainedQuantize of binary16 input, one group per workgroup.
-template <int BITS, int P, int CODEC>
-__global__ __launch_bounds__(kBlockThreads) void k_quantize_wide(
+template <int BITS, int P, int CODEC, int BT>
+__global__ __launch_bounds__(BT) void k_quantize_wide(
     const uint16_t *__restrict__ x, int group, uint8_t *__restrict__ codes,
     float *__restrict__ scales, float *__restrict__ zeros)
 {
     constexpr int EPL = lane_elems(BITS);
     constexpr int kPieces = EPL * 2 / 16;                       // 1 KB input pieces per wavefront
-    __shared__ __attribute__((aligned(16))) uint8_t img[P][kBlockWaves][kPieces * 1024];
-    __shared__ float slot[kBlockWaves][2];
+    __shared__ __attribute__((aligned(16))) uint8_t img[P][BT / 64][kPieces * 1024];
+    __shared__ float slot[BT / 64][2];
 
     const u32 tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
     const int64_t e0 = (int64_t)blockIdx.x * group;
-    const u32 sub_elems = blockDim.x * EPL;
+    const u32 sub_elems = (u32)BT * EPL;
     const rsrc_t rx = make_rsrc(x + e0, (int64_t)group * 2);
     const rsrc_t rc = make_rsrc(codes + e0 * BITS / 8, (int64_t)group * BITS / 8);
 
@@ -82,7 +86,7 @@ __global__ __launch_bounds__(kBlockThreads) void k_quantize_wide(
         mn = fminf(mn, a);
         mx = fmaxf(mx, b);
     }
-    block_minmax(mn, mx, slot, wave, lane);
+    block_minmax<BT>(mn, mx, slot, wave, lane);
 
     float s, inv, zf = 0.0f;
     if constexpr (CODEC == kFp8)
@@ -101,7 +105,7 @@ __global__ __launch_bounds__(kBlockThreads) void k_quantize_wide(
         else
             pack_lane<BITS, EPL>(v[p], inv, zf, mx, word);
         __builtin_amdgcn_raw_buffer_store_b128(u32x4{word[0], word[1], word[2], word[3]}, rc,
-                                               (p * blockDim.x + tid) * 16, 0, kStreamStorePolicy);
+                                               (p * (u32)BT + tid) * 16, 0, kStreamStorePolicy);
     }
     if (tid == 0) {
         scales[blockIdx.x] = CODEC == kAsymH ? __builtin_bit_cast(float, pack_meta(s, zf)) : s;
@@ -146,7 +150,7 @@ __global__ __launch_bounds__(kBlockThreads) void k_dequant_reduce_requant_wide(
                 const rsrc_t r = make_rsrc(base + (int64_t)(j0 + d) * codes_stride, in_bytes);
 #pragma unroll
                 for (int p = 0; p < P; ++p)
-                    dst[d][p] = __builtin_amdgcn_raw_buffer_load_b128(r, (p * blockDim.x + tid) * 16, 0,
+                    dst[d][p] = __builtin_amdgcn_raw_buffer_load_b128(r, (p * (u32)kBlockThreads + tid) * 16, 0,
                                                                       kStreamLoadPolicy);
             }
     };
@@ -210,7 +214,7 @@ __global__ __launch_bounds__(kBlockThreads) void k_dequant_reduce_requant_wide(
         mn = fminf(mn, a);
         mx = fmaxf(mx, b);
     }
-    block_minmax(mn, mx, slot, wave, lane);
+    block_minmax<kBlockThreads>(mn, mx, slot, wave, lane);
 
     float s, inv, zf = 0.0f;
     if constexpr (CODEC == kFp8)
@@ -221,7 +225,7 @@ __global__ __launch_bounds__(kBlockThreads) void k_dequant_reduce_requant_wide(
         group_params<BITS_OUT, CODEC == kAsymH>(mn, mx, s, inv, zf);
 
     const int64_t out_bytes = (int64_t)group * BITS_OUT / 8;
-    const u32 sub_out = blockDim.x * kOutBytes;               // output bytes of one sub-tile
+    const u32 sub_out = (u32)kBlockThreads * kOutBytes;               // output bytes of one sub-tile
 #pragma unroll
     for (int p = 0; p < P; ++p) {
         u32 word[EPL * BITS_OUT / 32];
@@ -269,11 +273,13 @@ hipError_t quantize_wide_bits(const uint16_t *x, int64_t n_elems, int group, uin
     const WideShape w = wide_shape(BITS, group);
     const dim3 grid((unsigned)(n_elems / group)), block(w.threads);
     switch (w.p) {
-    case 1: return launch_kernel(k_quantize_wide<BITS, 1, CODEC>, grid, block, stream, x, group, c, scales, zeros);
-    case 2: return launch_kernel(k_quantize_wide<BITS, 2, CODEC>, grid, block, stream, x, group, c, scales, zeros);
+    case 1:
+        if (w.threads == 128) return launch_kernel(k_quantize_wide<BITS, 1, CODEC, 128>, grid, block, stream, x, group, c, scales, zeros);
+        return launch_kernel(k_quantize_wide<BITS, 1, CODEC, 256>, grid, block, stream, x, group, c, scales, zeros);
+    case 2: return launch_kernel(k_quantize_wide<BITS, 2, CODEC, 256>, grid, block, stream, x, group, c, scales, zeros);
     case 4:
         if constexpr (BITS == 8)
-            return launch_kernel(k_quantize_wide<BITS, 4, CODEC>, grid, block, stream, x, group, c, scales, zeros);
+            return launch_kernel(k_quantize_wide<BITS, 4, CODEC, 256>, grid, block, stream, x, group, c, scales, zeros);
         [[fallthrough]];
     default: return hipErrorInvalidValue;
     }
@@ -283,15 +289,14 @@ template <int BI, int BO, int CODEC>
 hipError_t fused_wide_bits(const FusedArgs &a, hipStream_t stream)
 {
     const WideShape w = wide_shape(BI, a.group);
-    const dim3 grid((unsigned)(a.n_elems / a.group)), block(w.threads);
+    const dim3 grid((unsigned)(a.n_elems / a.group)), block(kBlockThreads);
     const uint8_t *ci = static_cast<const uint8_t *>(a.codes_in);
     uint8_t *co = static_cast<uint8_t *>(a.codes_out);
 #define FC_WIDE_LAUNCH(PP)                                                                                  \
     launch_kernel(k_dequant_reduce_requant_wide<BI, BO, PP, CODEC>, grid, block, stream, ci, a.codes_stride, \
                   a.scales_in, a.zeros_in, a.meta_stride, a.n_src, a.group, co, a.scales_out, a.zeros_out)
     switch (w.p) {
-    case 1: return FC_WIDE_LAUNCH(1);
-    case 2: return FC_WIDE_LAUNCH(2);
+    case 2: return FC_WIDE_LAUNCH(2);      // fewer lanes: the kernel of fc_fused.hip
     case 4:
         if constexpr (BI == 8) return FC_WIDE_LAUNCH(4);
         [[fallthrough]];
