@@ -57,13 +57,13 @@ constexpr int kFusedSmallMinWaves = 24;
 //   group 4096: N = 4  1/2: 3.05 / 2.79   2: 4.08 / 3.80;   N = 8  1: 4.06 / 3.56.   group 8192: N = 4  1/4: 3.19 / 3.19   1: 3.42 / 3.53
 //   8 -> 8 bit, group 512: N = 8  1/4: 3.24 / 2.92   1/2: 3.36 / 3.20   1.5: 4.92 / 5.32;   N = 2  1/8: 2.33 / 2.23;   group 1024: N = 8  1/4: 3.21 / 2.99   1/2: 3.32 /
 //     3.47;   N = 4  1/64: 2.53 / 2.28   1/2: 2.84 / 2.98, FP8 1/4: 2.25 / 2.30;   group 4096: N = 4  1/4: 2.77 / 2.78
-//   group 8192: N = 2  1: 3.98 / 3.29   4: 5.47 / 5.33;   N = 4  1: 5.84 / 3.69   4: 7.97 / 7.17   6: 9.49 / 9.42;   N = 8  1/2: 8.44 / 4.30   4: 11.98 / 9.95;   FP8 N = 4
-//     1: 4.87 / 3.28   4: 6.84 / 6.38   6: 8.21 / 8.89
+//   group 8192: N = 1  2: 3.38 / 3.28   2.5: 3.82 / 3.87;   N = 2  1: 3.68 / 3.18   3.5: 4.89 / 4.67   4: 5.04 / 5.16;   N = 4  1: 4.60 / 3.57   3.5: 6.81 / 6.72   4: 7.12 / 6.99   5: 7.98 /
+//     8.64;   N = 8  1: 6.79 / 4.33   3.5: 9.69 / 9.51   5: 11.33 / 12.10;   FP8 N = 4  1: 3.82 / 3.22   3.5: 5.79 / 5.63   4: 6.10 / 6.35;   N = 8  2: 6.29 / 5.80   2.5: 7.30 / 7.55
 inline bool fused_spans_applies(int codec, int bits_in, int n_src, int64_t n_elems, int group)
 {
     constexpr int64_t k1M = (int64_t)1 << 20;
     if (bits_in == 4) return group <= 4096 && n_elems <= (n_src <= 2 ? k1M * 3 / 4 : codec == CODEC_ASYMH ? k1M * 3 / 2 : 2 * k1M);
-    if (group == 8192) return n_elems <= 4 * k1M;
+    if (group == 8192) return n_elems <= (n_src == 1 || (codec == CODEC_FP8 && n_src >= 6) ? 4 : 7) * (k1M / 2);
     return group <= 2048 && n_elems <= (n_src >= 5 ? k1M / 4 : n_src >= 2 ? k1M / 8 : 0);
 }
 

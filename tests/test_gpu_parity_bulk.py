@@ -1,5 +1,5 @@
 """The fused step's cases once more at volumes past every limit of its launch-bound kernel (at most 6144 wavefronts of 512
-four-bit elements, 3 * 2^20, or 2^22 in groups of 8192), where the bulk kernels take them; and both kernels on the two sides of each limit.  Run with
+four-bit elements, 3 * 2^20, or 7 * 2^19 in groups of 8192), where the bulk kernels take them; and both kernels on the two sides of each limit.  Run with
 ``-m gpu`` on an MI355X."""
 import numpy as np
 import pytest
@@ -59,7 +59,7 @@ def test_fused_on_both_sides_of_every_limit(fc, name, n_src):
 @pytest.mark.parametrize("name", ["asym"] + list(PAIRS))
 @pytest.mark.parametrize("n_src", [1, 2, 3, 5, 8])
 @pytest.mark.parametrize("bits_in, group, limits", [(4, 1024, (3 << 18, 3 << 19, 2 << 20)), (4, 4096, (3 << 18, 3 << 19, 2 << 20)),
-                                                    (8, 512, (1 << 17, 1 << 18)), (8, 2048, (1 << 17, 1 << 18)), (8, 8192, (4 << 20,))])
+                                                    (8, 512, (1 << 17, 1 << 18)), (8, 2048, (1 << 17, 1 << 18)), (8, 8192, (2 << 20, 7 << 19))])
 def test_fused_groups_of_several_wavefronts(fc, name, n_src, bits_in, group, limits):
     # a group that is a workgroup up to these volumes, the bulk kernels' above them
     t, h = 7, max(4096, group)
