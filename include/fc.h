@@ -41,7 +41,8 @@
  *     on the calling thread must own the buffers and the stream.
  *   - bits in {4, 8};  group a power of two in [32, 16384] (group == hidden: one group per token);
  *     hidden % group == 0;  tokens >= 0 (0 is a no-op returning FC_OK);
- *     tokens*hidden <= 2^36;  1 <= n_src <= FC_MAX_SRC.
+ *     tokens*hidden <= 2^36 (exactly 2^36 may be refused with FC_ERR_HIP: plain steps on 8-bit codes, and
+ *     fc_allreduce_sim* without rotation);  1 <= n_src <= FC_MAX_SRC.
  *   - Inputs must be finite.  NaN / Inf inputs give unspecified codes.
  *   - Return value: FC_OK or a negative FC_ERR_* code.  Argument checks come
  *     first and make no HIP call, so they work on a host without a GPU.

@@ -23,7 +23,9 @@ thread_local int g_last_hip_error = 0;
 constexpr int kMaxDevices = 64;
 std::atomic<void *> g_scratch_ptr[kMaxDevices];     // device address of `scratch`, per device
 
-constexpr int64_t kMaxElems = (int64_t)1 << 36;   // keeps grid*block below 2^32 threads
+// Keeps a launch below 2^32 threads, the runtime's limit, where a thread has more than 16 elements; a kernel with 16 takes any volume
+// below this one, and the launch of exactly this many is refused (FC_ERR_HIP).
+constexpr int64_t kMaxElems = (int64_t)1 << 36;
 
 bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 

@@ -29,6 +29,7 @@ struct QuantizeForm {
 };
 static QuantizeForm quantize_form(int64_t n_elems, int group)
 {
+    if (n_elems / 16 >= (int64_t)1 << 32) return {32, 256};             // more threads than the runtime launches
     if (group <= 128) return {16, n_elems <= kOneRound ? 128 : 64};
     if (group <= 1024 && n_elems >= 3 * kOneRound) return {16, 64};
     return {32, group == 256 ? 128 : 256};
@@ -146,11 +147,11 @@ static hipError_t launch_q_bits(int codec, hipStream_t stream, const uint16_t *x
     if (is_wide_group(BITS, group)) return launch_quantize_wide(BITS, codec, x, n_elems, group, c, scales, zeros, stream);
     if constexpr (BITS == 4) {
         const QuantizeForm f = quantize_form(n_elems, group);
-        if (group <= 128)
+        if (group <= 128 && f.epl == 16)
             return f.threads == 64 ? launch_q_narrow<4, 64>(codec, stream, x, n_elems, group, c, scales, zeros)
                                    : launch_q_narrow<4, 128>(codec, stream, x, n_elems, group, c, scales, zeros);
         if (f.epl == 16) return launch_q<4, 16, 64, 0>(codec, stream, x, n_elems, group, c, scales, zeros);
-        if (group == 256) return launch_q<4, 32, 128, 8>(codec, stream, x, n_elems, group, c, scales, zeros);
+        if (f.threads == 128) return launch_q<4, 32, 128, 8>(codec, stream, x, n_elems, group, c, scales, zeros);
     } else if (group <= 128) {
         return launch_q_narrow<8, 256>(codec, stream, x, n_elems, group, c, scales, zeros);
     }
