@@ -11,18 +11,18 @@ namespace fc {
 // 20 52.0); symmetric 128 M 57.8 / 52.6.  8-bit codes write half as much as they read, and no limit gains anything.
 static bool limits_wavefronts(int bits, int64_t n_elems) { return bits == 4 && n_elems >= (int64_t)36 << 20; }
 
-// Elements per lane and threads per workgroup of the quantizer for 4-bit codes, past quantize_small_applies.  A wavefront waits for all that it reads before it computes, so the
-// finer its tile the earlier arithmetic and stores begin, and the more evenly the memory system is asked; a wider tile has fewer reductions
-// and metadata per element, which counts where a group spans 16 lanes or more.  us by elements (2^20), hidden 8192, 16 elements per lane in
-// workgroups of 64 / 128 / 256 threads, and 32 elements in workgroups of 128:
-//   4-bit codes, group 32      1: 2.69 2.77 2.73 2.89   4: 3.89 3.89 3.86 4.01   8: 5.81 5.77 5.80 5.86   12: 7.49 7.76 7.86 7.75   24: 12.2 12.5 12.7 13.0
-//                group 128  1/4: 2.13 2.24 2.30 2.42    6: 4.83 4.71 4.79 4.82   8: 5.70 5.60 5.68 5.70   10: 6.48 6.75 6.85 6.43   32: 15.4 15.2 15.4 15.8
-//                          128: 52.6 52.9 53.9 53.6 (with fewer wavefronts per compute unit than fit: 53.8 with 24, 58 with 20)
-//   16 elements in workgroups of 64, and 32 in workgroups of 256 (of 128 for group 256):
-//                group 256    6: 4.93 4.79   16: 8.99 8.89   24: 12.10 12.22   32: 15.36 15.67   128: 52.4 53.5
-//                group 1024   6: 4.97 4.85   16: 8.92 8.98   24: 11.98 12.25   32: 15.08 15.67   128: 51.3 54.0
-//   8-bit codes have 16 elements in any case; workgroups of 64 and of 256: group 32  4: 4.29 4.10   16: 10.37 10.40   64: 33.3 33.5;   group 128  3: 3.55 3.49
-//     32: 18.1 17.7
+// Elements per lane and threads per workgroup of the quantizer for 4-bit codes, past quantize_small_applies.  A wavefront waits for
+// all that it reads before it computes, so the finer its tile the earlier arithmetic and stores begin, and the more evenly the memory
+// system is asked; a wider tile has fewer reductions and metadata per element, which counts where a group spans 16 lanes or more.
+// Replayed graphs over two or three buffer sets / over 700 MB of them, us by elements (2^20), hidden 8192:
+//   groups of up to 128, 32 elements per lane in workgroups of 128; 16 in workgroups of 64 / 256 (128 threads lie between)
+//     asymmetric, group 128   4.5: 3.24, 3.55 / 3.28   6: 3.72, 4.20 / 3.60   8: 4.72, 4.96 / 4.64   10: 5.81, 5.91 / 6.13
+//       16: 8.31, 8.65 / 8.61   40: 19.5, 19.1 / 19.2   64: 30.2, 29.1 / 29.1;   700 MB  6: 3.93, 4.28 / 3.82   10: 6.54, 6.62 / 6.85
+//       24: 12.8, 12.4 / 12.6   64: 30.2, 29.2 / 29.5
+//     symmetric, group 32     4.5: 3.13, 3.41 / 3.09   8: 4.69, 4.83 / 4.56   10: 5.75, 5.70 / 6.03   24: 11.3, 10.9 / 11.2
+//   groups of 256 to 1024, 32 elements / 16 in workgroups of 64
+//     asymmetric, group 256   24: 11.2 / 11.9   32: 15.3 / 15.7   36: 17.9 / 17.5   64: 29.9 / 29.1;   700 MB  24: 12.6 / 12.4   40: 19.8 / 19.3
+//     group 1024              32: 14.7 / 15.1   36: 17.3 / 17.1   64: 29.8 / 28.1
 constexpr int64_t kOneRound = (int64_t)8 << 20;          // elements that 256 compute units of 32 wavefronts hold, at 16 per lane
 struct QuantizeForm {
     int epl, threads;
@@ -30,21 +30,29 @@ struct QuantizeForm {
 static QuantizeForm quantize_form(int64_t n_elems, int group)
 {
     if (n_elems / 16 >= (int64_t)1 << 32) return {32, 256};             // more threads than the runtime launches
-    if (group <= 128) return {16, n_elems <= kOneRound ? 128 : 64};
-    if (group <= 1024 && n_elems >= 3 * kOneRound) return {16, 64};
+    if (group <= 128) return {16, n_elems <= kOneRound ? 256 : 64};
+    if (group <= 1024 && n_elems >= (int64_t)36 << 20) return {16, 64};
     return {32, group == 256 ? 128 : 256};
 }
 
-// Few elements: 8 per lane, loaded straight into registers instead of through LDS, since a lane's 16 bytes are one access.  us by elements (2^20),
-// hidden 8192, the other forms / this one: 4-bit codes, group 32  1/8: 2.09 / 2.03   1/2: 2.54 / 2.23   1: 2.68 / 2.34   2: 3.05 / 2.77   2.5: 3.24 / 3.19   3: 3.42 / 3.44;
-// group 128  1: 2.72 / 2.37   2: 3.05 / 2.66   2.5: 3.27 / 3.14;   group 256  1/2: 2.70 / 2.32   2.5: 3.44 / 3.30;   8-bit codes, group 32  1/2: 2.53 / 2.28   1: 2.72 /
-// 2.35   1.5: 2.89 / 2.59   2: 3.06 / 3.17;   group 256  1.5: 3.00 / 2.71   2: 3.11 / 3.20.  Workgroups of 64 instead of 256 threads: 1 M 2.44, 2 M 3.00.
-// SPANS, a group of more than 512 is a workgroup, its wavefronts exchange minimum and maximum with one barrier: 4-bit codes, group 1024  1/8: 2.55 / 2.09   1: 2.95 / 2.50   2: 3.25 /
-// 3.00   3: 3.79 / 3.98;   group 2048  1: 2.98 / 2.47   3: 3.83 / 3.69   4: 4.08 / 4.49;   group 8192  1/4: 3.05 / 2.30   1: 3.35 / 2.72   3: 4.33 / 3.84   4: 4.57 / 4.53;   8-bit codes,
-// group 1024  1: 2.89 / 2.55   1.5: 3.12 / 2.90   2: 3.25 / 3.28;   group 4096  1/4: 2.54 / 2.21   2: 3.59 / 3.24   3: 4.03 / 4.36.
-static bool quantize_small_applies(int bits, int64_t n_elems, int group)
+// Few elements: 8 per lane, loaded straight into registers instead of through LDS, since a lane's 16 bytes are one access.  SPANS, a
+// group of more than 512 is a workgroup, its wavefronts exchange minimum and maximum with one barrier.  The limits by how the two sides
+// cross; the quantizers without a zero-point have less to compute per lane and cross earlier.  us by elements (2^20), hidden 8192, the
+// other forms / this one:
+//   4-bit codes, group 128: asymmetric  1/8: 2.09 / 2.03   1: 2.72 / 2.31   2.5: 2.61 / 2.38   3: 2.64 / 2.57   4: 2.76 / 2.85   4.5: 3.24 / 3.20
+//     5: 3.44 / 3.48, over 700 MB  3: 3.03 / 2.71   4: 3.14 / 3.09   5: 3.54 / 3.70;   symmetric  4: 2.60 / 2.69, 700 MB 2.98 / 2.93
+//   group 256, 512: 2.5: 2.60 / 2.57   3.5: 2.63 / 2.91;   group 1024: symmetric, 700 MB  1.5: +3 %   2.5: +7 %
+//   group 8192: asymmetric  1: 3.35 / 2.72   3: 4.33 / 3.84;   symmetric  2: -7 %   2.5: +4 %
+//   8-bit codes, group 32: 1/2: 2.53 / 2.28   1: 2.72 / 2.35;   group 256: asymmetric  1.5: 3.00 / 2.71, symmetric +3 %
+//   group 1024: 1: 2.89 / 2.55   1.25: +2 to +5 %   1.5: +6 to +9 %;   group 4096: 1/4: 2.54 / 2.21   2: 3.59 / 3.24   3: 4.03 / 4.36
+static bool quantize_small_applies(int codec, int bits, int64_t n_elems, int group)
 {
-    const int halves = (bits == 4 ? 5 : 3) + (group >= 2048 ? 1 : 0);    // of 2^20 elements
+    const bool zero_point = codec == CODEC_ASYM || codec == CODEC_ASYMH;
+    int halves;                                                          // of 2^20 elements
+    if (bits == 4)
+        halves = group <= 128 ? 8 : group <= 512 ? 5 : group == 1024 ? 3 : zero_point ? 6 : group == 2048 ? 3 : 4;
+    else
+        halves = group >= 2048 ? 4 : zero_point && group <= 512 ? 3 : 2;
     return group <= 8192 && n_elems <= halves * ((int64_t)1 << 19);
 }
 template <int BITS, int CODEC, bool SPANS>
@@ -141,7 +149,7 @@ template <int BITS>
 static hipError_t launch_q_bits(int codec, hipStream_t stream, const uint16_t *x, int64_t n_elems, int group,
                                 uint8_t *c, float *scales, float *zeros)
 {
-    if (quantize_small_applies(BITS, n_elems, group))
+    if (quantize_small_applies(codec, BITS, n_elems, group))
         return group > 512 ? launch_q_small<BITS, true>(codec, stream, x, n_elems, group, c, scales, zeros)
                            : launch_q_small<BITS, false>(codec, stream, x, n_elems, group, c, scales, zeros);
     if (is_wide_group(BITS, group)) return launch_quantize_wide(BITS, codec, x, n_elems, group, c, scales, zeros, stream);
@@ -149,7 +157,7 @@ static hipError_t launch_q_bits(int codec, hipStream_t stream, const uint16_t *x
         const QuantizeForm f = quantize_form(n_elems, group);
         if (group <= 128 && f.epl == 16)
             return f.threads == 64 ? launch_q_narrow<4, 64>(codec, stream, x, n_elems, group, c, scales, zeros)
-                                   : launch_q_narrow<4, 128>(codec, stream, x, n_elems, group, c, scales, zeros);
+                                   : launch_q_narrow<4, 256>(codec, stream, x, n_elems, group, c, scales, zeros);
         if (f.epl == 16) return launch_q<4, 16, 64, 0>(codec, stream, x, n_elems, group, c, scales, zeros);
         if (f.threads == 128) return launch_q<4, 32, 128, 8>(codec, stream, x, n_elems, group, c, scales, zeros);
     } else if (group <= 128) {

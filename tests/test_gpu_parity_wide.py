@@ -409,9 +409,10 @@ def test_codecs_where_a_launch_limits_its_wavefronts(fc, variant, group):
 
 @pytest.mark.parametrize("variant", ["asym", "sym", "cmeta", "fp8"])
 @pytest.mark.parametrize("bits, group, limits", [
-    (4, 32, (5 << 19, 8 << 20)), (4, 64, (8 << 20,)), (4, 128, (5 << 19, 8 << 20)), (4, 256, (5 << 19, 24 << 20)), (4, 512, (5 << 19,)),
-    (4, 1024, (5 << 19, 8 << 20, 24 << 20)), (4, 2048, (6 << 19, 8 << 20, 24 << 20)), (4, 8192, (6 << 19,)), (8, 32, (3 << 19,)),
-    (8, 128, (3 << 19,)), (8, 512, (3 << 19,)), (8, 1024, (3 << 19,)), (8, 2048, (4 << 19,)), (8, 8192, (4 << 19,))])
+    (4, 32, (4 << 20, 8 << 20)), (4, 64, (4 << 20, 8 << 20)), (4, 128, (4 << 20, 8 << 20)), (4, 256, (5 << 19, 36 << 20)), (4, 512, (5 << 19,)),
+    (4, 1024, (3 << 19, 8 << 20, 36 << 20)), (4, 2048, (3 << 19, 6 << 19, 8 << 20, 36 << 20)), (4, 8192, (4 << 19, 6 << 19)),
+    (8, 32, (1 << 20, 3 << 19)), (8, 128, (1 << 20, 3 << 19)), (8, 512, (1 << 20, 3 << 19)), (8, 1024, (1 << 20,)), (8, 2048, (4 << 19,)),
+    (8, 8192, (4 << 19,))])
 def test_codecs_on_both_sides_of_every_limit(fc, variant, bits, group, limits):
     # the tiles of quantizer and dequantizer follow volume and group: the same rows over and over, of a length that leaves ragged tiles
     if variant == "fp8" and bits != 8:

@@ -23,3 +23,25 @@ def test_the_largest_4_bit_volume_is_launched(quantizer, group):
     for call in (quantize(quantizer, 1 << 36, group, 4), dequantize(quantizer, 1 << 36, group, 4), fused(quantizer, 2, 1 << 36, group, 4, 4)):
         (rc, seen), = launches([call])
         assert rc == 0 and len(seen) == 1, "%s: %d %s" % (call[0], rc, seen)
+
+
+def forms(make, limits):
+    """limits: [(what make takes, elements, the kernel's beginning up to there, the beginning above)].  One row of 8192 is one step"""
+    calls = [make(*what, elems) for what, limit, _, _ in limits for elems in (limit, limit + 8192)]
+    got = kernels(*calls)
+    for (what, limit, upto, above), a, b in zip(limits, got[::2], got[1::2]):
+        assert a[0].startswith(upto) and b[0].startswith(above), "%s at %.2f M elements: %s, then %s" % (what, limit / M, a, b)
+
+
+def test_quantizer_forms():
+    # 8 elements per lane; 16 in workgroups of 256; 16 in workgroups of 64; 32
+    forms(lambda q, bits, group, elems: quantize(q, elems, group, bits), [
+        (("asym", 4, 128), 4 * M, "k_quantize_small<4,0,0>", "k_quantize<4,8,0,16,256>"), (("asym", 4, 128), 8 * M, "k_quantize<4,8,0,16,256>", "k_quantize<4,8,0,16,64>"),
+        (("sym", 4, 32), 4 * M, "k_quantize_small<4,1,0>", "k_quantize<4,2,1,16,256>"), (("cmeta", 4, 64), 8 * M, "k_quantize<4,4,3,16,256>", "k_quantize<4,4,3,16,64>"),
+        (("asym", 4, 256), 5 * M // 2, "k_quantize_small<4,0,0>", "k_quantize<4,8,0,32,128>"), (("asym", 4, 256), 36 * M - 8192, "k_quantize<4,8,0,32,128>", "k_quantize<4,0,0,16,64>"),
+        (("sym", 4, 512), 36 * M - 8192, "k_quantize<4,0,1,32,256>", "k_quantize<4,0,1,16,64>"), (("asym", 4, 1024), 3 * M // 2, "k_quantize_small<4,0,1>", "k_quantize<4,0,0,32,256>"),
+        (("cmeta", 4, 1024), 36 * M - 8192, "k_quantize<4,0,3,32,256>", "k_quantize<4,0,3,16,64>"), (("asym", 4, 2048), 3 * M, "k_quantize_small<4,0,1>", "k_quantize<4,0,0,32,256>"),
+        (("sym", 4, 2048), 3 * M // 2, "k_quantize_small<4,1,1>", "k_quantize<4,0,1,32,256>"), (("sym", 4, 8192), 2 * M, "k_quantize_small<4,1,1>", "k_quantize_wide<4,1,1,256>"),
+        (("asym", 8, 512), 3 * M // 2, "k_quantize_small<8,0,0>", "k_quantize<8,0,0,16,256>"), (("asym", 8, 1024), M, "k_quantize_small<8,0,1>", "k_quantize<8,0,0,16,256>"),
+        (("sym", 8, 256), M, "k_quantize_small<8,1,0>", "k_quantize<8,0,1,16,256>"), (("fp8", 8, 1024), M, "k_quantize_small<8,2,1>", "k_quantize<8,0,2,16,256>"),
+        (("sym", 8, 2048), 2 * M, "k_quantize_small<8,1,1>", "k_quantize_wide<8,1,1,128>")])
