@@ -274,7 +274,14 @@ hipError_t quantize_wide_bits(const uint16_t *x, int64_t n_elems, int group, uin
     const dim3 grid((unsigned)(n_elems / group)), block(w.threads);
     switch (w.p) {
     case 1:
-        if (w.threads == 128) return launch_kernel(k_quantize_wide<BITS, 1, CODEC, 128>, grid, block, stream, x, group, c, scales, zeros);
+        if (w.threads == 128) {
+            // 4-bit codes, many rounds of wavefronts: with all that fit more reads wait in the memory system than it serves well.  us by
+            // elements (2^20), group 4096, as many workgroups per compute unit as fit / 10:  24: 11.7 / 12.4   32: 15.0 / 15.6   40: 20.1 / 19.4
+            // 48: 23.8 / 22.6   64: 30.6 / 29.4;  over 700 MB of buffers  32: 16.8 / 16.5   40: 20.4 / 20.0   64: 30.9 / 29.5.  8-bit codes lose with 10 or 8.
+            const size_t own = sizeof(float) * 4 + 128 * lane_elems(BITS) * 2;
+            const size_t pad = BITS == 4 && n_elems >= (int64_t)36 << 20 ? lds_to_limit(10, own) : 0;
+            return launch_kernel_lds(k_quantize_wide<BITS, 1, CODEC, 128>, grid, block, pad, stream, x, group, c, scales, zeros);
+        }
         return launch_kernel(k_quantize_wide<BITS, 1, CODEC, 256>, grid, block, stream, x, group, c, scales, zeros);
     case 2: return launch_kernel(k_quantize_wide<BITS, 2, CODEC, 256>, grid, block, stream, x, group, c, scales, zeros);
     case 4:

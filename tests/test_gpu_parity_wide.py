@@ -386,7 +386,7 @@ def test_value_distributions_end_to_end(fc, kind):
 
 
 @pytest.mark.parametrize("variant", ["asym", "sym", "cmeta"])
-@pytest.mark.parametrize("group", [32, 128, 1024])
+@pytest.mark.parametrize("group", [32, 128, 1024, 4096])
 def test_codecs_where_a_launch_limits_its_wavefronts(fc, variant, group):
     # 4-bit codes from 36 * 2^20 elements on; rows do not depend on each other: a few of them over and over
     hidden, rows = 4096, 23

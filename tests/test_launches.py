@@ -45,3 +45,12 @@ def test_quantizer_forms():
         (("asym", 8, 512), 3 * M // 2, "k_quantize_small<8,0,0>", "k_quantize<8,0,0,16,256>"), (("asym", 8, 1024), M, "k_quantize_small<8,0,1>", "k_quantize<8,0,0,16,256>"),
         (("sym", 8, 256), M, "k_quantize_small<8,1,0>", "k_quantize<8,0,1,16,256>"), (("fp8", 8, 1024), M, "k_quantize_small<8,2,1>", "k_quantize<8,0,2,16,256>"),
         (("sym", 8, 2048), 2 * M, "k_quantize_small<8,1,1>", "k_quantize_wide<8,1,1,128>")])
+
+
+def test_wide_quantizer_leaves_room_at_large_volumes():
+    # LDS beyond the kernel's own limits the workgroups per compute unit, 4-bit codes in groups of 4096 from 36 * 2^20 elements on
+    for quantizer, bits, elems, limited in (("asym", 4, 36 * M, True), ("sym", 4, 64 * M, True), ("cmeta", 4, 36 * M - 8192, False), ("asym", 8, 64 * M, False)):
+        (rc, seen), = launches([quantize(quantizer, elems, 16384 // bits, bits)])
+        assert rc == 0 and seen[0][0].startswith("k_quantize_wide<%d,1" % bits) and seen[0][2] == 128
+        room = 160 * 1024 // (seen[0][3] + 128 * (128 // bits) * 2 + 16)
+        assert (room == 10) == limited, "%s %d bits, %d elements: %d" % (quantizer, bits, elems, room)
