@@ -6,10 +6,11 @@
 namespace fc {
 
 // Dequantizer, 4-bit codes, volumes of many rounds of wavefronts: with all that fit more accesses wait in the memory system than it serves
-// well (see fc_sim.hip), and the launch limits the wavefronts per compute unit to 24, from 36 * 2^20 elements on.  us, without and with
-// so many, hidden 8192, group 128: 24 M elements 11.18 / 11.22, 40 M 18.52 / 18.47, 48 M 21.7 / 21.0, 64 M 28.5 / 27.3, 128 M 55.2 / 51.6 (with
-// 20 52.0); symmetric 128 M 57.8 / 52.6.  8-bit codes write half as much as they read, and no limit gains anything.
-static bool limits_wavefronts(int bits, int64_t n_elems) { return bits == 4 && n_elems >= (int64_t)36 << 20; }
+// well (see fc_sim.hip), and the launch limits the wavefronts per compute unit to 24, from 48 * 2^20 elements on.  us, without and with
+// so many, hidden 8192, group 128: 24 M elements 11.18 / 11.22, 48 M 21.7 / 21.0, 64 M 29.4 / 28.4, 128 M 55.2 / 51.6 (with 20 52.0);
+// symmetric 40 M 16.9 / 17.7 (over 700 MB of buffers 19.2 / 19.2), 64 M 29.4 / 28.4, 128 M 57.8 / 52.6.  8-bit codes write half as much as
+// they read, and no limit gains anything.
+static bool limits_wavefronts(int bits, int64_t n_elems) { return bits == 4 && n_elems >= (int64_t)48 << 20; }
 
 // Elements per lane and threads per workgroup of the quantizer for 4-bit codes, past quantize_small_applies.  A wavefront waits for
 // all that it reads before it computes, so the finer its tile the earlier arithmetic and stores begin, and the more evenly the memory
@@ -177,9 +178,12 @@ hipError_t launch_quantize(int bits, int codec, const void *x_f16, int64_t n_ele
 }
 
 // 4-bit codes: up to one round of wavefronts 16 elements per lane, for the reason given at quantize_form; above it 32 elements, whose
-// loads and stores are twice as wide.  us by elements (2^20), hidden 8192, 32 / 16 elements: group 32  1/4: 2.11 / 1.92   2: 2.76 / 2.67   6: 4.16 / 4.00
-// 8: 4.91 / 4.79   12: 6.41 / 6.96   32: 15.4 / 16.2;   group 128  1/4: 2.11 / 1.92   1: 2.39 / 2.22   6: 4.09 / 3.92   8: 4.79 / 4.65   12: 6.03 / 6.90.
-// Workgroups of 64 or 128 threads: from -2 to +25 %.  8-bit codes with 8 elements per lane: 1/4 M 1.94 / 1.87, 2 M 2.77 / 2.88, 8 M 5.28 / 6.58.
+// loads and stores are twice as wide.  Without zero-points to load the wide tile catches up sooner where the buffers are not cached, hence
+// another limit.  us by elements (2^20), hidden 8192, group 128, 32 / 16 elements (over 700 MB of buffers): asymmetric  1/4: 2.11 / 1.92
+// 1: 2.39 / 2.22   6: 3.52 / 3.46 (4.11 / 3.94)   8: 4.09 / 4.10 (4.76 / 4.67)   12: 6.03 / 6.90;   symmetric  4: 2.80 / 2.85 (3.19 / 3.01)   5: 3.10 / 3.05
+// (3.47 / 3.46)   6: 3.37 / 3.33 (3.76 / 3.94)   8: 3.95 / 3.92 (4.36 / 5.08);   binary16 metadata  8: 4.08 / 3.95 (4.42 / 4.67).  Workgroups of 64 or
+// 128 threads: from -2 to +25 %.  8-bit codes with 8 elements per lane: 1/4 M 1.94 / 1.87, 2 M 2.77 / 2.88, 8 M 5.28 / 6.58.
+static bool dequantize_narrow_applies(int codec, int64_t n_elems) { return n_elems <= (codec == CODEC_ASYM ? kOneRound : kOneRound * 5 / 8); }
 template <int BITS, int EPL>
 static hipError_t launch_dq(int codec, hipStream_t stream, const uint8_t *c, const float *scales, const float *zeros, int64_t n_elems,
                             int group_shift, uint16_t *y)
@@ -205,7 +209,7 @@ hipError_t launch_dequantize(int bits, int codec, const void *codes, const float
     uint16_t *y = static_cast<uint16_t *>(y_f16);
     const int sh = log2_int(group);
     if (bits == 8) return launch_dq<8, 16>(codec, stream, c, scales, zeros, n_elems, sh, y);
-    if (n_elems <= kOneRound) return launch_dq<4, 16>(codec, stream, c, scales, zeros, n_elems, sh, y);
+    if (dequantize_narrow_applies(codec, n_elems)) return launch_dq<4, 16>(codec, stream, c, scales, zeros, n_elems, sh, y);
     return launch_dq<4, 32>(codec, stream, c, scales, zeros, n_elems, sh, y);
 }
 

@@ -388,7 +388,8 @@ def test_value_distributions_end_to_end(fc, kind):
 @pytest.mark.parametrize("variant", ["asym", "sym", "cmeta"])
 @pytest.mark.parametrize("group", [32, 128, 1024, 4096])
 def test_codecs_where_a_launch_limits_its_wavefronts(fc, variant, group):
-    # 4-bit codes from 36 * 2^20 elements on; rows do not depend on each other: a few of them over and over
+    # 4-bit codes from 36 * 2^20 (quantizer, groups of 4096) and 48 * 2^20 elements on (dequantizer); rows do not depend on each other:
+    # a few of them over and over
     hidden, rows = 4096, 23
     sfx = "" if variant == "asym" else "_" + variant
     x = synth_inputs.make_partials(1, rows, hidden, seed=group, outlier_frac=0.01)[0]
@@ -397,7 +398,7 @@ def test_codecs_where_a_launch_limits_its_wavefronts(fc, variant, group):
     xd = torch.from_numpy(x.view(np.uint16)).cuda().view(torch.float16)
     want = [torch.from_numpy(np.ascontiguousarray(a).view(np.uint8)).cuda() for a in coded]
     want_y = torch.from_numpy(back.view(np.int16)).cuda()
-    for tokens in (36 * 256 - 1, 36 * 256, 36 * 256 + 1):
+    for tokens in (36 * 256 - 1, 36 * 256, 36 * 256 + 1, 48 * 256 - 1, 48 * 256, 48 * 256 + 1):
         at = torch.arange(tokens, device="cuda") % rows
         got = getattr(fc, "quantize" + sfx)(xd[at], group, 4)
         for g, w in zip(got, want):
@@ -409,7 +410,7 @@ def test_codecs_where_a_launch_limits_its_wavefronts(fc, variant, group):
 
 @pytest.mark.parametrize("variant", ["asym", "sym", "cmeta", "fp8"])
 @pytest.mark.parametrize("bits, group, limits", [
-    (4, 32, (4 << 20, 8 << 20)), (4, 64, (4 << 20, 8 << 20)), (4, 128, (4 << 20, 8 << 20)), (4, 256, (5 << 19, 36 << 20)), (4, 512, (5 << 19,)),
+    (4, 32, (4 << 20, 5 << 20, 8 << 20)), (4, 64, (4 << 20, 8 << 20)), (4, 128, (4 << 20, 5 << 20, 8 << 20)), (4, 256, (5 << 19, 36 << 20)), (4, 512, (5 << 19,)),
     (4, 1024, (3 << 19, 8 << 20, 36 << 20)), (4, 2048, (3 << 19, 6 << 19, 8 << 20, 36 << 20)), (4, 8192, (4 << 19, 6 << 19)),
     (8, 32, (1 << 20, 3 << 19)), (8, 128, (1 << 20, 3 << 19)), (8, 512, (1 << 20, 3 << 19)), (8, 1024, (1 << 20,)), (8, 2048, (4 << 19,)),
     (8, 8192, (4 << 19,))])

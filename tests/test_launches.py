@@ -54,3 +54,12 @@ def test_wide_quantizer_leaves_room_at_large_volumes():
         assert rc == 0 and seen[0][0].startswith("k_quantize_wide<%d,1" % bits) and seen[0][2] == 128
         room = 160 * 1024 // (seen[0][3] + 128 * (128 // bits) * 2 + 16)
         assert (room == 10) == limited, "%s %d bits, %d elements: %d" % (quantizer, bits, elems, room)
+
+
+def test_dequantizer_forms():
+    forms(lambda q, group, elems: dequantize(q, elems, group, 4), [
+        (("asym", 32), 8 * M, "k_dequantize<4,0,16>", "k_dequantize<4,0,32>"), (("sym", 128), 5 * M, "k_dequantize<4,1,16>", "k_dequantize<4,1,32>"),
+        (("cmeta", 8192), 5 * M, "k_dequantize<4,3,16>", "k_dequantize<4,3,32>")])
+    for elems, limited in ((48 * M - 8192, False), (48 * M, True)):
+        (rc, seen), = launches([dequantize("sym", elems, 128, 4)])
+        assert rc == 0 and (seen[0][3] > 0) == limited
