@@ -75,7 +75,7 @@ __global__ __launch_bounds__(kSimBlockThreads) void k_allreduce_fused(const uint
     const int64_t e_tile = (int64_t)tile * kSimTileElems;
     const int64_t left = (n_elems - e_tile) * 2;                       // bytes from the tile to the end of a partial
 
-auto fetch = [&](int j) {
+    auto fetch = [&](int j) {
         const rsrc_t rx = make_rsrc(x + (int64_t)j * n_elems + e_tile, left);
         dma_piece(rx, wave * kZone + lane * 16, &landing[wave][j % DEPTH][0]);
         dma_piece(rx, wave * kZone + 1024 + lane * 16, &landing[wave][j % DEPTH][1024]);
@@ -217,11 +217,13 @@ hipError_t launch_sim_src(const uint16_t *x, int64_t n_elems, int group, uint16_
 {
     const dim3 grid((unsigned)((n_elems + kSimTileElems - 1) / kSimTileElems)), block(kSimBlockThreads);
     const int lpg = group / kSimLaneElems;
-    // Many sources in less than two rounds of wavefronts: a wavefront's chain of loads bounds the call, two at a time shorten
-    // it (group 128, us, one / two at a time: N = 8 1.2 M elements 7.50 / 6.87, 2 M 9.14 / 8.45, 3 M 11.8 / 11.6, 4 M 13.7 / 14.5; N = 6
-    // 2 M 7.70 / 7.16; N = 4 1.2 M 4.99 / 4.89, 2 M 6.06 / 5.91, 4 M 8.89 / 9.26; all at once N = 8 2 M 9.88, 4 M 17.9, N = 4 9.62).
-    if constexpr (NSRC >= 5)
-        if (n_elems <= (int64_t)3 << 20)
+    // Less than two rounds of wavefronts: a wavefront's chain of loads bounds the call, two at a time shorten it.  us, group 128, all
+    // at once / one / two at a time: INT4 N = 2 (two are all)  3.5 M elements 4.81 / 5.08;  N = 3  2.5 M 5.00 / 5.41 / 4.90;  N = 4  2.5 M 6.14 /
+    // 6.27 / 5.82;  N = 6  2 M 6.95 / 6.97 / 5.95;  N = 8  1.25 M 6.84 / 7.24 / 6.57   3 M 13.97 / 10.73 / 10.36   4 M 16.69 / 12.99 / 13.35;  symmetric
+    // N = 4  1.75 M 4.38 / 4.87 / 4.02;  binary16 metadata N = 2  3.5 M 4.87 / 5.50;  N = 3  3.5 M 6.31 / 6.57 / 6.30;  N = 4  1.75 M 4.76 / 5.30 / 4.68   3 M 6.90 /
+    // 7.38 / 6.83.  Where the buffers are not cached (700 MB of them) one at a time is up to 8 % faster with two or three sources.
+    if constexpr (NSRC >= 2)
+        if (n_elems <= (int64_t)(NSRC <= 3 ? 7 : 6) << 19)
             return lpg == 8 ? launch_kernel(k_allreduce_fused<CODEC, BITS_RS, BITS_AG, NSRC, 8, 2>, grid, block, stream, x,
                                             n_elems, lpg, y)
                             : launch_kernel(k_allreduce_fused<CODEC, BITS_RS, BITS_AG, NSRC, 0, 2>, grid, block, stream, x,

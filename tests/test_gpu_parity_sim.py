@@ -318,22 +318,23 @@ def test_wide_groups_fill_the_chip(fc, name, group):
 
 
 # --------------------------------------------------------------------------- #
-# volumes where a launch takes another form: two partials ahead instead of one up to 3 * 2^20 elements (five sources and more),
-# a limited number of workgroups per compute unit from 18 * 2^20 on (groups of 2048 and more: 12 * 2^20)
+# volumes where a launch takes another form: two partials ahead instead of one up to 3.5 * 2^20 elements (two and three sources) or
+# 3 * 2^20 (more), a limited number of workgroups per compute unit from 18 * 2^20 on (groups of 2048 and more: 12 * 2^20)
 # --------------------------------------------------------------------------- #
 
 @pytest.mark.parametrize("name", ["asym", "sym", "fp8", "cmeta"])
-@pytest.mark.parametrize("n_src,group,limit", [(5, 128, 3), (6, 1024, 3), (8, 32, 3), (2, 128, 18), (4, 512, 18), (7, 32, 18),
+@pytest.mark.parametrize("n_src,group,limit", [(2, 32, 3.5), (2, 128, 3.5), (3, 128, 3.5), (3, 512, 3.5), (4, 128, 3), (5, 128, 3), (6, 1024, 3), (8, 32, 3), (2, 128, 18), (4, 512, 18), (7, 32, 18),
                                                (2, 2048, 12), (3, 8192, 12), (8, 4096, 12)])
 def test_volumes_where_the_form_changes(fc, name, n_src, group, limit):
     # rows do not depend on each other: the volume is a few rows over and over, and so is the result
     hidden, rows = 8192, 41
-    x = synth_inputs.make_partials(n_src, rows, hidden, seed=limit + group + n_src, outlier_frac=0.01)
+    x = synth_inputs.make_partials(n_src, rows, hidden, seed=int(limit) + group + n_src, outlier_frac=0.01)
     ref = oracle.allreduce_sim if name == "asym" else variant(fc, name)[1]
     sfx, bits = ("" if name == "asym" else "_" + name), bit_pairs(name)[0]
     want = dev16(ref(x, group, *bits)).view(torch.int16)
     base = dev16(x)
-    for tokens in (limit * 128 - 1, limit * 128, limit * 128 + 1):
+    limit = int(limit * 128)
+    for tokens in (limit - 1, limit, limit + 1):
         at = torch.arange(tokens, device="cuda") % rows
         y = torch.full((tokens, hidden), 7.0, dtype=torch.float16, device="cuda")
         getattr(fc, "allreduce_sim" + sfx)(base[:, at], group, *(() if name == "fp8" else bits), out=y)

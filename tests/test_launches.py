@@ -63,3 +63,13 @@ def test_dequantizer_forms():
     for elems, limited in ((48 * M - 8192, False), (48 * M, True)):
         (rc, seen), = launches([dequantize("sym", elems, 128, 4)])
         assert rc == 0 and (seen[0][3] > 0) == limited
+
+
+def test_partials_in_flight():
+    # the last template argument: two at a time up to 7 or 6 * 2^19 elements, one at a time above
+    forms(lambda q, n_src, group, elems: allreduce(q, n_src, elems, group, 8, 8), [
+        (("asym", 2, 128), 7 * M // 2, "k_allreduce_fused<0,8,8,2,8,2>", "k_allreduce_fused<0,8,8,2,8,1>"),
+        (("cmeta", 3, 32), 7 * M // 2, "k_allreduce_fused<3,8,8,3,0,2>", "k_allreduce_fused<3,8,8,3,0,1>"),
+        (("sym", 4, 128), 3 * M, "k_allreduce_fused<1,8,8,4,8,2>", "k_allreduce_fused<1,8,8,4,8,1>"),
+        (("fp8", 8, 512), 3 * M, "k_allreduce_fused<2,8,8,8,0,2>", "k_allreduce_fused<2,8,8,8,0,1>")])
+    assert kernels(allreduce("asym", 1, 2 * M, 128)) == [["k_allreduce_fused<0,8,8,1,8,1>"]]
