@@ -221,9 +221,10 @@ hipError_t launch_sim_src(const uint16_t *x, int64_t n_elems, int group, uint16_
     // at once / one / two at a time: INT4 N = 2 (two are all)  3.5 M elements 4.81 / 5.08;  N = 3  2.5 M 5.00 / 5.41 / 4.90;  N = 4  2.5 M 6.14 /
     // 6.27 / 5.82;  N = 6  2 M 6.95 / 6.97 / 5.95;  N = 8  1.25 M 6.84 / 7.24 / 6.57   3 M 13.97 / 10.73 / 10.36   4 M 16.69 / 12.99 / 13.35;  symmetric
     // N = 4  1.75 M 4.38 / 4.87 / 4.02;  binary16 metadata N = 2  3.5 M 4.87 / 5.50;  N = 3  3.5 M 6.31 / 6.57 / 6.30;  N = 4  1.75 M 4.76 / 5.30 / 4.68   3 M 6.90 /
-    // 7.38 / 6.83.  Where the buffers are not cached (700 MB of them) one at a time is up to 8 % faster with two or three sources.
+    // 7.38 / 6.83.  Where the buffers are not cached (700 MB of them) one at a time is up to 8 % faster with two or three sources; where two sets of them
+    // stay in the caches two at a time go on to win: symmetric N = 2  4 M 4.78 / 4.26, binary16 metadata N = 2  5 M 6.49 / 6.07, N = 4  3.5 M 7.60 / 7.03.
     if constexpr (NSRC >= 2)
-        if (n_elems <= (int64_t)(NSRC <= 3 ? 7 : 6) << 19)
+        if (n_elems <= (int64_t)(NSRC == 2 ? 10 : NSRC == 3 ? 8 : NSRC == 4 ? 7 : 6) << 19)
             return lpg == 8 ? launch_kernel(k_allreduce_fused<CODEC, BITS_RS, BITS_AG, NSRC, 8, 2>, grid, block, stream, x,
                                             n_elems, lpg, y)
                             : launch_kernel(k_allreduce_fused<CODEC, BITS_RS, BITS_AG, NSRC, 0, 2>, grid, block, stream, x,

@@ -318,12 +318,12 @@ def test_wide_groups_fill_the_chip(fc, name, group):
 
 
 # --------------------------------------------------------------------------- #
-# volumes where a launch takes another form: two partials ahead instead of one up to 3.5 * 2^20 elements (two and three sources) or
-# 3 * 2^20 (more), a limited number of workgroups per compute unit from 18 * 2^20 on (groups of 2048 and more: 12 * 2^20)
+# volumes where a launch takes another form: two partials ahead instead of one up to 5, 4, 3.5 and 3 * 2^20 elements (two, three, four
+# and more sources), a limited number of workgroups per compute unit from 18 * 2^20 on (groups of 2048 and more: 12 * 2^20)
 # --------------------------------------------------------------------------- #
 
 @pytest.mark.parametrize("name", ["asym", "sym", "fp8", "cmeta"])
-@pytest.mark.parametrize("n_src,group,limit", [(2, 32, 3.5), (2, 128, 3.5), (3, 128, 3.5), (3, 512, 3.5), (4, 128, 3), (5, 128, 3), (6, 1024, 3), (8, 32, 3), (2, 128, 18), (4, 512, 18), (7, 32, 18),
+@pytest.mark.parametrize("n_src,group,limit", [(2, 32, 5), (2, 128, 5), (3, 128, 4), (3, 512, 4), (4, 128, 3.5), (5, 128, 3), (6, 1024, 3), (8, 32, 3), (2, 128, 18), (4, 512, 18), (7, 32, 18),
                                                (2, 2048, 12), (3, 8192, 12), (8, 4096, 12)])
 def test_volumes_where_the_form_changes(fc, name, n_src, group, limit):
     # rows do not depend on each other: the volume is a few rows over and over, and so is the result

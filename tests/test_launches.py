@@ -66,10 +66,10 @@ def test_dequantizer_forms():
 
 
 def test_partials_in_flight():
-    # the last template argument: two at a time up to 7 or 6 * 2^19 elements, one at a time above
+    # the last template argument: two at a time up to 10 to 6 * 2^19 elements, one at a time above
     forms(lambda q, n_src, group, elems: allreduce(q, n_src, elems, group, 8, 8), [
-        (("asym", 2, 128), 7 * M // 2, "k_allreduce_fused<0,8,8,2,8,2>", "k_allreduce_fused<0,8,8,2,8,1>"),
-        (("cmeta", 3, 32), 7 * M // 2, "k_allreduce_fused<3,8,8,3,0,2>", "k_allreduce_fused<3,8,8,3,0,1>"),
-        (("sym", 4, 128), 3 * M, "k_allreduce_fused<1,8,8,4,8,2>", "k_allreduce_fused<1,8,8,4,8,1>"),
+        (("asym", 2, 128), 5 * M, "k_allreduce_fused<0,8,8,2,8,2>", "k_allreduce_fused<0,8,8,2,8,1>"),
+        (("cmeta", 3, 32), 4 * M, "k_allreduce_fused<3,8,8,3,0,2>", "k_allreduce_fused<3,8,8,3,0,1>"),
+        (("sym", 4, 128), 7 * M // 2, "k_allreduce_fused<1,8,8,4,8,2>", "k_allreduce_fused<1,8,8,4,8,1>"),
         (("fp8", 8, 512), 3 * M, "k_allreduce_fused<2,8,8,8,0,2>", "k_allreduce_fused<2,8,8,8,0,1>")])
     assert kernels(allreduce("asym", 1, 2 * M, 128)) == [["k_allreduce_fused<0,8,8,1,8,1>"]]
