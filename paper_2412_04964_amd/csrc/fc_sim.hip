@@ -200,16 +200,21 @@ namespace {
 
 constexpr int CODEC = FC_SIM_CODEC;
 
-// Workgroups that a compute unit shall hold at once, 0: as many as fit.  From 18 * 2^20 elements per partial on (over four
-// rounds of wavefronts) the chip would otherwise have more reads waiting than the memory system serves well.  With few sources
-// more of the wavefronts are at the start or the end of their tile, and the limit is higher.  INT4, group 128, us, without a limit and with so many workgroups: N = 2
-// 8192 x 8192 63.5, 10: 61.9, 8: 63.2, 7: 66.2; N = 3 86.0, 9: 82.7, 8: 82.0, 7: 85; N = 4 109.5, 8: 103.0, 7: 102.2; N = 5 131.8, 8:
-// 126.2, 7: 121.2, 6: 127.8; N = 6 151.8, 148.9, 142.2, 149.3; N = 8 205.4, 196.1, 187.9, 194.3.  N = 4 x 4096: 8 M elements 15.3 / 15.9
-// with 8, 16 M 28.4 / 28.9, 20 M 35.4 / 35.2, 24 M 42.3 / 41.2, 32 M 56.0 / 53.5.  N = 1: no gain from any limit.
-int sim_workgroups_per_unit(int n_src, int64_t n_elems)
+// Workgroups that a compute unit shall hold at once, 0: as many as fit.  From 18 * 2^20 elements per partial on (over four rounds of
+// wavefronts) the chip would otherwise have more reads waiting than the memory system serves well.  With few sources more of the
+// wavefronts are at the start or the end of their tile, and the limit is higher.  INT4, group 128, us, without a limit and with so many
+// workgroups: N = 2  8192 x 8192 63.5, 10: 61.9, 8: 63.2, 7: 66.2; N = 3 86.0, 9: 82.7, 8: 82.0, 7: 85; N = 4 109.5, 8: 103.0, 7: 102.2; N = 5 131.8,
+// 8: 126.2, 7: 121.2, 6: 127.8; N = 6 151.8, 148.9, 142.2, 149.3; N = 8 205.4, 196.1, 187.9, 194.3.  N = 4 x 4096: 8 M elements 15.3 / 15.9 with 8,
+// 16 M 28.4 / 28.9, 20 M 35.4 / 35.2, 24 M 42.3 / 41.2, 32 M 56.0 / 53.5.  N = 1: no gain from any limit.
+// A minimum and a maximum over more than 8 lanes take instructions that fewer wavefronts do not cover: asymmetric, group 512, N = 2
+// without / 10: 18 M 20.8 / 21.8, 32 M 34.6 / 35.7, 64 M 66.5 / 67.7 (group 32 66.6 / 66.1, symmetric 66.1 / 64.5); N = 6  8 / 7: 24 M 60.6 / 62.2,
+// 40 M 96.7 / 97.6.
+int sim_workgroups_per_unit(int n_src, int64_t n_elems, int group)
 {
     if (n_src == 1 || n_elems < (int64_t)18 << 20) return 0;
-    return n_src == 2 ? 10 : n_src <= 4 ? 8 : 7;
+    const bool more = is_asym(CODEC) && group > 128;
+    if (n_src == 2) return more ? 0 : 10;
+    return n_src <= 4 || (n_src == 6 && more) ? 8 : 7;
 }
 
 template <int BITS_RS, int BITS_AG, int NSRC>
@@ -229,7 +234,7 @@ hipError_t launch_sim_src(const uint16_t *x, int64_t n_elems, int group, uint16_
                                             n_elems, lpg, y)
                             : launch_kernel(k_allreduce_fused<CODEC, BITS_RS, BITS_AG, NSRC, 0, 2>, grid, block, stream, x,
                                             n_elems, lpg, y);
-    const size_t pad = lds_to_limit(sim_workgroups_per_unit(NSRC, n_elems), kSimTileElems * 2);
+    const size_t pad = lds_to_limit(sim_workgroups_per_unit(NSRC, n_elems, group), kSimTileElems * 2);
     if (lpg == 8)                                                      // g = 128: the lane pattern is a constant
         return launch_kernel_lds(k_allreduce_fused<CODEC, BITS_RS, BITS_AG, NSRC, 8, 1>, grid, block, pad, stream, x, n_elems,
                                  lpg, y);

@@ -323,7 +323,7 @@ def test_wide_groups_fill_the_chip(fc, name, group):
 # --------------------------------------------------------------------------- #
 
 @pytest.mark.parametrize("name", ["asym", "sym", "fp8", "cmeta"])
-@pytest.mark.parametrize("n_src,group,limit", [(2, 32, 5), (2, 128, 5), (3, 128, 4), (3, 512, 4), (4, 128, 3.5), (5, 128, 3), (6, 1024, 3), (8, 32, 3), (2, 128, 18), (4, 512, 18), (7, 32, 18),
+@pytest.mark.parametrize("n_src,group,limit", [(2, 32, 5), (2, 128, 5), (3, 128, 4), (3, 512, 4), (4, 128, 3.5), (5, 128, 3), (6, 1024, 3), (8, 32, 3), (2, 128, 18), (2, 512, 18), (6, 512, 18), (4, 512, 18), (7, 32, 18),
                                                (2, 2048, 12), (3, 8192, 12), (8, 4096, 12)])
 def test_volumes_where_the_form_changes(fc, name, n_src, group, limit):
     # rows do not depend on each other: the volume is a few rows over and over, and so is the result

@@ -73,3 +73,12 @@ def test_partials_in_flight():
         (("sym", 4, 128), 7 * M // 2, "k_allreduce_fused<1,8,8,4,8,2>", "k_allreduce_fused<1,8,8,4,8,1>"),
         (("fp8", 8, 512), 3 * M, "k_allreduce_fused<2,8,8,8,0,2>", "k_allreduce_fused<2,8,8,8,0,1>")])
     assert kernels(allreduce("asym", 1, 2 * M, 128)) == [["k_allreduce_fused<0,8,8,1,8,1>"]]
+
+
+def test_all_reduce_workgroups_per_compute_unit():
+    # 4 KB of LDS of the kernel's own; what the launch asks for beyond that leaves room for so many in 160 KB (0: asks for nothing)
+    cases = [("asym", 2, 18 * M, 128, 10), ("asym", 2, 18 * M, 512, 0), ("cmeta", 2, 64 * M, 256, 0), ("sym", 2, 64 * M, 512, 10), ("asym", 4, 18 * M, 512, 8),
+             ("asym", 6, 24 * M, 512, 8), ("asym", 6, 24 * M, 128, 7), ("fp8", 6, 24 * M, 512, 7), ("asym", 8, 24 * M, 512, 7), ("asym", 3, 18 * M - 8192, 128, 0)]
+    for case, (rc, seen) in zip(cases, launches([allreduce(q, n, elems, g) for q, n, elems, g, _ in cases])):
+        assert rc == 0 and seen[0][0].startswith("k_allreduce_fused")
+        assert (160 * 1024 // (seen[0][3] + 4096) if seen[0][3] else 0) == case[-1], "%s %s" % (case, seen)
