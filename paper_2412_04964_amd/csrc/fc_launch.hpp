@@ -153,13 +153,15 @@ FC_DECLARE_SIM(asym) FC_DECLARE_SIM(sym) FC_DECLARE_SIM(fp8) FC_DECLARE_SIM(cmet
 // the first kernel less.  us, fc_sim / fc_sim_wide, hidden 8192: INT4 N = 2 64 tokens 3.40 / 3.01, 400 5.61 / 5.29, 1000 10.11 / 10.50,
 // 2500 22.7 / 21.4, 8192 65.5 / 62.6; N = 4 8 tokens 3.99 / 3.14, 160 5.33 / 4.90, 400 8.13 / 7.82, 1000 15.9 / 15.7, 2500 36.9 / 35.1, 8192 105.7 /
 // 103.0; N = 8 8 tokens 5.75 / 4.19, 160 7.98 / 7.01, 260 9.90 / 9.81, 400 12.1 / 13.2; symmetric INT8 N = 2 400 tokens 4.96 / 5.29, N = 4
-// 8 tokens 3.66 / 2.99, 160 4.98 / 4.58, 400 7.63 / 7.72, 8192 103.5 / 103.6; FP8 N = 8 160 tokens 7.57 / 7.11, 400 11.8 / 13.3.
+// 8 tokens 3.66 / 2.99, 160 4.98 / 4.58, 400 7.63 / 7.72, 8192 103.5 / 103.6; FP8 N = 8 160 tokens 7.57 / 7.11, 400 11.8 / 13.3.  One source has nothing
+// to share: symmetric INT8 1 M 2.57 / 2.58, 1.25 M 2.53 / 2.67, FP8 1.5 M 2.72 / 2.86.
 inline bool allreduce_wide_applies(int codec, int n_src, int64_t n_elems, int group)
 {
     constexpr int64_t k1M = (int64_t)1 << 20;
     if (group != kFusedAllreduceMaxGroup) return group > kFusedAllreduceMaxGroup;
-    if (n_elems <= 3 * k1M / 2) return true;
-    return (codec == CODEC_ASYM || codec == CODEC_ASYMH) && n_src <= 4 && (n_elems <= 4 * k1M || n_elems >= 12 * k1M);
+    const bool asym = codec == CODEC_ASYM || codec == CODEC_ASYMH;
+    if (n_elems <= (n_src == 1 ? 2 : 3) * k1M / 2) return true;
+    return asym && n_src <= 4 && (n_elems <= 4 * k1M || n_elems >= 12 * k1M);
 }
 inline hipError_t launch_allreduce_fused(int codec, int bits_rs, int bits_ag, const void *x_f16, int n_src,
                                          int64_t n_elems, int group, void *y_f16, hipStream_t stream)

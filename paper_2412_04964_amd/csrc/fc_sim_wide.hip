@@ -191,16 +191,20 @@ namespace {
 
 constexpr int CODEC = FC_SIM_CODEC;
 
-// Workgroups that a compute unit shall hold at once, 0: as many as fit.  From 12 * 2^20 elements per partial on: 16 wavefronts with
-// two sources, 14 with three, 12 from four on, in workgroups of two or more (groups of 8192: two workgroups in every case; of
-// 16384: no limit, one workgroup to a compute unit is too few).  INT4, us, without and with so many workgroups: 8192 x 8192, groups
-// of 2048, N = 1 42.9 / 16: 42.9, 12: 41.7, 8: 46.9; N = 2 68.3 / 10: 63.1, 8: 60.8, 7: 63.2; N = 3 93.8 / 8: 86.7, 7: 80.9, 6: 83.7; N = 4
+// Workgroups that a compute unit shall hold at once, 0: as many as fit.  Many rounds of wavefronts: 16 wavefronts per compute unit with two
+// sources, 14 with three, 12 from four on, in workgroups of two or more (groups of 8192: two workgroups in every case; of 16384: no
+// limit, one workgroup to a compute unit is too few).  INT4, us, without and with so many workgroups: 8192 x 8192, groups of
+// 2048, N = 1 42.9 / 16: 42.9, 12: 41.7, 8: 46.9; N = 2 68.3 / 10: 63.1, 8: 60.8, 7: 63.2; N = 3 93.8 / 8: 86.7, 7: 80.9, 6: 83.7; N = 4
 // 114.9 / 7: 104.3, 6: 100.7, 5: 106.1; N = 6 163.9 / 7: 157, 6: 154, 5: 150; N = 8 209.6 / 7: 200, 6: 190, 5: 189; groups of 4096 N = 2
 // 67.2 / 4: 61.3, 3: 65.1; N = 3 86.7 / 4: 83.3, 3: 81.1; N = 4 109.8 / 3: 101.8, 2: 111.5; N = 8 203.8 / 3: 184.4.  Groups of
-// 2048, N = 4, 6.5 M elements 13.4 / 6: 14.2, 13 M 24.2 / 23.6, 26 M 45.9 / 42.4; N = 8 23.1 / 23.5, 42.4 / 41.2, 82.1 / 76.6.
+// 2048, N = 4, 6.5 M elements 13.4 / 6: 14.2, 13 M 24.2 / 23.6, 26 M 45.9 / 42.4; N = 8 23.1 / 23.5, 42.4 / 41.2, 82.1 / 76.6.  Few sources have
+// fewer reads waiting, and it begins later: groups of 2048, N = 2  12 M 13.7 / 8: 14.4, 16 M 18.6 / 18.8, 20 M 22.9 / 22.4; N = 3  12 M 18.7 / 7: 19.1,
+// 14 M 21.9 / 21.6.  Two sources in groups of 1024, one wavefront each, or 8192 are best without: 12 M 13.4 / 14.5, 24 M 26.0 / 26.6, 64 M 66.4 / 66.2;
+// 14 M 16.2 / 17.5, 32 M 34.9 / 35.4.
 int wide_workgroups_per_unit(int n_src, int64_t n_elems, int group)
 {
-    if (n_src == 1 || group > 8192 || n_elems < (int64_t)12 << 20) return 0;
+    if (n_src == 1 || group > 8192 || n_elems < (int64_t)(n_src == 2 ? 20 : n_src == 3 ? 14 : 12) << 20) return 0;
+    if (n_src == 2 && (group == 1024 || group == 8192)) return 0;
     const int waves = n_src == 2 ? 16 : n_src == 3 ? 14 : 12, per_group = group / 1024;
     return waves / per_group > 2 ? waves / per_group : 2;
 }

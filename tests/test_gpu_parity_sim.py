@@ -319,12 +319,12 @@ def test_wide_groups_fill_the_chip(fc, name, group):
 
 # --------------------------------------------------------------------------- #
 # volumes where a launch takes another form: two partials ahead instead of one up to 5, 4, 3.5 and 3 * 2^20 elements (two, three, four
-# and more sources), a limited number of workgroups per compute unit from 18 * 2^20 on (groups of 2048 and more: 12 * 2^20)
+# and more sources), a limited number of workgroups per compute unit from 18 * 2^20 on (groups of 2048 and more: 20, 14 and 12 * 2^20)
 # --------------------------------------------------------------------------- #
 
 @pytest.mark.parametrize("name", ["asym", "sym", "fp8", "cmeta"])
 @pytest.mark.parametrize("n_src,group,limit", [(2, 32, 5), (2, 128, 5), (3, 128, 4), (3, 512, 4), (4, 128, 3.5), (5, 128, 3), (6, 1024, 3), (8, 32, 3), (2, 128, 18), (2, 512, 18), (6, 512, 18), (4, 512, 18), (7, 32, 18),
-                                               (2, 2048, 12), (3, 8192, 12), (8, 4096, 12)])
+                                               (2, 2048, 20), (3, 8192, 14), (8, 4096, 12)])
 def test_volumes_where_the_form_changes(fc, name, n_src, group, limit):
     # rows do not depend on each other: the volume is a few rows over and over, and so is the result
     hidden, rows = 8192, 41
@@ -344,7 +344,7 @@ def test_volumes_where_the_form_changes(fc, name, n_src, group, limit):
 @pytest.mark.parametrize("name", ["asym", "sym", "fp8", "cmeta"])
 @pytest.mark.parametrize("n_src", [1, 2, 4, 5, 8])
 def test_groups_of_1024_in_both_forms(fc, name, n_src):
-    # a wavefront's tile, or a workgroup of one wavefront: by volume (3 * 2^19, 4 * 2^20 and 12 * 2^20 elements), quantizer and fan-in
+    # a wavefront's tile, or a workgroup of one wavefront: by volume (2^20 or 3 * 2^19, 4 * 2^20 and 12 * 2^20 elements), quantizer and fan-in
     hidden, rows = 3072, 13
     x = synth_inputs.make_partials_stress(n_src, rows, hidden, n_src % synth_inputs.STRESS_KINDS, seed=n_src)
     ref = oracle.allreduce_sim if name == "asym" else variant(fc, name)[1]
@@ -352,7 +352,7 @@ def test_groups_of_1024_in_both_forms(fc, name, n_src):
     base = dev16(x)
     for bits in bit_pairs(name):
         want = dev16(ref(x, 1024, *bits)).view(torch.int16)
-        for tokens in (1, 2, 512, 513, 1365, 1366, 4096):
+        for tokens in (1, 2, 341, 342, 512, 513, 1365, 1366, 4096):
             at = torch.arange(tokens, device="cuda") % rows
             y = torch.full((tokens + 2, hidden), 7.0, dtype=torch.float16, device="cuda")
             getattr(fc, "allreduce_sim" + sfx)(base[:, at], 1024, *(() if name == "fp8" else bits), out=y[1:-1])

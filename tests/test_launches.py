@@ -82,3 +82,15 @@ def test_all_reduce_workgroups_per_compute_unit():
     for case, (rc, seen) in zip(cases, launches([allreduce(q, n, elems, g) for q, n, elems, g, _ in cases])):
         assert rc == 0 and seen[0][0].startswith("k_allreduce_fused")
         assert (160 * 1024 // (seen[0][3] + 4096) if seen[0][3] else 0) == case[-1], "%s %s" % (case, seen)
+
+
+def test_all_reduce_of_wide_groups():
+    # which kernel takes groups of 1024, and where the wide one leaves room
+    forms(lambda q, n, group, elems: allreduce(q, n, elems, group, 8, 8), [
+        (("sym", 1, 1024), M, "k_allreduce_wide<1", "k_allreduce_fused<1"), (("fp8", 3, 1024), 3 * M // 2, "k_allreduce_wide<2", "k_allreduce_fused<2"),
+        (("asym", 4, 1024), 4 * M, "k_allreduce_wide<0", "k_allreduce_fused<0"), (("cmeta", 1, 1024), 4 * M, "k_allreduce_wide<3", "k_allreduce_fused<3")])
+    cases = [("asym", 2, 20 * M - 8192, 2048, False), ("sym", 2, 20 * M, 2048, True), ("asym", 2, 64 * M, 1024, False), ("fp8", 2, 64 * M, 8192, False),
+             ("cmeta", 2, 20 * M, 4096, True), ("asym", 3, 14 * M - 8192, 4096, False), ("asym", 3, 14 * M, 8192, True), ("asym", 4, 12 * M, 1024, True),
+             ("sym", 8, 12 * M, 2048, True), ("sym", 8, 12 * M - 8192, 2048, False), ("asym", 1, 64 * M, 2048, False)]
+    for case, (rc, seen) in zip(cases, launches([allreduce(q, n, elems, g) for q, n, elems, g, _ in cases])):
+        assert rc == 0 and seen[0][0].startswith("k_allreduce_wide") and (seen[0][3] > 0) == case[-1], "%s %s" % (case, seen)
