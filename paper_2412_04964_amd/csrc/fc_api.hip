@@ -142,7 +142,7 @@ int fused_impl(int codec, const void *codes_in, int64_t codes_src_stride_bytes,
     a.zeros_out = sym ? nullptr : zeros_out;
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
     hipError_t e;
-    if (fc::exceeds_tile(bits_in, group) && !fc::fused_small_applies(codec, bits_in, n_src, n, group))
+    if (fc::exceeds_tile(bits_in, group) && !fc::fused_small_applies(codec, bits_in, bits_out, n_src, n, group))
         e = fc::launch_fused_wide(bits_in, bits_out, a, st);
     else if (bits_in == 4)
         e = (bits_out == 4) ? fc::launch_fused_4_4(a, st) : fc::launch_fused_4_8(a, st);

@@ -101,7 +101,7 @@ template <int NSRC>
 static hipError_t launch_n(const FusedArgs &a, hipStream_t stream)
 {
     // launch-bound volumes: one code word per lane and source
-    if (fused_small_applies(a.codec, FC_BITS_IN, NSRC, a.n_elems, a.group)) {
+    if (fused_small_applies(a.codec, FC_BITS_IN, FC_BITS_OUT, NSRC, a.n_elems, a.group)) {
         switch (a.codec) {
         case CODEC_ASYM: return launch_small<kAsym, NSRC>(a, stream);
         case CODEC_SYM: return launch_small<kSym, NSRC>(a, stream);

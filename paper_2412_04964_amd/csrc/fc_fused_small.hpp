@@ -20,7 +20,10 @@ constexpr int fused_small_lane_elems(int bits_in) { return 32 / bits_in; }
 constexpr int fused_small_wave_elems(int bits_in) { return 64 * fused_small_lane_elems(bits_in); }
 // Up to how many wavefronts of this kernel, in units of 1024 (one per SIMD of the part), a launch takes it rather than the
 // bulk kernel, whose wavefronts hold four times the elements: past that many the bulk kernel's shorter instruction stream per element
-// counts more than the number of wavefronts.  Time against the bulk kernel's, per cent, replayed graphs, hidden 4096, at 1024 x 1.5, 2, 3, 4, 5,
+// counts more than the number of wavefronts.  Eight bits out of four take longer to form than to move, and the bulk kernel has fewer
+// instructions for them: with few sources it crosses earlier there (us, bulk / this one: asymmetric, N = 2, group 32  1.75 M
+// elements 2.89 / 2.86, 2.5 M 2.88 / 3.24, group 256  2 M 3.08 / 3.08, 2.5 M 3.05 / 3.32;  N = 4, group 128  2 M 3.38 / 3.21, 2.5 M 3.42 / 3.54;  compact metadata,
+// group 256, N = 2  1.5 M 2.98 / 2.74, 2 M 2.93 / 3.14;  N = 4  1.5 M 3.41 / 3.00, 2 M 3.42 / 3.53).  Time against the bulk kernel's, per cent, replayed graphs, hidden 4096, at 1024 x 1.5, 2, 3, 4, 5,
 // 6, 7 wavefronts (us at 3072: asymmetric 4 -> 4 bit, N = 4, group 128 3.88 / 3.07):
 //   16 lanes to a group (128 elements at 4 bit, 64 at 8 bit)
 //     asymmetric 4 -> 4 bit  N = 2 -23 -19 -19 -13 -12 -8 -3; N = 4 -26 -23 -21 -16 -14 -11 -5; N = 8 -25 -21 -29 -19 -12 -6 -2
@@ -37,11 +40,12 @@ constexpr int fused_small_wave_elems(int bits_in) { return 64 * fused_small_lane
 // that a wavefront has a compute unit to itself in the smallest launches (N = 8 10 K elements 2.22 / 2.30): 64 threads up to kFusedSmallAlone wavefronts.
 // The number is a constant of the kernel: as an argument it costs 0.04 us, read from the launch's description 0.15 (1/4 M 2.70 / 2.53).
 constexpr int kFusedSmallAlone = 256;
-inline int fused_small_limit(int codec, int bits_in, int n_src, bool wide)
+inline int fused_small_limit(int codec, int bits_in, int bits_out, int n_src, bool wide)
 {
     if (n_src == 1) return bits_in == 8 ? 3 : 2;
     if (bits_in == 8) return wide ? 5 : 6;
-    return codec == CODEC_SYM ? 6 : codec == CODEC_ASYMH ? 4 : 5;
+    const int widens = bits_out == 8 && n_src <= 4 ? 1 : 0;
+    return codec == CODEC_SYM ? 6 : (codec == CODEC_ASYMH ? 4 : 5) - widens;
 }
 
 // The other quantizers' bulk kernels read less metadata.  With few sources at 8 bit, a volume of at most three workgroups of the bulk kernel starts sooner
@@ -56,7 +60,7 @@ constexpr int kFusedSmallMinWaves = 24;
 //     compact metadata N = 4  1/2: 3.01 / 2.71   1.5: 3.83 / 3.84   2: 3.89 / 3.93, 4 -> 8 bit, group 2048, N = 8  1.5: 5.24 / 4.86   2: 5.33 / 5.69
 //   group 4096: N = 4  1/2: 3.05 / 2.79   2: 4.08 / 3.80;   N = 8  1: 4.06 / 3.56.   group 8192: N = 4  1/4: 3.19 / 3.19   1: 3.42 / 3.53
 //   8 -> 8 bit, group 512: N = 8  1/4: 3.24 / 2.92   1/2: 3.36 / 3.20   1.5: 4.92 / 5.32;   N = 2  1/8: 2.33 / 2.23;   group 1024: N = 8  1/4: 3.21 / 2.99   1/2: 3.32 /
-//     3.47;   N = 4  1/64: 2.53 / 2.28   1/2: 2.84 / 2.98, FP8 1/4: 2.25 / 2.30;   group 4096: N = 4  1/4: 2.77 / 2.78
+//     3.47;   N = 2, symmetric, group 512  1/16: 2.06 / 2.08, 1024 2.09 / 2.18, 2048 -3 %;   N = 4  1/64: 2.53 / 2.28   1/2: 2.84 / 2.98, FP8 1/4: 2.25 / 2.30;   group 4096: N = 4  1/4: 2.77 / 2.78
 //   group 8192: N = 1  2: 3.38 / 3.28   2.5: 3.82 / 3.87;   N = 2  1: 3.68 / 3.18   3.5: 4.89 / 4.67   4: 5.04 / 5.16;   N = 4  1: 4.60 / 3.57   3.5: 6.81 / 6.72   4: 7.12 / 6.99   5: 7.98 /
 //     8.64;   N = 8  1: 6.79 / 4.33   3.5: 9.69 / 9.51   5: 11.33 / 12.10;   FP8 N = 4  1: 3.82 / 3.22   3.5: 5.79 / 5.63   4: 6.10 / 6.35;   N = 8  2: 6.29 / 5.80   2.5: 7.30 / 7.55
 inline bool fused_spans_applies(int codec, int bits_in, int n_src, int64_t n_elems, int group)
@@ -64,15 +68,16 @@ inline bool fused_spans_applies(int codec, int bits_in, int n_src, int64_t n_ele
     constexpr int64_t k1M = (int64_t)1 << 20;
     if (bits_in == 4) return group <= 4096 && n_elems <= (n_src <= 2 ? k1M * 3 / 4 : codec == CODEC_ASYMH ? k1M * 3 / 2 : 2 * k1M);
     if (group == 8192) return n_elems <= (n_src == 1 || (codec == CODEC_FP8 && n_src >= 6) ? 4 : 7) * (k1M / 2);
+    if (codec != CODEC_ASYM && n_src == 2 && group == 1024) return false;
     return group <= 2048 && n_elems <= (n_src >= 5 ? k1M / 4 : n_src >= 2 ? k1M / 8 : 0);
 }
 
-inline bool fused_small_applies(int codec, int bits_in, int n_src, int64_t n_elems, int group)
+inline bool fused_small_applies(int codec, int bits_in, int bits_out, int n_src, int64_t n_elems, int group)
 {
     const int64_t waves = (n_elems + fused_small_wave_elems(bits_in) - 1) / fused_small_wave_elems(bits_in);
     if (group > fused_small_wave_elems(bits_in)) return fused_spans_applies(codec, bits_in, n_src, n_elems, group);
     const bool wide = group >= 32 * fused_small_lane_elems(bits_in);
-    if (waves > fused_small_limit(codec, bits_in, n_src, wide) * 1024) return false;
+    if (waves > fused_small_limit(codec, bits_in, bits_out, n_src, wide) * 1024) return false;
     if (codec != CODEC_ASYM && bits_in == 8 && n_src <= (codec == CODEC_ASYMH ? 1 : 3) && waves <= kFusedSmallMinWaves) return false;
     return true;
 }

@@ -94,3 +94,15 @@ def test_all_reduce_of_wide_groups():
              ("sym", 8, 12 * M, 2048, True), ("sym", 8, 12 * M - 8192, 2048, False), ("asym", 1, 64 * M, 2048, False)]
     for case, (rc, seen) in zip(cases, launches([allreduce(q, n, elems, g) for q, n, elems, g, _ in cases])):
         assert rc == 0 and seen[0][0].startswith("k_allreduce_wide") and (seen[0][3] > 0) == case[-1], "%s %s" % (case, seen)
+
+
+def test_fused_step_forms():
+    # the launch-bound kernel up to 1024 wavefronts times 2 to 6, by quantizer, code widths and fan-in
+    small, bulk = "k_fused_small<", "k_dequant_reduce_requant"
+    forms(lambda q, n, group, b, elems: fused(q, n, elems, group, *b), [
+        (("asym", 2, 128, (4, 4)), 5 * M // 2, small, bulk), (("asym", 2, 32, (4, 8)), 2 * M, small, bulk), (("asym", 4, 128, (4, 8)), 2 * M, small, bulk),
+        (("asym", 5, 128, (4, 8)), 5 * M // 2, small, bulk), (("cmeta", 3, 256, (4, 8)), 3 * M // 2, small, bulk), (("cmeta", 3, 256, (4, 4)), 2 * M, small, bulk),
+        (("cmeta", 8, 128, (4, 8)), 2 * M, small, bulk), (("sym", 2, 128, (4, 8)), 3 * M, small, bulk), (("sym", 4, 32, (8, 4)), 3 * M // 2, small, bulk),
+        (("fp8", 4, 256, ()), 5 * M // 4, small, bulk), (("asym", 1, 128, (8, 8)), 3 * M // 4, small, bulk), (("asym", 8, 8192, (8, 8)), 7 * M // 2, small, "k_dequant_reduce_requant_wide<")])
+    got = kernels(fused("sym", 2, M // 16, 1024), fused("fp8", 2, M // 16, 1024), fused("asym", 2, M // 16, 1024), fused("sym", 3, M // 16, 1024), fused("sym", 2, M // 16, 2048))
+    assert [k[0].startswith(small) for k in got] == [False, False, True, True, True], got
