@@ -118,10 +118,10 @@ bool allreduce_rot_fine_applies(int log_b, int n_src, int64_t n_elems);
 hipError_t launch_allreduce_rot_fine(int codec, int bits_rs, int bits_ag, const void *x_f16, int n_src, int64_t n_elems, int log_b, int group,
                                      void *y_f16, hipStream_t stream);
 
-// fc_rot_rows.hip: the same for volumes between those and a full chip, blocks of 1024, 2048 and 4096 (2^log_b); the quantizer for FP8, the
-// dequantizer at 4 bit in blocks of 1024 only.
-hipError_t launch_quantize_rot_rows(const void *x_f16, int64_t n_elems, int log_b, int group, void *codes, float *scales,
-                                    hipStream_t stream);
+// fc_rot_rows.hip: the same for volumes between those and a full chip, blocks of 1024, 2048 and 4096 (2^log_b); at 4 bit in blocks of
+// 1024 only, the quantizer in blocks of 4096 for FP8 only.
+hipError_t launch_quantize_rot_rows(int bits, int codec, const void *x_f16, int64_t n_elems, int log_b, int group,
+                                    void *codes, float *scales, float *zeros, hipStream_t stream);
 hipError_t launch_dequantize_rot_rows(int bits, int codec, const void *codes, const float *scales, const float *zeros,
                                       int64_t n_elems, int log_b, int group, void *y_f16, hipStream_t stream);
 // fc_rot_sim.hip: the whole rotated all-reduce in one launch, every group and fan-in.

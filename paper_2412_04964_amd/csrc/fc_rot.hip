@@ -437,30 +437,30 @@ hipError_t dequantize_rot_h(int log_b, const uint8_t *c, const float *scales, co
     }
 }
 
-// Whether the form of fc_rot_fine.hip is the fastest one (its header has both sides' times): the quantizer up to 2^21 elements, of blocks of 8192
-// in FP8 only, 8-bit codes of blocks of 2048 up to 5 * 2^19; the dequantizer up to 2^20, at 4 bit in blocks of 2048 and 4096 up to 2^21.
-// The row form comes next, then the one here.
-bool rot_fine_applies(bool quantize, int codec, int bits, int log_b, int64_t n_elems)
+// Whether the form of fc_rot_fine.hip is the fastest one (both headers have all sides' times): the quantizer up to 5 * 2^18 elements in
+// blocks of 1024, 2^20 in those of 2048 and 4096, 3 * 2^19 at 4 bit in blocks of 2048; the dequantizer up to 2^20, at 4 bit in blocks
+// of 2048 and 4096 up to 2^21.  The row form comes next, then the one here.
+bool rot_fine_applies(bool quantize, int bits, int log_b, int64_t n_elems)
 {
     constexpr int64_t k1M = (int64_t)1 << 20;
-    if (quantize) return (log_b <= 12 || codec == CODEC_FP8) && n_elems <= (bits == 8 && log_b == 11 ? 5 : 4) * (k1M / 2);
+    if (quantize) return log_b <= 12 && n_elems <= (log_b == 10 ? 5 : log_b == 11 && bits == 4 ? 6 : 4) * (k1M / 4);
     return n_elems <= (bits == 4 && (log_b == 11 || log_b == 12) ? 2 : 1) * k1M;
 }
 
 // Whether the form of fc_rot_rows.hip is the faster one (its header has both sides' times) where that of fc_rot_fine.hip is not taken.  At 8 bit
-// a wavefront here has twice the work of one there, and FP8's stages cost most in a chain that nothing covers, so the limits lie between 2^21
+// a wavefront here has twice the work of one there, and FP8's stages cost most in a chain that nothing covers, so its limits lie between 2^21
 // and 2^22 elements; at 4 bit a wavefront has 2048 elements in both forms.  Just past the third wavefront per SIMD, 5 to 6 * 2^20 elements,
 // the row form wins once more in two cases (rows / registers, 5.5 M: 4-bit dequantizer, blocks of 1024 4.90 / 5.12; FP8 quantizer, 2048
 // 6.19 / 6.50; 6.5 M 5.44 / 5.22, 6.91 / 6.88).
 bool rot_rows_apply(bool quantize, int codec, int bits, int log_b, int64_t n_elems)
 {
-    // up to so many times 2^19 elements, blocks of 1024, 2048, 4096: FP8 quantizer; dequantizer at 4 bit, 8 bit, FP8
-    static constexpr unsigned char kQuantize[3] = {6, 8, 8}, kDequantize[3][3] = {{4, 0, 0}, {4, 4, 6}, {5, 6, 8}};
+    // up to so many times 2^19 elements, blocks of 1024, 2048, 4096: 4 bit, 8 bit, FP8
+    static constexpr unsigned char kQuantize[3][3] = {{4, 0, 0}, {4, 4, 0}, {6, 8, 8}}, kDequantize[3][3] = {{4, 0, 0}, {4, 4, 6}, {5, 6, 8}};
     constexpr int64_t k1M = (int64_t)1 << 20;
     const bool fp8 = codec == CODEC_FP8;
-    if (log_b > 12 || (quantize && !fp8)) return false;
-    if (n_elems <= (quantize ? kQuantize : kDequantize[fp8 ? 2 : bits == 8])[log_b - 10] * (k1M / 2)) return true;
-    return (quantize ? log_b == 11 : bits == 4 && log_b == 10) && n_elems > 5 * k1M && n_elems <= 6 * k1M;
+    if (log_b > 12) return false;
+    if (n_elems <= (quantize ? kQuantize : kDequantize)[fp8 ? 2 : bits == 8][log_b - 10] * (k1M / 2)) return true;
+    return (quantize ? fp8 && log_b == 11 : bits == 4 && log_b == 10) && n_elems > 5 * k1M && n_elems <= 6 * k1M;
 }
 
 }  // namespace
@@ -472,9 +472,10 @@ hipError_t launch_quantize_rot(int bits, int codec, const void *x_f16, int64_t t
     uint8_t *c = static_cast<uint8_t *>(codes);
     const int lb = log2_int(rotation_block(hidden));
     const int64_t n = tokens * hidden;
-    if (rot_fine_applies(true, codec, bits, lb, n))
+    if (rot_fine_applies(true, bits, lb, n))
         return launch_quantize_rot_fine(bits, codec, x_f16, n, lb, group, codes, scales, zeros, stream);
-    if (bits == 8 && rot_rows_apply(true, codec, bits, lb, n)) return launch_quantize_rot_rows(x_f16, n, lb, group, codes, scales, stream);
+    if (rot_rows_apply(true, codec, bits, lb, n))
+        return launch_quantize_rot_rows(bits, codec, x_f16, n, lb, group, codes, scales, zeros, stream);
     if (codec == CODEC_FP8)
         return bits == 8 ? quantize_rot_h<8, kFp8>(lb, x, n, group, c, scales, nullptr, stream)
                          : hipErrorInvalidValue;
@@ -492,7 +493,7 @@ hipError_t launch_dequantize_rot(int bits, int codec, const void *codes, const f
     uint16_t *y = static_cast<uint16_t *>(y_f16);
     const int lb = log2_int(rotation_block(hidden));
     const int64_t n = tokens * hidden;
-    if (rot_fine_applies(false, codec, bits, lb, n))
+    if (rot_fine_applies(false, bits, lb, n))
         return launch_dequantize_rot_fine(bits, codec, codes, scales, zeros, n, lb, group, y_f16, stream);
     if (rot_rows_apply(false, codec, bits, lb, n))
         return launch_dequantize_rot_rows(bits, codec, codes, scales, zeros, n, lb, group, y_f16, stream);

@@ -7,11 +7,11 @@
 // What bounds it: latency, of the launch (1.6 us), of one load, of the chain of some 250 instructions and of one barrier or two; past one
 // wavefront per SIMD (2^19 elements) the instructions themselves, of which there are more per element than in the other forms.  us per launch
 // under graph replay, group 128, the other forms (fc_rot.hip, fc_rot_rows.hip) / this one (rot_fine_applies says where it is taken):
-//   quantize, INT4, blocks of 1024: 10 K elements 3.07 / 2.34; 1/2 M 3.25 / 2.74; 1 M 3.76 / 3.09; 2 M 4.09 / 3.92; 2.5 M 4.53 / 4.71
-//     2048: 3.02 / 2.46; 1 M 3.79 / 3.32; 2 M 4.38 / 4.15; 2.5 M 4.55 / 4.66.   4096: 3.21 / 2.76; 1 M 3.98 / 3.44; 2 M 4.51 / 4.36; 2.5 M 4.72 / 5.05
-//     8192, group 64: 3.43 / 3.61; 1 M 4.27 / 4.35.   One group per block of 4096, symmetric: 3.29 / 2.95; 2 M 4.57 / 4.37
-//   INT8, blocks of 1024: 2.79 / 2.36; 1 M 3.69 / 3.13; 2 M 4.21 / 4.09.   2048: 1 M 3.68 / 3.27; 2.5 M 4.68 / 4.72.   FP8, 1024: 2.77 / 2.33; 1 M 3.57 /
-//     3.07; 2 M 4.13 / 3.97.   8192: 3.67 / 3.54; 1 M 4.44 / 4.27; 2 M 4.77 / 4.76; 2.5 M 5.48 / 5.98
+//   quantize, INT4, blocks of 1024: 10 K elements 3.07 / 2.34; 1/2 M 3.25 / 2.74; 1 M 3.09 / 2.60; 1.25 M 3.20 / 3.01; 1.5 M 3.32 / 3.38, group 1024 3.54 / 3.87
+//     2048: 3.02 / 2.46; 1 M 3.11 / 2.77; 1.5 M 3.53 / 3.23; 2 M 3.58 / 3.70.   4096: 3.21 / 2.76; 1 M 3.34 / 2.96; 1.25 M 3.74 / 3.75; 2 M 3.67 / 3.79
+//     8192, group 64: 3.43 / 3.61; 1 M 4.27 / 4.35.   One group per block of 4096, symmetric: 3.29 / 2.95
+//   INT8, blocks of 1024: 2.79 / 2.36; 1 M 3.05 / 2.61; 1.5 M 3.21 / 3.40.   2048: 1 M 3.07 / 2.90; 1.25 M 3.15 / 3.17; 2 M 3.47 / 3.71.   FP8, 1024: 2.77 / 2.33; 2048: 1 M 2.88 /
+//     2.63; 2 M 3.36 / 3.53.   8192: one group per block 1 M 4.03 / 4.35; 2 M 4.17 / 4.64, groups of up to 128  -2 to +3 %
 //   dequantize, INT4, blocks of 1024: 2.77 / 2.20; 1/2 M 2.89 / 2.49; 1 M 3.09 / 2.82; 1.5 M 3.27 / 3.50.   2048: 3.04 / 2.22; 1 M 3.11 / 2.92; 2 M 3.97 /
 //     3.72; 2.5 M 3.85 / 4.20.   4096: 3.09 / 2.45; 1 M 3.46 / 2.97; 2 M 4.26 / 3.90.   8192, group 64: 3.39 / 3.16; 1 M 3.75 / 3.72; 2 M 4.09 / 4.19
 //   INT8, blocks of 1024: 2.51 / 2.19; 1 M 3.07 / 2.95; 2 M 3.75 / 3.77.   FP8, 4096: 2.66 / 2.43; 1 M 3.25 / 3.18; 2 M 3.97 / 4.08
@@ -374,10 +374,7 @@ hipError_t quantize_block(int log_b, const uint16_t *x, int64_t n_elems, int gro
     case 10: return quantize_one<BITS, CODEC, 10>(x, n_elems, group, c, scales, zeros, stream);
     case 11: return quantize_one<BITS, CODEC, 11>(x, n_elems, group, c, scales, zeros, stream);
     case 12: return quantize_one<BITS, CODEC, 12>(x, n_elems, group, c, scales, zeros, stream);
-    case 13:
-        if constexpr (CODEC == kFp8) return quantize_one<BITS, CODEC, 13>(x, n_elems, group, c, scales, zeros, stream);
-        return hipErrorInvalidValue;       // integer codes: the form of fc_rot.hip at every volume
-    default: return hipErrorInvalidValue;
+    default: return hipErrorInvalidValue;  // 8192: the form of fc_rot.hip at every volume
     }
 }
 

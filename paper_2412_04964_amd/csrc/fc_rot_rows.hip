@@ -1,5 +1,5 @@
-// fc_rot_rows.hip -- the rotated quantizer (FP8) and dequantizer between the launch-bound volumes of fc_rot_fine.hip and those that fill the
-// chip: the row in LDS.
+// fc_rot_rows.hip -- the rotated quantizer and dequantizer between the launch-bound volumes of fc_rot_fine.hip and those that fill the chip:
+// the row in LDS.
 //
 // The same arithmetic as fc_rot.hip (butterflies in the order of the spans, so bit-identical), split the other way: a lane
 // holds one 128-bit word of codes, 32 elements at 4 bit and 16 at 8 bit, as in the plain kernels, transforms these, and then the row lies
@@ -9,6 +9,9 @@
 //
 // What bounds it: latency of one wavefront.  us per launch under graph replay, this / register form, group 128
 // (rot_rows_apply says where each is taken):
+//   quantize, this / register form / the form of fc_rot_fine.hip, blocks of 1024: 4 bit, group 128  1.25 M 3.20 / 3.56 / 3.01, 1.5 M 3.32 / 3.59 / 3.38, group 1024  1.5 M
+//     3.54 / 3.77 / 3.87, 2 M 3.83 / 3.96 / 3.91; 8 bit, group 128  1.5 M 3.21 / 3.56 / 3.40, 2 M 3.46 / 3.62 / 3.55; 2048: 8 bit, group 128  1 M 3.07 / 3.20 / 2.90, 1.5 M
+//     3.18 / 3.52 / 3.22, 2 M 3.47 / 3.59 / 3.71, 2.5 M 3.83 / 3.79.
 //   quantize FP8, blocks of 1024: 3 M 4.67 / 4.79; 4 M 5.22 / 5.11; 2048: 3 M 4.70 / 4.99; 4 M 5.25 / 5.33; 5 M 5.89 / 5.83; 4096: 3 M
 //     5.02 / 5.39; 4 M 5.67 / 5.79; 5 M 6.30 / 6.20.
 //   dequantize, blocks of 1024: 8 bit 1 M elements 3.08 / 3.20; 2 M 3.62 / 3.85; 2.5 M 3.95 / 3.93; 8 M 7.23 / 5.78; FP8 1 M 2.98 / 3.47;
@@ -122,14 +125,14 @@ __device__ __forceinline__ void hadamard_row(float (&v)[NE], float *row, u32 tid
     }
 }
 
-// Rotate one row block by block and quantize it to FP8 (FinegrainedQuantize of Algorithm 1 on the rotated values).
+// Rotate one row block by block and quantize it (FinegrainedQuantize of Algorithm 1 on the rotated values).
 // n_elems: elements of the whole tensor (a multiple of 2^LB; the last row may be a partial one when LB < LOGH:
 // lanes beyond the end read zeros and have their stores dropped or skipped).
-template <int LOGH, int LB>
-__global__ __launch_bounds__((RowShape<8, LOGH>::T)) void k_quantize_rot_rows(
-    const uint16_t *__restrict__ x, int64_t n_elems, int lpg, int group_shift, uint8_t *__restrict__ codes, float *__restrict__ scales)
+template <int BITS, int CODEC, int LOGH, int LB>
+__global__ __launch_bounds__((RowShape<BITS, LOGH>::T)) void k_quantize_rot_rows(
+    const uint16_t *__restrict__ x, int64_t n_elems, int lpg, int group_shift, uint8_t *__restrict__ codes,
+    float *__restrict__ scales, float *__restrict__ zeros)
 {
-    constexpr int BITS = 8;
     using S = RowShape<BITS, LOGH>;
     constexpr int EPL = S::EPL, kPieces = S::kPieces;
     __shared__ __attribute__((aligned(16))) uint8_t lds[S::kLdsBytes];
@@ -161,17 +164,28 @@ __global__ __launch_bounds__((RowShape<8, LOGH>::T)) void k_quantize_rot_rows(
     hadamard_row<BITS, LOGH, LB, 1>(v, row, tid);
     // the forward scaling goes into the group's min and max and its reciprocal (see k_quantize_rot)
     constexpr float fwd = 1.0f / (float)(1 << ((LB + 1) / 2));
-    float mn, mx, s, inv;
+    float mn, mx, s, inv, zf = 0.0f;
     lane_minmax(v, mn, mx);
     group_minmax<0>(mn, mx, lpg);
     if (lpg > 64) cross_wave_minmax(mn, mx, slot, wave, lane, (u32)lpg >> 6);
 
     u32 word[4];
-    group_params_absmax<448>(fmaxf(fabsf(mn * fwd), fabsf(mx * fwd)), s, inv);
-    pack_lane_fp8<EPL>(v, inv * fwd, word);
+    const float mn_s = mn * fwd, mx_s = mx * fwd;
+    if constexpr (CODEC == kFp8) {
+        group_params_absmax<448>(fmaxf(fabsf(mn_s), fabsf(mx_s)), s, inv);
+        pack_lane_fp8<EPL>(v, inv * fwd, word);
+    } else if constexpr (CODEC == kSym) {
+        group_params_sym<BITS>(fmaxf(fabsf(mn_s), fabsf(mx_s)), s, inv);
+        pack_lane_sym<BITS, EPL>(v, inv * fwd, word);
+    } else {
+        group_params<BITS>(mn_s, mx_s, s, inv, zf);
+        pack_lane<BITS, EPL>(v, inv * fwd, zf, mx, word);
+    }
     __builtin_amdgcn_raw_buffer_store_b128(u32x4{word[0], word[1], word[2], word[3]}, rc, tid * 16, 0, kStreamStorePolicy);
     if ((tid & (u32)(lpg - 1)) == 0 && (int64_t)(tid * EPL) < here) {
-        scales[(e0 >> group_shift) + ((tid * EPL) >> group_shift)] = s;
+        const int64_t gi = (e0 >> group_shift) + ((tid * EPL) >> group_shift);
+        scales[gi] = s;
+        if constexpr (CODEC == kAsym) zeros[gi] = zf;
     }
 }
 
@@ -246,12 +260,13 @@ __global__ __launch_bounds__((RowShape<BITS, LOGH>::T)) void k_dequantize_rot_ro
 
 namespace {
 
-template <int LOGH, int LB>
-hipError_t quantize_one(const uint16_t *x, int64_t n_elems, int group, uint8_t *c, float *scales, hipStream_t stream)
+template <int BITS, int CODEC, int LOGH, int LB>
+hipError_t quantize_one(const uint16_t *x, int64_t n_elems, int group, uint8_t *c, float *scales, float *zeros,
+                        hipStream_t stream)
 {
     const unsigned grid = (unsigned)((n_elems + ((int64_t)1 << LOGH) - 1) >> LOGH);
-    return launch_kernel(k_quantize_rot_rows<LOGH, LB>, dim3(grid), dim3(RowShape<8, LOGH>::T), stream, x, n_elems,
-                         group / lane_elems(8), log2_int(group), c, scales);
+    return launch_kernel(k_quantize_rot_rows<BITS, CODEC, LOGH, LB>, dim3(grid), dim3(RowShape<BITS, LOGH>::T), stream, x,
+                         n_elems, group / lane_elems(BITS), log2_int(group), c, scales, zeros);
 }
 
 template <int BITS, int CODEC, int LOGH, int LB>
@@ -264,6 +279,18 @@ hipError_t dequantize_one(const uint8_t *c, const float *scales, const float *ze
 }
 
 // blocks of 1024 go two to a row
+template <int BITS, int CODEC>
+hipError_t quantize_block(int log_b, const uint16_t *x, int64_t n_elems, int group, uint8_t *c, float *scales,
+                          float *zeros, hipStream_t stream)
+{
+    if (log_b == 10) return quantize_one<BITS, CODEC, 11, 10>(x, n_elems, group, c, scales, zeros, stream);
+    if constexpr (BITS == 8)               // at 4 bit the other forms
+        if (log_b == 11) return quantize_one<BITS, CODEC, 11, 11>(x, n_elems, group, c, scales, zeros, stream);
+    if constexpr (CODEC == kFp8)
+        if (log_b == 12) return quantize_one<BITS, CODEC, 12, 12>(x, n_elems, group, c, scales, zeros, stream);
+    return hipErrorInvalidValue;
+}
+
 template <int BITS, int CODEC>
 hipError_t dequantize_block(int log_b, const uint8_t *c, const float *scales, const float *zeros, int64_t n_elems,
                             int group, uint16_t *y, hipStream_t stream)
@@ -278,17 +305,19 @@ hipError_t dequantize_block(int log_b, const uint8_t *c, const float *scales, co
 
 }  // namespace
 
-hipError_t launch_quantize_rot_rows(const void *x_f16, int64_t n_elems, int log_b, int group, void *codes, float *scales,
-                                    hipStream_t stream)
+hipError_t launch_quantize_rot_rows(int bits, int codec, const void *x_f16, int64_t n_elems, int log_b, int group,
+                                    void *codes, float *scales, float *zeros, hipStream_t stream)
 {
     const uint16_t *x = static_cast<const uint16_t *>(x_f16);
     uint8_t *c = static_cast<uint8_t *>(codes);
-    switch (log_b) {
-    case 10: return quantize_one<11, 10>(x, n_elems, group, c, scales, stream);
-    case 11: return quantize_one<11, 11>(x, n_elems, group, c, scales, stream);
-    case 12: return quantize_one<12, 12>(x, n_elems, group, c, scales, stream);
-    default: return hipErrorInvalidValue;
-    }
+    if (codec == CODEC_FP8)
+        return bits == 8 ? quantize_block<8, kFp8>(log_b, x, n_elems, group, c, scales, nullptr, stream)
+                         : hipErrorInvalidValue;
+    if (bits == 4)
+        return codec == CODEC_ASYM ? quantize_block<4, kAsym>(log_b, x, n_elems, group, c, scales, zeros, stream)
+                                   : quantize_block<4, kSym>(log_b, x, n_elems, group, c, scales, nullptr, stream);
+    return codec == CODEC_ASYM ? quantize_block<8, kAsym>(log_b, x, n_elems, group, c, scales, zeros, stream)
+                               : quantize_block<8, kSym>(log_b, x, n_elems, group, c, scales, nullptr, stream);
 }
 
 hipError_t launch_dequantize_rot_rows(int bits, int codec, const void *codes, const float *scales, const float *zeros,

@@ -465,7 +465,7 @@ def test_allreduce_sim_rot_sources_side_by_side(fc, quantizer, n_src, hidden):
 @pytest.mark.parametrize("quantizer,bits", [(oracle.ASYM, 4), (oracle.ASYM, 8), (oracle.SYM, 4), (oracle.SYM, 8), (oracle.FP8, 8)])
 @pytest.mark.parametrize("hidden", [1024, 2048, 4096, 8192])
 def test_rot_codecs_on_both_sides_of_the_volume_limits(fc, quantizer, bits, hidden):
-    # 2^20, 2^21 and 5 * 2^19 elements, where other forms of the rotated quantizer and dequantizer take over
+    # 2^20, 5 * 2^18, 3 * 2^19, 2^21, 5 * 2^19 and 2^22 elements, where other forms of the rotated quantizer and dequantizer take over
     x = synth_inputs.make_partials(1, 5, hidden, seed=hidden + bits, outlier_frac=0.01)[0]
     x[1] = 0
     x[2] = np.float16(6e-8) * (np.arange(hidden) % 5)
@@ -476,7 +476,7 @@ def test_rot_codecs_on_both_sides_of_the_volume_limits(fc, quantizer, bits, hidd
         coded = oracle.quantize_rot(x, group, bits, quantizer)
         back = dev(oracle.dequantize_rot(*coded, hidden, group, bits, quantizer).view(np.int16))
         want = [dev(np.ascontiguousarray(a).view(np.uint8)) for a in coded[:3 if quantizer == oracle.ASYM else 2]]
-        for limit in (1 << 20, 1 << 21, 5 << 19):
+        for limit in (1 << 20, 5 << 18, 3 << 19, 1 << 21, 5 << 19, 1 << 22):
             for rows in (1, limit // hidden, limit // hidden + 1):
                 pick = torch.arange(rows, device="cuda") % 5
                 got = fc.quantize_rot(few[pick], group, bits, quantizer)

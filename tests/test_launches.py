@@ -106,3 +106,21 @@ def test_fused_step_forms():
         (("fp8", 4, 256, ()), 5 * M // 4, small, bulk), (("asym", 1, 128, (8, 8)), 3 * M // 4, small, bulk), (("asym", 8, 8192, (8, 8)), 7 * M // 2, small, "k_dequant_reduce_requant_wide<")])
     got = kernels(fused("sym", 2, M // 16, 1024), fused("fp8", 2, M // 16, 1024), fused("asym", 2, M // 16, 1024), fused("sym", 3, M // 16, 1024), fused("sym", 2, M // 16, 2048))
     assert [k[0].startswith(small) for k in got] == [False, False, True, True, True], got
+
+
+def test_rotated_codec_forms():
+    fine, rows, registers = "k_quantize_rot_fine<", "k_quantize_rot_rows<", "k_quantize_rot<"
+    def block(q, bits, hidden, elems):
+        return quantize_rot(q, elems // hidden * hidden, hidden, 128, bits)
+    def both(cases):
+        calls = [block(q, bits, hidden, elems) for q, bits, hidden, limit, _, _ in cases for elems in (limit, limit + hidden)]
+        got = kernels(*calls)
+        for (q, bits, hidden, limit, upto, above), a, b in zip(cases, got[::2], got[1::2]):
+            assert a[0].startswith(upto) and b[0].startswith(above), "%s %d bits h=%d %.2f M: %s, then %s" % (q, bits, hidden, limit / M, a, b)
+    both([("asym", 4, 1024, 5 * M // 4, fine, rows), ("sym", 4, 1024, 2 * M, rows, registers), ("asym", 8, 5120, 5 * M // 4, fine, rows), ("sym", 8, 1024, 2 * M, rows, registers),
+          ("asym", 4, 2048, 3 * M // 2, fine, registers), ("sym", 8, 2048, M, fine, rows), ("asym", 8, 2048, 2 * M, rows, registers), ("fp8", 8, 2048, M, fine, rows),
+          ("fp8", 8, 2048, 4 * M, rows, registers), ("asym", 4, 4096, M, fine, registers), ("sym", 8, 4096, M, fine, registers), ("fp8", 8, 4096, 4 * M, rows, registers),
+          ("fp8", 8, 8192, M, registers, registers), ("asym", 4, 8192, M, registers, registers)])
+    got = kernels(*[dequantize_rot(q, elems, hidden, 128, bits) for q, bits, hidden, elems in
+                    (("asym", 4, 2048, 2 * M), ("asym", 4, 2048, 2 * M + 2048), ("sym", 8, 8192, M), ("sym", 8, 8192, M + 8192), ("asym", 8, 1024, 2 * M), ("fp8", 8, 1024, 3 * M))])
+    assert [k[0].split("<")[0] for k in got] == ["k_dequantize_rot" + s for s in ("_fine", "", "_fine", "", "_rows", "")]
