@@ -314,43 +314,31 @@ int rot_steps(int codec, const void *x_f16, int n_src, int64_t tokens, int64_t h
                                                  static_cast<hipStream_t>(hip_stream)));
 }
 
-// Whether the steps are the faster form of the rotated all-reduce.  The one launch works through the sources one after
-// the other, 1.5 us each in blocks of up to 2048 elements, 2.0 us in blocks of 8192 (FP8 1.9 / 2.3), until the chip is full; the
-// three steps take 8 to 10 us, their quantizations spread over the chip.  Up to this many elements, in units of 2^16, by the
-// block and the number of sources, the steps are taken.  The limits were found with earlier kernels; with those of today the lines
-// cross somewhat elsewhere (last number of each entry: where, mean of two cards), most of all in blocks of 8192 with five to
-// seven sources, where the worst volume takes 18 % longer than it could.  Symmetric codes cross where asymmetric ones do.  Group 128,
-// three steps / one launch, us under graph replay:
-//   INT4, block 2048: N = 4, 256 K elements 9.1 / 9.7, 512 K 9.8 / 9.7 (6); N = 5, 512 K 10.0 / 11.3, 768 K 10.6 / 11.6, 1280 K 13.6 /
-//     13.6 (18); N = 6, 1024 K 12.1 / 13.5, 1536 K 15.5 / 16.0 (26); N = 8, 1536 K 18.2 / 20.7, 2048 K 20.8 / 21.2 (32).
-//   INT4, block 4096: N = 4, 256 K 9.6 / 10.8, 768 K 10.8 / 11.3, 1152 K 13.0 / 12.4 (16); N = 5 (20); N = 6, 2048 K 18.9 / 17.6 (26);
-//     N = 7 (28); N = 8, 2048 K 21.9 / 21.9 (31).
-//   INT4, block 8192: N = 3, 8 K 9.0 / 9.0 (0); N = 4, 512 K 10.6 / 12.3, 768 K 11.3 / 12.6, 1280 K 13.5 / 12.8 (16); N = 5 (24);
-//     N = 6 (30); N = 7, 1408 K 17.0 / 19.9, 2048 K 20.7 / 20.9 (34); N = 8, 8 K 10.1 / 19.0, 2048 K 22.3 / 23.2 (36).
-//   FP8, block 2048: N = 3, 256 K 8.4 / 9.4, 512 K 9.2 / 9.6, 768 K 10.0 / 9.8 (10); N = 8, 2048 K 21.6 / 24.4, 2560 K 25.2 / 24.6 (36).
-//   FP8, block 8192: N = 3, 256 K 10.5 / 11.4, 768 K 11.9 / 11.8 (11); N = 4 (26); N = 5, 1664 K 16.4 / 17.8 (36); N = 8, 2048 K 23.8 /
-//     27.2, 3072 K 30.5 / 30.4 (46).
-// Groups of 1024 elements and more cost the steps another 1.1 us, the one launch 0.2 to 0.7: four sources of short blocks do not cross
-// then (64 K 9.6 / 8.9), in blocks of 4096 at 12 (256 K 10.6 / 11.4).
-// Partials whose metadata are not a multiple of 16 bytes (few tokens, coarse groups) follow the same limits in blocks of 2048 and
-// more (one group per token, 8 x 1 x 8192 20.3 -> 11.4, 5 x 7 x 4096 12.7 -> 10.7, FP8 4 x 5 x 8192 14.3 -> 12.4), except
-// three sources of FP8 in blocks of 8192 (11.5 / 12.1).  In blocks of 1024 the steps would win as much (8 x 1 x 5120 14.8 / 10.4), but
-// that call leaves the caller's workspace alone, which the tests hold it to.
-// These figures are those of three launches, before the last two of them became one, and of the one launch with one source after the other
-// everywhere (by now side by side in small volumes, rot_spread_applies); most limits have stayed, since callers may count on when the workspace
-// is written.  us, three launches / two: INT4, group 128, block 2048  N = 4  1/4 M 7.46 / 6.18;  N = 8  1/4 M 8.65 / 7.50   1 M 12.74 / 10.91;  block
-// 4096  N = 4  1/2 M 9.18 / 7.92;  N = 8  1.5 M 16.10 / 14.40;  block 8192  N = 4  1/2 M 10.37 / 9.47;  N = 8  1 M 14.23 / 13.01;  FP8  block 1024
-// N = 4  1/4 M 7.15 / 5.65   1.5 M 12.68 / 11.02;  block 4096  N = 8  3 M 27.02 / 25.35.
-// With today's forms, two launches / one, lie the limits of six and seven sources, and FP8's of four: INT4, block 1024  N = 6  1/2 M 8.29 / 6.66   1 M 9.73 / 8.30
-// 1.25 M 10.64 / 13.85   2 M 14.09 / 14.25;  N = 7  1 M 10.12 / 8.60   2.25 M 17.63 / 16.10;  block 2048  N = 7  1/8 M 6.35 / 6.62   1/2 M 8.37 / 7.25   2 M 16.06 / 17.93;
-// block 4096  N = 6  1/2 M 8.83 / 8.71   1 M 10.40 / 9.48   1.5 M 12.73 / 16.14   2.25 M 17.81 / 17.60;  N = 7  2 M 16.92 / 18.41;  block 8192  N = 6  1/2 M 10.40 / 14.68   1.5 M
-// 13.37 / 15.44   2 M 16.08 / 16.06;  N = 7  1.5 M 14.84 / 15.83   1.75 M 16.46 / 16.16;  FP8  N = 4  block 1024  1/2 M 6.93 / 4.90   2 M 12.23 / 9.96;  block 4096  1/2 M
-// 7.66 / 8.06   1 M 9.79 / 8.68   2 M 13.34 / 12.01;  N = 6  block 1024  1 M 10.55 / 9.01   1.25 M 11.48 / 16.87.
-bool rot_steps_apply(int codec, int n_src, int64_t n_elems, int64_t hidden, int group)
+// Whether the steps are the faster form of the rotated all-reduce: with few elements of many sources all partials' quantizations
+// spread over the chip and one more launch take less time than one launch of few workgroups, each of which goes through the sources in
+// turn (up to 2^21 elements of few sources side by side, rot_spread_applies and allreduce_rot_fine_applies).  Up to this many
+// elements, in units of 2^16, by the block and the number of sources, the steps are taken; blocks of 2048 stand with 1024.
+// us by elements (2^20), group 128, steps / one launch:
+//   INT4, block 2048: N = 3  1/4: 6.0 / 4.4   1: 8.2 / 6.2;   N = 4  1/4: 6.0 / 4.8   1: 8.5 / 6.5;   N = 5  1/2: 7.6 / 6.5   1.25: 10.5 / 11.0;   N = 6  1: 10.1 / 8.4
+//     1.25: 11.1 / 15.7   2: 14.3 / 16.2;   N = 7  1: 10.5 / 9.0   2.25: 17.1 / 19.0;   N = 8  1: 10.9 / 10.1   2: 16.9 / 20.6
+//   block 4096: N = 4  1/2: 7.3 / 7.0   1: 8.7 / 7.3;   N = 5  1.25: 11.0 / 13.9   2: 13.3 / 14.5;   N = 6  2.25: 16.6 / 17.9;   N = 8  1/4: 7.5 / 9.6   2: 17.3 / 21.6
+//   block 8192: N = 4  1/2: 8.8 / 10.0   1: 9.8 / 9.9;   N = 5  1: 10.9 / 14.7   2: 13.7 / 15.6;   N = 6  2: 15.0 / 16.2;   N = 7  1.75: 15.4 / 16.5;   N = 8  1.75: 16.5 / 17.1
+//   FP8, block 2048: N = 3  1/4: 5.7 / 4.3;   N = 4  1/4: 5.7 / 4.7;   N = 5  1.75: 14.1 / 15.9;   N = 6  1.25: 13.1 / 17.6   2: 18.1 / 18.5;   N = 7  2: 18.8 / 21.3   2.25: 22.7 / 21.6
+//     N = 8  2: 21.9 / 23.8   2.25: 25.8 / 24.0;   block 4096: N = 3  1/2: 6.8 / 7.3   1: 8.4 / 7.5;   N = 4  1/2: 7.1 / 7.7   1: 9.4 / 7.9;   N = 8  3: 27.1 / 30.4
+//   block 8192: N = 3  1/4: 7.9 / 9.3   1: 10.0 / 9.3;   N = 4  1: 10.2 / 10.5;   N = 8  2: 20.7 / 19.3   3: 28.6 / 30.0
+// 8-bit codes cost the second launch twice the bytes; with six sources and more in blocks of up to 2048 it shows: INT8, block 2048, N = 6  1.5: 13.7 /
+// 15.7   2: 18.5 / 16.3;   N = 7  1.5: 15.0 / 17.7   1.75: 17.6 / 18.2   2: 19.2 / 18.6;   N = 8  1.75: 19.5 / 20.3   2: 22.0 / 20.5.  Groups of 1024 elements and more cost the
+// steps another 1.1 us, the one launch 0.2 to 0.7: four sources of short blocks never take them then.
+// Some limits lie above the crossing (four sources, INT4, five and eight in short blocks, FP8's three): they date from the one launch with one source after
+// the other, and below them the steps are still faster than that was.
+// Partials whose metadata are not a multiple of 16 bytes (few tokens, coarse groups) follow the same limits (one group per token, INT4 8 x 1 x 8192
+// 11.4 us for 20.3 in one launch), but for blocks of 1024 and FP8's three sources in blocks of 8192 (11.5 / 12.1).
+bool rot_steps_apply(int codec, int bits_rs, int n_src, int64_t n_elems, int64_t hidden, int group)
 {
     //                                           n_src 3  4   5   6   7   8
     static constexpr unsigned char kLimit[2][3][6] = {{{0, 4, 8, 32, 36, 32}, {0, 8, 28, 35, 36, 32}, {0, 8, 16, 30, 28, 28}},
-                                                      {{7, 0, 32, 34, 40, 40}, {8, 8, 40, 40, 44, 48}, {6, 18, 24, 40, 44, 48}}};
+                                                      {{7, 0, 32, 34, 32, 32}, {8, 8, 40, 40, 44, 48}, {6, 18, 24, 40, 44, 48}}};
+    static constexpr unsigned char kLimit8[3] = {24, 24, 28};           // INT8, six sources and more in short blocks
     static_assert(FC_MAX_SRC == 8, "one column per fan-in");
     if (n_src < 3) return false;
     const bool fp8 = codec == fc::CODEC_FP8;
@@ -358,6 +346,7 @@ bool rot_steps_apply(int codec, int n_src, int64_t n_elems, int64_t hidden, int 
     const int row = block == 8192 ? 2 : block == 4096 ? 1 : 0;
     if (row == 0 && (n_src == 6 || n_src == 7) && n_elems <= (int64_t)1 << 20) return false;
     int limit = kLimit[fp8][row][n_src - 3];
+    if (!fp8 && bits_rs == 8 && row == 0 && n_src >= 6) limit = kLimit8[n_src - 6];
     if (!fp8 && n_src == 4 && group >= 1024 && row < 2) limit = 4 * row;
     const bool padded = n_elems / group % 4 != 0;
     if (padded && (block == 1024 || (fp8 && n_src == 3 && block == 8192))) return false;
@@ -560,7 +549,7 @@ int fc_allreduce_sim_rot(const void *x_f16, int n_src, int64_t tokens, int64_t h
     if (!workspace || workspace_bytes < L.total) return FC_ERR_WORKSPACE;
     if (!aligned16(workspace)) return FC_ERR_ALIGN;
 
-    if (rot_steps_apply(quantizer, n_src, n, hidden, group))
+    if (rot_steps_apply(quantizer, bits_rs, n_src, n, hidden, group))
         return rot_steps(quantizer, x_f16, n_src, tokens, hidden, group, bits_rs, bits_ag, y_f16, L, workspace, hip_stream);
     // one kernel; nothing goes through the workspace
     return hip_result(fc::launch_allreduce_rot(quantizer, bits_rs, bits_ag, x_f16, n_src, tokens, (int)hidden, group,

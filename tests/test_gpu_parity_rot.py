@@ -211,17 +211,18 @@ def test_wide_blocks_both_layouts_every_group(fc, quantizer, bits, hidden):
                 assert torch.equal(got.view(torch.uint8), w[pick].view(torch.uint8)), "h=%d g=%d rows=%d" % (hidden, group, rows)
 
 
-@pytest.mark.parametrize("quantizer,n_src", [(oracle.ASYM, 3), (oracle.ASYM, 4), (oracle.ASYM, 8), (oracle.SYM, 5), (oracle.SYM, 8),
-                                             (oracle.FP8, 2), (oracle.FP8, 3), (oracle.FP8, 8)])
+@pytest.mark.parametrize("quantizer,n_src", [(oracle.ASYM, 3), (oracle.ASYM, 4), (oracle.ASYM, 6), (oracle.ASYM, 8), (oracle.SYM, 5), (oracle.SYM, 7),
+                                             (oracle.SYM, 8), (oracle.FP8, 2), (oracle.FP8, 3), (oracle.FP8, 4), (oracle.FP8, 6), (oracle.FP8, 7),
+                                             (oracle.FP8, 8)])
 @pytest.mark.parametrize("hidden", [1024, 3072, 4096, 8192])
 def test_allreduce_sim_rot_on_both_sides_of_the_limit(fc, quantizer, n_src, hidden):
-    # up to a limit (2^16 elements; by block, code and number of sources) the three steps run, through the workspace, above it
-    # one kernel, which leaves the workspace alone; slabs of a length that needs padding always take the kernel.  A few rows
-    # (compared with the oracle) are repeated up to the limit.
+    # up to a limit (2^16 elements; by block, code and number of sources) the steps run, through the workspace, above it one kernel, which
+    # leaves the workspace alone; so does the kernel for six and seven sources of up to 2^20 elements in short blocks, and slabs of a
+    # length that needs padding in blocks of 1024.  A few rows (compared with the oracle) are repeated up to the limit.
     bits = 8 if quantizer == oracle.FP8 else 4
     column = n_src - 3
-    limit = {1024: ((0, 4, 8, 24, 28, 32), (7, 28, 32, 34, 40, 40)), 4096: ((0, 8, 28, 32, 32, 32), (8, 32, 40, 40, 44, 48)),
-             8192: ((0, 8, 16, 18, 21, 28), (6, 18, 24, 40, 44, 48))}[hidden & -hidden][bits == 8][column] << 16 if column >= 0 else 0
+    limit = {1024: ((0, 4, 8, 32, 36, 32), (7, 0, 32, 34, 32, 32)), 4096: ((0, 8, 28, 35, 36, 32), (8, 8, 40, 40, 44, 48)),
+             8192: ((0, 8, 16, 30, 28, 28), (6, 18, 24, 40, 44, 48))}[hidden & -hidden][bits == 8][column] << 16 if column >= 0 else 0
     x = synth_inputs.make_partials(n_src, 5, hidden, seed=hidden + n_src)
     x[:, 1] = 0
     x[0, 2] = np.float16(6e-8) * (np.arange(hidden) % 5)
@@ -229,9 +230,9 @@ def test_allreduce_sim_rot_on_both_sides_of_the_limit(fc, quantizer, n_src, hidd
     few = dev(x.view(np.uint16)).view(torch.float16)
     for group in (128, 1024):
         want = dev(oracle.allreduce_sim_rot(x, group, bits, bits, quantizer).view(np.int16))
-        if n_src == 4 and group == 1024 and hidden < 8192:
+        if bits == 4 and n_src == 4 and group == 1024 and hidden < 8192:
             limit = {1024: 0, 4096: 4 << 16}[hidden & -hidden]
-        for rows in sorted({1, 2, 5, 12, limit // hidden, limit // hidden + 1, limit // hidden + 4} - {0}):
+        for rows in sorted({1, 2, 5, 12, (1 << 20) // hidden, (1 << 20) // hidden + 1, limit // hidden, limit // hidden + 1, limit // hidden + 4} - {0}):
             pick = torch.arange(rows, device="cuda") % 5
             need = fc.allreduce_sim_workspace_bytes(n_src, rows, hidden, group, bits, bits)
             space = torch.full((need + 64,), 0xA5, dtype=torch.uint8, device="cuda")
@@ -239,7 +240,8 @@ def test_allreduce_sim_rot_on_both_sides_of_the_limit(fc, quantizer, n_src, hidd
             fc.allreduce_sim_rot(few[:, pick], group, bits, bits, quantizer, out=y.t, workspace=space[:need])
             torch.cuda.synchronize(); y.check()
             assert (space[need:] == 0xA5).all(), "written past the workspace"
-            steps = rows * hidden <= limit and rows * hidden // group % 4 == 0
+            steps = rows * hidden <= limit and (rows * hidden // group % 4 == 0 or hidden & -hidden != 1024)
+            steps = steps and (n_src not in (6, 7) or hidden & -hidden != 1024 or rows * hidden > 1 << 20)
             assert bool((space[:need] != 0xA5).any()) == steps, "N=%d h=%d g=%d rows=%d: form" % (n_src, hidden, group, rows)
             assert torch.equal(y.t.view(torch.int16), want[pick]), "N=%d h=%d g=%d rows=%d" % (n_src, hidden, group, rows)
 
@@ -496,6 +498,7 @@ def test_allreduce_sim_rot_in_steps(fc, quantizer, bits_rs, bits_ag, hidden, gro
     # few rows of many sources: the sum, its codes and the inverse transform in one launch.  Zero-points far outside the codes, sums that
     # cancel to zero, partials of -0 and subnormals, groups of less and more than a wavefront
     for n_src in (5, 7, 8):
+        rows = 12 if n_src != 7 or hidden & -hidden > 2048 else (1 << 20) // hidden + 1      # seven sources of short blocks: past 2^20 elements
         x = synth_inputs.make_partials(n_src, 12, hidden, seed=hidden + group + n_src, outlier_frac=0.01)
         x[:, 1] = 0
         x[:, 2] = np.float16(-0.0)
@@ -504,7 +507,11 @@ def test_allreduce_sim_rot_in_steps(fc, quantizer, bits_rs, bits_ag, hidden, gro
         x[:, 5] = np.float16(6e-8) * (np.arange(hidden) % 5)
         x[:, 6] *= np.float16(60.0)
         want = oracle.allreduce_sim_rot(x, group, bits_rs, bits_ag, quantizer).view(np.uint16)
-        y = Guarded((12, hidden), torch.float16)
-        fc.allreduce_sim_rot(dev(x.view(np.uint16)).view(torch.float16), group, bits_rs, bits_ag, quantizer, out=y.t)
+        pick = np.arange(rows) % 12
+        need = fc.allreduce_sim_workspace_bytes(n_src, rows, hidden, group, bits_rs, bits_ag)
+        space = torch.full((need,), 0xA5, dtype=torch.uint8, device="cuda")
+        y = Guarded((rows, hidden), torch.float16)
+        fc.allreduce_sim_rot(dev(x.view(np.uint16)).view(torch.float16)[:, torch.from_numpy(pick).cuda()], group, bits_rs, bits_ag, quantizer, out=y.t, workspace=space)
         torch.cuda.synchronize(); y.check()
-        assert np.array_equal(y.t.cpu().numpy().view(np.uint16), want), "N=%d h=%d g=%d %d->%d" % (n_src, hidden, group, bits_rs, bits_ag)
+        assert hidden // group * rows % 4 or (space != 0xA5).any(), "not in steps: N=%d h=%d g=%d" % (n_src, hidden, group)
+        assert np.array_equal(y.t.cpu().numpy().view(np.uint16), want[pick]), "N=%d h=%d g=%d %d->%d" % (n_src, hidden, group, bits_rs, bits_ag)

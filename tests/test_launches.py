@@ -124,3 +124,18 @@ def test_rotated_codec_forms():
     got = kernels(*[dequantize_rot(q, elems, hidden, 128, bits) for q, bits, hidden, elems in
                     (("asym", 4, 2048, 2 * M), ("asym", 4, 2048, 2 * M + 2048), ("sym", 8, 8192, M), ("sym", 8, 8192, M + 8192), ("asym", 8, 1024, 2 * M), ("fp8", 8, 1024, 3 * M))])
     assert [k[0].split("<")[0] for k in got] == ["k_dequantize_rot" + s for s in ("_fine", "", "_fine", "", "_rows", "")]
+
+
+def test_rotated_all_reduce_in_steps():
+    # the last volume in steps and the next one, by code, block and number of sources; and where the steps begin
+    cases = [("asym", 4, 2048, 6, 32), ("asym", 4, 1024, 7, 36), ("sym", 4, 2048, 8, 32), ("asym", 8, 2048, 6, 24), ("sym", 8, 1024, 7, 24), ("asym", 8, 2048, 8, 28),
+             ("fp8", 8, 1024, 6, 34), ("fp8", 8, 2048, 7, 32), ("fp8", 8, 1024, 8, 32), ("fp8", 8, 4096, 4, 8), ("fp8", 8, 8192, 4, 18), ("asym", 8, 4096, 6, 35),
+             ("asym", 4, 4096, 7, 36), ("sym", 8, 8192, 6, 30), ("asym", 4, 8192, 7, 28), ("asym", 4, 2048, 5, 8)]
+    calls = [allreduce_rot(q, n, elems, h, 128, b, b) for q, b, h, n, limit in cases for elems in (limit << 16, (limit << 16) + h)]
+    got = kernels(*calls)
+    for case, a, b in zip(cases, got[::2], got[1::2]):
+        assert len(a) == 2 and a[1].startswith("k_reduce_rot_fine") and len(b) == 1, "%s: %s, then %s" % (case, a, b)
+    got = kernels(*[allreduce_rot(q, n, elems, 2048, 128, 8, 8) for q in ("asym", "fp8") for n in (6, 7) for elems in (M, M + 2048)])
+    assert [len(k) for k in got] == [1, 2] * 4
+    got = kernels(*[allreduce_rot("fp8", 4, elems, 2048, 128) for elems in (M // 16, M)])
+    assert [len(k) for k in got] == [1, 1]
