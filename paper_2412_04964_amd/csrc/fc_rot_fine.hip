@@ -458,15 +458,18 @@ hipError_t launch_reduce_rot_fine(int codec, int bits_rs, int bits_ag, const voi
     }
 }
 
-// All sources in one round of a workgroup, and at most 2^21 elements of all sources together (four wavefronts per SIMD).  us by elements (2^20) of a
-// partial, the form of fc_rot_sim.hip / this one, group 128: INT4, block 1024, N = 2  1/8: 4.67 / 3.28   1: 6.02 / 5.93   1.5: 6.35 / 7.11;   group 1024, N = 4  1/4: 5.34 /
-// 4.50   1/2: 5.63 / 5.70   3/4: 6.67 / 7.06;   block 2048, N = 1  1/8: 4.45 / 3.33   2: 6.35 / 6.30;   N = 2  1/8: 4.94 / 3.77   1: 6.39 / 5.43   1.5: 6.71 / 6.91;   N = 3  1/8: 5.09 /
-// 4.18   3/4: 6.45 / 6.31   1.5: 7.63 / 9.59;   block 4096, N = 1  1/8: 5.01 / 4.19   2: 6.83 / 6.74;   N = 2  1/8: 5.78 / 5.29   1: 6.46 / 6.08   2: 8.65 / 8.96;   N = 3 (two
-// rounds)  1/8: 6.65 / 7.80;   FP8, N = 2, block 2048  1/8: 5.46 / 3.70   1: 6.59 / 5.33;   block 4096  1/8: 6.17 / 5.22;   symmetric INT8, groups of the block, N = 3, block 2048
-// 1/8: 4.79 / 4.85.
+// All sources at once in a workgroup, and at most 2^21 elements of all sources together (four wavefronts per SIMD), 3 * 2^19 in blocks of 1024; a
+// single source, which no other hides, up to 5 * 2^18 in blocks of 1024 and 3 * 2^19 in blocks of 2048.  us by elements (2^20) of a partial, the
+// form of fc_rot_sim.hip / this one, group 128 unless said: INT4, block 1024, N = 1  1: 4.5 / 4.0   1.25: 5.3 / 4.8   1.38: 5.3 / 5.6   2: 5.3 / 5.8, group 1024  1.25: 5.4 / 5.2
+// 1.38: 5.4 / 6.1   2: 5.5 / 6.6;   N = 2  1/8: 4.67 / 3.28   3/4: 5.6 / 4.7   1: 5.7 / 5.7, group 1024  3/4: 5.6 / 5.3   1: 5.7 / 6.4;   group 1024, N = 4  1/4: 5.34 / 4.50   1/2: 5.63 / 5.70;   block 2048,
+// N = 1  1/8: 4.45 / 3.33   1.5: 5.7 / 5.1   1.75: 5.7 / 6.0;   N = 2  1/8: 4.94 / 3.77   1: 6.39 / 5.43   1.5: 6.71 / 6.91;   N = 3  1/8: 5.09 / 4.18   3/4: 6.45 / 6.31   1.5: 7.63 /
+// 9.59;   block 4096, N = 1  1/8: 5.01 / 4.19   2: 6.83 / 6.74;   N = 2  1/8: 5.78 / 5.29   1: 6.46 / 6.08   2: 8.65 / 8.96;   FP8, N = 2, block 2048  1/8: 5.46 / 3.70   1: 6.59 / 5.33;   block
+// 4096  1/8: 6.17 / 5.22;   symmetric INT8, groups of the block, N = 3, block 2048  1/8: 4.79 / 4.85.  Three sources in blocks of 4096 would take two rounds: 1/8: 6.65 / 7.80.
 bool allreduce_rot_fine_applies(int log_b, int n_src, int64_t n_elems)
 {
-    return log_b <= 12 && n_src <= 16 / fine_waves(log_b) && n_src * n_elems <= (int64_t)1 << 21;
+    if (log_b > 12 || n_src > 16 / fine_waves(log_b)) return false;
+    const int quarters = log_b == 10 ? (n_src == 1 ? 5 : 6) : log_b == 11 && n_src == 1 ? 6 : 8;      // of 2^20 elements
+    return n_src * n_elems <= quarters * ((int64_t)1 << 18);
 }
 
 template <int CODEC, int LB>

@@ -441,7 +441,8 @@ def test_dequantize_rot_signs_of_zero(fc, quantizer, bits, hidden):
 @pytest.mark.parametrize("hidden", [1024, 2048, 4096, 8192])
 def test_allreduce_sim_rot_sources_side_by_side(fc, quantizer, n_src, hidden):
     # few elements: the sources of a block go side by side through one workgroup, up to 2^21 elements and one round of workgroups, in two
-    # rounds from five sources on in blocks of 8192; shorter blocks with 8 elements per lane up to 2^21 elements of all sources together.
+    # rounds from five sources on in blocks of 8192; shorter blocks with 8 elements per lane up to 2^21 elements of all sources together, less in
+    # blocks of 1024 and of a single source.
     # Rows on both sides of that, an odd number of blocks of 1024 among them
     bits = 8 if quantizer == oracle.FP8 else 4
     waves = max(1, hidden // 2048)
@@ -455,7 +456,8 @@ def test_allreduce_sim_rot_sources_side_by_side(fc, quantizer, n_src, hidden):
     few = dev(x.view(np.uint16)).view(torch.float16)
     for group in (64, hidden):
         want = dev(oracle.allreduce_sim_rot(x, group, bits, bits, quantizer).view(np.int16))
-        fine = (1 << 21) // n_src // hidden
+        quarters = {1024: 6 - (n_src == 1), 2048: 8 - 2 * (n_src == 1)}.get(hidden, 8)
+        fine = (quarters << 18) // n_src // hidden
         for rows in (1, 3, fine, fine + 1, limit - 1, limit, limit + 1):
             pick = torch.arange(rows, device="cuda") % 5
             y = Guarded((rows, hidden), torch.float16)
