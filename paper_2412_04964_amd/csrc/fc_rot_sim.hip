@@ -351,12 +351,12 @@ RotLevels levels(int codec, int bits)
 //     1/4: 9.36 / 5.33   1: 9.86 / 7.01   2: 11.17 / 9.36   2.25: 11.20 / 11.32
 //   INT4, block 4096: N = 2  1/4: 7.14 / 5.80   1: 7.56 / 6.46   2: 9.24 / 8.62   3: 9.76 / 11.02;   N = 3  1/4: 8.67 / 6.87   2: 10.85 / 10.65
 //   INT4, block 8192: N = 2  1/4: 7.63 / 7.05   2: 9.00 / 8.39   2.25: 9.32 / 10.03 (INT8);   N = 3  1/4: 9.81 / 8.53   2: 11.07 / 9.71;   N = 4  1: 12.46 /
-//     10.09   2: 13.17 / 10.98;   N = 5  1.5: 15.18 / 15.19   2: 15.44 / 15.66;   N = 7  1.5: 19.48 / 15.80;   N = 8  2: 21.82 / 16.91
+//     10.09   2: 13.17 / 10.98;   N = 5, whose second round has one source  1.25: 14.4 / 15.3   2: 14.9 / 15.5;   N = 7  1.5: 19.48 / 15.80;   N = 8  2: 21.82 / 16.91
 //   FP8, N = 2: block 2048  1/4: 7.01 / 5.52   2: 9.45 / 8.03;   block 4096  1/4: 7.71 / 6.18   2: 10.58 / 9.43;   block 8192  1/4: 8.35 / 7.57   2: 9.90 / 9.02
 //   A single source: 5.03 / 5.09, 5.57 / 5.61.
 inline bool rot_spread_applies(int lb, int n_src, int64_t n_elems)
 {
-    if (n_src < 2 || n_elems > (int64_t)1 << 21) return false;
+    if (n_src < 2 || n_elems > (int64_t)1 << 21 || (lb == 13 && n_src == 5)) return false;
     const int waves = rot_block_waves(lb), at_once = 256 * (16 / (waves * rot_parts(lb, n_src)));
     return n_elems <= (int64_t)at_once * waves * 2048;
 }
@@ -379,7 +379,7 @@ hipError_t launch_one(const uint16_t *x, int n_src, int64_t n_elems, int group, 
     constexpr int kTile = 2048 * rot_group_waves(LB);
     if (rot_spread_applies(LB, n_src, n_elems)) return launch_spread<CODEC, LB>(x, n_src, n_elems, group, rs, ag, y, stream);
     const dim3 grid((unsigned)((n_elems + kTile - 1) / kTile)), block(64 * rot_group_waves(LB));
-    if constexpr (LB == 13)                // see k_allreduce_rot; a single source, the others go side by side
+    if constexpr (LB == 13)                // see k_allreduce_rot; one and five sources, the others go side by side
         if (n_elems <= 256 * (int64_t)kTile)
             return launch_kernel(k_allreduce_rot<CODEC, true, LB>, grid, block, stream, x, n_elems, n_src, log2_int(group), rs, ag, y);
     return launch_kernel(k_allreduce_rot<CODEC, false, LB>, grid, block, stream, x, n_elems, n_src, log2_int(group), rs, ag, y);

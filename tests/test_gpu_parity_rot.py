@@ -441,7 +441,7 @@ def test_dequantize_rot_signs_of_zero(fc, quantizer, bits, hidden):
 @pytest.mark.parametrize("hidden", [1024, 2048, 4096, 8192])
 def test_allreduce_sim_rot_sources_side_by_side(fc, quantizer, n_src, hidden):
     # few elements: the sources of a block go side by side through one workgroup, up to 2^21 elements and one round of workgroups, in two
-    # rounds from five sources on in blocks of 8192; shorter blocks with 8 elements per lane up to 2^21 elements of all sources together, less in
+    # rounds from six sources on in blocks of 8192; shorter blocks with 8 elements per lane up to 2^21 elements of all sources together, less in
     # blocks of 1024 and of a single source.
     # Rows on both sides of that, an odd number of blocks of 1024 among them
     bits = 8 if quantizer == oracle.FP8 else 4

@@ -145,7 +145,8 @@ def test_rotated_all_reduce_in_one_launch():
     # all sources at once with 8 elements per lane; side by side; one after the other
     fine, spread, plain = "k_allreduce_rot_fine<", "k_allreduce_rot_spread<", "k_allreduce_rot<"
     cases = [("asym", 1, 1024, 5 * M // 4, fine, plain), ("sym", 1, 2048, 3 * M // 2, fine, plain), ("fp8", 1, 4096, 2 * M, fine, plain), ("asym", 2, 1024, 3 * M // 4, fine, spread),
-             ("asym", 2, 2048, M, fine, spread), ("fp8", 2, 4096, M, fine, spread), ("sym", 3, 1024, M // 2, fine, spread), ("asym", 2, 8192, 2 * M, spread, plain), ("sym", 3, 4096, 2 * M, spread, plain)]
+             ("asym", 2, 2048, M, fine, spread), ("fp8", 2, 4096, M, fine, spread), ("sym", 3, 1024, M // 2, fine, spread), ("asym", 2, 8192, 2 * M, spread, plain), ("sym", 3, 4096, 2 * M, spread, plain),
+             ("asym", 5, 8192, M + 8192, plain, plain), ("sym", 6, 8192, 2 * M, spread, plain)]
     got = kernels(*[allreduce_rot(q, n, elems, h, 128, 8, 8) for q, n, h, limit, _, _ in cases for elems in (limit, limit + h)])
     for case, a, b in zip(cases, got[::2], got[1::2]):
         assert len(a) == len(b) == 1 and a[0].startswith(case[4]) and b[0].startswith(case[5]), "%s: %s, then %s" % (case, a, b)
