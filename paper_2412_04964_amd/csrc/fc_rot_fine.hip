@@ -292,8 +292,8 @@ __global__ __launch_bounds__(64 * fine_waves(LB)) void k_reduce_rot_fine(
     *reinterpret_cast<u32x4 *>(y + e0 + at * 8) = fine_back<LB>(v, s2, L, lds, wave);
 }
 
-// The whole rotated all-reduce of a block in one workgroup, n_parts sources at once (see SPREAD in fc_rot_sim.hip), 8 elements per lane; what does
-// not fit goes in further rounds.  LDS: two areas of 2 KB per wavefront, for the exchanges and (the second one) the handing over
+// The whole rotated all-reduce of a block in one workgroup, 8 elements per lane: a part of the workgroup per source (see SPREAD in
+// fc_rot_sim.hip), n_src <= 16 / fine_waves(LB).  LDS: two areas of 2 KB per wavefront, for the exchanges and (the second one) the handing over
 template <int CODEC, int LB>
 __global__ __launch_bounds__(1024) void k_allreduce_rot_fine(const uint16_t *__restrict__ x, int64_t n_elems, int n_src, int lpg, float q_rs,
                                                             float rcp_rs, float q_ag, float rcp_ag, uint16_t *__restrict__ y)
@@ -305,46 +305,34 @@ __global__ __launch_bounds__(1024) void k_allreduce_rot_fine(const uint16_t *__r
     const u32 lane = threadIdx.x & 63u;
     const u32 wave_all = (u32)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const u32 wave = wave_all % (u32)kWaves, part = wave_all / (u32)kWaves;
-    const int n_parts = n_src < 16 / kWaves ? n_src : 16 / kWaves;
     uint8_t *mine = lds + part * (2 * kArea);
     float (*slot)[2] = slots + part * kWaves;
     const RotLane L = rot_lane<true>(lane);
     const int64_t e = ((int64_t)blockIdx.x << LB) + (wave * 64 + L.pos) * 8;
-    auto fetch = [&](int j) { return *reinterpret_cast<const u32x4 *>(x + (int64_t)j * n_elems + e); };
     constexpr float fwd = 1.0f / (float)(1 << ((LB + 1) / 2));          // 2^-ceil(n/2), n = LB
 
+    const u32x4 raw = *reinterpret_cast<const u32x4 *>(x + (int64_t)part * n_elems + e);
+    float v[8], s;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) first_stage(raw[i], v[2 * i], v[2 * i + 1]);
+    fine_transform<LB, 1>(v, L, mine, wave);
+    fine_codes<CODEC>(v, fwd, lpg, slot, wave, lane, q_rs, rcp_rs, s);
+    if constexpr (LB == 12) lds_barrier();                             // every wavefront has taken the second exchange
+    if (part != 0) {
+        fine_put(v, mine + kArea + wave * 2048 + lane * 16);
+        scale[wave_all][lane] = s;
+    }
+    lds_barrier();
+    if (part != 0) return;                                             // a barrier waits for the wavefronts that are left
     float acc[8];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) acc[i] = 0.0f;
-    u32x4 raw = fetch((int)part);                                      // n_parts <= n_src
-    for (int j = 0; j < n_src; j += n_parts) {
-        float v[8], s;
+    for (int i = 0; i < 8; ++i) acc[i] = fmaf(v[i], s, 0.0f);
+    for (int k = 1; k < n_src; ++k) {                                  // ReduceSum, source order
+        fine_get(lds + k * (2 * kArea) + kArea + wave * 2048 + lane * 16, v);
+        s = scale[k * kWaves + wave][lane];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) first_stage(raw[i], v[2 * i], v[2 * i + 1]);
-        const int next = j + n_parts + (int)part;                      // a part without a source repeats the last one; nothing takes it
-        if (j + n_parts < n_src) raw = fetch(next < n_src ? next : n_src - 1);
-        fine_transform<LB, 1>(v, L, mine, wave);
-        fine_codes<CODEC>(v, fwd, lpg, slot, wave, lane, q_rs, rcp_rs, s);
-        if constexpr (LB == 12) lds_barrier();                         // every wavefront has taken the second exchange
-        if (part != 0) {
-            fine_put(v, mine + kArea + wave * 2048 + lane * 16);
-            scale[wave_all][lane] = s;
-        }
-        lds_barrier();
-        if (part == 0) {
-#pragma unroll
-            for (int i = 0; i < 8; ++i) acc[i] = fmaf(v[i], s, acc[i]);
-            for (int k = 1; k < n_parts && j + k < n_src; ++k) {       // ReduceSum, source order
-                fine_get(lds + k * (2 * kArea) + kArea + wave * 2048 + lane * 16, v);
-                s = scale[k * kWaves + wave][lane];
-#pragma unroll
-                for (int i = 0; i < 8; ++i) acc[i] = fmaf(v[i], s, acc[i]);
-            }
-        }
-        if (j + n_parts < n_src) lds_barrier();
+        for (int i = 0; i < 8; ++i) acc[i] = fmaf(v[i], s, acc[i]);
     }
-    if (part != 0) return;                                             // a barrier waits for the wavefronts that are left
-    float s;
     fine_codes<CODEC>(acc, 1.0f, lpg, slot, wave, lane, q_ag, rcp_ag, s);
     *reinterpret_cast<u32x4 *>(y + e) = fine_back<LB>(acc, s, L, mine, wave);
 }
@@ -477,10 +465,10 @@ static hipError_t allreduce_one(const uint16_t *x, int n_src, int64_t n_elems, i
                                 hipStream_t stream)
 {
     const auto top = [](int bits) { return CODEC == kFp8 ? 448.0f : (float)((1 << (CODEC == kSym ? bits - 1 : bits)) - 1); };
-    constexpr int kWaves = fine_waves(LB), kMost = 16 / kWaves;
-    const int parts = n_src < kMost ? n_src : kMost;
-    return launch_kernel_lds(k_allreduce_rot_fine<CODEC, LB>, dim3((unsigned)(n_elems >> LB)), dim3(64 * kWaves * parts),
-                             (size_t)(parts * kWaves * 4096), stream, x, n_elems, n_src, group / 8, top(bits_rs), 1.0f / top(bits_rs),
+    constexpr int kWaves = fine_waves(LB);
+    if (n_src > 16 / kWaves) return hipErrorInvalidValue;
+    return launch_kernel_lds(k_allreduce_rot_fine<CODEC, LB>, dim3((unsigned)(n_elems >> LB)), dim3(64 * kWaves * n_src),
+                             (size_t)(n_src * kWaves * 4096), stream, x, n_elems, n_src, group / 8, top(bits_rs), 1.0f / top(bits_rs),
                              top(bits_ag), 1.0f / top(bits_ag), y);
 }
 
