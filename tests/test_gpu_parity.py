@@ -71,9 +71,10 @@ def gpu_quantize(fc, x16, group, bits):
     return c.t.cpu().numpy(), s.t.cpu().numpy(), z.t.cpu().numpy()
 
 
-# fc_dequant_reduce_requant has two kernels for the asymmetric quantizer: a launch-bound one (one code word per lane
-# and source) up to 2048 wavefronts of it, i.e. at most 2^20 elements, and the bulk kernel above.  Groups never
-# cross token rows, so repeating the token rows of a case gives the same case at a volume the bulk kernel takes.
+# fc_dequant_reduce_requant has two kernels: a launch-bound one (one code word per lane and source) up to 6144 wavefronts of it, i.e.
+# at most 3 * 2^20 elements (7 * 2^19 in groups of 8192), and the bulk kernel above.  Groups never cross token rows, so repeating the
+# token rows of a case gives the same case at another volume: here one with workgroups of several wavefronts, which the launch-bound
+# kernel still takes in part; test_gpu_parity_bulk.py runs the cases once more at volumes past every limit.
 BULK_ELEMS = 1 << 20
 
 

@@ -398,7 +398,7 @@ def test_full_chip_runs_repeat(fc, quantizer, bits, hidden):
 @pytest.mark.parametrize("quantizer,bits", [(oracle.ASYM, 4), (oracle.ASYM, 8), (oracle.SYM, 4), (oracle.SYM, 8)])
 @pytest.mark.parametrize("hidden", [1024, 2048, 4096, 8192])
 def test_dequantize_rot_signs_of_zero(fc, quantizer, bits, hidden):
-    # the short form drops signs of zero inside the transform, the literal one keeps them, and the wavefronts (2048
+    # the short form of large volumes drops signs of zero inside the transform, the literal one keeps them, and the wavefronts (2048
     # elements) of one block may take different ones: rows that cancel to zeros everywhere, with zero-points and
     # scales out of the short form's reach in all, in one and in none of the wavefronts; fractional zero-points and
     # subnormal scales whose products underflow to -0.  The result must agree in every bit, zeros included.
@@ -434,6 +434,13 @@ def test_dequantize_rot_signs_of_zero(fc, quantizer, bits, hidden):
     for r in range(rows):
         assert same_bits(got[r].view(np.uint16), want[r].view(np.uint16)), \
             "row %d h=%d b=%d q=%d: %s" % (r, hidden, bits, quantizer, first_diff(got[r].view(np.uint16), want[r].view(np.uint16)))
+    # the same rows over and over in volumes past the limits of the launch-bound forms, which have the literal form only
+    pick = torch.arange((4 << 20) // hidden + 1, device="cuda") % rows
+    y = Guarded((pick.numel(), hidden), torch.float16)
+    fc.dequantize_rot(dev(codes)[pick], dev(s)[pick], dev(z)[pick], hidden, group, bits, quantizer, out=y.t)
+    torch.cuda.synchronize(); y.check()
+    same = (y.t.view(torch.int16) == dev(want.view(np.int16))[pick]).all(dim=1)
+    assert same.all(), "rows %s of 12, h=%d b=%d q=%d" % (sorted(set((torch.nonzero(~same)[:, 0] % rows).tolist())), hidden, bits, quantizer)
 
 
 @pytest.mark.parametrize("quantizer", [oracle.ASYM, oracle.SYM, oracle.FP8])

@@ -408,12 +408,15 @@ def test_codecs_where_a_launch_limits_its_wavefronts(fc, variant, group):
         assert torch.equal(y[1:-1].view(torch.int16), want_y[at]) and (y[0] == 7.0).all() and (y[-1] == 7.0).all()
 
 
-@pytest.mark.parametrize("variant", ["asym", "sym", "cmeta", "fp8"])
-@pytest.mark.parametrize("bits, group, limits", [
+CODEC_LIMITS = [
     (4, 32, (4 << 20, 5 << 20, 8 << 20)), (4, 64, (4 << 20, 8 << 20)), (4, 128, (4 << 20, 5 << 20, 8 << 20)), (4, 256, (5 << 19, 36 << 20)), (4, 512, (5 << 19,)),
     (4, 1024, (3 << 19, 8 << 20, 36 << 20)), (4, 2048, (3 << 19, 6 << 19, 8 << 20, 36 << 20)), (4, 8192, (4 << 19, 6 << 19)),
     (8, 32, (1 << 20, 3 << 19)), (8, 128, (1 << 20, 3 << 19)), (8, 512, (1 << 20, 3 << 19)), (8, 1024, (1 << 20,)), (8, 2048, (4 << 19,)),
-    (8, 8192, (4 << 19,))])
+    (8, 8192, (4 << 19,))]
+
+
+@pytest.mark.parametrize("variant", ["asym", "sym", "cmeta", "fp8"])
+@pytest.mark.parametrize("bits, group, limits", CODEC_LIMITS)
 def test_codecs_on_both_sides_of_every_limit(fc, variant, bits, group, limits):
     # the tiles of quantizer and dequantizer follow volume and group: the same rows over and over, of a length that leaves ragged tiles
     if variant == "fp8" and bits != 8:
@@ -436,3 +439,52 @@ def test_codecs_on_both_sides_of_every_limit(fc, variant, bits, group, limits):
             y = torch.full((tokens + 2, hidden), 7.0, dtype=torch.float16, device="cuda")
             getattr(fc, "dequantize" + sfx)(*got, hidden, group, *width, out=y[1:-1])
             assert torch.equal(y[1:-1].view(torch.int16), want_y[at]) and (y[0] == 7.0).all() and (y[-1] == 7.0).all()
+
+
+@pytest.mark.parametrize("variant", ["asym", "sym", "cmeta", "fp8"])
+@pytest.mark.parametrize("bits, group, limits", CODEC_LIMITS)
+def test_hard_values_in_every_form_of_the_codecs(fc, variant, bits, group, limits):
+    # constant and degenerate groups, ties, subnormals, the upper clamp, every binary16 value, and metadata that no quantizer gives (huge,
+    # tiny and fractional ones, zero-points out of reach), as a few rows over and over in the forms of small and large volumes
+    if variant == "fp8" and bits != 8:
+        pytest.skip("FP8 codes have 8 bits")
+    hidden = (31 if group <= 2048 else 3) * group
+    sfx = "" if variant == "asym" else "_" + variant
+    width = () if variant == "fp8" else (bits,)
+    rng = np.random.default_rng(group + bits)
+    hard = [synth_inputs.adversarial_groups(group, seed=group).reshape(-1, group)]
+    hard += [synth_inputs.make_partials_stress(1, 1, 6 * group, kind, seed=group + kind).reshape(-1, group) for kind in range(1, synth_inputs.STRESS_KINDS)]
+    every = np.arange(1 << 16, dtype=np.uint16).view(np.float16)
+    every = rng.permutation(every[np.isfinite(every.astype(np.float32))])
+    hard.append(np.resize(every, (-(-every.size // group), group)))
+    hard = np.concatenate(hard)
+    rows = min(-(-hard.shape[0] * group // hidden), 61)
+    x = np.resize(hard[rng.permutation(hard.shape[0])], (rows * hidden // group, group)).reshape(rows, hidden)
+    coded = getattr(oracle, "quantize" + sfx)(x, group, *width)
+    odd = [rng.integers(0, 256, size=coded[0].shape, dtype=np.uint8)]
+    if variant == "fp8":
+        odd[0][(odd[0] & 0x7F) == 0x7F] = 0x7E                           # no NaN bytes
+    if variant == "cmeta":
+        meta = np.empty(coded[1].shape + (2,), np.float16)
+        meta[..., 0] = np.exp(rng.uniform(-16, 11, size=coded[1].shape))
+        meta[..., 1] = rng.uniform(-6e4, 6e4, size=coded[1].shape)
+        meta[::2, :, 1] = np.rint(rng.uniform(-1100, 1100, size=coded[1][::2].shape))
+        odd.append(meta.view(np.uint32)[..., 0])
+    else:
+        odd.append(np.exp(rng.uniform(-95, 12, size=coded[1].shape)).astype(np.float32))
+    if variant == "asym":
+        z = rng.uniform(-5e4, 5e4, size=coded[2].shape).astype(np.float32)
+        z[::2] = np.rint(rng.uniform(-1100, 1100, size=z[::2].shape))
+        odd.append(z)
+    put = lambda a: torch.from_numpy(np.ascontiguousarray(a).view(np.int32) if a.dtype == np.uint32 else np.ascontiguousarray(a)).cuda()
+    xd = torch.from_numpy(x.view(np.uint16)).cuda().view(torch.float16)
+    want = [torch.from_numpy(np.ascontiguousarray(a).view(np.uint8)).cuda() for a in coded]
+    odd_d = [put(a) for a in odd]
+    want_y = torch.from_numpy(getattr(oracle, "dequantize" + sfx)(*odd, hidden, group, *width).view(np.int16)).cuda()
+    for tokens in sorted({rows} | {n for limit in limits for n in (limit // hidden, limit // hidden + 1)}):
+        at = torch.arange(tokens, device="cuda") % rows
+        what = "%s %d bits g=%d %d rows" % (variant, bits, group, tokens)
+        for g, w in zip(getattr(fc, "quantize" + sfx)(xd[at], group, *width), want):
+            assert torch.equal(g.view(torch.uint8), w[at]), what
+        y = getattr(fc, "dequantize" + sfx)(*[a[at] for a in odd_d], hidden, group, *width)
+        assert torch.equal(y.view(torch.int16), want_y[at]), what

@@ -64,7 +64,7 @@ def test_fused_small_and_bulk(fc, name, n_src):
 @pytest.mark.parametrize("name", list(PAIRS))
 @pytest.mark.parametrize("n_src", [1, 2, 3, 4, 5, 8])
 def test_fused_at_the_limit_of_the_launch_bound_kernel(fc, name, n_src):
-    # the largest volume of the launch-bound kernel (a number of wavefronts, by fan-in where a group spans 32 lanes) and the next row on the
+    # the largest volume of the launch-bound kernel (a number of wavefronts, by quantizer, widths and fan-in) and the next row on the
     # bulk kernel; 6 rows of 8-bit codes are the largest volume of few sources that is too small for it
     t, h = 6, 1024
     meta_type = torch.int32 if name == "cmeta" else torch.float32
@@ -74,7 +74,9 @@ def test_fused_at_the_limit_of_the_launch_bound_kernel(fc, name, n_src):
         c, m = wire(name, n_src, t, h, g, bits_in, seed=n_src)
         want = [dev(np.ascontiguousarray(a).view(np.uint8)) for a in getattr(oracle, "dequant_reduce_requant_" + name)(c, m, h, g, *bits)]
         few_c, few_m = dev(c), dev(m.view(np.int32)) if name == "cmeta" else dev(m)
-        limit = (2048 if lanes < 32 else min(2048, 448 * n_src * (8 // bits_in))) * (2048 // bits_in)      # elements
+        waves = 3 if n_src == 1 and bits_in == 8 else 2 if n_src == 1 else (6 if lanes < 32 else 5) if bits_in == 8 else \
+            6 if name == "sym" else 3 if bits_out == 8 and n_src <= 4 else 4
+        limit = waves * 1024 * (2048 // bits_in)                              # elements
         for rows in (6, 7, limit // h, limit // h + 1):
             pick = torch.arange(rows, device="cuda") % t
             co = Guarded((rows, h * bits_out // 8), torch.uint8)

@@ -104,6 +104,14 @@ def test_fused_step_forms():
         (("asym", 5, 128, (4, 8)), 5 * M // 2, small, bulk), (("cmeta", 3, 256, (4, 8)), 3 * M // 2, small, bulk), (("cmeta", 3, 256, (4, 4)), 2 * M, small, bulk),
         (("cmeta", 8, 128, (4, 8)), 2 * M, small, bulk), (("sym", 2, 128, (4, 8)), 3 * M, small, bulk), (("sym", 4, 32, (8, 4)), 3 * M // 2, small, bulk),
         (("fp8", 4, 256, ()), 5 * M // 4, small, bulk), (("asym", 1, 128, (8, 8)), 3 * M // 4, small, bulk), (("asym", 8, 8192, (8, 8)), 7 * M // 2, small, "k_dequant_reduce_requant_wide<")])
+    # the rule that test_fused_at_the_limit_of_the_launch_bound_kernel works with
+    for name, pairs in (("sym", ((4, 4), (4, 8), (8, 4), (8, 8))), ("cmeta", ((4, 4), (4, 8), (8, 4), (8, 8))), ("fp8", ((8, 8),))):
+        for n in (1, 2, 3, 4, 5, 8):
+            for (bits_in, bits_out), lanes in [(p, l) for p in pairs for l in (16, 32)]:
+                waves = 3 if n == 1 and bits_in == 8 else 2 if n == 1 else (6 if lanes < 32 else 5) if bits_in == 8 else 6 if name == "sym" else 3 if bits_out == 8 and n <= 4 else 4
+                limit = waves * 1024 * (2048 // bits_in)
+                a, b = kernels(*[fused(name, n, elems, lanes * 32 // bits_in, bits_in, bits_out) for elems in (limit, limit + 1024)])
+                assert a[0].startswith(small) and b[0].startswith(bulk), "%s N=%d %d>%d %d lanes: %s, then %s" % (name, n, bits_in, bits_out, lanes, a, b)
     got = kernels(fused("sym", 2, M // 16, 1024), fused("fp8", 2, M // 16, 1024), fused("asym", 2, M // 16, 1024), fused("sym", 3, M // 16, 1024), fused("sym", 2, M // 16, 2048))
     assert [k[0].startswith(small) for k in got] == [False, False, True, True, True], got
 
