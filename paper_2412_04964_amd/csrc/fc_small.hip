@@ -181,15 +181,18 @@ static hipError_t launch_small_codec(int bits_rs, int bits_ag, const uint16_t *x
     }
 }
 
-// Where the two forms cross (hidden 8192, g = 128, us per launch under graph replay, this one / bulk; asymmetric INT8, symmetric
-// INT4, compact metadata INT4, FP8):
-//   N = 8   64 tokens 4.07 / 5.09, 3.82 / 4.72, 4.14 / 4.94, 3.86 / 4.93; 128 tokens (the limit) 6.55 / 6.72, 6.26 / 5.92,
-//           6.60 / 6.68, 6.29 / 6.83; 160 tokens 7.35 / 6.88, 6.96 / 6.29, 7.48 / 7.02, 6.99 / 6.95
-//   N = 7   96 tokens 5.65 / 6.06, 5.37 / 5.14, 5.62 / 5.99, 5.37 / 5.97; 128 tokens 6.72 / 6.30, 6.43 / 5.48, 6.76 / 6.30,
-//           6.38 / 6.16: seven wavefronts leave one of a workgroup's SIMDs half empty
-//   N = 4   128 tokens 4.19 / 4.87, 4.03 / 4.51, 4.25 / 5.01, 4.01 / 4.70; 160 tokens 4.88 / 5.04, 4.59 / 4.74, 4.90 / 5.18,
-//           4.62 / 4.96; 192 tokens 5.23 / 5.21, 4.95 / 4.98, 5.25 / 5.35, 4.98 / 5.12
-// Hence at most 2^20 elements per partial, and of seven partials at most 6 * 2^20 altogether.
+// Where the two forms cross (hidden 8192, g = 128, us per launch under graph replay, this one / bulk; asymmetric, symmetric, compact metadata
+// INT4, FP8):
+//   N = 2   128 tokens (the limit) 2.80 / 3.03, 2.60 / 2.66, 2.81 / 3.04, 2.61 / 2.84; 160 tokens 3.13 / 3.07, 2.89 / 2.73, 3.23 / 3.17, 2.93 / 2.96
+//   N = 4   128 tokens 3.46 / 3.94, 3.07 / 3.38, 3.48 / 3.90, 3.14 / 3.84; 160 tokens 4.13 / 4.35, 3.85 / 3.80, 4.18 / 4.35, 3.85 / 4.29; 192 tokens 4.73 /
+//           4.45, 4.40 / 3.92, 4.76 / 4.51, 4.41 / 4.36
+//   N = 6   128 tokens 4.88 / 5.29, 4.53 / 4.49, 4.98 / 5.33, 4.55 / 5.19; 160 tokens 5.76 / 5.55, 5.39 / 4.74, 5.85 / 5.58, 5.39 / 5.38
+//   N = 7   96 tokens 4.84 / 5.60, 4.53 / 4.74, 4.88 / 5.53, 4.54 / 5.51; 115 tokens 5.73 / 5.80, 5.34 / 4.97, 5.77 / 5.79, 5.36 / 5.71; 128 tokens 6.13 /
+//           5.85, 5.76 / 4.99, 6.16 / 5.86, 5.77 / 5.77: seven wavefronts leave one of a workgroup's SIMDs half empty
+//   N = 8   64 tokens 3.40 / 4.96, 3.09 / 4.57, 3.54 / 4.77, 3.12 / 4.86; 128 tokens 5.92 / 6.33, 5.55 / 5.45, 6.00 / 6.32, 5.59 / 6.23; 160 tokens
+//           6.74 / 6.48, 6.29 / 5.62, 6.88 / 6.45, 6.34 / 6.41
+// They cross between 128 and 192 tokens, 128 and 160 for most: at most 2^20 elements per partial for all of them, 1 to 2 % too many for six and eight
+// sources of symmetric codes, and of seven partials at most 6 * 2^20 altogether.
 bool allreduce_small_applies(int n_src, int64_t n_elems, int group)
 {
     return group <= kSmallWaveElems && n_elems <= kSmallAllreduceMaxElems &&
