@@ -41,7 +41,8 @@ static QuantizeForm quantize_form(int64_t n_elems, int group)
 // cross; the quantizers without a zero-point have less to compute per lane and cross earlier.  us by elements (2^20), hidden 8192, the
 // other forms / this one:
 //   4-bit codes, group 128: asymmetric  1/8: 2.09 / 2.03   1: 2.72 / 2.31   2.5: 2.61 / 2.38   3: 2.64 / 2.57   4: 2.76 / 2.85   4.5: 3.24 / 3.20
-//     5: 3.44 / 3.48, over 700 MB  3: 3.03 / 2.71   4: 3.14 / 3.09   5: 3.54 / 3.70;   symmetric  4: 2.60 / 2.69, 700 MB 2.98 / 2.93
+//     5: 3.44 / 3.48, over 700 MB  3: 3.03 / 2.71   4: 3.14 / 3.09   5: 3.54 / 3.70;   symmetric  4: 2.69 / 2.67, 700 MB 2.98 / 2.93
+//     binary16 metadata  3.5: 2.68 / 2.73, 700 MB -3 to -5 %   4: 2.77 / 2.93
 //   group 256, 512: 2.5: 2.60 / 2.57   3.5: 2.63 / 2.91;   group 1024: symmetric, 700 MB  1.5: +3 %   2.5: +7 %
 //   group 8192: asymmetric  1: 3.35 / 2.72   3: 4.33 / 3.84;   symmetric  2: -7 %   2.5: +4 %
 //   8-bit codes, group 32: 1/2: 2.53 / 2.28   1: 2.72 / 2.35;   group 256: asymmetric  1.5: 3.00 / 2.71, symmetric +3 %
@@ -51,7 +52,7 @@ static bool quantize_small_applies(int codec, int bits, int64_t n_elems, int gro
     const bool zero_point = codec == CODEC_ASYM || codec == CODEC_ASYMH;
     int halves;                                                          // of 2^20 elements
     if (bits == 4)
-        halves = group <= 128 ? 8 : group <= 512 ? 5 : group == 1024 ? 3 : zero_point ? 6 : group == 2048 ? 3 : 4;
+        halves = group <= 128 ? (zero_point ? 7 : 8) : group <= 512 ? 5 : group == 1024 ? 3 : zero_point ? 6 : group == 2048 ? 3 : 4;
     else
         halves = group >= 2048 ? 4 : zero_point && group <= 512 ? 3 : 2;
     return group <= 8192 && n_elems <= halves * ((int64_t)1 << 19);

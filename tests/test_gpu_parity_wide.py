@@ -409,7 +409,7 @@ def test_codecs_where_a_launch_limits_its_wavefronts(fc, variant, group):
 
 
 CODEC_LIMITS = [
-    (4, 32, (4 << 20, 5 << 20, 8 << 20)), (4, 64, (4 << 20, 8 << 20)), (4, 128, (4 << 20, 5 << 20, 8 << 20)), (4, 256, (5 << 19, 36 << 20)), (4, 512, (5 << 19,)),
+    (4, 32, (7 << 19, 4 << 20, 5 << 20, 8 << 20)), (4, 64, (7 << 19, 4 << 20, 8 << 20)), (4, 128, (7 << 19, 4 << 20, 5 << 20, 8 << 20)), (4, 256, (5 << 19, 36 << 20)), (4, 512, (5 << 19,)),
     (4, 1024, (3 << 19, 8 << 20, 36 << 20)), (4, 2048, (3 << 19, 6 << 19, 8 << 20, 36 << 20)), (4, 8192, (4 << 19, 6 << 19)),
     (8, 32, (1 << 20, 3 << 19)), (8, 128, (1 << 20, 3 << 19)), (8, 512, (1 << 20, 3 << 19)), (8, 1024, (1 << 20,)), (8, 2048, (4 << 19,)),
     (8, 8192, (4 << 19,))]

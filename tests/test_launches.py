@@ -36,7 +36,7 @@ def forms(make, limits):
 def test_quantizer_forms():
     # 8 elements per lane; 16 in workgroups of 256; 16 in workgroups of 64; 32
     forms(lambda q, bits, group, elems: quantize(q, elems, group, bits), [
-        (("asym", 4, 128), 4 * M, "k_quantize_small<4,0,0>", "k_quantize<4,8,0,16,256>"), (("asym", 4, 128), 8 * M, "k_quantize<4,8,0,16,256>", "k_quantize<4,8,0,16,64>"),
+        (("asym", 4, 128), 7 * M // 2, "k_quantize_small<4,0,0>", "k_quantize<4,8,0,16,256>"), (("asym", 4, 128), 8 * M, "k_quantize<4,8,0,16,256>", "k_quantize<4,8,0,16,64>"),
         (("sym", 4, 32), 4 * M, "k_quantize_small<4,1,0>", "k_quantize<4,2,1,16,256>"), (("cmeta", 4, 64), 8 * M, "k_quantize<4,4,3,16,256>", "k_quantize<4,4,3,16,64>"),
         (("asym", 4, 256), 5 * M // 2, "k_quantize_small<4,0,0>", "k_quantize<4,8,0,32,128>"), (("asym", 4, 256), 36 * M - 8192, "k_quantize<4,8,0,32,128>", "k_quantize<4,0,0,16,64>"),
         (("sym", 4, 512), 36 * M - 8192, "k_quantize<4,0,1,32,256>", "k_quantize<4,0,1,16,64>"), (("asym", 4, 1024), 3 * M // 2, "k_quantize_small<4,0,1>", "k_quantize<4,0,0,32,256>"),
