@@ -314,43 +314,44 @@ int rot_steps(int codec, const void *x_f16, int n_src, int64_t tokens, int64_t h
                                                  static_cast<hipStream_t>(hip_stream)));
 }
 
-// Whether the steps are the faster form of the rotated all-reduce: with few elements of many sources all partials' quantizations
-// spread over the chip and one more launch take less time than one launch of few workgroups, each of which goes through the sources in
-// turn (up to 2^21 elements of few sources side by side, rot_spread_applies and allreduce_rot_fine_applies).  Up to this many
-// elements, in units of 2^16, by the block and the number of sources, the steps are taken; blocks of 2048 stand with 1024.
-// us by elements (2^20), group 128, steps / one launch:
-//   INT4, block 2048: N = 3  1/4: 6.0 / 4.4   1: 8.2 / 6.2;   N = 4  1/4: 6.0 / 4.8   1: 8.5 / 6.5;   N = 5  1/2: 7.6 / 6.5   1.25: 10.5 / 11.0;   N = 6  1: 10.1 / 8.4
-//     1.25: 11.1 / 15.7   2: 14.3 / 16.2;   N = 7  1: 10.5 / 9.0   2.25: 17.1 / 19.0;   N = 8  1: 10.9 / 10.1   2: 16.9 / 20.6
-//   block 4096: N = 4  1/2: 7.3 / 7.0   1: 8.7 / 7.3;   N = 5  1.25: 11.0 / 13.9   2: 13.3 / 14.5;   N = 6  2.25: 16.6 / 17.9;   N = 8  1/4: 7.5 / 9.6   2: 17.3 / 21.6
-//   block 8192: N = 4  1/2: 8.8 / 10.0   1: 9.8 / 9.9;   N = 5  1: 10.9 / 14.7   2: 13.7 / 15.6;   N = 6  2: 15.0 / 16.2;   N = 7  1.75: 15.4 / 16.5;   N = 8  1.75: 16.5 / 17.1
-//   FP8, block 2048: N = 3  1/4: 5.7 / 4.3;   N = 4  1/4: 5.7 / 4.7;   N = 5  1.75: 14.1 / 15.9;   N = 6  1.25: 13.1 / 17.6   2: 18.1 / 18.5;   N = 7  2: 18.8 / 21.3   2.25: 22.7 / 21.6
-//     N = 8  2: 21.9 / 23.8   2.25: 25.8 / 24.0;   block 4096: N = 3  1/2: 6.8 / 7.3   1: 8.4 / 7.5;   N = 4  1/2: 7.1 / 7.7   1: 9.4 / 7.9;   N = 8  3: 27.1 / 30.4
-//   block 8192: N = 3  1/4: 7.9 / 9.3   1: 10.0 / 9.3;   N = 4  1: 10.2 / 10.5;   N = 8  2: 20.7 / 19.3   3: 28.6 / 30.0
-// 8-bit codes cost the second launch twice the bytes; with six sources and more in blocks of up to 2048 it shows: INT8, block 2048, N = 6  1.5: 13.7 /
-// 15.7   2: 18.5 / 16.3;   N = 7  1.5: 15.0 / 17.7   1.75: 17.6 / 18.2   2: 19.2 / 18.6;   N = 8  1.75: 19.5 / 20.3   2: 22.0 / 20.5.  Groups of 1024 elements and more cost the
-// steps another 1.1 us, the one launch 0.2 to 0.7: four sources of short blocks never take them then.
-// Some limits lie above the crossing (four sources, INT4, five and eight in short blocks, FP8's three): they date from the one launch with one source after
-// the other, and below them the steps are still faster than that was.
-// Partials whose metadata are not a multiple of 16 bytes (few tokens, coarse groups) follow the same limits (one group per token, INT4 8 x 1 x 8192
-// 11.4 us for 20.3 in one launch), but for blocks of 1024 and FP8's three sources in blocks of 8192 (11.5 / 12.1).
+// Whether the steps are the faster form of the rotated all-reduce.  All partials' quantizations spread over the chip, and one more
+// launch, take less time than one launch of few workgroups.  That one goes through the sources in turn or, up to a volume by block and
+// sources (allreduce_rot_at_once), has them side by side and then mostly wins.  Hence two limits, in units of 2^16 elements: up to the
+// first the steps are taken in any case, up to the second where the one launch would take the sources in turn.  us by elements (2^20),
+// group 128, steps / one launch, there at once and past the ';' in turn:
+//   block 1024: INT4 N = 4  1/8: 5.5 / 3.6;   N = 8  1/2: 8.4 / 6.5   1: 10.3 / 8.9 ;  1.125: 11.7 / 16.9   1.75: 17.0 / 18.0   2: 18.9 / 18.3
+//   block 2048: INT4 N = 4  1/4: 5.8 / 4.6;   N = 8  1/8: 6.1 / 6.5   1/4: 7.7 / 6.5   1: 10.4 / 9.5 ;  1.125: 11.8 / 18.7   2: 18.2 / 20.2   2.125: 20.7 / 20.5
+//     INT8 N = 8  1: 12.1 / 9.2 ;  1.5: 17.3 / 18.9   1.625: 19.3 / 19.0;   FP8 N = 5  1/8: 5.5 / 6.4   1/2: 7.2 / 6.5   1.5: 12.6 / 11.4 ;  1.625: 13.5 / 15.2   2.125: 15.9 / 16.2
+//   block 4096: INT4 N = 3  1/4: 6.0 / 6.7   3/8: 7.2 / 6.7;   N = 4  1/4: 6.1 / 7.0   5/16: 7.7 / 7.0;   N = 8  1/8: 6.5 / 9.5   1/2: 8.6 / 9.8   1: 10.4 / 10.0 ;
+//     1.125: 12.5 / 19.5   2.25: 22.1 / 22.3   2.5: 23.1 / 22.4;   INT8 N = 8  1.75: 18.4 / 19.4   1.875: 20.1 / 19.8;   FP8 N = 8  2.75: 27.6 / 27.9   3: 28.5 / 28.2
+//   block 8192: INT4 N = 4  1/2: 8.8 / 9.4   1: 9.3 / 9.6;   N = 5, never at once  1: 10.4 / 13.5   2: 13.2 / 14.4;   N = 8  1: 12.1 / 15.0   1.5: 15.2 / 16.0
+//     1.75: 17.2 / 16.7 ;  2.25: 23.4 / 23.8;   FP8 N = 8  1.5: 17.1 / 17.5   2: 22.1 / 18.8 ;  2.125: 26.0 / 27.6   2.75: 29.0 / 28.6
+// 8-bit codes cost the second launch twice the bytes, and groups of 1024 and more the steps another 1.1 us, the one launch 0.2 to 0.7
+// (blocks of 2048, up to six sources in blocks of 4096 and four in 8192: the first limit is 2^17 elements lower).  Partials whose metadata are not a
+// multiple of 16 bytes (few tokens, coarse groups) follow the same limits (one group per token, INT4 8 x 1 x 8192 11.4 us for 20.3 in one launch), but
+// for blocks of 1024 and FP8's three sources in blocks of 8192 (11.5 / 12.1).
 bool rot_steps_apply(int codec, int bits_rs, int n_src, int64_t n_elems, int64_t hidden, int group)
 {
-    //                                           n_src 3  4   5   6   7   8
-    static constexpr unsigned char kLimit[2][3][6] = {{{0, 4, 8, 32, 36, 32}, {0, 8, 28, 35, 36, 32}, {0, 8, 16, 30, 28, 28}},
-                                                      {{7, 0, 32, 34, 32, 32}, {8, 8, 40, 40, 44, 48}, {6, 18, 24, 40, 44, 48}}};
-    static constexpr unsigned char kLimit8[3] = {24, 24, 28};           // INT8, six sources and more in short blocks
+    // INT4, INT8, FP8; blocks of 1024 to 8192; 3 to 8 sources
+    static constexpr unsigned char kAtOnce[3][4][6] = {
+        {{0, 0, 0, 0, 0, 0}, {0, 0, 2, 2, 2, 2}, {4, 4, 8, 8, 10, 10}, {0, 10, 0, 32, 30, 25}},
+        {{0, 0, 0, 0, 0, 0}, {0, 0, 2, 2, 2, 2}, {2, 4, 8, 8, 10, 10}, {0, 8, 0, 30, 26, 22}},
+        {{0, 0, 0, 0, 0, 0}, {0, 0, 3, 3, 3, 3}, {6, 6, 9, 8, 10, 10}, {8, 16, 0, 32, 28, 24}}};
+    static constexpr unsigned char kInTurn[3][4][6] = {
+        {{0, 0, 30, 31, 30, 30}, {0, 0, 37, 37, 36, 33}, {0, 0, 38, 39, 36, 37}, {0, 0, 32, 0, 36, 38}},
+        {{0, 0, 0, 20, 22, 21}, {0, 0, 0, 29, 26, 25}, {0, 0, 31, 32, 30, 29}, {0, 0, 30, 0, 0, 0}},
+        {{0, 0, 33, 31, 28, 29}, {0, 0, 34, 32, 33, 32}, {0, 44, 40, 40, 41, 45}, {0, 0, 38, 38, 38, 42}}};
     static_assert(FC_MAX_SRC == 8, "one column per fan-in");
     if (n_src < 3) return false;
     const bool fp8 = codec == fc::CODEC_FP8;
-    const int block = fc::rotation_block(hidden);
-    const int row = block == 8192 ? 2 : block == 4096 ? 1 : 0;
-    if (row == 0 && (n_src == 6 || n_src == 7) && n_elems <= (int64_t)1 << 20) return false;
-    int limit = kLimit[fp8][row][n_src - 3];
-    if (!fp8 && bits_rs == 8 && row == 0 && n_src >= 6) limit = kLimit8[n_src - 6];
-    if (!fp8 && n_src == 4 && group >= 1024 && row < 2) limit = 4 * row;
+    const int kind = fp8 ? 2 : bits_rs == 8;
+    const int log_b = fc::log2_int(fc::rotation_block((int)hidden));
     const bool padded = n_elems / group % 4 != 0;
-    if (padded && (block == 1024 || (fp8 && n_src == 3 && block == 8192))) return false;
-    return n_elems <= (int64_t)limit << 16;
+    if (padded && (log_b == 10 || (fp8 && n_src == 3 && log_b == 13))) return false;
+    int at_once = kAtOnce[kind][log_b - 10][n_src - 3];
+    if (group >= 1024 && n_src <= 30 - 2 * log_b) at_once -= 2;
+    if (n_elems <= (int64_t)at_once * (1 << 16)) return true;
+    return n_elems <= (int64_t)kInTurn[kind][log_b - 10][n_src - 3] << 16 && !fc::allreduce_rot_at_once(log_b, n_src, n_elems);
 }
 
 }  // namespace

@@ -115,6 +115,8 @@ hipError_t launch_reduce_rot_fine(int codec, int bits_rs, int bits_ag, const voi
 
 // the whole rotated all-reduce, where that is the fastest form of it
 bool allreduce_rot_fine_applies(int log_b, int n_src, int64_t n_elems);
+// whether the one-launch form has all sources of a block, or a round of them, in one workgroup
+bool allreduce_rot_at_once(int log_b, int n_src, int64_t n_elems);
 hipError_t launch_allreduce_rot_fine(int codec, int bits_rs, int bits_ag, const void *x_f16, int n_src, int64_t n_elems, int log_b, int group,
                                      void *y_f16, hipStream_t stream);
 

@@ -418,4 +418,9 @@ hipError_t launch_allreduce_rot(int codec, int bits_rs, int bits_ag, const void 
     }
 }
 
+bool allreduce_rot_at_once(int log_b, int n_src, int64_t n_elems)
+{
+    return allreduce_rot_fine_applies(log_b, n_src, n_elems) || rot_spread_applies(log_b, n_src, n_elems);
+}
+
 }  // namespace fc

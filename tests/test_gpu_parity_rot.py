@@ -211,18 +211,26 @@ def test_wide_blocks_both_layouts_every_group(fc, quantizer, bits, hidden):
                 assert torch.equal(got.view(torch.uint8), w[pick].view(torch.uint8)), "h=%d g=%d rows=%d" % (hidden, group, rows)
 
 
+# by block: for INT4 and FP8 the two limits of the steps of three to eight sources
+STEPS = {1024: (((0, 0, 0, 0, 0, 0), (0, 0, 30, 31, 30, 30)), ((0, 0, 0, 0, 0, 0), (0, 0, 33, 31, 28, 29))),
+         2048: (((0, 0, 2, 2, 2, 2), (0, 0, 37, 37, 36, 33)), ((0, 0, 3, 3, 3, 3), (0, 0, 34, 32, 33, 32))),
+         4096: (((4, 4, 8, 8, 10, 10), (0, 0, 38, 39, 36, 37)), ((6, 6, 9, 8, 10, 10), (0, 44, 40, 40, 41, 45))),
+         8192: (((0, 10, 0, 32, 30, 25), (0, 0, 32, 0, 36, 38)), ((8, 16, 0, 32, 28, 24), (0, 0, 38, 38, 38, 42)))}
+
+
 @pytest.mark.parametrize("quantizer,n_src", [(oracle.ASYM, 3), (oracle.ASYM, 4), (oracle.ASYM, 6), (oracle.ASYM, 8), (oracle.SYM, 5), (oracle.SYM, 7),
                                              (oracle.SYM, 8), (oracle.FP8, 2), (oracle.FP8, 3), (oracle.FP8, 4), (oracle.FP8, 6), (oracle.FP8, 7),
                                              (oracle.FP8, 8)])
-@pytest.mark.parametrize("hidden", [1024, 3072, 4096, 8192])
+@pytest.mark.parametrize("hidden", [1024, 2048, 3072, 4096, 8192])
 def test_allreduce_sim_rot_on_both_sides_of_the_limit(fc, quantizer, n_src, hidden):
-    # up to a limit (2^16 elements; by block, code and number of sources) the steps run, through the workspace, above it one kernel, which
-    # leaves the workspace alone; so does the kernel for six and seven sources of up to 2^20 elements in short blocks, and slabs of a
-    # length that needs padding in blocks of 1024.  A few rows (compared with the oracle) are repeated up to the limit.
+    # the steps, which write the workspace, and the one launch, which leaves it alone: up to a first limit (2^16 elements; by block, code
+    # and number of sources) the steps run, up to a second where the one launch takes the sources in turn.  Slabs of a length that
+    # needs padding never run in steps in blocks of 1024.  A few rows (compared with the oracle) are repeated up to the limits.
     bits = 8 if quantizer == oracle.FP8 else 4
-    column = n_src - 3
-    limit = {1024: ((0, 4, 8, 32, 36, 32), (7, 0, 32, 34, 32, 32)), 4096: ((0, 8, 28, 35, 36, 32), (8, 8, 40, 40, 44, 48)),
-             8192: ((0, 8, 16, 30, 28, 28), (6, 18, 24, 40, 44, 48))}[hidden & -hidden][bits == 8][column] << 16 if column >= 0 else 0
+    block = hidden & -hidden
+    first, second = (STEPS[block][quantizer == oracle.FP8][i][n_src - 3] if n_src >= 3 else 0 for i in range(2))
+    turns = {1024: (2 << 20, 2 << 20, 3 << 19), 2048: (2 << 20, 2 << 20, 3 << 19), 4096: (2 << 20, 2 << 20), 8192: (2 << 20, 2 << 20, 0, 2 << 20, 2 << 20, 2 << 20)}[block]
+    turns = turns[n_src - 3] if n_src - 3 < len(turns) else 1 << 20      # past so many elements the one launch takes the sources in turn
     x = synth_inputs.make_partials(n_src, 5, hidden, seed=hidden + n_src)
     x[:, 1] = 0
     x[0, 2] = np.float16(6e-8) * (np.arange(hidden) % 5)
@@ -230,9 +238,9 @@ def test_allreduce_sim_rot_on_both_sides_of_the_limit(fc, quantizer, n_src, hidd
     few = dev(x.view(np.uint16)).view(torch.float16)
     for group in (128, 1024):
         want = dev(oracle.allreduce_sim_rot(x, group, bits, bits, quantizer).view(np.int16))
-        if bits == 4 and n_src == 4 and group == 1024 and hidden < 8192:
-            limit = {1024: 0, 4096: 4 << 16}[hidden & -hidden]
-        for rows in sorted({1, 2, 5, 12, (1 << 20) // hidden, (1 << 20) // hidden + 1, limit // hidden, limit // hidden + 1, limit // hidden + 4} - {0}):
+        few_limit = max(first - 2 * (group == 1024 and n_src <= {1024: 8, 2048: 8, 4096: 6, 8192: 4}[block]), 0) << 16
+        edges = {limit // hidden + more for limit in (few_limit, turns, second << 16) for more in (0, 1, 4)}
+        for rows in sorted({1, 2, 5, 12} | edges - {0}):
             pick = torch.arange(rows, device="cuda") % 5
             need = fc.allreduce_sim_workspace_bytes(n_src, rows, hidden, group, bits, bits)
             space = torch.full((need + 64,), 0xA5, dtype=torch.uint8, device="cuda")
@@ -240,8 +248,9 @@ def test_allreduce_sim_rot_on_both_sides_of_the_limit(fc, quantizer, n_src, hidd
             fc.allreduce_sim_rot(few[:, pick], group, bits, bits, quantizer, out=y.t, workspace=space[:need])
             torch.cuda.synchronize(); y.check()
             assert (space[need:] == 0xA5).all(), "written past the workspace"
-            steps = rows * hidden <= limit and (rows * hidden // group % 4 == 0 or hidden & -hidden != 1024)
-            steps = steps and (n_src not in (6, 7) or hidden & -hidden != 1024 or rows * hidden > 1 << 20)
+            elems = rows * hidden
+            steps = elems <= few_limit or turns < elems <= second << 16
+            steps = steps and (elems // group % 4 == 0 or block != 1024)
             assert bool((space[:need] != 0xA5).any()) == steps, "N=%d h=%d g=%d rows=%d: form" % (n_src, hidden, group, rows)
             assert torch.equal(y.t.view(torch.int16), want[pick]), "N=%d h=%d g=%d rows=%d" % (n_src, hidden, group, rows)
 
@@ -506,8 +515,9 @@ def test_rot_codecs_on_both_sides_of_the_volume_limits(fc, quantizer, bits, hidd
 def test_allreduce_sim_rot_in_steps(fc, quantizer, bits_rs, bits_ag, hidden, group):
     # few rows of many sources: the sum, its codes and the inverse transform in one launch.  Zero-points far outside the codes, sums that
     # cancel to zero, partials of -0 and subnormals, groups of less and more than a wavefront
-    for n_src in (5, 7, 8):
-        rows = 12 if n_src != 7 or hidden & -hidden > 2048 else (1 << 20) // hidden + 1      # seven sources of short blocks: past 2^20 elements
+    short = hidden & -hidden <= 2048
+    for n_src in (6 if short else 5, 7, 8):
+        rows = (1 << 20) // hidden + 1 if short else 12
         x = synth_inputs.make_partials(n_src, 12, hidden, seed=hidden + group + n_src, outlier_frac=0.01)
         x[:, 1] = 0
         x[:, 2] = np.float16(-0.0)

@@ -135,18 +135,29 @@ def test_rotated_codec_forms():
 
 
 def test_rotated_all_reduce_in_steps():
-    # the last volume in steps and the next one, by code, block and number of sources; and where the steps begin
-    cases = [("asym", 4, 2048, 6, 32), ("asym", 4, 1024, 7, 36), ("sym", 4, 2048, 8, 32), ("asym", 8, 2048, 6, 24), ("sym", 8, 1024, 7, 24), ("asym", 8, 2048, 8, 28),
-             ("fp8", 8, 1024, 6, 34), ("fp8", 8, 2048, 7, 32), ("fp8", 8, 1024, 8, 32), ("fp8", 8, 4096, 4, 8), ("fp8", 8, 8192, 4, 18), ("asym", 8, 4096, 6, 35),
-             ("asym", 4, 4096, 7, 36), ("sym", 8, 8192, 6, 30), ("asym", 4, 8192, 7, 28), ("asym", 4, 2048, 5, 8)]
-    calls = [allreduce_rot(q, n, elems, h, 128, b, b) for q, b, h, n, limit in cases for elems in (limit << 16, (limit << 16) + h)]
-    got = kernels(*calls)
+    # the last volume in steps and the next one, by code, block and number of sources: where the one launch has all sources at once, and
+    # where it would take them in turn
+    at_once = [("asym", 4, 2048, 8, 2), ("fp8", 8, 2048, 5, 3), ("asym", 4, 4096, 3, 4), ("sym", 4, 4096, 4, 4), ("asym", 4, 4096, 5, 8), ("sym", 8, 4096, 6, 8), ("asym", 4, 4096, 7, 10),
+               ("fp8", 8, 4096, 3, 6), ("fp8", 8, 4096, 5, 9), ("asym", 4, 8192, 4, 10), ("asym", 8, 8192, 4, 8), ("fp8", 8, 8192, 3, 8), ("fp8", 8, 8192, 4, 16), ("asym", 4, 8192, 6, 32),
+               ("sym", 8, 8192, 6, 30), ("asym", 4, 8192, 7, 30), ("asym", 4, 8192, 8, 25), ("sym", 8, 8192, 8, 22), ("fp8", 8, 8192, 7, 28)]
+    in_turn = [("asym", 4, 1024, 5, 30), ("asym", 4, 1024, 8, 30), ("sym", 8, 1024, 6, 20), ("asym", 8, 1024, 7, 22), ("fp8", 8, 1024, 5, 33), ("asym", 4, 2048, 6, 37), ("asym", 8, 2048, 8, 25),
+               ("fp8", 8, 2048, 7, 33), ("asym", 4, 4096, 5, 38), ("sym", 8, 4096, 6, 32), ("fp8", 8, 4096, 4, 44), ("fp8", 8, 4096, 8, 45), ("asym", 4, 8192, 5, 32), ("sym", 8, 8192, 5, 30),
+               ("asym", 4, 8192, 8, 38), ("fp8", 8, 8192, 6, 38)]
+    cases = at_once + in_turn
+    got = kernels(*[allreduce_rot(q, n, elems, h, 128, b, b) for q, b, h, n, limit in cases for elems in (limit << 16, (limit << 16) + h)])
     for case, a, b in zip(cases, got[::2], got[1::2]):
         assert len(a) == 2 and a[1].startswith("k_reduce_rot_fine") and len(b) == 1, "%s: %s, then %s" % (case, a, b)
-    got = kernels(*[allreduce_rot(q, n, elems, 2048, 128, 8, 8) for q in ("asym", "fp8") for n in (6, 7) for elems in (M, M + 2048)])
-    assert [len(k) for k in got] == [1, 2] * 4
-    got = kernels(*[allreduce_rot("fp8", 4, elems, 2048, 128) for elems in (M // 16, M)])
-    assert [len(k) for k in got] == [1, 1]
+    # all sources at once up to a volume, and in steps past it
+    cases = [("asym", 4, 2048, 6, M), ("sym", 8, 2048, 7, M), ("fp8", 8, 1024, 8, M), ("asym", 4, 2048, 5, 3 * M // 2), ("fp8", 8, 1024, 5, 3 * M // 2), ("asym", 4, 4096, 5, M), ("fp8", 8, 4096, 8, M),
+             ("fp8", 8, 4096, 4, 2 * M), ("asym", 4, 8192, 8, 2 * M), ("fp8", 8, 8192, 7, 2 * M)]
+    got = kernels(*[allreduce_rot(q, n, elems, h, 128, b, b) for q, b, h, n, limit in cases for elems in (limit, limit + h)])
+    for case, a, b in zip(cases, got[::2], got[1::2]):
+        assert len(a) == 1 and len(b) == 2, "%s: %s, then %s" % (case, a, b)
+    # coarse groups: the first limit lies 2^17 elements lower up to eight, six, four sources; padded slabs of blocks of 1024 never
+    cases = [("asym", 4, 4096, 7, 10), ("asym", 4, 4096, 6, 6), ("fp8", 8, 2048, 8, 1), ("asym", 4, 8192, 4, 8), ("asym", 4, 8192, 8, 25)]
+    got = kernels(*[allreduce_rot(q, n, elems, h, 1024, b, b) for q, b, h, n, limit in cases for elems in (limit << 16, (limit << 16) + h)])
+    assert [len(k) for k in got] == [2, 1] * len(cases), got
+    assert [len(k) for k in kernels(allreduce_rot("asym", 8, M + 3 * 1024, 1024, 1024, 4, 4), allreduce_rot("asym", 8, M + 4 * 1024, 1024, 1024, 4, 4))] == [1, 2]
 
 
 def test_rotated_all_reduce_in_one_launch():
@@ -154,7 +165,7 @@ def test_rotated_all_reduce_in_one_launch():
     fine, spread, plain = "k_allreduce_rot_fine<", "k_allreduce_rot_spread<", "k_allreduce_rot<"
     cases = [("asym", 1, 1024, 5 * M // 4, fine, plain), ("sym", 1, 2048, 3 * M // 2, fine, plain), ("fp8", 1, 4096, 2 * M, fine, plain), ("asym", 2, 1024, 3 * M // 4, fine, spread),
              ("asym", 2, 2048, M, fine, spread), ("fp8", 2, 4096, M, fine, spread), ("sym", 3, 1024, M // 2, fine, spread), ("asym", 2, 8192, 2 * M, spread, plain), ("sym", 3, 4096, 2 * M, spread, plain),
-             ("asym", 5, 8192, M + 8192, plain, plain), ("sym", 6, 8192, 2 * M, spread, plain)]
+             ("asym", 5, 8192, 31 * M // 16, plain, plain), ("sym", 6, 8192, 2 * M, spread, plain)]
     got = kernels(*[allreduce_rot(q, n, elems, h, 128, 8, 8) for q, n, h, limit, _, _ in cases for elems in (limit, limit + h)])
     for case, a, b in zip(cases, got[::2], got[1::2]):
         assert len(a) == len(b) == 1 and a[0].startswith(case[4]) and b[0].startswith(case[5]), "%s: %s, then %s" % (case, a, b)
