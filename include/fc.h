@@ -291,7 +291,7 @@ FC_API int fc_dequantize_rot(const void *codes, const float *scales, const float
                              void *y_f16, void *hip_stream);
 
 /* Algorithm 1 with the rotation around it: fc_quantize_rot x n_src -> fc_dequant_reduce_requant* -> fc_dequantize_rot
-   through the workspace for launch-bound volumes of several sources, one kernel, bit-identical, for all others;
+   through the workspace where that is faster (some volumes of three and more sources), else one kernel, bit-identical;
    workspace as for fc_allreduce_sim. */
 FC_API int fc_allreduce_sim_rot(const void *x_f16, int n_src, int64_t tokens, int64_t hidden,
                                 int group, int bits_rs, int bits_ag, int quantizer, void *y_f16,

@@ -240,7 +240,7 @@ __device__ __forceinline__ u32x4 fine_back(float (&v)[8], float s, const RotLane
 
 // The last two steps of the rotated all-reduce on one block: dequantize the sources' codes, sum, quantize, dequantize, rotate back.
 // One launch and one way through memory less than fc_dequant_reduce_requant and fc_dequantize_rot, term by term the same: all-reduces in steps
-// 1.1 to 1.9 us shorter at every volume they are taken for (figures at rot_steps_apply).  All loads of all sources come first.  qmax and
+// became 1.1 to 1.9 us shorter by it.  All loads of all sources come first.  qmax and
 // rcp: highest code of the second quantization and its reciprocal
 template <int BITS, int CODEC, int LB>
 __global__ __launch_bounds__(64 * fine_waves(LB)) void k_reduce_rot_fine(

@@ -42,8 +42,8 @@
 // What bounds it: HBM, and the number of reads that wait in the memory system at once.  A bare stream of this shape (four
 // 128 MB partials read, one written, no arithmetic) takes 99 to 103 us with 48 to 64 KB in flight per compute unit and
 // 107 to 111 with 128 KB and more: past what the latency needs, requests only queue and get in each other's way.  Hence one
-// partial at a time instead of all N, and, for volumes that take several rounds of wavefronts, a limit on the workgroups
-// per compute unit (sim_workgroups_per_unit).  4 partials of 8192 x 8192, INT4, group 128, us: all partials at once 109.7,
+// partial at a time instead of all N (two where few wavefronts leave the latency uncovered, launch_sim_src), and, for volumes that take
+// several rounds of wavefronts, a limit on the workgroups per compute unit (sim_workgroups_per_unit).  4 partials of 8192 x 8192, INT4, group 128, us: all partials at once 109.7,
 // one at a time 108.5, with 10 / 9 / 8 / 7 / 6 workgroups per compute unit 108.3 / 106.5 / 103.0 / 102.0 / 107.7.
 #include "fc_device.hpp"
 #include "fc_launch.hpp"
